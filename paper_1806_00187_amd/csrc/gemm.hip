@@ -139,9 +139,13 @@ struct TransOp {
   int wave;
   __device__ __forceinline__ static int sw(int k) { return (k & 3) << (R == 64 ? 1 : 2); }
   __device__ __forceinline__ static const half_t* origin(const half_t* p, int ld, int r0, int k0) { return p + (size_t)k0 * ld + r0; }
-  // k rows >= K lie beyond the extent and arrive as zeros
+  // k rows >= K lie beyond the extent and arrive as zeros.  (Masked, not selected: with a branch here the compiler's
+  // count of the requests in flight came out low in the loops of every k-major product, and it put a wait for all but
+  // six -- in the two-stage rings for all -- of them in front of the first fragment read after each k-tile's requests:
+  // 128 x 64 tiles, 384 x 1024 x 1024: 13.1 -> 11.5 us.)
   __device__ __forceinline__ static uint32_t extent(int rows_in, int ld, int kleft) {
-    return kleft > 0 ? ((uint32_t)(min(kleft, BK) - 1) * ld + (uint32_t)rows_in) * 2u : 0u;
+    const uint32_t e = ((uint32_t)(min(kleft, BK) - 1) * ld + (uint32_t)rows_in) * 2u;
+    return e & (uint32_t)~((kleft - 1) >> 31);
   }
   __device__ __forceinline__ void init(int ld, int rows_in, int tid) {
     wave = tid >> 6;
@@ -219,141 +223,32 @@ __device__ __forceinline__ void wave_sync() {
 constexpr int wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
 constexpr int wait_vm_lds(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0070; }
 
-// NS stages of BK k each form a ring: while k-tile t is multiplied, tiles t+1 .. t+NS-1 are in LDS
-// or on their way.
-template <int BM, int BN, bool AT, bool BT, int BK, int NS, int NW>
-__global__ void __launch_bounds__(64 * NW) gemm_kernel(const GemmArgs g) {
-  using T = Tile<BM, BN, AT, BT, BK, NW>;
-  using OpA = typename T::OpA;
-  using OpB = typename T::OpB;
-  static_assert(NS >= 2 && NS <= 4, "two to four stages");
-  // separate arrays, so that the compiler can tell that fragment reads of one stage do not depend
-  // on the loads in flight into the others
-  __shared__ __align__(1024) unsigned char stage0[T::STAGE];
-  __shared__ __align__(1024) unsigned char stage1[T::STAGE];
-  __shared__ __align__(1024) unsigned char stage2[NS > 2 ? T::STAGE : 16];
-  __shared__ __align__(1024) unsigned char stage3[NS > 3 ? T::STAGE : 16];
-  constexpr int WGN = NW / 2;  // the waves form a 2 x WGN grid over the block tile
-  constexpr int WM = BM / 2, WN = BN / WGN, TM = WM / 32, TN = WN / 32, KS = BK / 16;
+// Work-group -> (k-split, tile).  Consecutive work-group ids go round-robin over the XCDs; undo
+// that so each XCD (own L2) gets a contiguous run of tiles of as few k-splits as possible: the
+// tiles of one split read the same k-range of A and B and share those panels in L2.
+// Then grouped order: group_m tile rows are swept column by column, so the work-groups an XCD runs at a
+// time form a patch of tiles and each A / B panel they stream is shared by several of them in L2.
+__device__ __forceinline__ int xcd_order(int lin, int total, int xcds) {
+  const int xcd = lin % xcds, idx = lin / xcds, base = total / xcds, rem = total % xcds;
+  return xcd * base + (xcd < rem ? xcd : rem) + idx;
+}
+__device__ __forceinline__ void place(const GemmArgs& g, int lin, int total, int& split, int& tm, int& tn) {
+  const int nt = g.tiles_m * g.tiles_n, at = xcd_order(lin, total, g.xcds);
+  split = at / nt;
+  const int pid = at - split * nt, per_group = g.group_m * g.tiles_n;
+  const int first = (pid / per_group) * g.group_m;
+  const int rows = min(g.tiles_m - first, g.group_m);
+  tm = first + (pid % per_group) % rows;
+  tn = (pid % per_group) / rows;
+}
+
+// Epilogue of one tile: accumulators -> per-wave LDS staging (fp32) -> row-wise 16-byte stores.
+template <int BM, int BN, int NW, int STAGE>
+__device__ __forceinline__ void store_tile(const GemmArgs& g, const floatx16 (&acc)[BM / 64][BN / (32 * (NW / 2))], int m0, int n0, int split,
+                                           unsigned char* stage0, unsigned char* stage1) {
+  constexpr int WGN = NW / 2, WM = BM / 2, WN = BN / WGN, TM = WM / 32;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
-
-  // Work-group -> (k-split, tile).  Consecutive work-group ids go round-robin over the XCDs; undo
-  // that so each XCD (own L2) gets a contiguous run of tiles of as few k-splits as possible: the
-  // tiles of one split read the same k-range of A and B and share those panels in L2.
-  int pid, split;
-  {
-    const int nt = g.tiles_m * g.tiles_n, total = nt * (int)gridDim.y;
-    const int lin = (int)blockIdx.x + (int)blockIdx.y * nt, xcd = lin % g.xcds, idx = lin / g.xcds;
-    const int base = total / g.xcds, rem = total % g.xcds;
-    const int at = xcd * base + (xcd < rem ? xcd : rem) + idx;
-    split = at / nt;
-    pid = at - split * nt;
-  }
-  // Grouped order: group_m tile rows are swept column by column, so the work-groups an XCD runs at a
-  // time form a patch of tiles and each A / B panel they stream is shared by several of them in L2.
-  int tm, tn;
-  {
-    const int per_group = g.group_m * g.tiles_n;
-    const int first = (pid / per_group) * g.group_m;
-    const int rows = min(g.tiles_m - first, g.group_m);
-    tm = first + (pid % per_group) % rows;
-    tn = (pid % per_group) / rows;
-  }
-  const int m0 = tm * BM, n0 = tn * BN;
-
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  OpA opa;
-  OpB opb;
-  const int rows_a = min(g.M - m0, BM), rows_b = min(g.N - n0, BN);
-  opa.init(g.lda, rows_a, tid);
-  opb.init(g.ldb, rows_b, tid);
-  const typename OpA::Frag fa = OpA::frag_init(wm * WM, lane);
-  const typename OpB::Frag fb = OpB::frag_init(wn * WN, lane);
-
-  const int k_base = g.partial ? split * g.k_chunk : 0;
-  const int k_end = g.partial ? min(g.K, k_base + g.k_chunk) : g.K;
-  auto request = [&](unsigned char* stage, int k0) {  // asynchronous: tile k0 streams into `stage`
-    const int kleft = k_end - k0;
-    opa.load(make_rsrc(OpA::origin(g.A, g.lda, m0, k0), OpA::extent(rows_a, g.lda, kleft)), stage, kleft);
-    opb.load(make_rsrc(OpB::origin(g.B, g.ldb, n0, k0), OpB::extent(rows_b, g.ldb, kleft)), stage + OpA::BYTES, kleft);
-    __builtin_amdgcn_sched_barrier(0);  // keep the requests ahead of the products they overlap with
-  };
-  constexpr int kPerTile = OpA::NV + OpB::NV;  // vector-memory instructions of one request, per wave
-  half8_t af[2][TM], bf[2][TN];  // fragments of two consecutive k-steps
-  auto fetch = [&](const unsigned char* stage, int s, int set) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i) af[set][i] = OpA::frag(stage, fa, i, s);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) bf[set][j] = OpB::frag(stage + OpA::BYTES, fb, j, s);
-  };
-  auto multiply = [&](int set) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)  // B first: the result tile is transposed, lane = row of C, registers = columns
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[set][j], af[set][i], acc[i][j], 0, 0, 0);
-  };
-  auto interleave = [&]() { Interleave<0, TM * TN, OpA::READS * TM + OpB::READS * TN>::run(); };
-  // One k-tile.  On entry the fragments of k-step 0 of `cur` are in registers and the next NS-1
-  // tiles have been requested.  Before the last k-step every wave holds its last fragments of `cur`
-  // in registers and has seen its own part of `nxt` land (the requests of the NS-2 tiles behind it
-  // may still be in flight); the barrier then publishes `nxt` and frees `cur`, which is refilled at
-  // once with the tile NS ahead.
-  auto k_tile = [&](unsigned char* cur, const unsigned char* nxt, int k_refill) {
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      if (s == KS - 1) {
-        __builtin_amdgcn_s_waitcnt(wait_vm_lds((NS - 2) * kPerTile));
-        __builtin_amdgcn_s_barrier();
-        request(cur, k_refill);
-      }
-      fetch(s == KS - 1 ? nxt : cur, (s + 1) % KS, (s + 1) & 1);
-      multiply(s & 1);
-      interleave();
-    }
-  };
-
-  // A k-tile past the end reads zeros (it lies outside the extent of its buffer descriptor) and
-  // multiplying it changes nothing, so the loop always runs whole rings and carries no edge conditions.
-  const int nk = (k_end - k_base + BK - 1) / BK;
-  request(stage0, k_base);
-  request(stage1, k_base + BK);
-  if constexpr (NS >= 3) request(stage2, k_base + 2 * BK);
-  if constexpr (NS == 4) request(stage3, k_base + 3 * BK);
-  __builtin_amdgcn_s_waitcnt(wait_vm((NS - 1) * kPerTile));
-  __builtin_amdgcn_s_barrier();
-  fetch(stage0, 0, 0);
-  if constexpr (NS == 2) {
-    for (int kt = 0; kt < nk; kt += 2) {
-      k_tile(stage0, stage1, k_base + (kt + 2) * BK);
-      k_tile(stage1, stage0, k_base + (kt + 3) * BK);
-    }
-  } else if constexpr (NS == 3) {
-    for (int kt = 0; kt < nk; kt += 3) {
-      k_tile(stage0, stage1, k_base + (kt + 3) * BK);
-      k_tile(stage1, stage2, k_base + (kt + 4) * BK);
-      k_tile(stage2, stage0, k_base + (kt + 5) * BK);
-    }
-  } else {
-    for (int kt = 0; kt < nk; kt += 4) {
-      k_tile(stage0, stage1, k_base + (kt + 4) * BK);
-      k_tile(stage1, stage2, k_base + (kt + 5) * BK);
-      k_tile(stage2, stage3, k_base + (kt + 6) * BK);
-      k_tile(stage3, stage0, k_base + (kt + 7) * BK);
-    }
-  }
-  __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));  // the last refills (all zeros) must land before the stages are reused
-  __syncthreads();
-
-  // ---- epilogue: accumulators -> per-wave LDS staging (fp32) -> row-wise 16-byte stores -------
   // The products were formed as (B tile) x (A tile)^T, so in the MFMA result layout lane l holds row
   // l%32 of the C tile and, in registers 4q..4q+3, the four consecutive columns 8q + 4(l/32) .. +3:
   // one 16-byte LDS write per register quad.  A staged row is SW floats; its 16-byte chunks are
@@ -362,8 +257,8 @@ __global__ void __launch_bounds__(64 * NW) gemm_kernel(const GemmArgs g) {
   // (half of the waves stage in stage0, the other half in stage1, so that a staged row can be 64 columns
   //  = whole 128-byte lines of fp16 output even when a stage is small)
   constexpr int HW = NW / 2;
-  constexpr int SW = (HW * 32 * WN * 4 <= T::STAGE) ? WN : (HW * 32 * 64 * 4 <= T::STAGE && WN % 64 == 0) ? 64 : 32;
-  static_assert(HW * 32 * SW * 4 <= T::STAGE, "epilogue staging does not fit");
+  constexpr int SW = (HW * 32 * WN * 4 <= STAGE) ? WN : (HW * 32 * 64 * 4 <= STAGE && WN % 64 == 0) ? 64 : 32;
+  static_assert(HW * 32 * SW * 4 <= STAGE, "epilogue staging does not fit");
   float* stg = reinterpret_cast<float*>(wave < HW ? stage0 : stage1) + (wave % HW) * (32 * SW);
   constexpr int CH = SW / 8;    // 8-column chunks per staged row
   constexpr int QC = SW / 4;    // 16-byte chunks per staged row (8, 16 or 32)
@@ -466,6 +361,234 @@ __global__ void __launch_bounds__(64 * NW) gemm_kernel(const GemmArgs g) {
   }
 }
 
+// NS stages of BK k each form a ring: while k-tile t is multiplied, tiles t+1 .. t+NS-1 are in LDS
+// or on their way.
+template <int BM, int BN, bool AT, bool BT, int BK, int NS, int NW>
+__global__ void __launch_bounds__(64 * NW) gemm_kernel(const GemmArgs g) {
+  using T = Tile<BM, BN, AT, BT, BK, NW>;
+  using OpA = typename T::OpA;
+  using OpB = typename T::OpB;
+  static_assert(NS >= 2 && NS <= 4, "two to four stages");
+  // separate arrays, so that the compiler can tell that fragment reads of one stage do not depend
+  // on the loads in flight into the others
+  __shared__ __align__(1024) unsigned char stage0[T::STAGE];
+  __shared__ __align__(1024) unsigned char stage1[T::STAGE];
+  __shared__ __align__(1024) unsigned char stage2[NS > 2 ? T::STAGE : 16];
+  __shared__ __align__(1024) unsigned char stage3[NS > 3 ? T::STAGE : 16];
+  constexpr int WGN = NW / 2;  // the waves form a 2 x WGN grid over the block tile
+  constexpr int WM = BM / 2, WN = BN / WGN, TM = WM / 32, TN = WN / 32, KS = BK / 16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave / WGN, wn = wave % WGN;
+
+  int split, tm, tn;
+  place(g, (int)blockIdx.x + (int)blockIdx.y * (g.tiles_m * g.tiles_n), g.tiles_m * g.tiles_n * (int)gridDim.y, split, tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+
+  floatx16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  OpA opa;
+  OpB opb;
+  const int rows_a = min(g.M - m0, BM), rows_b = min(g.N - n0, BN);
+  opa.init(g.lda, rows_a, tid);
+  opb.init(g.ldb, rows_b, tid);
+  const typename OpA::Frag fa = OpA::frag_init(wm * WM, lane);
+  const typename OpB::Frag fb = OpB::frag_init(wn * WN, lane);
+
+  const int k_base = g.partial ? split * g.k_chunk : 0;
+  const int k_end = g.partial ? min(g.K, k_base + g.k_chunk) : g.K;
+  auto request = [&](unsigned char* stage, int k0) {  // asynchronous: tile k0 streams into `stage`
+    const int kleft = k_end - k0;
+    opa.load(make_rsrc(OpA::origin(g.A, g.lda, m0, k0), OpA::extent(rows_a, g.lda, kleft)), stage, kleft);
+    opb.load(make_rsrc(OpB::origin(g.B, g.ldb, n0, k0), OpB::extent(rows_b, g.ldb, kleft)), stage + OpA::BYTES, kleft);
+    __builtin_amdgcn_sched_barrier(0);  // keep the requests ahead of the products they overlap with
+  };
+  constexpr int kPerTile = OpA::NV + OpB::NV;  // vector-memory instructions of one request, per wave
+  half8_t af[2][TM], bf[2][TN];  // fragments of two consecutive k-steps
+  auto fetch = [&](const unsigned char* stage, int s, int set) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) af[set][i] = OpA::frag(stage, fa, i, s);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) bf[set][j] = OpB::frag(stage + OpA::BYTES, fb, j, s);
+  };
+  auto multiply = [&](int set) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)  // B first: the result tile is transposed, lane = row of C, registers = columns
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[set][j], af[set][i], acc[i][j], 0, 0, 0);
+  };
+  auto interleave = [&]() { Interleave<0, TM * TN, OpA::READS * TM + OpB::READS * TN>::run(); };
+  // One k-tile.  On entry the fragments of k-step 0 of `cur` are in registers and the next NS-1
+  // tiles have been requested.  Before the last k-step every wave holds its last fragments of `cur`
+  // in registers and has seen its own part of `nxt` land (the requests of the NS-2 tiles behind it
+  // may still be in flight); the barrier then publishes `nxt` and frees `cur`, which is refilled at
+  // once with the tile NS ahead.
+  auto k_tile = [&](unsigned char* cur, const unsigned char* nxt, int k_refill) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      if (s == KS - 1) {
+        __builtin_amdgcn_s_waitcnt(wait_vm_lds((NS - 2) * kPerTile));
+        __builtin_amdgcn_s_barrier();
+        request(cur, k_refill);
+      }
+      fetch(s == KS - 1 ? nxt : cur, (s + 1) % KS, (s + 1) & 1);
+      multiply(s & 1);
+      interleave();
+    }
+  };
+
+  // A k-tile past the end reads zeros (it lies outside the extent of its buffer descriptor) and
+  // multiplying it changes nothing, so the loop always runs whole rings and carries no edge conditions.
+  const int nk = (k_end - k_base + BK - 1) / BK;
+  request(stage0, k_base);
+  request(stage1, k_base + BK);
+  if constexpr (NS >= 3) request(stage2, k_base + 2 * BK);
+  if constexpr (NS == 4) request(stage3, k_base + 3 * BK);
+  __builtin_amdgcn_s_waitcnt(wait_vm((NS - 1) * kPerTile));
+  __builtin_amdgcn_s_barrier();
+  fetch(stage0, 0, 0);
+  if constexpr (NS == 2) {
+    for (int kt = 0; kt < nk; kt += 2) {
+      k_tile(stage0, stage1, k_base + (kt + 2) * BK);
+      k_tile(stage1, stage0, k_base + (kt + 3) * BK);
+    }
+  } else if constexpr (NS == 3) {
+    for (int kt = 0; kt < nk; kt += 3) {
+      k_tile(stage0, stage1, k_base + (kt + 3) * BK);
+      k_tile(stage1, stage2, k_base + (kt + 4) * BK);
+      k_tile(stage2, stage0, k_base + (kt + 5) * BK);
+    }
+  } else {
+    for (int kt = 0; kt < nk; kt += 4) {
+      k_tile(stage0, stage1, k_base + (kt + 4) * BK);
+      k_tile(stage1, stage2, k_base + (kt + 5) * BK);
+      k_tile(stage2, stage3, k_base + (kt + 6) * BK);
+      k_tile(stage3, stage0, k_base + (kt + 7) * BK);
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));  // the last refills (all zeros) must land before the stages are reused
+  __syncthreads();
+
+  store_tile<BM, BN, NW, T::STAGE>(g, acc, m0, n0, split, stage0, stage1);
+}
+
+// ------------------------------------------------------------------------------------------------
+// Tiles of up to 128 x 128: products with too few rows for 256 x 256 tiles.  Such a product is one round of
+// work-groups that each walk 8 to 64 k-tiles, so its time is a fixed part (launch, first operands, epilogue: 4-5 us)
+// plus k-tiles x the time of one.  What bounds a k-tile here is its trip through the vector-memory unit (64 bytes per
+// clock and compute unit; 43 reached), as long as two things do not come first: the latency of the requests, so the
+// ring has four stages and three k-tiles are in flight; and the latency of the fragment reads (a k-step of a small
+// tile has 1 to 4 matrix instructions, less than the ~120 clocks of an LDS read), so a whole k-tile of fragments is
+// held in registers and the next k-tile's are read behind all matrix instructions of the current one.  Per 64-deep k-tile on
+// one work-group per compute unit: 64 x 64 0.42 -> 0.165 us, 128 x 64 0.48 -> 0.24, 128 x 128 0.55 -> 0.33 (0.45 with every
+// compute unit busy) against the same tiles with two stages and one k-step of fragments ahead; 3000 x 1024 x 4096: 42.4 -> 33.2 us,
+// 384 x 1024 x 1024: 11.5 -> 6.5 us, 384 x 1024 x 4096: 34.4 -> 14.4 us.
+// The two-stage ring remains for 128 x 128 tiles on four wavefronts, two work-groups per compute unit, where there are
+// enough tiles for that: the second work-group's k-tiles then cover the first one's prologue and epilogue.
+// ------------------------------------------------------------------------------------------------
+template <int BM, int BN, bool AT, bool BT, int NS, int NW>
+__global__ void __launch_bounds__(64 * NW) gemm_small_kernel(const GemmArgs g) {
+  constexpr int BK = 64;
+  using T = Tile<BM, BN, AT, BT, BK, NW>;
+  using OpA = typename T::OpA;
+  using OpB = typename T::OpB;
+  static_assert(NS == 2 || NS == 4, "two or four stages (the fragments' register set alternates with the stage)");
+  __shared__ __align__(1024) unsigned char stage0[T::STAGE];  // separate arrays (see gemm_kernel)
+  __shared__ __align__(1024) unsigned char stage1[T::STAGE];
+  __shared__ __align__(1024) unsigned char stage2[NS > 2 ? T::STAGE : 16];
+  __shared__ __align__(1024) unsigned char stage3[NS > 2 ? T::STAGE : 16];
+  constexpr int WGN = NW / 2, WM = BM / 2, WN = BN / WGN, TM = WM / 32, TN = WN / 32, KS = BK / 16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave / WGN, wn = wave % WGN;
+  int split, tm, tn;
+  place(g, (int)blockIdx.x + (int)blockIdx.y * (g.tiles_m * g.tiles_n), g.tiles_m * g.tiles_n * (int)gridDim.y, split, tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+
+  floatx16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  OpA opa;
+  OpB opb;
+  const int rows_a = min(g.M - m0, BM), rows_b = min(g.N - n0, BN);
+  opa.init(g.lda, rows_a, tid);
+  opb.init(g.ldb, rows_b, tid);
+  const typename OpA::Frag fa = OpA::frag_init(wm * WM, lane);
+  const typename OpB::Frag fb = OpB::frag_init(wn * WN, lane);
+  const int k_base = g.partial ? split * g.k_chunk : 0;
+  const int k_end = g.partial ? min(g.K, k_base + g.k_chunk) : g.K;
+  auto request = [&](unsigned char* stage, int k0) {
+    const int kleft = k_end - k0;
+    opa.load(make_rsrc(OpA::origin(g.A, g.lda, m0, k0), OpA::extent(rows_a, g.lda, kleft)), stage, kleft);
+    opb.load(make_rsrc(OpB::origin(g.B, g.ldb, n0, k0), OpB::extent(rows_b, g.ldb, kleft)), stage + OpA::BYTES, kleft);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  constexpr int kPerTile = OpA::NV + OpB::NV;
+  half8_t af[2][KS][TM], bf[2][KS][TN];  // the fragments of two consecutive k-tiles
+  auto fetch = [&](const unsigned char* stage, int set) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) af[set][s][i] = OpA::frag(stage, fa, i, s);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) bf[set][s][j] = OpB::frag(stage + OpA::BYTES, fb, j, s);
+    }
+  };
+  // One k-tile, whose fragments are in register set `set`.  The barrier publishes `nxt` (every wave has seen its own
+  // part of it land) and frees `cur` (every wave's fragments of it have arrived), which is refilled at once.
+  auto k_tile = [&](unsigned char* cur, const unsigned char* nxt, int k_refill, int set) {
+    __builtin_amdgcn_s_waitcnt(wait_vm_lds((NS - 2) * kPerTile));
+    __builtin_amdgcn_s_barrier();
+    request(cur, k_refill);
+    fetch(nxt, set ^ 1);
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)  // (B first, k-steps in increasing order: the same sums as gemm_kernel's)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[set][s][j], af[set][s][i], acc[i][j], 0, 0, 0);
+    Interleave<0, KS * TM * TN, KS * (OpA::READS * TM + OpB::READS * TN)>::run();
+  };
+
+  const int nk = (k_end - k_base + BK - 1) / BK;  // (k-tiles past the end multiply zeros: whole rings, no edge conditions)
+  request(stage0, k_base);
+  request(stage1, k_base + BK);
+  if constexpr (NS == 4) {
+    request(stage2, k_base + 2 * BK);
+    request(stage3, k_base + 3 * BK);
+  }
+  __builtin_amdgcn_s_waitcnt(wait_vm((NS - 1) * kPerTile));
+  __builtin_amdgcn_s_barrier();
+  fetch(stage0, 0);
+  if constexpr (NS == 2) {
+    for (int kt = 0; kt < nk; kt += 2) {
+      k_tile(stage0, stage1, k_base + (kt + 2) * BK, 0);
+      k_tile(stage1, stage0, k_base + (kt + 3) * BK, 1);
+    }
+  } else {
+    for (int kt = 0; kt < nk; kt += 4) {
+      k_tile(stage0, stage1, k_base + (kt + 4) * BK, 0);
+      k_tile(stage1, stage2, k_base + (kt + 5) * BK, 1);
+      k_tile(stage2, stage3, k_base + (kt + 6) * BK, 0);
+      k_tile(stage3, stage0, k_base + (kt + 7) * BK, 1);
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));  // the last refills (all zeros) must land before the stages are reused
+  __syncthreads();
+  store_tile<BM, BN, NW, T::STAGE>(g, acc, m0, n0, split, stage0, stage1);
+}
+
 // ------------------------------------------------------------------------------------------------
 // Persistent form of the 256 x 256, 8-wave kernel for products whose epilogue loads nothing per
 // element (bias, ReLU and the output scale only): one work-group per compute unit walks its tiles
@@ -532,8 +655,7 @@ __global__ void __launch_bounds__(512) gemm_persistent_kernel(const GemmArgs g) 
   const int nt = g.tiles_m * g.tiles_n;
 
   auto decode = [&](int lin, int& m0, int& n0) {
-    const int xcd = lin % g.xcds, idx = lin / g.xcds, base = nt / g.xcds, rem = nt % g.xcds;
-    const int pid = xcd * base + (xcd < rem ? xcd : rem) + idx;
+    const int pid = xcd_order(lin, nt, g.xcds);
     const int per_group = g.group_m * g.tiles_n;
     const int first = (pid / per_group) * g.group_m;
     const int rows = min(g.tiles_m - first, g.group_m);
@@ -740,10 +862,10 @@ __global__ void __launch_bounds__(kThreads) splitk_reduce_kernel(const float* __
 }
 
 template <int BM, int BN, bool AT, bool BT, int BK, int NS, int NW>
-int launch_variant(const GemmArgs& g, int splits, hipStream_t stream) {
-  hipLaunchKernelGGL((gemm_kernel<BM, BN, AT, BT, BK, NS, NW>), dim3(g.tiles_m * g.tiles_n, splits), dim3(64 * NW), 0, stream, g);
-  NMT_LAUNCH_CHECK();
-  return NMT_OK;
+void launch_variant(const GemmArgs& g, int splits, hipStream_t stream) {
+  const dim3 grid(g.tiles_m * g.tiles_n, splits), block(64 * NW);
+  if constexpr (BM == 256) hipLaunchKernelGGL((gemm_kernel<BM, BN, AT, BT, BK, NS, NW>), grid, block, 0, stream, g);
+  else hipLaunchKernelGGL((gemm_small_kernel<BM, BN, AT, BT, NS, NW>), grid, block, 0, stream, g);
 }
 
 template <int BM, int BN, int BK, int NS, int NW = 4>
@@ -765,28 +887,62 @@ int launch_tile(const GemmArgs& a, bool a_t, bool b_t, int splits, hipStream_t s
     g.partial = nullptr;
     splits = 1;
   }
-  int rc;
-  if (!a_t && !b_t) rc = launch_variant<BM, BN, false, false, BK, NS, NW>(g, splits, stream);
-  else if (!a_t && b_t) rc = launch_variant<BM, BN, false, true, BK, NS, NW>(g, splits, stream);
-  else if (a_t && b_t) rc = launch_variant<BM, BN, true, true, BK, NS, NW>(g, splits, stream);
-  else rc = launch_variant<BM, BN, true, false, BK, NS, NW>(g, splits, stream);
-  if (rc != NMT_OK || splits == 1) return rc;
+  if (!a_t && !b_t) launch_variant<BM, BN, false, false, BK, NS, NW>(g, splits, stream);
+  else if (!a_t && b_t) launch_variant<BM, BN, false, true, BK, NS, NW>(g, splits, stream);
+  else if (a_t && b_t) launch_variant<BM, BN, true, true, BK, NS, NW>(g, splits, stream);
+  else launch_variant<BM, BN, true, false, BK, NS, NW>(g, splits, stream);
+  NMT_LAUNCH_CHECK();
+  if (splits == 1) return NMT_OK;
   const int64_t n = (int64_t)g.M * (g.N / 8);
   hipLaunchKernelGGL(splitk_reduce_kernel, dim3(ceil_div(n, kThreads)), dim3(kThreads), 0, stream, g.partial, splits, g.M, g.N, g.C, g.ldc, g.ep.out_scale);
   NMT_LAUNCH_CHECK();
   return NMT_OK;
 }
 
-// Estimated efficiency of a tile shape on a (M, N) problem: useful fraction of the padded tiles,
-// times how well the tile count fills whole rounds of the compute units, times a per-shape factor (small
-// tiles re-read LDS more often per MFMA).
-double tile_score(int M, int N, int bm, int bn, int per_cu, double shape_eff) {
-  const double tiles = (double)ceil_div(M, bm) * ceil_div(N, bn);
-  const double useful = ((double)M * N) / (tiles * bm * bn);
-  const double slots = (double)device_info().cus * per_cu;
-  const double rounds = (tiles + slots - 1) / slots;
-  const double fill = tiles / (double)((int64_t)rounds * slots);
-  return useful * fill * shape_eff;
+// The tile shapes below 256 x 256 and what a product takes with each, in us, from timings of 32 shapes (384 to 6000 rows,
+// 512 to 4096 columns, k 512 to 4096; forward form, operands rotating through 300 MB): `fixed` (launch, first operands,
+// epilogue) + k-tiles of 64 x the time of one, which depends on how many tiles share a compute unit (at most `per_cu`, by
+// LDS), + `again` for every further round of work-groups.  The model is within 20 % of
+// the measured times and the shape it picks within 13 % of the fastest of the six on all of them.
+enum SmallTile { kTile64, kTile128x64, kTile64x128, kTile128, kTile128x64Many, kTile128Many, kSmallTiles };
+struct TileCost {
+  int bm, bn, per_cu;
+  double fixed, again;
+  double k_tile[3];  // one k-tile while 1, 2, 3 tiles share the compute unit
+};
+constexpr TileCost kTileCost[kSmallTiles] = {
+    {64, 64, 2, 3.6, 1.0, {0.165, 0.40, 0.}},         // four stages
+    {128, 64, 1, 4.1, 3.8, {0.25, 0., 0.}},           // four stages
+    {64, 128, 1, 4.1, 3.8, {0.25, 0., 0.}},           // four stages
+    {128, 128, 1, 4.4, 5.8, {0.44, 0., 0.}},          // four stages, eight wavefronts
+    {128, 64, 3, 4.3, 1.8, {0.48, 0.66, 0.94}},       // two stages
+    {128, 128, 2, 5.7, 3.5, {0.55, 0.88, 0.}},        // two stages
+};
+double tile_us(const TileCost& c, int64_t tiles, int K) {
+  const int cus = device_info().cus, nk = ceil_div(K, 64);
+  const int64_t slots = (int64_t)cus * c.per_cu, rounds = tiles / slots, rest = tiles - rounds * slots;
+  double us = c.fixed + rounds * nk * c.k_tile[c.per_cu - 1];
+  if (rest) us += nk * c.k_tile[ceil_div(rest, cus) - 1];
+  return us + c.again * (double)(rounds + (rest ? 1 : 0) - 1);
+}
+SmallTile choose_small_tile(int M, int N, int K) {
+  int best = kTile64;
+  double best_us = 0.;
+  for (int t = 0; t < kSmallTiles; ++t) {
+    const double us = tile_us(kTileCost[t], (int64_t)ceil_div(M, kTileCost[t].bm) * ceil_div(N, kTileCost[t].bn), K);
+    if (t == 0 || us < best_us) { best = t; best_us = us; }
+  }
+  return (SmallTile)best;
+}
+int launch_small_tile(SmallTile t, const GemmArgs& g, bool a_t, bool b_t, int splits, hipStream_t stream) {
+  switch (t) {
+    case kTile64: return launch_tile<64, 64, 64, 4>(g, a_t, b_t, splits, stream);
+    case kTile128x64: return launch_tile<128, 64, 64, 4>(g, a_t, b_t, splits, stream);
+    case kTile64x128: return launch_tile<64, 128, 64, 4>(g, a_t, b_t, splits, stream);
+    case kTile128: return launch_tile<128, 128, 64, 4, 8>(g, a_t, b_t, splits, stream);
+    case kTile128x64Many: return launch_tile<128, 64, 64, 2>(g, a_t, b_t, splits, stream);
+    default: return launch_tile<128, 128, 64, 2>(g, a_t, b_t, splits, stream);
+  }
 }
 
 }  // namespace
@@ -839,10 +995,10 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
   if (const int forced = tuning().gemm_tile; forced && splits <= 1) {
     switch (forced) {
       case 1: return (!a_t && !b_t) ? launch_tile<256, 256, 64, 2, 8>(g, a_t, b_t, 1, stream) : launch_tile<256, 256, 32, 4, 8>(g, a_t, b_t, 1, stream);
-      case 2: return launch_tile<128, 128, 64, 2>(g, a_t, b_t, 1, stream);
-      case 3: return launch_tile<128, 64, 64, 2>(g, a_t, b_t, 1, stream);
-      case 4: return launch_tile<64, 128, 64, 2>(g, a_t, b_t, 1, stream);
-      default: return launch_tile<64, 64, 64, 2>(g, a_t, b_t, 1, stream);
+      case 2: return launch_small_tile(kTile128, g, a_t, b_t, 1, stream);
+      case 3: return launch_small_tile(kTile128x64, g, a_t, b_t, 1, stream);
+      case 4: return launch_small_tile(kTile64x128, g, a_t, b_t, 1, stream);
+      default: return launch_small_tile(kTile64, g, a_t, b_t, 1, stream);
     }
   }
   // (a caller that keeps several passes in flight says so: each product then counts on its share of the chip)
@@ -891,15 +1047,8 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
     if (!a_t && !b_t) return launch_tile<256, 256, 64, 2, 8>(g, a_t, b_t, splits, stream);
     return launch_tile<256, 256, 32, 4, 8>(g, a_t, b_t, splits, stream);
   }
-  if (splits > 1) return launch_tile<128, 128, 64, 2>(g, a_t, b_t, splits, stream);
-  const double s128 = tile_score(M, N, 128, 128, 2, 1.0);
-  const double s12864 = tile_score(M, N, 128, 64, 2, 0.85);
-  const double s64128 = tile_score(M, N, 64, 128, 2, 0.85);
-  const double s64 = tile_score(M, N, 64, 64, 4, 0.65);
-  if (s128 >= s12864 && s128 >= s64128 && s128 >= s64) return launch_tile<128, 128, 64, 2>(g, a_t, b_t, 1, stream);
-  if (s12864 >= s64128 && s12864 >= s64) return launch_tile<128, 64, 64, 2>(g, a_t, b_t, 1, stream);
-  if (s64128 >= s64) return launch_tile<64, 128, 64, 2>(g, a_t, b_t, 1, stream);
-  return launch_tile<64, 64, 64, 2>(g, a_t, b_t, 1, stream);
+  if (splits > 1) return launch_small_tile(kTile128Many, g, a_t, b_t, splits, stream);
+  return launch_small_tile(choose_small_tile(M, N, K), g, a_t, b_t, 1, stream);
 }
 
 // Optional timing of every product with HIP events on the stream it is launched on (the benchmark's roofline leg):

@@ -56,6 +56,23 @@ def test_gemm_matches_oracle(M, N, K, mode):
     assert_close16(host(dC), Am @ Bm.T, f"gemm {mode} {M}x{N}x{K}")
 
 
+# one product per small tile shape and ring the library chooses by itself (64 x 64 twice), each ragged in rows, columns and k:
+# k-tiles that are not a multiple of the ring, a last k-tile of 8, 40 or 8 of 64, fewer k-tiles than the ring has stages
+@pytest.mark.parametrize("M,N,K", [(65, 72, 40), (129, 136, 200), (1003, 1032, 1032), (960, 2056, 1032), (2101, 1032, 1032), (3003, 1544, 328),
+                                   (6005, 1032, 264)])
+@pytest.mark.parametrize("mode", ["fwd", "dgrad", "wgrad"])
+def test_gemm_small_tiles_match_oracle(M, N, K, mode):
+    rng = np.random.default_rng(M + N * 3 + K)
+    a_t, b_t = {"fwd": (0, 0), "dgrad": (0, 1), "wgrad": (1, 1)}[mode]
+    if a_t:
+        M = (M + 7) // 8 * 8
+    Am, Bm = f16(rng.normal(size=(M, K))), f16(rng.normal(size=(N, K)) / math.sqrt(K))
+    bias = f16(rng.normal(size=N))
+    dC = torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV)
+    A.nmt_op_gemm(dev16(Am.T if a_t else Am), a_t, M if a_t else K, dev16(Bm.T if b_t else Bm), b_t, N if b_t else K, dC, N, M, N, K, bias=dev16(bias))
+    assert_close16(host(dC), Am @ Bm.T + bias, f"small tiles {mode} {M}x{N}x{K}")
+
+
 @pytest.mark.parametrize("M,N,K", [(128, 128, 16), (200, 136, 72), (37, 1000, 66), (515, 264, 203), (1031, 2052, 1024)])
 @pytest.mark.parametrize("mode", ["fwd", "dgrad", "wgrad"])
 def test_fp32_comparison_gemm_matches_oracle(M, N, K, mode):
