@@ -113,20 +113,19 @@ __device__ __forceinline__ uint32_t drop_row_pos(const DropDev& dd, uint32_t row
   return dd.rowkey ? (dd.rowkey[row].y & 0xFFFFu) : row % (uint32_t)dd.n_pos;
 }
 
-// Keep decisions of the 8 columns [8*grp, 8*grp+8) of row `row`: bit i set = column 8*grp+i kept.
-__device__ __forceinline__ uint32_t drop_keep8(const DropDev& dd, uint32_t row, uint32_t grp) {
-  uint32_t uid, pos, c3 = dd.c3;
+// What row `row` puts into the counters, for kernels that fetch it ahead of the draws.
+struct DropRow { uint32_t uid, pos, c3; };
+__device__ __forceinline__ DropRow drop_row(const DropDev& dd, uint32_t row) {
   if (dd.rowkey) {
     const uint2 rk = dd.rowkey[row];
-    uid = rk.x;
-    pos = rk.y & 0xFFFFu;
-    c3 = (c3 & 0xFFFFFF00u) | (rk.y >> 16);
-  } else {
-    const uint32_t sent = row / (uint32_t)dd.n_pos;
-    pos = row - sent * (uint32_t)dd.n_pos;
-    uid = dd.uid ? dd.uid[sent] : sent;
+    return DropRow{rk.x, rk.y & 0xFFFFu, (dd.c3 & 0xFFFFFF00u) | (rk.y >> 16)};
   }
-  const uint4 w = philox4x32_10(make_uint4(grp, uid, dd.site_hi | pos, c3), dd.k0, dd.k1);
+  const uint32_t sent = row / (uint32_t)dd.n_pos;
+  return DropRow{dd.uid ? dd.uid[sent] : sent, row - sent * (uint32_t)dd.n_pos, dd.c3};
+}
+// Keep decisions of the 8 columns [8*grp, 8*grp+8) of a row: bit i set = column 8*grp+i kept.
+__device__ __forceinline__ uint32_t drop_keep8(const DropDev& dd, const DropRow& r, uint32_t grp) {
+  const uint4 w = philox4x32_10(make_uint4(grp, r.uid, dd.site_hi | r.pos, r.c3), dd.k0, dd.k1);
   const uint32_t words[4] = {w.x, w.y, w.z, w.w};
   uint32_t bits = 0;
 #pragma unroll
@@ -136,6 +135,7 @@ __device__ __forceinline__ uint32_t drop_keep8(const DropDev& dd, uint32_t row, 
   }
   return bits;
 }
+__device__ __forceinline__ uint32_t drop_keep8(const DropDev& dd, uint32_t row, uint32_t grp) { return drop_keep8(dd, drop_row(dd, row), grp); }
 
 // ---- small vector helpers ---------------------------------------------------------------------
 __device__ __forceinline__ half8_t ld_half8(const half_t* p) { return *reinterpret_cast<const half8_t*>(p); }
@@ -218,9 +218,10 @@ int64_t colsum_scratch_floats(int cols);
 int launch_colsum(const half_t* src, int ld, half_t* dst, float* partial, int rows, int cols, hipStream_t stream, float scale = 1.f);
 int launch_colsum_static(const half_t* src, int ld, half_t* dst, int rows, int cols, hipStream_t stream);  // partial sums in a fixed device array
 int64_t embed_bwd_scratch_ints(int vocab, int rows_total, int d);
-int launch_embed_bwd(const int32_t* ids_a, const half_t* dx_a, int rows_a, const DropDev& drop_a,
-                     const int32_t* ids_b, const half_t* dx_b, int rows_b, const DropDev& drop_b, half_t* gE, int d,
-                     int vocab, int32_t* scratch, hipStream_t stream, float scale = 1.f);
+// Embedding gradient in two parts that share `scratch`: the order of the positions by id (ids alone), then the sums.
+int launch_embed_sort(const int32_t* ids_a, int rows_a, const int32_t* ids_b, int rows_b, int d, int vocab, int32_t* scratch, hipStream_t stream);
+int launch_embed_sum(const half_t* dx_a, int rows_a, const DropDev& drop_a, const half_t* dx_b, int rows_b, const DropDev& drop_b, half_t* gE,
+                     int d, const int32_t* scratch, hipStream_t stream, float scale = 1.f);
 int launch_accumulate(const half_t* g16, float* acc, int64_t n, int first, hipStream_t stream, float mult = 1.f);
 // in_place: acc *= inv_scale in the same pass; otherwise acc is only read
 int launch_check_overflow(float* acc, int64_t n, float inv_scale, int32_t* flag, hipStream_t stream, bool in_place = true);

@@ -141,7 +141,7 @@ struct nmt_ctx {
   Plan plan;
   // second stream for the weight-gradient kernels of the backward pass (created on first use)
   hipStream_t side = nullptr;
-  hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_done[2] = {nullptr, nullptr};
+  hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_embed = nullptr, ev_done[2] = {nullptr, nullptr};
 };
 
 namespace {
@@ -347,6 +347,7 @@ extern "C" void nmt_destroy(nmt_ctx* ctx) {
   if (ctx->ev_fork) {
     (void)hipEventDestroy(ctx->ev_fork);
     (void)hipEventDestroy(ctx->ev_join);
+    (void)hipEventDestroy(ctx->ev_embed);
     (void)hipEventDestroy(ctx->ev_done[0]);
     (void)hipEventDestroy(ctx->ev_done[1]);
   }
@@ -653,6 +654,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   if (!c->ev_fork) {
     NMT_HIP_CHECK(hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
     NMT_HIP_CHECK(hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming));
+    NMT_HIP_CHECK(hipEventCreateWithFlags(&c->ev_embed, hipEventDisableTiming));
     NMT_HIP_CHECK(hipEventCreateWithFlags(&c->ev_done[0], hipEventDisableTiming));
     NMT_HIP_CHECK(hipEventCreateWithFlags(&c->ev_done[1], hipEventDisableTiming));
   }
@@ -747,8 +749,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   };
 
   // ---- output projection: logits = x E^T; the workspace holds d logits ----
-  // (the tied matrix's gradient is finished by the embedding kernels at the very end, so its
-  //  weight-gradient product stays on the main stream)
+  // (the tied matrix's gradient is finished by the embedding kernels at the very end)
   const half_t* dlogits = r.ws<half_t>(p.logits);
   const half_t* x_dec = r.ws<half_t>(p.dec[k.dec_layers - 1].x3);
   half_t* dx = r.ws<half_t>(p.dx_dec);
@@ -756,6 +757,9 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   GemmEpilogue vocab_ep;
   vocab_ep.out_scale = c->gscale;
   NMT_TRY(launch_gemm(dlogits, true, V, x_dec, true, d, w.g(c->embed), d, V, d, Nt, vocab_ep, sd));
+  // (the order of the positions by id, which the embedding gradient at the end needs, depends on the ids alone)
+  NMT_TRY(launch_embed_sort(c->src, Ns, c->tgt_in, Nt, d, V, r.ws<int32_t>(p.embscratch), sd));
+  if (two_streams) NMT_HIP_CHECK(hipEventRecord(c->ev_embed, sd));
   NMT_TRY(launch_gemm(dlogits, false, V, r.w(c->embed), true, d, dx, d, Nt, d, V, GemmEpilogue{}, st));
 
   // ---- decoder, top to bottom ----
@@ -808,11 +812,13 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
                      r.ws<float>(W.st1), P.attn, P.ln1, layer_site(l, kKindSelfRes), c->src, 0));
   }
 
-  // ---- join, then the embeddings: both id streams add into the row gradients of the shared matrix ----
+  // ---- the embeddings: both id streams add into the row gradients of the shared matrix (beside the second stream's last
+  //      weight gradients, which touch other tensors), then join ----
+  if (two_streams) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_embed, 0));
+  NMT_TRY(launch_embed_sum(denc, Ns, r.drop(kSiteEmbSrc, false, k.dropout), dx_dec0, Nt, r.drop(kSiteEmbTgt, true, k.dropout), r.g(c->embed), d,
+                           r.ws<int32_t>(p.embscratch), st, c->gscale));
   NMT_HIP_CHECK(hipEventRecord(c->ev_join, sd));
   NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_join, 0));
-  NMT_TRY(launch_embed_bwd(c->src, denc, Ns, r.drop(kSiteEmbSrc, false, k.dropout), c->tgt_in, dx_dec0, Nt, r.drop(kSiteEmbTgt, true, k.dropout),
-                           r.g(c->embed), d, V, r.ws<int32_t>(p.embscratch), st, c->gscale));
   return NMT_OK;
 }
 
@@ -998,9 +1004,10 @@ extern "C" int nmt_op_embed_bwd(const int32_t* d_ids_a, const void* d_dx_a, int3
                                 int32_t d, int32_t vocab, int32_t* d_scratch, void* stream) {
   NMT_TRY(check_drop(drop_a, "nmt_op_embed_bwd"));
   NMT_TRY(check_drop(drop_b, "nmt_op_embed_bwd"));
-  return launch_embed_bwd(d_ids_a, static_cast<const half_t*>(d_dx_a), rows_a, make_drop(drop_a), d_ids_b,
-                          static_cast<const half_t*>(d_dx_b), rows_b, make_drop(drop_b), static_cast<half_t*>(d_gE), d, vocab, d_scratch,
-                          static_cast<hipStream_t>(stream));
+  NMT_REQUIRE((rows_a <= 0 || d_dx_a) && (rows_b <= 0 || d_dx_b) && d_gE, "nmt_op_embed_bwd: null pointer");
+  NMT_TRY(launch_embed_sort(d_ids_a, rows_a, d_ids_b, rows_b, d, vocab, d_scratch, static_cast<hipStream_t>(stream)));
+  return launch_embed_sum(static_cast<const half_t*>(d_dx_a), rows_a, make_drop(drop_a), static_cast<const half_t*>(d_dx_b), rows_b,
+                          make_drop(drop_b), static_cast<half_t*>(d_gE), d, d_scratch, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int nmt_op_accumulate(const void* d_g16, float* d_acc32, int64_t n, int32_t first, void* stream) {

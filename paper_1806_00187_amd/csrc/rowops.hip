@@ -463,68 +463,114 @@ __global__ void __launch_bounds__(1024) loss_reduce_kernel(const float* __restri
 // order.  The sorted list is cut into segments of kEmbSeg entries; one block per segment sums the
 // gradient rows of each run of equal ids.  A run that holds all positions of its id is added to the
 // row of the shared matrix at once; runs of ids that spill over segment borders leave fp32 partial
-// sums, which a second kernel adds up in segment order.  The order of every sum is fixed, so results
-// do not depend on scheduling.
+// sums, which a second kernel adds up in a fixed order.  The order of every sum is fixed, so results
+// do not depend on scheduling.  Where a run begins and ends is read off the sorted ids themselves.
+// The sort needs the ids alone: the backward pass enqueues it beside its first products, and only the
+// two summing kernels are left for the end.
 // ------------------------------------------------------------------------------------------------
-constexpr int kEmbSeg = 64;        // sorted entries per block of the row-summing kernel
+constexpr int kEmbSeg = 16;          // sorted entries per block of the row-summing kernel
 constexpr int kSortPerBlock = 1024;  // entries per block of a radix pass
 
-__global__ void fill_int_kernel(int32_t* p, int n, int32_t v) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
 __device__ __forceinline__ int clamp_id(int id, int vocab) { return id < 0 ? 0 : (id >= vocab ? vocab - 1 : id); }
 __device__ __forceinline__ int id_at(const int32_t* a, int na, const int32_t* b, int i, int vocab) {
   return clamp_id(i < na ? a[i] : b[i - na], vocab);
 }
-// Histogram of the ids.  A frequent id (the end-of-sentence symbol, the most common word) would serialise one global
-// atomic per occurrence; each block therefore counts its contiguous share of the positions in LDS first, two 16-bit
-// counters per word (a block takes at most 65535 positions, so a counter cannot carry into its neighbour), and then
-// adds its non-zero counts to the global ones: one global atomic per (block, id that occurs in it).  Integer sums:
-// the result does not depend on the order.
-constexpr int kHistThreads = 1024;
-constexpr int kHistMaxPerBlock = 32768;
-__global__ void __launch_bounds__(kHistThreads) emb_hist_kernel(const int32_t* a, int na, const int32_t* b, int nb, int vocab, int per_block,
-                                                                int32_t* cnt) {
-  extern __shared__ uint32_t hist[];  // (vocab + 1) / 2 words
-  const int words = (vocab + 1) >> 1;
-  for (int w = threadIdx.x; w < words; w += kHistThreads) hist[w] = 0u;
+// Exclusive scan over the block's 1024 threads; `total` is the sum of all.
+__device__ __forceinline__ int block_scan_1024(int v, int* sh, int& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int s = v;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int u = __shfl_up(s, o, kWave);
+    if (lane >= o) s += u;
+  }
+  if (lane == 63) sh[wave] = s;
   __syncthreads();
-  const int n = na + nb, lo = min(n, (int)blockIdx.x * per_block), hi = min(n, lo + per_block);
-  for (int i = lo + (int)threadIdx.x; i < hi; i += kHistThreads) {
-    const int id = id_at(a, na, b, i, vocab);  // clamped to [0, vocab)
-    atomicAdd(&hist[id >> 1], 1u << (16 * (id & 1)));
+  int before = 0;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const int x = sh[w];
+    before += w < wave ? x : 0;
+    total += x;
   }
   __syncthreads();
-  for (int w = threadIdx.x; w < words; w += kHistThreads) {
-    const uint32_t v = hist[w];
-    if (v & 0xFFFFu) atomicAdd(&cnt[2 * w], (int32_t)(v & 0xFFFFu));
-    if ((v >> 16) && 2 * w + 1 < vocab) atomicAdd(&cnt[2 * w + 1], (int32_t)(v >> 16));
+  return before + s - v;
+}
+// exclusive scan of cnt[0..n) in place, n a multiple of 4; single block of 1024 threads, 4 entries per thread at a time
+__global__ void __launch_bounds__(1024) radix_scan_kernel(int32_t* cnt, int n) {
+  __shared__ int sh[16];
+  int run = 0;
+  for (int base = 0; base < n; base += 4096) {
+    const int i = base + (int)threadIdx.x * 4;
+    int4 c = make_int4(0, 0, 0, 0);
+    if (i < n) c = *reinterpret_cast<const int4*>(cnt + i);
+    int total;
+    const int at = run + block_scan_1024(c.x + c.y + c.z + c.w, sh, total);
+    if (i < n) *reinterpret_cast<int4*>(cnt + i) = make_int4(at, at + c.x, at + c.x + c.y, at + c.x + c.y + c.z);
+    run += total;
   }
 }
-// exclusive scan of cnt[0..V) into start[0..V]; single block of 1024 threads
-// (start may be cnt itself)
-__global__ void __launch_bounds__(1024) emb_scan_kernel(const int32_t* cnt, int32_t* start, int V) {
-  __shared__ int sh[1024];
-  const int per = (V + 1023) / 1024;
-  const int lo = min(V, (int)threadIdx.x * per), hi = min(V, lo + per);
-  int s = 0;
-  for (int i = lo; i < hi; ++i) s += cnt[i];
-  sh[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    const int v = (int)threadIdx.x >= o ? sh[threadIdx.x - o] : 0;
-    __syncthreads();
-    sh[threadIdx.x] += v;
-    __syncthreads();
+
+// Lanes of the wavefront that hold the same 8-bit digit as this one (among those with `valid`).
+__device__ __forceinline__ unsigned long long same_digit(int digit, bool valid) {
+  unsigned long long peers = __ballot(valid);
+#pragma unroll
+  for (int bit = 0; bit < 8; ++bit) {
+    const unsigned long long set = __ballot((digit >> bit) & 1);
+    peers &= ((digit >> bit) & 1) ? set : ~set;
   }
-  int run = sh[threadIdx.x] - s;
-  for (int i = lo; i < hi; ++i) {
-    const int c = cnt[i];
-    start[i] = run;
-    run += c;
+  return peers;
+}
+// The whole sort in one block, for lists that fit its LDS as (id << 16 | position) words: six launches
+// of about 4 us each, whatever their work, become one (5 us at 260 entries, 23 us at 6000).  Each of
+// the sixteen wavefronts owns a contiguous run of the list and its own counters, so it ranks its entries
+// without waiting for the others; counters are scanned digit by digit, wavefront by wavefront, which keeps
+// the sort stable.
+constexpr int kSmallSort = 16384;
+constexpr size_t kSmallSortLds = (size_t)2 * kSmallSort * sizeof(uint32_t) + 16 * 256 * sizeof(int);
+__global__ void __launch_bounds__(1024) emb_sort_small_kernel(const int32_t* a, int na, const int32_t* b, int vocab, int n,
+                                                              int32_t* __restrict__ keys_out, int32_t* __restrict__ vals_out) {
+  extern __shared__ __align__(16) uint32_t sort_lds[];
+  __shared__ int sh[16];
+  uint32_t *from = sort_lds, *to = sort_lds + kSmallSort;
+  int* hist = reinterpret_cast<int*>(sort_lds + 2 * kSmallSort);  // [256 digits][16 wavefronts]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int per = ((n + 16 * kWave - 1) / (16 * kWave)) * kWave, lo = min(n, wave * per), hi = min(n, lo + per);
+  for (int i = threadIdx.x; i < n; i += 1024) from[i] = (uint32_t)id_at(a, na, b, i, vocab) << 16 | (uint32_t)i;
+  for (int pass = 0; pass < 2; ++pass) {
+    const int shift = 16 + 8 * pass;
+    for (int i = threadIdx.x; i < 4096; i += 1024) hist[i] = 0;
+    __syncthreads();
+    for (int i = lo + lane; i < hi; i += kWave) atomicAdd(&hist[((from[i] >> shift) & 255u) * 16 + wave], 1);
+    __syncthreads();
+    int4* h4 = reinterpret_cast<int4*>(hist) + threadIdx.x;
+    const int4 c = *h4;
+    int total;
+    const int at = block_scan_1024(c.x + c.y + c.z + c.w, sh, total);
+    *h4 = make_int4(at, at + c.x, at + c.x + c.y, at + c.x + c.y + c.z);
+    __syncthreads();
+    for (int i0 = lo; i0 < hi; i0 += kWave) {
+      const bool valid = i0 + lane < hi;
+      const uint32_t e = valid ? from[i0 + lane] : 0u;
+      const int digit = (int)((e >> shift) & 255u);
+      const unsigned long long peers = same_digit(digit, valid);
+      if (valid) {
+        const int rank = __popcll(peers & ((1ull << lane) - 1ull));
+        const int first = hist[digit * 16 + wave];
+        to[first + rank] = e;
+        if (rank == 0) hist[digit * 16 + wave] = first + __popcll(peers);  // (every peer has read it: lock-step)
+      }
+    }
+    __syncthreads();
+    uint32_t* t = from;
+    from = to;
+    to = t;
   }
-  if (threadIdx.x == 1023) start[V] = sh[1023];
+  for (int i = threadIdx.x; i < n; i += 1024) {
+    keys_out[i] = (int32_t)(from[i] >> 16);
+    vals_out[i] = (int32_t)(from[i] & 0xFFFFu);
+  }
 }
 
 // One radix pass over (key, value) pairs; pass 0 takes key = id of position i, value = i.
@@ -563,12 +609,7 @@ __global__ void __launch_bounds__(kThreads) radix_scatter_kernel(const int32_t* 
     const int digit = (key >> shift) & 255;
     for (int w = 0; w < kThreads / kWave; ++w) {
       if (wave == w) {
-        unsigned long long peers = __ballot(valid);
-#pragma unroll
-        for (int bit = 0; bit < 8; ++bit) {
-          const unsigned long long set = __ballot((digit >> bit) & 1);
-          peers &= ((digit >> bit) & 1) ? set : ~set;
-        }
+        const unsigned long long peers = same_digit(digit, valid);
         if (valid) {
           const int rank = __popcll(peers & ((1ull << lane) - 1ull));
           const int slot = next[digit] + rank;
@@ -582,27 +623,9 @@ __global__ void __launch_bounds__(kThreads) radix_scatter_kernel(const int32_t* 
   }
 }
 
-// dropout-masked, unscaled gradient chunk (8 columns) of sorted entry `pos`
-__device__ __forceinline__ void emb_row_chunk(int pos, int c, int d, const half_t* __restrict__ dxa, int na, const DropDev& da,
-                                              const half_t* __restrict__ dxb, const DropDev& db, float (&acc)[8]) {
-  const bool in_a = pos < na;
-  const int row = in_a ? pos : pos - na;
-  const DropDev& dd = in_a ? da : db;
-  float x[8];
-  unpack8(ld_half8((in_a ? dxa : dxb) + (size_t)row * d + c * 8), x);
-  uint32_t bits = 0xFFu;
-  float sc = 1.f;
-  if (dd.thr) {
-    bits = drop_keep8(dd, (uint32_t)row, (uint32_t)c);
-    sc = dd.scale;
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) acc[e] += ((bits >> e) & 1u) ? x[e] * sc : 0.f;
-}
-__device__ __forceinline__ void emb_add_to_row(half_t* __restrict__ gE, int v, int c, int d, const float (&tot)[8], float scale) {
-  half_t* dst = gE + (size_t)v * d + c * 8;
+__device__ __forceinline__ void emb_add(half_t* __restrict__ dst, const half8_t row, int d, const float (&tot)[8], float scale) {
   float cur[8];
-  unpack8(ld_half8(dst), cur);
+  unpack8(row, cur);
   const float sq = sqrtf((float)d) * scale;
 #pragma unroll
   for (int e = 0; e < 8; ++e) cur[e] += sq * tot[e];
@@ -612,62 +635,118 @@ __device__ __forceinline__ void emb_add_to_row(half_t* __restrict__ gE, int v, i
 // One block per segment of kEmbSeg sorted entries, one thread per 8 columns.
 // part[(2 * seg + 0) * d ..]: sum of the segment's first run if that run began in an earlier segment;
 // part[(2 * seg + 1) * d ..]: sum of its last run if that run began here and goes on in the next one.
-__global__ void __launch_bounds__(kThreads) emb_segment_kernel(const int32_t* a, const half_t* __restrict__ dxa, int na, DropDev da,
-                                                               const int32_t* b, const half_t* __restrict__ dxb, int nb, DropDev db,
-                                                               half_t* __restrict__ gE, int d, int vocab,
-                                                               const int32_t* __restrict__ start, const int32_t* __restrict__ perm,
+// Bound by latency (a few hundred thousand columns in all): the gradient rows, row keys and table rows of
+// kEmbAhead entries are requested together before any is used, in place of a chain of dependent loads per
+// entry, and a segment is short (94 -> 16 us at 6000 entries x 512 columns, 113 -> 81 us at 107000 x 1024;
+// 64-entry segments took 27 us at 6000).
+constexpr int kEmbAhead = 8;
+static_assert(kEmbSeg % kEmbAhead == 0 && kEmbSeg + 2 <= kWave, "a block's first wavefront stages the segment's ids");
+__global__ void __launch_bounds__(kThreads) emb_segment_kernel(const half_t* __restrict__ dxa, int na, DropDev da,
+                                                               const half_t* __restrict__ dxb, DropDev db, half_t* __restrict__ gE, int n,
+                                                               int d, const int32_t* __restrict__ keys, const int32_t* __restrict__ perm,
                                                                float* __restrict__ part, float scale) {
-  __shared__ int s_pos[kEmbSeg], s_id[kEmbSeg];
-  const int n = na + nb, e0 = blockIdx.x * kEmbSeg, cnt = min(kEmbSeg, n - e0);
-  if ((int)threadIdx.x < cnt) {
-    const int pos = perm[e0 + threadIdx.x];
-    s_pos[threadIdx.x] = pos;
-    s_id[threadIdx.x] = id_at(a, na, b, pos, vocab);
+  __shared__ int s_pos[kEmbSeg], s_key[kEmbSeg + 2];  // s_key: with the entries before and after the segment (-1: none)
+  __shared__ DropRow s_drop[kEmbSeg];
+  const int e0 = blockIdx.x * kEmbSeg, cnt = min(kEmbSeg, n - e0);
+  if (threadIdx.x < kEmbSeg + 2) {
+    const int i = e0 - 1 + (int)threadIdx.x;
+    s_key[threadIdx.x] = i >= 0 && i < n ? keys[i] : -1;
+    if (threadIdx.x < kEmbSeg) {
+      const int pos = i + 1 < n ? perm[i + 1] : 0;
+      s_pos[threadIdx.x] = pos;
+      if (pos < na ? da.thr : db.thr) s_drop[threadIdx.x] = drop_row(pos < na ? da : db, (uint32_t)(pos < na ? pos : pos - na));
+    }
   }
   __syncthreads();
   const int c = threadIdx.x;
   if (c >= (d >> 3)) return;
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   int run_begin = 0;
-  for (int k = 0; k < cnt; ++k) {
-    emb_row_chunk(s_pos[k], c, d, dxa, na, da, dxb, db, acc);
-    const int v = s_id[k];
-    if (k + 1 < cnt && s_id[k + 1] == v) continue;
-    const int g_begin = start[v], g_end = start[v + 1];  // where id v's positions lie in the sorted list
-    if (g_begin == e0 + run_begin && g_end == e0 + k + 1) {
-      emb_add_to_row(gE, v, c, d, acc, scale);
-    } else {
-      float* dst = part + ((size_t)2 * blockIdx.x + (g_begin < e0 ? 0 : 1)) * d + c * 8;
+  for (int k0 = 0; k0 < cnt; k0 += kEmbAhead) {
+    half8_t x[kEmbAhead], row[kEmbAhead];
+    uint32_t bits[kEmbAhead];
+    int pos[kEmbAhead], key[kEmbAhead + 1];  // the same in every lane: kept in scalar registers
 #pragma unroll
-      for (int e = 0; e < 8; ++e) dst[e] = acc[e];
+    for (int u = 0; u <= kEmbAhead; ++u) key[u] = __builtin_amdgcn_readfirstlane(s_key[min(k0 + u, cnt) + 1]);
+#pragma unroll
+    for (int u = 0; u < kEmbAhead; ++u) {
+      pos[u] = __builtin_amdgcn_readfirstlane(s_pos[min(k0 + u, cnt - 1)]);  // (an entry past the end repeats the last one and is not added)
+      x[u] = ld_half8((pos[u] < na ? dxa + (size_t)pos[u] * d : dxb + (size_t)(pos[u] - na) * d) + c * 8);
+      row[u] = zero_half8();
+      if (key[u + 1] != key[u] && key[u] >= 0) row[u] = ld_half8(gE + (size_t)key[u] * d + c * 8);  // the run ends here: its row is needed
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-    run_begin = k + 1;
+    for (int u = 0; u < kEmbAhead; ++u) {
+      const bool in_a = pos[u] < na;
+      bits[u] = (in_a ? da.thr : db.thr) ? drop_keep8(in_a ? da : db, s_drop[min(k0 + u, cnt - 1)], (uint32_t)c) : 0xFFu;
+    }
+#pragma unroll
+    for (int u = 0; u < kEmbAhead; ++u) {
+      const int k = k0 + u;
+      if (k >= cnt) break;
+      const float sc = pos[u] < na ? (da.thr ? da.scale : 1.f) : (db.thr ? db.scale : 1.f);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] += ((bits[u] >> e) & 1u) ? (float)x[u][e] * sc : 0.f;
+      const bool goes_on = key[u + 1] == key[u];
+      if (goes_on && k + 1 < cnt) continue;
+      const bool came_in = run_begin == 0 && __builtin_amdgcn_readfirstlane(s_key[0]) == key[u];
+      if (!came_in && !goes_on) {
+        emb_add(gE + (size_t)key[u] * d + c * 8, row[u], d, acc, scale);
+      } else {
+        float* dst = part + ((size_t)2 * blockIdx.x + (came_in ? 0 : 1)) * d + c * 8;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dst[e] = acc[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+      run_begin = k + 1;
+    }
   }
 }
-// Block s finishes the id whose run began in an earlier segment and ends in segment s.
-__global__ void __launch_bounds__(kThreads) emb_finish_kernel(const int32_t* a, int na, const int32_t* b, int nb, half_t* __restrict__ gE,
-                                                              int d, int vocab, const int32_t* __restrict__ start,
-                                                              const int32_t* __restrict__ perm, const float* __restrict__ part,
-                                                              float scale) {
+// Block s finishes the id whose run began in an earlier segment and ends in segment s: kEmbFinish / (d / 8)
+// groups of threads stride over the run's partial sums and are added up in a fixed order.
+constexpr int kEmbFinish = 1024;
+__global__ void __launch_bounds__(kEmbFinish) emb_finish_kernel(half_t* __restrict__ gE, int n, int d, const int32_t* __restrict__ keys,
+                                                                const float* __restrict__ part, float scale) {
   const int e0 = blockIdx.x * kEmbSeg;
-  const int v = id_at(a, na, b, perm[e0], vocab);
-  const int g_begin = start[v], g_end = start[v + 1];
-  if (g_begin >= e0 || g_end > e0 + kEmbSeg) return;  // no run carried in, or it goes on: a later block finishes it
-  const int c = threadIdx.x;
-  if (c >= (d >> 3)) return;
-  const int first = g_begin / kEmbSeg;
-  float tot[8];
-  const float* p = part + ((size_t)2 * first + 1) * d + c * 8;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) tot[e] = p[e];
-  for (int sg = first + 1; sg <= (int)blockIdx.x; ++sg) {
-    p = part + (size_t)2 * sg * d + c * 8;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) tot[e] += p[e];
+  const int v = keys[e0];
+  if (e0 == 0 || keys[e0 - 1] != v) return;                          // no run carried in
+  if (e0 + kEmbSeg < n && keys[e0 + kEmbSeg] == v) return;           // it goes on: a later block finishes it
+  // the first segment whose first entry is v, by sixty-four probes at a time (every wavefront for itself)
+  int lo = 0, hi = blockIdx.x;  // keys[lo - 1 segments] < v <= keys[hi segments]; hi's first entry is v
+  while (lo < hi) {
+    const int step = (hi - lo + kWave - 1) / kWave, at = min(hi, lo + (int)(threadIdx.x & 63) * step);
+    const int below = __popcll(__ballot(keys[at * kEmbSeg] < v));     // probes are increasing: the first `below` lie before v
+    if (below == 0) { hi = lo; break; }
+    const int last = lo + (below - 1) * step;                         // (a probe clamped to hi is not below v)
+    hi = min(hi, last + step);
+    lo = last + 1;
   }
-  emb_add_to_row(gE, v, c, d, tot, scale);
+  const int first = hi > 0 && keys[hi * kEmbSeg - 1] == v ? hi - 1 : hi;  // where the run began
+  __shared__ __align__(16) float red[kEmbFinish * 8];
+  const int chunks = d >> 3, groups = kEmbFinish / chunks, r = threadIdx.x / chunks, c = threadIdx.x % chunks;
+  const int count = (int)blockIdx.x - first + 1;
+  if (r < groups) {
+    float tot[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int i = r; i < count; i += groups) {
+      const float* p = part + ((size_t)2 * (first + i) + (i == 0 ? 1 : 0)) * d + c * 8;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) tot[e] += p[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[threadIdx.x * 8 + e] = tot[e];
+  }
+  __syncthreads();
+  if (r != 0) return;
+  float tot[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) tot[e] = red[c * 8 + e];
+  for (int g = 1; g < min(groups, count); ++g) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) tot[e] += red[(g * chunks + c) * 8 + e];
+  }
+  half_t* dst = gE + (size_t)v * d + c * 8;
+  emb_add(dst, ld_half8(dst), d, tot, scale);
 }
 
 __global__ void __launch_bounds__(kThreads) dropout_mask_kernel(uint8_t* keep, int rows, int n_cols, DropDev drop) {
@@ -899,10 +978,10 @@ int launch_softmax_xent(half_t* logits, const int32_t* targets, float* row_loss,
 
 namespace {
 struct EmbScratch {
-  int64_t cnt, start, k1, v1, k2, perm, hist, part, total;  // offsets in int32 units
+  int64_t k1, v1, keys, perm, hist, part, total;  // offsets in int32 units
   int nblk, nseg;
 };
-EmbScratch emb_scratch(int vocab, int n, int d) {
+EmbScratch emb_scratch(int n, int d) {
   EmbScratch e;
   e.nblk = ceil_div(n, kSortPerBlock);
   e.nseg = ceil_div(n, kEmbSeg);
@@ -912,71 +991,64 @@ EmbScratch emb_scratch(int vocab, int n, int d) {
     cur += round_up(ints, 4);
     return off;
   };
-  e.cnt = take(vocab);
-  e.start = take(vocab + 1);
   e.k1 = take(n);
   e.v1 = take(n);
-  e.k2 = take(n);
+  e.keys = take(n);
   e.perm = take(n);
-  e.hist = take((int64_t)256 * e.nblk + 1);
+  e.hist = take((int64_t)256 * e.nblk);
   e.part = take((int64_t)2 * e.nseg * d);
   e.total = cur;
   return e;
 }
-}  // namespace
-
-int64_t embed_bwd_scratch_ints(int vocab, int rows_total, int d) { return emb_scratch(vocab, rows_total, d).total; }
-
-int launch_embed_bwd(const int32_t* ids_a, const half_t* dx_a, int rows_a, const DropDev& drop_a, const int32_t* ids_b,
-                     const half_t* dx_b, int rows_b, const DropDev& drop_b, half_t* gE, int d, int vocab, int32_t* scratch,
-                     hipStream_t stream, float scale) {
+int check_embed(const int32_t* ids_a, int rows_a, const int32_t* ids_b, int rows_b, int d, int vocab, const int32_t* scratch) {
   NMT_REQUIRE(rows_a >= 0 && rows_b >= 0 && rows_a + rows_b > 0, "embed_bwd: no rows");
   NMT_REQUIRE(d >= 8 && d % 8 == 0 && d / 8 <= kThreads && vocab > 0 && vocab <= 65536, "embed_bwd: bad d=%d or vocab=%d", d, vocab);
-  NMT_REQUIRE((rows_a == 0 || (ids_a && dx_a && aligned16(dx_a))) && (rows_b == 0 || (ids_b && dx_b && aligned16(dx_b))) && gE &&
-                  aligned16(gE) && scratch && aligned16(scratch),
+  NMT_REQUIRE((rows_a == 0 || ids_a) && (rows_b == 0 || ids_b) && scratch && aligned16(scratch), "embed_bwd: null or misaligned pointer");
+  return NMT_OK;
+}
+}  // namespace
+
+int64_t embed_bwd_scratch_ints(int /*vocab*/, int rows_total, int d) { return emb_scratch(rows_total, d).total; }
+
+int launch_embed_sort(const int32_t* ids_a, int rows_a, const int32_t* ids_b, int rows_b, int d, int vocab, int32_t* scratch, hipStream_t stream) {
+  if (int rc = check_embed(ids_a, rows_a, ids_b, rows_b, d, vocab, scratch)) return rc;
+  const int n = rows_a + rows_b;
+  const EmbScratch e = emb_scratch(n, d);
+  int32_t *k1 = scratch + e.k1, *v1 = scratch + e.v1, *keys = scratch + e.keys, *perm = scratch + e.perm, *hist = scratch + e.hist;
+  if (n <= kSmallSort) {
+    NMT_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(emb_sort_small_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmallSortLds));
+    hipLaunchKernelGGL(emb_sort_small_kernel, dim3(1), dim3(1024), kSmallSortLds, stream, ids_a, rows_a, ids_b, vocab, n, keys, perm);
+    NMT_LAUNCH_CHECK();
+    return NMT_OK;
+  }
+  // stable sort of the positions by id: low byte, then high byte
+  const int nh = 256 * e.nblk;
+  for (int pass = 0; pass < 2; ++pass) {
+    const int32_t *kin = pass ? k1 : nullptr, *vin = pass ? v1 : nullptr;
+    hipLaunchKernelGGL(radix_hist_kernel, dim3(e.nblk), dim3(kThreads), 0, stream, ids_a, rows_a, ids_b, vocab, kin, n, 8 * pass, e.nblk, hist);
+    NMT_LAUNCH_CHECK();
+    hipLaunchKernelGGL(radix_scan_kernel, dim3(1), dim3(1024), 0, stream, hist, nh);
+    NMT_LAUNCH_CHECK();
+    hipLaunchKernelGGL(radix_scatter_kernel, dim3(e.nblk), dim3(kThreads), 0, stream, ids_a, rows_a, ids_b, vocab, kin, vin, n, 8 * pass,
+                       e.nblk, hist, pass ? keys : k1, pass ? perm : v1);
+    NMT_LAUNCH_CHECK();
+  }
+  return NMT_OK;
+}
+
+int launch_embed_sum(const half_t* dx_a, int rows_a, const DropDev& drop_a, const half_t* dx_b, int rows_b, const DropDev& drop_b, half_t* gE,
+                     int d, const int32_t* scratch, hipStream_t stream, float scale) {
+  NMT_REQUIRE((rows_a == 0 || (dx_a && aligned16(dx_a))) && (rows_b == 0 || (dx_b && aligned16(dx_b))) && gE && aligned16(gE),
               "embed_bwd: null or misaligned pointer");
   NMT_REQUIRE((!drop_a.thr || drop_a.n_pos > 0) && (!drop_b.thr || drop_b.n_pos > 0), "embed_bwd: positions per sentence must be positive");
   const int n = rows_a + rows_b;
-  const EmbScratch e = emb_scratch(vocab, n, d);
-  int32_t *cnt = scratch + e.cnt, *start = scratch + e.start, *k1 = scratch + e.k1, *v1 = scratch + e.v1, *k2 = scratch + e.k2;
-  int32_t *perm = scratch + e.perm, *hist = scratch + e.hist;
-  float* part = reinterpret_cast<float*>(scratch + e.part);
-  hipLaunchKernelGGL(fill_int_kernel, dim3(ceil_div(vocab, kThreads)), dim3(kThreads), 0, stream, cnt, vocab, 0);
+  const EmbScratch e = emb_scratch(n, d);
+  const int32_t *keys = scratch + e.keys, *perm = scratch + e.perm;
+  float* part = const_cast<float*>(reinterpret_cast<const float*>(scratch + e.part));
+  const int threads = (int)round_up(d / 8, kWave);
+  hipLaunchKernelGGL(emb_segment_kernel, dim3(e.nseg), dim3(threads), 0, stream, dx_a, rows_a, drop_a, dx_b, drop_b, gE, n, d, keys, perm, part, scale);
   NMT_LAUNCH_CHECK();
-  {
-    // one block per compute unit, more if a block's share would exceed what its 16-bit counters hold
-    int blocks = device_info().cus;
-    if (ceil_div(n, blocks) > kHistMaxPerBlock) blocks = ceil_div(n, kHistMaxPerBlock);
-    const int per_block = ceil_div(n, blocks);
-    const size_t hist_bytes = (size_t)((vocab + 1) / 2) * sizeof(uint32_t);
-    if (hist_bytes > 64 * 1024)
-      NMT_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(emb_hist_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)hist_bytes));
-    hipLaunchKernelGGL(emb_hist_kernel, dim3(blocks), dim3(kHistThreads), hist_bytes, stream, ids_a, rows_a, ids_b, rows_b, vocab, per_block, cnt);
-    NMT_LAUNCH_CHECK();
-  }
-  hipLaunchKernelGGL(emb_scan_kernel, dim3(1), dim3(1024), 0, stream, cnt, start, vocab);
-  NMT_LAUNCH_CHECK();
-  // stable sort of the positions by id: low byte, then high byte
-  const int nh = 256 * e.nblk;
-  hipLaunchKernelGGL(radix_hist_kernel, dim3(e.nblk), dim3(kThreads), 0, stream, ids_a, rows_a, ids_b, vocab, (const int32_t*)nullptr, n, 0,
-                     e.nblk, hist);
-  NMT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(emb_scan_kernel, dim3(1), dim3(1024), 0, stream, hist, hist, nh);
-  NMT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(radix_scatter_kernel, dim3(e.nblk), dim3(kThreads), 0, stream, ids_a, rows_a, ids_b, vocab, (const int32_t*)nullptr,
-                     (const int32_t*)nullptr, n, 0, e.nblk, hist, k1, v1);
-  NMT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(radix_hist_kernel, dim3(e.nblk), dim3(kThreads), 0, stream, ids_a, rows_a, ids_b, vocab, k1, n, 8, e.nblk, hist);
-  NMT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(emb_scan_kernel, dim3(1), dim3(1024), 0, stream, hist, hist, nh);
-  NMT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(radix_scatter_kernel, dim3(e.nblk), dim3(kThreads), 0, stream, ids_a, rows_a, ids_b, vocab, k1, v1, n, 8, e.nblk, hist,
-                     k2, perm);
-  NMT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(emb_segment_kernel, dim3(e.nseg), dim3(kThreads), 0, stream, ids_a, dx_a, rows_a, drop_a, ids_b, dx_b, rows_b, drop_b, gE,
-                     d, vocab, start, perm, part, scale);
-  NMT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(emb_finish_kernel, dim3(e.nseg), dim3(kThreads), 0, stream, ids_a, rows_a, ids_b, rows_b, gE, d, vocab, start, perm, part, scale);
+  hipLaunchKernelGGL(emb_finish_kernel, dim3(e.nseg), dim3(kEmbFinish), 0, stream, gE, n, d, keys, part, scale);
   NMT_LAUNCH_CHECK();
   return NMT_OK;
 }

@@ -437,6 +437,32 @@ def test_embedding_backward_matches_oracle_and_is_deterministic(d, V, p, Ba, Sa,
     assert_close16(outs[0], want, "embedding backward", rel=2e-3, l2=1e-3)
 
 
+# list lengths around the segments of the summing kernel and around the limit of the one-block sort; runs that begin or end
+# exactly on a segment border, one run over all segments, d from one thread per row to 256
+@pytest.mark.parametrize("d,V,na,nb,kind", [(8, 16, 1, 0, "zipf"), (64, 264, 20, 12, "border"), (64, 1000, 0, 33, "zipf"), (2048, 40, 70, 59, "border"),
+                                            (64, 65536, 9000, 7384, "zipf"), (64, 65536, 9000, 7385, "zipf"), (64, 8, 30000, 10000, "one"),
+                                            (1024, 304, 3000, 2001, "zipf"), (128, 512, 16640, 0, "border")])
+def test_embedding_backward_run_and_list_borders(d, V, na, nb, kind):
+    rng = np.random.default_rng(d + V + na)
+    n = na + nb
+    if kind == "one":
+        ids = np.full(n, 5)
+    elif kind == "border":
+        ids = rng.permutation(np.minimum(np.arange(n) // 16, V - 1))      # every run fills one segment of 16
+    else:
+        ids = np.minimum(rng.zipf(1.3, size=n), V) - 1
+    dx = f16(rng.normal(size=(n, d)))
+    g0 = f16(rng.normal(size=(V, d)))
+    want = g0.copy()
+    np.add.at(want, ids, dx * math.sqrt(d))
+    scratch = torch.full((A.nmt_op_embed_bwd_scratch(V, n, d),), -1, dtype=torch.int32, device=DEV)
+    gE, ids_d, dx_d = dev16(g0), devi(ids), dev16(dx)
+    none = _drop(0.0, 0, 1, 0, 1, 1)
+    A.nmt_op_embed_bwd(ids_d[:na] if na else None, dx_d[:na] if na else None, na, none, ids_d[na:] if nb else None, dx_d[na:] if nb else None, nb, none,
+                       gE, d, V, scratch)
+    assert_close16(host(gE), want, f"embedding backward {kind} {n}", rel=2e-3, l2=1e-3)
+
+
 # ---- fused softmax + label-smoothed cross-entropy -------------------------------------------------
 @pytest.mark.parametrize("rows,V,scale", [(128, 1000, 128.0), (37, 32768, 128.0), (9, 40000, 1.0), (16, 8, 4.0), (20, 2056, 2.0 ** 27)])
 def test_softmax_xent_matches_oracle(rows, V, scale):
