@@ -248,6 +248,23 @@ int nmt_op_gemm_splitk(const void* d_A, int32_t a_t, int32_t lda, const void* d_
                        void* d_C, int32_t ldc, int32_t M, int32_t N, int32_t K, float* d_partial,
                        int64_t partial_floats, int32_t splits, void* stream);
 
+/* The weight gradients of several linear layers in one launch (the form the backward pass uses for a layer): for each
+ * product g_w[out, in] = out_scale * sum_r dy[r, out] x[r, in] and, if d_gb is not null, g_b[out] = out_scale *
+ * sum_r dy[r, out].  out and in are multiples of 8, matrices 16-byte aligned.  With more than one split (0 = chosen by the
+ * library) the rows are cut into that many pieces whose fp32 sums go to d_partial (partial_floats >= splits * sum over
+ * the products of out * (in + 1); may be null: never cut) and are added in increasing order by a second kernel.  tile:
+ * 0 = chosen by the library; 1..4 force 256 x 256, 128 x 128 (two work-groups per compute unit), 128 x 128 and 64 x 64. */
+typedef struct nmt_wgrad {
+  const void* d_dy;
+  const void* d_x;
+  void* d_gw;
+  void* d_gb;
+  int32_t ld_dy, ld_x, ld_gw;
+  int32_t out, in, rows;
+} nmt_wgrad;
+int nmt_op_wgrad_group(int32_t n, const nmt_wgrad* products, float out_scale, float* d_partial, int64_t partial_floats, int32_t tile,
+                       int32_t splits, void* stream);
+
 /* The same product with fp32 operands and an fp32 result, no epilogue: C[M,N] = sum_k A(m,k) B(n,k) on the fp32
  * matrix instructions.  Benchmark only -- the training step never calls it: it times what the step's products cost
  * without half precision ("Half-Precision Training" compares fp32 and fp16 training at equal settings; Table 1,

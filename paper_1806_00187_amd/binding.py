@@ -35,6 +35,11 @@ class nmt_segment(C.Structure):
     _fields_ = [("B", C.c_int32), ("S", C.c_int32), ("T", C.c_int32), ("micro_idx", C.c_uint32)]
 
 
+class nmt_wgrad(C.Structure):
+    _fields_ = [("d_dy", C.c_void_p), ("d_x", C.c_void_p), ("d_gw", C.c_void_p), ("d_gb", C.c_void_p), ("ld_dy", C.c_int32), ("ld_x", C.c_int32),
+                ("ld_gw", C.c_int32), ("out", C.c_int32), ("in_", C.c_int32), ("rows", C.c_int32)]
+
+
 _P, _I32, _I64, _F, _U32 = C.c_void_p, C.c_int32, C.c_int64, C.c_float, C.c_uint32
 _DP = C.POINTER(nmt_dropout)
 _SP = C.POINTER(nmt_segment)
@@ -67,6 +72,7 @@ _SIGNATURES = {
     "nmt_op_gemm": (C.c_int, [_P, _I32, _I32, _P, _I32, _I32, _P, _I32, _I32, _I32, _I32, _P, _I32, _DP, _P, _P, _F, _P]),
     "nmt_op_gemm_f32": (C.c_int, [_P, _I32, _I32, _P, _I32, _I32, _P, _I32, _I32, _I32, _I32, _I32, _P]),
     "nmt_op_gemm_splitk": (C.c_int, [_P, _I32, _I32, _P, _I32, _I32, _P, _I32, _I32, _I32, _I32, _P, _I64, _I32, _P]),
+    "nmt_op_wgrad_group": (C.c_int, [_I32, C.POINTER(nmt_wgrad), _F, _P, _I64, _I32, _I32, _P]),
     "nmt_op_attention_fwd": (C.c_int, [_P, _I32, _P, _I32, _P, _I32, _P, _I32, _P, _P, _I32, _I32, _I32, _I32, _I32, _I32, _I32, _P]),
     "nmt_op_attention_bwd": (C.c_int, [_P, _I32, _P, _I32, _P, _I32, _P, _I32, _P, _I32, _P, _P, _I32, _P, _I32, _P, _I32, _P,
                                        _I32, _I32, _I32, _I32, _I32, _I32, _I32, _P]),
@@ -301,6 +307,16 @@ def nmt_op_gemm_f32(A, a_t, lda, B, b_t, ldb, Cout, ldc, M, N, K, splits=1, stre
 def nmt_op_gemm_splitk(A, a_t, lda, B, b_t, ldb, Cout, ldc, M, N, K, partial, splits=0, stream=None):
     _check(load().nmt_op_gemm_splitk(_p(A), int(a_t), lda, _p(B), int(b_t), ldb, _p(Cout), ldc, M, N, K, _p(partial), partial.numel(),
                                      splits, _stream(stream)))
+
+
+def nmt_op_wgrad_group(products, out_scale=1.0, partial=None, tile=0, splits=0, stream=None):
+    """products: list of (dy, ld_dy, x, ld_x, gw, ld_gw, gb or None, out, in, rows)."""
+    arr = (nmt_wgrad * len(products))()
+    for w, (dy, ld_dy, x, ld_x, gw, ld_gw, gb, n_out, n_in, rows) in zip(arr, products):
+        w.d_dy, w.d_x, w.d_gw, w.d_gb = (None if t is None else t.data_ptr() for t in (dy, x, gw, gb))
+        w.ld_dy, w.ld_x, w.ld_gw, w.out, w.in_, w.rows = ld_dy, ld_x, ld_gw, n_out, n_in, rows
+    _check(load().nmt_op_wgrad_group(len(products), arr, out_scale, _p(partial), 0 if partial is None else partial.numel(), tile, splits,
+                                     _stream(stream)))
 
 
 def nmt_op_attention_fwd(Q, ldq, K, ldk, V, ldv, O, ldo, lse, key_ids, pad_id, causal, B, H, dh, Tq, Tk, stream=None):

@@ -167,6 +167,18 @@ int launch_gemm(const half_t* A, bool a_t, int lda, const half_t* B, bool b_t, i
                 int M, int N, int K, const GemmEpilogue& ep, hipStream_t stream, float* partial = nullptr,
                 int64_t partial_floats = 0, int splits = 1);
 
+// One weight gradient: C[M, N] = sum_k A[k, M] B[k, N], and, if colsum is set, colsum[M] = sum_k A[k, M] (the bias gradient).
+struct WgradProduct {
+  const half_t *A, *B;
+  half_t *C, *colsum;
+  int lda, ldb, ldc, M, N, K;
+};
+constexpr int kMaxWgrad = 8;
+// All products (1..kMaxWgrad of them, results times out_scale) in one launch, or two if they are cut along k.  partial: fp32 scratch for that
+// (may be null: never cut).  tile, splits: 0 = chosen by cost.
+int launch_wgrad_group(const WgradProduct* products, int n, float out_scale, float* partial, int64_t partial_floats, hipStream_t stream,
+                       int tile = 0, int splits = 0);
+
 // fp32 product on the matrix cores, for the benchmark's fp32 comparison leg (not used by the training step)
 int launch_gemm_f32(const float* A, bool a_t, int lda, const float* B, bool b_t, int ldb, float* C, int ldc, int M, int N, int K,
                     int splits, hipStream_t stream);

@@ -56,6 +56,10 @@ struct GemmArgs {
   // fp32 tile to partial[z][M][N]; partial == nullptr: one work-group per tile, epilogue, fp16 result
   float* partial;
   int k_chunk;
+  // column sums of A over k, for the products of a weight-gradient group: `colsum` where the product is not cut along
+  // k, else `partial_colsum`, fp32 [z][M]
+  half_t* colsum = nullptr;
+  float* partial_colsum = nullptr;
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const half_t* p, uint32_t bytes) {
@@ -361,28 +365,50 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const floatx16 (&a
   }
 }
 
+// Column sums of the A operand, the bias gradient of the weight-gradient products whose C tile this is: every lane adds up
+// the eight k of its row in each A fragment.  The fragments are in registers anyway, so the bias gradients cost no
+// pass over memory of their own; only the work-groups of the first tile column do it.
+__device__ __forceinline__ void add_colsum(float& sum, const half8_t& f) {
+  typedef _Float16 half2v_t __attribute__((ext_vector_type(2)));
+  struct Pairs { half2v_t p[4]; };
+  const half2v_t ones = {(_Float16)1.f, (_Float16)1.f};
+  const Pairs h = __builtin_bit_cast(Pairs, f);
+  float s = 0.f;  // (the two-element product adds in fp32 and keeps denormal halves)
+#pragma unroll
+  for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_fdot2(h.p[e], ones, s, false);
+  sum += s;
+}
+template <int BM, int TM>
+__device__ __forceinline__ void store_colsum(const GemmArgs& g, const float (&sum)[TM], int m0, int split) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const float s = sum[i] + __shfl_xor(sum[i], 32, kWave);
+    const int row = m0 + i * 32 + lane;
+    if (lane < 32 && row < g.M) {
+      if (g.partial) g.partial_colsum[(size_t)split * g.M + row] = s;
+      else g.colsum[row] = (half_t)(s * g.ep.out_scale);
+    }
+  }
+}
+
 // NS stages of BK k each form a ring: while k-tile t is multiplied, tiles t+1 .. t+NS-1 are in LDS
 // or on their way.
-template <int BM, int BN, bool AT, bool BT, int BK, int NS, int NW>
-__global__ void __launch_bounds__(64 * NW) gemm_kernel(const GemmArgs g) {
+// (The stages are separate arrays, so that the compiler can tell that fragment reads of one stage do not depend on
+// the loads in flight into the others.)
+template <int BM, int BN, bool AT, bool BT, int BK, int NS, int NW, bool SUMS>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int split, int tm, int tn, unsigned char* stage0, unsigned char* stage1,
+                                          unsigned char* stage2, unsigned char* stage3) {
   using T = Tile<BM, BN, AT, BT, BK, NW>;
   using OpA = typename T::OpA;
   using OpB = typename T::OpB;
   static_assert(NS >= 2 && NS <= 4, "two to four stages");
-  // separate arrays, so that the compiler can tell that fragment reads of one stage do not depend
-  // on the loads in flight into the others
-  __shared__ __align__(1024) unsigned char stage0[T::STAGE];
-  __shared__ __align__(1024) unsigned char stage1[T::STAGE];
-  __shared__ __align__(1024) unsigned char stage2[NS > 2 ? T::STAGE : 16];
-  __shared__ __align__(1024) unsigned char stage3[NS > 3 ? T::STAGE : 16];
   constexpr int WGN = NW / 2;  // the waves form a 2 x WGN grid over the block tile
   constexpr int WM = BM / 2, WN = BN / WGN, TM = WM / 32, TN = WN / 32, KS = BK / 16;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
-
-  int split, tm, tn;
-  place(g, (int)blockIdx.x + (int)blockIdx.y * (g.tiles_m * g.tiles_n), g.tiles_m * g.tiles_n * (int)gridDim.y, split, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
+  float colsum[SUMS ? TM : 1] = {};
 
   floatx16 acc[TM][TN];
 #pragma unroll
@@ -422,6 +448,10 @@ __global__ void __launch_bounds__(64 * NW) gemm_kernel(const GemmArgs g) {
 #pragma unroll
       for (int j = 0; j < TN; ++j)  // B first: the result tile is transposed, lane = row of C, registers = columns
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[set][j], af[set][i], acc[i][j], 0, 0, 0);
+    if constexpr (SUMS) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) add_colsum(colsum[i], af[set][i]);
+    }
   };
   auto interleave = [&]() { Interleave<0, TM * TN, OpA::READS * TM + OpB::READS * TN>::run(); };
   // One k-tile.  On entry the fragments of k-step 0 of `cur` are in registers and the next NS-1
@@ -475,7 +505,21 @@ __global__ void __launch_bounds__(64 * NW) gemm_kernel(const GemmArgs g) {
   __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));  // the last refills (all zeros) must land before the stages are reused
   __syncthreads();
 
+  if constexpr (SUMS) {
+    if (wn == 0) store_colsum<BM, TM>(g, colsum, m0 + wm * WM, split);
+  }
   store_tile<BM, BN, NW, T::STAGE>(g, acc, m0, n0, split, stage0, stage1);
+}
+template <int BM, int BN, bool AT, bool BT, int BK, int NS, int NW>
+__global__ void __launch_bounds__(64 * NW) gemm_kernel(const GemmArgs g) {
+  using T = Tile<BM, BN, AT, BT, BK, NW>;
+  __shared__ __align__(1024) unsigned char stage0[T::STAGE];
+  __shared__ __align__(1024) unsigned char stage1[T::STAGE];
+  __shared__ __align__(1024) unsigned char stage2[NS > 2 ? T::STAGE : 16];
+  __shared__ __align__(1024) unsigned char stage3[NS > 3 ? T::STAGE : 16];
+  int split, tm, tn;
+  place(g, (int)blockIdx.x + (int)blockIdx.y * (g.tiles_m * g.tiles_n), g.tiles_m * g.tiles_n * (int)gridDim.y, split, tm, tn);
+  gemm_tile<BM, BN, AT, BT, BK, NS, NW, false>(g, split, tm, tn, stage0, stage1, stage2, stage3);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -492,23 +536,19 @@ __global__ void __launch_bounds__(64 * NW) gemm_kernel(const GemmArgs g) {
 // The two-stage ring remains for 128 x 128 tiles on four wavefronts, two work-groups per compute unit, where there are
 // enough tiles for that: the second work-group's k-tiles then cover the first one's prologue and epilogue.
 // ------------------------------------------------------------------------------------------------
-template <int BM, int BN, bool AT, bool BT, int NS, int NW>
-__global__ void __launch_bounds__(64 * NW) gemm_small_kernel(const GemmArgs g) {
+template <int BM, int BN, bool AT, bool BT, int NS, int NW, bool SUMS>
+__device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int split, int tm, int tn, unsigned char* stage0, unsigned char* stage1,
+                                                unsigned char* stage2, unsigned char* stage3) {
   constexpr int BK = 64;
   using T = Tile<BM, BN, AT, BT, BK, NW>;
   using OpA = typename T::OpA;
   using OpB = typename T::OpB;
   static_assert(NS == 2 || NS == 4, "two or four stages (the fragments' register set alternates with the stage)");
-  __shared__ __align__(1024) unsigned char stage0[T::STAGE];  // separate arrays (see gemm_kernel)
-  __shared__ __align__(1024) unsigned char stage1[T::STAGE];
-  __shared__ __align__(1024) unsigned char stage2[NS > 2 ? T::STAGE : 16];
-  __shared__ __align__(1024) unsigned char stage3[NS > 2 ? T::STAGE : 16];
   constexpr int WGN = NW / 2, WM = BM / 2, WN = BN / WGN, TM = WM / 32, TN = WN / 32, KS = BK / 16;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
-  int split, tm, tn;
-  place(g, (int)blockIdx.x + (int)blockIdx.y * (g.tiles_m * g.tiles_n), g.tiles_m * g.tiles_n * (int)gridDim.y, split, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
+  float colsum[SUMS ? TM : 1] = {};
 
   floatx16 acc[TM][TN];
 #pragma unroll
@@ -558,6 +598,12 @@ __global__ void __launch_bounds__(64 * NW) gemm_small_kernel(const GemmArgs g) {
 #pragma unroll
         for (int j = 0; j < TN; ++j)  // (B first, k-steps in increasing order: the same sums as gemm_kernel's)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[set][s][j], af[set][s][i], acc[i][j], 0, 0, 0);
+    if constexpr (SUMS) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) add_colsum(colsum[i], af[set][s][i]);
+    }
     Interleave<0, KS * TM * TN, KS * (OpA::READS * TM + OpB::READS * TN)>::run();
   };
 
@@ -586,7 +632,21 @@ __global__ void __launch_bounds__(64 * NW) gemm_small_kernel(const GemmArgs g) {
   }
   __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));  // the last refills (all zeros) must land before the stages are reused
   __syncthreads();
+  if constexpr (SUMS) {
+    if (wn == 0) store_colsum<BM, TM>(g, colsum, m0 + wm * WM, split);
+  }
   store_tile<BM, BN, NW, T::STAGE>(g, acc, m0, n0, split, stage0, stage1);
+}
+template <int BM, int BN, bool AT, bool BT, int NS, int NW>
+__global__ void __launch_bounds__(64 * NW) gemm_small_kernel(const GemmArgs g) {
+  using T = Tile<BM, BN, AT, BT, 64, NW>;
+  __shared__ __align__(1024) unsigned char stage0[T::STAGE];  // separate arrays (see gemm_tile)
+  __shared__ __align__(1024) unsigned char stage1[T::STAGE];
+  __shared__ __align__(1024) unsigned char stage2[NS > 2 ? T::STAGE : 16];
+  __shared__ __align__(1024) unsigned char stage3[NS > 2 ? T::STAGE : 16];
+  int split, tm, tn;
+  place(g, (int)blockIdx.x + (int)blockIdx.y * (g.tiles_m * g.tiles_n), g.tiles_m * g.tiles_n * (int)gridDim.y, split, tm, tn);
+  gemm_small_tile<BM, BN, AT, BT, NS, NW, false>(g, split, tm, tn, stage0, stage1, stage2, stage3);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -637,7 +697,7 @@ __global__ void __launch_bounds__(512) gemm_persistent_kernel(const GemmArgs g) 
   using OpB = typename T::OpB;
   static_assert(NS == 2 || NS == 4, "two or four stages");
   static_assert(NS * T::STAGE == 128 * 1024, "the ring takes 128 KB; the staging rows take the 32 KB that are left");
-  // separate arrays (see gemm_kernel); the third and fourth exist only in the four-stage form
+  // separate arrays (see gemm_tile); the third and fourth exist only in the four-stage form
   __shared__ __align__(1024) unsigned char stage0[T::STAGE];
   __shared__ __align__(1024) unsigned char stage1[T::STAGE];
   unsigned char *stage2 = nullptr, *stage3 = nullptr;
@@ -861,6 +921,106 @@ __global__ void __launch_bounds__(kThreads) splitk_reduce_kernel(const float* __
   st_half8(C + (size_t)row * ldc + c8 * 8, o);
 }
 
+// ------------------------------------------------------------------------------------------------
+// Weight gradients of one layer in one launch.  Each of them alone is too small to fill the chip (512 x 2048 results are
+// 64 tiles of 128 x 128), so one by one they were cut along the positions, wrote fp32 partial sums and needed a
+// second kernel each; together a layer's four to seven products are one launch of whole tiles, and the bias gradients
+// ride along (no pass over memory for the column sums).  An encoder layer's over 3000 positions, alone on the chip: 36 us
+// 512 wide, 91 us 1024 wide (0.83 PFLOP/s), where the products, reductions and column sums one by one took 145 and 276 us of kernel
+// time beside the chain; over 53000 positions 1024 wide: 1.29 ms (1.04 PFLOP/s).
+// ------------------------------------------------------------------------------------------------
+struct GroupArgs {
+  int n, xcds, group_m, splits, total;
+  float out_scale;
+  struct Product {
+    WgradProduct w;
+    float *partial, *partial_colsum;
+    int begin;            // first work item of the product
+    int tiles_m, tiles_n, k_chunk;
+  } p[kMaxWgrad];
+};
+// Work item -> product, split and tile; consecutive items of one XCD's run share operand panels (as in place()).
+__device__ __forceinline__ GemmArgs group_item(const GroupArgs& a, int lin, int& split, int& tm, int& tn, bool& sums) {
+  const int at = xcd_order(lin, a.total, a.xcds);
+  int i = 0;
+  while (i + 1 < a.n && at >= a.p[i + 1].begin) ++i;
+  const GroupArgs::Product& p = a.p[i];
+  GemmArgs g{p.w.A, p.w.B, p.w.C, p.w.lda, p.w.ldb, p.w.ldc, p.w.M, p.w.N, p.w.K, p.tiles_m, p.tiles_n, a.group_m, a.xcds, GemmEpilogue{},
+             p.partial, p.k_chunk, p.w.colsum, p.partial_colsum};
+  g.ep.out_scale = a.out_scale;
+  const int nt = g.tiles_m * g.tiles_n;
+  split = (at - p.begin) / nt;
+  const int pid = (at - p.begin) - split * nt, per_group = g.group_m * g.tiles_n;
+  const int first = (pid / per_group) * g.group_m;
+  const int rows = min(g.tiles_m - first, g.group_m);
+  tm = first + (pid % per_group) % rows;
+  tn = (pid % per_group) / rows;
+  sums = tn == 0 && g.colsum;
+  return g;
+}
+template <int BM, int BN, int BK, int NS, int NW>
+__global__ void __launch_bounds__(64 * NW) wgrad_group_kernel(const GroupArgs a) {
+  using T = Tile<BM, BN, true, true, BK, NW>;
+  __shared__ __align__(1024) unsigned char stage0[T::STAGE];
+  __shared__ __align__(1024) unsigned char stage1[T::STAGE];
+  __shared__ __align__(1024) unsigned char stage2[NS > 2 ? T::STAGE : 16];
+  __shared__ __align__(1024) unsigned char stage3[NS > 2 ? T::STAGE : 16];
+  int split, tm, tn;
+  bool sums;
+  const GemmArgs g = group_item(a, (int)blockIdx.x, split, tm, tn, sums);
+  if constexpr (BM == 256) {
+    if (sums) gemm_tile<BM, BN, true, true, BK, NS, NW, true>(g, split, tm, tn, stage0, stage1, stage2, stage3);
+    else gemm_tile<BM, BN, true, true, BK, NS, NW, false>(g, split, tm, tn, stage0, stage1, stage2, stage3);
+  } else {
+    if (sums) gemm_small_tile<BM, BN, true, true, NS, NW, true>(g, split, tm, tn, stage0, stage1, stage2, stage3);
+    else gemm_small_tile<BM, BN, true, true, NS, NW, false>(g, split, tm, tn, stage0, stage1, stage2, stage3);
+  }
+}
+// C and the column sums of every product of the group from the splits' fp32 sums, 8 columns per thread, splits in
+// increasing order
+struct GroupReduceArgs {
+  int n, splits;
+  float scale;
+  struct Product {
+    const float *partial, *partial_colsum;
+    half_t *C, *colsum;
+    int M, N, ldc;
+    int64_t begin;  // first work item: M * N / 8 of C, then ceil(M / 8) of the column sums
+  } p[kMaxWgrad];
+  int64_t total;
+};
+__global__ void __launch_bounds__(kThreads) wgrad_group_reduce_kernel(const GroupReduceArgs a) {
+  const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (gid >= a.total) return;
+  int i = 0;
+  while (i + 1 < a.n && gid >= a.p[i + 1].begin) ++i;
+  const GroupReduceArgs::Product& p = a.p[i];
+  const int64_t at = gid - p.begin, chunks = p.N >> 3, of_c = (int64_t)p.M * chunks;
+  if (at >= of_c) {
+    const int m0 = (int)(at - of_c) * 8;
+    for (int m = m0; m < min(m0 + 8, p.M); ++m) {
+      float s = 0.f;
+      for (int z = 0; z < a.splits; ++z) s += p.partial_colsum[(size_t)z * p.M + m];
+      p.colsum[m] = (half_t)(s * a.scale);
+    }
+    return;
+  }
+  const int row = (int)(at / chunks), c8 = (int)(at % chunks);
+  const size_t off = (size_t)row * p.N + c8 * 8, plane = (size_t)p.M * p.N;
+  floatx4 lo = *reinterpret_cast<const floatx4*>(p.partial + off), hi = *reinterpret_cast<const floatx4*>(p.partial + off + 4);
+  for (int z = 1; z < a.splits; ++z) {
+    lo += *reinterpret_cast<const floatx4*>(p.partial + z * plane + off);
+    hi += *reinterpret_cast<const floatx4*>(p.partial + z * plane + off + 4);
+  }
+  half8_t o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    o[e] = (half_t)(lo[e] * a.scale);
+    o[4 + e] = (half_t)(hi[e] * a.scale);
+  }
+  st_half8(p.C + (size_t)row * p.ldc + c8 * 8, o);
+}
+
 template <int BM, int BN, bool AT, bool BT, int BK, int NS, int NW>
 void launch_variant(const GemmArgs& g, int splits, hipStream_t stream) {
   const dim3 grid(g.tiles_m * g.tiles_n, splits), block(64 * NW);
@@ -1051,6 +1211,135 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
   return launch_small_tile(choose_small_tile(M, N, K), g, a_t, b_t, 1, stream);
 }
 
+// ---- weight-gradient groups ----
+enum GroupTile { kGroup256 = 1, kGroup128Many, kGroup128, kGroup64, kGroupTiles = kGroup64 };
+constexpr int kGroupEdge[kGroupTiles + 1] = {0, 256, 128, 128, 64};
+// What one work-group takes for a 64-deep piece of the contraction, in us, from timings of the layer groups of four widths
+// (64 to 1024) over 130 to 53000 positions: with few compute units at work, and with all of them; per_cu work-groups share one.
+struct GroupCost {
+  int per_cu;
+  double fixed, k_tile_few, k_tile[2];
+};
+constexpr GroupCost kGroupCost[kGroupTiles + 1] = {
+    {}, {1, 8.0, 1.50, {2.05, 0.}}, {2, 6.0, 0.62, {0.72, 1.13}}, {1, 6.0, 0.54, {0.68, 0.}}, {2, 4.0, 0.25, {0.31, 0.53}}};
+// Time of the whole group alone on `cus` compute units, and the compute-unit time it takes (us x compute units).
+double group_us(int tile, const WgradProduct* p, int n, int splits, int cus, double& cu_us) {
+  const GroupCost& c = kGroupCost[tile];
+  const int edge = kGroupEdge[tile];
+  int64_t tiles = 0, floats = 0;
+  int longest = 0;
+  for (int i = 0; i < n; ++i) {
+    tiles += (int64_t)ceil_div(p[i].M, edge) * ceil_div(p[i].N, edge) * splits;
+    floats += (int64_t)p[i].M * p[i].N;
+    longest = p[i].K > longest ? p[i].K : longest;
+  }
+  const int nk = ceil_div(ceil_div(longest, splits), 64);
+  const int64_t slots = (int64_t)cus * c.per_cu, rounds = tiles / slots, rest = tiles - rounds * slots;
+  double us = rounds * (c.fixed + nk * c.k_tile[c.per_cu - 1]);
+  cu_us = us * cus;
+  if (rest) {
+    const int on_one = ceil_div(rest, cus);
+    const double fill = rest < cus ? (double)rest / cus : 1.0;
+    const double last = c.fixed + nk * (on_one > 1 ? c.k_tile[1] : c.k_tile_few + fill * (c.k_tile[0] - c.k_tile_few));
+    us += last;
+    cu_us += last * (rest < cus ? (double)rest : (double)cus);
+  }
+  if (splits > 1) {  // fp32 sums written and read back, one more launch
+    const double reduce = 4.0 + (double)floats * splits * 8.0 / 8e6;
+    us += reduce;
+    cu_us += reduce * cus;
+  }
+  return us;
+}
+// The tile and the number of k splits of a group.  A group runs beside the next layer's chain of input gradients, so
+// what counts is the compute-unit time it takes from that chain; its own latency counts too (the last group of a pass has
+// only the embedding kernels beside it, and with one stream there is nothing).  Weights of 0 to 1 for it measured the same
+// updates within 1 %; 10 cost the packed ones 3 %, because small tiles then win and take more compute-unit time.
+constexpr double kGroupLatencyWeight = 0.5;
+void choose_group(const WgradProduct* p, int n, int64_t most, int cus, int& tile, int& splits) {
+  int shortest = p[0].K, best_tile = tile ? tile : kGroup256, best_splits = splits ? splits : 1;
+  for (int i = 1; i < n; ++i) shortest = p[i].K < shortest ? p[i].K : shortest;
+  double best = 0.;
+  for (int t = tile ? tile : 1; t <= (tile ? tile : kGroupTiles); ++t) {
+    for (int z = splits ? splits : 1; z <= (splits ? splits : 32); z = z < 4 ? z + 1 : z * 2) {
+      if (!splits && z > 1 && (z > most || shortest / z < 256)) break;
+      double cu_us;
+      const double us = group_us(t, p, n, z, cus, cu_us), score = kGroupLatencyWeight * us + cu_us / cus;
+      if (best == 0. || score < best) {
+        best = score;
+        best_tile = t;
+        best_splits = z;
+      }
+    }
+  }
+  tile = best_tile;
+  splits = best_splits;
+}
+int check_wgrad(const WgradProduct& w) {
+  NMT_REQUIRE(w.M > 0 && w.N > 0 && w.K > 0, "weight gradient: empty problem M=%d N=%d K=%d", w.M, w.N, w.K);
+  NMT_REQUIRE(w.A && w.B && w.C && aligned16(w.A) && aligned16(w.B) && aligned16(w.C), "weight gradient: null or misaligned operand");
+  NMT_REQUIRE(w.lda % 8 == 0 && w.ldb % 8 == 0 && w.ldc % 8 == 0 && w.N % 8 == 0 && w.M % 8 == 0, "weight gradient: lda/ldb/ldc/M/N must be multiples of 8");
+  NMT_REQUIRE(w.lda >= w.M && w.ldb >= w.N && w.ldc >= w.N, "weight gradient: leading dimension too small");
+  NMT_REQUIRE(w.lda <= (1 << 20) && w.ldb <= (1 << 20) && w.ldc <= (1 << 20), "weight gradient: leading dimensions above 2^20 are not supported");
+  return NMT_OK;
+}
+int launch_wgrad_group_impl(const WgradProduct* products, int n, float out_scale, float* partial, int64_t partial_floats, hipStream_t stream,
+                            int tile, int splits) {
+  NMT_REQUIRE(products && n >= 1 && n <= kMaxWgrad, "weight gradients: %d products outside [1, %d]", n, kMaxWgrad);
+  NMT_REQUIRE(tile >= 0 && tile <= kGroupTiles && splits >= 0 && splits <= 64, "weight gradients: tile %d or number of k splits %d out of range", tile, splits);
+  NMT_REQUIRE(!partial || aligned16(partial), "weight gradients: partial-sum buffer must be 16-byte aligned");
+  int64_t per_split = 0;  // floats one split leaves behind
+  for (int i = 0; i < n; ++i) {
+    if (int rc = check_wgrad(products[i])) return rc;
+    per_split += (int64_t)products[i].M * products[i].N + products[i].M;
+  }
+  const int64_t most = partial ? partial_floats / per_split : 1;
+  // (callers that keep several passes in flight: the tile is chosen for the group's share of the chip, the splits are not,
+  //  so that sums do not depend on how many passes are in flight)
+  int whole_chip_tile = tile;
+  choose_group(products, n, most, device_info().cus, whole_chip_tile, splits);
+  choose_group(products, n, most, device_info().cus / tuning().gemm_share > 1 ? device_info().cus / tuning().gemm_share : 1, tile, splits);
+  NMT_REQUIRE(splits == 1 || splits <= most, "weight gradients: partial-sum buffer of %lld floats too small for %d splits", (long long)partial_floats, splits);
+  const int edge = kGroupEdge[tile];
+  GroupArgs a = {};
+  GroupReduceArgs ra = {};
+  a.n = ra.n = n;
+  a.xcds = device_info().xcds;
+  a.group_m = tuning().gemm_group;
+  a.splits = ra.splits = splits;
+  a.out_scale = ra.scale = out_scale;
+  float* at = partial;
+  for (int i = 0; i < n; ++i) {
+    const WgradProduct& w = products[i];
+    GroupArgs::Product& p = a.p[i];
+    p.w = w;
+    p.begin = a.total;
+    p.tiles_m = ceil_div(w.M, edge);
+    p.tiles_n = ceil_div(w.N, edge);
+    p.k_chunk = (int)round_up(ceil_div(w.K, splits), 64);  // (a split past the end of a short contraction writes zeros)
+    a.total += p.tiles_m * p.tiles_n * splits;
+    if (splits > 1) {
+      p.partial = at;
+      p.partial_colsum = at + (int64_t)splits * w.M * w.N;
+      at += (int64_t)splits * ((int64_t)w.M * w.N + w.M);
+      ra.p[i] = {p.partial, p.partial_colsum, w.C, w.colsum, w.M, w.N, w.ldc, ra.total};
+      ra.total += (int64_t)w.M * (w.N / 8) + (w.colsum ? w.M / 8 : 0);
+    }
+  }
+  const dim3 grid(a.total);
+  switch (tile) {
+    case kGroup256: hipLaunchKernelGGL((wgrad_group_kernel<256, 256, 32, 4, 8>), grid, dim3(512), 0, stream, a); break;
+    case kGroup128Many: hipLaunchKernelGGL((wgrad_group_kernel<128, 128, 64, 2, 4>), grid, dim3(256), 0, stream, a); break;
+    case kGroup128: hipLaunchKernelGGL((wgrad_group_kernel<128, 128, 64, 4, 8>), grid, dim3(512), 0, stream, a); break;
+    default: hipLaunchKernelGGL((wgrad_group_kernel<64, 64, 64, 4, 4>), grid, dim3(256), 0, stream, a); break;
+  }
+  NMT_LAUNCH_CHECK();
+  if (splits == 1) return NMT_OK;
+  hipLaunchKernelGGL(wgrad_group_reduce_kernel, dim3(ceil_div(ra.total, kThreads)), dim3(kThreads), 0, stream, ra);
+  NMT_LAUNCH_CHECK();
+  return NMT_OK;
+}
+
 // Optional timing of every product with HIP events on the stream it is launched on (the benchmark's roofline leg):
 // pairs of events from a pool that grows as needed and is read and reset by gemm_timing_read.
 struct TimedProduct {
@@ -1062,9 +1351,9 @@ size_t g_timed_used = 0;
 std::mutex g_timed_mutex;
 }  // namespace
 
-int launch_gemm(const half_t* A, bool a_t, int lda, const half_t* B, bool b_t, int ldb, half_t* C, int ldc, int M,
-                int N, int K, const GemmEpilogue& ep, hipStream_t stream, float* partial, int64_t partial_floats, int splits) {
-  if (!tuning().gemm_timing) return launch_gemm_impl(A, a_t, lda, B, b_t, ldb, C, ldc, M, N, K, ep, stream, partial, partial_floats, splits);
+template <typename Launch>
+static int timed_launch(double flops, hipStream_t stream, Launch launch) {
+  if (!tuning().gemm_timing) return launch();
   TimedProduct t;
   {
     std::lock_guard<std::mutex> lock(g_timed_mutex);
@@ -1074,13 +1363,27 @@ int launch_gemm(const half_t* A, bool a_t, int lda, const half_t* B, bool b_t, i
       NMT_HIP_CHECK(hipEventCreate(&fresh.stop));
       g_timed.push_back(fresh);
     }
-    g_timed[g_timed_used].flops = 2.0 * M * N * K;
+    g_timed[g_timed_used].flops = flops;
     t = g_timed[g_timed_used++];
   }
   NMT_HIP_CHECK(hipEventRecord(t.start, stream));
-  const int rc = launch_gemm_impl(A, a_t, lda, B, b_t, ldb, C, ldc, M, N, K, ep, stream, partial, partial_floats, splits);
+  const int rc = launch();
   NMT_HIP_CHECK(hipEventRecord(t.stop, stream));
   return rc;
+}
+
+int launch_gemm(const half_t* A, bool a_t, int lda, const half_t* B, bool b_t, int ldb, half_t* C, int ldc, int M,
+                int N, int K, const GemmEpilogue& ep, hipStream_t stream, float* partial, int64_t partial_floats, int splits) {
+  return timed_launch(2.0 * M * N * K, stream, [&] {
+    return launch_gemm_impl(A, a_t, lda, B, b_t, ldb, C, ldc, M, N, K, ep, stream, partial, partial_floats, splits);
+  });
+}
+
+int launch_wgrad_group(const WgradProduct* products, int n, float out_scale, float* partial, int64_t partial_floats, hipStream_t stream,
+                       int tile, int splits) {
+  double flops = 0.0;
+  for (int i = 0; products && i < n && i < kMaxWgrad; ++i) flops += 2.0 * products[i].M * products[i].N * products[i].K;
+  return timed_launch(flops, stream, [&] { return launch_wgrad_group_impl(products, n, out_scale, partial, partial_floats, stream, tile, splits); });
 }
 
 int gemm_timing_read(double* ms, int64_t* products, double* flops) {

@@ -4,6 +4,7 @@
 #include <stdarg.h>
 #include <stdlib.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -94,7 +95,6 @@ struct DecP { AttnP self; LnP ln1; AttnP cross; LnP ln2; FfnP ffn; LnP ln3; };
 
 // dropout sites: a site id selects an independent random stream
 constexpr int kMaxSegments = NMT_MAX_SEGMENTS;
-constexpr int64_t kWgradPartialFloats = 16ll << 20;
 constexpr uint32_t kSiteEmbSrc = 0, kSiteEmbTgt = 1;
 constexpr uint32_t kKindSelfRes = 0, kKindCrossRes = 1, kKindFfnAct = 2, kKindFfnRes = 3;
 inline uint32_t layer_site(int layer_index, uint32_t kind) { return 16u * (1u + (uint32_t)layer_index) + kind; }
@@ -110,7 +110,7 @@ struct Plan {
   int64_t x0, y0, logits, rowloss;
   std::vector<EncW> enc;
   std::vector<DecW> dec;
-  int64_t dx_dec, dx_enc, dy[2], dym[2], dO, dqkv[2], dh[2], dq[2], dkv[2], lnpart, cspart, embscratch, wgpart, wgpart_floats;
+  int64_t dx_dec, dx_enc, dy, dsub[2][3], dO, dqkv[2], dh[2], dq[2], dkv[2], lnpart, embscratch, wgpart, wgpart_floats;
   int64_t total;
 };
 
@@ -245,20 +245,20 @@ int64_t plan_workspace(const nmt_ctx* c, const GroupDims& gd, Plan& p) {
   p.dx_dec = take(Nt * d * h2);
   p.dx_enc = take(Ns * d * h2);
   p.dO = take(Nm * d * h2);
-  for (int b = 0; b < 2; ++b) {  // two sets: weight-gradient kernels of one sub-layer overlap the next sub-layer
-    p.dy[b] = take(Nm * d * h2);
-    p.dym[b] = take(Nm * d * h2);
+  p.dy = take(Nm * d * h2);
+  for (int b = 0; b < 2; ++b) {  // two sets: the weight gradients of one layer overlap the next layer
+    for (int64_t& sub : p.dsub[b]) sub = take(Nm * d * h2);
     p.dqkv[b] = take(Nm * 3 * d * h2);
     p.dh[b] = take(Nm * F * h2);
     p.dq[b] = take(Nt * d * h2);
     p.dkv[b] = take(Ns * 2 * d * h2);
   }
   p.lnpart = take(layernorm_bwd_scratch_floats((int)d) * f4);
-  const int64_t widest = F > 3 * d ? F : 3 * d;
-  p.cspart = take(colsum_scratch_floats((int)widest) * f4);
   p.embscratch = take(embed_bwd_scratch_ints((int)V, (int)(Ns + Nt), (int)d) * (int64_t)sizeof(int32_t));
-  // fp32 partial sums of weight-gradient products cut along the (long) position axis
-  p.wgpart_floats = kWgradPartialFloats;
+  // fp32 partial sums of a layer's weight gradients cut along the (long) position axis: 4 pieces of a decoder layer's, up to 32 of
+  // a small one's
+  const int64_t layer = 2 * F * (d + 1) + 8 * d * (d + 1);
+  p.wgpart_floats = std::max(4 * layer, std::min<int64_t>(32 * layer, 16ll << 20));
   p.wgpart = take(p.wgpart_floats * f4);
   p.total = cur;
   return cur;
@@ -428,13 +428,6 @@ struct Run {
   // dx[N, in] = dy[N, out] W (+ add)
   int dgrad(const half_t* dy, int N, int out, int64_t W, int in, half_t* dx, GemmEpilogue ep = {}) const {
     return launch_gemm(dy, false, out, c->w16 + W, true, in, dx, in, N, in, out, ep, st);
-  }
-  // gW[out, in] = dy^T x
-  int wgrad(const half_t* dy, int N, int out, const half_t* x, int in, int64_t gW) const {
-    GemmEpilogue ep;
-    ep.out_scale = c->gscale;
-    return launch_gemm(dy, true, out, x, true, in, c->g16 + gW, in, out, in, N, ep, st,
-                       c->plan.wgpart_floats ? ws<float>(c->plan.wgpart) : nullptr, c->plan.wgpart_floats, 0);
   }
 };
 
@@ -638,10 +631,9 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
 // backward
 // ================================================================================================
 // Weight gradients (and the bias column sums) are leaves of the backward graph: nothing downstream
-// waits for them.  They are enqueued on a second stream so that they run beside the chain of
-// input-gradient kernels and fill the compute units those leave idle.  Temporaries read by the
-// second stream exist twice; set s is reused two sub-layers later, after the event recorded
-// behind its last reader.
+// waits for them.  A layer's are collected and enqueued as one group on a second stream, where they run beside the
+// next layer's chain of input-gradient kernels and fill the compute units that leaves idle.  Temporaries read by the
+// second stream exist twice; set s is reused two layers later, after the event recorded behind its last reader.
 extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   NMT_REQUIRE(ctx, "nmt_backward: null context");
   nmt_ctx* c = ctx;
@@ -669,7 +661,6 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   // so per-kernel times are those of kernels running alone)
   hipStream_t st = static_cast<hipStream_t>(stream), sd = two_streams ? c->side : st;
   const Run r{c, st};   // input-gradient chain
-  const Run w{c, sd};   // weight gradients
   const bool dropping = c->training && k.dropout > 0.f;
   const float act_scale = (c->training && k.act_dropout > 0.f) ? 1.f / (1.f - k.act_dropout) : 1.f;
   half_t* dO = r.ws<half_t>(p.dO);
@@ -677,75 +668,83 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   const AttnWork wl_ss = attention_work(r.ws<int32_t>(p.wl_ss), Bt, Ns, 0), wl_tt = attention_work(r.ws<int32_t>(p.wl_tt), Bt, Nt, 0),
                  wl_ts = attention_work(r.ws<int32_t>(p.wl_ts), Bt, Nt, Ns);
   float* lnpart = r.ws<float>(p.lnpart);
-  float* cspart = r.ws<float>(p.cspart);  // used on the second stream only
 
-  int set = 0;            // temporaries of the current sub-layer
+  int set = 0, sub_at = 0;  // temporaries of the current layer; its sub-layers so far
   bool used[2] = {false, false};
-  half_t *dy = nullptr, *dym = nullptr, *dqkv = nullptr, *dhid = nullptr, *dq = nullptr, *dkv = nullptr;
-  const half_t* dsub = nullptr;  // gradient at a sub-layer's output
-  auto begin_sublayer = [&]() -> int {
+  half_t *dym = nullptr, *dqkv = nullptr, *dhid = nullptr, *dq = nullptr, *dkv = nullptr;
+  half_t* dy = nullptr;          // gradient at a sub-layer's sum, for the residual connection
+  const half_t* dsub = nullptr;  // gradient at a sub-layer's output (the same without dropout)
+  WgradProduct leaves[kMaxWgrad];
+  int n_leaves = 0;
+  auto begin_layer = [&]() -> int {
     set ^= 1;
-    if (used[set]) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_done[set], 0));
+    sub_at = 0;
+    if (used[set] && two_streams) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_done[set], 0));
     used[set] = true;
-    dy = r.ws<half_t>(p.dy[set]);
-    dym = dropping ? r.ws<half_t>(p.dym[set]) : nullptr;
-    dsub = dropping ? dym : dy;
     dqkv = r.ws<half_t>(p.dqkv[set]);
     dhid = r.ws<half_t>(p.dh[set]);
     dq = r.ws<half_t>(p.dq[set]);
     dkv = r.ws<half_t>(p.dkv[set]);
     return NMT_OK;
   };
+  auto begin_sublayer = [&]() {
+    half_t* sub = r.ws<half_t>(p.dsub[set][sub_at++]);
+    dy = dropping ? r.ws<half_t>(p.dy) : sub;
+    dym = dropping ? sub : nullptr;
+    dsub = sub;
+  };
   auto fork = [&]() -> int {  // the second stream may start on everything enqueued so far
+    if (!two_streams) return NMT_OK;
     NMT_HIP_CHECK(hipEventRecord(c->ev_fork, st));
     NMT_HIP_CHECK(hipStreamWaitEvent(sd, c->ev_fork, 0));
     return NMT_OK;
   };
-  auto end_sublayer = [&]() -> int {
-    NMT_HIP_CHECK(hipEventRecord(c->ev_done[set], sd));
+  // gW[out, in] = dy^T x, and the bias gradient gb[out] = column sums of dy where it has one of its own
+  auto leaf = [&](const half_t* grad, int N, int out, const half_t* x, int in, int64_t gW, int64_t gb = -1) {
+    leaves[n_leaves++] = {grad, x, r.g(gW), gb < 0 ? nullptr : r.g(gb), out, in, in, out, in, N};
+  };
+  // (called when the last gradient that the layer's leaves read has been enqueued)
+  auto flush_leaves = [&]() -> int {
+    NMT_TRY(fork());
+    NMT_TRY(launch_wgrad_group(leaves, n_leaves, c->gscale, r.ws<float>(p.wgpart), p.wgpart_floats, sd));
+    n_leaves = 0;
+    if (two_streams) NMT_HIP_CHECK(hipEventRecord(c->ev_done[set], sd));
     return NMT_OK;
   };
 
   // feed-forward sub-layer: out = LN(x_in + drop(relu(x_in W1^T + b1) W2^T + b2)); dx holds d out on entry, d x_in on exit
   auto ffn_bwd = [&](half_t* dx, int N, bool tgt, const half_t* x_in, const half_t* hact, const half_t* sub, const float* stats,
                      const FfnP& f, const LnP& ln, uint32_t site_res) -> int {
-    NMT_TRY(begin_sublayer());
+    begin_sublayer();
     NMT_TRY(launch_residual_layernorm_bwd(dx, sub, x_in, r.w(ln.g), stats, dy, dym, r.g(ln.g), r.g(ln.b), r.g(f.b2), lnpart, N, d,
                                           r.drop(site_res, tgt, k.dropout), st, c->gscale));
-    NMT_TRY(fork());
-    NMT_TRY(w.wgrad(dsub, N, d, hact, F, f.w2));
+    leaf(dsub, N, d, hact, F, f.w2);
     GemmEpilogue relu_bwd;
     relu_bwd.relu_src = hact;
     relu_bwd.mask_scale = act_scale;
     NMT_TRY(r.dgrad(dsub, N, d, f.w2, F, dhid, relu_bwd));
-    NMT_TRY(fork());
-    NMT_TRY(launch_colsum(dhid, F, w.g(f.b1), cspart, N, F, sd, c->gscale));
-    NMT_TRY(w.wgrad(dhid, N, F, x_in, d, f.w1));
+    leaf(dhid, N, F, x_in, d, f.w1, f.b1);
     GemmEpilogue res;
     res.add = dy;
-    NMT_TRY(r.dgrad(dhid, N, F, f.w1, d, dx, res));
-    return end_sublayer();
+    return r.dgrad(dhid, N, F, f.w1, d, dx, res);
   };
   // self-attention sub-layer (fused q, k, v projection)
   auto self_bwd = [&](half_t* dx, int N, bool tgt, const half_t* x_in, const half_t* qkv, const half_t* o, const float* lse,
                       const half_t* sub, const float* stats, const AttnP& a, const LnP& ln, uint32_t site_res, const int32_t* key_ids,
                       int causal) -> int {
-    NMT_TRY(begin_sublayer());
+    begin_sublayer();
     NMT_TRY(launch_residual_layernorm_bwd(dx, sub, x_in, r.w(ln.g), stats, dy, dym, r.g(ln.g), r.g(ln.b), r.g(a.bo), lnpart, N, d,
                                           r.drop(site_res, tgt, k.dropout), st, c->gscale));
-    NMT_TRY(fork());
-    NMT_TRY(w.wgrad(dsub, N, d, o, d, a.wo));
+    leaf(dsub, N, d, o, d, a.wo);
     NMT_TRY(r.dgrad(dsub, N, d, a.wo, d, dO));
     NMT_TRY(launch_attention_bwd(qkv, 3 * d, qkv + d, 3 * d, qkv + 2 * d, 3 * d, o, d, dO, d, lse, dqkv, 3 * d, dqkv + d, 3 * d,
                                  dqkv + 2 * d, 3 * d, key_ids, k.pad_id, causal, Bt, H, dh, tgt ? maxT : maxS, tgt ? maxT : maxS,
                                  tgt ? tab_tt : tab_ss, N, tgt ? &wl_tt : &wl_ss, st));
-    NMT_TRY(fork());
-    NMT_TRY(launch_colsum(dqkv, 3 * d, w.g(a.bqkv), cspart, N, 3 * d, sd, c->gscale));
-    NMT_TRY(w.wgrad(dqkv, N, 3 * d, x_in, d, a.wqkv));
+    leaf(dqkv, N, 3 * d, x_in, d, a.wqkv, a.bqkv);
+    NMT_TRY(flush_leaves());  // (the self-attention sub-layer is a layer's last)
     GemmEpilogue res;
     res.add = dy;
-    NMT_TRY(r.dgrad(dqkv, N, 3 * d, a.wqkv, d, dx, res));
-    return end_sublayer();
+    return r.dgrad(dqkv, N, 3 * d, a.wqkv, d, dx, res);
   };
 
   // ---- output projection: logits = x E^T; the workspace holds d logits ----
@@ -756,7 +755,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   NMT_TRY(fork());
   GemmEpilogue vocab_ep;
   vocab_ep.out_scale = c->gscale;
-  NMT_TRY(launch_gemm(dlogits, true, V, x_dec, true, d, w.g(c->embed), d, V, d, Nt, vocab_ep, sd));
+  NMT_TRY(launch_gemm(dlogits, true, V, x_dec, true, d, r.g(c->embed), d, V, d, Nt, vocab_ep, sd));
   // (the order of the positions by id, which the embedding gradient at the end needs, depends on the ids alone)
   NMT_TRY(launch_embed_sort(c->src, Ns, c->tgt_in, Nt, d, V, r.ws<int32_t>(p.embscratch), sd));
   if (two_streams) NMT_HIP_CHECK(hipEventRecord(c->ev_embed, sd));
@@ -770,31 +769,27 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     const DecW& W = p.dec[l];
     const int li = k.enc_layers + l;
     const half_t* x_in = l ? r.ws<half_t>(p.dec[l - 1].x3) : r.ws<half_t>(p.y0);
+    NMT_TRY(begin_layer());
     NMT_TRY(ffn_bwd(dx, Nt, true, r.ws<half_t>(W.x2), r.ws<half_t>(W.h), r.ws<half_t>(W.s3), r.ws<float>(W.st3), P.ffn, P.ln3,
                     layer_site(li, kKindFfnRes)));
     // encoder-decoder attention
-    NMT_TRY(begin_sublayer());
+    begin_sublayer();
     NMT_TRY(launch_residual_layernorm_bwd(dx, r.ws<half_t>(W.s2), r.ws<half_t>(W.x1), r.w(P.ln2.g), r.ws<float>(W.st2), dy, dym,
                                           r.g(P.ln2.g), r.g(P.ln2.b), r.g(P.cross.bo), lnpart, Nt, d,
                                           r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st, c->gscale));
-    NMT_TRY(fork());
-    NMT_TRY(w.wgrad(dsub, Nt, d, r.ws<half_t>(W.o2), d, P.cross.wo));
+    leaf(dsub, Nt, d, r.ws<half_t>(W.o2), d, P.cross.wo);
     NMT_TRY(r.dgrad(dsub, Nt, d, P.cross.wo, d, dO));
     const half_t* kv = r.ws<half_t>(W.kv);
     NMT_TRY(launch_attention_bwd(r.ws<half_t>(W.q), d, kv, 2 * d, kv + d, 2 * d, r.ws<half_t>(W.o2), d, dO, d, r.ws<float>(W.lse2), dq, d,
                                  dkv, 2 * d, dkv + d, 2 * d, c->src, k.pad_id, 0, Bt, H, dh, maxT, maxS, tab_ts, Nt, &wl_ts, st));
-    NMT_TRY(fork());
-    NMT_TRY(launch_colsum(dq, d, w.g(P.cross.bq), cspart, Nt, d, sd, c->gscale));
-    NMT_TRY(launch_colsum(dkv, 2 * d, w.g(P.cross.bkv), cspart, Ns, 2 * d, sd, c->gscale));
-    NMT_TRY(w.wgrad(dq, Nt, d, r.ws<half_t>(W.x1), d, P.cross.wq));
-    NMT_TRY(w.wgrad(dkv, Ns, 2 * d, enc_out, d, P.cross.wkv));
+    leaf(dq, Nt, d, r.ws<half_t>(W.x1), d, P.cross.wq, P.cross.bq);
+    leaf(dkv, Ns, 2 * d, enc_out, d, P.cross.wkv, P.cross.bkv);
     GemmEpilogue res;
     res.add = dy;
     NMT_TRY(r.dgrad(dq, Nt, d, P.cross.wq, d, dx, res));
     GemmEpilogue accum;
     accum.add = (l == k.dec_layers - 1) ? nullptr : denc;  // the encoder output feeds every decoder layer
     NMT_TRY(r.dgrad(dkv, Ns, 2 * d, P.cross.wkv, d, denc, accum));
-    NMT_TRY(end_sublayer());
     // masked self-attention
     NMT_TRY(self_bwd(dx, Nt, true, x_in, r.ws<half_t>(W.qkv), r.ws<half_t>(W.o1), r.ws<float>(W.lse1), r.ws<half_t>(W.s1),
                      r.ws<float>(W.st1), P.self, P.ln1, layer_site(li, kKindSelfRes), c->tgt_in, 1));
@@ -806,6 +801,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     const EncP& P = c->enc[l];
     const EncW& W = p.enc[l];
     const half_t* x_in = l ? r.ws<half_t>(p.enc[l - 1].x2) : r.ws<half_t>(p.x0);
+    NMT_TRY(begin_layer());
     NMT_TRY(ffn_bwd(denc, Ns, false, r.ws<half_t>(W.x1), r.ws<half_t>(W.h), r.ws<half_t>(W.s2), r.ws<float>(W.st2), P.ffn, P.ln2,
                     layer_site(l, kKindFfnRes)));
     NMT_TRY(self_bwd(denc, Ns, false, x_in, r.ws<half_t>(W.qkv), r.ws<half_t>(W.o), r.ws<float>(W.lse), r.ws<half_t>(W.s1),
@@ -817,8 +813,10 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   if (two_streams) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_embed, 0));
   NMT_TRY(launch_embed_sum(denc, Ns, r.drop(kSiteEmbSrc, false, k.dropout), dx_dec0, Nt, r.drop(kSiteEmbTgt, true, k.dropout), r.g(c->embed), d,
                            r.ws<int32_t>(p.embscratch), st, c->gscale));
-  NMT_HIP_CHECK(hipEventRecord(c->ev_join, sd));
-  NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_join, 0));
+  if (two_streams) {
+    NMT_HIP_CHECK(hipEventRecord(c->ev_join, sd));
+    NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_join, 0));
+  }
   return NMT_OK;
 }
 
@@ -929,6 +927,18 @@ extern "C" int nmt_op_gemm_splitk(const void* d_A, int32_t a_t, int32_t lda, con
   return launch_gemm(static_cast<const half_t*>(d_A), a_t != 0, lda, static_cast<const half_t*>(d_B), b_t != 0, ldb,
                      static_cast<half_t*>(d_C), ldc, M, N, K, GemmEpilogue{}, static_cast<hipStream_t>(stream), d_partial, partial_floats,
                      splits);
+}
+
+extern "C" int nmt_op_wgrad_group(int32_t n, const nmt_wgrad* products, float out_scale, float* d_partial, int64_t partial_floats,
+                                  int32_t tile, int32_t splits, void* stream) {
+  NMT_REQUIRE(products && n >= 1 && n <= kMaxWgrad, "nmt_op_wgrad_group: %d products outside [1, %d]", n, kMaxWgrad);
+  WgradProduct w[kMaxWgrad];
+  for (int i = 0; i < n; ++i) {
+    const nmt_wgrad& p = products[i];
+    w[i] = {static_cast<const half_t*>(p.d_dy), static_cast<const half_t*>(p.d_x), static_cast<half_t*>(p.d_gw), static_cast<half_t*>(p.d_gb),
+            p.ld_dy, p.ld_x, p.ld_gw, p.out, p.in, p.rows};
+  }
+  return launch_wgrad_group(w, n, out_scale, d_partial, partial_floats, static_cast<hipStream_t>(stream), tile, splits);
 }
 
 extern "C" int nmt_op_attention_fwd(const void* d_Q, int32_t ldq, const void* d_K, int32_t ldk, const void* d_V, int32_t ldv,

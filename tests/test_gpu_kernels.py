@@ -116,6 +116,34 @@ def test_gemm_split_along_k_matches_oracle(M, N, K, splits):
         A.nmt_op_gemm_splitk(dev16(Am.T), 1, M, dev16(Bm.T), 1, N, dC, N + 8, M, N, K, part[: M * N], 2)
 
 
+# one group per tile shape, cut along the positions or not, products of unequal sizes and numbers of positions: ragged tiles, fewer
+# positions than a k-tile or than the splits (a split without positions adds zeros), strided operands, with and without bias gradients
+@pytest.mark.parametrize("tile,splits", [(1, 1), (1, 3), (2, 1), (2, 4), (3, 1), (3, 2), (4, 1), (4, 7), (0, 0)])
+def test_weight_gradient_groups_match_oracle(tile, splits):
+    rng = np.random.default_rng(10 * tile + splits)
+    shapes = [(264, 520, 1003, True), (8, 8, 1, True), (520, 72, 1600, False), (136, 264, 65, True), (72, 136, 1003, False)]
+    products, want, part = [], [], 0
+    for n_out, n_in, rows, bias in shapes:
+        dy, x = f16(rng.normal(size=(rows, n_out)) / math.sqrt(rows)), f16(rng.normal(size=(rows, n_in)))
+        ddy, dx = torch.full((rows, n_out + 8), 9.0, dtype=torch.float16, device=DEV), torch.full((rows, n_in + 16), 9.0, dtype=torch.float16, device=DEV)
+        ddy[:, :n_out], dx[:, :n_in] = dev16(dy), dev16(x)
+        gw = torch.full((n_out, n_in + 8), float("nan"), dtype=torch.float16, device=DEV)
+        gb = torch.full((n_out,), float("nan"), dtype=torch.float16, device=DEV) if bias else None
+        products.append((ddy, n_out + 8, dx, n_in + 16, gw, n_in + 8, gb, n_out, n_in, rows))
+        want.append((dy.T @ x, dy.sum(axis=0)))
+        part += n_out * (n_in + 1)
+    partial = torch.full((max(splits, 1) * part,), float("nan"), dtype=torch.float32, device=DEV)
+    A.nmt_op_wgrad_group(products, 0.5, partial, tile, splits)
+    for (n_out, n_in, rows, bias), (_, _, _, _, gw, _, gb, *_), (w, b) in zip(shapes, products, want):
+        assert_close16(host(gw)[:, :n_in], 0.5 * w, f"weight gradient {n_out}x{n_in}x{rows}")
+        assert torch.isnan(gw[:, n_in:]).all()
+        if bias:
+            assert_close16(host(gb), 0.5 * b, f"bias gradient {n_out}x{rows}")
+    if splits > 1:
+        with pytest.raises(A.NmtError):
+            A.nmt_op_wgrad_group(products, 0.5, partial[:-1], tile, splits)
+
+
 def test_gemm_large_problem_with_a_small_tile_tail_keeps_epilogue_rows():
     """Enough rows for one full round of large tiles plus a remainder, which goes to a second launch
     with small tiles: bias, ReLU and the dropout counters of the remainder must be those of its rows."""
