@@ -218,10 +218,20 @@ int launch_residual_layernorm_fwd(const half_t* sub, const half_t* resid, const 
                                   half_t* out, float* stats, int rows, int d, float eps, const DropDev& drop,
                                   hipStream_t stream);
 int64_t layernorm_bwd_scratch_floats(int d);
+// Partial rows of column sums as a kernel left them: `rows` rows of up to three quantities, and where their totals go.
+struct ColumnSums {
+  const float* partial;
+  int rows;
+  half_t* dst[3];
+};
+constexpr int kMaxColumnSums = 4;
+// The row gradients; the gradients of gamma, beta and the bias are left as partial rows described by `sums`, which
+// launch_layernorm_param_grads adds up (several calls' in one launch).
 int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const half_t* resid, const half_t* gamma,
                                   const float* stats, half_t* dy, half_t* dym, half_t* dgamma, half_t* dbeta,
                                   half_t* dbias, float* partial, int rows, int d, const DropDev& drop,
-                                  hipStream_t stream, float vec_scale = 1.f);  // vec_scale: factor on dgamma, dbeta, dbias
+                                  hipStream_t stream, ColumnSums& sums);
+int launch_layernorm_param_grads(const ColumnSums* sums, int n, int d, float scale, hipStream_t stream);  // scale: factor on all of them
 int launch_embed_fwd(const int32_t* ids, const half_t* E, half_t* x, int rows, int d, int vocab, const DropDev& drop,
                      hipStream_t stream);
 int launch_softmax_xent(half_t* logits, const int32_t* targets, float* row_loss, int rows, int V, int pad_id,

@@ -110,7 +110,7 @@ struct Plan {
   int64_t x0, y0, logits, rowloss;
   std::vector<EncW> enc;
   std::vector<DecW> dec;
-  int64_t dx_dec, dx_enc, dy, dsub[2][3], dO, dqkv[2], dh[2], dq[2], dkv[2], lnpart, embscratch, wgpart, wgpart_floats;
+  int64_t dx_dec, dx_enc, dy, dsub[2][3], dO, dqkv[2], dh[2], dq[2], dkv[2], lnpart[2][3], embscratch, wgpart, wgpart_floats;
   int64_t total;
 };
 
@@ -248,12 +248,12 @@ int64_t plan_workspace(const nmt_ctx* c, const GroupDims& gd, Plan& p) {
   p.dy = take(Nm * d * h2);
   for (int b = 0; b < 2; ++b) {  // two sets: the weight gradients of one layer overlap the next layer
     for (int64_t& sub : p.dsub[b]) sub = take(Nm * d * h2);
+    for (int64_t& part : p.lnpart[b]) part = take(layernorm_bwd_scratch_floats((int)d) * f4);
     p.dqkv[b] = take(Nm * 3 * d * h2);
     p.dh[b] = take(Nm * F * h2);
     p.dq[b] = take(Nt * d * h2);
     p.dkv[b] = take(Ns * 2 * d * h2);
   }
-  p.lnpart = take(layernorm_bwd_scratch_floats((int)d) * f4);
   p.embscratch = take(embed_bwd_scratch_ints((int)V, (int)(Ns + Nt), (int)d) * (int64_t)sizeof(int32_t));
   // fp32 partial sums of a layer's weight gradients cut along the (long) position axis: 4 pieces of a decoder layer's, up to 32 of
   // a small one's
@@ -667,14 +667,15 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   const int4 *tab_ss = r.ws<int4>(p.tab_ss), *tab_tt = r.ws<int4>(p.tab_tt), *tab_ts = r.ws<int4>(p.tab_ts);
   const AttnWork wl_ss = attention_work(r.ws<int32_t>(p.wl_ss), Bt, Ns, 0), wl_tt = attention_work(r.ws<int32_t>(p.wl_tt), Bt, Nt, 0),
                  wl_ts = attention_work(r.ws<int32_t>(p.wl_ts), Bt, Nt, Ns);
-  float* lnpart = r.ws<float>(p.lnpart);
 
   int set = 0, sub_at = 0;  // temporaries of the current layer; its sub-layers so far
   bool used[2] = {false, false};
   half_t *dym = nullptr, *dqkv = nullptr, *dhid = nullptr, *dq = nullptr, *dkv = nullptr;
+  float* lnpart = nullptr;       // partial sums of the sub-layer's LayerNorm gradients
   half_t* dy = nullptr;          // gradient at a sub-layer's sum, for the residual connection
   const half_t* dsub = nullptr;  // gradient at a sub-layer's output (the same without dropout)
   WgradProduct leaves[kMaxWgrad];
+  ColumnSums ln_sums[kMaxColumnSums];
   int n_leaves = 0;
   auto begin_layer = [&]() -> int {
     set ^= 1;
@@ -688,7 +689,8 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     return NMT_OK;
   };
   auto begin_sublayer = [&]() {
-    half_t* sub = r.ws<half_t>(p.dsub[set][sub_at++]);
+    half_t* sub = r.ws<half_t>(p.dsub[set][sub_at]);
+    lnpart = r.ws<float>(p.lnpart[set][sub_at++]);
     dy = dropping ? r.ws<half_t>(p.dy) : sub;
     dym = dropping ? sub : nullptr;
     dsub = sub;
@@ -708,6 +710,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     NMT_TRY(fork());
     NMT_TRY(launch_wgrad_group(leaves, n_leaves, c->gscale, r.ws<float>(p.wgpart), p.wgpart_floats, sd));
     n_leaves = 0;
+    NMT_TRY(launch_layernorm_param_grads(ln_sums, sub_at, d, c->gscale, sd));
     if (two_streams) NMT_HIP_CHECK(hipEventRecord(c->ev_done[set], sd));
     return NMT_OK;
   };
@@ -717,7 +720,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
                      const FfnP& f, const LnP& ln, uint32_t site_res) -> int {
     begin_sublayer();
     NMT_TRY(launch_residual_layernorm_bwd(dx, sub, x_in, r.w(ln.g), stats, dy, dym, r.g(ln.g), r.g(ln.b), r.g(f.b2), lnpart, N, d,
-                                          r.drop(site_res, tgt, k.dropout), st, c->gscale));
+                                          r.drop(site_res, tgt, k.dropout), st, ln_sums[sub_at - 1]));
     leaf(dsub, N, d, hact, F, f.w2);
     GemmEpilogue relu_bwd;
     relu_bwd.relu_src = hact;
@@ -734,7 +737,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
                       int causal) -> int {
     begin_sublayer();
     NMT_TRY(launch_residual_layernorm_bwd(dx, sub, x_in, r.w(ln.g), stats, dy, dym, r.g(ln.g), r.g(ln.b), r.g(a.bo), lnpart, N, d,
-                                          r.drop(site_res, tgt, k.dropout), st, c->gscale));
+                                          r.drop(site_res, tgt, k.dropout), st, ln_sums[sub_at - 1]));
     leaf(dsub, N, d, o, d, a.wo);
     NMT_TRY(r.dgrad(dsub, N, d, a.wo, d, dO));
     NMT_TRY(launch_attention_bwd(qkv, 3 * d, qkv + d, 3 * d, qkv + 2 * d, 3 * d, o, d, dO, d, lse, dqkv, 3 * d, dqkv + d, 3 * d,
@@ -776,7 +779,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     begin_sublayer();
     NMT_TRY(launch_residual_layernorm_bwd(dx, r.ws<half_t>(W.s2), r.ws<half_t>(W.x1), r.w(P.ln2.g), r.ws<float>(W.st2), dy, dym,
                                           r.g(P.ln2.g), r.g(P.ln2.b), r.g(P.cross.bo), lnpart, Nt, d,
-                                          r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st, c->gscale));
+                                          r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st, ln_sums[sub_at - 1]));
     leaf(dsub, Nt, d, r.ws<half_t>(W.o2), d, P.cross.wo);
     NMT_TRY(r.dgrad(dsub, Nt, d, P.cross.wo, d, dO));
     const half_t* kv = r.ws<half_t>(W.kv);
@@ -974,11 +977,13 @@ extern "C" int nmt_op_residual_layernorm_bwd(const void* d_dout, const void* d_s
                                              void* d_dbias, float* d_partial, int32_t rows, int32_t d, const nmt_dropout* drop,
                                              void* stream) {
   NMT_TRY(check_drop(drop, "nmt_op_residual_layernorm_bwd"));
-  return launch_residual_layernorm_bwd(static_cast<const half_t*>(d_dout), static_cast<const half_t*>(d_sub),
-                                       static_cast<const half_t*>(d_resid), static_cast<const half_t*>(d_gamma), d_stats,
-                                       static_cast<half_t*>(d_dy), static_cast<half_t*>(d_dym), static_cast<half_t*>(d_dgamma),
-                                       static_cast<half_t*>(d_dbeta), static_cast<half_t*>(d_dbias), d_partial, rows, d, make_drop(drop),
-                                       static_cast<hipStream_t>(stream));
+  ColumnSums sums;
+  NMT_TRY(launch_residual_layernorm_bwd(static_cast<const half_t*>(d_dout), static_cast<const half_t*>(d_sub),
+                                        static_cast<const half_t*>(d_resid), static_cast<const half_t*>(d_gamma), d_stats,
+                                        static_cast<half_t*>(d_dy), static_cast<half_t*>(d_dym), static_cast<half_t*>(d_dgamma),
+                                        static_cast<half_t*>(d_dbeta), static_cast<half_t*>(d_dbias), d_partial, rows, d, make_drop(drop),
+                                        static_cast<hipStream_t>(stream), sums));
+  return launch_layernorm_param_grads(&sums, 1, d, 1.f, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int nmt_op_embed_fwd(const int32_t* d_ids, const void* d_E, void* d_x, int32_t rows, int32_t d, int32_t vocab,
