@@ -233,7 +233,7 @@ __device__ __forceinline__ void attn_fwd_item(const AttnArgs& a, int bx, int by,
       s[r] = hid ? -INFINITY : s[r] * sc;
       tmax = fmaxf(tmax, s[r]);
     }
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
+    tmax = half_max(tmax);
     const float m_new = fmaxf(m, tmax);
     const float alpha = exp2f(m - m_new);
     m = m_new;
@@ -255,7 +255,7 @@ __device__ __forceinline__ void attn_fwd_item(const AttnArgs& a, int bx, int by,
       for (int s2 = 0; s2 < 2; ++s2) oacc[t] = MFMA(tr_frag<DH>(Vs, PR, 16 * s2 + 4 * g, t, lane), pf[s2], oacc[t]);
     }
   }
-  l += __shfl_xor(l, 32, kWave);
+  l = half_sum(l);
   store_rows<DH>(Vs, oacc, 1.f / l, a.Out + (size_t)se.q0 * a.ldo + h * DH, a.ldo, q0, se.Tq, lane);
   if (!qvalid) return;
   if (g == 0) a.lse[(size_t)h * a.Nq + se.q0 + q] = (m + log2f(l)) * kLn2;
@@ -323,7 +323,7 @@ __global__ void __launch_bounds__(kThreads) attn_bwd_dkv_kernel(const AttnArgs a
     for (int s = 0; s < KS; ++s)
 #pragma unroll
       for (int e = 0; e < 8; ++e) Dq += (float)dof[s][e] * (float)of[s][e];
-    Dq += __shfl_xor(Dq, 32, kWave);
+    Dq = half_sum(Dq);
     wave_sync();  // the previous tile's reads are done
     put_rows<DH>(Qs, lane, qf);
     put_rows<DH>(dOs, lane, dof);
@@ -392,7 +392,7 @@ __global__ void __launch_bounds__(kThreads) attn_bwd_dq_kernel(const AttnArgs a)
   for (int s = 0; s < KS; ++s)
 #pragma unroll
     for (int e = 0; e < 8; ++e) Dq += (float)dof[s][e] * (float)of[s][e];
-  Dq += __shfl_xor(Dq, 32, kWave);
+  Dq = half_sum(Dq);
   const float lse_q = qvalid ? a.lse[(size_t)h * a.Nq + se.q0 + q] * kLog2e : 0.f;
   const float scale = rsqrtf((float)DH), sc = scale * kLog2e;
   floatx16 dQt[DT];
@@ -484,7 +484,7 @@ __device__ __forceinline__ void attn_bwd_fused_item(const AttnArgs& a, int bx, u
       for (int s = 0; s < KS; ++s)
 #pragma unroll
         for (int e = 0; e < 8; ++e) Dq += (float)dof[s][e] * (float)of[s][e];
-      Dq += __shfl_xor(Dq, 32, kWave);
+      Dq = half_sum(Dq);
       put_rows<DH>(Qs + qt * TILE, lane, qf);
       put_rows<DH>(dOs + qt * TILE, lane, dof);
       if (g == 0) {

@@ -62,23 +62,22 @@ __global__ void __launch_bounds__(kThreads) embed_fwd_kernel(const int32_t* __re
 template <int NCH>
 __device__ __forceinline__ void load_presum(float (&y)[NCH][8], const half_t* __restrict__ sub,
                                             const half_t* __restrict__ resid, int row, int d, int lane,
-                                            const DropDev& drop, uint32_t (&bits)[NCH]) {
+                                            const DropDev& drop) {
   const int chunks = d >> 3;
+  half8_t hs[NCH], hr[NCH];  // everything the row needs is requested before anything is used
+  DropRow key = {};
+  if (drop.thr) key = drop_row(drop, (uint32_t)row);
 #pragma unroll
   for (int i = 0; i < NCH; ++i) {
     const int c = lane + kWave * i;
-    bits[i] = 0xFFu;
-    if (c < chunks) {
-      float s[8], r[8];
-      unpack8(ld_half8_nt(sub + (size_t)row * d + c * 8), s);
-      unpack8(ld_half8_nt(resid + (size_t)row * d + c * 8), r);
-      if (drop.thr) bits[i] = drop_keep8(drop, (uint32_t)row, (uint32_t)c);
+    hs[i] = c < chunks ? ld_half8_nt(sub + (size_t)row * d + c * 8) : zero_half8();
+    hr[i] = c < chunks ? ld_half8_nt(resid + (size_t)row * d + c * 8) : zero_half8();
+  }
 #pragma unroll
-      for (int e = 0; e < 8; ++e) y[i][e] = r[e] + (((bits[i] >> e) & 1u) ? s[e] * drop.scale : 0.f);
-    } else {
+  for (int i = 0; i < NCH; ++i) {
+    const uint32_t bits = drop.thr ? drop_keep8(drop, key, (uint32_t)(lane + kWave * i)) : 0xFFu;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) y[i][e] = 0.f;
-    }
+    for (int e = 0; e < 8; ++e) y[i][e] = (float)hr[i][e] + (((bits >> e) & 1u) ? (float)hs[i][e] * drop.scale : 0.f);
   }
 }
 
@@ -92,8 +91,14 @@ __global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(const half_t* __re
   if (row >= rows) return;
   const int chunks = d >> 3;
   float y[NCH][8];
-  uint32_t bits[NCH];
-  load_presum<NCH>(y, sub, resid, row, d, lane, drop, bits);
+  half8_t gam[NCH], bet[NCH];
+#pragma unroll
+  for (int i = 0; i < NCH; ++i) {
+    const int c = lane + kWave * i;
+    gam[i] = c < chunks ? ld_half8(gamma + c * 8) : zero_half8();
+    bet[i] = c < chunks ? ld_half8(beta + c * 8) : zero_half8();
+  }
+  load_presum<NCH>(y, sub, resid, row, d, lane, drop);
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < NCH; ++i)
@@ -112,11 +117,9 @@ __global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(const half_t* __re
   for (int i = 0; i < NCH; ++i) {
     const int c = lane + kWave * i;
     if (c < chunks) {
-      float g[8], b[8], o[8];
-      unpack8(ld_half8(gamma + c * 8), g);
-      unpack8(ld_half8(beta + c * 8), b);
+      float o[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] = (y[i][e] - mean) * rstd * g[e] + b[e];
+      for (int e = 0; e < 8; ++e) o[e] = (y[i][e] - mean) * rstd * (float)gam[i][e] + (float)bet[i][e];
       st_half8_nt(out + (size_t)row * d + c * 8, pack8(o));
     }
   }
@@ -154,6 +157,7 @@ __global__ void __launch_bounds__(kThreads) res_ln_bwd_kernel(const half_t* __re
   for (int row0 = (blockIdx.x * kWavesPerBlock + wave) * kLnRows; row0 < rows; row0 += gridDim.x * kWavesPerBlock * kLnRows) {
     half8_t hs[kLnRows][NCH], hr[kLnRows][NCH], hg[kLnRows][NCH];
     uint32_t bits[kLnRows][NCH];
+    DropRow key[kLnRows] = {};
     float mean[kLnRows], rstd[kLnRows], s1[kLnRows], s2[kLnRows];
 #pragma unroll
     for (int u = 0; u < kLnRows; ++u) {
@@ -168,14 +172,12 @@ __global__ void __launch_bounds__(kThreads) res_ln_bwd_kernel(const half_t* __re
       }
       mean[u] = stats[2 * row];
       rstd[u] = stats[2 * row + 1];
+      if (drop.thr) key[u] = drop_row(drop, (uint32_t)row);
     }
 #pragma unroll
-    for (int u = 0; u < kLnRows; ++u) {
-      const int row = min(row0 + u, rows - 1);
+    for (int u = 0; u < kLnRows; ++u)
 #pragma unroll
-      for (int i = 0; i < NCH; ++i)
-        bits[u][i] = (drop.thr && lane + kWave * i < chunks) ? drop_keep8(drop, (uint32_t)row, (uint32_t)(lane + kWave * i)) : 0xFFu;
-    }
+      for (int i = 0; i < NCH; ++i) bits[u][i] = drop.thr ? drop_keep8(drop, key[u], (uint32_t)(lane + kWave * i)) : 0xFFu;
     // normalised value of element e of chunk i of row u (the pre-normalisation sum is formed in fp32, as in the forward pass)
     auto xhat = [&](int u, int i, int e) {
       const float y = (float)hr[u][i][e] + (((bits[u][i] >> e) & 1u) ? (float)hs[u][i][e] * drop.scale : 0.f);
@@ -203,12 +205,9 @@ __global__ void __launch_bounds__(kThreads) res_ln_bwd_kernel(const half_t* __re
       }
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-#pragma unroll
-      for (int u = 0; u < kLnRows; ++u) {
-        s1[u] += __shfl_xor(s1[u], o, kWave);
-        s2[u] += __shfl_xor(s2[u], o, kWave);
-      }
+    for (int u = 0; u < kLnRows; ++u) {
+      s1[u] = wave_sum(s1[u]);
+      s2[u] = wave_sum(s2[u]);
     }
     // (the widened copies of the first pass are not kept: the inputs are widened again from their fp16 registers)
 #pragma unroll
