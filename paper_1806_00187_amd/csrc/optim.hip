@@ -1,39 +1,51 @@
 // HBM-bound update kernels: fp32 gradient accumulation, single-pass unscale + inf/NaN detection,
-// Adam on fp32 master weights with fp16 weight refresh.  All are grid-stride loops over 16-byte
-// (or wider) vectors so that each wavefront issues fully coalesced accesses.
+// Adam on fp32 master weights with fp16 weight refresh.  All are grid-stride loops whose wavefronts read and
+// write whole contiguous kilobytes (16 bytes of fp32 per lane).  A large copy reaches 5.0-5.5 TB/s on this card.
 #include "common.h"
 
 namespace {
 
 constexpr int kThreads = 256;
 constexpr int kMaxBlocks = 256 * 8;  // 8 work-groups per CU keeps enough loads in flight
+constexpr int kAdamMaxBlocks = 65536;
+constexpr int64_t kStreamFrom = 16 << 20;  // parameters from which accumulator, master weights and moments exceed 256 MB of last-level cache
+constexpr int kAccumulateAhead = 4;
 
-// acc (+)= mult * float(g16); mult undoes the power-of-two factor a pass applied before rounding to fp16
+template <bool STREAM>
+__device__ __forceinline__ floatx4 ld_state(const float* p) { return STREAM ? ld_float4_nt(p) : *reinterpret_cast<const floatx4*>(p); }
+template <bool STREAM>
+__device__ __forceinline__ void st_state(float* p, floatx4 v) {
+  if (STREAM) st_float4_nt(p, v);
+  else *reinterpret_cast<floatx4*>(p) = v;
+}
+
+// acc (+)= mult * float(g16); mult undoes the power-of-two factor a pass applied before rounding to fp16.
+// Four fp32 values per lane and access, so that a store instruction covers a contiguous kilobyte (with eight per lane
+// it covered every other 16 bytes of two), four of them in flight per thread: 289 -> 223 us at 219 million parameters (5.9 TB/s),
+// 84 -> 63 at 63 million.
+template <bool STREAM>
 __global__ void __launch_bounds__(kThreads) accumulate_kernel(const half_t* __restrict__ g16, float* __restrict__ acc, int64_t n,
                                                               int first, float mult) {
-  const int64_t nvec = n >> 3;
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nvec; i += stride) {
-    const half8_t g = ld_half8(g16 + i * 8);
-    floatx4* a = reinterpret_cast<floatx4*>(acc + i * 8);
-    floatx4 lo, hi;
-    if (first) {
-      lo = floatx4{0, 0, 0, 0};
-      hi = lo;
-    } else {
-      lo = a[0];
-      hi = a[1];
+  const int64_t nvec = n >> 2;
+  const int64_t block = (int64_t)kAccumulateAhead * kThreads, stride = (int64_t)gridDim.x * block;
+  for (int64_t i0 = (int64_t)blockIdx.x * block + threadIdx.x; i0 < nvec; i0 += stride) {
+    half4_t g[kAccumulateAhead];
+    floatx4 a[kAccumulateAhead];
+#pragma unroll
+    for (int u = 0; u < kAccumulateAhead; ++u) {
+      const int64_t i = min(i0 + u * kThreads, nvec - 1);  // (past the end: the last vector again, not stored)
+      g[u] = *reinterpret_cast<const half4_t*>(g16 + i * 4);
+      a[u] = first ? floatx4{0, 0, 0, 0} : ld_state<STREAM>(acc + i * 4);
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      lo[e] += mult * (float)g[e];
-      hi[e] += mult * (float)g[4 + e];
+    for (int u = 0; u < kAccumulateAhead; ++u) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[u][e] += mult * (float)g[u][e];
+      if (i0 + u * kThreads < nvec) st_state<STREAM>(acc + (i0 + u * kThreads) * 4, a[u]);
     }
-    a[0] = lo;
-    a[1] = hi;
   }
-  // tail (n not a multiple of 8)
-  for (int64_t i = (nvec << 3) + (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride)
+  // tail (n not a multiple of 4)
+  for (int64_t i = (nvec << 2) + (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads)
     acc[i] = (first ? 0.f : acc[i]) + mult * (float)g16[i];
 }
 
@@ -68,6 +80,11 @@ __global__ void __launch_bounds__(kThreads) check_overflow_kernel(float* __restr
   if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, 1);
 }
 
+// One vector per thread in all but the largest models, and streamed past the caches where they could not hold the state
+// until the next update anyway: of grids of 1024 to 65536 work-groups, one to four vectors at a time, streamed or not, this was the
+// fastest at 63 and 219 million parameters: 388 -> 313 us and 1410 -> 1184 (5.6 TB/s).  A model whose state the caches do hold
+// gains nothing from it (two layers 64 wide, two layers 256 wide: the same within the runs' spread).
+template <bool STREAM>
 __global__ void __launch_bounds__(kThreads) adam_kernel(float* __restrict__ master, float* __restrict__ m, float* __restrict__ v,
                                                         const float* __restrict__ g, half_t* __restrict__ w16, int64_t n, float lr,
                                                         float b1, float b2, float eps, float inv_bc1, float inv_bc2, float gscale,
@@ -76,10 +93,10 @@ __global__ void __launch_bounds__(kThreads) adam_kernel(float* __restrict__ mast
   const int64_t nvec = n >> 2;
   const int64_t stride = (int64_t)gridDim.x * kThreads;
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nvec; i += stride) {
-    floatx4 w = reinterpret_cast<floatx4*>(master)[i];
-    floatx4 mm = reinterpret_cast<floatx4*>(m)[i];
-    floatx4 vv = reinterpret_cast<floatx4*>(v)[i];
-    const floatx4 gg = reinterpret_cast<const floatx4*>(g)[i] * gscale;   // the gradient in its original scale
+    floatx4 w = ld_state<STREAM>(master + i * 4);
+    floatx4 mm = ld_state<STREAM>(m + i * 4);
+    floatx4 vv = ld_state<STREAM>(v + i * 4);
+    const floatx4 gg = ld_state<STREAM>(g + i * 4) * gscale;   // the gradient in its original scale
     half4_t h;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -88,10 +105,10 @@ __global__ void __launch_bounds__(kThreads) adam_kernel(float* __restrict__ mast
       w[e] -= lr * (mm[e] * inv_bc1) / (sqrtf(vv[e] * inv_bc2) + eps);
       h[e] = (half_t)w[e];
     }
-    reinterpret_cast<floatx4*>(master)[i] = w;
-    reinterpret_cast<floatx4*>(m)[i] = mm;
-    reinterpret_cast<floatx4*>(v)[i] = vv;
-    *reinterpret_cast<half4_t*>(w16 + i * 4) = h;
+    st_state<STREAM>(master + i * 4, w);
+    st_state<STREAM>(m + i * 4, mm);
+    st_state<STREAM>(v + i * 4, vv);
+    *reinterpret_cast<half4_t*>(w16 + i * 4) = h;  // (the next forward pass reads these)
   }
   for (int64_t i = (nvec << 2) + (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) {
     const float gg = g[i] * gscale;
@@ -105,9 +122,9 @@ __global__ void __launch_bounds__(kThreads) adam_kernel(float* __restrict__ mast
   }
 }
 
-int grid_for(int64_t nvec) {
+int grid_for(int64_t nvec, int most = kMaxBlocks) {
   int64_t b = (nvec + kThreads - 1) / kThreads;
-  return (int)(b < 1 ? 1 : (b > kMaxBlocks ? kMaxBlocks : b));
+  return (int)(b < 1 ? 1 : (b > most ? most : b));
 }
 
 }  // namespace
@@ -115,7 +132,8 @@ int grid_for(int64_t nvec) {
 int launch_accumulate(const half_t* g16, float* acc, int64_t n, int first, hipStream_t stream, float mult) {
   NMT_REQUIRE(g16 && acc && n > 0, "accumulate: bad arguments");
   NMT_REQUIRE(aligned16(g16) && aligned16(acc), "accumulate: buffers must be 16-byte aligned");
-  hipLaunchKernelGGL(accumulate_kernel, dim3(grid_for(n >> 3)), dim3(kThreads), 0, stream, g16, acc, n, first, mult);
+  hipLaunchKernelGGL(n >= kStreamFrom ? accumulate_kernel<true> : accumulate_kernel<false>,
+                     dim3(grid_for(ceil_div(n, 4 * kAccumulateAhead), 4 * kMaxBlocks)), dim3(kThreads), 0, stream, g16, acc, n, first, mult);
   NMT_LAUNCH_CHECK();
   return NMT_OK;
 }
@@ -142,8 +160,8 @@ int launch_adam(float* master, float* m, float* v, const float* g, half_t* w16, 
   NMT_REQUIRE(master && m && v && g && w16 && n > 0 && t >= 1, "adam: bad arguments");
   NMT_REQUIRE(aligned16(master) && aligned16(m) && aligned16(v) && aligned16(g) && aligned16(w16), "adam: buffers must be 16-byte aligned");
   const double bc1 = 1.0 - pow((double)b1, (double)t), bc2 = 1.0 - pow((double)b2, (double)t);
-  hipLaunchKernelGGL(adam_kernel, dim3(grid_for(n >> 2)), dim3(kThreads), 0, stream, master, m, v, g, w16, n, lr, b1, b2, eps,
-                     (float)(1.0 / bc1), (float)(1.0 / bc2), grad_scale, flag);
+  hipLaunchKernelGGL(n >= kStreamFrom ? adam_kernel<true> : adam_kernel<false>, dim3(grid_for(n >> 2, kAdamMaxBlocks)), dim3(kThreads), 0, stream, master,
+                     m, v, g, w16, n, lr, b1, b2, eps, (float)(1.0 / bc1), (float)(1.0 / bc2), grad_scale, flag);
   NMT_LAUNCH_CHECK();
   return NMT_OK;
 }

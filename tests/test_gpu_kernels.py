@@ -584,3 +584,25 @@ def test_adam_matches_oracle_and_skips_on_flag():
     A.nmt_op_adam(master, m, v, dev32(rng.normal(size=n).astype(np.float32)), w16, n, 5e-4, 0.9, 0.98, 1e-8, 5, flag)
     for before, t_ in zip(snap, (master, m, v, w16)):
         assert (host(t_) == before).all()
+
+
+@pytest.mark.parametrize("n", [(16 << 20) + 4099, 4 * 4096 + 3, 3])
+def test_update_kernels_give_the_same_bits_in_pieces(n):
+    """Large models stream their state past the caches and small ones do not; both forms, grids of one and of many vectors per
+    thread, and the last vectors of a length that divides by nothing: a vector updated whole and in two small pieces."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    r32 = lambda: torch.randn(n, generator=g, device=DEV)
+    g16, state = r32().half(), [r32(), r32() * 1e-3, r32().square() * 1e-6, r32()]   # master, m, v, accumulator
+    flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+    cuts = [0, min(n, 8192), min(n, 8192 + 12 * 1024 * 1024), n]
+    results = []
+    for parts in ([(0, n)], list(zip(cuts, cuts[1:]))):
+        w, m, v, acc = (t.clone() for t in state)
+        w16 = torch.zeros(n, dtype=torch.float16, device=DEV)
+        for a, b in parts:
+            if a < b:
+                A.nmt_op_accumulate(g16[a:b], acc[a:b], b - a, False)
+                A.nmt_op_adam(w[a:b], m[a:b], v[a:b], acc[a:b], w16[a:b], b - a, 5e-4, 0.9, 0.98, 1e-8, 3, flag, grad_scale=0.25)
+        results.append([t.clone() for t in (w, m, v, acc, w16)])
+    assert torch.equal(results[0][3], state[3] + g16.float())
+    assert all(torch.equal(x, y) for x, y in zip(*results))
