@@ -1,10 +1,10 @@
-// Fused masked multi-head attention for gfx950: forward with online softmax, and backward as two
-// kernels (dK/dV: a wavefront owns 32 keys and sweeps the queries; dQ: a wavefront owns 32 queries
-// and sweeps the keys).  Scores never go to memory.  All products run on 32x32x16 fp16 MFMAs.
+// Fused masked multi-head attention for gfx950: forward with online softmax; backward by key tiles for sentences of up to
+// 256 positions (a few wavefronts share a sentence and head), and as two kernels for longer ones (dK/dV: a wavefront
+// owns 32 keys and sweeps the queries; dQ: a wavefront owns 32 queries and sweeps the keys).  Scores never go to
+// memory.  All products run on 32x32x16 fp16 MFMAs.
 //
 // Sentences here are short (tens of positions), so the unit of work is small: ONE WAVEFRONT per
-// (sentence, head, 32-row tile), four heads of a sentence per work-group, and no work-group
-// barrier anywhere.  Operands whose contraction index is contiguous in memory (Q, K, V, dO rows
+// (sentence, head, 32-row tile), and in all kernels but the backward one by key tiles no work-group barrier anywhere.  Operands whose contraction index is contiguous in memory (Q, K, V, dO rows
 // against the head dimension) are loaded from global memory straight into MFMA operand registers,
 // 16 bytes per lane.  An operand that is contracted over its row index (V in P V, K in dS K, Q and
 // dO in dS^T Q and P^T dO) passes through a wavefront-private 32-row LDS tile and comes back through
@@ -30,6 +30,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
+constexpr int kClasses = kAttnClasses;
 
 struct AttnArgs {
   const half_t *Q, *K, *V, *O, *dO;
@@ -42,11 +43,12 @@ struct AttnArgs {
   int Nq;                            // query rows in total: lse is [H, Nq]
   int fused_max;                     // backward: sentences with max(Tq, Tk) <= this are left to the fused kernel
   // work lists over the table (or nullptr: every (sentence, tile) of the grid is looked at)
-  const int32_t* wl_counts;          // [0..3] sentences by tiles of the longer side, [4] longer ones, [5] query tiles
-  const int4* wl_sent;               // [4][B] table entries of the sentences of each class
+  const int32_t* wl_counts;          // [0..kClasses-1] sentences by tiles of the longer side, [kClasses] longer ones, [kClasses + 1] query tiles
+  const int4* wl_sent;               // [kClasses][B] table entries of the sentences of each class
   const int4* wl_qsent;              // per query tile: its sentence's table entry ...
   const int32_t* wl_qtile;           // ... and its tile number
   int vgx, vgy;                      // persistent kernels: the grid of work items their work-groups walk through
+  int cls_lo, cls_hi;                // backward by key tiles: classes (tiles of the longer side) this launch covers
 };
 
 // Rows and lengths of sentence b: from the table when several batches of different shapes are
@@ -114,7 +116,7 @@ __device__ __forceinline__ Item work_item(const AttnArgs& a, int bx, int by, int
   it.tile = by;
   it.live = it.h < a.H;
   if (LIST == 1 && a.wl_qsent) {
-    it.live = it.live && idx < a.wl_counts[5];
+    it.live = it.live && idx < a.wl_counts[kClasses + 1];
     const int4 t = it.live ? a.wl_qsent[idx] : make_int4(0, 0, 0, 0);
     it.tile = it.live ? a.wl_qtile[idx] : 0;
     it.se = Sent{t.x, t.y, t.z, t.w};
@@ -571,18 +573,186 @@ __device__ __forceinline__ void attn_bwd_fused_item(const AttnArgs& a, int bx, u
   for (int qt = 0; qt < NT; ++qt)
     if (qt < nqt) store_rows<DH>(Qs + qt * TILE, dQt[qt], 1.f, a.dQ + (size_t)se.q0 * a.lddq + h * DH, a.lddq, qt * 32, se.Tq, lane);
 }
-// Persistent, as the forward kernel, for sentences of up to 64 positions; the instances for longer ones need
-// every register for one item (the loop form spills) and take one item per work-group.
+// Persistent, as the forward kernel.  (Head size 128: sentences of up to 64 positions.)
 template <int DH, int NT>
 __global__ void __launch_bounds__(kThreads) attn_bwd_fused_kernel(const AttnArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  if constexpr (NT <= 2) {
-    for (int v = blockIdx.x; v < a.vgx; v += gridDim.x) {
-      wave_sync();  // the wavefront's LDS tiles are free again
-      attn_bwd_fused_item<DH, NT>(a, v, smem_raw);
+  for (int v = blockIdx.x; v < a.vgx; v += gridDim.x) {
+    wave_sync();  // the wavefront's LDS tiles are free again
+    attn_bwd_fused_item<DH, NT>(a, v, smem_raw);
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// backward by key tiles: sentences of up to 256 positions, head sizes up to 64.  A (sentence, head) whose longer side takes
+// nt tiles of 32 positions is shared by nt wavefronts, each of which owns one key tile (dK and dV stay in its
+// registers) and brings one query tile of Q and dO to LDS for all of them; a work-group of W wavefronts holds W / nt of
+// them.  Scores are formed once per tile pair.  Two query tiles at a time, the wavefronts leave their dS tiles in LDS, and
+// then share out dQ of those two tiles by column halves, each summed over all keys.  One launch covers all lengths of a
+// batch (longest first, so that the last round is short): what bounds a small batch is the serial chain of tile pairs per
+// wavefront (nt here, nt * nt with one wavefront per sentence and head, whose unrolled code of up to 69 KB also
+// had to be fetched) and the number of launches.  Per pass of 18 attentions, with the instances per length it replaces: fourteen
+// sentences of up to 256 positions, 8 heads: 930 -> 370 us; 130 of 16 to 40: 405 -> 268; 53000 positions, 16 heads: 5.3 -> 4.9 ms
+// (beside the weight gradients).
+// ------------------------------------------------------------------------------------------------
+constexpr int kBwdTiles = 8;  // longest sentence, in tiles
+template <int DH>
+constexpr int block_wave_lds() {
+  return 3 * 32 * (DH + 8) * 2 + 2 * 32 * kDsPitch * 2 + 2 * 32 * 4;  // Q, dO and K tiles, two dS tiles, lse and D
+}
+template <int DH, int W>
+__device__ __forceinline__ void attn_bwd_tiles_item(const AttnArgs& a, int nt, int pair, int pairs, unsigned char* smem) {
+  constexpr int DHP = DH < 32 ? 32 : DH, KS = DH / 16, DT = DHP / 32, PR = DH + 8, LDS = block_wave_lds<DH>();
+  const int lane = threadIdx.x & 63, g = lane >> 5, wave = threadIdx.x >> 6;
+  const int group = wave / nt, j = wave - group * nt, at = pair + group;
+  // the group's (sentence, head); a group past the end, or of another class where there is no list, only keeps the barriers
+  bool live = group < W / nt && at < pairs;
+  Sent se = {0, 0, 0, 0};
+  int h = 0;
+  if (live) {
+    h = at % a.H;
+    if (a.wl_sent) {
+      const int4 t = a.wl_sent[(size_t)(nt - 1) * a.B + at / a.H];
+      se = Sent{t.x, t.y, t.z, t.w};
+    } else {
+      se = sentence(a, at / a.H);
+      live = (max(max(se.Tq, se.Tk), 1) + 31) >> 5 == nt;
     }
-  } else {
-    attn_bwd_fused_item<DH, NT>(a, blockIdx.x, smem_raw);
+  }
+  const int nqt = live ? (se.Tq + 31) >> 5 : 0, nkt = live ? (se.Tk + 31) >> 5 : 0;
+  unsigned char* const mine = smem + wave * LDS;
+  unsigned char* const team = smem + group * nt * LDS;  // the group's first wavefront's
+  auto q_tile = [&](int t) { return reinterpret_cast<half_t*>(team + t * LDS); };
+  auto do_tile = [&](int t) { return q_tile(t) + 32 * PR; };
+  auto k_tile = [&](int t) { return q_tile(t) + 2 * 32 * PR; };
+  auto ds_tile = [&](int t, int u) { return q_tile(t) + 3 * 32 * PR + u * 32 * kDsPitch; };
+  auto row_stats = [&](int t) { return reinterpret_cast<float*>(ds_tile(t, 2)); };  // lse[32], D[32]
+  half_t* const my_k = reinterpret_cast<half_t*>(mine) + 2 * 32 * PR;
+
+  wave_sync();  // (what this wavefront staged for its last item has been stored)
+  if (j < nqt) {
+    half8_t qf[KS], dof[KS], of[KS];
+    load_rows<DH>(a.Q + (size_t)se.q0 * a.ldq + h * DH, a.ldq, j * 32, se.Tq, lane, qf);
+    load_rows<DH>(a.dO + (size_t)se.q0 * a.lddo + h * DH, a.lddo, j * 32, se.Tq, lane, dof);
+    load_rows<DH>(a.O + (size_t)se.q0 * a.ldo + h * DH, a.ldo, j * 32, se.Tq, lane, of);
+    const int q = j * 32 + (lane & 31);
+    const float lse_q = q < se.Tq ? a.lse[(size_t)h * a.Nq + se.q0 + q] * kLog2e : 0.f;
+    float Dq = 0.f;
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) Dq += (float)dof[s][e] * (float)of[s][e];
+    Dq = half_sum(Dq);
+    put_rows<DH>(q_tile(j), lane, qf);
+    put_rows<DH>(do_tile(j), lane, dof);
+    if (g == 0) {
+      row_stats(j)[lane] = lse_q;
+      row_stats(j)[32 + lane] = Dq;
+    }
+  }
+  const int key = j * 32 + (lane & 31);
+  const bool khid = key >= se.Tk || (a.key_ids && a.key_ids[se.k0 + key] == a.pad_id);
+  half8_t kf[KS], vf[KS];
+  floatx16 dKt[DT], dVt[DT];
+#pragma unroll
+  for (int t = 0; t < DT; ++t) dKt[t] = dVt[t] = zero16();
+  if (j < nkt) {
+    load_rows<DH>(a.K + (size_t)se.k0 * a.ldk + h * DH, a.ldk, j * 32, se.Tk, lane, kf);
+    load_rows<DH>(a.V + (size_t)se.k0 * a.ldv + h * DH, a.ldv, j * 32, se.Tk, lane, vf);
+    put_rows<DH>(my_k, lane, kf);
+  }
+  const float scale = rsqrtf((float)DH), sc = scale * kLog2e;
+  __syncthreads();  // Q, dO, K tiles and the row statistics of all groups are in LDS
+#pragma unroll 1
+  for (int q0 = 0; q0 < nt; q0 += 2) {  // (nt is the work-group's class: every wavefront makes the same rounds)
+#pragma unroll 1
+    for (int u = 0; u < 2; ++u) {
+      const int qt = q0 + u;
+      if (j < nkt && qt < nqt && !(a.causal && qt < j)) {  // causal: earlier query tiles precede every key of this tile
+        const half_t *Qs = q_tile(qt), *dOs = do_tile(qt);
+        const float* st = row_stats(qt);
+        floatx16 s = zero16(), dp = zero16();
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const int off = (lane & 31) * PR + ks * 16 + g * 8;
+          s = MFMA(ld_half8(Qs + off), kf[ks], s);
+          dp = MFMA(ld_half8(dOs + off), vf[ks], dp);
+        }
+        half8_t pf[2], dsf[2];
+        half_t* ds = ds_tile(j, u);
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+          const floatx4 l4 = *reinterpret_cast<const floatx4*>(st + 8 * rq + 4 * g);
+          const floatx4 d4 = *reinterpret_cast<const floatx4*>(st + 32 + 8 * rq + 4 * g);
+          half4_t ds4;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int r = 4 * rq + e;
+            const int qq = qt * 32 + 8 * rq + 4 * g + e;
+            const bool hid = khid || qq >= se.Tq || (a.causal && key > qq);
+            const float p = hid ? 0.f : exp2f(s[r] * sc - l4[e]);
+            pf[r >> 3][r & 7] = (half_t)p;
+            ds4[e] = (half_t)(p * (dp[r] - d4[e]) * scale);
+            dsf[r >> 3][r & 7] = ds4[e];
+          }
+          *reinterpret_cast<half4_t*>(ds + (lane & 31) * kDsPitch + 8 * rq + 4 * g) = ds4;  // dS[key][query]
+        }
+#pragma unroll
+        for (int t = 0; t < DT; ++t)
+#pragma unroll
+          for (int s2 = 0; s2 < 2; ++s2) {
+            const int kb = 16 * s2 + 4 * g;
+            dVt[t] = MFMA(tr_frag<DH>(dOs, PR, kb, t, lane), pf[s2], dVt[t]);
+            dKt[t] = MFMA(tr_frag<DH>(Qs, PR, kb, t, lane), dsf[s2], dKt[t]);
+          }
+      }
+    }
+    __syncthreads();  // the two query tiles' dS tiles are complete; their Q tiles have been read for the last time
+    for (int x = j; x < 2 * DT; x += nt) {
+      const int qt = q0 + x / DT, t = x % DT;
+      if (group >= W / nt || qt >= nqt) continue;
+      const int last = a.causal ? min(qt + 1, nkt) : nkt;
+      floatx16 dQ = zero16();
+      for (int kt = 0; kt < last; ++kt) {
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          const half8_t ds = tr_frag<32>(ds_tile(kt, x / DT), kDsPitch, 16 * s2 + 4 * g, 0, lane);  // lane = query, slots = keys
+          dQ = MFMA(tr_frag<DH>(k_tile(kt), PR, 16 * s2 + 4 * g, t, lane), ds, dQ);
+        }
+      }
+      // 32 queries x (up to) 32 columns through the query tile's own place in LDS: whole 64-byte pieces of rows
+      half_t* out = q_tile(qt) + t * 32;
+      constexpr int COLS = DH < 32 ? DH : 32, CH = COLS / 8;
+#pragma unroll
+      for (int rq = 0; rq < COLS / 8; ++rq) {
+        half4_t o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (half_t)dQ[4 * rq + e];
+        *reinterpret_cast<half4_t*>(out + (lane & 31) * PR + 8 * rq + 4 * g) = o;
+      }
+      wave_sync();
+      half_t* dst = a.dQ + (size_t)se.q0 * a.lddq + h * DH + t * 32;
+#pragma unroll
+      for (int it = 0; it < (32 * CH + 63) / 64; ++it) {
+        const int idx = it * 64 + lane, r = idx / CH, c = idx % CH;
+        if (r < 32 && qt * 32 + r < se.Tq) st_half8(dst + (size_t)(qt * 32 + r) * a.lddq + c * 8, ld_half8(out + r * PR + c * 8));
+      }
+    }
+    __syncthreads();  // the dS tiles (and, after the last round, the K tiles) are free
+  }
+  if (j < nkt) {
+    store_rows<DH>(my_k, dKt, 1.f, a.dK + (size_t)se.k0 * a.lddk + h * DH, a.lddk, j * 32, se.Tk, lane);
+    store_rows<DH>(my_k, dVt, 1.f, a.dV + (size_t)se.k0 * a.lddv + h * DH, a.lddv, j * 32, se.Tk, lane);
+  }
+}
+template <int DH, int W>
+__global__ void __launch_bounds__(64 * W) attn_bwd_tiles_kernel(const AttnArgs a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  int v = blockIdx.x;
+  for (int nt = a.cls_hi; nt >= a.cls_lo; --nt) {
+    const int pairs = (a.wl_sent ? a.wl_counts[nt - 1] : a.B) * a.H, per = W / nt, items = (pairs + per - 1) / per;
+    for (; v < items; v += gridDim.x) attn_bwd_tiles_item<DH, W>(a, nt, v * per, pairs, smem_raw);
+    v -= items;
   }
 }
 
@@ -655,7 +825,7 @@ int fwd_launch(const AttnArgs& a0, hipStream_t stream) {
 }
 template <int DH, int NT>
 int fused_launch(const AttnArgs& a, int n_k_rows, hipStream_t stream) {
-  constexpr int kWaves = NT == 1 ? 4 : (NT == 2 ? 2 : 1);   // wavefronts (heads) per work-group: bounded by LDS
+  constexpr int kWaves = NT == 1 ? 4 : 2;   // wavefronts (heads) per work-group: bounded by LDS
   const size_t smem = (size_t)kWaves * fused_wave_lds<DH, NT>();
   if (int rc = allow_big_lds(attn_bwd_fused_kernel<DH, NT>, smem)) return rc;
   const int64_t n = a.wl_sent ? class_bound(a.B, a.Nq, n_k_rows, NT - 1) : a.B;
@@ -665,13 +835,34 @@ int fused_launch(const AttnArgs& a, int n_k_rows, hipStream_t stream) {
   b.vgy = 1;
   static std::atomic<int> resident_once{0};
   int resident = resident_once.load(std::memory_order_relaxed);
-  if (NT <= 2 && !resident) {
+  if (!resident) {
     if (int rc = resident_blocks(attn_bwd_fused_kernel<DH, NT>, 64 * kWaves, smem, &resident)) return rc;
     resident_once.store(resident, std::memory_order_relaxed);
   }
-  // (the instances for longer sentences, and everything with the persistent form switched off: one item per work-group)
-  const int grid = (NT > 2 || b.vgx < resident || !tuning().attn_persist) ? b.vgx : resident;
+  const int grid = (b.vgx < resident || !tuning().attn_persist) ? b.vgx : resident;  // (not persistent: one item per work-group)
   hipLaunchKernelGGL((attn_bwd_fused_kernel<DH, NT>), dim3((unsigned)grid), dim3(64 * kWaves), smem, stream, b);
+  NMT_LAUNCH_CHECK();
+  return NMT_OK;
+}
+// One launch over the classes lo..hi (tiles of the longer side); W wavefronts per work-group, at least hi.
+template <int DH, int W>
+int tiles_launch(const AttnArgs& a0, int lo, int hi, int n_k_rows, hipStream_t stream) {
+  AttnArgs a = a0;
+  a.cls_lo = lo;
+  a.cls_hi = hi;
+  const size_t smem = (size_t)W * block_wave_lds<DH>();
+  if (int rc = allow_big_lds(attn_bwd_tiles_kernel<DH, W>, smem)) return rc;
+  int64_t most = 0;  // work items at most
+  for (int nt = lo; nt <= hi; ++nt) most += ((a.wl_sent ? class_bound(a.B, a.Nq, n_k_rows, nt - 1) : a.B) * a.H + W / nt - 1) / (W / nt);
+  NMT_REQUIRE(most < (1ll << 31), "attention_bwd: too many work items");
+  static std::atomic<int> resident_once{0};
+  int resident = resident_once.load(std::memory_order_relaxed);
+  if (!resident) {
+    if (int rc = resident_blocks(attn_bwd_tiles_kernel<DH, W>, 64 * W, smem, &resident)) return rc;
+    resident_once.store(resident, std::memory_order_relaxed);
+  }
+  const int64_t grid = (most < resident || !tuning().attn_persist) ? most : resident;
+  hipLaunchKernelGGL((attn_bwd_tiles_kernel<DH, W>), dim3((unsigned)grid), dim3(64 * W), smem, stream, a);
   NMT_LAUNCH_CHECK();
   return NMT_OK;
 }
@@ -679,20 +870,21 @@ template <int DH>
 int bwd_launch(const AttnArgs& a0, int n_k_rows, hipStream_t stream) {
   AttnArgs a = a0;
   const int tmax = a.Tq > a.Tk ? a.Tq : a.Tk, nt_max = ceil_div(tmax, 32);
-  // sentences of up to 128 positions on both sides (64 for the largest head size, whose accumulators would not
-  // fit the register file): everything in one kernel, one wavefront per (sentence, head).  One instance per
-  // number of 32-position tiles; without a table all sentences have the same lengths and need just one.
-  a.fused_max = DH <= 64 ? 128 : 64;
-  auto wanted = [&](int nt) { return nt <= nt_max && (a.tab || nt == nt_max); };
-  if (wanted(1))
-    if (int rc = fused_launch<DH, 1>(a, n_k_rows, stream)) return rc;
-  if (wanted(2))
-    if (int rc = fused_launch<DH, 2>(a, n_k_rows, stream)) return rc;
   if constexpr (DH <= 64) {
-    if (wanted(3))
-      if (int rc = fused_launch<DH, 3>(a, n_k_rows, stream)) return rc;
-    if (wanted(4))
-      if (int rc = fused_launch<DH, 4>(a, n_k_rows, stream)) return rc;
+    // sentences of up to 256 positions on both sides; without a table all sentences have the same lengths
+    a.fused_max = 32 * kBwdTiles;
+    const int hi = nt_max < kBwdTiles ? nt_max : kBwdTiles, lo = a.tab ? 1 : hi;
+    if (a.tab || nt_max <= kBwdTiles) {
+      if (int rc = hi <= 4 ? tiles_launch<DH, 4>(a, lo, hi, n_k_rows, stream) : tiles_launch<DH, 8>(a, lo, hi, n_k_rows, stream)) return rc;
+    }
+  } else {
+    // sentences of up to 64 positions on both sides: everything in one kernel, one wavefront per (sentence, head).  One
+    // instance per number of 32-position tiles; without a table all sentences have the same lengths and need just one.
+    a.fused_max = 64;
+    if (a.tab || nt_max == 1)
+      if (int rc = fused_launch<DH, 1>(a, n_k_rows, stream)) return rc;
+    if (nt_max >= 2 && (a.tab || nt_max == 2))
+      if (int rc = fused_launch<DH, 2>(a, n_k_rows, stream)) return rc;
   }
   if (tmax <= a.fused_max) return NMT_OK;
   // longer ones: a wavefront per 32 queries for dQ, a wavefront per 32 keys for dK and dV
@@ -768,67 +960,73 @@ int launch_attention_bwd(const half_t* Q, int ldq, const half_t* K, int ldk, con
 // ------------------------------------------------------------------------------------------------
 // Work lists of one attention kind over a sentence table.  One block; thread t takes a contiguous run of
 // sentences, so every list is in sentence order (and so the same from run to run).
-// storage (int32 words): [0..7] counts, then [4][n_sent] int4 table entries by class, then bound_q int4
+// storage (int32 words): [0..15] counts, then [kClasses][n_sent] int4 table entries by class, then bound_q int4
 // table entries and bound_q tile numbers of the query tiles.
 // ------------------------------------------------------------------------------------------------
 namespace {
 __global__ void __launch_bounds__(1024) attn_worklists_kernel(const int4* __restrict__ tab, int n_sent, int bound_q,
                                                               int32_t* __restrict__ st) {
-  __shared__ int sh[6][1024];
+  constexpr int kLists = kClasses + 2;
+  __shared__ int sh[kLists][1024];
   const int t = threadIdx.x, per = (n_sent + 1023) / 1024;
   const int lo = min(n_sent, t * per), hi = min(n_sent, lo + per);
-  int cnt[6] = {0, 0, 0, 0, 0, 0};
+  int cnt[kLists] = {};
   for (int i = lo; i < hi; ++i) {
     const int4 e = tab[i];
     const int nt = max(1, (max(e.z, e.w) + 31) >> 5);
-    ++cnt[nt <= 4 ? nt - 1 : 4];
-    cnt[5] += (e.z + 31) >> 5;
+    const int cls = nt <= kClasses ? nt - 1 : kClasses;
+#pragma unroll
+    for (int c = 0; c <= kClasses; ++c) cnt[c] += c == cls;
+    cnt[kClasses + 1] += (e.z + 31) >> 5;
   }
 #pragma unroll
-  for (int c = 0; c < 6; ++c) sh[c][t] = cnt[c];
+  for (int c = 0; c < kLists; ++c) sh[c][t] = cnt[c];
   __syncthreads();
   for (int o = 1; o < 1024; o <<= 1) {
-    int v[6];
+    int v[kLists];
 #pragma unroll
-    for (int c = 0; c < 6; ++c) v[c] = t >= o ? sh[c][t - o] : 0;
+    for (int c = 0; c < kLists; ++c) v[c] = t >= o ? sh[c][t - o] : 0;
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < 6; ++c) sh[c][t] += v[c];
+    for (int c = 0; c < kLists; ++c) sh[c][t] += v[c];
     __syncthreads();
   }
-  int at[6];
+  int at[kLists];
 #pragma unroll
-  for (int c = 0; c < 6; ++c) at[c] = sh[c][t] - cnt[c];
-  int4* by_tiles = reinterpret_cast<int4*>(st + 8);
-  int4* qsent = by_tiles + 4 * (size_t)n_sent;
+  for (int c = 0; c < kLists; ++c) at[c] = sh[c][t] - cnt[c];
+  int4* by_tiles = reinterpret_cast<int4*>(st + 16);
+  int4* qsent = by_tiles + kClasses * (size_t)n_sent;
   int32_t* qtile = reinterpret_cast<int32_t*>(qsent + bound_q);
   for (int i = lo; i < hi; ++i) {
     const int4 e = tab[i];
     const int nt = max(1, (max(e.z, e.w) + 31) >> 5);
-    if (nt <= 4) by_tiles[(size_t)(nt - 1) * n_sent + at[nt - 1]++] = e;
-    for (int q = 0; q < (e.z + 31) >> 5; ++q, ++at[5])
-      if (at[5] < bound_q) {
-        qsent[at[5]] = e;
-        qtile[at[5]] = q;
+#pragma unroll
+    for (int c = 0; c < kClasses; ++c)
+      if (nt - 1 == c) by_tiles[(size_t)c * n_sent + at[c]++] = e;
+    int& aq = at[kClasses + 1];
+    for (int q = 0; q < (e.z + 31) >> 5; ++q, ++aq)
+      if (aq < bound_q) {
+        qsent[aq] = e;
+        qtile[aq] = q;
       }
   }
   if (t == 1023) {
 #pragma unroll
-    for (int c = 0; c < 5; ++c) st[c] = sh[c][1023];
-    st[5] = min(sh[5][1023], bound_q);
+    for (int c = 0; c <= kClasses; ++c) st[c] = sh[c][1023];
+    st[kClasses + 1] = min(sh[kClasses + 1][1023], bound_q);
   }
 }
 }  // namespace
 
 int64_t attention_worklist_ints(int n_sent, int n_q_rows) {
-  return 8 + 16 * (int64_t)n_sent + 5 * qtile_capacity(n_sent, n_q_rows);
+  return 16 + 4 * kClasses * (int64_t)n_sent + 5 * qtile_capacity(n_sent, n_q_rows);
 }
 
 AttnWork attention_work(const int32_t* storage, int n_sent, int n_q_rows, int n_k_rows) {
   AttnWork w;
   w.counts = storage;
-  w.by_tiles = reinterpret_cast<const int4*>(storage + 8);
-  w.qsent = w.by_tiles + 4 * (size_t)n_sent;
+  w.by_tiles = reinterpret_cast<const int4*>(storage + 16);
+  w.qsent = w.by_tiles + kClasses * (size_t)n_sent;
   w.qtile = reinterpret_cast<const int32_t*>(w.qsent + qtile_capacity(n_sent, n_q_rows));
   w.n_k_rows = n_k_rows;
   return w;

@@ -212,10 +212,11 @@ int gemm_timing_read(double* ms, int64_t* products, double* flops);
 
 // Work lists of one attention kind over a sentence table, made on the device (launch_attention_worklists)
 // so that the attention kernels start no work-group for a (sentence, tile) that does not exist:
-// counts[c], c = 0..3: sentences whose longer side takes c + 1 tiles of 32 positions, [4]: longer ones,
-// [5]: query tiles; by_tiles [4][n_sent]: the table entries of the sentences of each class; qsent / qtile:
+// counts[c], c = 0..kAttnClasses-1: sentences whose longer side takes c + 1 tiles of 32 positions, [kAttnClasses]: longer ones,
+// [kAttnClasses + 1]: query tiles; by_tiles [kAttnClasses][n_sent]: the table entries of the sentences of each class; qsent / qtile:
 // per query tile its sentence's table entry and its tile number (entries are copies, so that a work
 // item needs one dependent load).
+constexpr int kAttnClasses = 8;
 struct AttnWork {
   const int32_t* counts = nullptr;
   const int4* by_tiles = nullptr;

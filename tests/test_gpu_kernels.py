@@ -376,6 +376,13 @@ def test_attention_forward_and_backward_match_oracle(B, H, dh, Tq, Tk, causal):
 
 
 # ---- fused residual + dropout + LayerNorm -----------------------------------------------------------
+# five to eight 32-position tiles on one side or both, and one position more than the tile form takes
+@pytest.mark.parametrize("B,H,dh,Tq,Tk,causal", [(1, 3, 64, 130, 160, 0), (2, 3, 64, 192, 192, 1), (1, 2, 32, 224, 40, 0), (1, 5, 64, 33, 225, 0),
+                                                 (1, 2, 64, 256, 256, 1), (1, 2, 16, 256, 250, 0), (1, 2, 64, 257, 257, 1), (1, 2, 16, 161, 161, 1)])
+def test_attention_of_long_sentences_matches_oracle(B, H, dh, Tq, Tk, causal):
+    test_attention_forward_and_backward_match_oracle(B, H, dh, Tq, Tk, causal)
+
+
 @pytest.mark.parametrize("rows,n_pos,d,p", [(48, 16, 64, 0.1), (99, 33, 1024, 0.3), (70, 35, 512, 0.0), (26, 13, 2048, 0.2),
                                             (10, 5, 200, 0.5)])
 def test_residual_layernorm_forward_and_backward_match_oracle(rows, n_pos, d, p):

@@ -435,6 +435,38 @@ def test_packed_sentences_without_padding_match_the_oracle_and_the_padded_pass()
         sess.close()
 
 
+@pytest.mark.parametrize("heads,shapes", [
+    (2, [(1, 290, 270), (1, 256, 250), (2, 225, 200), (1, 192, 161), (2, 160, 130), (1, 97, 128), (2, 60, 90), (3, 20, 31)]),   # head size 64
+    (4, [(1, 256, 225), (2, 130, 193), (3, 70, 65), (2, 33, 8)])])                                                             # 32
+def test_packed_pass_over_all_attention_tile_counts_matches_the_oracle(heads, shapes):
+    """Sentences of one to eight 32-position tiles on the longer side in one launch, and longer ones, with head sizes 64 and 32:
+    groups of wavefronts of every size, source and target of different tile counts; then the same pass without the work lists."""
+    model = dict(enc_layers=1, dec_layers=1, d_model=128, n_heads=heads, d_ff=128, vocab=264, dropout=0.0)
+    weights = I.init_weights(seed=31, perturb=0.05, **model)
+    batches = [I.tiny_batch(seed=700 + i, B=B, S=S, T=T, vocab=model["vocab"], short_rows=0, short_by=0) for i, (B, S, T) in enumerate(shapes)]
+    uids = [np.arange(50 * i, 50 * i + b["src"].shape[0], dtype=np.uint32) for i, b in enumerate(batches)]
+    batches = [dict(b, sent_uid=uids[i]) for i, b in enumerate(batches)]
+    P16 = {k: v.astype(np.float64) for k, v in weights.items()}
+    sess = Session(model, weights, max_sentences=32, max_len=320)
+    try:
+        (pk,) = sess.pack(batches)
+        sess.forward_loss(pk, 32.0, 1)
+        sess.backward()
+        lists = sess.g16.clone()
+        _pass_parity(sess, model, P16, _oracle_cfg(model), batches, uids, 32.0, 1, f"packed pass, one to ten tiles, {heads} heads: g16", packed=True)
+        try:
+            A.nmt_tuning("worklists", 0)
+            A.nmt_tuning("attn_persist", 0)
+            sess.forward_loss(pk, 32.0, 1)
+            sess.backward()
+            torch.cuda.synchronize()
+        finally:
+            A.nmt_tuning("defaults")
+        assert torch.equal(sess.g16.view(torch.int16), lists.view(torch.int16))
+    finally:
+        sess.close()
+
+
 def test_packed_pass_with_every_sentence_length_class_matches_the_oracle():
     """Sentences of 3 to 150 positions in one packed pass: the attention kernels take them from per-class
     work lists (one to four 32-position tiles on the longer side, and longer ones), all of which occur here."""
