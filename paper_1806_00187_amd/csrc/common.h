@@ -226,7 +226,8 @@ struct AttnWork {
 };
 int64_t attention_worklist_ints(int n_sent, int n_q_rows);  // int32 words of storage behind one AttnWork (16-byte aligned)
 AttnWork attention_work(const int32_t* storage, int n_sent, int n_q_rows, int n_k_rows);
-int launch_attention_worklists(const int4* tab, int n_sent, int n_q_rows, int32_t* storage, hipStream_t stream);
+// The lists of up to three tables of n_sent sentences each, in one launch.
+int launch_attention_worklists(const int4* const* tabs, const int* n_q_rows, int32_t* const* storage, int n, int n_sent, hipStream_t stream);
 
 int launch_attention_fwd(const half_t* Q, int ldq, const half_t* K, int ldk, const half_t* V, int ldv, half_t* O,
                          int ldo, float* lse, const int32_t* key_ids, int pad_id, int causal, int B, int H,

@@ -1253,8 +1253,8 @@ double group_us(int tile, const WgradProduct* p, int n, int splits, int cus, dou
 }
 // The tile and the number of k splits of a group.  A group runs beside the next layer's chain of input gradients, so
 // what counts is the compute-unit time it takes from that chain; its own latency counts too (the last group of a pass has
-// only the embedding kernels beside it, and with one stream there is nothing).  Weights of 0 to 1 for it measured the same
-// updates within 1 %; 10 cost the packed ones 3 %, because small tiles then win and take more compute-unit time.
+// only the embedding kernels beside it, and with one stream there is nothing).  Weights of 0 to 4 for it measured the
+// same updates within 1 to 2 %, this one at the lower end throughout.
 constexpr double kGroupLatencyWeight = 0.5;
 void choose_group(const WgradProduct* p, int n, int64_t most, int cus, int& tile, int& splits) {
   int shortest = p[0].K, best_tile = tile ? tile : kGroup256, best_splits = splits ? splits : 1;

@@ -141,7 +141,7 @@ struct nmt_ctx {
   Plan plan;
   // second stream for the weight-gradient kernels of the backward pass (created on first use)
   hipStream_t side = nullptr;
-  hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_embed = nullptr, ev_done[2] = {nullptr, nullptr};
+  hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_embed = nullptr, ev_kv = nullptr, ev_denc = nullptr, ev_done[2] = {nullptr, nullptr};
 };
 
 namespace {
@@ -344,13 +344,8 @@ extern "C" void nmt_destroy(nmt_ctx* ctx) {
     (void)hipStreamSynchronize(ctx->side);
     (void)hipStreamDestroy(ctx->side);
   }
-  if (ctx->ev_fork) {
-    (void)hipEventDestroy(ctx->ev_fork);
-    (void)hipEventDestroy(ctx->ev_join);
-    (void)hipEventDestroy(ctx->ev_embed);
-    (void)hipEventDestroy(ctx->ev_done[0]);
-    (void)hipEventDestroy(ctx->ev_done[1]);
-  }
+  for (hipEvent_t e : {ctx->ev_fork, ctx->ev_join, ctx->ev_embed, ctx->ev_kv, ctx->ev_denc, ctx->ev_done[0], ctx->ev_done[1]})
+    if (e) (void)hipEventDestroy(e);
   delete ctx;
 }
 extern "C" int64_t nmt_param_count(const nmt_ctx* ctx) { return ctx ? ctx->P : -1; }
@@ -405,6 +400,32 @@ extern "C" int nmt_bind(nmt_ctx* ctx, void* d_w16, void* d_g16, float* d_master3
 // forward + loss
 // ================================================================================================
 namespace {
+
+// The second stream and the events that order the two.  (They come into being when they are first needed: a stream that exists
+// takes a place on one of the process's few hardware queues even if nothing is ever enqueued on it.)
+int ensure_second_stream(nmt_ctx* c) {
+  if (!c->ev_fork) {
+    hipEvent_t* const events[] = {&c->ev_join, &c->ev_embed, &c->ev_kv, &c->ev_denc, &c->ev_done[0], &c->ev_done[1], &c->ev_fork};
+    for (hipEvent_t* e : events)
+      if (!*e) NMT_HIP_CHECK(hipEventCreateWithFlags(e, hipEventDisableTiming));
+  }
+  if (!c->side) NMT_HIP_CHECK(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
+  return NMT_OK;
+}
+// Whether the backward pass (and the products below) use the second stream.  Not for a pass so small that a layer's weight gradients
+// take a few us: the events cost the host about as much as a launch each, and such a pass is bound by the host
+// (two layers, 64 wide, 133 positions, 13 MFLOP a layer: 660 us with two streams, 568 with one; 256 wide, 1500
+// positions, 2.4 GFLOP a layer: 1390 and 1430).
+bool use_second_stream(const nmt_ctx* c) {
+  const double layer = 4.0 * c->cfg.d_model * c->cfg.d_model + 2.0 * c->cfg.d_model * c->cfg.d_ff;
+  return !tuning().one_stream && 2.0 * layer * (c->Ns > c->Nt ? c->Ns : c->Nt) >= 0.25e9;
+}
+// The decoder layers' products over the encoder output (keys and values, and their gradient back to it) depend on nothing
+// in the decoder's chain but its own layer's end.  Where one of them does not fill the chip they run on the second stream beside the
+// chain; a product that does would only take the chain's compute units.
+bool encoder_products_beside(const nmt_ctx* c) {
+  return use_second_stream(c) && (int64_t)ceil_div(c->Ns, 256) * ceil_div(2 * c->cfg.d_model, 256) < device_info().cus;
+}
 
 struct Run {
   nmt_ctx* c;
@@ -555,9 +576,12 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
     NMT_TRY(launch_build_tables(sl, Bt, tsrc.uid, r.ws<uint2>(p.rk_src), r.ws<uint2>(p.rk_tgt), r.ws<int4>(p.tab_ss),
                                 r.ws<int4>(p.tab_tt), r.ws<int4>(p.tab_ts), st));
   }
-  NMT_TRY(launch_attention_worklists(tab_ss, Bt, Ns, r.ws<int32_t>(p.wl_ss), st));
-  NMT_TRY(launch_attention_worklists(tab_tt, Bt, Nt, r.ws<int32_t>(p.wl_tt), st));
-  NMT_TRY(launch_attention_worklists(tab_ts, Bt, Nt, r.ws<int32_t>(p.wl_ts), st));
+  {
+    const int4* tabs[3] = {tab_ss, tab_tt, tab_ts};
+    const int q_rows[3] = {Ns, Nt, Nt};
+    int32_t* lists[3] = {r.ws<int32_t>(p.wl_ss), r.ws<int32_t>(p.wl_tt), r.ws<int32_t>(p.wl_ts)};
+    NMT_TRY(launch_attention_worklists(tabs, q_rows, lists, 3, Bt, st));
+  }
   const AttnWork wl_ss = attention_work(r.ws<int32_t>(p.wl_ss), Bt, Ns, 0), wl_tt = attention_work(r.ws<int32_t>(p.wl_tt), Bt, Nt, 0),
                  wl_ts = attention_work(r.ws<int32_t>(p.wl_ts), Bt, Nt, Ns);
 
@@ -585,6 +609,23 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
   }
   const half_t* enc_out = x;
 
+  // ---- keys and values of the encoder-decoder attentions: beside the decoder's chain where they leave it room ----
+  auto project_kv = [&](const Run& on, int l) {
+    return on.linear(enc_out, Ns, d, c->dec[l].cross.wkv, c->dec[l].cross.bkv, 2 * d, r.ws<half_t>(p.dec[l].kv));
+  };
+  const bool beside = encoder_products_beside(c);
+  if (beside) {
+    NMT_TRY(ensure_second_stream(c));
+    const Run side{c, c->side};
+    NMT_HIP_CHECK(hipEventRecord(c->ev_fork, st));
+    NMT_HIP_CHECK(hipStreamWaitEvent(c->side, c->ev_fork, 0));
+    for (int l = 0; l < k.dec_layers; ++l) {
+      NMT_TRY(project_kv(side, l));
+      if (l == 0) NMT_HIP_CHECK(hipEventRecord(c->ev_kv, c->side));
+    }
+    if (k.dec_layers > 1) NMT_HIP_CHECK(hipEventRecord(c->ev_join, c->side));
+  }
+
   // ---- decoder ----
   half_t* y = r.ws<half_t>(p.y0);
   NMT_TRY(launch_embed_fwd(d_tgt_in, r.w(c->embed), y, Nt, d, V, r.drop(kSiteEmbTgt, true, k.dropout), st));
@@ -601,7 +642,8 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
                                           Nt, d, k.ln_eps, r.drop(layer_site(li, kKindSelfRes), true, k.dropout), st));
     half_t* kv = r.ws<half_t>(W.kv);
     NMT_TRY(r.linear(r.ws<half_t>(W.x1), Nt, d, P.cross.wq, P.cross.bq, d, r.ws<half_t>(W.q)));
-    NMT_TRY(r.linear(enc_out, Ns, d, P.cross.wkv, P.cross.bkv, 2 * d, kv));
+    if (!beside) NMT_TRY(project_kv(r, l));
+    else if (l < 2) NMT_HIP_CHECK(hipStreamWaitEvent(st, l ? c->ev_join : c->ev_kv, 0));
     NMT_TRY(launch_attention_fwd(r.ws<half_t>(W.q), d, kv, 2 * d, kv + d, 2 * d, r.ws<half_t>(W.o2), d, r.ws<float>(W.lse2), d_src,
                                  k.pad_id, 0, Bt, H, dh, maxT, maxS, tab_ts, Nt, &wl_ts, st));
     NMT_TRY(r.linear(r.ws<half_t>(W.o2), Nt, d, P.cross.wo, P.cross.bo, d, r.ws<half_t>(W.s2)));
@@ -642,17 +684,8 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     return NMT_ESTATE;
   }
   c->have_fwd = false;
-  const bool two_streams = !tuning().one_stream;
-  if (!c->ev_fork) {
-    NMT_HIP_CHECK(hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
-    NMT_HIP_CHECK(hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming));
-    NMT_HIP_CHECK(hipEventCreateWithFlags(&c->ev_embed, hipEventDisableTiming));
-    NMT_HIP_CHECK(hipEventCreateWithFlags(&c->ev_done[0], hipEventDisableTiming));
-    NMT_HIP_CHECK(hipEventCreateWithFlags(&c->ev_done[1], hipEventDisableTiming));
-  }
-  // (the second stream comes into being when it is first needed: a stream that exists takes a place on one of the
-  //  process's few hardware queues even if nothing is ever enqueued on it)
-  if (two_streams && !c->side) NMT_HIP_CHECK(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
+  const bool two_streams = use_second_stream(c);
+  if (two_streams) NMT_TRY(ensure_second_stream(c));
   const nmt_config& k = c->cfg;
   const int Bt = c->Bt, Ns = c->Ns, Nt = c->Nt, maxS = c->maxS, maxT = c->maxT;
   const int d = k.d_model, F = k.d_ff, V = k.vocab, H = k.n_heads, dh = d / H;
@@ -661,6 +694,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   // so per-kernel times are those of kernels running alone)
   hipStream_t st = static_cast<hipStream_t>(stream), sd = two_streams ? c->side : st;
   const Run r{c, st};   // input-gradient chain
+  const Run side{c, sd};
   const bool dropping = c->training && k.dropout > 0.f;
   const float act_scale = (c->training && k.act_dropout > 0.f) ? 1.f / (1.f - k.act_dropout) : 1.f;
   half_t* dO = r.ws<half_t>(p.dO);
@@ -765,6 +799,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   NMT_TRY(launch_gemm(dlogits, false, V, r.w(c->embed), true, d, dx, d, Nt, d, V, GemmEpilogue{}, st));
 
   // ---- decoder, top to bottom ----
+  const bool beside = encoder_products_beside(c);
   half_t* denc = r.ws<half_t>(p.dx_enc);
   const half_t* enc_out = k.enc_layers ? r.ws<half_t>(p.enc[k.enc_layers - 1].x2) : r.ws<half_t>(p.x0);
   for (int l = k.dec_layers - 1; l >= 0; --l) {
@@ -792,12 +827,19 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     NMT_TRY(r.dgrad(dq, Nt, d, P.cross.wq, d, dx, res));
     GemmEpilogue accum;
     accum.add = (l == k.dec_layers - 1) ? nullptr : denc;  // the encoder output feeds every decoder layer
-    NMT_TRY(r.dgrad(dkv, Ns, 2 * d, P.cross.wkv, d, denc, accum));
+    if (beside) {
+      NMT_TRY(fork());
+      NMT_TRY(side.dgrad(dkv, Ns, 2 * d, P.cross.wkv, d, denc, accum));
+      if (l == 0) NMT_HIP_CHECK(hipEventRecord(c->ev_denc, sd));
+    } else {
+      NMT_TRY(r.dgrad(dkv, Ns, 2 * d, P.cross.wkv, d, denc, accum));
+    }
     // masked self-attention
     NMT_TRY(self_bwd(dx, Nt, true, x_in, r.ws<half_t>(W.qkv), r.ws<half_t>(W.o1), r.ws<float>(W.lse1), r.ws<half_t>(W.s1),
                      r.ws<float>(W.st1), P.self, P.ln1, layer_site(li, kKindSelfRes), c->tgt_in, 1));
   }
   const half_t* dx_dec0 = dx;
+  if (beside) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_denc, 0));
 
   // ---- encoder ----
   for (int l = k.enc_layers - 1; l >= 0; --l) {

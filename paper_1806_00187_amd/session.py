@@ -60,9 +60,10 @@ class Session:
         self.loss_sums = [torch.zeros(1, dtype=torch.float32, device=self.device) for _ in range(n_pipes)]
         self.ntoks = [torch.zeros(1, dtype=torch.int32, device=self.device) for _ in range(n_pipes)]
         self.loss_sum, self.ntok = self.loss_sums[0], self.ntoks[0]
-        self.flag = torch.zeros(1, dtype=torch.int32, device=self.device)
-        self.loss_tot = torch.zeros(1, dtype=torch.float32, device=self.device)
-        self.ntok_tot = torch.zeros(1, dtype=torch.int32, device=self.device)
+        # what an update reports, side by side so that the host fetches it with one copy
+        self._report = torch.zeros(3, dtype=torch.int32, device=self.device)
+        self.flag, self.ntok_tot = self._report[0:1], self._report[1:2]
+        self.loss_tot = self._report[2:3].view(torch.float32)
         self.streams = [torch.cuda.Stream(device=self.device) for _ in range(n_pipes)] if n_pipes > 1 else [None]
         # with several pipes, the first update tries a few sets of streams and keeps the best (choose_streams)
         self._streams_chosen = n_pipes == 1 or not auto_streams
@@ -207,7 +208,8 @@ class Session:
             n_tok = int(self.ntok_tot.item())
         self.check_overflow(1.0 / (loss_scale * max(n_tok, 1)))
         self.adam_step(lr, t, betas, eps)
-        return float(self.loss_tot.item()), n_tok, int(self.flag.item())
+        report = self._report.cpu()
+        return float(report[2:3].view(torch.float32).item()), n_tok, int(report[0].item())
 
     def _update_pipes(self, dbatches, loss_scale, step, main):
         """Sub-batch j goes through pipe j % n_pipes; accumulation is chained with events in sub-batch order.  One host
