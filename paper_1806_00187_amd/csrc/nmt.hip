@@ -107,7 +107,7 @@ struct Plan {
   int64_t rk_src, rk_tgt, tab_ss, tab_tt, tab_ts;  // row keys (dropout, positions) and per-sentence attention tables
   int64_t wl_ss, wl_tt, wl_ts;                     // attention work lists over those tables
   int64_t sent_rows;                                // first source / target row of every sentence (packed batches)
-  int64_t x0, y0, logits, rowloss;
+  int64_t x0, y0, logits, rowloss, rowlse;
   std::vector<EncW> enc;
   std::vector<DecW> dec;
   int64_t dx_dec, dx_enc, dy, dsub[2][3], dO, dqkv[2], dh[2], dq[2], dkv[2], lnpart[2][3], embscratch, wgpart, wgpart_floats;
@@ -242,6 +242,7 @@ int64_t plan_workspace(const nmt_ctx* c, const GroupDims& gd, Plan& p) {
   }
   p.logits = take(Nt * V * h2);
   p.rowloss = take(Nt * f4);
+  p.rowlse = take(Nt * f4);
   p.dx_dec = take(Nt * d * h2);
   p.dx_enc = take(Ns * d * h2);
   p.dO = take(Nm * d * h2);
@@ -663,7 +664,7 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
   half_t* logits = r.ws<half_t>(p.logits);
   NMT_TRY(launch_gemm(y, false, d, r.w(c->embed), false, d, logits, V, Nt, V, d, GemmEpilogue{}, st));
   NMT_TRY(launch_softmax_xent(logits, d_tgt_out, r.ws<float>(p.rowloss), Nt, V, k.pad_id, k.label_smoothing, loss_scale, d_loss_sum,
-                              d_ntok, st));
+                              d_ntok, st, c->training ? nullptr : r.ws<float>(p.rowlse)));
   c->have_fwd = true;
   return NMT_OK;
 }
@@ -786,7 +787,9 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
 
   // ---- output projection: logits = x E^T; the workspace holds d logits ----
   // (the tied matrix's gradient is finished by the embedding kernels at the very end)
-  const half_t* dlogits = r.ws<half_t>(p.logits);
+  half_t* dlogits = r.ws<half_t>(p.logits);
+  if (!c->training)  // (a forward pass without training leaves the logits as they are)
+    NMT_TRY(launch_softmax_grad(dlogits, c->tgt_out, r.ws<float>(p.rowlse), Nt, V, k.pad_id, k.label_smoothing, c->loss_scale, st));
   const half_t* x_dec = r.ws<half_t>(p.dec[k.dec_layers - 1].x3);
   half_t* dx = r.ws<half_t>(p.dx_dec);
   NMT_TRY(fork());

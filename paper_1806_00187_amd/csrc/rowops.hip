@@ -358,7 +358,9 @@ __global__ void __launch_bounds__(kThreads) colsum_kernel(const half_t* __restri
 
 // ------------------------------------------------------------------------------------------------
 // Fused softmax + label-smoothed cross-entropy + gradient; one block per row, the row held in
-// registers (NCH chunks of 8 logits per thread).
+// registers (NCH chunks of 8 logits per thread).  A pass without training needs the loss alone: the row is read and not
+// written back (26000 x 32768: 591 -> 297 us; the written half was the gradient), and its log-sum-exp is kept in case a
+// backward pass is asked for after all, which then forms the same gradient from it.
 // ------------------------------------------------------------------------------------------------
 __device__ __forceinline__ float block_reduce(float v, bool is_max, float* sh) {
   v = is_max ? wave_max(v) : wave_sum(v);
@@ -372,18 +374,21 @@ __device__ __forceinline__ float block_reduce(float v, bool is_max, float* sh) {
   return r;
 }
 
-template <int NCH>
+enum XentForm { kLossAndGrad, kLossOnly, kGradOnly };
+template <int NCH, XentForm FORM>
 __global__ void __launch_bounds__(kThreads) softmax_xent_kernel(half_t* __restrict__ logits, const int32_t* __restrict__ targets,
-                                                                float* __restrict__ row_loss, int V, int pad_id, float eps_ls,
-                                                                float loss_scale) {
+                                                                float* __restrict__ row_loss, float* __restrict__ row_lse, int V, int pad_id,
+                                                                float eps_ls, float loss_scale) {
   __shared__ float sh[kWavesPerBlock];
   const int row = blockIdx.x;
   const int chunks = V >> 3;
   half_t* z = logits + (size_t)row * V;
   const int y = targets[row];
   if (y == pad_id) {  // padding positions contribute neither loss nor gradient
-    for (int c = threadIdx.x; c < chunks; c += kThreads) st_half8(z + c * 8, zero_half8());
-    if (threadIdx.x == 0) row_loss[row] = 0.f;
+    if constexpr (FORM != kLossOnly)
+      for (int c = threadIdx.x; c < chunks; c += kThreads) st_half8(z + c * 8, zero_half8());
+    if constexpr (FORM != kGradOnly)
+      if (threadIdx.x == 0) row_loss[row] = 0.f;
     return;
   }
   // The row stays in registers as fp16.  Pass 1 (maximum, plain sum) runs on pairs of halfs; the two
@@ -410,21 +415,30 @@ __global__ void __launch_bounds__(kThreads) softmax_xent_kernel(half_t* __restri
     }
   }
   const int yc = min(max(y, 0), V - 1);
-  const float zy = (float)z[yc];
-  const float mx = block_reduce(fmaxf((float)mx2[0], (float)mx2[1]), true, sh);
-  const float shift = -mx * kLog2e;
-  float se = 0.f;
+  float lse;
+  if constexpr (FORM == kGradOnly) {
+    lse = row_lse[row];
+  } else {
+    const float zy = (float)z[yc];
+    const float mx = block_reduce(fmaxf((float)mx2[0], (float)mx2[1]), true, sh);
+    const float shift = -mx * kLog2e;
+    float se = 0.f;
 #pragma unroll
-  for (int i = 0; i < NCH; ++i) {
-    if (threadIdx.x + kThreads * i < chunks) {
+    for (int i = 0; i < NCH; ++i) {
+      if (threadIdx.x + kThreads * i < chunks) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) se += __builtin_amdgcn_exp2f(fmaf((float)reg[i][e], kLog2e, shift));
+        for (int e = 0; e < 8; ++e) se += __builtin_amdgcn_exp2f(fmaf((float)reg[i][e], kLog2e, shift));
+      }
+    }
+    se = block_reduce(se, false, sh);
+    sz = block_reduce(sz, false, sh);
+    lse = mx + logf(se);
+    if (threadIdx.x == 0) row_loss[row] = lse - (1.f - eps_ls) * zy - (eps_ls / (float)V) * sz;
+    if constexpr (FORM == kLossOnly) {
+      if (threadIdx.x == 0) row_lse[row] = lse;
+      return;
     }
   }
-  se = block_reduce(se, false, sh);
-  sz = block_reduce(sz, false, sh);
-  const float lse = mx + logf(se);
-  if (threadIdx.x == 0) row_loss[row] = lse - (1.f - eps_ls) * zy - (eps_ls / (float)V) * sz;
   const float q_scaled = loss_scale * eps_ls / (float)V, hit = loss_scale * (1.f - eps_ls);
   const float shift2 = -lse * kLog2e + log2f(loss_scale);
 #pragma unroll
@@ -978,13 +992,14 @@ int launch_colsum(const half_t* src, int ld, half_t* dst, float* partial, int ro
   return launch_finalize(&sums, 1, 1, cols, cols, scale, stream);
 }
 
-int launch_softmax_xent(half_t* logits, const int32_t* targets, float* row_loss, int rows, int V, int pad_id, float eps_ls,
-                        float loss_scale, float* loss_sum, int32_t* ntok, hipStream_t stream) {
-  NMT_REQUIRE(rows > 0 && V >= 8 && V % 8 == 0 && V <= 65536, "softmax_xent: V=%d must be a multiple of 8 in [8, 65536]", V);
-  NMT_REQUIRE(logits && targets && row_loss && loss_sum && ntok && aligned16(logits), "softmax_xent: null or misaligned pointer");
+namespace {
+template <XentForm FORM>
+int launch_xent_rows(half_t* logits, const int32_t* targets, float* row_loss, float* row_lse, int rows, int V, int pad_id, float eps_ls,
+                     float loss_scale, hipStream_t stream) {
   const dim3 grid(rows), block(kThreads);
   const int nch = ceil_div(V / 8, kThreads);
-#define NMT_XENT(N) hipLaunchKernelGGL(softmax_xent_kernel<N>, grid, block, 0, stream, logits, targets, row_loss, V, pad_id, eps_ls, loss_scale)
+#define NMT_XENT(N) \
+  hipLaunchKernelGGL((softmax_xent_kernel<N, FORM>), grid, block, 0, stream, logits, targets, row_loss, row_lse, V, pad_id, eps_ls, loss_scale)
   if (nch <= 1) NMT_XENT(1);
   else if (nch <= 4) NMT_XENT(4);
   else if (nch <= 16) NMT_XENT(16);
@@ -992,9 +1007,25 @@ int launch_softmax_xent(half_t* logits, const int32_t* targets, float* row_loss,
   else NMT_XENT(32);
 #undef NMT_XENT
   NMT_LAUNCH_CHECK();
+  return NMT_OK;
+}
+}  // namespace
+
+int launch_softmax_xent(half_t* logits, const int32_t* targets, float* row_loss, int rows, int V, int pad_id, float eps_ls,
+                        float loss_scale, float* loss_sum, int32_t* ntok, hipStream_t stream, float* row_lse) {
+  NMT_REQUIRE(rows > 0 && V >= 8 && V % 8 == 0 && V <= 65536, "softmax_xent: V=%d must be a multiple of 8 in [8, 65536]", V);
+  NMT_REQUIRE(logits && targets && row_loss && loss_sum && ntok && aligned16(logits), "softmax_xent: null or misaligned pointer");
+  if (int rc = row_lse ? launch_xent_rows<kLossOnly>(logits, targets, row_loss, row_lse, rows, V, pad_id, eps_ls, loss_scale, stream)
+                       : launch_xent_rows<kLossAndGrad>(logits, targets, row_loss, nullptr, rows, V, pad_id, eps_ls, loss_scale, stream))
+    return rc;
   hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, stream, row_loss, targets, rows, pad_id, loss_sum, ntok);
   NMT_LAUNCH_CHECK();
   return NMT_OK;
+}
+int launch_softmax_grad(half_t* logits, const int32_t* targets, float* row_lse, int rows, int V, int pad_id, float eps_ls, float loss_scale,
+                        hipStream_t stream) {
+  NMT_REQUIRE(rows > 0 && V >= 8 && V % 8 == 0 && V <= 65536 && logits && targets && row_lse && aligned16(logits), "softmax_grad: bad arguments");
+  return launch_xent_rows<kGradOnly>(logits, targets, nullptr, row_lse, rows, V, pad_id, eps_ls, loss_scale, stream);
 }
 
 namespace {

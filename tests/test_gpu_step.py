@@ -491,6 +491,25 @@ def test_packed_pass_with_every_sentence_length_class_matches_the_oracle():
         sess.close()
 
 
+@pytest.mark.parametrize("vocab", [264, 2056, 9000])
+def test_backward_after_a_pass_without_training_gives_the_same_bits(vocab):
+    """A forward pass without training computes the loss alone and keeps the logits; without dropout, loss and gradients must be
+    those of the training form, bit for bit (padded batch: rows that contribute nothing are among them)."""
+    model = dict(enc_layers=1, dec_layers=1, d_model=64, n_heads=4, d_ff=128, vocab=vocab, dropout=0.0)
+    sess = Session(model, I.init_weights(seed=4, **model), max_sentences=8)
+    try:
+        db = sess.to_device(I.tiny_batch(seed=12, B=6, S=14, T=11, vocab=vocab))
+        seen = []
+        for training in (True, False):
+            sess.forward_loss(db, 64.0, 1, 0, training=training)
+            loss = sess.loss_sum.clone()
+            sess.backward()
+            seen.append((loss, sess.ntok.clone(), sess.g16.clone()))
+        assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(*seen))
+    finally:
+        sess.close()
+
+
 def test_packed_entry_point_clamps_inconsistent_lengths_and_rejects_bad_totals():
     """Lengths on the device that exceed what the host announced are cut to the announced totals (no
     access outside the buffers; the result is then undefined but finite buffers stay in bounds);
