@@ -1183,15 +1183,16 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
                                 K, tail, stream, nullptr, 0, 1);
       }
     }
-    // At least two tiles per compute unit, no split along k, row-major A, an epilogue that loads nothing per
+    // More tiles than compute units, no split along k, row-major A, an epilogue that loads nothing per
     // element (bias, ReLU, scale): the persistent form.  (With an addend or a mask to load it gained 1-11 % on a
     // product running alone but nothing on the update, where the weight-gradient kernels of the second stream
     // share the chip and work-groups that never leave their compute unit cost more than they gain; the form no
     // longer has those epilogues.  Not for a k-major A either: the one such product without a split, the
     // vocabulary weight gradient, has so long a contraction that the tile change hardly counts, and measured
-    // 6 % slower in this form.)
+    // 6 % slower in this form.  From one round on and not only from two: 26000 x 1536 x 512 is 510 tiles in its full rounds,
+    // 50 us one tile per work-group, 44 in this form.)
     const bool loads_in_epilogue = ep.add || ep.relu_src || ep.drop.thr;
-    if (splits == 1 && t256 >= 2 * cus && !a_t && tuning().gemm_persist && !loads_in_epilogue) {
+    if (splits == 1 && t256 > cus && !a_t && tuning().gemm_persist && !loads_in_epilogue) {
       GemmArgs pg = g;
       pg.tiles_m = ceil_div(M, 256);
       pg.tiles_n = ceil_div(N, 256);
