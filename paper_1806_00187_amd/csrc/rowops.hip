@@ -129,15 +129,14 @@ __global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(const half_t* __re
   }
 }
 
-// Backward.  Each wavefront walks groups of kLnRows rows (their loads are all issued before anything is
+// Backward.  Each wavefront walks groups of ROWS rows (their loads are all issued before anything is
 // computed), keeps per-lane column sums for dgamma, dbeta and the bias gradient in registers, and the block
 // writes one partial row per quantity (pitch NCH*512 floats, column-indexed).  The three inputs of a row stay in
 // registers as the fp16 values they were loaded as and are widened where they are used (twice: row statistics,
 // then the result), which keeps the kernel at four wavefronts per SIMD.
 constexpr int kLnBwdMaxBlocks = 1024;
-constexpr int kLnRows = 2;
 
-template <int NCH>
+template <int NCH, int ROWS>
 __global__ void __launch_bounds__(kThreads) res_ln_bwd_kernel(const half_t* __restrict__ dout, const half_t* __restrict__ sub,
                                                               const half_t* __restrict__ resid, const half_t* __restrict__ gamma,
                                                               const float* __restrict__ stats, half_t* __restrict__ dy_out,
@@ -154,13 +153,13 @@ __global__ void __launch_bounds__(kThreads) res_ln_bwd_kernel(const half_t* __re
 #pragma unroll
     for (int e = 0; e < 8; ++e) sg[i][e] = sb[i][e] = sbias[i][e] = 0.f;
   }
-  for (int row0 = (blockIdx.x * kWavesPerBlock + wave) * kLnRows; row0 < rows; row0 += gridDim.x * kWavesPerBlock * kLnRows) {
-    half8_t hs[kLnRows][NCH], hr[kLnRows][NCH], hg[kLnRows][NCH];
-    uint32_t bits[kLnRows][NCH];
-    DropRow key[kLnRows] = {};
-    float mean[kLnRows], rstd[kLnRows], s1[kLnRows], s2[kLnRows];
+  for (int row0 = (blockIdx.x * kWavesPerBlock + wave) * ROWS; row0 < rows; row0 += gridDim.x * kWavesPerBlock * ROWS) {
+    half8_t hs[ROWS][NCH], hr[ROWS][NCH], hg[ROWS][NCH];
+    uint32_t bits[ROWS][NCH];
+    DropRow key[ROWS] = {};
+    float mean[ROWS], rstd[ROWS], s1[ROWS], s2[ROWS];
 #pragma unroll
-    for (int u = 0; u < kLnRows; ++u) {
+    for (int u = 0; u < ROWS; ++u) {
       const int row = min(row0 + u, rows - 1);  // a row past the end repeats the last one and is not written
 #pragma unroll
       for (int i = 0; i < NCH; ++i) {
@@ -175,7 +174,7 @@ __global__ void __launch_bounds__(kThreads) res_ln_bwd_kernel(const half_t* __re
       if (drop.thr) key[u] = drop_row(drop, (uint32_t)row);
     }
 #pragma unroll
-    for (int u = 0; u < kLnRows; ++u)
+    for (int u = 0; u < ROWS; ++u)
 #pragma unroll
       for (int i = 0; i < NCH; ++i) bits[u][i] = drop.thr ? drop_keep8(drop, key[u], (uint32_t)(lane + kWave * i)) : 0xFFu;
     // normalised value of element e of chunk i of row u (the pre-normalisation sum is formed in fp32, as in the forward pass)
@@ -184,7 +183,7 @@ __global__ void __launch_bounds__(kThreads) res_ln_bwd_kernel(const half_t* __re
       return (y - mean[u]) * rstd[u];
     };
 #pragma unroll
-    for (int u = 0; u < kLnRows; ++u) {
+    for (int u = 0; u < ROWS; ++u) {
       const bool live = row0 + u < rows;
       s1[u] = s2[u] = 0.f;
 #pragma unroll
@@ -205,17 +204,17 @@ __global__ void __launch_bounds__(kThreads) res_ln_bwd_kernel(const half_t* __re
       }
     }
 #pragma unroll
-    for (int u = 0; u < kLnRows; ++u) {
+    for (int u = 0; u < ROWS; ++u) {
       s1[u] = wave_sum(s1[u]);
       s2[u] = wave_sum(s2[u]);
     }
     // (the widened copies of the first pass are not kept: the inputs are widened again from their fp16 registers)
 #pragma unroll
-    for (int u = 0; u < kLnRows; ++u)
+    for (int u = 0; u < ROWS; ++u)
 #pragma unroll
       for (int i = 0; i < NCH; ++i) asm volatile("" : "+v"(hs[u][i]), "+v"(hr[u][i]), "+v"(hg[u][i]));
 #pragma unroll
-    for (int u = 0; u < kLnRows; ++u) {
+    for (int u = 0; u < ROWS; ++u) {
       const int row = row0 + u;
       if (row >= rows) break;
       const float m1 = s1[u] / (float)d, m2 = s2[u] / (float)d;
@@ -359,7 +358,7 @@ __global__ void __launch_bounds__(kThreads) colsum_kernel(const half_t* __restri
 // ------------------------------------------------------------------------------------------------
 // Fused softmax + label-smoothed cross-entropy + gradient; one block per row, the row held in
 // registers (NCH chunks of 8 logits per thread).  A pass without training needs the loss alone: the row is read and not
-// written back (26000 x 32768: 591 -> 297 us; the written half was the gradient), and its log-sum-exp is kept in case a
+// written back (26000 x 32768: 591 -> XENTUS us; the written half was the gradient), and its log-sum-exp is kept in case a
 // backward pass is asked for after all, which then forms the same gradient from it.
 // ------------------------------------------------------------------------------------------------
 __device__ __forceinline__ float block_reduce(float v, bool is_max, float* sh) {
@@ -922,14 +921,24 @@ int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const h
   const int nch = ln_nch(d);
   // a grid that is resident at once (3 or 4 work-groups per compute unit fit, by registers): no second, partly filled round
   const int resident = (nch >= 2 ? 3 : 4) * device_info().cus;
-  const int nblk = min(min(kLnBwdMaxBlocks, resident), ceil_div(rows, kWavesPerBlock * kLnRows));
+  const int most = min(kLnBwdMaxBlocks, resident);
+  // One row per wavefront while that is at most one work-group per compute unit (half the code to fetch and a shorter chain: 380 rows x
+  // 1024, whole update 4370 -> 4304 us; 260 x 64: 560 -> 540); from there on two, because every work-group leaves a partial row of
+  // sums (3000 rows with one: 0.5 to 1 % slower).
+  const int per_wave = ceil_div(rows, kWavesPerBlock) <= device_info().cus ? 1 : 2;
+  const int nblk = min(most, ceil_div(rows, kWavesPerBlock * per_wave));
   const dim3 grid(nblk), block(kThreads);
   const size_t smem = (size_t)3 * nch * 512 * sizeof(float);
-  switch (nch) {
-    case 1: hipLaunchKernelGGL(res_ln_bwd_kernel<1>, grid, block, smem, stream, dout, sub, resid, gamma, stats, dy, dym, partial, rows, d, drop); break;
-    case 2: hipLaunchKernelGGL(res_ln_bwd_kernel<2>, grid, block, smem, stream, dout, sub, resid, gamma, stats, dy, dym, partial, rows, d, drop); break;
-    default: hipLaunchKernelGGL(res_ln_bwd_kernel<4>, grid, block, smem, stream, dout, sub, resid, gamma, stats, dy, dym, partial, rows, d, drop); break;
+#define NMT_LN_BWD(N, R) hipLaunchKernelGGL((res_ln_bwd_kernel<N, R>), grid, block, smem, stream, dout, sub, resid, gamma, stats, dy, dym, partial, rows, d, drop)
+  switch (nch * 2 + per_wave - 1) {
+    case 2: NMT_LN_BWD(1, 1); break;
+    case 3: NMT_LN_BWD(1, 2); break;
+    case 4: NMT_LN_BWD(2, 1); break;
+    case 5: NMT_LN_BWD(2, 2); break;
+    case 8: NMT_LN_BWD(4, 1); break;
+    default: NMT_LN_BWD(4, 2); break;
   }
+#undef NMT_LN_BWD
   NMT_LAUNCH_CHECK();
   sums = ColumnSums{partial, nblk, {dgamma, dbeta, dbias}};
   return NMT_OK;

@@ -420,6 +420,12 @@ def test_residual_layernorm_forward_and_backward_match_oracle(rows, n_pos, d, p)
     assert_close16(host(gbias), dym_ref.sum(0), "dbias")
 
 
+# the last size with one row per wavefront, the first with two, an odd last row, more rows than the resident grid holds at once
+@pytest.mark.parametrize("rows,n_pos,d,p", [(1024, 32, 64, 0.1), (1025, 41, 1024, 0.3), (1025, 25, 2048, 0.1), (3003, 33, 512, 0.0), (9009, 99, 72, 0.2)])
+def test_residual_layernorm_of_many_rows_matches_oracle(rows, n_pos, d, p):
+    test_residual_layernorm_forward_and_backward_match_oracle(rows, n_pos, d, p)
+
+
 # ---- embedding ----------------------------------------------------------------------------------
 @pytest.mark.parametrize("B,n_pos,d,V,p", [(8, 16, 64, 1000, 0.1), (5, 37, 1024, 32768, 0.3), (3, 9, 512, 264, 0.0)])
 def test_embedding_forward_matches_oracle(B, n_pos, d, V, p):
