@@ -41,7 +41,7 @@ struct AttnArgs {
   int pad_id, causal, B, H, Tq, Tk;  // with a sentence table: Tq, Tk are the largest lengths in it
   const int4* tab;                   // per sentence (first query row, first key row, Tq, Tk), or nullptr
   int Nq;                            // query rows in total: lse is [H, Nq]
-  int fused_max;                     // backward: sentences with max(Tq, Tk) <= this are left to the fused kernel
+  int fused_max;                     // backward: sentences with max(Tq, Tk) <= this are left to the kernels that form the scores once
   // work lists over the table (or nullptr: every (sentence, tile) of the grid is looked at)
   const int32_t* wl_counts;          // [0..kClasses-1] sentences by tiles of the longer side, [kClasses] longer ones, [kClasses + 1] query tiles
   const int4* wl_sent;               // [kClasses][B] table entries of the sentences of each class

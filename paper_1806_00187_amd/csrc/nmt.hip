@@ -614,7 +614,12 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
   auto project_kv = [&](const Run& on, int l) {
     return on.linear(enc_out, Ns, d, c->dec[l].cross.wkv, c->dec[l].cross.bkv, 2 * d, r.ws<half_t>(p.dec[l].kv));
   };
-  const bool beside = encoder_products_beside(c);
+  bool beside = encoder_products_beside(c);
+  if (beside && !c->side) {  // (a stream is not made while the caller's is being captured: such a first pass keeps to one)
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    beside = hipStreamIsCapturing(st, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+  }
   if (beside) {
     NMT_TRY(ensure_second_stream(c));
     const Run side{c, c->side};
