@@ -1078,21 +1078,28 @@ constexpr TileCost kTileCost[kSmallTiles] = {
     {128, 64, 3, 4.3, 1.8, {0.48, 0.66, 0.94}},       // two stages
     {128, 128, 2, 5.7, 3.5, {0.55, 0.88, 0.}},        // two stages
 };
-double tile_us(const TileCost& c, int64_t tiles, int K) {
-  const int cus = device_info().cus, nk = ceil_div(K, 64);
+double tile_us(const TileCost& c, int64_t tiles, int K, int cus) {
+  const int nk = ceil_div(K, 64);
   const int64_t slots = (int64_t)cus * c.per_cu, rounds = tiles / slots, rest = tiles - rounds * slots;
   double us = c.fixed + rounds * nk * c.k_tile[c.per_cu - 1];
   if (rest) us += nk * c.k_tile[ceil_div(rest, cus) - 1];
   return us + c.again * (double)(rounds + (rest ? 1 : 0) - 1);
 }
-SmallTile choose_small_tile(int M, int N, int K) {
+SmallTile choose_small_tile(int M, int N, int K, int cus, double& best_us) {
   int best = kTile64;
-  double best_us = 0.;
+  best_us = 0.;
   for (int t = 0; t < kSmallTiles; ++t) {
-    const double us = tile_us(kTileCost[t], (int64_t)ceil_div(M, kTileCost[t].bm) * ceil_div(N, kTileCost[t].bn), K);
+    const double us = tile_us(kTileCost[t], (int64_t)ceil_div(M, kTileCost[t].bm) * ceil_div(N, kTileCost[t].bn), K, cus);
     if (t == 0 || us < best_us) { best = t; best_us = us; }
   }
   return (SmallTile)best;
+}
+// The same for at most one 256 x 256 tile per compute unit (row-major A; 6000 to 26000 rows, 512 to 4096 columns, k 512 to
+// 4096: within 10 % of the measured times): a k-tile costs more the more compute units are at work, because the clocks drop.
+double large_us(int64_t tiles, int K, int cus) {
+  constexpr double kFixed = 8.6, kFew = 1.05, kFull = 1.65;
+  const double fill = (double)tiles / cus;
+  return kFixed + ceil_div(K, 64) * (kFew + (kFull - kFew) * fill * fill * fill);
 }
 int launch_small_tile(SmallTile t, const GemmArgs& g, bool a_t, bool b_t, int splits, hipStream_t stream) {
   switch (t) {
@@ -1162,16 +1169,23 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
     }
   }
   // (a caller that keeps several passes in flight says so: each product then counts on its share of the chip)
-  const int64_t full_shared = full / tuning().gemm_share > 1 ? full / tuning().gemm_share : 1;
-  if (t256 * splits >= full_shared) {
+  const int share = tuning().gemm_share;
+  double small_us;
+  const SmallTile small = choose_small_tile(M, N, K, cus, small_us);
+  // Up to one round of large tiles they are taken where they cost less than the best small ones (9000 x 1024 x 4096, 144 large tiles:
+  // 79 us against 97; 17700 x 512 x 2048, 140: 44 against 52); a fixed line at three quarters of a round gave these small
+  // ones.  That line remains where the costs were not measured: products cut along k, with a k-major A, or beside others.
+  const bool large = (splits > 1 || a_t || share > 1 || t256 > cus) ? t256 * splits * share >= full : large_us(t256, K, cus) <= small_us;
+  if (large) {
     // A last, partly filled round of 256 x 256 tiles leaves compute units idle for a whole tile's
     // time.  If that round is small, the rows it would cover are given to a second launch with small
-    // tiles (two work-groups per compute unit), which costs about a third of a round.
+    // tiles (two work-groups per compute unit), which costs about 0.4 of a round for every round of its own.  (Up to half a round:
+    // 17700 x 2048 x 512, 2.2 rounds: 52 -> 45 us; not above: 26000 x 1024 x 4096, 1.6 rounds, 192 us in one launch, was 217 in two.)
     const int tiles_n = ceil_div(N, 256), rounds = (int)(t256 / cus);
     if (splits == 1 && rounds >= 1 && t256 % cus != 0) {
       const int main_tm = cus * rounds / tiles_n, m_main = main_tm * 256, m_tail = M - m_main;
       const int64_t tail128 = (int64_t)ceil_div(m_tail, 128) * ceil_div(N, 128);
-      const double cost_split = ceil_div((int64_t)main_tm * tiles_n, cus) + 0.3 * ceil_div(tail128, 2 * cus);
+      const double cost_split = ceil_div((int64_t)main_tm * tiles_n, cus) + 0.4 * ceil_div(tail128, 2 * cus);
       if (main_tm >= 1 && cost_split + 0.25 <= rounds + 1) {
         int rc = launch_gemm_impl(A, a_t, lda, B, b_t, ldb, C, ldc, m_main, N, K, ep, stream, nullptr, 0, 1);
         if (rc != NMT_OK) return rc;
@@ -1209,7 +1223,7 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
     return launch_tile<256, 256, 32, 4, 8>(g, a_t, b_t, splits, stream);
   }
   if (splits > 1) return launch_small_tile(kTile128Many, g, a_t, b_t, splits, stream);
-  return launch_small_tile(choose_small_tile(M, N, K), g, a_t, b_t, 1, stream);
+  return launch_small_tile(small, g, a_t, b_t, 1, stream);
 }
 
 // ---- weight-gradient groups ----
