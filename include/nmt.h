@@ -84,7 +84,10 @@ int nmt_bind(nmt_ctx* ctx, void* d_w16, void* d_g16, float* d_master32, float* d
  * fp16 gradient exists ("Half-Precision Training").
  * step (< 2^24) and micro_idx (< 256) select the dropout streams; d_sent_uid [B] (uint32, may
  * be NULL = row index) names each sentence so its dropout mask does not depend on batching.
- * training == 0 disables dropout.
+ * training == 0 disables dropout and computes the loss alone: the logits stay, and an nmt_backward that follows all the
+ * same first forms that gradient from them and from the log-sum-exps and targets the forward pass kept in the workspace
+ * (the same bits; one more read of the logits than with training != 0).
+ * An nmt_backward that follows reads d_src and d_tgt_in again, never d_tgt_out.
  * Outputs: *d_loss_sum = sum over non-pad target tokens of the UNSCALED loss in nats,
  * *d_ntok = number of non-pad target tokens. */
 int nmt_forward_loss(nmt_ctx* ctx, const int32_t* d_src, const int32_t* d_tgt_in,

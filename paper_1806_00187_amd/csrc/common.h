@@ -261,9 +261,10 @@ int launch_embed_fwd(const int32_t* ids, const half_t* E, half_t* x, int rows, i
                      hipStream_t stream);
 int launch_softmax_xent(half_t* logits, const int32_t* targets, float* row_loss, int rows, int V, int pad_id,
                         float eps_ls, float loss_scale, float* loss_sum, int32_t* ntok, hipStream_t stream,
-                        float* row_lse = nullptr);  // given: the loss alone; logits stay, and the rows' log-sum-exp goes there ...
-int launch_softmax_grad(half_t* logits, const int32_t* targets, float* row_lse, int rows, int V, int pad_id, float eps_ls, float loss_scale,
-                        hipStream_t stream);        // ... from which this makes the gradient, in place
+                        float* row_lse = nullptr, int32_t* row_target = nullptr);  // given: the loss alone; logits stay, and the rows'
+                                                    // log-sum-exps and targets go there ...
+int launch_softmax_grad(half_t* logits, const int32_t* row_target, float* row_lse, int rows, int V, int pad_id, float eps_ls, float loss_scale,
+                        hipStream_t stream);                        // ... from which this makes the gradient, in place
 int64_t colsum_scratch_floats(int cols);
 int launch_colsum(const half_t* src, int ld, half_t* dst, float* partial, int rows, int cols, hipStream_t stream, float scale = 1.f);
 int launch_colsum_static(const half_t* src, int ld, half_t* dst, int rows, int cols, hipStream_t stream);  // partial sums in a fixed device array

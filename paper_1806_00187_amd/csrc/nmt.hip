@@ -107,7 +107,7 @@ struct Plan {
   int64_t rk_src, rk_tgt, tab_ss, tab_tt, tab_ts;  // row keys (dropout, positions) and per-sentence attention tables
   int64_t wl_ss, wl_tt, wl_ts;                     // attention work lists over those tables
   int64_t sent_rows;                                // first source / target row of every sentence (packed batches)
-  int64_t x0, y0, logits, rowloss, rowlse;
+  int64_t x0, y0, logits, rowloss, rowlse, targets;
   std::vector<EncW> enc;
   std::vector<DecW> dec;
   int64_t dx_dec, dx_enc, dy, dsub[2][3], dO, dqkv[2], dh[2], dq[2], dkv[2], lnpart[2][3], embscratch, wgpart, wgpart_floats;
@@ -135,7 +135,7 @@ struct nmt_ctx {
   float gscale = 1.f;  // power-of-two factor on everything the current pass writes to g16
   float inv_scale = 1.f;  // what nmt_check_overflow was given: nmt_adam_step applies it to acc32 on the fly
   uint32_t step = 0;
-  const int32_t *src = nullptr, *tgt_in = nullptr, *tgt_out = nullptr;
+  const int32_t *src = nullptr, *tgt_in = nullptr;
   const float* last_loss = nullptr;   // where the last forward call wrote its loss sum and token count
   const int32_t* last_ntok = nullptr;
   Plan plan;
@@ -243,6 +243,7 @@ int64_t plan_workspace(const nmt_ctx* c, const GroupDims& gd, Plan& p) {
   p.logits = take(Nt * V * h2);
   p.rowloss = take(Nt * f4);
   p.rowlse = take(Nt * f4);
+  p.targets = take(Nt * (int64_t)sizeof(int32_t));
   p.dx_dec = take(Nt * d * h2);
   p.dx_enc = take(Ns * d * h2);
   p.dO = take(Nm * d * h2);
@@ -555,7 +556,7 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
   // sub-batch's gradient has, so grouping does not lower the loss scale at which fp16 overflows.
   c->gscale = 1.f;
   for (int64_t n = gd.Nt; n >= 8192; n >>= 1) c->gscale *= 0.5f;
-  c->src = d_src; c->tgt_in = d_tgt_in; c->tgt_out = d_tgt_out;
+  c->src = d_src; c->tgt_in = d_tgt_in;
   c->last_loss = d_loss_sum; c->last_ntok = d_ntok;
 
   const nmt_config& k = c->cfg;
@@ -669,7 +670,7 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
   half_t* logits = r.ws<half_t>(p.logits);
   NMT_TRY(launch_gemm(y, false, d, r.w(c->embed), false, d, logits, V, Nt, V, d, GemmEpilogue{}, st));
   NMT_TRY(launch_softmax_xent(logits, d_tgt_out, r.ws<float>(p.rowloss), Nt, V, k.pad_id, k.label_smoothing, loss_scale, d_loss_sum,
-                              d_ntok, st, c->training ? nullptr : r.ws<float>(p.rowlse)));
+                              d_ntok, st, c->training ? nullptr : r.ws<float>(p.rowlse), c->training ? nullptr : r.ws<int32_t>(p.targets)));
   c->have_fwd = true;
   return NMT_OK;
 }
@@ -794,7 +795,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   // (the tied matrix's gradient is finished by the embedding kernels at the very end)
   half_t* dlogits = r.ws<half_t>(p.logits);
   if (!c->training)  // (a forward pass without training leaves the logits as they are)
-    NMT_TRY(launch_softmax_grad(dlogits, c->tgt_out, r.ws<float>(p.rowlse), Nt, V, k.pad_id, k.label_smoothing, c->loss_scale, st));
+    NMT_TRY(launch_softmax_grad(dlogits, r.ws<int32_t>(p.targets), r.ws<float>(p.rowlse), Nt, V, k.pad_id, k.label_smoothing, c->loss_scale, st));
   const half_t* x_dec = r.ws<half_t>(p.dec[k.dec_layers - 1].x3);
   half_t* dx = r.ws<half_t>(p.dx_dec);
   NMT_TRY(fork());

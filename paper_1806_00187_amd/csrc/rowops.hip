@@ -358,8 +358,8 @@ __global__ void __launch_bounds__(kThreads) colsum_kernel(const half_t* __restri
 // ------------------------------------------------------------------------------------------------
 // Fused softmax + label-smoothed cross-entropy + gradient; one block per row, the row held in
 // registers (NCH chunks of 8 logits per thread).  A pass without training needs the loss alone: the row is read and not
-// written back (26000 x 32768: 591 -> XENTUS us; the written half was the gradient), and its log-sum-exp is kept in case a
-// backward pass is asked for after all, which then forms the same gradient from it.
+// written back (26000 x 32768: 591 -> 297 us; the written half was the gradient), and its log-sum-exp and target are kept in case a
+// backward pass is asked for after all, which then forms the same gradient from them (the caller's targets may be gone by then).
 // ------------------------------------------------------------------------------------------------
 __device__ __forceinline__ float block_reduce(float v, bool is_max, float* sh) {
   v = is_max ? wave_max(v) : wave_sum(v);
@@ -376,13 +376,16 @@ __device__ __forceinline__ float block_reduce(float v, bool is_max, float* sh) {
 enum XentForm { kLossAndGrad, kLossOnly, kGradOnly };
 template <int NCH, XentForm FORM>
 __global__ void __launch_bounds__(kThreads) softmax_xent_kernel(half_t* __restrict__ logits, const int32_t* __restrict__ targets,
-                                                                float* __restrict__ row_loss, float* __restrict__ row_lse, int V, int pad_id,
-                                                                float eps_ls, float loss_scale) {
+                                                                float* __restrict__ row_loss, float* __restrict__ row_lse,
+                                                                int32_t* __restrict__ row_target, int V, int pad_id, float eps_ls,
+                                                                float loss_scale) {
   __shared__ float sh[kWavesPerBlock];
   const int row = blockIdx.x;
   const int chunks = V >> 3;
   half_t* z = logits + (size_t)row * V;
   const int y = targets[row];
+  if constexpr (FORM == kLossOnly)
+    if (threadIdx.x == 0) row_target[row] = y;
   if (y == pad_id) {  // padding positions contribute neither loss nor gradient
     if constexpr (FORM != kLossOnly)
       for (int c = threadIdx.x; c < chunks; c += kThreads) st_half8(z + c * 8, zero_half8());
@@ -1003,12 +1006,13 @@ int launch_colsum(const half_t* src, int ld, half_t* dst, float* partial, int ro
 
 namespace {
 template <XentForm FORM>
-int launch_xent_rows(half_t* logits, const int32_t* targets, float* row_loss, float* row_lse, int rows, int V, int pad_id, float eps_ls,
-                     float loss_scale, hipStream_t stream) {
+int launch_xent_rows(half_t* logits, const int32_t* targets, float* row_loss, float* row_lse, int32_t* row_target, int rows, int V, int pad_id,
+                     float eps_ls, float loss_scale, hipStream_t stream) {
   const dim3 grid(rows), block(kThreads);
   const int nch = ceil_div(V / 8, kThreads);
 #define NMT_XENT(N) \
-  hipLaunchKernelGGL((softmax_xent_kernel<N, FORM>), grid, block, 0, stream, logits, targets, row_loss, row_lse, V, pad_id, eps_ls, loss_scale)
+  hipLaunchKernelGGL((softmax_xent_kernel<N, FORM>), grid, block, 0, stream, logits, targets, row_loss, row_lse, row_target, V, pad_id, eps_ls, \
+                     loss_scale)
   if (nch <= 1) NMT_XENT(1);
   else if (nch <= 4) NMT_XENT(4);
   else if (nch <= 16) NMT_XENT(16);
@@ -1021,20 +1025,21 @@ int launch_xent_rows(half_t* logits, const int32_t* targets, float* row_loss, fl
 }  // namespace
 
 int launch_softmax_xent(half_t* logits, const int32_t* targets, float* row_loss, int rows, int V, int pad_id, float eps_ls,
-                        float loss_scale, float* loss_sum, int32_t* ntok, hipStream_t stream, float* row_lse) {
+                        float loss_scale, float* loss_sum, int32_t* ntok, hipStream_t stream, float* row_lse, int32_t* row_target) {
   NMT_REQUIRE(rows > 0 && V >= 8 && V % 8 == 0 && V <= 65536, "softmax_xent: V=%d must be a multiple of 8 in [8, 65536]", V);
   NMT_REQUIRE(logits && targets && row_loss && loss_sum && ntok && aligned16(logits), "softmax_xent: null or misaligned pointer");
-  if (int rc = row_lse ? launch_xent_rows<kLossOnly>(logits, targets, row_loss, row_lse, rows, V, pad_id, eps_ls, loss_scale, stream)
-                       : launch_xent_rows<kLossAndGrad>(logits, targets, row_loss, nullptr, rows, V, pad_id, eps_ls, loss_scale, stream))
+  NMT_REQUIRE(!row_lse == !row_target, "softmax_xent: the loss alone needs room for both the log-sum-exps and the targets");
+  if (int rc = row_lse ? launch_xent_rows<kLossOnly>(logits, targets, row_loss, row_lse, row_target, rows, V, pad_id, eps_ls, loss_scale, stream)
+                       : launch_xent_rows<kLossAndGrad>(logits, targets, row_loss, nullptr, nullptr, rows, V, pad_id, eps_ls, loss_scale, stream))
     return rc;
   hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, stream, row_loss, targets, rows, pad_id, loss_sum, ntok);
   NMT_LAUNCH_CHECK();
   return NMT_OK;
 }
-int launch_softmax_grad(half_t* logits, const int32_t* targets, float* row_lse, int rows, int V, int pad_id, float eps_ls, float loss_scale,
+int launch_softmax_grad(half_t* logits, const int32_t* row_target, float* row_lse, int rows, int V, int pad_id, float eps_ls, float loss_scale,
                         hipStream_t stream) {
-  NMT_REQUIRE(rows > 0 && V >= 8 && V % 8 == 0 && V <= 65536 && logits && targets && row_lse && aligned16(logits), "softmax_grad: bad arguments");
-  return launch_xent_rows<kGradOnly>(logits, targets, nullptr, row_lse, rows, V, pad_id, eps_ls, loss_scale, stream);
+  NMT_REQUIRE(rows > 0 && V >= 8 && V % 8 == 0 && V <= 65536 && logits && row_target && row_lse && aligned16(logits), "softmax_grad: bad arguments");
+  return launch_xent_rows<kGradOnly>(logits, row_target, nullptr, row_lse, nullptr, rows, V, pad_id, eps_ls, loss_scale, stream);
 }
 
 namespace {

@@ -510,6 +510,30 @@ def test_backward_after_a_pass_without_training_gives_the_same_bits(vocab):
         sess.close()
 
 
+@pytest.mark.parametrize("form", ["padded", "packed"])
+def test_targets_may_be_overwritten_between_a_pass_without_training_and_its_backward(form):
+    """The gradient of a forward pass belongs to the targets that pass was given: a caller that reuses their buffer before it
+    asks for the backward pass gets the same bits (ids from the start, the end and the middle of the vocabulary, and padding)."""
+    model = dict(enc_layers=1, dec_layers=1, d_model=64, n_heads=4, d_ff=128, vocab=264, dropout=0.0)
+    sess = Session(model, I.init_weights(seed=4, **model), max_sentences=8)
+    try:
+        batch = I.tiny_batch(seed=12, B=6, S=14, T=11, vocab=264)
+        db = sess.to_device(batch) if form == "padded" else sess.pack([batch])[0]
+        seen = []
+        for other in (None, 0, 7, 263, 1):
+            kept = db["tgt_out"].clone()
+            sess.forward_loss(db, 64.0, 1, 0, training=False)
+            if other is not None:
+                db["tgt_out"].fill_(other)
+            sess.backward()
+            seen.append(sess.g16.clone())
+            db["tgt_out"].copy_(kept)
+        assert float(seen[0].float().abs().max()) > 0
+        assert all(torch.equal(g.view(torch.int16), seen[0].view(torch.int16)) for g in seen[1:])
+    finally:
+        sess.close()
+
+
 def test_packed_entry_point_clamps_inconsistent_lengths_and_rejects_bad_totals():
     """Lengths on the device that exceed what the host announced are cut to the announced totals (no
     access outside the buffers; the result is then undefined but finite buffers stay in bounds);
