@@ -201,6 +201,8 @@ constexpr int kMaxWgrad = 8;
 // (may be null: never cut).  tile, splits: 0 = chosen by cost.
 int launch_wgrad_group(const WgradProduct* products, int n, float out_scale, float* partial, int64_t partial_floats, hipStream_t stream,
                        int tile = 0, int splits = 0);
+// Partial sums that a group with `per_split` floats of results and column sums, over up to `rows` positions, can use of `most`.
+int64_t wgrad_group_floats(int64_t per_split, int64_t rows, int64_t most);
 
 // fp32 product on the matrix cores, for the benchmark's fp32 comparison leg (not used by the training step)
 int launch_gemm_f32(const float* A, bool a_t, int lda, const float* B, bool b_t, int ldb, float* C, int ldc, int M, int N, int K,
@@ -242,7 +244,8 @@ int launch_attention_bwd(const half_t* Q, int ldq, const half_t* K, int ldk, con
 int launch_residual_layernorm_fwd(const half_t* sub, const half_t* resid, const half_t* gamma, const half_t* beta,
                                   half_t* out, float* stats, int rows, int d, float eps, const DropDev& drop,
                                   hipStream_t stream);
-int64_t layernorm_bwd_scratch_floats(int d);
+int64_t layernorm_bwd_scratch_floats(int d);                        // partial sums of a call of any number of rows ...
+int64_t layernorm_bwd_partial_floats(int most_rows, int d);         // ... of up to `most_rows`
 // Partial rows of column sums as a kernel left them: `rows` rows of up to three quantities, and where their totals go.
 struct ColumnSums {
   const float* partial;

@@ -1271,13 +1271,16 @@ double group_us(int tile, const WgradProduct* p, int n, int splits, int cus, dou
 // only the embedding kernels beside it, and with one stream there is nothing).  Weights of 0 to 4 for it measured the
 // same updates within 1 to 2 %, this one at the lower end throughout.
 constexpr double kGroupLatencyWeight = 0.5;
+// The numbers of k splits looked at, and the fewest positions a split may have.
+constexpr int kGroupMaxSplits = 32, kGroupMinRows = 256;
+int next_splits(int z) { return z < 4 ? z + 1 : z * 2; }
 void choose_group(const WgradProduct* p, int n, int64_t most, int cus, int& tile, int& splits) {
   int shortest = p[0].K, best_tile = tile ? tile : kGroup256, best_splits = splits ? splits : 1;
   for (int i = 1; i < n; ++i) shortest = p[i].K < shortest ? p[i].K : shortest;
   double best = 0.;
   for (int t = tile ? tile : 1; t <= (tile ? tile : kGroupTiles); ++t) {
-    for (int z = splits ? splits : 1; z <= (splits ? splits : 32); z = z < 4 ? z + 1 : z * 2) {
-      if (!splits && z > 1 && (z > most || shortest / z < 256)) break;
+    for (int z = splits ? splits : 1; z <= (splits ? splits : kGroupMaxSplits); z = next_splits(z)) {
+      if (!splits && z > 1 && (z > most || shortest / z < kGroupMinRows)) break;
       double cu_us;
       const double us = group_us(t, p, n, z, cus, cu_us), score = kGroupLatencyWeight * us + cu_us / cus;
       if (best == 0. || score < best) {
@@ -1392,6 +1395,12 @@ int launch_gemm(const half_t* A, bool a_t, int lda, const half_t* B, bool b_t, i
   return timed_launch(2.0 * M * N * K, stream, [&] {
     return launch_gemm_impl(A, a_t, lda, B, b_t, ldb, C, ldc, M, N, K, ep, stream, partial, partial_floats, splits);
   });
+}
+
+int64_t wgrad_group_floats(int64_t per_split, int64_t rows, int64_t most) {
+  int64_t used = 0;
+  for (int z = 2; z <= kGroupMaxSplits && rows / z >= kGroupMinRows && z * per_split <= most; z = next_splits(z)) used = z * per_split;
+  return used;
 }
 
 int launch_wgrad_group(const WgradProduct* products, int n, float out_scale, float* partial, int64_t partial_floats, hipStream_t stream,

@@ -95,6 +95,8 @@ struct DecP { AttnP self; LnP ln1; AttnP cross; LnP ln2; FfnP ffn; LnP ln3; };
 
 // dropout sites: a site id selects an independent random stream
 constexpr int kMaxSegments = NMT_MAX_SEGMENTS;
+constexpr int64_t kWgradPartialFloats = 16ll << 20;
+constexpr int64_t kVocabCuts = 16, kVocabCutFrom = 2048;  // most pieces of the vocabulary's input gradient, and the shortest
 constexpr uint32_t kSiteEmbSrc = 0, kSiteEmbTgt = 1;
 constexpr uint32_t kKindSelfRes = 0, kKindCrossRes = 1, kKindFfnAct = 2, kKindFfnRes = 3;
 inline uint32_t layer_site(int layer_index, uint32_t kind) { return 16u * (1u + (uint32_t)layer_index) + kind; }
@@ -110,7 +112,7 @@ struct Plan {
   int64_t x0, y0, logits, rowloss, rowlse, targets;
   std::vector<EncW> enc;
   std::vector<DecW> dec;
-  int64_t dx_dec, dx_enc, dy, dsub[2][3], dO, dqkv[2], dh[2], dq[2], dkv[2], lnpart[2][3], embscratch, wgpart, wgpart_floats;
+  int64_t dx_dec, dx_enc, dy, dsub_dec, dsub_enc, dO, dqkv[2], dh[2], dq[2], dkv[2], lnpart[2][3], embscratch, wgpart, wgpart_floats, wg_most;
   int64_t total;
 };
 
@@ -248,19 +250,27 @@ int64_t plan_workspace(const nmt_ctx* c, const GroupDims& gd, Plan& p) {
   p.dx_enc = take(Ns * d * h2);
   p.dO = take(Nm * d * h2);
   p.dy = take(Nm * d * h2);
+  // The gradient at a sub-layer's output goes where the output of the sub-layer before it (in the order of the backward pass) was,
+  // which that one's LayerNorm backward was the last to read.  The encoder's first goes where the keys and values of the last
+  // decoder layer were (read for the last time by its attention), the decoder's first has a place of its own.
+  p.dsub_dec = take(Nt * d * h2);
+  p.dsub_enc = p.dec[0].kv;
   for (int b = 0; b < 2; ++b) {  // two sets: the weight gradients of one layer overlap the next layer
-    for (int64_t& sub : p.dsub[b]) sub = take(Nm * d * h2);
-    for (int64_t& part : p.lnpart[b]) part = take(layernorm_bwd_scratch_floats((int)d) * f4);
+    for (int64_t& part : p.lnpart[b]) part = take(layernorm_bwd_partial_floats((int)Nm, (int)d) * f4);
     p.dqkv[b] = take(Nm * 3 * d * h2);
     p.dh[b] = take(Nm * F * h2);
     p.dq[b] = take(Nt * d * h2);
     p.dkv[b] = take(Ns * 2 * d * h2);
   }
   p.embscratch = take(embed_bwd_scratch_ints((int)V, (int)(Ns + Nt), (int)d) * (int64_t)sizeof(int32_t));
-  // fp32 partial sums of a layer's weight gradients cut along the (long) position axis: 4 pieces of a decoder layer's, up to 32 of
-  // a small one's
+  // fp32 partial sums of a layer's weight gradients cut along the (long) position axis (at most 4 pieces of a decoder layer's, up to 32
+  // of a small one's), and of the vocabulary's input gradient before them.  What the first can use of 64 MB is set aside; more
+  // is there where the logits take more, whose place is free by the time the first layer's weight gradients run.
   const int64_t layer = 2 * F * (d + 1) + 8 * d * (d + 1);
-  p.wgpart_floats = std::max(4 * layer, std::min<int64_t>(32 * layer, 16ll << 20));
+  p.wg_most = std::max(4 * layer, std::min(32 * layer, kWgradPartialFloats));
+  const int64_t aside = std::min(p.wg_most, kWgradPartialFloats), enc_layer = 2 * F * d + F + 4 * d * d + 5 * d;
+  const int64_t vocab_cut = V / kVocabCutFrom < 3 ? 0 : std::min<int64_t>(kVocabCuts * Nt * d, 2ll * device_info().cus * 128 * 128);
+  p.wgpart_floats = std::min(aside, std::max({wgrad_group_floats(enc_layer, Ns, aside), wgrad_group_floats(enc_layer + 4 * d * d + 4 * d, Nt, aside), vocab_cut}));
   p.wgpart = take(p.wgpart_floats * f4);
   p.total = cur;
   return cur;
@@ -709,6 +719,14 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   const AttnWork wl_ss = attention_work(r.ws<int32_t>(p.wl_ss), Bt, Ns, 0), wl_tt = attention_work(r.ws<int32_t>(p.wl_tt), Bt, Nt, 0),
                  wl_ts = attention_work(r.ws<int32_t>(p.wl_ts), Bt, Nt, Ns);
 
+  // where the group of a layer's weight gradients leaves partial sums: in the gradient of the logits if that is the larger place
+  // (both kernels that read it lie before the first group in the order of either stream)
+  float* wgpart = r.ws<float>(p.wgpart);
+  int64_t wgpart_floats = p.wgpart_floats;
+  if (const int64_t floats = (int64_t)Nt * V / 2; floats > wgpart_floats) {
+    wgpart = r.ws<float>(p.logits);
+    wgpart_floats = std::min(floats, p.wg_most);
+  }
   int set = 0, sub_at = 0;  // temporaries of the current layer; its sub-layers so far
   bool used[2] = {false, false};
   half_t *dym = nullptr, *dqkv = nullptr, *dhid = nullptr, *dq = nullptr, *dkv = nullptr;
@@ -729,8 +747,11 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     dkv = r.ws<half_t>(p.dkv[set]);
     return NMT_OK;
   };
-  auto begin_sublayer = [&]() {
-    half_t* sub = r.ws<half_t>(p.dsub[set][sub_at]);
+  half_t* next_dsub = r.ws<half_t>(p.dsub_dec);
+  // (`output`: the saved output of the sub-layer, read for the last time by the LayerNorm backward that comes next)
+  auto begin_sublayer = [&](const half_t* output) {
+    half_t* sub = next_dsub;
+    next_dsub = const_cast<half_t*>(output);
     lnpart = r.ws<float>(p.lnpart[set][sub_at++]);
     dy = dropping ? r.ws<half_t>(p.dy) : sub;
     dym = dropping ? sub : nullptr;
@@ -749,7 +770,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   // (called when the last gradient that the layer's leaves read has been enqueued)
   auto flush_leaves = [&]() -> int {
     NMT_TRY(fork());
-    NMT_TRY(launch_wgrad_group(leaves, n_leaves, c->gscale, r.ws<float>(p.wgpart), p.wgpart_floats, sd));
+    NMT_TRY(launch_wgrad_group(leaves, n_leaves, c->gscale, wgpart, wgpart_floats, sd));
     n_leaves = 0;
     NMT_TRY(launch_layernorm_param_grads(ln_sums, sub_at, d, c->gscale, sd));
     if (two_streams) NMT_HIP_CHECK(hipEventRecord(c->ev_done[set], sd));
@@ -759,7 +780,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   // feed-forward sub-layer: out = LN(x_in + drop(relu(x_in W1^T + b1) W2^T + b2)); dx holds d out on entry, d x_in on exit
   auto ffn_bwd = [&](half_t* dx, int N, bool tgt, const half_t* x_in, const half_t* hact, const half_t* sub, const float* stats,
                      const FfnP& f, const LnP& ln, uint32_t site_res) -> int {
-    begin_sublayer();
+    begin_sublayer(sub);
     NMT_TRY(launch_residual_layernorm_bwd(dx, sub, x_in, r.w(ln.g), stats, dy, dym, r.g(ln.g), r.g(ln.b), r.g(f.b2), lnpart, N, d,
                                           r.drop(site_res, tgt, k.dropout), st, ln_sums[sub_at - 1]));
     leaf(dsub, N, d, hact, F, f.w2);
@@ -776,7 +797,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   auto self_bwd = [&](half_t* dx, int N, bool tgt, const half_t* x_in, const half_t* qkv, const half_t* o, const float* lse,
                       const half_t* sub, const float* stats, const AttnP& a, const LnP& ln, uint32_t site_res, const int32_t* key_ids,
                       int causal) -> int {
-    begin_sublayer();
+    begin_sublayer(sub);
     NMT_TRY(launch_residual_layernorm_bwd(dx, sub, x_in, r.w(ln.g), stats, dy, dym, r.g(ln.g), r.g(ln.b), r.g(a.bo), lnpart, N, d,
                                           r.drop(site_res, tgt, k.dropout), st, ln_sums[sub_at - 1]));
     leaf(dsub, N, d, o, d, a.wo);
@@ -810,7 +831,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   // at least 2048 (two pieces of 3000 x 1024 gained nothing).  The partial sums lie where the weight gradients' do, whose first group
   // waits for kernels behind this one.  Whole update on 379 tokens 4395 -> 4363 us, Transformer-base on 2990 3960 -> 3917.
   const int64_t tiles = (int64_t)ceil_div(Nt, 128) * ceil_div(d, 128), fits = p.wgpart_floats / ((int64_t)Nt * d);
-  const int64_t cuts = std::min<int64_t>({2 * device_info().cus / tiles, V / 2048, fits, 16});
+  const int64_t cuts = std::min<int64_t>({2 * device_info().cus / tiles, V / kVocabCutFrom, fits, kVocabCuts});
   NMT_TRY(launch_gemm(dlogits, false, V, r.w(c->embed), true, d, dx, d, Nt, d, V, GemmEpilogue{}, st, r.ws<float>(p.wgpart), p.wgpart_floats,
                       cuts >= 3 ? (int)cuts : 1));
 
@@ -827,7 +848,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     NMT_TRY(ffn_bwd(dx, Nt, true, r.ws<half_t>(W.x2), r.ws<half_t>(W.h), r.ws<half_t>(W.s3), r.ws<float>(W.st3), P.ffn, P.ln3,
                     layer_site(li, kKindFfnRes)));
     // encoder-decoder attention
-    begin_sublayer();
+    begin_sublayer(r.ws<half_t>(W.s2));
     NMT_TRY(launch_residual_layernorm_bwd(dx, r.ws<half_t>(W.s2), r.ws<half_t>(W.x1), r.w(P.ln2.g), r.ws<float>(W.st2), dy, dym,
                                           r.g(P.ln2.g), r.g(P.ln2.b), r.g(P.cross.bo), lnpart, Nt, d,
                                           r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st, ln_sums[sub_at - 1]));
@@ -858,6 +879,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   if (beside) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_denc, 0));
 
   // ---- encoder ----
+  next_dsub = r.ws<half_t>(p.dsub_enc);
   for (int l = k.enc_layers - 1; l >= 0; --l) {
     const EncP& P = c->enc[l];
     const EncW& W = p.enc[l];

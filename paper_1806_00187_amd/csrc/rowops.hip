@@ -131,7 +131,7 @@ __global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(const half_t* __re
 
 // Backward.  Each wavefront walks groups of ROWS rows (their loads are all issued before anything is
 // computed), keeps per-lane column sums for dgamma, dbeta and the bias gradient in registers, and the block
-// writes one partial row per quantity (pitch NCH*512 floats, column-indexed).  The three inputs of a row stay in
+// writes one partial row of d floats per quantity.  The three inputs of a row stay in
 // registers as the fp16 values they were loaded as and are widened where they are used (twice: row statistics,
 // then the result), which keeps the kernel at four wavefronts per SIMD.
 constexpr int kLnBwdMaxBlocks = 1024;
@@ -257,8 +257,11 @@ __global__ void __launch_bounds__(kThreads) res_ln_bwd_kernel(const half_t* __re
     }
     __syncthreads();
   }
-  floatx4* dst = reinterpret_cast<floatx4*>(partial + (size_t)blockIdx.x * 3 * NCH * 512);
-  for (int i = threadIdx.x; i < 3 * NCH * 128; i += kThreads) dst[i] = red4[i];
+  floatx4* dst = reinterpret_cast<floatx4*>(partial + (size_t)blockIdx.x * 3 * d);
+  const int quads = d >> 2;
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+    for (int i = threadIdx.x; i < quads; i += kThreads) dst[q * quads + i] = red4[q * NCH * 128 + i];
 }
 
 // dst[k][col] = fp16(scale * sum_b partial[b][k][col]), k = 0..nq-1, for up to kMaxColumnSums buffers of partial rows in one
@@ -912,6 +915,23 @@ int launch_residual_layernorm_fwd(const half_t* sub, const half_t* resid, const 
 
 int64_t layernorm_bwd_scratch_floats(int d) { return (int64_t)kLnBwdMaxBlocks * 3 * ln_nch(d) * 512; }
 
+namespace {
+// One row per wavefront while that is at most one work-group per compute unit (half the code to fetch and a shorter chain: 380 rows x
+// 1024, whole update 4370 -> 4304 us; 260 x 64: 560 -> 540); from there on two, because every work-group leaves a partial row of
+// sums (3000 rows with one: 0.5 to 1 % slower).
+int ln_bwd_rows_per_wave(int rows) { return ceil_div(rows, kWavesPerBlock) <= device_info().cus ? 1 : 2; }
+// a grid that is resident at once (3 or 4 work-groups per compute unit fit, by registers): no second, partly filled round
+int ln_bwd_blocks(int rows, int d) {
+  const int resident = (ln_nch(d) >= 2 ? 3 : 4) * device_info().cus;
+  return min(min(kLnBwdMaxBlocks, resident), ceil_div(rows, kWavesPerBlock * ln_bwd_rows_per_wave(rows)));
+}
+}  // namespace
+
+int64_t layernorm_bwd_partial_floats(int most_rows, int d) {
+  const int one_row = kWavesPerBlock * device_info().cus;  // (the most rows that go one to a wavefront: they leave the most partial rows for their number)
+  return (int64_t)max(ln_bwd_blocks(most_rows, d), ln_bwd_blocks(min(most_rows, one_row), d)) * 3 * d;
+}
+
 int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const half_t* resid, const half_t* gamma,
                                   const float* stats, half_t* dy, half_t* dym, half_t* dgamma, half_t* dbeta,
                                   half_t* dbias, float* partial, int rows, int d, const DropDev& drop,
@@ -922,14 +942,7 @@ int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const h
               "layernorm_bwd: misaligned pointer");
   NMT_REQUIRE(!drop.thr || (drop.n_pos > 0 && dym), "layernorm_bwd: dropout needs the masked output and positions per sentence");
   const int nch = ln_nch(d);
-  // a grid that is resident at once (3 or 4 work-groups per compute unit fit, by registers): no second, partly filled round
-  const int resident = (nch >= 2 ? 3 : 4) * device_info().cus;
-  const int most = min(kLnBwdMaxBlocks, resident);
-  // One row per wavefront while that is at most one work-group per compute unit (half the code to fetch and a shorter chain: 380 rows x
-  // 1024, whole update 4370 -> 4304 us; 260 x 64: 560 -> 540); from there on two, because every work-group leaves a partial row of
-  // sums (3000 rows with one: 0.5 to 1 % slower).
-  const int per_wave = ceil_div(rows, kWavesPerBlock) <= device_info().cus ? 1 : 2;
-  const int nblk = min(most, ceil_div(rows, kWavesPerBlock * per_wave));
+  const int per_wave = ln_bwd_rows_per_wave(rows), nblk = ln_bwd_blocks(rows, d);
   const dim3 grid(nblk), block(kThreads);
   const size_t smem = (size_t)3 * nch * 512 * sizeof(float);
 #define NMT_LN_BWD(N, R) hipLaunchKernelGGL((res_ln_bwd_kernel<N, R>), grid, block, smem, stream, dout, sub, resid, gamma, stats, dy, dym, partial, rows, d, drop)
@@ -947,7 +960,7 @@ int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const h
   return NMT_OK;
 }
 int launch_layernorm_param_grads(const ColumnSums* sums, int n, int d, float scale, hipStream_t stream) {
-  return launch_finalize(sums, n, 3, d, ln_nch(d) * 512, scale, stream);
+  return launch_finalize(sums, n, 3, d, d, scale, stream);
 }
 
 int64_t colsum_scratch_floats(int cols) { return (int64_t)kColsumMaxSplits * cols; }

@@ -491,6 +491,47 @@ def test_packed_pass_with_every_sentence_length_class_matches_the_oracle():
         sess.close()
 
 
+def _pass_bits(sess, db, one_stream, fill):
+    """Loss, token count, gradient and decoder output of one training pass in a workspace whose bytes all held `fill` and behind which
+    nothing may be written."""
+    sess._reserve_for(db)
+    need = sess.workspace.numel()
+    guarded = torch.full((need + 65536,), fill, dtype=torch.uint8, device=sess.device)
+    sess.workspaces[0] = guarded[:need]
+    sess._bind(0)
+    sess.g16.fill_(float("nan"))
+    try:
+        A.nmt_tuning("one_stream", int(one_stream))
+        sess.forward_loss(db, 32.0, 3, 0)
+        out = sess.activation("dec%d.out" % (sess.model["dec_layers"] - 1)).clone()
+        sess.backward()
+        torch.cuda.synchronize()
+    finally:
+        A.nmt_tuning("defaults")
+    assert bool((guarded[need:] == fill).all())
+    return sess.loss_sum.clone(), sess.ntok.clone(), sess.g16.clone(), out
+
+
+# Passes above the line from which the second stream is used, with products over the encoder output beside the decoder's chain.
+# One to three decoder layers: a layer's temporaries are used again two layers later.  180 sentences: weight gradients cut along
+# the positions, whose partial sums lie in a place of their own (136 symbols) or in that of the logits.
+@pytest.mark.parametrize("enc_layers,dec_layers,d,vocab,dropout,B", [(2, 1, 256, 2056, 0.1, 45), (1, 2, 256, 264, 0.0, 45), (3, 3, 256, 2056, 0.0, 45),
+                                                                     (2, 3, 256, 12296, 0.2, 45), (2, 2, 64, 136, 0.1, 180), (2, 2, 64, 1000, 0.0, 180)])
+def test_second_stream_and_what_the_workspace_held_change_no_bit(enc_layers, dec_layers, d, vocab, dropout, B):
+    model = dict(enc_layers=enc_layers, dec_layers=dec_layers, d_model=d, n_heads=4, d_ff=4 * d, vocab=vocab, dropout=dropout)
+    sess = Session(model, I.init_weights(seed=9, perturb=0.05, **model), max_sentences=256, max_len=64)
+    try:
+        batches = [I.tiny_batch(seed=60 + i, B=B, S=S, T=T, vocab=vocab, short_rows=3, short_by=4) for i, (B, S, T) in enumerate([(B, 38, 40), (3, 7, 9)])]
+        (pk,) = sess.pack(batches)
+        want = _pass_bits(sess, pk, True, 0)
+        assert bool(torch.isfinite(want[2]).all()) and float(want[2].float().abs().max()) > 0
+        for one_stream, fill in ((False, 0), (False, 255), (True, 255), (False, 255)):
+            got = _pass_bits(sess, pk, one_stream, fill)
+            assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(got, want)), (one_stream, fill)
+    finally:
+        sess.close()
+
+
 @pytest.mark.parametrize("vocab", [264, 2056, 9000])
 def test_backward_after_a_pass_without_training_gives_the_same_bits(vocab):
     """A forward pass without training computes the loss alone and keeps the logits; without dropout, loss and gradients must be

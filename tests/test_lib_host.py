@@ -66,6 +66,30 @@ def test_workspace_grows_with_the_batch_and_rejects_bad_shapes():
     A.nmt_destroy(ctx)
 
 
+# (layers, width, heads, feed-forward width, vocabulary), then B, S, T and the bytes callers have sized a workspace by: what a
+# pass took with 64 MB of weight-gradient partial sums and two sets of sub-layer gradients
+@pytest.mark.parametrize("model,B,S,T,known", [
+    ((2, 2, 64, 4, 256, 1000), 8, 16, 16, 75683328), ((2, 2, 64, 4, 256, 1000), 100, 35, 35, 121707264),
+    ((2, 2, 256, 4, 1024, 2056), 45, 40, 40, 165490944), ((2, 2, 256, 4, 1024, 2056), 300, 30, 30, 525396224),
+    ((6, 6, 512, 8, 2048, 32768), 1, 1, 1, 78156544), ((6, 6, 512, 8, 2048, 32768), 130, 27, 27, 1062640640),
+    ((6, 6, 512, 8, 2048, 32768), 300, 30, 30, 2602927616), ((6, 6, 512, 8, 2048, 32768), 1000, 50, 50, 14105768192),
+    ((6, 6, 1024, 16, 4096, 32768), 20, 20, 18, 275609088), ((6, 6, 1024, 16, 4096, 32768), 130, 27, 27, 1826796032),
+    ((6, 6, 1024, 16, 4096, 32768), 1000, 50, 50, 24852256000), ((6, 6, 1024, 16, 4096, 40000), 130, 27, 27, 1877622528),
+    ((6, 1, 512, 8, 2048, 32768), 300, 30, 30, 1769524736), ((6, 6, 768, 12, 3072, 32768), 300, 30, 30, 3577560064),
+    ((2, 2, 2048, 16, 8192, 32768), 150, 40, 40, 2696043264), ((1, 1, 16, 1, 8, 8), 2000, 100, 100, 387694592)])
+def test_workspace_takes_no_more_than_callers_have_sized_it_by(model, B, S, T, known):
+    layout = dict(zip(("enc_layers", "dec_layers", "d_model", "n_heads", "d_ff", "vocab"), model))
+    ctx = A.nmt_create(**_cfg(layout, max_sentences=4096))
+    try:
+        assert 0 < A.nmt_workspace_bytes(ctx, B, S, T) <= known
+        sizes = [A.nmt_workspace_bytes(ctx, b, S, T) for b in range(max(1, B - 300), B + 1)]
+        assert sizes == sorted(sizes)                       # one sized for the largest pass serves all smaller ones
+        for side in ((S, T + 1), (S + 1, T)):
+            assert A.nmt_workspace_bytes(ctx, B, *side) >= sizes[-1]
+    finally:
+        A.nmt_destroy(ctx)
+
+
 @pytest.mark.parametrize("bad", [dict(d_model=60), dict(n_heads=3), dict(vocab=1001), dict(dropout=1.0), dict(max_len=4096),
                                  dict(d_ff=10), dict(pad_id=-1), dict(ln_eps=0.0), dict(attn_dropout=0.1)])
 def test_create_rejects_invalid_configurations(bad):
