@@ -414,7 +414,8 @@ extern "C" int nmt_bind(nmt_ctx* ctx, void* d_w16, void* d_g16, float* d_master3
 namespace {
 
 // The second stream and the events that order the two.  (They come into being when they are first needed: a stream that exists
-// takes a place on one of the process's few hardware queues even if nothing is ever enqueued on it.)
+// takes a place on one of the process's few hardware queues even if nothing is ever enqueued on it.  Making them is no work on a
+// stream, so a first pass may do it while the caller's stream is being captured; the second stream then joins the capture.)
 int ensure_second_stream(nmt_ctx* c) {
   if (!c->ev_fork) {
     hipEvent_t* const events[] = {&c->ev_join, &c->ev_embed, &c->ev_kv, &c->ev_denc, &c->ev_done[0], &c->ev_done[1], &c->ev_fork};
@@ -625,12 +626,7 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
   auto project_kv = [&](const Run& on, int l) {
     return on.linear(enc_out, Ns, d, c->dec[l].cross.wkv, c->dec[l].cross.bkv, 2 * d, r.ws<half_t>(p.dec[l].kv));
   };
-  bool beside = encoder_products_beside(c);
-  if (beside && !c->side) {  // (a stream is not made while the caller's is being captured: such a first pass keeps to one)
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    beside = hipStreamIsCapturing(st, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-  }
+  const bool beside = encoder_products_beside(c);
   if (beside) {
     NMT_TRY(ensure_second_stream(c));
     const Run side{c, c->side};

@@ -532,6 +532,48 @@ def test_second_stream_and_what_the_workspace_held_change_no_bit(enc_layers, dec
         sess.close()
 
 
+@pytest.mark.parametrize("first", ["captured", "eager"])
+def test_a_captured_pass_gives_the_bits_of_an_eager_one_at_every_replay(first):
+    """Forward and backward recorded into one graph, as the first pass of a context (which makes its second stream meanwhile) and
+    after an eager pass; eager passes on other ids between the replays."""
+    model = dict(enc_layers=2, dec_layers=2, d_model=256, n_heads=4, d_ff=1024, vocab=2056, dropout=0.1)
+    weights = I.init_weights(seed=9, perturb=0.05, **model)
+    batches = [I.tiny_batch(seed=70 + i, B=40, S=38, T=40, vocab=2056, short_rows=3, short_by=4) for i in range(2)]
+
+    def one_pass(sess, pk):
+        sess.forward_loss(pk, 32.0, 3)
+        sess.backward()
+
+    def state(sess):
+        torch.cuda.synchronize()
+        return [t.clone() for t in (sess.loss_sum, sess.ntok, sess.g16)]
+
+    eager = Session(model, weights, max_sentences=64, max_len=64)
+    sess = Session(model, weights, max_sentences=64, max_len=64)
+    try:
+        want = []
+        for b in batches:
+            one_pass(eager, eager.pack([b])[0])
+            want.append(state(eager))
+        pks = [sess.pack([b])[0] for b in batches]
+        sess._reserve_for(pks[0])
+        if first == "eager":
+            one_pass(sess, pks[0])
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            one_pass(sess, pks[0])
+        for _ in range(3):
+            sess.g16.fill_(float("nan"))
+            graph.replay()
+            assert all(torch.equal(a, b) for a, b in zip(state(sess), want[0]))
+            one_pass(sess, pks[1])
+            assert all(torch.equal(a, b) for a, b in zip(state(sess), want[1]))
+    finally:
+        eager.close()
+        sess.close()
+
+
 @pytest.mark.parametrize("vocab", [264, 2056, 9000])
 def test_backward_after_a_pass_without_training_gives_the_same_bits(vocab):
     """A forward pass without training computes the loss alone and keeps the logits; without dropout, loss and gradients must be
