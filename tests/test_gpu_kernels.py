@@ -144,6 +144,50 @@ def test_weight_gradient_groups_match_oracle(tile, splits):
             A.nmt_op_wgrad_group(products, 0.5, partial[:-1], tile, splits)
 
 
+# the library's own choice, at numbers of positions where it cuts a small layer's products: room for 32 pieces, for fewer than it
+# would take, and for one
+@pytest.mark.parametrize("room", [32, 5, 1])
+def test_weight_gradient_group_chooses_its_pieces_within_the_buffer(room):
+    rng = np.random.default_rng(room)
+    shapes = [(64, 136, 8200, True), (136, 64, 8197, True), (64, 64, 8205, True), (72, 136, 8200, False)]
+    products, want = [], []
+    for n_out, n_in, rows, bias in shapes:
+        dy, x = f16(rng.normal(size=(rows, n_out)) / math.sqrt(rows)), f16(rng.normal(size=(rows, n_in)))
+        gw = torch.full((n_out, n_in), float("nan"), dtype=torch.float16, device=DEV)
+        gb = torch.full((n_out,), float("nan"), dtype=torch.float16, device=DEV) if bias else None
+        products.append((dev16(dy), n_out, dev16(x), n_in, gw, n_in, gb, n_out, n_in, rows))
+        want.append((dy.T @ x, dy.sum(axis=0)))
+    piece = sum(n_out * (n_in + 1) for n_out, n_in, _, _ in shapes)
+    guarded = torch.full((room * piece + 4096,), float("nan"), dtype=torch.float32, device=DEV)
+    A.nmt_op_wgrad_group(products, 1.0, guarded[:room * piece])
+    for (n_out, n_in, rows, bias), (_, _, _, _, gw, _, gb, *_), (w, b) in zip(shapes, products, want):
+        assert_close16(host(gw), w, f"weight gradient {n_out}x{n_in}x{rows}")
+        if bias:
+            assert_close16(host(gb), b, f"bias gradient {n_out}x{rows}")
+    written = int((~torch.isnan(guarded[:room * piece])).sum())
+    per_piece = sum(n_out * (n_in + bias) for n_out, n_in, _, bias in shapes)
+    assert torch.isnan(guarded[room * piece:]).all()
+    assert written == 0 if room == 1 else (written % per_piece == 0 and 2 <= written // per_piece <= room), written / per_piece
+
+
+@pytest.mark.parametrize("tile", [1, 2, 3, 4])
+def test_bias_gradients_keep_denormal_halves_and_long_sums(tile):
+    """Column sums of the smallest positive halves (a sum of 2^-24 is exact, and zero if they were flushed), and of 53000 positions
+    of one sign: one fp32 sum per half of a column's positions, each of its 3313 additions (and the few within one) off by at most 2^-24 of the sum so far, before
+    the one rounding to fp16 (2^-11)."""
+    n, rows = 264, 1000
+    gw, gb = torch.zeros(n, 8, dtype=torch.float16, device=DEV), torch.full((n,), float("nan"), dtype=torch.float16, device=DEV)
+    dy, x = torch.full((rows, n), 2.0 ** -24, dtype=torch.float16, device=DEV), torch.ones(rows, 8, dtype=torch.float16, device=DEV)
+    A.nmt_op_wgrad_group([(dy, n, x, 8, gw, 8, gb, n, 8, rows)], 1.0, None, tile, 1)
+    assert (host(gb).astype(np.float64) == rows * 2.0 ** -24).all()
+    rows = 53000
+    dy = (torch.rand(rows, n, generator=torch.Generator(device=DEV).manual_seed(tile), device=DEV) * 0.1).half()
+    x = torch.zeros(rows, 8, dtype=torch.float16, device=DEV)
+    A.nmt_op_wgrad_group([(dy, n, x, 8, gw, 8, gb, n, 8, rows)], 1.0, None, tile, 1)
+    want = host(dy).astype(np.float64).sum(axis=0)
+    assert (np.abs(host(gb) - want) <= want * (2.0 ** -11 + 3320 * 2.0 ** -24)).all()
+
+
 def test_gemm_large_problem_with_a_small_tile_tail_keeps_epilogue_rows():
     """Enough rows for one full round of large tiles plus a remainder, which goes to a second launch
     with small tiles: bias, ReLU and the dropout counters of the remainder must be those of its rows."""
@@ -172,7 +216,7 @@ def test_gemm_large_problem_with_a_small_tile_tail_keeps_epilogue_rows():
 
 
 def test_gemm_persistent_form_matches_oracle_and_the_tile_per_work_group_form():
-    """Products of at least two large tiles per compute unit, no split along k and an epilogue that loads nothing per
+    """Products of more large tiles than compute units, no split along k and an epilogue that loads nothing per
     element run as one persistent work-group per compute unit that requests the next tile's first k-tiles before it
     stores the current one.  Ragged M, N and k; bias + ReLU and the k-major form against the oracle, then bias, ReLU and
     output scale bit for bit against the one-tile-per-work-group kernel (switch 0): both add the same products in the
@@ -375,7 +419,6 @@ def test_attention_forward_and_backward_match_oracle(B, H, dh, Tq, Tk, causal):
         assert err < 4e-3, (name, err)
 
 
-# ---- fused residual + dropout + LayerNorm -----------------------------------------------------------
 # five to eight 32-position tiles on one side or both, and one position more than the tile form takes
 @pytest.mark.parametrize("B,H,dh,Tq,Tk,causal", [(1, 3, 64, 130, 160, 0), (2, 3, 64, 192, 192, 1), (1, 2, 32, 224, 40, 0), (1, 5, 64, 33, 225, 0),
                                                  (1, 2, 64, 256, 256, 1), (1, 2, 16, 256, 250, 0), (1, 2, 64, 257, 257, 1), (1, 2, 16, 161, 161, 1)])
@@ -383,6 +426,7 @@ def test_attention_of_long_sentences_matches_oracle(B, H, dh, Tq, Tk, causal):
     test_attention_forward_and_backward_match_oracle(B, H, dh, Tq, Tk, causal)
 
 
+# ---- fused residual + dropout + LayerNorm -----------------------------------------------------------
 @pytest.mark.parametrize("rows,n_pos,d,p", [(48, 16, 64, 0.1), (99, 33, 1024, 0.3), (70, 35, 512, 0.0), (26, 13, 2048, 0.2),
                                             (10, 5, 200, 0.5)])
 def test_residual_layernorm_forward_and_backward_match_oracle(rows, n_pos, d, p):
@@ -443,7 +487,7 @@ def test_embedding_forward_matches_oracle(B, n_pos, d, V, p):
 @pytest.mark.parametrize("d,V,p,Ba,Sa,Bb,Sb", [(64, 1000, 0.1, 6, 11, 6, 9), (1024, 4096, 0.3, 6, 11, 6, 9), (128, 40000, 0.1, 40, 33, 37, 29),
                                                (64, 65536, 0.0, 3, 400, 5, 300)])
 def test_embedding_backward_matches_oracle_and_is_deterministic(d, V, p, Ba, Sa, Bb, Sb):
-    """The larger cases have ids whose positions fill several 64-entry blocks of the sorted list (sums
+    """The larger cases have ids whose positions fill several 16-entry segments of the sorted list (sums
     carried over block borders), ids above 255 * 256 and more than one 1024-entry block per sort pass."""
     rng = np.random.default_rng(d)
     ids_a = rng.integers(4, V, size=(Ba, Sa))

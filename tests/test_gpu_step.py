@@ -352,6 +352,49 @@ def test_sub_batches_in_flight_give_bit_identical_updates():
             assert (a == b).all()
 
 
+def test_passes_that_use_the_second_stream_are_unchanged_by_others_in_flight():
+    """The model of the test above is too small for the second stream; this one uses it.  Serial updates (second stream) against two
+    and three pipes in flight (each on its own stream alone), then two contexts whose passes, both with a second stream, are in
+    flight at once against the same passes one after the other."""
+    model = dict(enc_layers=2, dec_layers=2, d_model=256, n_heads=4, d_ff=1024, vocab=2056, dropout=0.1)
+    weights = I.init_weights(seed=9, perturb=0.05, **model)
+    batches = [I.tiny_batch(seed=80 + i, B=45 - i, S=40 - i, T=38 + i, vocab=2056, short_rows=3, short_by=4) for i in range(5)]
+    outs = []
+    for pipes in (1, 2, 3):
+        sess = Session(model, weights, max_sentences=64, max_len=64, n_pipes=pipes, auto_streams=False)
+        dbs = [sess.to_device(b) for b in batches]
+        res = [sess.update(dbs, 64.0, 5e-4, t) for t in (1, 2)]
+        outs.append((res, host(sess.acc).copy(), host(sess.master).copy(), host(sess.m).copy()))
+        sess.close()
+    for other in outs[1:]:
+        assert other[0] == outs[0][0]
+        assert all((a == b).all() for a, b in zip(other[1:], outs[0][1:]))
+    sessions = [Session(model, weights, max_sentences=64, max_len=64) for _ in range(2)]
+    try:
+        dbs = [s.to_device(b) for s, b in zip(sessions, batches)]
+        want = []
+        for s, db in zip(sessions, dbs):
+            s.forward_loss(db, 32.0, 3)
+            s.backward()
+            torch.cuda.synchronize()
+            want.append((s.loss_sum.clone(), s.g16.clone()))
+        streams = [torch.cuda.Stream() for _ in sessions]
+        for s in sessions:
+            s.g16.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for _ in range(3):
+            for s, db, stream in zip(sessions, dbs, streams):
+                with torch.cuda.stream(stream):
+                    s.forward_loss(db, 32.0, 3)
+                    s.backward()
+        torch.cuda.synchronize()
+        for s, (loss, g16) in zip(sessions, want):
+            assert torch.equal(s.loss_sum, loss) and torch.equal(s.g16, g16)
+    finally:
+        for s in sessions:
+            s.close()
+
+
 def test_group_of_sub_batches_in_one_pass_matches_the_oracle_accumulation():
     """Three sub-batches of different padded shapes stacked into one forward / backward pass: loss,
     token count and the gradient (rounded to fp16 once, after the sum) against the oracle's per
