@@ -11,8 +11,9 @@
  *    the message of the last failure on the calling thread.  No C++ exception crosses the ABI.
  *  - Pointers named d_* (and all buffers handed to nmt_bind) are DEVICE pointers owned by the
  *    caller; they must stay valid until the work enqueued on them has finished.  The library
- *    never allocates or frees device memory (nmt_backward creates one extra stream and four
- *    events per context on first use).  Host pointers are marked "host".
+ *    never allocates or frees device memory.  A forward or backward pass large enough to use a second
+ *    stream creates it, and seven events, on the context's first such pass; every pass ends with the
+ *    caller's stream waiting for it.  Host pointers are marked "host".
  *  - `stream` is a hipStream_t passed as void*; all kernels are enqueued on it and no function
  *    synchronises unless it says so.
  *  - fp16 buffers are IEEE binary16 (passed as void*).  Matrices are row-major.
@@ -201,11 +202,12 @@ int nmt_debug_activation(const nmt_ctx* ctx, const char* name, const void** d_pt
  * result bit.  name: "gemm_group" (tile rows swept together, >= 1; default 4), "gemm_persist" (0: never the
  * persistent GEMM form / 1: for large products whose epilogue loads nothing per element; default 1),
  * "attn_persist" (0: one attention work item per work-group; default 1), "worklists" (0: attention
- * kernels enumerate every (sentence, tile); default 1), "one_stream" (1: nmt_backward enqueues the weight
- * gradients on the caller's stream; default 0), "gemm_share" (1..16, default 1: the number of products a
+ * kernels enumerate every (sentence, tile); default 1), "one_stream" (1: forward and backward passes enqueue everything
+ * on the caller's stream; default 0), "gemm_share" (1..16, default 1: the number of products a
  * caller keeps running side by side on streams of its own; large tiles are then chosen as if each product had
  * that fraction of the compute units), "gemm_tile" (0: tile shape chosen per product, the default; 1..5: every
- * product that is not cut along k takes 256x256 / 128x128 / 128x64 / 64x128 / 64x64 tiles), "gemm_timing" (1: every GEMM product is bracketed by a pair of
+ * product that is not cut along k, except a layer's weight gradients, takes 256x256 / 128x128 / 128x64 / 64x128 / 64x64
+ * tiles), "gemm_timing" (1: every GEMM product, and every launch of a layer's weight gradients, is bracketed by a pair of
  * HIP events on the stream it is launched on; default 0), "defaults" (value ignored: all of the above back to
  * default).  Unknown names and values out of range return NMT_EINVAL. */
 int nmt_tuning(const char* name, int32_t value);
@@ -245,8 +247,8 @@ int nmt_op_gemm(const void* d_A, int32_t a_t, int32_t lda, const void* d_B, int3
 
 /* The same product without epilogue, with the contraction cut into `splits` (1..64; 0 = chosen by
  * the library) equal pieces whose fp32 partial results go to d_partial (partial_floats >= splits *
- * M * N floats, 16-byte aligned) and are summed in increasing k order by a second kernel: the form
- * used for weight gradients, whose contraction runs over all positions of a pass. */
+ * M * N floats, 16-byte aligned) and are summed in increasing k order by a second kernel.  (The backward pass
+ * uses it for the vocabulary's input gradient, with a number of its own; a layer's weight gradients are nmt_op_wgrad_group.) */
 int nmt_op_gemm_splitk(const void* d_A, int32_t a_t, int32_t lda, const void* d_B, int32_t b_t, int32_t ldb,
                        void* d_C, int32_t ldc, int32_t M, int32_t N, int32_t K, float* d_partial,
                        int64_t partial_floats, int32_t splits, void* stream);

@@ -51,11 +51,11 @@ struct Tuning {
   int gemm_persist = 1;   // 0: never the persistent GEMM form, 1: where it applies (large products whose epilogue loads nothing per element)
   int attn_persist = 1;   // 0: one attention work item per work-group
   int worklists = 1;      // 0: attention kernels enumerate every (sentence, tile) instead of taking work lists
-  int one_stream = 0;     // 1: the backward pass's weight-gradient kernels run on the caller's stream, not beside it
+  int one_stream = 0;     // 1: forward and backward passes keep to the caller's stream
   int gemm_share = 1;     // products expected to run side by side (callers that keep several passes in flight): large tiles
                           // are chosen as if each product had 1/gemm_share of the compute units
-  int gemm_tile = 0;      // experiments: 0 = chosen per product; 1..5 force 256x256, 128x128, 128x64, 64x128, 64x64 tiles (products not cut along k)
-  int gemm_timing = 0;    // 1: every GEMM product is bracketed by HIP events on its launch stream (nmt_gemm_timing reads them)
+  int gemm_tile = 0;      // experiments: 0 = chosen per product; 1..5 force 256x256, 128x128, 128x64, 64x128, 64x64 tiles (products not cut along k, no weight-gradient groups)
+  int gemm_timing = 0;    // 1: every GEMM product (a weight-gradient group: its launch) is bracketed by HIP events on its launch stream (nmt_gemm_timing reads them)
 };
 Tuning& tuning();
 
@@ -185,7 +185,8 @@ struct GemmEpilogue {
   float out_scale = 1.f;  // the accumulated product is multiplied by this first (weight gradients of a large pass)
 };
 // partial: optional fp32 scratch of partial_floats floats for cutting the contraction into `splits`
-// pieces summed by a second kernel (splits == 0: the launcher decides; needs an empty epilogue).
+// pieces summed by a second kernel (needs an empty epilogue; splits == 0: the launcher decides, which only the entry point
+// nmt_op_gemm_splitk offers).
 int launch_gemm(const half_t* A, bool a_t, int lda, const half_t* B, bool b_t, int ldb, half_t* C, int ldc,
                 int M, int N, int K, const GemmEpilogue& ep, hipStream_t stream, float* partial = nullptr,
                 int64_t partial_floats = 0, int splits = 1);

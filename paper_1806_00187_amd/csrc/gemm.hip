@@ -1136,7 +1136,7 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
   // Work-groups of 256 x 256 tiles run one per compute unit; they pay off once there are enough of them.
   const int64_t t256 = (int64_t)ceil_div(M, 256) * ceil_div(N, 256);
   const int64_t full = 3 * (int64_t)cus / 4;  // large tiles from three quarters of a round on
-  if (splits == 0) {  // choose: a short, wide problem (a weight gradient over many positions) is cut along k
+  if (splits == 0) {  // choose: a problem with a small result and a long contraction is cut along k
     splits = 1;
     if (partial && plain && t256 < full) {
       int64_t want = (cus + t256 / 2) / t256;                   // large tiles: one work-group per compute unit
@@ -1269,7 +1269,9 @@ double group_us(int tile, const WgradProduct* p, int n, int splits, int cus, dou
 // The tile and the number of k splits of a group.  A group runs beside the next layer's chain of input gradients, so
 // what counts is the compute-unit time it takes from that chain; its own latency counts too (the last group of a pass has
 // only the embedding kernels beside it, and with one stream there is nothing).  Weights of 0 to 4 for it measured the
-// same updates within 1 to 2 %, this one at the lower end throughout.
+// same updates within 1 to 2 %, this one at the lower end throughout.  (What the model leaves out: a group of 256 x 256 tiles takes every
+// compute unit whole, one work-group of 128 KB of LDS each, so the next layer's first kernels wait for it or crawl beside it; the
+// compute-unit time is right, the moment it is taken is not.)
 constexpr double kGroupLatencyWeight = 0.5;
 // The numbers of k splits looked at, and the fewest positions a split may have.
 constexpr int kGroupMaxSplits = 32, kGroupMinRows = 256;

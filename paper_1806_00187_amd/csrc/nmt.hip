@@ -426,9 +426,11 @@ int ensure_second_stream(nmt_ctx* c) {
   return NMT_OK;
 }
 // Whether the backward pass (and the products below) use the second stream.  Not for a pass so small that a layer's weight gradients
-// take a few us: the events cost the host about as much as a launch each, and such a pass is bound by the host
-// (two layers, 64 wide, 133 positions, 13 MFLOP a layer: 660 us with two streams, 568 with one; 256 wide, 1500
-// positions, 2.4 GFLOP a layer: 1390 and 1430).
+// take a few us: the events cost the host about as much as a launch each, and such a pass is bound by the host.
+// The line lies where the second stream no longer costs much, below the point from which it gains: whole updates of two layers, one
+// stream / two, us, by GFLOP a layer: 64 wide 0.01 477 / 631, 0.10 516 / 618, 0.25 607 / 634, 0.39 654 / 628; 128 wide 0.17 514 / 603,
+// 0.25 519 / 540, 0.59 566 / 581; 256 wide 0.16 557 / 627, 0.35 564 / 589, 0.94 598 / 646, two passes of 2.4 1430 / 1390; 512 wide 0.25
+// 693 / 706, 1.0 739 / 730; 1024 wide 0.25 1073 / 1088, 2.0 1153 / 1184.
 bool use_second_stream(const nmt_ctx* c) {
   const double layer = 4.0 * c->cfg.d_model * c->cfg.d_model + 2.0 * c->cfg.d_model * c->cfg.d_ff;
   return !tuning().one_stream && 2.0 * layer * (c->Ns > c->Nt ? c->Ns : c->Nt) >= 0.25e9;
@@ -688,7 +690,8 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
 // Weight gradients (and the bias column sums) are leaves of the backward graph: nothing downstream
 // waits for them.  A layer's are collected and enqueued as one group on a second stream, where they run beside the
 // next layer's chain of input-gradient kernels and fill the compute units that leaves idle.  Temporaries read by the
-// second stream exist twice; set s is reused two layers later, after the event recorded behind its last reader.
+// second stream exist twice (set s is reused two layers later, after the event recorded behind its last reader) or lie where
+// nothing else is written in the rest of the pass.
 extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   NMT_REQUIRE(ctx, "nmt_backward: null context");
   nmt_ctx* c = ctx;
@@ -826,6 +829,8 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   // tiles of 64 x 64, 147 us).  It is cut so that two work-groups share each compute unit, if that makes three pieces or more of
   // at least 2048 (two pieces of 3000 x 1024 gained nothing).  The partial sums lie where the weight gradients' do, whose first group
   // waits for kernels behind this one.  Whole update on 379 tokens 4395 -> 4363 us, Transformer-base on 2990 3960 -> 3917.
+  // Shorter fp32 sums are also the more exact ones: relative error of the fp16 result against 64 bits, whole / cut / of the rounding
+  // alone, 380 x 1024: 2.11476e-4 / 2.11472e-4 / 2.11472e-4, and likewise at 100 to 2990 rows.
   const int64_t tiles = (int64_t)ceil_div(Nt, 128) * ceil_div(d, 128), fits = p.wgpart_floats / ((int64_t)Nt * d);
   const int64_t cuts = std::min<int64_t>({2 * device_info().cus / tiles, V / kVocabCutFrom, fits, kVocabCuts});
   NMT_TRY(launch_gemm(dlogits, false, V, r.w(c->embed), true, d, dx, d, Nt, d, V, GemmEpilogue{}, st, r.ws<float>(p.wgpart), p.wgpart_floats,
