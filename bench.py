@@ -84,6 +84,15 @@ def gemm_shapes(model, Ns, Nt):
     return out
 
 
+def wgrad_groups(model, Ns, Nt):
+    """(layers, [(out, in, positions, with a bias gradient of its own)]) of the weight-gradient launches of one pass: a layer's
+    products are one launch, the vocabulary's is a product like the others."""
+    d, F = model["d_model"], model["d_ff"]
+    enc = [(d, F, Ns, False), (F, d, Ns, True), (d, d, Ns, False), (3 * d, d, Ns, True)]
+    dec = [(d, F, Nt, False), (F, d, Nt, True), (d, d, Nt, False), (d, d, Nt, True), (2 * d, d, Ns, True), (d, d, Nt, False), (3 * d, d, Nt, True)]
+    return [(model["enc_layers"], enc), (model["dec_layers"], dec)]
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -222,7 +231,7 @@ def main():
     sess.close()
     del sess, tr, dbatches
     # after the session above is gone: its second stream, while it exists, takes a place on the process's hardware
-    # queues, and the four pipes of the one-by-one order then overlap less (134-137 ms instead of 107)
+    # queues, and the four pipes of the one-by-one order then overlap less
     if not args.no_legs and (packed or group > 1):
         result["strict_order"] = strict_leg(model, weights, batches, ntoks, shapes, args.steps, Session, Trainer, torch, log)
     if not args.no_cpu_baseline:
@@ -257,7 +266,7 @@ def strict_leg(model, weights, batches, ntoks, shapes, steps, Session, Trainer, 
     for b in batches:
         sess.reserve(b["src"].shape[0], b["src"].shape[1], b["tgt_in"].shape[1])
     tr = Trainer(sess, peak_lr=1e-3, warmup=4000, init_scale=128.0)
-    # which hardware queues the runtime has put the four streams on decides how well the pipes overlap (107 to 141 ms
+    # which hardware queues the runtime has put the four streams on decides how well the pipes overlap (89 to 115 ms
     # measured for the same work): the session tries a few sets of streams on the forward/backward part of an update
     chosen_ms = sess.choose_streams(dbs, loss_scale=32.0, tries=6, log=log)
     # (with several pipes the session keeps each pipe's weight gradients on the pipe's own stream and lets every
@@ -287,7 +296,7 @@ def strict_leg(model, weights, batches, ntoks, shapes, steps, Session, Trainer, 
             "ms_per_step": ms, "value": sum(ntoks) / (ms * 1e-3), "unit": "tokens/s", "steps": steps, "loss_scale": tr.scale,
             "overflow_updates": int(sum(flags)), "achieved_tflops": tflops, "frac_of_fp16_peak": tflops / PEAK_FP16_TFLOPS,
             "streams": "the fastest of 6 sets of 4 streams on the forward/backward part of one update (the runtime's placement of streams "
-                       "on hardware queues decides how well the pipes overlap: 107-141 ms measured for the same work)",
+                       "on hardware queues decides how well the pipes overlap: 89-115 ms measured for the same work)",
             "forward_backward_ms_on_the_chosen_streams": chosen_ms,
             "phases_ms_per_update_serial": phases}
 
@@ -352,9 +361,9 @@ def gemm_event_leg(sess, tr, dbatches, ntoks, A, torch, log, traffic, updates=3)
     finally:
         A.nmt_tuning("defaults")
     achieved = flops / ms / 1e9
-    log(f"[bench] GEMM products in the step (HIP events, one stream): {achieved:.1f} TFLOP/s over {n // updates} products per update, "
+    log(f"[bench] GEMM products in the step (HIP events, one stream): {achieved:.1f} TFLOP/s over {n // updates} launches per update, "
         f"{ms / updates:.2f} ms per update")
-    return {"bound": "mfma", "kernel": "gemm_kernel / gemm_persistent_kernel (every GEMM product of the timed update, incl. split-k reduction)",
+    return {"bound": "mfma", "kernel": "gemm_kernel / gemm_persistent_kernel / wgrad_group_kernel (every GEMM product of the timed update, incl. split-k reduction)",
             "achieved": achieved, "peak": PEAK_FP16_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_FP16_TFLOPS, "traffic": traffic,
             "how": f"HIP events around every product on its launch stream, {updates} updates of the timed step with the backward pass on one stream",
             "launches_per_update": n // updates, "avg_launch_us": ms * 1e3 / n, "ms_per_update": ms / updates,
@@ -362,22 +371,34 @@ def gemm_event_leg(sess, tr, dbatches, ntoks, A, torch, log, traffic, updates=3)
 
 
 def gemm_leg(model, pass_rows, A, torch, log):
-    """Every distinct GEMM shape of the update timed alone through nmt_op_gemm on random operands (HIP events, 10
-    launches each): which shapes are fast and which are slow."""
-    agg = {}
+    """Every distinct GEMM launch of the update timed alone on random operands (HIP events, 10 launches each): which shapes are
+    fast and which are slow.  A layer's weight gradients are one launch, as in the step."""
+    agg, groups = {}, []
     for s in pass_rows:
         for (M, N, K, a_t, b_t, count, epi) in gemm_shapes(model, *s):
+            if a_t and M != model["vocab"]:
+                continue          # (in a layer's group)
             key = (M, N, K, a_t, b_t, epi)
             agg[key] = agg.get(key, 0) + count
-    tot_flops = tot_ms = 0.0
-    n_launch = 0
-    worst, best = None, None
+        groups += wgrad_groups(model, *s)
+    tot = dict(flops=0.0, ms=0.0, launches=0, worst=None, best=None)
     per_kind = {}
     cache = {}
-    partial = torch.empty(16 << 20, dtype=torch.float32, device="cuda")   # the step's partial-sum scratch size
     warm = torch.randn(8192, 8192, device="cuda", dtype=torch.float16)   # the first shape is not timed on a chip at rest
     _timed(torch, lambda: A.nmt_op_gemm(warm, 0, 8192, warm, 0, 8192, warm.new_empty(8192, 8192), 8192, 8192, 8192, 8192), 20)
     del warm
+
+    def record(ms, fl, count, kind, shape):
+        tot["flops"] += fl * count
+        tot["ms"] += ms * count
+        tot["launches"] += count
+        pk = per_kind.setdefault(kind, [0.0, 0.0])
+        pk[0] += fl * count
+        pk[1] += ms * count
+        one = (fl / ms / 1e9, shape + [kind])
+        tot["worst"] = one if tot["worst"] is None else min(tot["worst"], one, key=lambda t: t[0])
+        tot["best"] = one if tot["best"] is None else max(tot["best"], one, key=lambda t: t[0])
+
     for (M, N, K, a_t, b_t, epi), count in agg.items():
         rows_a, cols_a = (K, M) if a_t else (M, K)
         rows_b, cols_b = (K, N) if b_t else (N, K)
@@ -388,30 +409,26 @@ def gemm_leg(model, pass_rows, A, torch, log):
                     torch.empty(M, N, device="cuda", dtype=torch.float16))
             cache = {(rows_a, cols_a, rows_b, cols_b, M, N): bufs}
         a, b, c = bufs
-        if a_t and b_t:   # weight gradient: as in the step, the library may cut the contraction into pieces (fp32 partial sums)
-            ms = _timed(torch, lambda: A.nmt_op_gemm_splitk(a, a_t, cols_a, b, b_t, cols_b, c, N, M, N, K, partial, 0), 10)
-        else:             # with the epilogue the step uses for this product
-            bias = torch.zeros(N, device="cuda", dtype=torch.float16) if epi.startswith("bias") else None
-            other = torch.randn(M, N, device="cuda", dtype=torch.float16) if epi in ("add", "relu_mask") else None
-            ms = _timed(torch, lambda: A.nmt_op_gemm(a, a_t, cols_a, b, b_t, cols_b, c, N, M, N, K, bias, epi == "bias_relu", None,
-                                                      other if epi == "add" else None, other if epi == "relu_mask" else None), 10)
-            del other
-        fl = 2.0 * M * N * K
-        tot_flops += fl * count
-        tot_ms += ms * count
-        n_launch += count
-        kind = {(0, 0): "forward", (0, 1): "dgrad", (1, 1): "wgrad"}[(a_t, b_t)]
-        pk = per_kind.setdefault(kind, [0.0, 0.0])
-        pk[0] += fl * count
-        pk[1] += ms * count
-        rate = fl / ms / 1e9
-        if worst is None or rate < worst[0]:
-            worst = (rate, [M, N, K, kind])
-        if best is None or rate > best[0]:
-            best = (rate, [M, N, K, kind])
+        # with the epilogue the step uses for this product
+        bias = torch.zeros(N, device="cuda", dtype=torch.float16) if epi.startswith("bias") else None
+        other = torch.randn(M, N, device="cuda", dtype=torch.float16) if epi in ("add", "relu_mask") else None
+        ms = _timed(torch, lambda: A.nmt_op_gemm(a, a_t, cols_a, b, b_t, cols_b, c, N, M, N, K, bias, epi == "bias_relu", None,
+                                                 other if epi == "add" else None, other if epi == "relu_mask" else None), 10)
+        del other
+        record(ms, 2.0 * M * N * K, count, {(0, 0): "forward", (0, 1): "dgrad", (1, 1): "wgrad"}[(a_t, b_t)], [M, N, K])
+    del cache
+    partial = torch.empty(16 << 20, dtype=torch.float32, device="cuda")
+    for count, products in groups:
+        args = [(torch.randn(rows, n_out, device="cuda", dtype=torch.float16) * 0.03, n_out, torch.randn(rows, n_in, device="cuda", dtype=torch.float16), n_in,
+                 torch.empty(n_out, n_in, device="cuda", dtype=torch.float16), n_in,
+                 torch.empty(n_out, device="cuda", dtype=torch.float16) if bias else None, n_out, n_in, rows) for n_out, n_in, rows, bias in products]
+        ms = _timed(torch, lambda: A.nmt_op_wgrad_group(args, partial=partial), 10)
+        record(ms, sum(2.0 * n_out * n_in * rows for n_out, n_in, rows, _ in products), count, "wgrad", [[p[:3] for p in products]])
+        del args
+    tot_flops, tot_ms, n_launch, worst, best = (tot[k] for k in ("flops", "ms", "launches", "worst", "best"))
     achieved = tot_flops / tot_ms / 1e9
     log(f"[bench] GEMM leg: {achieved:.1f} TFLOP/s over {n_launch} launches, {tot_ms:.2f} ms per update; worst {worst}, best {best}")
-    return {"what": "each distinct shape timed alone on random operands", "achieved": achieved, "frac": achieved / PEAK_FP16_TFLOPS,
+    return {"what": "each distinct launch timed alone on random operands", "achieved": achieved, "frac": achieved / PEAK_FP16_TFLOPS,
             "launches_per_update": n_launch, "avg_launch_us": tot_ms * 1e3 / n_launch, "ms_per_update": tot_ms,
             "by_kind_tflops": {k: v[0] / v[1] / 1e9 for k, v in per_kind.items()}, "worst_tflops": worst, "best_tflops": best}
 

@@ -17,9 +17,9 @@ class Session:
     the forward pass of one sub-batch overlaps the backward pass of the previous one.  Accumulation
     into the shared fp32 buffer is chained with events in sub-batch order, which keeps the sum
     deterministic.  How well the pipes overlap depends on how the runtime spreads the process's streams over its few
-    hardware queues, which a caller does not control: the same sixteen-sub-batch update of the big model measured
-    107 ms with four pipes in a process that had no other stream of its own, and 134-137 ms when a stream created
-    earlier (another session's second stream; it need not carry any work) was still alive.  So the first update of a
+    hardware queues, which a caller does not control: the forward and backward passes of the same sixteen-sub-batch update
+    of the big model measured 89 to 91 ms on five sets of four streams and 115 on a sixth (a stream created earlier, such as
+    another session's second stream, counts even if it carries no work).  So the first update of a
     session with several pipes times a few sets of streams on its own sub-batches and keeps the fastest
     (choose_streams; auto_streams=False keeps the streams as created)."""
 
