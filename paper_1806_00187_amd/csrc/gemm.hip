@@ -1270,8 +1270,9 @@ double group_us(int tile, const WgradProduct* p, int n, int splits, int cus, dou
 // what counts is the compute-unit time it takes from that chain; its own latency counts too (the last group of a pass has
 // only the embedding kernels beside it, and with one stream there is nothing).  Weights of 0 to 4 for it measured the
 // same updates within 1 to 2 %, this one at the lower end throughout.  (What the model leaves out: a group of 256 x 256 tiles takes every
-// compute unit whole, one work-group of 128 KB of LDS each, so the next layer's first kernels wait for it or crawl beside it; the
-// compute-unit time is right, the moment it is taken is not.)
+// compute unit whole, one work-group of 128 KB of LDS each, so the next layer's first kernels wait for it or crawl beside it: over
+// 52000 positions 1024 wide LayerNorm backward takes 183 us on average beside the groups, 107 alone, while attention backward, later in
+// the layer, finds nothing beside it any more.)
 constexpr double kGroupLatencyWeight = 0.5;
 // The numbers of k splits looked at, and the fewest positions a split may have.
 constexpr int kGroupMaxSplits = 32, kGroupMinRows = 256;
