@@ -141,7 +141,7 @@ struct nmt_ctx {
   const float* last_loss = nullptr;   // where the last forward call wrote its loss sum and token count
   const int32_t* last_ntok = nullptr;
   Plan plan;
-  // second stream for the weight-gradient kernels of the backward pass (created on first use)
+  // second stream: weight gradients, and products over the encoder output beside the decoder (created on first use)
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_embed = nullptr, ev_kv = nullptr, ev_denc = nullptr, ev_done[2] = {nullptr, nullptr};
 };
