@@ -7,9 +7,10 @@
 // input gradient dy W (B transposed) and weight gradient dy^T x (both transposed).
 //
 // Measured on this chip: ds_read_b128 streams ~200 B/clk per CU (the 8-byte transposing read half
-// of that), global -> LDS loads ~50 B/clk per CU, and with fp16 data of full entropy the sustained
-// rate of LDS reads + MFMAs alone is ~1.2-1.35 PFLOP/s (clocks drop under that load).  The loop is
-// therefore organised around the load path and around keeping the matrix pipe fed:
+// of that), global -> LDS loads ~50 B/clk per CU.  With fp16 data of full entropy the clock drops under matrix load
+// (1.4-1.8 GHz), and how far depends on the instruction: 16x16x32 sustains 1820 TFLOP/s on register operands where
+// 32x32x16 sustains 1580 (its result is read and written half as often per product), so that is the one used.  The loop is
+// organised around the load path and around keeping the matrix pipe fed:
 //  * global -> LDS directly (buffer_load ... lds, 16 bytes per lane, 1 KB contiguous per wave
 //    instruction): no ds_write, no staging registers.  Every k-tile gets a buffer descriptor that
 //    starts at the tile's first element and ends at its last, so out-of-range rows / k arrive as
@@ -22,10 +23,12 @@
 //    ds_read_b64_tr_b16 (the gfx950 transposing read: within 16 lanes, lane L receives element
 //    L%4 of the 8-byte words addressed by lanes 4j + L/4, j = 0..3) for a transposed tile, so
 //    no register shuffling is needed;
-//  * the fragments of k-step s+1 are read while the MFMAs of step s issue (two register sets,
-//    instruction order pinned with scheduling groups);
-//  * a ring of 2 or 4 LDS stages: the next 1 or 3 k-tiles stream in while one is multiplied; one
-//    barrier per k-tile both publishes the next tile and frees the current one for refilling.
+//  * the fragments of the next step are read while the MFMAs of the current one issue;
+//  * a ring of 2 or 4 LDS stages of 64 k: the next 1 or 3 k-tiles stream in while one is multiplied; one
+//    barrier per k-tile both publishes the next tile and frees the current one for refilling;
+//  * the requests of a k-tile are spread between the MFMAs.  Issued in one go behind the barrier they hold up all
+//    wavefronts of the compute unit at once (the path to memory takes 16 clocks for each) while the matrix pipes run dry:
+//    8192^3, x W^T form, 867 -> 839 us, and 773 with the smaller matrix instruction.
 #include <stdlib.h>
 
 #include <mutex>
@@ -72,12 +75,12 @@ __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t rsrc, unsigned char
 }
 
 // ---- direct operand: memory [rows][K] (k contiguous), LDS tile [R][BK k] -------------------------
-// BK = 64: 128 bytes per row; slot p (16 bytes) of row r holds chunk p ^ (r & 7) ^ ((r >> 3) & 1).
-// BK = 32:  64 bytes per row; slot p of row r holds chunk p ^ ((r >> 2) & 3).
-// Either way a wavefront's ds_read_b128 of 32 rows x 2 chunks touches every bank equally often.
+// 128 bytes per row; slot p (16 bytes) of row r holds chunk p ^ (r >> 1 & 7): a wavefront's ds_read_b128 of 16 rows x 4 chunks
+// touches every bank equally often, and so does any 16 lanes of it that take every row once.
 // All offsets are relative to the first element of the block's current k-tile, so operands of any
 // size work with 32-bit offsets.
-template <int R, int BK, int NW>
+constexpr int BK = 64;  // k of one stage
+template <int R, int NW>
 struct DirectOp {
   static constexpr int ROWB = BK * 2;             // bytes per tile row
   static constexpr int CPR = BK / 8;              // 16-byte chunks per row
@@ -85,53 +88,60 @@ struct DirectOp {
   static constexpr int BYTES = R * ROWB;
   static constexpr int NV = BYTES / (1024 * NW);  // wave instructions per wave and k-tile
   static_assert(NV >= 1 && BYTES % (1024 * NW) == 0, "tile too small for the work-group's waves");
-  uint32_t voff[NV];
-  int c8, wave;
-  __device__ __forceinline__ static int swz(int row) { return BK == 64 ? ((row & 7) ^ ((row >> 3) & 1)) : ((row >> 2) & 3); }
+  uint32_t voff;   // of wave instruction 0; instruction `it` starts RPI * NW rows further on: its descriptor does, not the lane
+  int c8, wave, ld;
+  __device__ __forceinline__ static int swz(int row) { return (row >> 1) & 7; }
   // first element of the k-tile at k0 of the block whose first row is r0
   __device__ __forceinline__ static const half_t* origin(const half_t* p, int ld, int r0, int k0) { return p + (size_t)r0 * ld + k0; }
   // bytes from there to the end of the tile's last row (0 if the k-tile lies past K)
   __device__ __forceinline__ static uint32_t extent(int rows_in, int ld, int kleft) {
-    return kleft > 0 ? ((uint32_t)(rows_in - 1) * ld + (uint32_t)min(kleft, BK)) * 2u : 0u;
+    const uint32_t e = ((uint32_t)(rows_in - 1) * ld + (uint32_t)min(kleft, BK)) * 2u;
+    return e & (uint32_t)~((kleft - 1) >> 31);  // (masked, not selected: see TransOp)
   }
-  __device__ __forceinline__ void init(int ld, int rows_in, int tid) {
-    wave = tid >> 6;
+  __device__ __forceinline__ void init(int ld_in, int /*rows_in*/, int tid) {
+    ld = ld_in;
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int L = tid & 63, rowl = L / CPR, p = L % CPR;
-    // RPI * (wave + NW it) adds nothing to the swizzle bits except, for BK = 64, bit 3 of the row (= wave & 1)
+    // RPI * (wave + NW it) adds nothing to the swizzle bits except bit 3 of the row (= wave & 1)
     c8 = (p ^ swz(RPI * wave + rowl)) << 3;
-#pragma unroll
-    for (int it = 0; it < NV; ++it) {
-      const int row = RPI * (wave + NW * it) + rowl;
-      voff[it] = row < rows_in ? ((uint32_t)row * (uint32_t)ld + (uint32_t)c8) * 2u : kOob;
-    }
+    voff = ((uint32_t)(RPI * wave + rowl) * (uint32_t)ld + (uint32_t)c8) * 2u;  // (rows past the last lie beyond the extent)
   }
-  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rsrc, unsigned char* tile, int kleft) const {
-    const bool kv = c8 < kleft;  // only the last k-tile can fail this
+  // One wave instruction after the other of a k-tile: `p` and `left`, its first element and its extent, move on with each.
+  static constexpr int STEP = RPI * NW;  // rows (or, transposed, k rows) from one to the next
+  __device__ __forceinline__ void load_next(const half_t*& p, int& left, int step, unsigned char* tile, int kleft, int it) const {
+    dma16(make_rsrc(p, (uint32_t)max(left, 0)), tile + (wave + NW * it) * 1024, c8 < kleft ? voff : kOob);  // (only the last k-tile can fail this)
+    p += step;
+    left -= step * 2;
+  }
+  __device__ __forceinline__ void load(const half_t* p, uint32_t bytes, unsigned char* tile, int kleft) const {
+    int left = (int)bytes;
 #pragma unroll
-    for (int it = 0; it < NV; ++it) dma16(rsrc, tile + (wave + NW * it) * 1024, kv ? voff[it] : kOob);
+    for (int it = 0; it < NV; ++it) load_next(p, left, STEP * ld, tile, kleft, it);
   }
   // per-lane fragment addresses, one per k-step (the swizzle is an XOR in the k-step bits)
-  struct Frag { uint32_t a[BK / 16]; };
+  struct Frag {
+    uint32_t a[BK / 32];
+    __device__ __forceinline__ void fresh() {}
+  };
   __device__ __forceinline__ static Frag frag_init(int row0, int lane) {
     Frag f;
-    const int row = row0 + (lane & 31);  // row0 and the 32-row steps between MFMA tiles leave the swizzle bits alone
+    const int row = row0 + (lane & 15);  // row0 and the 16-row steps between MFMA tiles leave the swizzle bits alone
 #pragma unroll
-    for (int s = 0; s < BK / 16; ++s) f.a[s] = row * ROWB + (((((lane >> 5) | (2 * s)) ^ swz(lane & 31)) & (CPR - 1)) << 4);
+    for (int s = 0; s < BK / 32; ++s) f.a[s] = row * ROWB + ((((lane >> 4) | (4 * s)) ^ swz(lane & 15)) << 4);
     return f;
   }
   static constexpr int READS = 1;  // LDS instructions per fragment
   __device__ __forceinline__ static half8_t frag(const unsigned char* tile, const Frag& f, int i, int s) {
-    return *reinterpret_cast<const half8_t*>(tile + f.a[s] + i * 32 * ROWB);
+    return *reinterpret_cast<const half8_t*>(tile + f.a[s] + i * 16 * ROWB);
   }
 };
 
 // ---- transposed operand: memory [K][rows] (rows contiguous), LDS tile [BK k][R] -------------------
-// Within k row k, slot q (16 bytes) holds chunk q ^ sw(k & 3).  A transposing read serves 32 lanes at a
-// time: two 16-lane groups (MFMA rows 0..15 and 16..31), each touching four k rows x two chunks.  With
-// sw(k) = k << 2 (chunk bits 2 and 3; bit 0 counts the two chunks of a group, bit 1 the group) those
-// sixteen chunks are all different, i.e. the 32 lanes cover every bank of a 256-byte row segment once.
-// (A 64-wide tile has only 8 chunks per k row: there sw(k) = k << 1 and the two groups share banks.)
-template <int R, int BK, int NW>
+// Within k row k, slot q (16 bytes) holds chunk q ^ sw(k).  A transposing read serves 32 lanes at a
+// time: two 16-lane groups (k 8 apart), each touching four k rows x two chunks.  With sw(k) = k & 3 in chunk bits 1 and 2, k & 8 in
+// bit 3 (bit 0 counts the two chunks of a group) those sixteen chunks are all different, i.e. the 32 lanes cover every bank of a
+// 256-byte row segment once.  (A 64-wide tile has only 8 chunks per k row, and two k rows side by side in a segment: there k & 2 and k & 8.)
+template <int R, int NW>
 struct TransOp {
   static constexpr int ROWB = R * 2;        // bytes per k row
   static constexpr int BYTES = BK * ROWB;
@@ -139,9 +149,9 @@ struct TransOp {
   static constexpr int CPR = R / 8;         // 16-byte chunks per k row
   static constexpr int KPI = 64 / CPR;      // k rows per wave instruction
   static_assert(NV >= 1 && BYTES % (1024 * NW) == 0, "tile too small for the work-group's waves");
-  uint32_t voff[NV];
-  int wave;
-  __device__ __forceinline__ static int sw(int k) { return (k & 3) << (R == 64 ? 1 : 2); }
+  uint32_t voff;   // (as above: KPI * NW k rows further on)
+  int wave, ld;
+  __device__ __forceinline__ static int sw(int k) { return R == 64 ? ((k & 2) | ((k & 8) >> 1)) : (((k & 3) << 1) | (k & 8)); }
   __device__ __forceinline__ static const half_t* origin(const half_t* p, int ld, int r0, int k0) { return p + (size_t)k0 * ld + r0; }
   // k rows >= K lie beyond the extent and arrive as zeros.  (Masked, not selected: with a branch here the compiler's
   // count of the requests in flight came out low in the loops of every k-major product, and it put a wait for all but
@@ -151,37 +161,42 @@ struct TransOp {
     const uint32_t e = ((uint32_t)(min(kleft, BK) - 1) * ld + (uint32_t)rows_in) * 2u;
     return e & (uint32_t)~((kleft - 1) >> 31);
   }
-  __device__ __forceinline__ void init(int ld, int rows_in, int tid) {
-    wave = tid >> 6;
+  __device__ __forceinline__ void init(int ld_in, int rows_in, int tid) {
+    ld = ld_in;
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int L = tid & 63, kl = L / CPR, slot = L % CPR;
-    const int cc = slot ^ sw(KPI * wave + kl);  // k row of instruction `it` is KPI * (wave + NW it) + kl: same k & 3 for every it
-    const bool ok = cc * 8 < rows_in;
-#pragma unroll
-    for (int it = 0; it < NV; ++it)
-      voff[it] = ok ? ((uint32_t)(KPI * (wave + NW * it) + kl) * (uint32_t)ld + (uint32_t)(cc * 8)) * 2u : kOob;
+    // k row of instruction `it` is KPI * (wave + NW it) + kl: the same bits 0, 1 and 3 for every it
+    static_assert(NV == 1 || KPI * NW % 16 == 0, "the swizzle of a lane's chunk must not change with `it`");
+    const int cc = slot ^ sw(KPI * wave + kl);
+    voff = cc * 8 < rows_in ? ((uint32_t)(KPI * wave + kl) * (uint32_t)ld + (uint32_t)(cc * 8)) * 2u : kOob;
   }
-  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rsrc, unsigned char* tile, int /*kleft*/) const {
+  static constexpr int STEP = KPI * NW;
+  __device__ __forceinline__ void load_next(const half_t*& p, int& left, int step, unsigned char* tile, int /*kleft*/, int it) const {
+    dma16(make_rsrc(p, (uint32_t)max(left, 0)), tile + (wave + NW * it) * 1024, voff);
+    p += step;
+    left -= step * 2;
+  }
+  __device__ __forceinline__ void load(const half_t* p, uint32_t bytes, unsigned char* tile, int kleft) const {
+    int left = (int)bytes;
 #pragma unroll
-    for (int it = 0; it < NV; ++it) dma16(rsrc, tile + (wave + NW * it) * 1024, voff[it]);
+    for (int it = 0; it < NV; ++it) load_next(p, left, STEP * ld, tile, kleft, it);
   }
   static constexpr int READS = 2;
-  struct Frag { uint32_t a[4]; };  // one address per MFMA tile of the wave (the swizzle reaches the bits a tile step changes)
-  // 16-lane group q = lane/16 serves rows 16*(q&1).. of the MFMA tile and k-half q/2; lane i of the group
-  // addresses k row i/4, row offset 4*(i%4) of its 4(k) x 16(row) block.
+  // 16-lane group q = lane / 16 serves the tile's 16 rows and k 8 q .. 8 q + 7; lane i of the group
+  // addresses k row i/4, row offset 4*(i%4) of its 4(k) x 16(row) block.  A step of one MFMA tile changes chunk bits 1 to 3, which
+  // the swizzle flips: the address is flipped likewise, by an instruction of its own (eight addresses kept would not fit the large
+  // tiles' registers; `fresh` keeps the compiler from keeping them all the same).
+  struct Frag {
+    uint32_t a;
+    __device__ __forceinline__ void fresh() { asm volatile("" : "+v"(a)); }
+  };
   __device__ __forceinline__ static Frag frag_init(int row0, int lane) {
     const int q = lane >> 4, i = lane & 15;
-    const int kk = 8 * (q >> 1) + (i >> 2);
-    Frag f;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int r = row0 + 32 * t + 16 * (q & 1) + 4 * (i & 3);
-      const int cc = ((r >> 3) ^ sw(i >> 2)) & (CPR - 1);   // (tiles past the wave's share are never read)
-      f.a[t] = (uint32_t)(kk * ROWB + cc * 16 + (r & 7) * 2);
-    }
-    return f;
+    const int kk = 8 * q + (i >> 2), r = row0 + 4 * (i & 3);  // (row0 is a multiple of the wave's rows: the bits of its tiles are free)
+    return Frag{(uint32_t)(kk * ROWB + ((r >> 3) ^ sw(kk)) * 16 + (r & 7) * 2)};
   }
   __device__ __forceinline__ static half8_t frag(const unsigned char* tile, const Frag& f, int i, int s) {
-    const unsigned char* p = tile + f.a[i] + s * 16 * ROWB;
+    const unsigned char* p = tile + (f.a ^ (uint32_t)(i * 32)) + s * 32 * ROWB;
     const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(p));
     const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(p + 4 * ROWB));
     const short8_t r = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -189,28 +204,30 @@ struct TransOp {
   }
 };
 
-// Instruction order of one k-step: the NR LDS reads of the next step's fragments go between the
-// first three quarters of this step's MF matrix instructions, so that every read has returned
-// before the next step starts.
-template <int M, int MF, int NR>
+// Instruction order of one k-tile of a small tile: the NR LDS reads of the next k-tile's fragments go between the first
+// three quarters of this one's MF matrix instructions, so that every read has returned before the next k-tile starts, and the NV
+// requests between all of them.
+template <int M, int MF, int NR, int NV>
 struct Interleave {
   static constexpr int SLOTS = MF - MF / 4, PER = (NR + SLOTS - 1) / SLOTS;
   static constexpr int DONE = M * PER < NR ? M * PER : NR, NOW = NR - DONE < PER ? NR - DONE : PER;
+  static constexpr int VNOW = (M + 1) * NV / MF - M * NV / MF;
   __device__ __forceinline__ static void run() {
     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
     if (NOW > 0) __builtin_amdgcn_sched_group_barrier(0x100, NOW, 0);
-    Interleave<M + 1, MF, NR>::run();
+    if (VNOW > 0) __builtin_amdgcn_sched_group_barrier(0x020, VNOW, 0);
+    Interleave<M + 1, MF, NR, NV>::run();
   }
 };
-template <int MF, int NR>
-struct Interleave<MF, MF, NR> {
+template <int MF, int NR, int NV>
+struct Interleave<MF, MF, NR, NV> {
   __device__ __forceinline__ static void run() {}
 };
 
-template <int BM, int BN, bool AT, bool BT, int BK, int NW>
+template <int BM, int BN, bool AT, bool BT, int NW>
 struct Tile {
-  using OpA = typename std::conditional<AT, TransOp<BM, BK, NW>, DirectOp<BM, BK, NW>>::type;
-  using OpB = typename std::conditional<BT, TransOp<BN, BK, NW>, DirectOp<BN, BK, NW>>::type;
+  using OpA = typename std::conditional<AT, TransOp<BM, NW>, DirectOp<BM, NW>>::type;
+  using OpB = typename std::conditional<BT, TransOp<BN, NW>, DirectOp<BN, NW>>::type;
   static constexpr int STAGE = OpA::BYTES + OpB::BYTES;   // (BM + BN) * BK * 2 bytes
 };
 
@@ -247,15 +264,15 @@ __device__ __forceinline__ void place(const GemmArgs& g, int lin, int total, int
 }
 
 // Epilogue of one tile: accumulators -> per-wave LDS staging (fp32) -> row-wise 16-byte stores.
-template <int BM, int BN, int NW, int STAGE>
-__device__ __forceinline__ void store_tile(const GemmArgs& g, const floatx16 (&acc)[BM / 64][BN / (32 * (NW / 2))], int m0, int n0, int split,
+// PLAIN: the epilogue is the output scale alone (weight gradients).
+template <int BM, int BN, int NW, int STAGE, bool PLAIN>
+__device__ __forceinline__ void store_tile(const GemmArgs& g, const floatx4 (&acc)[BM / 32][BN / (16 * (NW / 2))], int m0, int n0, int split,
                                            unsigned char* stage0, unsigned char* stage1) {
   constexpr int WGN = NW / 2, WM = BM / 2, WN = BN / WGN, TM = WM / 32;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
   // The products were formed as (B tile) x (A tile)^T, so in the MFMA result layout lane l holds row
-  // l%32 of the C tile and, in registers 4q..4q+3, the four consecutive columns 8q + 4(l/32) .. +3:
-  // one 16-byte LDS write per register quad.  A staged row is SW floats; its 16-byte chunks are
+  // l%16 of a 16 x 16 tile of C and the four consecutive columns 4(l/16) .. +3: one 16-byte LDS write per tile.  A staged row is SW floats; its 16-byte chunks are
   // XOR-swizzled with the row so that 16 lanes (16 rows, same logical chunk) hit every bank once.
   // staging width per pass: the wave's whole width if NW waves x 32 rows of it fit one stage, else less
   // (half of the waves stage in stage0, the other half in stage1, so that a staged row can be 64 columns
@@ -272,7 +289,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const floatx16 (&a
   // the fragments no longer need, so that its latency is paid once and behind the staging of the first rows
   // rather than once per 32 rows.  (Reading it all before any store is also what lets it alias C.)
   constexpr int kPre = TM * (WN / SW) * (CH / 2);
-  constexpr bool PRELOAD = kPre <= 16;
+  constexpr bool PRELOAD = !PLAIN && kPre <= 16;
   const half_t* pre_src = ep.add ? ep.add : ep.relu_src;
   half8_t pre[PRELOAD ? kPre : 1];
   if constexpr (PRELOAD) {
@@ -295,13 +312,11 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const floatx16 (&a
     for (int jg = 0; jg < WN / SW; ++jg) {
       if (i || jg) wave_sync();  // the staging area is the wave's own: no work-group barrier needed
 #pragma unroll
-      for (int jj = 0; jj < SW / 32; ++jj)
+      for (int jj = 0; jj < SW / 16; ++jj)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const floatx16& a = acc[i][jg * (SW / 32) + jj];
-          const floatx4 v4 = {a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
-          const int row = lane & 31, chunk = jj * 8 + 2 * q + (lane >> 5);
-          *reinterpret_cast<floatx4*>(stg + row * SW + swz(row, chunk) * 4) = v4;
+        for (int ii = 0; ii < 2; ++ii) {
+          const int row = ii * 16 + (lane & 15), chunk = jj * 4 + (lane >> 4);
+          *reinterpret_cast<floatx4*>(stg + row * SW + swz(row, chunk) * 4) = acc[2 * i + ii][jg * (SW / 16) + jj];
         }
       wave_sync();
 #pragma unroll
@@ -324,6 +339,8 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const floatx16 (&a
             v[e] = lo[e] * ep.out_scale;
             v[4 + e] = hi[e] * ep.out_scale;
           }
+          const size_t off = (size_t)gr * g.ldc + gc;
+          if constexpr (!PLAIN) {
           if (ep.bias) {
             const half8_t b = ld_half8(ep.bias + gc);
 #pragma unroll
@@ -338,7 +355,6 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const floatx16 (&a
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = ((bits >> e) & 1u) ? v[e] * ep.drop.scale : 0.f;
           }
-          const size_t off = (size_t)gr * g.ldc + gc;
           if (ep.add) {
             half8_t a;
             if constexpr (PRELOAD) a = pre[(i * (WN / SW) + jg) * (CH / 2) + it];
@@ -352,6 +368,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const floatx16 (&a
             else h = ld_half8(ep.relu_src + off);
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = ((float)h[e] > 0.f) ? v[e] * ep.mask_scale : 0.f;
+          }
           }
           half8_t o;
 #pragma unroll
@@ -383,143 +400,190 @@ __device__ __forceinline__ void store_colsum(const GemmArgs& g, const float (&su
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
-    const float s = sum[i] + __shfl_xor(sum[i], 32, kWave);
-    const int row = m0 + i * 32 + lane;
-    if (lane < 32 && row < g.M) {
+    float s = sum[i] + __shfl_xor(sum[i], 16, kWave);
+    s += __shfl_xor(s, 32, kWave);
+    const int row = m0 + i * 16 + lane;
+    if (lane < 16 && row < g.M) {
       if (g.partial) g.partial_colsum[(size_t)split * g.M + row] = s;
       else g.colsum[row] = (half_t)(s * g.ep.out_scale);
     }
   }
 }
 
-// NS stages of BK k each form a ring: while k-tile t is multiplied, tiles t+1 .. t+NS-1 are in LDS
-// or on their way.
-// (The stages are separate arrays, so that the compiler can tell that fragment reads of one stage do not depend on
-// the loads in flight into the others.)
-template <int BM, int BN, bool AT, bool BT, int BK, int NS, int NW, bool SUMS>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int split, int tm, int tn, unsigned char* stage0, unsigned char* stage1,
-                                          unsigned char* stage2, unsigned char* stage3) {
-  using T = Tile<BM, BN, AT, BT, BK, NW>;
+// ------------------------------------------------------------------------------------------------
+// Tiles multiplied strip by strip: 256 x 256 on eight wavefronts (2 x 4 of 128 x 64), one work-group per compute unit, and the tiles of
+// which two or three work-groups share one (128 x 128, 128 x 64 on four wavefronts).  Two stages: while one k-tile is multiplied, the
+// next is in LDS or on its way.  (The stages are separate arrays, so that the compiler can tell that fragment reads of one
+// do not depend on the loads in flight into the other.)
+// What bounds it: the power the chip may take (matrix pipes busy 0.7-0.8 of the cycles at 1.4-1.8 GHz) and, at k = 1024, the
+// 4-5 us a tile takes besides its k-tiles.  TFLOP/s before (32x32x16, requests in one go, four stages of 32 for k-major operands) and
+// now: 8192^3 x W^T 1268 / 1423, dy W 1244 / 1400, dy^T x 1251 / 1360; 52704 rows: 3072 x 1024 x W^T 1056 / 1150, 1024 x 4096 1116 / 1218,
+// 4096 x 1024 dy W 1083 / 1140; a layer's weight gradients over 52700 positions 1024 wide 840 / 933.  Two stages of 64 k against
+// four of 32 here: x W^T 760 / 808 us, dy W 773 / 793, dy^T x 794 / 805 (8192^3).
+// ------------------------------------------------------------------------------------------------
+// The product as an instruction of its own, so that the sums stay where they are: the compiler's form of this shape has a result
+// apart from the addend, and its register allocation then moves accumulators about, runs out and spills inside the loop (a
+// layer's weight gradients over 52700 positions 1024 wide: 1.65 -> 4.0 ms).  A result may be read (other than as the addend of
+// the same sum) a few instructions later only; `settle` is between the loop and the epilogue.
+__device__ __forceinline__ void mfma_add(floatx4& acc, const half8_t& b, const half8_t& a) {
+  asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(b), "v"(a));
+}
+template <int BM, int BN, bool AT, bool BT, int NW, bool SUMS>
+struct StripTile {
+  static constexpr int WGN = NW / 2, WM = BM / 2, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
+  using T = Tile<BM, BN, AT, BT, NW>;
   using OpA = typename T::OpA;
   using OpB = typename T::OpB;
-  static_assert(NS >= 2 && NS <= 4, "two to four stages");
-  constexpr int WGN = NW / 2;  // the waves form a 2 x WGN grid over the block tile
-  constexpr int WM = BM / 2, WN = BN / WGN, TM = WM / 32, TN = WN / 32, KS = BK / 16;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WGN, wn = wave % WGN;
-  const int m0 = tm * BM, n0 = tn * BN;
-  float colsum[SUMS ? TM : 1] = {};
-
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
+  const GemmArgs& g;
+  int m0, n0, rows_a, rows_b, k_end;
   OpA opa;
   OpB opb;
-  const int rows_a = min(g.M - m0, BM), rows_b = min(g.N - n0, BN);
-  opa.init(g.lda, rows_a, tid);
-  opb.init(g.ldb, rows_b, tid);
-  const typename OpA::Frag fa = OpA::frag_init(wm * WM, lane);
-  const typename OpB::Frag fb = OpB::frag_init(wn * WN, lane);
+  typename OpA::Frag fa;
+  typename OpB::Frag fb;
+  floatx4 acc[TM][TN];
+  half8_t af[TM], bf[2][TN];
+  float sums[SUMS ? TM : 1];
 
-  const int k_base = g.partial ? split * g.k_chunk : 0;
-  const int k_end = g.partial ? min(g.K, k_base + g.k_chunk) : g.K;
-  auto request = [&](unsigned char* stage, int k0) {  // asynchronous: tile k0 streams into `stage`
-    const int kleft = k_end - k0;
-    opa.load(make_rsrc(OpA::origin(g.A, g.lda, m0, k0), OpA::extent(rows_a, g.lda, kleft)), stage, kleft);
-    opb.load(make_rsrc(OpB::origin(g.B, g.ldb, n0, k0), OpB::extent(rows_b, g.ldb, kleft)), stage + OpA::BYTES, kleft);
-    __builtin_amdgcn_sched_barrier(0);  // keep the requests ahead of the products they overlap with
-  };
-  constexpr int kPerTile = OpA::NV + OpB::NV;  // vector-memory instructions of one request, per wave
-  half8_t af[2][TM], bf[2][TN];  // fragments of two consecutive k-steps
-  auto fetch = [&](const unsigned char* stage, int s, int set) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i) af[set][i] = OpA::frag(stage, fa, i, s);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) bf[set][j] = OpB::frag(stage + OpA::BYTES, fb, j, s);
-  };
-  auto multiply = [&](int set) {
+  __device__ __forceinline__ explicit StripTile(const GemmArgs& args) : g(args) {}
+  __device__ __forceinline__ void set_tile(int row, int col, int tid) {
+    m0 = row;
+    n0 = col;
+    rows_a = min(g.M - m0, BM);
+    rows_b = min(g.N - n0, BN);
+    opa.init(g.lda, rows_a, tid);
+    opb.init(g.ldb, rows_b, tid);
+  }
+  __device__ __forceinline__ void set_fragments(int wave, int lane) {
+    fa = OpA::frag_init(wave / WGN * WM, lane);
+    fb = OpB::frag_init(wave % WGN * WN, lane);
+  }
+  __device__ __forceinline__ void clear() {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)  // B first: the result tile is transposed, lane = row of C, registers = columns
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[set][j], af[set][i], acc[i][j], 0, 0, 0);
-    if constexpr (SUMS) {
+      for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    settle();
 #pragma unroll
-      for (int i = 0; i < TM; ++i) add_colsum(colsum[i], af[set][i]);
-    }
-  };
-  auto interleave = [&]() { Interleave<0, TM * TN, OpA::READS * TM + OpB::READS * TN>::run(); };
-  // One k-tile.  On entry the fragments of k-step 0 of `cur` are in registers and the next NS-1
-  // tiles have been requested.  Before the last k-step every wave holds its last fragments of `cur`
-  // in registers and has seen its own part of `nxt` land (the requests of the NS-2 tiles behind it
-  // may still be in flight); the barrier then publishes `nxt` and frees `cur`, which is refilled at
-  // once with the tile NS ahead.
-  auto k_tile = [&](unsigned char* cur, const unsigned char* nxt, int k_refill) {
+    for (int i = 0; i < (SUMS ? TM : 1); ++i) sums[i] = 0.f;
+  }
+  __device__ __forceinline__ const half_t* origin_a(int k0) const { return OpA::origin(g.A, g.lda, m0, k0); }
+  __device__ __forceinline__ const half_t* origin_b(int k0) const { return OpB::origin(g.B, g.ldb, n0, k0); }
+  __device__ __forceinline__ uint32_t extent_a(int k0) const { return OpA::extent(rows_a, g.lda, k_end - k0); }
+  __device__ __forceinline__ uint32_t extent_b(int k0) const { return OpB::extent(rows_b, g.ldb, k_end - k0); }
+  // What is in flight when the loop starts: the first k-tile and the A half of the second (asynchronous).
+  static constexpr int kAhead = OpA::NV;  // vector-memory instructions behind the first k-tile's
+  __device__ __forceinline__ void request_first(unsigned char* s0, unsigned char* s1, int k0) const {
+    opa.load(origin_a(k0), extent_a(k0), s0, k_end - k0);
+    opb.load(origin_b(k0), extent_b(k0), s0 + OpA::BYTES, k_end - k0);
+    opa.load(origin_a(k0 + BK), extent_a(k0 + BK), s1, k_end - k0 - BK);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __device__ __forceinline__ void first_fragments(const unsigned char* stage) {
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      if (s == KS - 1) {
-        __builtin_amdgcn_s_waitcnt(wait_vm_lds((NS - 2) * kPerTile));
+    for (int i = 0; i < TM; ++i) af[i] = OpA::frag(stage, fa, i, 0);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) bf[0][j] = OpB::frag(stage + OpA::BYTES, fb, j, 0);
+  }
+  // One step of 32 k, S = 0 or 1 of a k-tile.  On entry its fragments are in registers, A in `af`, B in bf[S].  The step multiplies one
+  // 16-row strip of A after the other; a strip's registers take its fragment of the next step (from stage `from`) once its
+  // products are issued, B's go to the other set.  The second step of a k-tile changes stages, half its strips in: by then every
+  // wave's last fragments of `to` have arrived and it has seen its own part of `from` land; the barrier publishes `from` and
+  // frees `to`.  The A half of `to` is requested over the strips behind the barrier (k-tile at k0), the B half over the first strips
+  // of the step after.
+  template <int S>
+  __device__ __forceinline__ void k_step(const unsigned char* from, unsigned char* to, int k0) {
+    constexpr int kAt = S ? TM / 2 : 0, kBehind = TM - kAt;  // strips before the first read from `from`, and behind it
+    constexpr int kReq = S ? OpA::NV : OpB::NV, kOver = S ? kBehind : TM / 2;  // requests, and the strips they are spread over
+    const int kleft = k_end - k0;
+    const half_t* at = S ? origin_a(k0) : origin_b(k0);
+    int left = (int)(S ? extent_a(k0) : extent_b(k0)), step = S ? OpA::STEP * g.lda : OpB::STEP * g.ldb;
+    asm volatile("" : "+s"(step));  // (multiples of it made ahead of the loop would fill the scalar registers)
+    fa.fresh();
+    fb.fresh();
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      if (S && i == kAt) {
+        __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));
         __builtin_amdgcn_s_barrier();
-        request(cur, k_refill);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      fetch(s == KS - 1 ? nxt : cur, (s + 1) % KS, (s + 1) & 1);
-      multiply(s & 1);
-      interleave();
+#pragma unroll
+      for (int j = 0; j < TN; ++j)  // B first: the result tile is transposed, lane = row of C, registers = columns
+        mfma_add(acc[i][j], bf[S][j], af[i]);
+      if constexpr (SUMS) add_colsum(sums[i], af[i]);
+      __builtin_amdgcn_sched_barrier(0);  // (a read moved ahead of these products would take registers of its own)
+      if (i >= kAt) {
+        const int r = i - kAt;
+#pragma unroll
+        for (int j = r; j < TN; j += kBehind) bf[S ^ 1][j] = OpB::frag(from + OpA::BYTES, fb, j, S ^ 1);
+        if (S && i == kAt) {
+#pragma unroll
+          for (int t = 0; t < kAt; ++t) af[t] = OpA::frag(from, fa, t, S ^ 1);
+        }
+        af[i] = OpA::frag(from, fa, i, S ^ 1);
+#pragma unroll
+        for (int q = r * kReq / kOver; q < (r + 1) * kReq / kOver && q < kReq; ++q) {
+          if (S) opa.load_next(at, left, step, to, kleft, q);
+          else opb.load_next(at, left, step, to + OpA::BYTES, kleft, q);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
-  };
-
+  }
   // A k-tile past the end reads zeros (it lies outside the extent of its buffer descriptor) and
   // multiplying it changes nothing, so the loop always runs whole rings and carries no edge conditions.
-  const int nk = (k_end - k_base + BK - 1) / BK;
-  request(stage0, k_base);
-  request(stage1, k_base + BK);
-  if constexpr (NS >= 3) request(stage2, k_base + 2 * BK);
-  if constexpr (NS == 4) request(stage3, k_base + 3 * BK);
-  __builtin_amdgcn_s_waitcnt(wait_vm((NS - 1) * kPerTile));
-  __builtin_amdgcn_s_barrier();
-  fetch(stage0, 0, 0);
-  if constexpr (NS == 2) {
+  __device__ __forceinline__ void multiply(unsigned char* s0, unsigned char* s1, int k0) {
+    const int nk = (k_end - k0 + BK - 1) / BK;
     for (int kt = 0; kt < nk; kt += 2) {
-      k_tile(stage0, stage1, k_base + (kt + 2) * BK);
-      k_tile(stage1, stage0, k_base + (kt + 3) * BK);
+      k_step<0>(s0, s1, k0 + (kt + 1) * BK);
+      k_step<1>(s1, s0, k0 + (kt + 2) * BK);
+      k_step<0>(s1, s0, k0 + (kt + 2) * BK);
+      k_step<1>(s0, s1, k0 + (kt + 3) * BK);
     }
-  } else if constexpr (NS == 3) {
-    for (int kt = 0; kt < nk; kt += 3) {
-      k_tile(stage0, stage1, k_base + (kt + 3) * BK);
-      k_tile(stage1, stage2, k_base + (kt + 4) * BK);
-      k_tile(stage2, stage0, k_base + (kt + 5) * BK);
-    }
-  } else {
-    for (int kt = 0; kt < nk; kt += 4) {
-      k_tile(stage0, stage1, k_base + (kt + 4) * BK);
-      k_tile(stage1, stage2, k_base + (kt + 5) * BK);
-      k_tile(stage2, stage3, k_base + (kt + 6) * BK);
-      k_tile(stage3, stage0, k_base + (kt + 7) * BK);
+    settle();
+  }
+  // Waits that the compiler puts around products it knows: the last results have arrived before they are read (at most 19 wait states;
+  // 16 for each strip here), and cleared sums are in place before the first product (2).
+  __device__ __forceinline__ void settle() {
+    static_assert(TN == 2 || TN == 4, "two or four tiles in a strip");
+#pragma unroll
+    for (int i = TM - 1; i >= 0; --i) {
+      if constexpr (TN == 4) asm volatile("s_nop 15" : "+v"(acc[i][0]), "+v"(acc[i][1]), "+v"(acc[i][2]), "+v"(acc[i][3]));
+      else asm volatile("s_nop 15" : "+v"(acc[i][0]), "+v"(acc[i][1]));
     }
   }
+};
+// One tile by one work-group.
+template <int BM, int BN, bool AT, bool BT, int NW, bool SUMS, bool PLAIN>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int split, int tm, int tn, unsigned char* stage0, unsigned char* stage1) {
+  using L = StripTile<BM, BN, AT, BT, NW, SUMS>;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int k_base = g.partial ? split * g.k_chunk : 0;
+  L t(g);
+  t.k_end = g.partial ? min(g.K, k_base + g.k_chunk) : g.K;
+  t.set_tile(tm * BM, tn * BN, tid);
+  t.set_fragments(wave, lane);
+  t.clear();
+  t.request_first(stage0, stage1, k_base);
+  __builtin_amdgcn_s_waitcnt(wait_vm(L::kAhead));
+  __builtin_amdgcn_s_barrier();
+  t.first_fragments(stage0);
+  t.multiply(stage0, stage1, k_base);
   __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));  // the last refills (all zeros) must land before the stages are reused
   __syncthreads();
-
   if constexpr (SUMS) {
-    if (wn == 0) store_colsum<BM, TM>(g, colsum, m0 + wm * WM, split);
+    if (wave % L::WGN == 0) store_colsum<BM, L::TM>(g, t.sums, t.m0 + wave / L::WGN * L::WM, split);
   }
-  store_tile<BM, BN, NW, T::STAGE>(g, acc, m0, n0, split, stage0, stage1);
+  store_tile<BM, BN, NW, L::T::STAGE, PLAIN>(g, t.acc, t.m0, t.n0, split, stage0, stage1);
 }
-template <int BM, int BN, bool AT, bool BT, int BK, int NS, int NW>
+template <int BM, int BN, bool AT, bool BT, int NW>
 __global__ void __launch_bounds__(64 * NW) gemm_kernel(const GemmArgs g) {
-  using T = Tile<BM, BN, AT, BT, BK, NW>;
+  using T = Tile<BM, BN, AT, BT, NW>;
   __shared__ __align__(1024) unsigned char stage0[T::STAGE];
   __shared__ __align__(1024) unsigned char stage1[T::STAGE];
-  __shared__ __align__(1024) unsigned char stage2[NS > 2 ? T::STAGE : 16];
-  __shared__ __align__(1024) unsigned char stage3[NS > 3 ? T::STAGE : 16];
   int split, tm, tn;
   place(g, (int)blockIdx.x + (int)blockIdx.y * (g.tiles_m * g.tiles_n), g.tiles_m * g.tiles_n * (int)gridDim.y, split, tm, tn);
-  gemm_tile<BM, BN, AT, BT, BK, NS, NW, false>(g, split, tm, tn, stage0, stage1, stage2, stage3);
+  gemm_tile<BM, BN, AT, BT, NW, false, false>(g, split, tm, tn, stage0, stage1);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -536,27 +600,24 @@ __global__ void __launch_bounds__(64 * NW) gemm_kernel(const GemmArgs g) {
 // The two-stage ring remains for 128 x 128 tiles on four wavefronts, two work-groups per compute unit, where there are
 // enough tiles for that: the second work-group's k-tiles then cover the first one's prologue and epilogue.
 // ------------------------------------------------------------------------------------------------
-template <int BM, int BN, bool AT, bool BT, int NS, int NW, bool SUMS>
+template <int BM, int BN, bool AT, bool BT, int NW, bool SUMS, bool PLAIN>
 __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int split, int tm, int tn, unsigned char* stage0, unsigned char* stage1,
                                                 unsigned char* stage2, unsigned char* stage3) {
-  constexpr int BK = 64;
-  using T = Tile<BM, BN, AT, BT, BK, NW>;
+  constexpr int NS = 4;
+  using T = Tile<BM, BN, AT, BT, NW>;
   using OpA = typename T::OpA;
   using OpB = typename T::OpB;
-  static_assert(NS == 2 || NS == 4, "two or four stages (the fragments' register set alternates with the stage)");
-  constexpr int WGN = NW / 2, WM = BM / 2, WN = BN / WGN, TM = WM / 32, TN = WN / 32, KS = BK / 16;
+  constexpr int WGN = NW / 2, WM = BM / 2, WN = BN / WGN, TM = WM / 16, TN = WN / 16, KS = BK / 32;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
   const int m0 = tm * BM, n0 = tn * BN;
   float colsum[SUMS ? TM : 1] = {};
 
-  floatx16 acc[TM][TN];
+  floatx4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   OpA opa;
   OpB opb;
@@ -569,9 +630,8 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int split, in
   const int k_end = g.partial ? min(g.K, k_base + g.k_chunk) : g.K;
   auto request = [&](unsigned char* stage, int k0) {
     const int kleft = k_end - k0;
-    opa.load(make_rsrc(OpA::origin(g.A, g.lda, m0, k0), OpA::extent(rows_a, g.lda, kleft)), stage, kleft);
-    opb.load(make_rsrc(OpB::origin(g.B, g.ldb, n0, k0), OpB::extent(rows_b, g.ldb, kleft)), stage + OpA::BYTES, kleft);
-    __builtin_amdgcn_sched_barrier(0);
+    opa.load(OpA::origin(g.A, g.lda, m0, k0), OpA::extent(rows_a, g.lda, kleft), stage, kleft);
+    opb.load(OpB::origin(g.B, g.ldb, n0, k0), OpB::extent(rows_b, g.ldb, kleft), stage + OpA::BYTES, kleft);
   };
   constexpr int kPerTile = OpA::NV + OpB::NV;
   half8_t af[2][KS][TM], bf[2][KS][TN];  // the fragments of two consecutive k-tiles
@@ -589,6 +649,7 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int split, in
   auto k_tile = [&](unsigned char* cur, const unsigned char* nxt, int k_refill, int set) {
     __builtin_amdgcn_s_waitcnt(wait_vm_lds((NS - 2) * kPerTile));
     __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
     request(cur, k_refill);
     fetch(nxt, set ^ 1);
 #pragma unroll
@@ -597,56 +658,48 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int split, in
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)  // (B first, k-steps in increasing order: the same sums as gemm_kernel's)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[set][s][j], af[set][s][i], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bf[set][s][j], af[set][s][i], acc[i][j], 0, 0, 0);
     if constexpr (SUMS) {
 #pragma unroll
       for (int s = 0; s < KS; ++s)
 #pragma unroll
         for (int i = 0; i < TM; ++i) add_colsum(colsum[i], af[set][s][i]);
     }
-    Interleave<0, KS * TM * TN, KS * (OpA::READS * TM + OpB::READS * TN)>::run();
+    Interleave<0, KS * TM * TN, KS * (OpA::READS * TM + OpB::READS * TN), kPerTile>::run();
   };
 
   const int nk = (k_end - k_base + BK - 1) / BK;  // (k-tiles past the end multiply zeros: whole rings, no edge conditions)
   request(stage0, k_base);
   request(stage1, k_base + BK);
-  if constexpr (NS == 4) {
-    request(stage2, k_base + 2 * BK);
-    request(stage3, k_base + 3 * BK);
-  }
+  request(stage2, k_base + 2 * BK);
+  request(stage3, k_base + 3 * BK);
+  __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_waitcnt(wait_vm((NS - 1) * kPerTile));
   __builtin_amdgcn_s_barrier();
   fetch(stage0, 0);
-  if constexpr (NS == 2) {
-    for (int kt = 0; kt < nk; kt += 2) {
-      k_tile(stage0, stage1, k_base + (kt + 2) * BK, 0);
-      k_tile(stage1, stage0, k_base + (kt + 3) * BK, 1);
-    }
-  } else {
-    for (int kt = 0; kt < nk; kt += 4) {
-      k_tile(stage0, stage1, k_base + (kt + 4) * BK, 0);
-      k_tile(stage1, stage2, k_base + (kt + 5) * BK, 1);
-      k_tile(stage2, stage3, k_base + (kt + 6) * BK, 0);
-      k_tile(stage3, stage0, k_base + (kt + 7) * BK, 1);
-    }
+  for (int kt = 0; kt < nk; kt += NS) {
+    k_tile(stage0, stage1, k_base + (kt + 4) * BK, 0);
+    k_tile(stage1, stage2, k_base + (kt + 5) * BK, 1);
+    k_tile(stage2, stage3, k_base + (kt + 6) * BK, 0);
+    k_tile(stage3, stage0, k_base + (kt + 7) * BK, 1);
   }
   __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));  // the last refills (all zeros) must land before the stages are reused
   __syncthreads();
   if constexpr (SUMS) {
     if (wn == 0) store_colsum<BM, TM>(g, colsum, m0 + wm * WM, split);
   }
-  store_tile<BM, BN, NW, T::STAGE>(g, acc, m0, n0, split, stage0, stage1);
+  store_tile<BM, BN, NW, T::STAGE, PLAIN>(g, acc, m0, n0, split, stage0, stage1);
 }
-template <int BM, int BN, bool AT, bool BT, int NS, int NW>
+template <int BM, int BN, bool AT, bool BT, int NW>
 __global__ void __launch_bounds__(64 * NW) gemm_small_kernel(const GemmArgs g) {
-  using T = Tile<BM, BN, AT, BT, 64, NW>;
-  __shared__ __align__(1024) unsigned char stage0[T::STAGE];  // separate arrays (see gemm_tile)
+  using T = Tile<BM, BN, AT, BT, NW>;
+  __shared__ __align__(1024) unsigned char stage0[T::STAGE];  // separate arrays (see StripTile)
   __shared__ __align__(1024) unsigned char stage1[T::STAGE];
-  __shared__ __align__(1024) unsigned char stage2[NS > 2 ? T::STAGE : 16];
-  __shared__ __align__(1024) unsigned char stage3[NS > 2 ? T::STAGE : 16];
+  __shared__ __align__(1024) unsigned char stage2[T::STAGE];
+  __shared__ __align__(1024) unsigned char stage3[T::STAGE];
   int split, tm, tn;
   place(g, (int)blockIdx.x + (int)blockIdx.y * (g.tiles_m * g.tiles_n), g.tiles_m * g.tiles_n * (int)gridDim.y, split, tm, tn);
-  gemm_small_tile<BM, BN, AT, BT, NS, NW, false>(g, split, tm, tn, stage0, stage1, stage2, stage3);
+  gemm_small_tile<BM, BN, AT, BT, NW, false, false>(g, split, tm, tn, stage0, stage1, stage2, stage3);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -689,195 +742,103 @@ __device__ __forceinline__ void out_read_slab(const uint32_t (&a)[4], half8_t (&
       : "memory");
 }
 
-template <bool AT, bool BT, int BK, int NS>
+template <bool AT, bool BT>
 __global__ void __launch_bounds__(512) gemm_persistent_kernel(const GemmArgs g) {
   constexpr int BM = 256, BN = 256, NW = 8;
-  using T = Tile<BM, BN, AT, BT, BK, NW>;
-  using OpA = typename T::OpA;
-  using OpB = typename T::OpB;
-  static_assert(NS == 2 || NS == 4, "two or four stages");
-  static_assert(NS * T::STAGE == 128 * 1024, "the ring takes 128 KB; the staging rows take the 32 KB that are left");
-  // separate arrays (see gemm_tile); the third and fourth exist only in the four-stage form
-  __shared__ __align__(1024) unsigned char stage0[T::STAGE];
-  __shared__ __align__(1024) unsigned char stage1[T::STAGE];
-  unsigned char *stage2 = nullptr, *stage3 = nullptr;
-  if constexpr (NS == 4) {
-    __shared__ __align__(1024) unsigned char stage2_[T::STAGE];
-    __shared__ __align__(1024) unsigned char stage3_[T::STAGE];
-    stage2 = stage2_;
-    stage3 = stage3_;
-  }
-  constexpr int WGN = 4, WM = 128, WN = 64, TM = 4, TN = 2, KS = BK / 16;
-  constexpr int kOutPitch = WN * 2;                       // bytes per staged row: 64 fp16
+  using L = StripTile<BM, BN, AT, BT, NW, false>;
+  static_assert(2 * L::T::STAGE == 128 * 1024, "the ring takes 128 KB; the staging rows take the 32 KB that are left");
+  __shared__ __align__(1024) unsigned char stage0[L::T::STAGE];
+  __shared__ __align__(1024) unsigned char stage1[L::T::STAGE];
+  constexpr int kOutPitch = L::WN * 2;                    // bytes per staged row: 64 fp16
   __shared__ __align__(16) unsigned char out_rows[NW * 32 * kOutPitch];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WGN, wn = wave % WGN;
+  const int wm = wave / L::WGN, wn = wave % L::WGN;
   const int nt = g.tiles_m * g.tiles_n;
 
-  auto decode = [&](int lin, int& m0, int& n0) {
+  L t(g);
+  t.k_end = g.K;
+  // Per-lane offsets are recomputed where they are needed rather than kept in registers across the
+  // epilogue (the register file is full there); the empty asm keeps the compiler from merging the copies.
+  auto setup = [&](int lin) {
     const int pid = xcd_order(lin, nt, g.xcds);
     const int per_group = g.group_m * g.tiles_n;
     const int first = (pid / per_group) * g.group_m;
     const int rows = min(g.tiles_m - first, g.group_m);
-    m0 = (first + (pid % per_group) % rows) * BM;
-    n0 = ((pid % per_group) / rows) * BN;
+    int x = tid;
+    asm volatile("" : "+v"(x));
+    t.set_tile((first + (pid % per_group) % rows) * BM, ((pid % per_group) / rows) * BN, x);
+    t.request_first(stage0, stage1, 0);
   };
-
-  OpA opa;
-  OpB opb;
-  int m0, n0, rows_a, rows_b;  // the tile the operand descriptors are set up for
-  // Per-lane offsets are recomputed where they are needed rather than kept in registers across the
-  // epilogue (the register file is full there); the empty asm keeps the compiler from merging the copies.
-  auto setup = [&]() {
-    int t = tid;
-    asm volatile("" : "+v"(t));
-    rows_a = min(g.M - m0, BM);
-    rows_b = min(g.N - n0, BN);
-    opa.init(g.lda, rows_a, t);
-    opb.init(g.ldb, rows_b, t);
-  };
-  typename OpA::Frag fa;
-  typename OpB::Frag fb;
   auto frag_setup = [&]() {
     int l = lane;
     asm volatile("" : "+v"(l));
-    fa = OpA::frag_init(wm * WM, l);
-    fb = OpB::frag_init(wn * WN, l);
+    t.set_fragments(wave, l);
   };
-  auto request = [&](unsigned char* stage, int k0) {
-    const int kleft = g.K - k0;
-    opa.load(make_rsrc(OpA::origin(g.A, g.lda, m0, k0), OpA::extent(rows_a, g.lda, kleft)), stage, kleft);
-    opb.load(make_rsrc(OpB::origin(g.B, g.ldb, n0, k0), OpB::extent(rows_b, g.ldb, kleft)), stage + OpA::BYTES, kleft);
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  constexpr int kPerTile = OpA::NV + OpB::NV;
-  floatx16 acc[TM][TN];
-  half8_t af[2][TM], bf[2][TN];
-  auto fetch = [&](const unsigned char* stage, int s, int set) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i) af[set][i] = OpA::frag(stage, fa, i, s);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) bf[set][j] = OpB::frag(stage + OpA::BYTES, fb, j, s);
-  };
-  auto multiply = [&](int set) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[set][j], af[set][i], acc[i][j], 0, 0, 0);
-  };
-  auto interleave = [&]() { Interleave<0, TM * TN, OpA::READS * TM + OpB::READS * TN>::run(); };
-  auto k_tile = [&](unsigned char* cur, const unsigned char* nxt, int k_refill) {
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      if (s == KS - 1) {
-        __builtin_amdgcn_s_waitcnt(wait_vm_lds((NS - 2) * kPerTile));
-        __builtin_amdgcn_s_barrier();
-        request(cur, k_refill);
-      }
-      fetch(s == KS - 1 ? nxt : cur, (s + 1) % KS, (s + 1) & 1);
-      multiply(s & 1);
-      interleave();
-    }
-  };
-  const int nk = (g.K + BK - 1) / BK;
   const GemmEpilogue& ep = g.ep;
-  // staged rows of this wave: row r, 16-byte chunk c (eight columns) at r * pitch + (c ^ (r & 7)) * 16, so that the
-  // eight lanes that read a row back cover its 128 bytes and sixteen lanes cover every bank once
+  // staged rows of this wave: row r, 16-byte chunk c (eight columns) at r * pitch + (c ^ (r >> 1 & 7)) * 16, so that the
+  // eight lanes that read a row back cover its 128 bytes, and sixteen rows' 8-byte pieces of two columns groups every bank once
   const uint32_t out = lds_addr(out_rows) + wave * (32 * kOutPitch);
-  constexpr int kStores = TM * 4;  // global stores of one wave's epilogue on a tile that lies wholly inside C
+  constexpr int kStores = L::WM / 8;  // global stores of one wave's epilogue on a tile that lies wholly inside C
 
   int lin = blockIdx.x;
-  decode(lin, m0, n0);
-  setup();
-  request(stage0, 0);
-  request(stage1, BK);
-  if constexpr (NS == 4) {
-    request(stage2, 2 * BK);
-    request(stage3, 3 * BK);
-  }
-  __builtin_amdgcn_s_waitcnt(wait_vm((NS - 1) * kPerTile));
+  setup(lin);
+  __builtin_amdgcn_s_waitcnt(wait_vm(L::kAhead));
   __builtin_amdgcn_s_barrier();
   frag_setup();
-  fetch(stage0, 0, 0);
+  t.first_fragments(stage0);
   for (;;) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    if constexpr (NS == 2) {
-      for (int kt = 0; kt < nk; kt += 2) {
-        k_tile(stage0, stage1, (kt + 2) * BK);
-        k_tile(stage1, stage0, (kt + 3) * BK);
-      }
-    } else {
-      for (int kt = 0; kt < nk; kt += 4) {
-        k_tile(stage0, stage1, (kt + 4) * BK);
-        k_tile(stage1, stage2, (kt + 5) * BK);
-        k_tile(stage2, stage3, (kt + 6) * BK);
-        k_tile(stage3, stage0, (kt + 7) * BK);
-      }
-    }
-    // What the epilogue needs of the current tile.  The bias of the lane's columns in the MFMA layout (column group
-    // cg = 4 jj + q holds columns 32 jj + 8 q + 4 (lane / 32) .. + 3 of the wave's 64) is fetched here, ahead of the
+    t.clear();
+    t.multiply(stage0, stage1, 0);
+    // What the epilogue needs of the current tile.  The bias of the lane's columns in the MFMA layout (16 j + 4 (lane / 16) .. + 3
+    // of the wave's 64) is fetched here, ahead of the
     // requests below, and waited for together with the last refills (zeros past k), so that no wait of the epilogue
     // has to pass those requests.
-    const int m0c = m0, n0c = n0;
-    const int g32 = lane >> 5, row = lane & 31;
-    const int col0 = n0c + wn * WN + 4 * g32;
-    half4v_t bias4[8];
+    const int m0c = t.m0, n0c = t.n0;
+    const int quad = lane >> 4, row = lane & 15;
+    half4v_t bias4[L::TN];
 #pragma unroll
-    for (int cg = 0; cg < 8; ++cg) {
-      const int col = col0 + 8 * cg;   // (N is a multiple of 8 and col of 4: the four columns are inside C or all outside)
-      bias4[cg] = half4v_t{0, 0, 0, 0};
-      if (ep.bias && col < g.N) bias4[cg] = *reinterpret_cast<const half4v_t*>(ep.bias + col);
+    for (int j = 0; j < L::TN; ++j) {
+      const int col = n0c + wn * L::WN + 16 * j + 4 * quad;   // (N is a multiple of 8 and col of 4: the four columns are inside C or all outside)
+      bias4[j] = half4v_t{0, 0, 0, 0};
+      if (ep.bias && col < g.N) bias4[j] = *reinterpret_cast<const half4v_t*>(ep.bias + col);
     }
     __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));
     __syncthreads();
     const int next = lin + (int)gridDim.x;
     const bool more = next < nt;
-    if (more) {
-      decode(next, m0, n0);
-      setup();
-      request(stage0, 0);
-      request(stage1, BK);
-      if constexpr (NS == 4) {
-        request(stage2, 2 * BK);
-        request(stage3, 3 * BK);
-      }
-    }
+    if (more) setup(next);
     // ---- epilogue of (m0c, n0c): accumulators -> fp16 -> the wave's staging rows -> 16-byte pieces of whole rows ----
     const int c8 = lane & 7;
-    const int gc = n0c + wn * WN + c8 * 8;
+    const int gc = n0c + wn * L::WN + c8 * 8;
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
+    for (int i = 0; i < L::TM / 2; ++i) {
       uint32_t wa[8];
       half4v_t wv[8];
 #pragma unroll
-      for (int cg = 0; cg < 8; ++cg) {
-        const floatx16& a = acc[i][cg >> 2];
-        const int q = cg & 3;
+      for (int j = 0; j < L::TN; ++j)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float v = a[4 * q + e] * ep.out_scale + (float)bias4[cg][e];
-          if (ep.relu) v = fmaxf(v, 0.f);
-          wv[cg][e] = (_Float16)v;
+        for (int ii = 0; ii < 2; ++ii) {
+          const floatx4& a = t.acc[2 * i + ii][j];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float v = a[e] * ep.out_scale + (float)bias4[j][e];
+            if (ep.relu) v = fmaxf(v, 0.f);
+            wv[2 * j + ii][e] = (_Float16)v;
+          }
+          wa[2 * j + ii] = out + (16 * ii + row) * kOutPitch + (((2 * j + (quad >> 1)) ^ (row >> 1)) << 4) + ((quad & 1) << 3);
         }
-        wa[cg] = out + row * kOutPitch + ((cg ^ (row & 7)) << 4) + (g32 << 3);
-      }
       out_write_slab(wa, wv);   // (the reads of the previous slab have returned: out_read_slab waits for them)
       uint32_t ra[4];
       half8_t rv[4];
 #pragma unroll
       for (int it = 0; it < 4; ++it) {
         const int rl = it * 8 + (lane >> 3);
-        ra[it] = out + rl * kOutPitch + ((c8 ^ (rl & 7)) << 4);
+        ra[it] = out + rl * kOutPitch + ((c8 ^ (rl >> 1 & 7)) << 4);
       }
       out_read_slab(ra, rv);
 #pragma unroll
       for (int it = 0; it < 4; ++it) {
-        const int gr = m0c + wm * WM + i * 32 + it * 8 + (lane >> 3);
+        const int gr = m0c + wm * L::WM + i * 32 + it * 8 + (lane >> 3);
         // streaming store: a result tile is not read again by this product, and letting it stay in L2 pushes out
         // the operand panels the XCD's other tiles are reading (products with wide results: +5-7 %)
         if (gr < g.M && gc < g.N) __builtin_nontemporal_store(rv[it], reinterpret_cast<half8_t*>(g.C + (size_t)gr * g.ldc + gc));
@@ -888,13 +849,13 @@ __global__ void __launch_bounds__(512) gemm_persistent_kernel(const GemmArgs g) 
     // requests and the stores of a full tile); a tile at the edge of C stores fewer rows or columns, so there the
     // wait is for everything
     const bool whole = m0c + BM <= g.M && n0c + BN <= g.N;
-    constexpr int kLater = (NS - 1) * kPerTile + kStores;
+    constexpr int kLater = L::kAhead + kStores;
     static_assert(kLater < 64, "s_waitcnt vmcnt holds six bits");
     if (whole) __builtin_amdgcn_s_waitcnt(wait_vm(kLater));
     else __builtin_amdgcn_s_waitcnt(wait_vm(0));
     __builtin_amdgcn_s_barrier();
     frag_setup();
-    fetch(stage0, 0, 0);
+    t.first_fragments(stage0);
     lin = next;
   }
 }
@@ -958,22 +919,22 @@ __device__ __forceinline__ GemmArgs group_item(const GroupArgs& a, int lin, int&
   sums = tn == 0 && g.colsum;
   return g;
 }
-template <int BM, int BN, int BK, int NS, int NW>
+template <int BM, int BN, int NS, int NW>
 __global__ void __launch_bounds__(64 * NW) wgrad_group_kernel(const GroupArgs a) {
-  using T = Tile<BM, BN, true, true, BK, NW>;
+  using T = Tile<BM, BN, true, true, NW>;
   __shared__ __align__(1024) unsigned char stage0[T::STAGE];
   __shared__ __align__(1024) unsigned char stage1[T::STAGE];
-  __shared__ __align__(1024) unsigned char stage2[NS > 2 ? T::STAGE : 16];
-  __shared__ __align__(1024) unsigned char stage3[NS > 2 ? T::STAGE : 16];
   int split, tm, tn;
   bool sums;
   const GemmArgs g = group_item(a, (int)blockIdx.x, split, tm, tn, sums);
-  if constexpr (BM == 256) {
-    if (sums) gemm_tile<BM, BN, true, true, BK, NS, NW, true>(g, split, tm, tn, stage0, stage1, stage2, stage3);
-    else gemm_tile<BM, BN, true, true, BK, NS, NW, false>(g, split, tm, tn, stage0, stage1, stage2, stage3);
+  if constexpr (NS == 2) {
+    if (sums) gemm_tile<BM, BN, true, true, NW, true, true>(g, split, tm, tn, stage0, stage1);
+    else gemm_tile<BM, BN, true, true, NW, false, true>(g, split, tm, tn, stage0, stage1);
   } else {
-    if (sums) gemm_small_tile<BM, BN, true, true, NS, NW, true>(g, split, tm, tn, stage0, stage1, stage2, stage3);
-    else gemm_small_tile<BM, BN, true, true, NS, NW, false>(g, split, tm, tn, stage0, stage1, stage2, stage3);
+    __shared__ __align__(1024) unsigned char stage2[T::STAGE];
+    __shared__ __align__(1024) unsigned char stage3[T::STAGE];
+    if (sums) gemm_small_tile<BM, BN, true, true, NW, true, true>(g, split, tm, tn, stage0, stage1, stage2, stage3);
+    else gemm_small_tile<BM, BN, true, true, NW, false, true>(g, split, tm, tn, stage0, stage1, stage2, stage3);
   }
 }
 // C and the column sums of every product of the group from the splits' fp32 sums, 8 columns per thread, splits in
@@ -1021,14 +982,15 @@ __global__ void __launch_bounds__(kThreads) wgrad_group_reduce_kernel(const Grou
   st_half8(p.C + (size_t)row * p.ldc + c8 * 8, o);
 }
 
-template <int BM, int BN, bool AT, bool BT, int BK, int NS, int NW>
+// NS = 2: two stages, strip by strip; 4: a ring of four, a whole k-tile of fragments ahead
+template <int BM, int BN, bool AT, bool BT, int NS, int NW>
 void launch_variant(const GemmArgs& g, int splits, hipStream_t stream) {
   const dim3 grid(g.tiles_m * g.tiles_n, splits), block(64 * NW);
-  if constexpr (BM == 256) hipLaunchKernelGGL((gemm_kernel<BM, BN, AT, BT, BK, NS, NW>), grid, block, 0, stream, g);
-  else hipLaunchKernelGGL((gemm_small_kernel<BM, BN, AT, BT, NS, NW>), grid, block, 0, stream, g);
+  if constexpr (NS == 2) hipLaunchKernelGGL((gemm_kernel<BM, BN, AT, BT, NW>), grid, block, 0, stream, g);
+  else hipLaunchKernelGGL((gemm_small_kernel<BM, BN, AT, BT, NW>), grid, block, 0, stream, g);
 }
 
-template <int BM, int BN, int BK, int NS, int NW = 4>
+template <int BM, int BN, int NS, int NW = 4>
 int launch_tile(const GemmArgs& a, bool a_t, bool b_t, int splits, hipStream_t stream) {
   GemmArgs g = a;
   g.tiles_m = ceil_div(g.M, BM);
@@ -1039,18 +1001,17 @@ int launch_tile(const GemmArgs& a, bool a_t, bool b_t, int splits, hipStream_t s
   g.group_m = tuning().gemm_group;
   g.xcds = device_info().xcds;
   if (splits > 1) {
-    static_assert(64 % BK == 0, "the k range of a split is a multiple of 64 whatever the tile, so that the tile shape changes no bit");
-    g.k_chunk = (int)round_up(ceil_div(g.K, splits), 64);
+    g.k_chunk = (int)round_up(ceil_div(g.K, splits), 64);  // (whatever the tile, so that its shape changes no bit)
     splits = ceil_div(g.K, g.k_chunk);  // no empty split
   }
   if (splits <= 1) {
     g.partial = nullptr;
     splits = 1;
   }
-  if (!a_t && !b_t) launch_variant<BM, BN, false, false, BK, NS, NW>(g, splits, stream);
-  else if (!a_t && b_t) launch_variant<BM, BN, false, true, BK, NS, NW>(g, splits, stream);
-  else if (a_t && b_t) launch_variant<BM, BN, true, true, BK, NS, NW>(g, splits, stream);
-  else launch_variant<BM, BN, true, false, BK, NS, NW>(g, splits, stream);
+  if (!a_t && !b_t) launch_variant<BM, BN, false, false, NS, NW>(g, splits, stream);
+  else if (!a_t && b_t) launch_variant<BM, BN, false, true, NS, NW>(g, splits, stream);
+  else if (a_t && b_t) launch_variant<BM, BN, true, true, NS, NW>(g, splits, stream);
+  else launch_variant<BM, BN, true, false, NS, NW>(g, splits, stream);
   NMT_LAUNCH_CHECK();
   if (splits == 1) return NMT_OK;
   const int64_t n = (int64_t)g.M * (g.N / 8);
@@ -1103,12 +1064,12 @@ double large_us(int64_t tiles, int K, int cus) {
 }
 int launch_small_tile(SmallTile t, const GemmArgs& g, bool a_t, bool b_t, int splits, hipStream_t stream) {
   switch (t) {
-    case kTile64: return launch_tile<64, 64, 64, 4>(g, a_t, b_t, splits, stream);
-    case kTile128x64: return launch_tile<128, 64, 64, 4>(g, a_t, b_t, splits, stream);
-    case kTile64x128: return launch_tile<64, 128, 64, 4>(g, a_t, b_t, splits, stream);
-    case kTile128: return launch_tile<128, 128, 64, 4, 8>(g, a_t, b_t, splits, stream);
-    case kTile128x64Many: return launch_tile<128, 64, 64, 2>(g, a_t, b_t, splits, stream);
-    default: return launch_tile<128, 128, 64, 2>(g, a_t, b_t, splits, stream);
+    case kTile64: return launch_tile<64, 64, 4>(g, a_t, b_t, splits, stream);
+    case kTile128x64: return launch_tile<128, 64, 4>(g, a_t, b_t, splits, stream);
+    case kTile64x128: return launch_tile<64, 128, 4>(g, a_t, b_t, splits, stream);
+    case kTile128: return launch_tile<128, 128, 4, 8>(g, a_t, b_t, splits, stream);
+    case kTile128x64Many: return launch_tile<128, 64, 2>(g, a_t, b_t, splits, stream);
+    default: return launch_tile<128, 128, 2>(g, a_t, b_t, splits, stream);
   }
 }
 
@@ -1161,7 +1122,7 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
               (long long)partial_floats, splits);
   if (const int forced = tuning().gemm_tile; forced && splits <= 1) {
     switch (forced) {
-      case 1: return (!a_t && !b_t) ? launch_tile<256, 256, 64, 2, 8>(g, a_t, b_t, 1, stream) : launch_tile<256, 256, 32, 4, 8>(g, a_t, b_t, 1, stream);
+      case 1: return launch_tile<256, 256, 2, 8>(g, a_t, b_t, 1, stream);
       case 2: return launch_small_tile(kTile128, g, a_t, b_t, 1, stream);
       case 3: return launch_small_tile(kTile128x64, g, a_t, b_t, 1, stream);
       case 4: return launch_small_tile(kTile64x128, g, a_t, b_t, 1, stream);
@@ -1212,15 +1173,12 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
       pg.tiles_n = ceil_div(N, 256);
       pg.group_m = tuning().gemm_group;
       pg.partial = nullptr;
-      if (!b_t) hipLaunchKernelGGL((gemm_persistent_kernel<false, false, 64, 2>), dim3(cus), dim3(512), 0, stream, pg);
-      else hipLaunchKernelGGL((gemm_persistent_kernel<false, true, 32, 4>), dim3(cus), dim3(512), 0, stream, pg);
+      if (!b_t) hipLaunchKernelGGL((gemm_persistent_kernel<false, false>), dim3(cus), dim3(512), 0, stream, pg);
+      else hipLaunchKernelGGL((gemm_persistent_kernel<false, true>), dim3(cus), dim3(512), 0, stream, pg);
       NMT_LAUNCH_CHECK();
       return NMT_OK;
     }
-    // k-contiguous operands are fetched in whole 128-byte lines by 64-deep stages; transposed ones
-    // gain more from the longer look-ahead of four 32-deep stages
-    if (!a_t && !b_t) return launch_tile<256, 256, 64, 2, 8>(g, a_t, b_t, splits, stream);
-    return launch_tile<256, 256, 32, 4, 8>(g, a_t, b_t, splits, stream);
+    return launch_tile<256, 256, 2, 8>(g, a_t, b_t, splits, stream);
   }
   if (splits > 1) return launch_small_tile(kTile128Many, g, a_t, b_t, splits, stream);
   return launch_small_tile(small, g, a_t, b_t, 1, stream);
@@ -1349,10 +1307,10 @@ int launch_wgrad_group_impl(const WgradProduct* products, int n, float out_scale
   }
   const dim3 grid(a.total);
   switch (tile) {
-    case kGroup256: hipLaunchKernelGGL((wgrad_group_kernel<256, 256, 32, 4, 8>), grid, dim3(512), 0, stream, a); break;
-    case kGroup128Many: hipLaunchKernelGGL((wgrad_group_kernel<128, 128, 64, 2, 4>), grid, dim3(256), 0, stream, a); break;
-    case kGroup128: hipLaunchKernelGGL((wgrad_group_kernel<128, 128, 64, 4, 8>), grid, dim3(512), 0, stream, a); break;
-    default: hipLaunchKernelGGL((wgrad_group_kernel<64, 64, 64, 4, 4>), grid, dim3(256), 0, stream, a); break;
+    case kGroup256: hipLaunchKernelGGL((wgrad_group_kernel<256, 256, 2, 8>), grid, dim3(512), 0, stream, a); break;
+    case kGroup128Many: hipLaunchKernelGGL((wgrad_group_kernel<128, 128, 2, 4>), grid, dim3(256), 0, stream, a); break;
+    case kGroup128: hipLaunchKernelGGL((wgrad_group_kernel<128, 128, 4, 8>), grid, dim3(512), 0, stream, a); break;
+    default: hipLaunchKernelGGL((wgrad_group_kernel<64, 64, 4, 4>), grid, dim3(256), 0, stream, a); break;
   }
   NMT_LAUNCH_CHECK();
   if (splits == 1) return NMT_OK;

@@ -73,6 +73,23 @@ def test_gemm_small_tiles_match_oracle(M, N, K, mode):
     assert_close16(host(dC), Am @ Bm.T + bias, f"small tiles {mode} {M}x{N}x{K}")
 
 
+# the two-stage loop with the large tile on results of one to four ragged tiles: contractions of less than one k-tile, of an odd and an even
+# number of them, with a last one of 8, 40 and 64 (the loop multiplies pairs of k-tiles; what lies past the end has to arrive as zeros)
+@pytest.mark.parametrize("K", [8, 64, 72, 128, 168, 320, 1000])
+@pytest.mark.parametrize("a_t,b_t", [(0, 0), (0, 1), (1, 1), (1, 0)])
+def test_gemm_large_tile_short_and_ragged_contractions_match_oracle(K, a_t, b_t):
+    M, N = 264, 520 - K % 64
+    rng = np.random.default_rng(K)
+    Am, Bm = f16(rng.normal(size=(M, K))), f16(rng.normal(size=(N, K)) / math.sqrt(K))
+    dC = torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV)
+    A.nmt_tuning("gemm_tile", 1)
+    try:
+        A.nmt_op_gemm(dev16(Am.T if a_t else Am), a_t, M if a_t else K, dev16(Bm.T if b_t else Bm), b_t, N if b_t else K, dC, N, M, N, K)
+    finally:
+        A.nmt_tuning("defaults")
+    assert_close16(host(dC), Am @ Bm.T, f"large tile {a_t}{b_t} {M}x{N}x{K}")
+
+
 @pytest.mark.parametrize("M,N,K", [(128, 128, 16), (200, 136, 72), (37, 1000, 66), (515, 264, 203), (1031, 2052, 1024)])
 @pytest.mark.parametrize("mode", ["fwd", "dgrad", "wgrad"])
 def test_fp32_comparison_gemm_matches_oracle(M, N, K, mode):
