@@ -703,24 +703,24 @@ __global__ void __launch_bounds__(64 * NW) gemm_small_kernel(const GemmArgs g) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Persistent form of the 256 x 256, 8-wave kernel for products whose epilogue loads nothing per
-// element (bias, ReLU and the output scale only): one work-group per compute unit walks its tiles
-// (the same tile -> XCD assignment as above) and asks for the first k-tiles of its next tile -- the
-// whole stage ring -- BEFORE it stores the current one, so that their latency passes behind the
-// epilogue and the next main loop starts with its ring full.  Vector-memory operations retire in
-// issue order on one counter: the wait for the first of those k-tiles is "at most as many operations
-// outstanding as were issued after it" (the other requests and the epilogue's stores), which does not
-// wait for the stores.  The epilogue leaves the stages alone: bias, ReLU and scale are applied to the
-// accumulators where they are (MFMA layout), the fp16 results pass through the 32 KB of LDS the stage
-// ring leaves free (32 rows x 64 columns per wave, wave-private, so no work-group barrier) and leave
-// as whole 128-byte rows.
+// Persistent form of the 256 x 256, 8-wave kernel: one work-group per compute unit walks its tiles (the same tile -> XCD assignment
+// as above) in one unbroken sequence of k-tiles.  The requests that the last k-tiles of a tile would make past its end are the
+// first ones of the next tile, and the fragment reads of its last step are the next tile's first, so that between the
+// last product of a tile and the first of the next there is the epilogue and nothing else: no drained ring, no first operands to
+// wait for.  The epilogue leaves the stages and the fragments' registers alone: results pass through the 32 KB of LDS that the stage
+// ring leaves free (wave-private, so no work-group barrier) and leave as whole 128-byte rows.  Bounds are checked by the
+// buffer descriptors of C and of what the epilogue loads, so it has no branches per row.
+// Before (next tile's first k-tiles requested in one go after the last product, one epilogue for all forms with a select per value,
+// sum and mask in the form with one tile per work-group) and now, us, 52704 rows: 4096 x 1024 with bias and ReLU 383 / 360, 1024 x 1024 104 /
+// 99, 32768 x 1024 3079 / 2810, + another matrix 1024 x 4096 421 / 375, ReLU mask 4096 x 1024 502 / 425; 26000 x 2048 x 512 with mask 89 / 73.
+// What is left per tile is the epilogue, about 2 us; the k-tiles are bound by power (see StripTile).
 // ------------------------------------------------------------------------------------------------
 // LDS accesses of the staging rows, written as instructions: while requests into the stages are in
 // flight the compiler would otherwise put a wait for ALL of them in front of any LDS access it
 // cannot tell apart from their targets.
 __device__ __forceinline__ uint32_t lds_addr(const void* p) { return (uint32_t)(uintptr_t)(lds_void_ptr)p; }
 typedef _Float16 half4v_t __attribute__((ext_vector_type(4)));
-// eight 8-byte writes: one 32 x 64 slab of results (the lane's four consecutive columns of each of its eight column groups)
+// eight 8-byte writes: one 32 x 64 slab of results (the lane's four consecutive columns in two rows of four column groups)
 __device__ __forceinline__ void out_write_slab(const uint32_t (&a)[8], const half4v_t (&v)[8]) {
   asm volatile(
       "ds_write_b64 %0, %8\n\tds_write_b64 %1, %9\n\tds_write_b64 %2, %10\n\tds_write_b64 %3, %11\n\t"
@@ -730,10 +730,18 @@ __device__ __forceinline__ void out_write_slab(const uint32_t (&a)[8], const hal
         "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7])
       : "memory");
 }
+// four 16-byte writes: one 16 x 64 slab of sums
+__device__ __forceinline__ void out_write_sums(const uint32_t (&a)[4], const floatx4 (&v)[4]) {
+  asm volatile("ds_write_b128 %0, %4\n\tds_write_b128 %1, %5\n\tds_write_b128 %2, %6\n\tds_write_b128 %3, %7"
+               :
+               : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3])
+               : "memory");
+}
 // the slab back as rows: four 16-byte reads, returned once all have arrived (LDS operations of a wave complete in
 // order, so the writes above are done too); one instruction sequence, so that nothing touches the registers between
 // the reads and the wait
-__device__ __forceinline__ void out_read_slab(const uint32_t (&a)[4], half8_t (&d)[4]) {
+template <typename V>
+__device__ __forceinline__ void out_read_slab(const uint32_t (&a)[4], V (&d)[4]) {
   asm volatile(
       "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
       "s_waitcnt lgkmcnt(0)"
@@ -741,123 +749,170 @@ __device__ __forceinline__ void out_read_slab(const uint32_t (&a)[4], half8_t (&
       : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
       : "memory");
 }
+typedef float floatx8 __attribute__((ext_vector_type(8)));
+typedef uint32_t uint4v_t __attribute__((ext_vector_type(4)));
+typedef uint32_t uint2v_t __attribute__((ext_vector_type(2)));
+constexpr int kStream = 2;  // non-temporal
+// 16 bytes at byte offset `off` (past the extent: zeros come back, nothing is stored)
+__device__ __forceinline__ half8_t buffer_half8(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+// streaming store: a result tile is not read again by its product, and letting it stay in L2 pushes out
+// the operand panels the XCD's other tiles are reading (products with wide results: +5-7 %)
+__device__ __forceinline__ void buffer_store_half8(__amdgpu_buffer_rsrc_t r, uint32_t off, half8_t v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4v_t, v), r, (int)off, 0, kStream);
+}
 
-template <bool AT, bool BT>
+// What an epilogue of the persistent form does: nothing; output scale and bias; these and ReLU; output scale and a sum with another matrix, or the
+// ReLU mask of the backward pass.  (A kernel each: chosen per value inside one they cost an instruction more each, chosen per
+// slab of rows the register file overflows.)
+enum StoreForm { kStorePlain, kStoreBias, kStoreRelu, kStoreAdd, kStoreMask };
+template <bool BT, StoreForm FORM>
 __global__ void __launch_bounds__(512) gemm_persistent_kernel(const GemmArgs g) {
   constexpr int BM = 256, BN = 256, NW = 8;
-  using L = StripTile<BM, BN, AT, BT, NW, false>;
+  using L = StripTile<BM, BN, false, BT, NW, false>;
   static_assert(2 * L::T::STAGE == 128 * 1024, "the ring takes 128 KB; the staging rows take the 32 KB that are left");
-  __shared__ __align__(1024) unsigned char stage0[L::T::STAGE];
+  __shared__ __align__(1024) unsigned char stage0[L::T::STAGE];  // separate arrays (see StripTile)
   __shared__ __align__(1024) unsigned char stage1[L::T::STAGE];
-  constexpr int kOutPitch = L::WN * 2;                    // bytes per staged row: 64 fp16
-  __shared__ __align__(16) unsigned char out_rows[NW * 32 * kOutPitch];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int kOutBytes = 4096;  // staging of a wave: 32 rows of 64 fp16, or 16 rows of 64 fp32
+  __shared__ __align__(16) unsigned char out_rows[NW * kOutBytes];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / L::WGN, wn = wave % L::WGN;
   const int nt = g.tiles_m * g.tiles_n;
 
   L t(g);
   t.k_end = g.K;
-  // Per-lane offsets are recomputed where they are needed rather than kept in registers across the
-  // epilogue (the register file is full there); the empty asm keeps the compiler from merging the copies.
-  auto setup = [&](int lin) {
+  auto set_tile = [&](int lin) {
     const int pid = xcd_order(lin, nt, g.xcds);
     const int per_group = g.group_m * g.tiles_n;
     const int first = (pid / per_group) * g.group_m;
     const int rows = min(g.tiles_m - first, g.group_m);
-    int x = tid;
-    asm volatile("" : "+v"(x));
-    t.set_tile((first + (pid % per_group) % rows) * BM, ((pid % per_group) / rows) * BN, x);
-    t.request_first(stage0, stage1, 0);
-  };
-  auto frag_setup = [&]() {
-    int l = lane;
-    asm volatile("" : "+v"(l));
-    t.set_fragments(wave, l);
+    t.set_tile((first + (pid % per_group) % rows) * BM, ((pid % per_group) / rows) * BN, tid);
   };
   const GemmEpilogue& ep = g.ep;
-  // staged rows of this wave: row r, 16-byte chunk c (eight columns) at r * pitch + (c ^ (r >> 1 & 7)) * 16, so that the
-  // eight lanes that read a row back cover its 128 bytes, and sixteen rows' 8-byte pieces of two columns groups every bank once
-  const uint32_t out = lds_addr(out_rows) + wave * (32 * kOutPitch);
-  constexpr int kStores = L::WM / 8;  // global stores of one wave's epilogue on a tile that lies wholly inside C
+  const uint32_t out = lds_addr(out_rows) + wave * kOutBytes;
+  const int last = ((g.K + BK - 1) / BK + 1) / 2 * 2;  // k-tiles of a tile, an even number (one past the end multiplies zeros)
 
   int lin = blockIdx.x;
-  setup(lin);
+  set_tile(lin);
+  t.set_fragments(wave, lane);
+  t.request_first(stage0, stage1, 0);
   __builtin_amdgcn_s_waitcnt(wait_vm(L::kAhead));
   __builtin_amdgcn_s_barrier();
-  frag_setup();
   t.first_fragments(stage0);
   for (;;) {
     t.clear();
-    t.multiply(stage0, stage1, 0);
-    // What the epilogue needs of the current tile.  The bias of the lane's columns in the MFMA layout (16 j + 4 (lane / 16) .. + 3
-    // of the wave's 64) is fetched here, ahead of the
-    // requests below, and waited for together with the last refills (zeros past k), so that no wait of the epilogue
-    // has to pass those requests.
-    const int m0c = t.m0, n0c = t.n0;
-    const int quad = lane >> 4, row = lane & 15;
-    half4v_t bias4[L::TN];
-#pragma unroll
-    for (int j = 0; j < L::TN; ++j) {
-      const int col = n0c + wn * L::WN + 16 * j + 4 * quad;   // (N is a multiple of 8 and col of 4: the four columns are inside C or all outside)
-      bias4[j] = half4v_t{0, 0, 0, 0};
-      if (ep.bias && col < g.N) bias4[j] = *reinterpret_cast<const half4v_t*>(ep.bias + col);
+    for (int kt = 0; kt + 2 < last; kt += 2) {
+      t.template k_step<0>(stage0, stage1, (kt + 1) * BK);
+      t.template k_step<1>(stage1, stage0, (kt + 2) * BK);
+      t.template k_step<0>(stage1, stage0, (kt + 2) * BK);
+      t.template k_step<1>(stage0, stage1, (kt + 3) * BK);
     }
-    __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));
-    __syncthreads();
-    const int next = lin + (int)gridDim.x;
-    const bool more = next < nt;
-    if (more) setup(next);
-    // ---- epilogue of (m0c, n0c): accumulators -> fp16 -> the wave's staging rows -> 16-byte pieces of whole rows ----
-    const int c8 = lane & 7;
-    const int gc = n0c + wn * L::WN + c8 * 8;
-#pragma unroll
-    for (int i = 0; i < L::TM / 2; ++i) {
-      uint32_t wa[8];
-      half4v_t wv[8];
+    // the last two k-tiles: from the stage change on, requests and fragment reads are the next tile's (there is none: past the end)
+    t.template k_step<0>(stage0, stage1, (last - 1) * BK);
+    const int m0 = t.m0, n0 = t.n0, rows = t.rows_a, cols = t.rows_b;
+    lin += (int)gridDim.x;
+    const bool more = lin < nt;
+    if (more) set_tile(lin);
+    const int k_next = more ? 0 : t.k_end;
+    half4v_t bias[L::TN];
+    if constexpr (FORM == kStoreBias || FORM == kStoreRelu) {
+      // the bias of the lane's columns in the MFMA layout (16 j + 4 (lane / 16) .. + 3 of the wave's 64; no bias: extent 0), waited for
+      // with the operands at the next stage change
+      const __amdgpu_buffer_rsrc_t r = make_rsrc(ep.bias + n0, ep.bias ? (uint32_t)cols * 2u : 0u);
 #pragma unroll
       for (int j = 0; j < L::TN; ++j)
+        bias[j] = __builtin_bit_cast(half4v_t, __builtin_amdgcn_raw_buffer_load_b64(r, (wn * L::WN + 16 * j + 4 * (lane >> 4)) * 2, 0, 0));
+    }
+    t.template k_step<1>(stage1, stage0, k_next);
+    t.template k_step<0>(stage1, stage0, k_next);
+    t.template k_step<1>(stage0, stage1, k_next + BK);
+    t.settle();
+
+    // ---- epilogue of the tile at (m0, n0) ----
+    // a lane's piece of a staged row: eight columns, in rows lane / 8, + 8, + 16, ... of the wave's 128
+    const int c8 = lane & 7, r8 = lane >> 3, quad = lane >> 4, row = lane & 15;
+    const uint32_t extent = ((uint32_t)(rows - 1) * (uint32_t)g.ldc + (uint32_t)cols) * 2u;
+    const __amdgpu_buffer_rsrc_t to = make_rsrc(g.C + (size_t)m0 * g.ldc + n0, extent);
+    const int col = wn * L::WN + c8 * 8;
+    const uint32_t step = 16u * (uint32_t)g.ldc;  // bytes of eight rows
+    uint32_t at = col < cols ? ((uint32_t)(wm * L::WM + r8) * (uint32_t)g.ldc + (uint32_t)col) * 2u : kOob;
+    if constexpr (FORM <= kStoreRelu) {
+      // accumulators -> fp16 -> 32 staged rows -> 16-byte pieces of whole rows.  Staged row r, 16-byte chunk c (eight columns) at
+      // r * 128 + (c ^ (r >> 1 & 7)) * 16: the eight lanes that read a row back cover its 128 bytes, and the 8-byte pieces that 32 lanes
+      // write every bank once.
 #pragma unroll
-        for (int ii = 0; ii < 2; ++ii) {
-          const floatx4& a = t.acc[2 * i + ii][j];
+      for (int i = 0; i < L::TM / 2; ++i) {
+        uint32_t wa[8];
+        half4v_t wv[8];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            float v = a[e] * ep.out_scale + (float)bias4[j][e];
-            if (ep.relu) v = fmaxf(v, 0.f);
-            wv[2 * j + ii][e] = (_Float16)v;
+        for (int j = 0; j < L::TN; ++j)
+#pragma unroll
+          for (int ii = 0; ii < 2; ++ii) {
+            floatx4 v = t.acc[2 * i + ii][j];
+            if constexpr (FORM != kStorePlain) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                v[e] = v[e] * ep.out_scale + (float)bias[j][e];
+                if constexpr (FORM == kStoreRelu) v[e] = fmaxf(v[e], 0.f);
+              }
+            }
+            wv[2 * j + ii] = __builtin_convertvector(v, half4v_t);
+            wa[2 * j + ii] = out + (16 * ii + row) * 128 + (((2 * j + (quad >> 1)) ^ (row >> 1)) << 4) + ((quad & 1) << 3);
           }
-          wa[2 * j + ii] = out + (16 * ii + row) * kOutPitch + (((2 * j + (quad >> 1)) ^ (row >> 1)) << 4) + ((quad & 1) << 3);
+        out_write_slab(wa, wv);   // (the reads of the previous slab have returned: out_read_slab waits for them)
+        uint32_t ra[4];
+        half8_t rv[4];
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+          const int rl = it * 8 + r8;
+          ra[it] = out + rl * 128 + ((c8 ^ (rl >> 1 & 7)) << 4);
         }
-      out_write_slab(wa, wv);   // (the reads of the previous slab have returned: out_read_slab waits for them)
-      uint32_t ra[4];
-      half8_t rv[4];
+        out_read_slab(ra, rv);
 #pragma unroll
-      for (int it = 0; it < 4; ++it) {
-        const int rl = it * 8 + (lane >> 3);
-        ra[it] = out + rl * kOutPitch + ((c8 ^ (rl >> 1 & 7)) << 4);
+        for (int it = 0; it < 4; ++it, at += step) buffer_store_half8(to, at, rv[it]);
       }
-      out_read_slab(ra, rv);
+    } else {
+      // what is added, or masks, comes in the pieces the results leave in, eight at a time; the sums are staged as they are, 16 rows
+      // at a time (one rounding, at the end).  Staged row r, 16-byte chunk c (four columns) at r * 256 + (c ^ r) * 16.
+      const half_t* const src = FORM == kStoreAdd ? ep.add : ep.relu_src;
+      const __amdgpu_buffer_rsrc_t from = make_rsrc(src + (size_t)m0 * g.ldc + n0, extent);
+      uint32_t next = at;
 #pragma unroll
-      for (int it = 0; it < 4; ++it) {
-        const int gr = m0c + wm * L::WM + i * 32 + it * 8 + (lane >> 3);
-        // streaming store: a result tile is not read again by this product, and letting it stay in L2 pushes out
-        // the operand panels the XCD's other tiles are reading (products with wide results: +5-7 %)
-        if (gr < g.M && gc < g.N) __builtin_nontemporal_store(rv[it], reinterpret_cast<half8_t*>(g.C + (size_t)gr * g.ldc + gc));
+      for (int h = 0; h < 2; ++h) {
+        half8_t pre[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q, next += step) pre[q] = buffer_half8(from, next);
+#pragma unroll
+        for (int i = 4 * h; i < 4 * h + 4; ++i) {
+          uint32_t wa[4], ra[4];
+          floatx4 rv[4];
+#pragma unroll
+          for (int j = 0; j < L::TN; ++j) wa[j] = out + row * 256 + (((4 * j + quad) ^ row) << 4);
+#pragma unroll
+          for (int it = 0; it < 4; ++it) {
+            const int rl = (it >> 1) * 8 + r8;
+            ra[it] = out + rl * 256 + (((2 * c8 + (it & 1)) ^ rl) << 4);
+          }
+          out_write_sums(wa, t.acc[i]);
+          out_read_slab(ra, rv);
+#pragma unroll
+          for (int it = 0; it < 2; ++it, at += step) {
+            const half8_t p = pre[2 * (i - 4 * h) + it];
+            floatx8 v;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const float x = rv[2 * it + (e >> 2)][e & 3] * ep.out_scale;
+              v[e] = FORM == kStoreAdd ? x + (float)p[e] : (float)p[e] > 0.f ? x * ep.mask_scale : 0.f;
+            }
+            buffer_store_half8(to, at, __builtin_convertvector(v, half8_t));  // (rounded to fp32 first, as in the form with one tile per work-group)
+          }
+        }
       }
     }
     if (!more) break;
-    // wait for the first k-tile of the new tile: everything issued after it may stay outstanding (the other early
-    // requests and the stores of a full tile); a tile at the edge of C stores fewer rows or columns, so there the
-    // wait is for everything
-    const bool whole = m0c + BM <= g.M && n0c + BN <= g.N;
-    constexpr int kLater = L::kAhead + kStores;
-    static_assert(kLater < 64, "s_waitcnt vmcnt holds six bits");
-    if (whole) __builtin_amdgcn_s_waitcnt(wait_vm(kLater));
-    else __builtin_amdgcn_s_waitcnt(wait_vm(0));
-    __builtin_amdgcn_s_barrier();
-    frag_setup();
-    t.first_fragments(stage0);
-    lin = next;
   }
+  __builtin_amdgcn_s_waitcnt(wait_vm(0));  // (the last requests, zeros, land in this work-group's LDS)
 }
 
 // C[m, n] = fp16(sum_z partial[z][m][n]), 8 columns per thread, splits summed in increasing order
@@ -1020,11 +1075,12 @@ int launch_tile(const GemmArgs& a, bool a_t, bool b_t, int splits, hipStream_t s
   return NMT_OK;
 }
 
-// The tile shapes below 256 x 256 and what a product takes with each, in us, from timings of 32 shapes (384 to 6000 rows,
-// 512 to 4096 columns, k 512 to 4096; forward form, operands rotating through 300 MB): `fixed` (launch, first operands,
+// The tile shapes below 256 x 256 and what a product takes with each, in us, fitted to timings of 160 shapes (130 to 26000 rows,
+// 64 to 4096 columns, k 64 to 4096; x W^T and dy W, operands rotating through 300 MB): `fixed` (launch, first operands,
 // epilogue) + k-tiles of 64 x the time of one, which depends on how many tiles share a compute unit (at most `per_cu`, by
-// LDS), + `again` for every further round of work-groups.  The model is within 20 % of
-// the measured times and the shape it picks within 13 % of the fastest of the six on all of them.
+// LDS), + `again` for every further round of work-groups.  The model is within 3 to 5 % of
+// the measured times on average; the shape it picks, with the large tile among them, costs 0.6 % more than the fastest on average and 15 % at worst
+// (constants fitted to the kernels before these: 1.3 % and 26 %, 6000 x 1024 x 3072 in large tiles, 55 us, for 44 in 128 x 128).
 enum SmallTile { kTile64, kTile128x64, kTile64x128, kTile128, kTile128x64Many, kTile128Many, kSmallTiles };
 struct TileCost {
   int bm, bn, per_cu;
@@ -1032,12 +1088,12 @@ struct TileCost {
   double k_tile[3];  // one k-tile while 1, 2, 3 tiles share the compute unit
 };
 constexpr TileCost kTileCost[kSmallTiles] = {
-    {64, 64, 2, 3.6, 1.0, {0.165, 0.40, 0.}},         // four stages
-    {128, 64, 1, 4.1, 3.8, {0.25, 0., 0.}},           // four stages
-    {64, 128, 1, 4.1, 3.8, {0.25, 0., 0.}},           // four stages
-    {128, 128, 1, 4.4, 5.8, {0.44, 0., 0.}},          // four stages, eight wavefronts
-    {128, 64, 3, 4.3, 1.8, {0.48, 0.66, 0.94}},       // two stages
-    {128, 128, 2, 5.7, 3.5, {0.55, 0.88, 0.}},        // two stages
+    {64, 64, 2, 4.3, 1.5, {0.16, 0.35, 0.}},          // four stages
+    {128, 64, 1, 4.0, 2.6, {0.295, 0., 0.}},          // four stages
+    {64, 128, 1, 4.0, 2.6, {0.295, 0., 0.}},          // four stages
+    {128, 128, 1, 4.0, 4.2, {0.41, 0., 0.}},          // four stages, eight wavefronts
+    {128, 64, 3, 4.5, 1.9, {0.49, 0.61, 0.875}},      // two stages
+    {128, 128, 2, 4.9, 3.6, {0.63, 0.87, 0.}},        // two stages
 };
 double tile_us(const TileCost& c, int64_t tiles, int K, int cus) {
   const int nk = ceil_div(K, 64);
@@ -1055,10 +1111,9 @@ SmallTile choose_small_tile(int M, int N, int K, int cus, double& best_us) {
   }
   return (SmallTile)best;
 }
-// The same for at most one 256 x 256 tile per compute unit (row-major A; 6000 to 26000 rows, 512 to 4096 columns, k 512 to
-// 4096: within 10 % of the measured times): a k-tile costs more the more compute units are at work, because the clocks drop.
+// The same for at most one 256 x 256 tile per compute unit (row-major A; within 3 % of the measured times on average): a k-tile costs more the more compute units are at work, because the clocks drop.
 double large_us(int64_t tiles, int K, int cus) {
-  constexpr double kFixed = 8.6, kFew = 1.05, kFull = 1.65;
+  constexpr double kFixed = 5.5, kFew = 1.09, kFull = 1.65;
   const double fill = (double)tiles / cus;
   return kFixed + ceil_div(K, 64) * (kFew + (kFull - kFew) * fill * fill * fill);
 }
@@ -1134,7 +1189,7 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
   double small_us;
   const SmallTile small = choose_small_tile(M, N, K, cus, small_us);
   // Up to one round of large tiles they are taken where they cost less than the best small ones (9000 x 1024 x 4096, 144 large tiles:
-  // 79 us against 97; 17700 x 512 x 2048, 140: 44 against 52); a fixed line at three quarters of a round gave these small
+  // 79 us against 90; 17700 x 512 x 2048, 140: 42 against 50; 6000 x 1024 x 4096, 96: 75 against 54); a fixed line at three quarters of a round gave all of these small
   // ones.  That line remains where the costs were not measured: products cut along k, with a k-major A, or beside others.
   const bool large = (splits > 1 || a_t || share > 1 || t256 > cus) ? t256 * splits * share >= full : large_us(t256, K, cus) <= small_us;
   if (large) {
@@ -1158,23 +1213,28 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
                                 K, tail, stream, nullptr, 0, 1);
       }
     }
-    // More tiles than compute units, no split along k, row-major A, an epilogue that loads nothing per
-    // element (bias, ReLU, scale): the persistent form.  (With an addend or a mask to load it gained 1-11 % on a
-    // product running alone but nothing on the update, where the weight-gradient kernels of the second stream
-    // share the chip and work-groups that never leave their compute unit cost more than they gain; the form no
-    // longer has those epilogues.  Not for a k-major A either: the one such product without a split, the
+    // No split along k, row-major A, one of the epilogues that have it: the persistent form, also where every work-group has one tile
+    // only (its epilogue is the faster one).  Not for a k-major A: the one such product without a split, the
     // vocabulary weight gradient, has so long a contraction that the tile change hardly counts, and measured
-    // 6 % slower in this form.  From one round on and not only from two: 26000 x 1536 x 512 is 510 tiles in its full rounds,
-    // 50 us one tile per work-group, 44 in this form.)
-    const bool loads_in_epilogue = ep.add || ep.relu_src || ep.drop.thr;
-    if (splits == 1 && t256 > cus && !a_t && tuning().gemm_persist && !loads_in_epilogue) {
+    // 6 % slower in this form.
+    if (splits == 1 && !a_t && tuning().gemm_persist && !ep.drop.thr && !((ep.add || ep.relu_src) && (ep.bias || ep.relu)) &&
+        !(ep.add && ep.relu_src)) {
+      const int groups = (int)(t256 < cus ? t256 : cus);
       GemmArgs pg = g;
       pg.tiles_m = ceil_div(M, 256);
       pg.tiles_n = ceil_div(N, 256);
       pg.group_m = tuning().gemm_group;
       pg.partial = nullptr;
-      if (!b_t) hipLaunchKernelGGL((gemm_persistent_kernel<false, false>), dim3(cus), dim3(512), 0, stream, pg);
-      else hipLaunchKernelGGL((gemm_persistent_kernel<false, true>), dim3(cus), dim3(512), 0, stream, pg);
+      auto run = [&](auto bt) {
+        constexpr bool BT = decltype(bt)::value;
+        if (ep.add) hipLaunchKernelGGL((gemm_persistent_kernel<BT, kStoreAdd>), dim3(groups), dim3(512), 0, stream, pg);
+        else if (ep.relu_src) hipLaunchKernelGGL((gemm_persistent_kernel<BT, kStoreMask>), dim3(groups), dim3(512), 0, stream, pg);
+        else if (ep.relu) hipLaunchKernelGGL((gemm_persistent_kernel<BT, kStoreRelu>), dim3(groups), dim3(512), 0, stream, pg);
+        else if (ep.bias || ep.out_scale != 1.f) hipLaunchKernelGGL((gemm_persistent_kernel<BT, kStoreBias>), dim3(groups), dim3(512), 0, stream, pg);
+        else hipLaunchKernelGGL((gemm_persistent_kernel<BT, kStorePlain>), dim3(groups), dim3(512), 0, stream, pg);
+      };
+      if (b_t) run(std::true_type{});
+      else run(std::false_type{});
       NMT_LAUNCH_CHECK();
       return NMT_OK;
     }

@@ -279,6 +279,32 @@ def test_gemm_persistent_form_matches_oracle_and_the_tile_per_work_group_form():
         assert_close16(host(dC), x2 @ Wt2, f"persistent, k-major B, k={K2}")
 
 
+# rows and columns that end inside a tile, contractions of one, two and five k-tiles; the sum also in place, as the gradient at the encoder output is
+@pytest.mark.parametrize("K", [40, 128, 264])
+@pytest.mark.parametrize("b_t", [0, 1])
+@pytest.mark.parametrize("form", ["add", "add in place", "mask"])
+def test_gemm_persistent_sum_and_mask_match_oracle_and_the_tile_per_work_group_form(K, b_t, form):
+    M, N = 11016, 1800                           # 44 x 8 tiles
+    rng = np.random.default_rng(K)
+    x, W = f16(rng.normal(size=(M, K))), f16(rng.normal(size=(N, K)) / math.sqrt(K))
+    other = f16(rng.normal(size=(M, N)))
+    want = x @ W.T
+    want = want * 1.25 * (other > 0) if form == "mask" else want + other
+    dx, dW, d_other = dev16(x), dev16(W.T if b_t else W), dev16(other)
+    got = []
+    try:
+        for mode in (1, 0):
+            A.nmt_tuning("gemm_persist", mode)
+            c = d_other.clone() if form == "add in place" else torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV)
+            kw = dict(relu_src=d_other, mask_scale=1.25) if form == "mask" else dict(add=c if form == "add in place" else d_other)
+            A.nmt_op_gemm(dx, 0, K, dW, b_t, N if b_t else K, c, N, M, N, K, **kw)
+            got.append(c)
+    finally:
+        A.nmt_tuning("defaults")
+    assert_close16(host(got[0]), want, f"persistent, {form}, k={K}")
+    assert torch.equal(got[0].view(torch.int16), got[1].view(torch.int16))
+
+
 def test_gemm_tile_order_changes_no_bit():
     """The order in which work-groups take the tiles (rows walked in groups, runs of tiles per XCD, runs of
     (k-split, tile) pairs) only decides who computes what: for any group size every tile is written exactly
