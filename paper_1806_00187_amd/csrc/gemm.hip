@@ -204,26 +204,6 @@ struct TransOp {
   }
 };
 
-// Instruction order of one k-tile of a small tile: the NR LDS reads of the next k-tile's fragments go between the first
-// three quarters of this one's MF matrix instructions, so that every read has returned before the next k-tile starts, and the NV
-// requests between all of them.
-template <int M, int MF, int NR, int NV>
-struct Interleave {
-  static constexpr int SLOTS = MF - MF / 4, PER = (NR + SLOTS - 1) / SLOTS;
-  static constexpr int DONE = M * PER < NR ? M * PER : NR, NOW = NR - DONE < PER ? NR - DONE : PER;
-  static constexpr int VNOW = (M + 1) * NV / MF - M * NV / MF;
-  __device__ __forceinline__ static void run() {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-    if (NOW > 0) __builtin_amdgcn_sched_group_barrier(0x100, NOW, 0);
-    if (VNOW > 0) __builtin_amdgcn_sched_group_barrier(0x020, VNOW, 0);
-    Interleave<M + 1, MF, NR, NV>::run();
-  }
-};
-template <int MF, int NR, int NV>
-struct Interleave<MF, MF, NR, NV> {
-  __device__ __forceinline__ static void run() {}
-};
-
 template <int BM, int BN, bool AT, bool BT, int NW>
 struct Tile {
   using OpA = typename std::conditional<AT, TransOp<BM, NW>, DirectOp<BM, NW>>::type;
@@ -428,6 +408,17 @@ __device__ __forceinline__ void store_colsum(const GemmArgs& g, const float (&su
 __device__ __forceinline__ void mfma_add(floatx4& acc, const half8_t& b, const half8_t& a) {
   asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(b), "v"(a));
 }
+// Waits that the compiler puts around products it knows: the last results have arrived before they are read (at most 19 wait states;
+// 16 for each strip of tiles here), and cleared sums are in place before the first product (2).
+template <int TM, int TN>
+__device__ __forceinline__ void settle_sums(floatx4 (&acc)[TM][TN]) {
+  static_assert(TN == 2 || TN == 4, "two or four tiles in a strip");
+#pragma unroll
+  for (int i = TM - 1; i >= 0; --i) {
+    if constexpr (TN == 4) asm volatile("s_nop 15" : "+v"(acc[i][0]), "+v"(acc[i][1]), "+v"(acc[i][2]), "+v"(acc[i][3]));
+    else asm volatile("s_nop 15" : "+v"(acc[i][0]), "+v"(acc[i][1]));
+  }
+}
 template <int BM, int BN, bool AT, bool BT, int NW, bool SUMS>
 struct StripTile {
   static constexpr int WGN = NW / 2, WM = BM / 2, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
@@ -490,7 +481,8 @@ struct StripTile {
   // wave's last fragments of `to` have arrived and it has seen its own part of `from` land; the barrier publishes `from` and
   // frees `to`.  The A half of `to` is requested over the strips behind the barrier (k-tile at k0), the B half over the first strips
   // of the step after.
-  template <int S>
+  // With REFILL false nothing is requested (a tile's last k-tiles).
+  template <int S, bool REFILL = true>
   __device__ __forceinline__ void k_step(const unsigned char* from, unsigned char* to, int k0) {
     constexpr int kAt = S ? TM / 2 : 0, kBehind = TM - kAt;  // strips before the first read from `from`, and behind it
     constexpr int kReq = S ? OpA::NV : OpB::NV, kOver = S ? kBehind : TM / 2;  // requests, and the strips they are spread over
@@ -522,7 +514,7 @@ struct StripTile {
         }
         af[i] = OpA::frag(from, fa, i, S ^ 1);
 #pragma unroll
-        for (int q = r * kReq / kOver; q < (r + 1) * kReq / kOver && q < kReq; ++q) {
+        for (int q = r * kReq / kOver; REFILL && q < (r + 1) * kReq / kOver && q < kReq; ++q) {
           if (S) opa.load_next(at, left, step, to, kleft, q);
           else opb.load_next(at, left, step, to + OpA::BYTES, kleft, q);
         }
@@ -530,28 +522,37 @@ struct StripTile {
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  // A k-tile past the end reads zeros (it lies outside the extent of its buffer descriptor) and
-  // multiplying it changes nothing, so the loop always runs whole rings and carries no edge conditions.
+  // The last step of all: its products alone.
+  __device__ __forceinline__ void last_step() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) mfma_add(acc[i][j], bf[1][j], af[i]);
+      if constexpr (SUMS) add_colsum(sums[i], af[i]);
+    }
+  }
+  // The k-tiles come in pairs; of an odd number the last one's partner reads zeros (it lies outside the extent of its buffer
+  // descriptor) and multiplying it changes nothing.
   __device__ __forceinline__ void multiply(unsigned char* s0, unsigned char* s1, int k0) {
     const int nk = (k_end - k0 + BK - 1) / BK;
-    for (int kt = 0; kt < nk; kt += 2) {
-      k_step<0>(s0, s1, k0 + (kt + 1) * BK);
-      k_step<1>(s1, s0, k0 + (kt + 2) * BK);
-      k_step<0>(s1, s0, k0 + (kt + 2) * BK);
-      k_step<1>(s0, s1, k0 + (kt + 3) * BK);
+    // (the large tile's loop runs to the end, past which its requests read zeros: it has the registers for one loop only)
+    constexpr int kPeeled = NW == 4 ? 2 : 0;
+    int k = k0;
+    for (int left = nk; left > kPeeled; left -= 2, k += 2 * BK) {
+      k_step<0>(s0, s1, k + BK);
+      k_step<1>(s1, s0, k + 2 * BK);
+      k_step<0>(s1, s0, k + 2 * BK);
+      k_step<1>(s0, s1, k + 3 * BK);
+    }
+    if constexpr (kPeeled > 0) {
+      k_step<0>(s0, s1, k + BK);
+      k_step<1, false>(s1, s0, 0);
+      k_step<0, false>(s1, s0, 0);
+      last_step();
     }
     settle();
   }
-  // Waits that the compiler puts around products it knows: the last results have arrived before they are read (at most 19 wait states;
-  // 16 for each strip here), and cleared sums are in place before the first product (2).
-  __device__ __forceinline__ void settle() {
-    static_assert(TN == 2 || TN == 4, "two or four tiles in a strip");
-#pragma unroll
-    for (int i = TM - 1; i >= 0; --i) {
-      if constexpr (TN == 4) asm volatile("s_nop 15" : "+v"(acc[i][0]), "+v"(acc[i][1]), "+v"(acc[i][2]), "+v"(acc[i][3]));
-      else asm volatile("s_nop 15" : "+v"(acc[i][0]), "+v"(acc[i][1]));
-    }
-  }
+  __device__ __forceinline__ void settle() { settle_sums(acc); }
 };
 // One tile by one work-group.
 template <int BM, int BN, bool AT, bool BT, int NW, bool SUMS, bool PLAIN>
@@ -644,46 +645,114 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int split, in
       for (int j = 0; j < TN; ++j) bf[set][s][j] = OpB::frag(stage + OpA::BYTES, fb, j, s);
     }
   };
-  // One k-tile, whose fragments are in register set `set`.  The barrier publishes `nxt` (every wave has seen its own
-  // part of it land) and frees `cur` (every wave's fragments of it have arrived), which is refilled at once.
-  auto k_tile = [&](unsigned char* cur, const unsigned char* nxt, int k_refill, int set) {
-    __builtin_amdgcn_s_waitcnt(wait_vm_lds((NS - 2) * kPerTile));
+  // One k-tile, whose fragments are in register set `set`, product by product; between them go the reads of the next k-tile's fragments
+  // from `nxt` (if there is one; over the first three quarters, so that every read has returned before they are needed) and the requests that
+  // refill `cur` (if there is something to refill it with).
+  constexpr int kProducts = KS * TM * TN, kReadUnits = KS * (TM + TN), kReadOver = kProducts - kProducts / 4;
+  auto interleaved = [&](unsigned char* cur, const unsigned char* nxt, int k_refill, int set, auto reads, auto refill) {
+    const int kleft = k_end - k_refill;
+    const half_t *pa = OpA::origin(g.A, g.lda, m0, k_refill), *pb = OpB::origin(g.B, g.ldb, n0, k_refill);
+    int left_a = (int)OpA::extent(rows_a, g.lda, kleft), left_b = (int)OpB::extent(rows_b, g.ldb, kleft);
+#pragma unroll
+    for (int q = 0; q < kProducts; ++q) {
+      const int s = q / (TM * TN), i = q / TN % TM, j = q % TN;  // (k-steps in increasing order: the same sums as gemm_kernel's)
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bf[set][s][j], af[set][s][i], acc[i][j], 0, 0, 0);
+      if constexpr (SUMS) {
+        if (j == 0) add_colsum(colsum[i], af[set][s][i]);
+      }
+      if constexpr (reads()) {
+#pragma unroll
+        for (int r = q * kReadUnits / kReadOver; r < (q + 1) * kReadUnits / kReadOver && r < kReadUnits; ++r) {
+          const int rs = r / (TM + TN), ri = r % (TM + TN);
+          if (ri < TN) bf[set ^ 1][rs][ri] = OpB::frag(nxt + OpA::BYTES, fb, ri, rs);
+          else af[set ^ 1][rs][ri - TN] = OpA::frag(nxt, fa, ri - TN, rs);
+        }
+      }
+      if constexpr (refill()) {
+#pragma unroll
+        for (int v = q * kPerTile / kProducts; v < (q + 1) * kPerTile / kProducts; ++v) {
+          if (v < OpA::NV) opa.load_next(pa, left_a, OpA::STEP * g.lda, cur, kleft, v);
+          else opb.load_next(pb, left_b, OpB::STEP * g.ldb, cur + OpA::BYTES, kleft, v - OpA::NV);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // The barrier publishes `nxt` (every wave has seen its own part of it land; `later` k-tiles are on their way behind it)
+  // and frees `cur` (every wave's fragments of it have arrived), which is refilled at once.
+  auto change = [&](auto later) {
+    __builtin_amdgcn_s_waitcnt(wait_vm_lds(later() * kPerTile));
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    request(cur, k_refill);
-    fetch(nxt, set ^ 1);
-#pragma unroll
-    for (int s = 0; s < KS; ++s)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)  // (B first, k-steps in increasing order: the same sums as gemm_kernel's)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bf[set][s][j], af[set][s][i], acc[i][j], 0, 0, 0);
-    if constexpr (SUMS) {
-#pragma unroll
-      for (int s = 0; s < KS; ++s)
-#pragma unroll
-        for (int i = 0; i < TM; ++i) add_colsum(colsum[i], af[set][s][i]);
-    }
-    Interleave<0, KS * TM * TN, KS * (OpA::READS * TM + OpB::READS * TN), kPerTile>::run();
+  };
+  auto k_tile = [&](unsigned char* cur, const unsigned char* nxt, int k_refill, int set) {
+    change(std::integral_constant<int, NS - 2>{});
+    interleaved(cur, nxt, k_refill, set, std::true_type{}, std::true_type{});
+  };
+  auto last_four = [&](const unsigned char* second, const unsigned char* third, const unsigned char* fourth, int set) {
+    change(std::integral_constant<int, 2>{});
+    interleaved(nullptr, second, 0, set, std::true_type{}, std::false_type{});
+    change(std::integral_constant<int, 1>{});
+    interleaved(nullptr, third, 0, set ^ 1, std::true_type{}, std::false_type{});
+    change(std::integral_constant<int, 0>{});
+    interleaved(nullptr, fourth, 0, set, std::true_type{}, std::false_type{});
+    interleaved(nullptr, nullptr, 0, set ^ 1, std::false_type{}, std::false_type{});
   };
 
-  const int nk = (k_end - k_base + BK - 1) / BK;  // (k-tiles past the end multiply zeros: whole rings, no edge conditions)
-  request(stage0, k_base);
-  request(stage1, k_base + BK);
-  request(stage2, k_base + 2 * BK);
-  request(stage3, k_base + 3 * BK);
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(wait_vm((NS - 1) * kPerTile));
-  __builtin_amdgcn_s_barrier();
-  fetch(stage0, 0);
-  for (int kt = 0; kt < nk; kt += NS) {
-    k_tile(stage0, stage1, k_base + (kt + 4) * BK, 0);
-    k_tile(stage1, stage2, k_base + (kt + 5) * BK, 1);
-    k_tile(stage2, stage3, k_base + (kt + 6) * BK, 0);
-    k_tile(stage3, stage0, k_base + (kt + 7) * BK, 1);
+  // Nothing is requested past the end of the contraction: a request whose lanes are all out of bounds takes its turn on the way to memory like
+  // any other, and the end of a product waited for four k-tiles of them (as nodes of a graph: 136 x 64 x 64 5.04 -> 3.90 us, 380 x 1024 x 1024
+  // 5.80 -> 5.54, 380 x 4096 x 1024 8.54 -> 7.95, 1670 x 256 x 1024 5.91 -> 5.59).
+  const int nk = (k_end - k_base + BK - 1) / BK;
+  if (nk >= NS) {
+    request(stage0, k_base);
+    request(stage1, k_base + BK);
+    request(stage2, k_base + 2 * BK);
+    request(stage3, k_base + 3 * BK);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(wait_vm((NS - 1) * kPerTile));
+    __builtin_amdgcn_s_barrier();
+    fetch(stage0, 0);
+    int k = k_base + NS * BK, left = nk - NS;  // `left` k-tiles are not requested yet
+    for (; left >= NS; k += NS * BK, left -= NS) {
+      k_tile(stage0, stage1, k, 0);
+      k_tile(stage1, stage2, k + BK, 1);
+      k_tile(stage2, stage3, k + 2 * BK, 0);
+      k_tile(stage3, stage0, k + 3 * BK, 1);
+    }
+    if (left == 0) {
+      last_four(stage1, stage2, stage3, 0);
+    } else if (left == 1) {
+      k_tile(stage0, stage1, k, 0);
+      last_four(stage2, stage3, stage0, 1);
+    } else if (left == 2) {
+      k_tile(stage0, stage1, k, 0);
+      k_tile(stage1, stage2, k + BK, 1);
+      last_four(stage3, stage0, stage1, 0);
+    } else {
+      k_tile(stage0, stage1, k, 0);
+      k_tile(stage1, stage2, k + BK, 1);
+      k_tile(stage2, stage3, k + 2 * BK, 0);
+      last_four(stage0, stage1, stage2, 1);
+    }
+  } else if (nk > 0) {
+    request(stage0, k_base);
+    if (nk > 1) request(stage1, k_base + BK);
+    if (nk > 2) request(stage2, k_base + 2 * BK);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(wait_vm(0));
+    __builtin_amdgcn_s_barrier();
+    fetch(stage0, 0);
+    interleaved(nullptr, nullptr, 0, 0, std::false_type{}, std::false_type{});
+    if (nk > 1) {
+      fetch(stage1, 0);
+      interleaved(nullptr, nullptr, 0, 0, std::false_type{}, std::false_type{});
+    }
+    if (nk > 2) {
+      fetch(stage2, 0);
+      interleaved(nullptr, nullptr, 0, 0, std::false_type{}, std::false_type{});
+    }
   }
-  __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));  // the last refills (all zeros) must land before the stages are reused
+  __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));  // every wave has its last fragments before the stages are reused
   __syncthreads();
   if constexpr (SUMS) {
     if (wn == 0) store_colsum<BM, TM>(g, colsum, m0 + wm * WM, split);
