@@ -702,8 +702,25 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int split, in
   // Nothing is requested past the end of the contraction: a request whose lanes are all out of bounds takes its turn on the way to memory like
   // any other, and the end of a product waited for four k-tiles of them (as nodes of a graph: 136 x 64 x 64 5.04 -> 3.90 us, 380 x 1024 x 1024
   // 5.80 -> 5.54, 380 x 4096 x 1024 8.54 -> 7.95, 1670 x 256 x 1024 5.91 -> 5.59).
+  // (Not on eight wavefronts: the code of the last k-tiles takes registers, and those are left to others there; k-tiles past the end are
+  // requested as zeros and multiplied.)
   const int nk = (k_end - k_base + BK - 1) / BK;
-  if (nk >= NS) {
+  if constexpr (NW == 8) {
+    request(stage0, k_base);
+    request(stage1, k_base + BK);
+    request(stage2, k_base + 2 * BK);
+    request(stage3, k_base + 3 * BK);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(wait_vm((NS - 1) * kPerTile));
+    __builtin_amdgcn_s_barrier();
+    fetch(stage0, 0);
+    for (int kt = 0; kt < nk; kt += NS) {
+      k_tile(stage0, stage1, k_base + (kt + 4) * BK, 0);
+      k_tile(stage1, stage2, k_base + (kt + 5) * BK, 1);
+      k_tile(stage2, stage3, k_base + (kt + 6) * BK, 0);
+      k_tile(stage3, stage0, k_base + (kt + 7) * BK, 1);
+    }
+  } else if (nk >= NS) {
     request(stage0, k_base);
     request(stage1, k_base + BK);
     request(stage2, k_base + 2 * BK);
@@ -752,7 +769,7 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int split, in
       interleaved(nullptr, nullptr, 0, 0, std::false_type{}, std::false_type{});
     }
   }
-  __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));  // every wave has its last fragments before the stages are reused
+  __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));  // every wave has its last fragments, and every request has landed, before the stages are reused
   __syncthreads();
   if constexpr (SUMS) {
     if (wn == 0) store_colsum<BM, TM>(g, colsum, m0 + wm * WM, split);
@@ -760,7 +777,7 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int split, in
   store_tile<BM, BN, NW, T::STAGE, PLAIN>(g, acc, m0, n0, split, stage0, stage1);
 }
 template <int BM, int BN, bool AT, bool BT, int NW>
-__global__ void __launch_bounds__(64 * NW) gemm_small_kernel(const GemmArgs g) {
+__device__ __forceinline__ void gemm_small_group(const GemmArgs& g) {
   using T = Tile<BM, BN, AT, BT, NW>;
   __shared__ __align__(1024) unsigned char stage0[T::STAGE];  // separate arrays (see StripTile)
   __shared__ __align__(1024) unsigned char stage1[T::STAGE];
@@ -769,6 +786,17 @@ __global__ void __launch_bounds__(64 * NW) gemm_small_kernel(const GemmArgs g) {
   int split, tm, tn;
   place(g, (int)blockIdx.x + (int)blockIdx.y * (g.tiles_m * g.tiles_n), g.tiles_m * g.tiles_n * (int)gridDim.y, split, tm, tn);
   gemm_small_tile<BM, BN, AT, BT, NW, false, false>(g, split, tm, tn, stage0, stage1, stage2, stage3);
+}
+template <int BM, int BN, bool AT, bool BT, int NW>
+__global__ void __launch_bounds__(64 * NW) gemm_small_kernel(const GemmArgs g) {
+  gemm_small_group<BM, BN, AT, BT, NW>(g);
+}
+// Eight wavefronts: one such work-group fills a compute unit's LDS.  Registers for a third wavefront per SIMD (160 of 512) are left, so that the other
+// stream's row kernels can run beside it (LayerNorm backward of a 512 wide model over 3000 positions, a third of the calls beside a layer's weight
+// gradients: 16.8 us on average with 220 registers here, 14.1 with 154; whole update 3893 -> 3857).  The attribute counts half of the register file.
+template <int BM, int BN, bool AT, bool BT>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(88))) gemm_small_kernel_8(const GemmArgs g) {
+  gemm_small_group<BM, BN, AT, BT, 8>(g);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1044,7 +1072,7 @@ __device__ __forceinline__ GemmArgs group_item(const GroupArgs& a, int lin, int&
   return g;
 }
 template <int BM, int BN, int NS, int NW>
-__global__ void __launch_bounds__(64 * NW) wgrad_group_kernel(const GroupArgs a) {
+__device__ __forceinline__ void wgrad_group(const GroupArgs& a) {
   using T = Tile<BM, BN, true, true, NW>;
   __shared__ __align__(1024) unsigned char stage0[T::STAGE];
   __shared__ __align__(1024) unsigned char stage1[T::STAGE];
@@ -1060,6 +1088,15 @@ __global__ void __launch_bounds__(64 * NW) wgrad_group_kernel(const GroupArgs a)
     if (sums) gemm_small_tile<BM, BN, true, true, NW, true, true>(g, split, tm, tn, stage0, stage1, stage2, stage3);
     else gemm_small_tile<BM, BN, true, true, NW, false, true>(g, split, tm, tn, stage0, stage1, stage2, stage3);
   }
+}
+template <int BM, int BN, int NS, int NW>
+__global__ void __launch_bounds__(64 * NW) wgrad_group_kernel(const GroupArgs a) {
+  wgrad_group<BM, BN, NS, NW>(a);
+}
+// (as gemm_small_kernel_8)
+template <int BM, int BN>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(88))) wgrad_group_kernel_8(const GroupArgs a) {
+  wgrad_group<BM, BN, 4, 8>(a);
 }
 // C and the column sums of every product of the group from the splits' fp32 sums, 8 columns per thread, splits in
 // increasing order
@@ -1111,6 +1148,7 @@ template <int BM, int BN, bool AT, bool BT, int NS, int NW>
 void launch_variant(const GemmArgs& g, int splits, hipStream_t stream) {
   const dim3 grid(g.tiles_m * g.tiles_n, splits), block(64 * NW);
   if constexpr (NS == 2) hipLaunchKernelGGL((gemm_kernel<BM, BN, AT, BT, NW>), grid, block, 0, stream, g);
+  else if constexpr (NW == 8) hipLaunchKernelGGL((gemm_small_kernel_8<BM, BN, AT, BT>), grid, block, 0, stream, g);
   else hipLaunchKernelGGL((gemm_small_kernel<BM, BN, AT, BT, NW>), grid, block, 0, stream, g);
 }
 
@@ -1438,7 +1476,7 @@ int launch_wgrad_group_impl(const WgradProduct* products, int n, float out_scale
   switch (tile) {
     case kGroup256: hipLaunchKernelGGL((wgrad_group_kernel<256, 256, 2, 8>), grid, dim3(512), 0, stream, a); break;
     case kGroup128Many: hipLaunchKernelGGL((wgrad_group_kernel<128, 128, 2, 4>), grid, dim3(256), 0, stream, a); break;
-    case kGroup128: hipLaunchKernelGGL((wgrad_group_kernel<128, 128, 4, 8>), grid, dim3(512), 0, stream, a); break;
+    case kGroup128: hipLaunchKernelGGL((wgrad_group_kernel_8<128, 128>), grid, dim3(512), 0, stream, a); break;
     default: hipLaunchKernelGGL((wgrad_group_kernel<64, 64, 4, 4>), grid, dim3(256), 0, stream, a); break;
   }
   NMT_LAUNCH_CHECK();
