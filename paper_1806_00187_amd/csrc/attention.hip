@@ -116,9 +116,9 @@ __device__ __forceinline__ Item work_item(const AttnArgs& a, int bx, int by, int
   it.tile = by;
   it.live = it.h < a.H;
   if (LIST == 1 && a.wl_qsent) {
+    const int4 t = a.wl_qsent[idx];  // (asked for beside the count: the grid ends with the list's storage)
+    it.tile = a.wl_qtile[idx];
     it.live = it.live && idx < a.wl_counts[kClasses + 1];
-    const int4 t = it.live ? a.wl_qsent[idx] : make_int4(0, 0, 0, 0);
-    it.tile = it.live ? a.wl_qtile[idx] : 0;
     it.se = Sent{t.x, t.y, t.z, t.w};
   } else if (LIST == 2 && a.wl_sent) {
     it.live = it.live && idx < a.wl_counts[cls];
@@ -593,7 +593,8 @@ __global__ void __launch_bounds__(kThreads) attn_bwd_fused_kernel(const AttnArgs
 // wavefront (nt here, nt * nt with one wavefront per sentence and head, whose unrolled code of up to 69 KB also
 // had to be fetched) and the number of launches.  Per pass of 18 attentions, with the instances per length it replaces: fourteen
 // sentences of up to 256 positions, 8 heads: 930 -> 370 us; 130 of 16 to 40: 405 -> 268; 53000 positions, 16 heads: 5.3 -> 4.9 ms
-// (beside the weight gradients).
+// (beside the weight gradients).  What bounds it at these lengths is trips to memory: everything a wavefront needs is asked for at once (K and V
+// used to follow Q, dO and O): per call 14.9 -> 14.0 us for 148 sentences of 24, 20.6 -> 20.1 for fourteen of up to 256, 40.7 -> 37.7 for 480 of about 27.
 // ------------------------------------------------------------------------------------------------
 constexpr int kBwdTiles = 8;  // longest sentence, in tiles
 template <int DH>
@@ -629,14 +630,19 @@ __device__ __forceinline__ void attn_bwd_tiles_item(const AttnArgs& a, int nt, i
   auto row_stats = [&](int t) { return reinterpret_cast<float*>(ds_tile(t, 2)); };  // lse[32], D[32]
   half_t* const my_k = reinterpret_cast<half_t*>(mine) + 2 * 32 * PR;
 
+  // Everything the wavefront needs from memory is requested before anything is used (one trip there instead of two; rows
+  // past a sentence's end, and a tile or sentence that does not exist, ask for nothing and are zeros).
+  const int q = j * 32 + (lane & 31), key = q;
+  half8_t qf[KS], dof[KS], of[KS], kf[KS], vf[KS];
+  load_rows<DH>(a.Q + (size_t)se.q0 * a.ldq + h * DH, a.ldq, j * 32, se.Tq, lane, qf);
+  load_rows<DH>(a.dO + (size_t)se.q0 * a.lddo + h * DH, a.lddo, j * 32, se.Tq, lane, dof);
+  load_rows<DH>(a.O + (size_t)se.q0 * a.ldo + h * DH, a.ldo, j * 32, se.Tq, lane, of);
+  const float lse_q = q < se.Tq ? a.lse[(size_t)h * a.Nq + se.q0 + q] * kLog2e : 0.f;
+  load_rows<DH>(a.K + (size_t)se.k0 * a.ldk + h * DH, a.ldk, j * 32, se.Tk, lane, kf);
+  load_rows<DH>(a.V + (size_t)se.k0 * a.ldv + h * DH, a.ldv, j * 32, se.Tk, lane, vf);
+  const bool khid = key >= se.Tk || (a.key_ids && a.key_ids[se.k0 + key] == a.pad_id);
   wave_sync();  // (what this wavefront staged for its last item has been stored)
   if (j < nqt) {
-    half8_t qf[KS], dof[KS], of[KS];
-    load_rows<DH>(a.Q + (size_t)se.q0 * a.ldq + h * DH, a.ldq, j * 32, se.Tq, lane, qf);
-    load_rows<DH>(a.dO + (size_t)se.q0 * a.lddo + h * DH, a.lddo, j * 32, se.Tq, lane, dof);
-    load_rows<DH>(a.O + (size_t)se.q0 * a.ldo + h * DH, a.ldo, j * 32, se.Tq, lane, of);
-    const int q = j * 32 + (lane & 31);
-    const float lse_q = q < se.Tq ? a.lse[(size_t)h * a.Nq + se.q0 + q] * kLog2e : 0.f;
     float Dq = 0.f;
 #pragma unroll
     for (int s = 0; s < KS; ++s)
@@ -650,17 +656,10 @@ __device__ __forceinline__ void attn_bwd_tiles_item(const AttnArgs& a, int nt, i
       row_stats(j)[32 + lane] = Dq;
     }
   }
-  const int key = j * 32 + (lane & 31);
-  const bool khid = key >= se.Tk || (a.key_ids && a.key_ids[se.k0 + key] == a.pad_id);
-  half8_t kf[KS], vf[KS];
   floatx16 dKt[DT], dVt[DT];
 #pragma unroll
   for (int t = 0; t < DT; ++t) dKt[t] = dVt[t] = zero16();
-  if (j < nkt) {
-    load_rows<DH>(a.K + (size_t)se.k0 * a.ldk + h * DH, a.ldk, j * 32, se.Tk, lane, kf);
-    load_rows<DH>(a.V + (size_t)se.k0 * a.ldv + h * DH, a.ldv, j * 32, se.Tk, lane, vf);
-    put_rows<DH>(my_k, lane, kf);
-  }
+  if (j < nkt) put_rows<DH>(my_k, lane, kf);
   const float scale = rsqrtf((float)DH), sc = scale * kLog2e;
   __syncthreads();  // Q, dO, K tiles and the row statistics of all groups are in LDS
 #pragma unroll 1
@@ -745,8 +744,9 @@ __device__ __forceinline__ void attn_bwd_tiles_item(const AttnArgs& a, int nt, i
     store_rows<DH>(my_k, dVt, 1.f, a.dV + (size_t)se.k0 * a.lddv + h * DH, a.lddv, j * 32, se.Tk, lane);
   }
 }
+// (two wavefronts per SIMD is what LDS leaves room for at head size 64; registers have to leave as much)
 template <int DH, int W>
-__global__ void __launch_bounds__(64 * W) attn_bwd_tiles_kernel(const AttnArgs a) {
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) attn_bwd_tiles_kernel(const AttnArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   int v = blockIdx.x;
   for (int nt = a.cls_hi; nt >= a.cls_lo; --nt) {
