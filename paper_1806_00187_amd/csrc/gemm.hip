@@ -500,8 +500,10 @@ struct StripTile {
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
-      for (int j = 0; j < TN; ++j)  // B first: the result tile is transposed, lane = row of C, registers = columns
+      for (int jj = 0; jj < TN; ++jj) {  // B first: the result tile is transposed, lane = row of C, registers = columns
+        const int j = i & 1 ? TN - 1 - jj : jj;  // (back and forth: from strip to strip B's operand stays, 0.2-1 % of the time, power again)
         mfma_add(acc[i][j], bf[S][j], af[i]);
+      }
       if constexpr (SUMS) add_colsum(sums[i], af[i]);
       __builtin_amdgcn_sched_barrier(0);  // (a read moved ahead of these products would take registers of its own)
       if (i >= kAt) {
@@ -793,7 +795,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_small_kernel(const GemmArgs g) {
 }
 // Eight wavefronts: one such work-group fills a compute unit's LDS.  Registers for a third wavefront per SIMD (160 of 512) are left, so that the other
 // stream's row kernels can run beside it (LayerNorm backward of a 512 wide model over 3000 positions, a third of the calls beside a layer's weight
-// gradients: 16.8 us on average with 220 registers here, 14.1 with 154; whole update 3893 -> 3857).  The attribute counts half of the register file.
+// gradients: 16.8 us on average with 220 registers here, 14.1 with 154).  The attribute counts half of the register file.
 template <int BM, int BN, bool AT, bool BT>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(88))) gemm_small_kernel_8(const GemmArgs g) {
   gemm_small_group<BM, BN, AT, BT, 8>(g);
