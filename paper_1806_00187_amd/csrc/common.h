@@ -48,7 +48,7 @@ const DeviceInfo& device_info();
 // Process-wide switches of launch forms (nmt_tuning): which work-group computes what, never what is computed.
 struct Tuning {
   int gemm_group = 4;     // tile rows swept column by column before the next rows
-  int gemm_persist = 1;   // 0: never the persistent GEMM form, 1: where it applies (large products whose epilogue loads nothing per element)
+  int gemm_persist = 1;   // 0: never the persistent GEMM form, 1: where it applies (256 x 256 tiles, row-major A, no split, one of its five epilogues)
   int attn_persist = 1;   // 0: one attention work item per work-group
   int worklists = 1;      // 0: attention kernels enumerate every (sentence, tile) instead of taking work lists
   int one_stream = 0;     // 1: forward and backward passes keep to the caller's stream

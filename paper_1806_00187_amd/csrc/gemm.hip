@@ -396,7 +396,7 @@ __device__ __forceinline__ void store_colsum(const GemmArgs& g, const float (&su
 // next is in LDS or on its way.  (The stages are separate arrays, so that the compiler can tell that fragment reads of one
 // do not depend on the loads in flight into the other.)
 // What bounds it: the power the chip may take (matrix pipes busy 0.7-0.8 of the cycles at 1.4-1.8 GHz) and, at k = 1024, the
-// 4-5 us a tile takes besides its k-tiles.  TFLOP/s before (32x32x16, requests in one go, four stages of 32 for k-major operands) and
+// 3-5 us a tile takes besides its k-tiles.  TFLOP/s before (32x32x16, requests in one go, four stages of 32 for k-major operands) and
 // now: 8192^3 x W^T 1268 / 1423, dy W 1244 / 1400, dy^T x 1251 / 1360; 52704 rows: 3072 x 1024 x W^T 1056 / 1150, 1024 x 4096 1116 / 1218,
 // 4096 x 1024 dy W 1083 / 1140; a layer's weight gradients over 52700 positions 1024 wide 840 / 933.  Two stages of 64 k against
 // four of 32 here: x W^T 760 / 808 us, dy W 773 / 793, dy^T x 794 / 805 (8192^3).
@@ -812,7 +812,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(88))) gemm
 // Before (next tile's first k-tiles requested in one go after the last product, one epilogue for all forms with a select per value,
 // sum and mask in the form with one tile per work-group) and now, us, 52704 rows: 4096 x 1024 with bias and ReLU 383 / 360, 1024 x 1024 104 /
 // 99, 32768 x 1024 3079 / 2810, + another matrix 1024 x 4096 421 / 375, ReLU mask 4096 x 1024 502 / 425; 26000 x 2048 x 512 with mask 89 / 73.
-// What is left per tile is the epilogue, about 2 us; the k-tiles are bound by power (see StripTile).
+// What is left per tile besides its k-tiles is 3-4 us at k = 1024 (5 before); the k-tiles are bound by power (see StripTile).
 // ------------------------------------------------------------------------------------------------
 // LDS accesses of the staging rows, written as instructions: while requests into the stages are in
 // flight the compiler would otherwise put a wait for ALL of them in front of any LDS access it
