@@ -246,6 +246,17 @@ def test_tiny_with_activation_dropout_and_other_seed():
     sess.close()
 
 
+# LayerNorm gradients summed in the launch of a layer's weight gradients: two groups of eight columns and more, a few partial rows
+# and more than the 128 that one round of the sum takes, two and three sums to a layer.
+@pytest.mark.parametrize("d,heads,B,S,T", [(16, 1, 2, 3, 4), (48, 3, 5, 9, 7), (80, 5, 90, 38, 31), (144, 9, 45, 21, 40)])
+def test_layernorm_gradients_beside_small_weight_gradients_match_oracle(d, heads, B, S, T):
+    model = dict(enc_layers=1, dec_layers=1, d_model=d, n_heads=heads, d_ff=2 * d, vocab=136, dropout=0.1)
+    weights = I.init_weights(seed=21, perturb=0.05, **model)
+    batch = I.tiny_batch(seed=300 + d, B=B, S=S, T=T, vocab=136, short_rows=min(B - 1, 3), short_by=1)
+    sess = _step_parity(model, [batch], weights, step=4, loss_scale=8.0, lr=1e-4, what=f"{d}-wide model, {B} sentences")
+    sess.close()
+
+
 def test_medium_model_spans_several_tiles_with_ragged_shapes():
     """d=256, 4 heads of 64, F=1024, V=2056, 45 sentences of up to 37/41 tokens: every GEMM spans
     several tiles with ragged edges; lengths vary per sentence."""
