@@ -205,6 +205,30 @@ def test_bias_gradients_keep_denormal_halves_and_long_sums(tile):
     assert (np.abs(host(gb) - want) <= want * (2.0 ** -11 + 3320 * 2.0 ** -24)).all()
 
 
+@pytest.mark.parametrize("tile", [1, 2, 3, 4])
+@pytest.mark.parametrize("n,rows", [(264, 4003), (72, 136)])
+def test_bias_gradient_sums_keep_their_order(tile, n, rows):
+    """A column is two fp32 sums, of the eight-position pieces of even and of odd number, each added up in the order of the
+    positions, then added.  The values make every piece exact in fp32, whatever the order within it, and the running sums not: pieces
+    of about 2^17 that cancel in the end, between pieces of about 8 in steps of 2^-8.  So the result is equal bit for bit to that order's
+    and, in some columns, to no other's."""
+    rng = np.random.default_rng(rows)
+    pieces = -(-rows // 8)
+    dy = rng.integers(-1023, 1024, size=(pieces, 8, n)) / 256.0
+    large = np.arange(0, pieces, 3)[: len(range(0, pieces, 3)) // 2 * 2]
+    up = rng.integers(1024, 2047, size=(len(large) // 2, 8, n)) * 16.0
+    dy[large[: len(up)]], dy[large[len(up):]] = up, -rng.permutation(up)
+    dy = dy.reshape(-1, n)[:rows]
+    sums = np.zeros((2, n), dtype=np.float32)
+    for k in range(pieces):
+        sums[k % 2] += dy[8 * k:8 * k + 8].sum(axis=0).astype(np.float32)
+    want = (sums[0] + sums[1]).astype(np.float16)
+    gw, gb = torch.zeros(n, 8, dtype=torch.float16, device=DEV), torch.full((n,), float("nan"), dtype=torch.float16, device=DEV)
+    A.nmt_op_wgrad_group([(dev16(dy), n, torch.zeros(rows, 8, dtype=torch.float16, device=DEV), 8, gw, 8, gb, n, 8, rows)], 1.0, None, tile, 1)
+    assert np.isfinite(want).all()
+    assert (host(gb) == want).all()
+
+
 def test_gemm_large_problem_with_a_small_tile_tail_keeps_epilogue_rows():
     """Enough rows for one full round of large tiles plus a remainder, which goes to a second launch
     with small tiles: bias, ReLU and the dropout counters of the remainder must be those of its rows."""
