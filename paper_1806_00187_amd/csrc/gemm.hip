@@ -412,7 +412,9 @@ __device__ __forceinline__ void store_colsum(const GemmArgs& g, float sum, int m
 // The product as an instruction of its own, so that the sums stay where they are: the compiler's form of this shape has a result
 // apart from the addend, and its register allocation then moves accumulators about, runs out and spills inside the loop (a
 // layer's weight gradients over 52700 positions 1024 wide: 1.65 -> 4.0 ms).  A result may be read (other than as the addend of
-// the same sum) a few instructions later only; `settle` is between the loop and the epilogue.
+// the same sum) a few instructions later only; `settle` is between the loop and the epilogue.  Nothing here keeps the compiler from
+// moving a source or a result about within that time, so tests/test_matrix_products_compiled.py looks for it in every kernel of
+// the built library (there is none in that of AMD clang 22.0.0git, ROCm 7.2.0: 2 wait states ahead of a product, 19 behind it).
 __device__ __forceinline__ void mfma_add(floatx4& acc, const half8_t& b, const half8_t& a) {
   asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(b), "v"(a));
 }
