@@ -246,7 +246,7 @@ def test_tiny_with_activation_dropout_and_other_seed():
     sess.close()
 
 
-# LayerNorm gradients summed in the launch of a layer's weight gradients: two groups of eight columns and more, a few partial rows
+# LayerNorm gradients of narrow models: fewer columns than the 32 of one work-group of the sum and more, a few partial rows
 # and more than the 128 that one round of the sum takes, two and three sums to a layer.
 @pytest.mark.parametrize("d,heads,B,S,T", [(16, 1, 2, 3, 4), (48, 3, 5, 9, 7), (80, 5, 90, 38, 31), (144, 9, 45, 21, 40)])
 def test_layernorm_gradients_beside_small_weight_gradients_match_oracle(d, heads, B, S, T):
