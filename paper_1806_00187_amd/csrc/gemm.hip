@@ -882,7 +882,7 @@ __device__ __forceinline__ void buffer_store_half8(__amdgpu_buffer_rsrc_t r, uin
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4v_t, v), r, (int)off, 0, kStream);
 }
 
-// What an epilogue of the persistent form does: nothing; output scale and bias; these and ReLU; output scale and a sum with another matrix, or the
+// What an epilogue of the persistent form does: nothing; bias; bias and ReLU; a sum with another matrix; the
 // ReLU mask of the backward pass.  (A kernel each: chosen per value inside one they cost an instruction more each, chosen per
 // slab of rows the register file overflows.)
 enum StoreForm { kStorePlain, kStoreBias, kStoreRelu, kStoreAdd, kStoreMask };
@@ -972,7 +972,7 @@ __global__ void __launch_bounds__(512) gemm_persistent_kernel(const GemmArgs g) 
             if constexpr (FORM != kStorePlain) {
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
-                v[e] = v[e] * ep.out_scale + (float)bias[j][e];
+                v[e] += (float)bias[j][e];
                 if constexpr (FORM == kStoreRelu) v[e] = fmaxf(v[e], 0.f);
               }
             }
@@ -1021,7 +1021,7 @@ __global__ void __launch_bounds__(512) gemm_persistent_kernel(const GemmArgs g) 
             floatx8 v;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-              const float x = rv[2 * it + (e >> 2)][e & 3] * ep.out_scale;
+              const float x = rv[2 * it + (e >> 2)][e & 3];
               v[e] = FORM == kStoreAdd ? x + (float)p[e] : (float)p[e] > 0.f ? x * ep.mask_scale : 0.f;
             }
             buffer_store_half8(to, at, __builtin_convertvector(v, half8_t));  // (rounded to fp32 first, as in the form with one tile per work-group)
@@ -1345,8 +1345,8 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
     // No split along k, row-major A, one of the epilogues that have it: the persistent form, also where every work-group has one tile
     // only (its epilogue is the faster one).  Not for a k-major A: the one such product without a split, the
     // vocabulary weight gradient, has so long a contraction that the tile change hardly counts, and measured
-    // 6 % slower in this form.
-    if (splits == 1 && !a_t && tuning().gemm_persist && !ep.drop.thr && !((ep.add || ep.relu_src) && (ep.bias || ep.relu)) &&
+    // 6 % slower in this form.  That one is also the only product with an output scale besides the groups: no epilogue here has it.
+    if (splits == 1 && !a_t && ep.out_scale == 1.f && tuning().gemm_persist && !ep.drop.thr && !((ep.add || ep.relu_src) && (ep.bias || ep.relu)) &&
         !(ep.add && ep.relu_src)) {
       const int groups = (int)(t256 < cus ? t256 : cus);
       GemmArgs pg = g;
@@ -1359,7 +1359,7 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
         if (ep.add) hipLaunchKernelGGL((gemm_persistent_kernel<BT, kStoreAdd>), dim3(groups), dim3(512), 0, stream, pg);
         else if (ep.relu_src) hipLaunchKernelGGL((gemm_persistent_kernel<BT, kStoreMask>), dim3(groups), dim3(512), 0, stream, pg);
         else if (ep.relu) hipLaunchKernelGGL((gemm_persistent_kernel<BT, kStoreRelu>), dim3(groups), dim3(512), 0, stream, pg);
-        else if (ep.bias || ep.out_scale != 1.f) hipLaunchKernelGGL((gemm_persistent_kernel<BT, kStoreBias>), dim3(groups), dim3(512), 0, stream, pg);
+        else if (ep.bias) hipLaunchKernelGGL((gemm_persistent_kernel<BT, kStoreBias>), dim3(groups), dim3(512), 0, stream, pg);
         else hipLaunchKernelGGL((gemm_persistent_kernel<BT, kStorePlain>), dim3(groups), dim3(512), 0, stream, pg);
       };
       if (b_t) run(std::true_type{});
