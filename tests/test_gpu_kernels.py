@@ -257,10 +257,9 @@ def test_gemm_large_problem_with_a_small_tile_tail_keeps_epilogue_rows():
 
 
 def test_gemm_persistent_form_matches_oracle_and_the_tile_per_work_group_form():
-    """Products of more large tiles than compute units, no split along k and an epilogue that loads nothing per
-    element run as one persistent work-group per compute unit that requests the next tile's first k-tiles before it
-    stores the current one.  Ragged M, N and k; bias + ReLU and the k-major form against the oracle, then bias, ReLU and
-    output scale bit for bit against the one-tile-per-work-group kernel (switch 0): both add the same products in the
+    """Products in large tiles run as one persistent work-group per compute unit that requests the next tile's first k-tiles
+    ahead of the end of the current one.  Ragged M, N and k; bias + ReLU and the k-major form against the oracle, then bias, ReLU,
+    both and neither bit for bit against the one-tile-per-work-group kernel (switch 0): both add the same products in the
     same order and round once."""
     rng = np.random.default_rng(29)
     n_pos, B = 40, 826
@@ -303,12 +302,15 @@ def test_gemm_persistent_form_matches_oracle_and_the_tile_per_work_group_form():
         assert_close16(host(dC), x2 @ Wt2, f"persistent, k-major B, k={K2}")
 
 
-# rows and columns that end inside a tile, contractions of one, two and five k-tiles; the sum also in place, as the gradient at the encoder output is
+# Columns that end inside a tile, contractions of one, two and five k-tiles; the sum also in place, as the gradient at the encoder output is.
+# On 256 compute units 57 x 8 tiles, the last row of them 8 rows high, are more than a round and a half, so they are one launch, and 200 work-groups
+# take a second tile.  44 x 8 are less than that: 8192 rows in this form, a tile to each work-group, the other 2824 in small tiles.
 @pytest.mark.parametrize("K", [40, 128, 264])
 @pytest.mark.parametrize("b_t", [0, 1])
 @pytest.mark.parametrize("form", ["add", "add in place", "mask"])
-def test_gemm_persistent_sum_and_mask_match_oracle_and_the_tile_per_work_group_form(K, b_t, form):
-    M, N = 11016, 1800                           # 44 x 8 tiles
+@pytest.mark.parametrize("M", [14344, 11016])
+def test_gemm_persistent_sum_and_mask_match_oracle_and_the_tile_per_work_group_form(M, K, b_t, form):
+    N = 1800
     rng = np.random.default_rng(K)
     x, W = f16(rng.normal(size=(M, K))), f16(rng.normal(size=(N, K)) / math.sqrt(K))
     other = f16(rng.normal(size=(M, N)))
