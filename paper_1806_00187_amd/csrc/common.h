@@ -198,10 +198,6 @@ struct WgradProduct {
   int lda, ldb, ldc, M, N, K;
 };
 constexpr int kMaxWgrad = 8;
-// All products (1..kMaxWgrad of them, results times out_scale) in one launch, or two if they are cut along k.  partial: fp32 scratch for that
-// (may be null: never cut).  tile, splits: 0 = chosen by cost.
-int launch_wgrad_group(const WgradProduct* products, int n, float out_scale, float* partial, int64_t partial_floats, hipStream_t stream,
-                       int tile = 0, int splits = 0);
 // Partial sums that a group with `per_split` floats of results and column sums, over up to `rows` positions, can use of `most`.
 int64_t wgrad_group_floats(int64_t per_split, int64_t rows, int64_t most);
 
@@ -254,6 +250,40 @@ struct ColumnSums {
   half_t* dst[3];
 };
 constexpr int kMaxColumnSums = 4;
+// dst[k][col] = fp16(scale * sum_b partial[b][k][col]), k = 0..nq-1, for up to kMaxColumnSums buffers of partial rows.
+struct FinalizeArgs {
+  int nq, cols, pitch;
+  float scale;
+  ColumnSums in[kMaxColumnSums];
+};
+// One work-group's share: it owns THREADS / 32 columns of one quantity; its 32 row-lanes stride over the partial rows
+// (independent loads, several in flight) and are combined in a fixed order, the same whatever THREADS.  red: 32 * (THREADS / 32 + 1) floats of LDS.
+template <int THREADS>
+__device__ __forceinline__ void finalize_columns(const FinalizeArgs& a, int block, float* red) {
+  constexpr int COLS = THREADS / 32, PITCH = COLS + 1;
+  const int cx = threadIdx.x % COLS, ry = threadIdx.x / COLS;
+  const int cblocks = (a.cols + COLS - 1) / COLS;
+  const int k = (block / cblocks) % a.nq, col = (block % cblocks) * COLS + cx;
+  const ColumnSums& in = a.in[block / (cblocks * a.nq)];
+  const int nblk = in.rows;
+  float s = 0.f;
+  if (col < a.cols) {
+    const float* p = in.partial + (size_t)k * a.pitch + col;
+    const size_t step = (size_t)a.nq * a.pitch;
+    int b = ry;
+    for (; b + 96 < nblk; b += 128)
+      s += (p[b * step] + p[(b + 32) * step]) + (p[(b + 64) * step] + p[(b + 96) * step]);
+    for (; b < nblk; b += 32) s += p[b * step];
+  }
+  red[ry * PITCH + cx] = s;
+  __syncthreads();
+  if (ry == 0 && col < a.cols) {
+    float t = red[cx];
+#pragma unroll
+    for (int r = 1; r < 32; ++r) t += red[r * PITCH + cx];
+    if (in.dst[k]) in.dst[k][col] = (half_t)(t * a.scale);
+  }
+}
 // The row gradients; the gradients of gamma, beta and the bias are left as partial rows described by `sums`, which
 // launch_layernorm_param_grads adds up (several calls' in one launch).
 int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const half_t* resid, const half_t* gamma,
@@ -261,6 +291,12 @@ int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const h
                                   half_t* dbias, float* partial, int rows, int d, const DropDev& drop,
                                   hipStream_t stream, ColumnSums& sums);
 int launch_layernorm_param_grads(const ColumnSums* sums, int n, int d, float scale, hipStream_t stream);  // scale: factor on all of them
+// All products (1..kMaxWgrad of them, results times out_scale) in one launch, or two if they are cut along k.  partial: fp32 scratch for that
+// (may be null: never cut).  tile, splits: 0 = chosen by cost.
+// sums: partial rows of d columns (a layer's LayerNorm gradients) that are added up as well, times out_scale: in the same launch where that is one of
+// small tiles.
+int launch_wgrad_group(const WgradProduct* products, int n, float out_scale, float* partial, int64_t partial_floats, hipStream_t stream,
+                       int tile = 0, int splits = 0, const ColumnSums* sums = nullptr, int n_sums = 0, int d = 0);
 int launch_embed_fwd(const int32_t* ids, const half_t* E, half_t* x, int rows, int d, int vocab, const DropDev& drop,
                      hipStream_t stream);
 int launch_softmax_xent(half_t* logits, const int32_t* targets, float* row_loss, int rows, int V, int pad_id,

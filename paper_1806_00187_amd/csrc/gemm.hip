@@ -1115,6 +1115,17 @@ template <int BM, int BN, int NS, int NW>
 __global__ void __launch_bounds__(64 * NW) wgrad_group_kernel(const GroupArgs a) {
   wgrad_group<BM, BN, NS, NW>(a);
 }
+// The smallest tiles with the sums of partial rows that the layer's LayerNorm gradients are: work-groups of 8 columns behind the products'.
+// Passes with such groups are bound by the number of their launches, 4 us each: whole updates of 136 positions, two layers 64 wide, 526 -> 508 us
+// (medians of ten processes of each form in turn; 521 to 538 and 505 to 518 but for one and two that ran faster, 481 and 469 / 489).  The larger tiles' groups keep the sums' own launch: their passes are not bound by launches.
+__global__ void __launch_bounds__(256) wgrad_group_sums_kernel(const GroupArgs a, const FinalizeArgs f) {
+  if ((int)blockIdx.x >= a.total) {
+    __shared__ float red[32 * 9];
+    finalize_columns<256>(f, (int)blockIdx.x - a.total, red);
+    return;
+  }
+  wgrad_group<64, 64, 4, 4>(a);
+}
 // (as gemm_small_kernel_8)
 template <int BM, int BN>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(88))) wgrad_group_kernel_8(const GroupArgs a) {
@@ -1452,7 +1463,7 @@ int check_wgrad(const WgradProduct& w) {
   return NMT_OK;
 }
 int launch_wgrad_group_impl(const WgradProduct* products, int n, float out_scale, float* partial, int64_t partial_floats, hipStream_t stream,
-                            int tile, int splits) {
+                            int tile, int splits, const FinalizeArgs& sums, int n_sums, bool& sums_done) {
   NMT_REQUIRE(products && n >= 1 && n <= kMaxWgrad, "weight gradients: %d products outside [1, %d]", n, kMaxWgrad);
   NMT_REQUIRE(tile >= 0 && tile <= kGroupTiles && splits >= 0 && splits <= 64, "weight gradients: tile %d or number of k splits %d out of range", tile, splits);
   NMT_REQUIRE(!partial || aligned16(partial), "weight gradients: partial-sum buffer must be 16-byte aligned");
@@ -1499,7 +1510,10 @@ int launch_wgrad_group_impl(const WgradProduct* products, int n, float out_scale
     case kGroup256: hipLaunchKernelGGL((wgrad_group_kernel<256, 256, 2, 8>), grid, dim3(512), 0, stream, a); break;
     case kGroup128Many: hipLaunchKernelGGL((wgrad_group_kernel<128, 128, 2, 4>), grid, dim3(256), 0, stream, a); break;
     case kGroup128: hipLaunchKernelGGL((wgrad_group_kernel_8<128, 128>), grid, dim3(512), 0, stream, a); break;
-    default: hipLaunchKernelGGL((wgrad_group_kernel<64, 64, 4, 4>), grid, dim3(256), 0, stream, a); break;
+    default:
+      if (n_sums) hipLaunchKernelGGL(wgrad_group_sums_kernel, dim3(a.total + n_sums * sums.nq * ceil_div(sums.cols, 256 / 32)), dim3(256), 0, stream, a, sums);
+      else hipLaunchKernelGGL((wgrad_group_kernel<64, 64, 4, 4>), grid, dim3(256), 0, stream, a);
+      sums_done = true;
   }
   NMT_LAUNCH_CHECK();
   if (splits == 1) return NMT_OK;
@@ -1554,10 +1568,18 @@ int64_t wgrad_group_floats(int64_t per_split, int64_t rows, int64_t most) {
 }
 
 int launch_wgrad_group(const WgradProduct* products, int n, float out_scale, float* partial, int64_t partial_floats, hipStream_t stream,
-                       int tile, int splits) {
+                       int tile, int splits, const ColumnSums* sums, int n_sums, int d) {
+  NMT_REQUIRE(n_sums >= 0 && n_sums <= kMaxColumnSums && (!n_sums || (sums && d > 0)), "weight gradients: %d column sums outside [0, %d]", n_sums, kMaxColumnSums);
   double flops = 0.0;
   for (int i = 0; products && i < n && i < kMaxWgrad; ++i) flops += 2.0 * products[i].M * products[i].N * products[i].K;
-  return timed_launch(flops, stream, [&] { return launch_wgrad_group_impl(products, n, out_scale, partial, partial_floats, stream, tile, splits); });
+  FinalizeArgs f = {3, d, d, out_scale, {}};
+  for (int i = 0; i < n_sums; ++i) f.in[i] = sums[i];
+  bool done = false;
+  const int rc = timed_launch(flops, stream, [&] {
+    return launch_wgrad_group_impl(products, n, out_scale, partial, partial_floats, stream, tile, splits, f, n_sums, done);
+  });
+  if (rc != NMT_OK || !n_sums || done) return rc;
+  return launch_layernorm_param_grads(sums, n_sums, d, out_scale, stream);
 }
 
 int gemm_timing_read(double* ms, int64_t* products, double* flops) {

@@ -769,9 +769,8 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   // (called when the last gradient that the layer's leaves read has been enqueued)
   auto flush_leaves = [&]() -> int {
     NMT_TRY(fork());
-    NMT_TRY(launch_wgrad_group(leaves, n_leaves, c->gscale, wgpart, wgpart_floats, sd));
+    NMT_TRY(launch_wgrad_group(leaves, n_leaves, c->gscale, wgpart, wgpart_floats, sd, 0, 0, ln_sums, sub_at, d));
     n_leaves = 0;
-    NMT_TRY(launch_layernorm_param_grads(ln_sums, sub_at, d, c->gscale, sd));
     if (two_streams) NMT_HIP_CHECK(hipEventRecord(c->ev_done[set], sd));
     return NMT_OK;
   };

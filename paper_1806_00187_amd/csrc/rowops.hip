@@ -264,41 +264,13 @@ __global__ void __launch_bounds__(kThreads) res_ln_bwd_kernel(const half_t* __re
     for (int i = threadIdx.x; i < quads; i += kThreads) dst[q * quads + i] = red4[q * NCH * 128 + i];
 }
 
-// dst[k][col] = fp16(scale * sum_b partial[b][k][col]), k = 0..nq-1, for up to kMaxColumnSums buffers of partial rows in one
-// launch: a layer's LayerNorm gradients are leaves like its weight gradients, so their two or three sums wait for the layer's
+// A layer's LayerNorm gradients are leaves like its weight gradients, so their two or three sums wait for the layer's
 // end and run on the second stream in place of a 3-6 us launch each in the chain of input gradients (whole updates of
-// 3000 positions x 512: 4.31 -> 4.18 ms).  A block of 1024 threads owns 32 columns of one quantity; its 32 row-lanes stride over the partial rows
-// (independent loads, several in flight) and are combined in a fixed order.
+// 3000 positions x 512: 4.31 -> 4.18 ms); beside small weight gradients they are part of those' launch.
 constexpr int kFinThreads = 1024;
-struct FinalizeArgs {
-  int nq, cols, pitch;
-  float scale;
-  ColumnSums in[kMaxColumnSums];
-};
 __global__ void __launch_bounds__(kFinThreads) finalize_partials_kernel(const FinalizeArgs a) {
-  __shared__ float red[32][33];
-  const int cx = threadIdx.x & 31, ry = threadIdx.x >> 5;
-  const int cblocks = (a.cols + 31) / 32;
-  const int k = (blockIdx.x / cblocks) % a.nq, col = (blockIdx.x % cblocks) * 32 + cx;
-  const ColumnSums& in = a.in[blockIdx.x / (cblocks * a.nq)];
-  const int nblk = in.rows;
-  float s = 0.f;
-  if (col < a.cols) {
-    const float* p = in.partial + (size_t)k * a.pitch + col;
-    const size_t step = (size_t)a.nq * a.pitch;
-    int b = ry;
-    for (; b + 96 < nblk; b += 128)
-      s += (p[b * step] + p[(b + 32) * step]) + (p[(b + 64) * step] + p[(b + 96) * step]);
-    for (; b < nblk; b += 32) s += p[b * step];
-  }
-  red[ry][cx] = s;
-  __syncthreads();
-  if (ry == 0 && col < a.cols) {
-    float t = red[0][cx];
-#pragma unroll
-    for (int r = 1; r < 32; ++r) t += red[r][cx];
-    if (in.dst[k]) in.dst[k][col] = (half_t)(t * a.scale);
-  }
+  __shared__ float red[32 * 33];
+  finalize_columns<kFinThreads>(a, blockIdx.x, red);
 }
 int launch_finalize(const ColumnSums* in, int n, int nq, int cols, int pitch, float scale, hipStream_t stream) {
   NMT_REQUIRE(in && n >= 1 && n <= kMaxColumnSums, "column sums: %d buffers outside [1, %d]", n, kMaxColumnSums);
