@@ -1115,7 +1115,7 @@ template <int BM, int BN, int NS, int NW>
 __global__ void __launch_bounds__(64 * NW) wgrad_group_kernel(const GroupArgs a) {
   wgrad_group<BM, BN, NS, NW>(a);
 }
-// The smallest tiles with the sums of partial rows that the layer's LayerNorm gradients are: work-groups of 8 columns behind the products'.
+// The smallest tiles, with the sums of partial rows (if any) that the layer's LayerNorm gradients are: work-groups of 8 columns behind the products'.
 // Passes with such groups are bound by the number of their launches, 4 us each: whole updates of 136 positions, two layers 64 wide, 526 -> 508 us
 // (medians of ten processes of each form in turn; 521 to 538 and 505 to 518 but for one and two that ran faster, 481 and 469 / 489).  The larger tiles' groups keep the sums' own launch: their passes are not bound by launches.
 __global__ void __launch_bounds__(256) wgrad_group_sums_kernel(const GroupArgs a, const FinalizeArgs f) {
@@ -1511,8 +1511,7 @@ int launch_wgrad_group_impl(const WgradProduct* products, int n, float out_scale
     case kGroup128Many: hipLaunchKernelGGL((wgrad_group_kernel<128, 128, 2, 4>), grid, dim3(256), 0, stream, a); break;
     case kGroup128: hipLaunchKernelGGL((wgrad_group_kernel_8<128, 128>), grid, dim3(512), 0, stream, a); break;
     default:
-      if (n_sums) hipLaunchKernelGGL(wgrad_group_sums_kernel, dim3(a.total + n_sums * sums.nq * ceil_div(sums.cols, 256 / 32)), dim3(256), 0, stream, a, sums);
-      else hipLaunchKernelGGL((wgrad_group_kernel<64, 64, 4, 4>), grid, dim3(256), 0, stream, a);
+      hipLaunchKernelGGL(wgrad_group_sums_kernel, dim3(a.total + n_sums * sums.nq * ceil_div(sums.cols, 256 / 32)), dim3(256), 0, stream, a, sums);
       sums_done = true;
   }
   NMT_LAUNCH_CHECK();

@@ -257,6 +257,28 @@ def test_layernorm_gradients_beside_small_weight_gradients_match_oracle(d, heads
     sess.close()
 
 
+# A layer's LayerNorm gradients are summed by 256 threads in the launch of its weight gradients where those have the smallest tiles, by 1024 in
+# a launch of their own otherwise, in the same order.  With 16 passes said to share the chip the groups below have larger tiles instead
+# (and as many pieces): one piece at 1500 positions, at 9000 three for the encoder's.
+@pytest.mark.parametrize("B,S,T", [(45, 34, 33), (225, 40, 40)])
+def test_layernorm_gradients_in_either_launch_are_the_same_bits(B, S, T):
+    model = dict(enc_layers=1, dec_layers=1, d_model=144, n_heads=9, d_ff=288, vocab=136, dropout=0.1)
+    sess = Session(model, I.init_weights(seed=23, perturb=0.05, **model), max_sentences=B)
+    db = sess.to_device(I.tiny_batch(seed=B, B=B, S=S, T=T, vocab=136, short_rows=3, short_by=1))
+    got = []
+    try:
+        for share in (1, 16):
+            A.nmt_tuning("gemm_share", share)
+            sess.g16.fill_(float("nan"))
+            sess.forward_loss(db, 8.0, 1, 0)
+            sess.backward()
+            got.append(sess.g16.clone())
+    finally:
+        A.nmt_tuning("defaults")
+        sess.close()
+    assert torch.isfinite(got[0]).all() and torch.equal(got[0].view(torch.int16), got[1].view(torch.int16))
+
+
 def test_medium_model_spans_several_tiles_with_ragged_shapes():
     """d=256, 4 heads of 64, F=1024, V=2056, 45 sentences of up to 37/41 tokens: every GEMM spans
     several tiles with ragged edges; lengths vary per sentence."""
