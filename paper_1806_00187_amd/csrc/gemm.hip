@@ -321,34 +321,34 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const floatx4 (&ac
           }
           const size_t off = (size_t)gr * g.ldc + gc;
           if constexpr (!PLAIN) {
-          if (ep.bias) {
-            const half8_t b = ld_half8(ep.bias + gc);
+            if (ep.bias) {
+              const half8_t b = ld_half8(ep.bias + gc);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] += (float)b[e];
-          }
-          if (ep.relu) {
+              for (int e = 0; e < 8; ++e) v[e] += (float)b[e];
+            }
+            if (ep.relu) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = fmaxf(v[e], 0.f);
-          }
-          if (ep.drop.thr) {
-            const uint32_t bits = drop_keep8(ep.drop, (uint32_t)(gr + ep.row0), (uint32_t)gc >> 3);
+              for (int e = 0; e < 8; ++e) v[e] = fmaxf(v[e], 0.f);
+            }
+            if (ep.drop.thr) {
+              const uint32_t bits = drop_keep8(ep.drop, (uint32_t)(gr + ep.row0), (uint32_t)gc >> 3);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = ((bits >> e) & 1u) ? v[e] * ep.drop.scale : 0.f;
-          }
-          if (ep.add) {
-            half8_t a;
-            if constexpr (PRELOAD) a = pre[(i * (WN / SW) + jg) * (CH / 2) + it];
-            else a = ld_half8(ep.add + off);
+              for (int e = 0; e < 8; ++e) v[e] = ((bits >> e) & 1u) ? v[e] * ep.drop.scale : 0.f;
+            }
+            if (ep.add) {
+              half8_t a;
+              if constexpr (PRELOAD) a = pre[(i * (WN / SW) + jg) * (CH / 2) + it];
+              else a = ld_half8(ep.add + off);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] += (float)a[e];
-          }
-          if (ep.relu_src) {
-            half8_t h;
-            if (PRELOAD && !ep.add) h = pre[(i * (WN / SW) + jg) * (CH / 2) + it];
-            else h = ld_half8(ep.relu_src + off);
+              for (int e = 0; e < 8; ++e) v[e] += (float)a[e];
+            }
+            if (ep.relu_src) {
+              half8_t h;
+              if (PRELOAD && !ep.add) h = pre[(i * (WN / SW) + jg) * (CH / 2) + it];
+              else h = ld_half8(ep.relu_src + off);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = ((float)h[e] > 0.f) ? v[e] * ep.mask_scale : 0.f;
-          }
+              for (int e = 0; e < 8; ++e) v[e] = ((float)h[e] > 0.f) ? v[e] * ep.mask_scale : 0.f;
+            }
           }
           half8_t o;
 #pragma unroll
@@ -369,7 +369,8 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const floatx4 (&ac
 // the instruction the products are formed with (bias gradients are the updates' most sensitive sums: those of the keys are zero but for
 // rounding).  Lanes 0..31 keep them for one strip, lanes 32..63 for the next: the swap puts q = 0 and 1 of both in one register, q = 2 and 3
 // in the other.  Every wavefront of a row half has the same fragments, so each sums a pair of strips of its own: sixteen sub-batches
-// of a 1024 wide model, whole update, 73.4 ms with all of them summing all strips, 72.1 so.
+// of a 1024 wide model, whole update, 73.4 ms with all of them summing all strips, 72.1 so; an encoder layer's group over 3000 positions 512
+// wide, alone, 40.5 and 34.0 us.
 __device__ __forceinline__ float piece_sum(const half8_t& f) {
   typedef _Float16 half2v_t __attribute__((ext_vector_type(2)));
   struct Pairs { half2v_t p[4]; };
@@ -406,7 +407,8 @@ __device__ __forceinline__ void store_colsum(const GemmArgs& g, float sum, int m
 // What bounds it: the power the chip may take (matrix pipes busy 0.7-0.8 of the cycles at 1.4-1.8 GHz) and, at k = 1024, the
 // 3-5 us a tile takes besides its k-tiles.  TFLOP/s before (32x32x16, requests in one go, four stages of 32 for k-major operands) and
 // now: 8192^3 x W^T 1268 / 1423, dy W 1244 / 1400, dy^T x 1251 / 1360; 52704 rows: 3072 x 1024 x W^T 1056 / 1150, 1024 x 4096 1116 / 1218,
-// 4096 x 1024 dy W 1083 / 1140; a layer's weight gradients over 52700 positions 1024 wide 840 / 933.  Two stages of 64 k against
+// 4096 x 1024 dy W 1083 / 1140; a layer's weight gradients over 52700 positions 1024 wide 840 / 933
+// (without and with each wavefront summing bias gradients of its own strips only, on another chip: 1017 / 1072).  Two stages of 64 k against
 // four of 32 here: x W^T 760 / 808 us, dy W 773 / 793, dy^T x 794 / 805 (8192^3).
 // ------------------------------------------------------------------------------------------------
 // The product as an instruction of its own, so that the sums stay where they are: the compiler's form of this shape has a result
@@ -1060,9 +1062,9 @@ __global__ void __launch_bounds__(kThreads) splitk_reduce_kernel(const float* __
 // Weight gradients of one layer in one launch.  Each of them alone is too small to fill the chip (512 x 2048 results are
 // 64 tiles of 128 x 128), so one by one they were cut along the positions, wrote fp32 partial sums and needed a
 // second kernel each; together a layer's four to seven products are one launch of whole tiles, and the bias gradients
-// ride along (no pass over memory for the column sums).  An encoder layer's over 3000 positions, alone on the chip: 36 us
-// 512 wide, 91 us 1024 wide (0.83 PFLOP/s), where the products, reductions and column sums one by one took 145 and 276 us of kernel
-// time beside the chain; over 53000 positions 1024 wide: 1.29 ms (1.04 PFLOP/s).
+// ride along (no pass over memory for the column sums).  An encoder layer's over 3000 positions, alone on the chip: 34 us
+// 512 wide, 78 us 1024 wide (0.97 PFLOP/s), where the products, reductions and column sums one by one took 145 and 276 us of kernel
+// time beside the chain; over 52700 positions 1024 wide: 1.24 ms (1.07 PFLOP/s).
 // ------------------------------------------------------------------------------------------------
 struct GroupArgs {
   int n, xcds, group_m, splits, total;
@@ -1389,6 +1391,7 @@ enum GroupTile { kGroup256 = 1, kGroup128Many, kGroup128, kGroup64, kGroupTiles 
 constexpr int kGroupEdge[kGroupTiles + 1] = {0, 256, 128, 128, 64};
 // What one work-group takes for a 64-deep piece of the contraction, in us, from timings of the layer groups of four widths
 // (64 to 1024) over 130 to 53000 positions: with few compute units at work, and with all of them; per_cu work-groups share one.
+// (The figures are older than the kernels: an encoder layer's group over 52200 positions 1024 wide, 1584 us by them, takes 1221.)
 struct GroupCost {
   int per_cu;
   double fixed, k_tile_few, k_tile[2];
@@ -1429,7 +1432,7 @@ double group_us(int tile, const WgradProduct* p, int n, int splits, int cus, dou
 // only the embedding kernels beside it, and with one stream there is nothing).  Weights of 0 to 4 for it measured the
 // same updates within 1 to 2 %, this one at the lower end throughout.  (What the model leaves out: a group of 256 x 256 tiles takes every
 // compute unit whole, one work-group of 128 KB of LDS each, so the next layer's first kernels wait for it or crawl beside it: over
-// 52000 positions 1024 wide LayerNorm backward takes 183 us on average beside the groups, 107 alone, while attention backward, later in
+// 52000 positions 1024 wide LayerNorm backward takes 171 us on average beside the groups, 106 alone, while attention backward, later in
 // the layer, finds nothing beside it any more.)
 constexpr double kGroupLatencyWeight = 0.5;
 // The numbers of k splits looked at, and the fewest positions a split may have.
