@@ -138,11 +138,9 @@ __device__ __forceinline__ uint32_t drop_row_pos(const DropDev& dd, uint32_t row
 
 // What row `row` puts into the counters, for kernels that fetch it ahead of the draws.
 struct DropRow { uint32_t uid, pos, c3; };
+__device__ __forceinline__ DropRow drop_row_of(const DropDev& dd, uint2 rk) { return DropRow{rk.x, rk.y & 0xFFFFu, (dd.c3 & 0xFFFFFF00u) | (rk.y >> 16)}; }
 __device__ __forceinline__ DropRow drop_row(const DropDev& dd, uint32_t row) {
-  if (dd.rowkey) {
-    const uint2 rk = dd.rowkey[row];
-    return DropRow{rk.x, rk.y & 0xFFFFu, (dd.c3 & 0xFFFFFF00u) | (rk.y >> 16)};
-  }
+  if (dd.rowkey) return drop_row_of(dd, dd.rowkey[row]);
   const uint32_t sent = row / (uint32_t)dd.n_pos;
   return DropRow{dd.uid ? dd.uid[sent] : sent, row - sent * (uint32_t)dd.n_pos, dd.c3};
 }

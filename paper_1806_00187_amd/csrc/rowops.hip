@@ -640,74 +640,111 @@ __device__ __forceinline__ void emb_add(half_t* __restrict__ dst, const half8_t 
   st_half8(dst, pack8(cur));
 }
 
-// One block per segment of kEmbSeg sorted entries, one thread per 8 columns.
+// One block per segment of kEmbSeg sorted entries.
 // part[(2 * seg + 0) * d ..]: sum of the segment's first run if that run began in an earlier segment;
 // part[(2 * seg + 1) * d ..]: sum of its last run if that run began here and goes on in the next one.
-// Bound by latency (a few hundred thousand columns in all): the gradient rows, row keys and table rows of
-// kEmbAhead entries are requested together before any is used, in place of a chain of dependent loads per
-// entry, and a segment is short (94 -> 16 us at 6000 entries x 512 columns, 113 -> 81 us at 107000 x 1024;
-// 64-entry segments took 27 us at 6000).
-constexpr int kEmbAhead = 8;
-static_assert(kEmbSeg % kEmbAhead == 0 && kEmbSeg + 2 <= kWave, "a block's first wavefront stages the segment's ids");
-__global__ void __launch_bounds__(kThreads) emb_segment_kernel(const half_t* __restrict__ dxa, int na, DropDev da,
-                                                               const half_t* __restrict__ dxb, DropDev db, half_t* __restrict__ gE, int n,
-                                                               int d, const int32_t* __restrict__ keys, const int32_t* __restrict__ perm,
-                                                               float* __restrict__ part, float scale) {
-  __shared__ int s_pos[kEmbSeg], s_key[kEmbSeg + 2];  // s_key: with the entries before and after the segment (-1: none)
-  __shared__ DropRow s_drop[kEmbSeg];
+// Bound by latency (a few hundred thousand columns in all): a position, its gradient row and row key, the dropout draws, the sum.
+// The draws are ten rounds of dependent multiplies for eight columns, so the entries of a segment are shared out: a group of d / 8
+// threads takes every groups-th entry (AHEAD of them, all requested together) and leaves the row after dropout in LDS; then
+// the first group adds the entries up in the order of the list, a thread per eight columns.  The ids are the same for the whole
+// block and come with one load; EARLY: the table rows of runs that end here are asked for beside the gradient rows.
+// Before (a thread per eight columns drew for all sixteen entries) and now, us: 260 entries x 64 16.2 / 6.5, 2800 x 256 16.7 / 6.8,
+// 6600 x 512 16 to 28 / 10, 27000 x 512 alone 18.1 / 16.6, 35700 x 1024 alone 31.5 / 33.8, of distinct ids 42.6 / 38.3.
+template <int THREADS, int AHEAD, bool EARLY>
+__global__ void __launch_bounds__(THREADS) emb_segment_kernel(const half_t* __restrict__ dxa, int na, DropDev da,
+                                                           const half_t* __restrict__ dxb, DropDev db, half_t* __restrict__ gE, int n,
+                                                           int d, const int32_t* __restrict__ keys, const int32_t* __restrict__ perm,
+                                                           float* __restrict__ part, float scale) {
+  extern __shared__ __align__(16) half_t s_row[];  // [kEmbSeg][d]
+  __shared__ float s_scale[kEmbSeg];
   const int e0 = blockIdx.x * kEmbSeg, cnt = min(kEmbSeg, n - e0);
-  if (threadIdx.x < kEmbSeg + 2) {
-    const int i = e0 - 1 + (int)threadIdx.x;
-    s_key[threadIdx.x] = i >= 0 && i < n ? keys[i] : -1;
-    if (threadIdx.x < kEmbSeg) {
-      const int pos = i + 1 < n ? perm[i + 1] : 0;
-      s_pos[threadIdx.x] = pos;
-      if (pos < na ? da.thr : db.thr) s_drop[threadIdx.x] = drop_row(pos < na ? da : db, (uint32_t)(pos < na ? pos : pos - na));
+  const int chunks = d >> 3, groups = THREADS / chunks, g = (int)threadIdx.x / chunks, c = (int)threadIdx.x - g * chunks;
+  const int lane = (int)threadIdx.x & 63, before = keys[max(0, min(e0 - 1 + min(lane, kEmbSeg + 1), n - 1))];
+  int pos[AHEAD];
+  half8_t x[AHEAD];
+  uint2 rk[AHEAD];
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u) pos[u] = perm[min(e0 + min(g + u * groups, kEmbSeg - 1), n - 1)];  // (one past the end repeats another)
+  const bool keyed = da.rowkey && db.rowkey;  // (in a pass of the training step; without row keys: rows of one rectangular batch)
+  auto row_of = [&](int u) { return pos[u] < na ? pos[u] : pos[u] - na; };
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u) {
+    x[u] = ld_half8((pos[u] < na ? dxa : dxb) + (size_t)row_of(u) * d + c * 8);
+  }
+  if (keyed) {
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) rk[u] = (pos[u] < na ? da.rowkey : db.rowkey)[row_of(u)];
+  } else {
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      const DropDev& dd = pos[u] < na ? da : db;
+      const DropRow row = dd.thr ? drop_row(dd, (uint32_t)row_of(u)) : DropRow{};
+      rk[u] = make_uint2(row.uid, row.pos | (row.c3 & 0xFFu) << 16);
+    }
+  }
+  // the ids of the entries before, in and behind the segment (-1: none), the same in every lane
+  int key[kEmbSeg + 2];
+#pragma unroll
+  for (int u = 0; u < kEmbSeg + 2; ++u) {
+    const int i = e0 - 1 + u, k = __builtin_amdgcn_readlane(before, u);
+    key[u] = i >= 0 && i < n ? k : -1;
+  }
+  // the table's rows of runs that end here (of runs that began earlier the next kernel takes care); the others' requests lie outside the extent
+  const __amdgpu_buffer_rsrc_t to = __builtin_amdgcn_make_buffer_rsrc(gE, 0, 0x7FFFFFFF, 0x00020000);
+  const bool sums = g == 0;  // (the threads of the first group add up, eight columns each: c is their chunk)
+  auto table_row = [&](int u) {
+    const bool ends = key[u + 1] != key[u + 2] && key[u + 1] != key[0] && key[u + 1] >= 0;
+    const uint32_t at = ((uint32_t)key[u + 1] * (uint32_t)d + (uint32_t)c * 8u) * 2u;
+    return __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(to, (int)(ends && sums ? at : 0x80000000u), 0, 0));
+  };
+  half8_t table[kEmbSeg];
+  if constexpr (EARLY) {
+#pragma unroll
+    for (int u = 0; u < kEmbSeg; ++u) table[u] = table_row(u);
+  }
+  if (da.thr || db.thr) {
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      const DropDev& dd = pos[u] < na ? da : db;
+      const uint32_t bits = drop_keep8(dd, drop_row_of(dd, rk[u]), (uint32_t)c);  // (a threshold of 0 keeps all)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[u][e] = (bits >> e) & 1u ? x[u][e] : (half_t)0;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u) {
+    const int k = g + u * groups;
+    if (g < groups && k < kEmbSeg) {
+      st_half8(s_row + (size_t)k * d + c * 8, x[u]);
+      if (c == 0) s_scale[k] = pos[u] < na ? (da.thr ? da.scale : 1.f) : (db.thr ? db.scale : 1.f);
     }
   }
   __syncthreads();
-  const int c = threadIdx.x;
-  if (c >= (d >> 3)) return;
+  if (!sums) return;
+  if constexpr (!EARLY) {
+#pragma unroll
+    for (int u = 0; u < kEmbSeg; ++u) table[u] = table_row(u);
+  }
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  int run_begin = 0;
-  for (int k0 = 0; k0 < cnt; k0 += kEmbAhead) {
-    half8_t x[kEmbAhead], row[kEmbAhead];
-    uint32_t bits[kEmbAhead];
-    int pos[kEmbAhead], key[kEmbAhead + 1];  // the same in every lane: kept in scalar registers
 #pragma unroll
-    for (int u = 0; u <= kEmbAhead; ++u) key[u] = __builtin_amdgcn_readfirstlane(s_key[min(k0 + u, cnt) + 1]);
+  for (int u = 0; u < kEmbSeg; ++u) {
+    if (u < cnt) {
+      const half8_t in = ld_half8(s_row + (size_t)u * d + c * 8);
+      const float sc = s_scale[u];
 #pragma unroll
-    for (int u = 0; u < kEmbAhead; ++u) {
-      pos[u] = __builtin_amdgcn_readfirstlane(s_pos[min(k0 + u, cnt - 1)]);  // (an entry past the end repeats the last one and is not added)
-      x[u] = ld_half8((pos[u] < na ? dxa + (size_t)pos[u] * d : dxb + (size_t)(pos[u] - na) * d) + c * 8);
-      row[u] = zero_half8();
-      if (key[u + 1] != key[u] && key[u] >= 0) row[u] = ld_half8(gE + (size_t)key[u] * d + c * 8);  // the run ends here: its row is needed
-    }
+      for (int e = 0; e < 8; ++e) acc[e] += (float)in[e] * sc;
+      const bool goes_on = key[u + 2] == key[u + 1], came_in = key[u + 1] == key[0];
+      if (!goes_on || u + 1 == cnt) {
+        if (!came_in && !goes_on) {
+          emb_add(gE + (size_t)key[u + 1] * d + c * 8, table[u], d, acc, scale);
+        } else {
+          floatx4* dst = reinterpret_cast<floatx4*>(part + ((size_t)2 * blockIdx.x + (came_in ? 0 : 1)) * d + c * 8);
+          dst[0] = floatx4{acc[0], acc[1], acc[2], acc[3]};
+          dst[1] = floatx4{acc[4], acc[5], acc[6], acc[7]};
+        }
 #pragma unroll
-    for (int u = 0; u < kEmbAhead; ++u) {
-      const bool in_a = pos[u] < na;
-      bits[u] = (in_a ? da.thr : db.thr) ? drop_keep8(in_a ? da : db, s_drop[min(k0 + u, cnt - 1)], (uint32_t)c) : 0xFFu;
-    }
-#pragma unroll
-    for (int u = 0; u < kEmbAhead; ++u) {
-      const int k = k0 + u;
-      if (k >= cnt) break;
-      const float sc = pos[u] < na ? (da.thr ? da.scale : 1.f) : (db.thr ? db.scale : 1.f);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] += ((bits[u] >> e) & 1u) ? (float)x[u][e] * sc : 0.f;
-      const bool goes_on = key[u + 1] == key[u];
-      if (goes_on && k + 1 < cnt) continue;
-      const bool came_in = run_begin == 0 && __builtin_amdgcn_readfirstlane(s_key[0]) == key[u];
-      if (!came_in && !goes_on) {
-        emb_add(gE + (size_t)key[u] * d + c * 8, row[u], d, acc, scale);
-      } else {
-        float* dst = part + ((size_t)2 * blockIdx.x + (came_in ? 0 : 1)) * d + c * 8;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dst[e] = acc[e];
+        for (int e = 0; e < 8; ++e) acc[e] = 0.f;
       }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-      run_begin = k + 1;
     }
   }
 }
@@ -1096,8 +1133,25 @@ int launch_embed_sum(const half_t* dx_a, int rows_a, const DropDev& drop_a, cons
   const EmbScratch e = emb_scratch(n, d);
   const int32_t *keys = scratch + e.keys, *perm = scratch + e.perm;
   float* part = const_cast<float*>(reinterpret_cast<const float*>(scratch + e.part));
-  const int threads = (int)round_up(d / 8, kWave);
-  hipLaunchKernelGGL(emb_segment_kernel, dim3(e.nseg), dim3(threads), 0, stream, dx_a, rows_a, drop_a, dx_b, drop_b, gE, n, d, keys, perm, part, scale);
+  const size_t lds = (size_t)kEmbSeg * d * sizeof(half_t);
+  auto segments = [&](auto kernel, int threads) -> int {
+    if (lds > 48 * 1024) NMT_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(kernel, dim3(e.nseg), dim3(threads), lds, stream, dx_a, rows_a, drop_a, dx_b, drop_b, gE, n, d, keys, perm, part, scale);
+    return NMT_OK;
+  };
+  // THREADS / (d / 8) groups times AHEAD entries are a segment or more.  From four segments per compute unit on the table's rows are asked for late and
+  // rows of 1024 take four wavefronts: what counts then is how many blocks share a compute unit, not the length of one (35700 x
+  // 1024, distinct ids: 42.6 us early and on eight, 38.3 so; 6600 x 512, all beside the last weight gradients: 14 late, 9.7 early).
+  auto form = [&](auto early) -> int {
+    constexpr bool E = decltype(early)::value;
+    const int chunks = d / 8;
+    if (chunks <= 256 / kEmbSeg) return segments(emb_segment_kernel<256, 1, E>, 256);
+    if (chunks <= 512 / kEmbSeg) return segments(emb_segment_kernel<256, 2, E>, 256);
+    if (chunks <= 1024 / kEmbSeg) return segments(emb_segment_kernel<256, 4, E>, 256);
+    if (chunks <= 2048 / kEmbSeg) return E ? segments(emb_segment_kernel<512, 4, E>, 512) : segments(emb_segment_kernel<256, 8, false>, 256);
+    return segments(emb_segment_kernel<1024, 4, E>, 1024);
+  };
+  if (int rc = e.nseg < 4 * device_info().cus ? form(std::true_type{}) : form(std::false_type{})) return rc;
   NMT_LAUNCH_CHECK();
   hipLaunchKernelGGL(emb_finish_kernel, dim3(e.nseg), dim3(kEmbFinish), 0, stream, gE, n, d, keys, part, scale);
   NMT_LAUNCH_CHECK();
