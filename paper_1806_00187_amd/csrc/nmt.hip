@@ -143,7 +143,7 @@ struct nmt_ctx {
   Plan plan;
   // second stream: weight gradients, and products over the encoder output beside the decoder (created on first use)
   hipStream_t side = nullptr;
-  hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_embed = nullptr, ev_kv = nullptr, ev_denc = nullptr, ev_done[2] = {nullptr, nullptr};
+  hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_embed = nullptr, ev_self = nullptr, ev_denc = nullptr, ev_done[2] = {nullptr, nullptr};
 };
 
 namespace {
@@ -356,7 +356,7 @@ extern "C" void nmt_destroy(nmt_ctx* ctx) {
     (void)hipStreamSynchronize(ctx->side);
     (void)hipStreamDestroy(ctx->side);
   }
-  for (hipEvent_t e : {ctx->ev_fork, ctx->ev_join, ctx->ev_embed, ctx->ev_kv, ctx->ev_denc, ctx->ev_done[0], ctx->ev_done[1]})
+  for (hipEvent_t e : {ctx->ev_fork, ctx->ev_join, ctx->ev_embed, ctx->ev_self, ctx->ev_denc, ctx->ev_done[0], ctx->ev_done[1]})
     if (e) (void)hipEventDestroy(e);
   delete ctx;
 }
@@ -418,7 +418,7 @@ namespace {
 // stream, so a first pass may do it while the caller's stream is being captured; the second stream then joins the capture.)
 int ensure_second_stream(nmt_ctx* c) {
   if (!c->ev_fork) {
-    hipEvent_t* const events[] = {&c->ev_join, &c->ev_embed, &c->ev_kv, &c->ev_denc, &c->ev_done[0], &c->ev_done[1], &c->ev_fork};
+    hipEvent_t* const events[] = {&c->ev_join, &c->ev_embed, &c->ev_self, &c->ev_denc, &c->ev_done[0], &c->ev_done[1], &c->ev_fork};
     for (hipEvent_t* e : events)
       if (!*e) NMT_HIP_CHECK(hipEventCreateWithFlags(e, hipEventDisableTiming));
   }
@@ -600,6 +600,40 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
   const AttnWork wl_ss = attention_work(r.ws<int32_t>(p.wl_ss), Bt, Ns, 0), wl_tt = attention_work(r.ws<int32_t>(p.wl_tt), Bt, Nt, 0),
                  wl_ts = attention_work(r.ws<int32_t>(p.wl_ts), Bt, Nt, Ns);
 
+  // a decoder layer up to the queries of its encoder-decoder attention
+  auto decoder_self = [&](const Run& on, int l) -> int {
+    const DecP& P = c->dec[l];
+    const DecW& W = p.dec[l];
+    const int li = k.enc_layers + l;
+    const half_t* y = l ? on.ws<half_t>(p.dec[l - 1].x3) : on.ws<half_t>(p.y0);
+    half_t* qkv = on.ws<half_t>(W.qkv);
+    NMT_TRY(on.linear(y, Nt, d, P.self.wqkv, P.self.bqkv, 3 * d, qkv));
+    NMT_TRY(launch_attention_fwd(qkv, 3 * d, qkv + d, 3 * d, qkv + 2 * d, 3 * d, on.ws<half_t>(W.o1), d, on.ws<float>(W.lse1), d_tgt_in,
+                                 k.pad_id, 1, Bt, H, dh, maxT, maxT, tab_tt, Nt, &wl_tt, on.st));
+    NMT_TRY(on.linear(on.ws<half_t>(W.o1), Nt, d, P.self.wo, P.self.bo, d, on.ws<half_t>(W.s1)));
+    NMT_TRY(launch_residual_layernorm_fwd(on.ws<half_t>(W.s1), y, on.w(P.ln1.g), on.w(P.ln1.b), on.ws<half_t>(W.x1), on.ws<float>(W.st1),
+                                          Nt, d, k.ln_eps, on.drop(layer_site(li, kKindSelfRes), true, k.dropout), on.st));
+    return on.linear(on.ws<half_t>(W.x1), Nt, d, P.cross.wq, P.cross.bq, d, on.ws<half_t>(W.q));
+  };
+  auto embed_targets = [&](const Run& on) {
+    return launch_embed_fwd(d_tgt_in, on.w(c->embed), on.ws<half_t>(p.y0), Nt, d, V, on.drop(kSiteEmbTgt, true, k.dropout), on.st);
+  };
+
+  // ---- the decoder's first layer needs the encoder from its second attention on: what comes before runs beside the encoder ----
+  // (Whole update of 3000 positions 512 wide, this and the backward pass's counterpart: 3787 -> 3766 us; 13000 512 wide 9120 -> 9014; 380 1024 wide
+  // 4300 -> 4270.  Not in a context's first pass: making the second stream takes 150 us, which that pass hides behind the encoder's kernels.
+  // Its launches come behind those of the encoder's first layer, so that the caller's stream is not kept waiting for the host.)
+  const bool beside = encoder_products_beside(c), self_beside = beside && c->side;
+  if (self_beside) NMT_HIP_CHECK(hipEventRecord(c->ev_fork, st));
+  auto decoder_ahead = [&]() -> int {
+    const Run side{c, c->side};
+    NMT_HIP_CHECK(hipStreamWaitEvent(c->side, c->ev_fork, 0));
+    NMT_TRY(embed_targets(side));
+    NMT_TRY(decoder_self(side, 0));
+    NMT_HIP_CHECK(hipEventRecord(c->ev_self, c->side));
+    return NMT_OK;
+  };
+
   // ---- encoder ----
   half_t* x = r.ws<half_t>(p.x0);
   NMT_TRY(launch_embed_fwd(d_src, r.w(c->embed), x, Ns, d, V, r.drop(kSiteEmbSrc, false, k.dropout), st));
@@ -621,6 +655,7 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
     NMT_TRY(launch_residual_layernorm_fwd(r.ws<half_t>(W.s2), r.ws<half_t>(W.x1), r.w(P.ln2.g), r.w(P.ln2.b), r.ws<half_t>(W.x2),
                                           r.ws<float>(W.st2), Ns, d, k.ln_eps, r.drop(layer_site(l, kKindFfnRes), false, k.dropout), st));
     x = r.ws<half_t>(W.x2);
+    if (self_beside && l == 0) NMT_TRY(decoder_ahead());
   }
   const half_t* enc_out = x;
 
@@ -628,37 +663,27 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
   auto project_kv = [&](const Run& on, int l) {
     return on.linear(enc_out, Ns, d, c->dec[l].cross.wkv, c->dec[l].cross.bkv, 2 * d, r.ws<half_t>(p.dec[l].kv));
   };
-  const bool beside = encoder_products_beside(c);
-  if (beside) {
+  if (beside && k.dec_layers > 1) {
     NMT_TRY(ensure_second_stream(c));
     const Run side{c, c->side};
     NMT_HIP_CHECK(hipEventRecord(c->ev_fork, st));
     NMT_HIP_CHECK(hipStreamWaitEvent(c->side, c->ev_fork, 0));
-    for (int l = 0; l < k.dec_layers; ++l) {
-      NMT_TRY(project_kv(side, l));
-      if (l == 0) NMT_HIP_CHECK(hipEventRecord(c->ev_kv, c->side));
-    }
-    if (k.dec_layers > 1) NMT_HIP_CHECK(hipEventRecord(c->ev_join, c->side));
+    for (int l = 1; l < k.dec_layers; ++l) NMT_TRY(project_kv(side, l));
+    NMT_HIP_CHECK(hipEventRecord(c->ev_join, c->side));
   }
 
   // ---- decoder ----
-  half_t* y = r.ws<half_t>(p.y0);
-  NMT_TRY(launch_embed_fwd(d_tgt_in, r.w(c->embed), y, Nt, d, V, r.drop(kSiteEmbTgt, true, k.dropout), st));
+  if (!self_beside) NMT_TRY(embed_targets(r));
+  const half_t* y = nullptr;
   for (int l = 0; l < k.dec_layers; ++l) {
     const DecP& P = c->dec[l];
     const DecW& W = p.dec[l];
     const int li = k.enc_layers + l;
-    half_t* qkv = r.ws<half_t>(W.qkv);
-    NMT_TRY(r.linear(y, Nt, d, P.self.wqkv, P.self.bqkv, 3 * d, qkv));
-    NMT_TRY(launch_attention_fwd(qkv, 3 * d, qkv + d, 3 * d, qkv + 2 * d, 3 * d, r.ws<half_t>(W.o1), d, r.ws<float>(W.lse1), d_tgt_in,
-                                 k.pad_id, 1, Bt, H, dh, maxT, maxT, tab_tt, Nt, &wl_tt, st));
-    NMT_TRY(r.linear(r.ws<half_t>(W.o1), Nt, d, P.self.wo, P.self.bo, d, r.ws<half_t>(W.s1)));
-    NMT_TRY(launch_residual_layernorm_fwd(r.ws<half_t>(W.s1), y, r.w(P.ln1.g), r.w(P.ln1.b), r.ws<half_t>(W.x1), r.ws<float>(W.st1),
-                                          Nt, d, k.ln_eps, r.drop(layer_site(li, kKindSelfRes), true, k.dropout), st));
     half_t* kv = r.ws<half_t>(W.kv);
-    NMT_TRY(r.linear(r.ws<half_t>(W.x1), Nt, d, P.cross.wq, P.cross.bq, d, r.ws<half_t>(W.q)));
-    if (!beside) NMT_TRY(project_kv(r, l));
-    else if (l < 2) NMT_HIP_CHECK(hipStreamWaitEvent(st, l ? c->ev_join : c->ev_kv, 0));
+    if (!self_beside || l) NMT_TRY(decoder_self(r, l));
+    if (!beside || !l) NMT_TRY(project_kv(r, l));
+    if (self_beside && l == 0) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_self, 0));
+    if (beside && l == 1) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_join, 0));
     NMT_TRY(launch_attention_fwd(r.ws<half_t>(W.q), d, kv, 2 * d, kv + d, 2 * d, r.ws<half_t>(W.o2), d, r.ws<float>(W.lse2), d_src,
                                  k.pad_id, 0, Bt, H, dh, maxT, maxS, tab_ts, Nt, &wl_ts, st));
     NMT_TRY(r.linear(r.ws<half_t>(W.o2), Nt, d, P.cross.wo, P.cross.bo, d, r.ws<half_t>(W.s2)));
@@ -713,7 +738,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   const Run side{c, sd};
   const bool dropping = c->training && k.dropout > 0.f;
   const float act_scale = (c->training && k.act_dropout > 0.f) ? 1.f / (1.f - k.act_dropout) : 1.f;
-  half_t* dO = r.ws<half_t>(p.dO);
+  half_t *dO = r.ws<half_t>(p.dO), *dy_place = r.ws<half_t>(p.dy);
   const int4 *tab_ss = r.ws<int4>(p.tab_ss), *tab_tt = r.ws<int4>(p.tab_tt), *tab_ts = r.ws<int4>(p.tab_ts);
   const AttnWork wl_ss = attention_work(r.ws<int32_t>(p.wl_ss), Bt, Ns, 0), wl_tt = attention_work(r.ws<int32_t>(p.wl_tt), Bt, Nt, 0),
                  wl_ts = attention_work(r.ws<int32_t>(p.wl_ts), Bt, Nt, Ns);
@@ -752,7 +777,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     half_t* sub = next_dsub;
     next_dsub = const_cast<half_t*>(output);
     lnpart = r.ws<float>(p.lnpart[set][sub_at++]);
-    dy = dropping ? r.ws<half_t>(p.dy) : sub;
+    dy = dropping ? dy_place : sub;
     dym = dropping ? sub : nullptr;
     dsub = sub;
   };
@@ -767,8 +792,8 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     leaves[n_leaves++] = {grad, x, r.g(gW), gb < 0 ? nullptr : r.g(gb), out, in, in, out, in, N};
   };
   // (called when the last gradient that the layer's leaves read has been enqueued)
-  auto flush_leaves = [&]() -> int {
-    NMT_TRY(fork());
+  auto flush_leaves = [&](bool forks) -> int {
+    if (forks) NMT_TRY(fork());
     NMT_TRY(launch_wgrad_group(leaves, n_leaves, c->gscale, wgpart, wgpart_floats, sd, 0, 0, ln_sums, sub_at, d));
     n_leaves = 0;
     if (two_streams) NMT_HIP_CHECK(hipEventRecord(c->ev_done[set], sd));
@@ -791,23 +816,27 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     res.add = dy;
     return r.dgrad(dhid, N, F, f.w1, d, dx, res);
   };
-  // self-attention sub-layer (fused q, k, v projection)
-  auto self_bwd = [&](half_t* dx, int N, bool tgt, const half_t* x_in, const half_t* qkv, const half_t* o, const float* lse,
+  // self-attention sub-layer (fused q, k, v projection); `on`: the stream its chain runs on
+  auto self_bwd = [&](const Run& on, half_t* dx, int N, bool tgt, const half_t* x_in, const half_t* qkv, const half_t* o, const float* lse,
                       const half_t* sub, const float* stats, const AttnP& a, const LnP& ln, uint32_t site_res, const int32_t* key_ids,
                       int causal) -> int {
     begin_sublayer(sub);
     NMT_TRY(launch_residual_layernorm_bwd(dx, sub, x_in, r.w(ln.g), stats, dy, dym, r.g(ln.g), r.g(ln.b), r.g(a.bo), lnpart, N, d,
-                                          r.drop(site_res, tgt, k.dropout), st, ln_sums[sub_at - 1]));
+                                          r.drop(site_res, tgt, k.dropout), on.st, ln_sums[sub_at - 1]));
     leaf(dsub, N, d, o, d, a.wo);
-    NMT_TRY(r.dgrad(dsub, N, d, a.wo, d, dO));
+    NMT_TRY(on.dgrad(dsub, N, d, a.wo, d, dO));
     NMT_TRY(launch_attention_bwd(qkv, 3 * d, qkv + d, 3 * d, qkv + 2 * d, 3 * d, o, d, dO, d, lse, dqkv, 3 * d, dqkv + d, 3 * d,
                                  dqkv + 2 * d, 3 * d, key_ids, k.pad_id, causal, Bt, H, dh, tgt ? maxT : maxS, tgt ? maxT : maxS,
-                                 tgt ? tab_tt : tab_ss, N, tgt ? &wl_tt : &wl_ss, st));
+                                 tgt ? tab_tt : tab_ss, N, tgt ? &wl_tt : &wl_ss, on.st));
     leaf(dqkv, N, 3 * d, x_in, d, a.wqkv, a.bqkv);
-    NMT_TRY(flush_leaves());  // (the self-attention sub-layer is a layer's last)
     GemmEpilogue res;
     res.add = dy;
-    return r.dgrad(dqkv, N, 3 * d, a.wqkv, d, dx, res);
+    if (on.st != st) {  // (a chain on the second stream: the group ends the layer's use of its temporaries)
+      NMT_TRY(on.dgrad(dqkv, N, 3 * d, a.wqkv, d, dx, res));
+      return flush_leaves(false);
+    }
+    NMT_TRY(flush_leaves(true));  // (the self-attention sub-layer is a layer's last)
+    return on.dgrad(dqkv, N, 3 * d, a.wqkv, d, dx, res);
   };
 
   // ---- output projection: logits = x E^T; the workspace holds d logits ----
@@ -836,7 +865,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
                       cuts >= 3 ? (int)cuts : 1));
 
   // ---- decoder, top to bottom ----
-  const bool beside = encoder_products_beside(c);
+  const bool beside = encoder_products_beside(c), self_beside = beside && k.dec_layers > 1;
   half_t* denc = r.ws<half_t>(p.dx_enc);
   const half_t* enc_out = k.enc_layers ? r.ws<half_t>(p.enc[k.enc_layers - 1].x2) : r.ws<half_t>(p.x0);
   for (int l = k.dec_layers - 1; l >= 0; --l) {
@@ -864,19 +893,32 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     NMT_TRY(r.dgrad(dq, Nt, d, P.cross.wq, d, dx, res));
     GemmEpilogue accum;
     accum.add = (l == k.dec_layers - 1) ? nullptr : denc;  // the encoder output feeds every decoder layer
-    if (beside) {
+    if (beside && !(self_beside && l == 0)) {
       NMT_TRY(fork());
       NMT_TRY(side.dgrad(dkv, Ns, 2 * d, P.cross.wkv, d, denc, accum));
-      if (l == 0) NMT_HIP_CHECK(hipEventRecord(c->ev_denc, sd));
-    } else {
+      if (l == (self_beside ? 1 : 0)) NMT_HIP_CHECK(hipEventRecord(c->ev_denc, sd));
+    } else {  // (the last one, which the encoder waits for, not behind the second layer's weight gradients)
+      if (self_beside) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_denc, 0));
       NMT_TRY(r.dgrad(dkv, Ns, 2 * d, P.cross.wkv, d, denc, accum));
     }
-    // masked self-attention
-    NMT_TRY(self_bwd(dx, Nt, true, x_in, r.ws<half_t>(W.qkv), r.ws<half_t>(W.o1), r.ws<float>(W.lse1), r.ws<half_t>(W.s1),
-                     r.ws<float>(W.st1), P.self, P.ln1, layer_site(li, kKindSelfRes), c->tgt_in, 1));
+    // masked self-attention.  The first layer's is the last of the decoder and nothing but the embeddings waits for it: its chain runs
+    // beside the encoder's, its two temporaries where the second layer's queries, keys and values were (that layer's
+    // attention was the last to read them).
+    if (self_beside && l == 0) {
+      NMT_TRY(fork());
+      dO = r.ws<half_t>(p.dec[1].qkv);
+      dy_place = dO + (int64_t)Nt * d;
+    }
+    NMT_TRY(self_bwd(self_beside && l == 0 ? side : r, dx, Nt, true, x_in, r.ws<half_t>(W.qkv), r.ws<half_t>(W.o1), r.ws<float>(W.lse1),
+                     r.ws<half_t>(W.s1), r.ws<float>(W.st1), P.self, P.ln1, layer_site(li, kKindSelfRes), c->tgt_in, 1));
+  }
+  if (self_beside) {
+    NMT_HIP_CHECK(hipEventRecord(c->ev_self, sd));
+    dO = r.ws<half_t>(p.dO);
+    dy_place = r.ws<half_t>(p.dy);
   }
   const half_t* dx_dec0 = dx;
-  if (beside) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_denc, 0));
+  if (beside && !self_beside) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_denc, 0));
 
   // ---- encoder ----
   next_dsub = r.ws<half_t>(p.dsub_enc);
@@ -887,13 +929,14 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     NMT_TRY(begin_layer());
     NMT_TRY(ffn_bwd(denc, Ns, false, r.ws<half_t>(W.x1), r.ws<half_t>(W.h), r.ws<half_t>(W.s2), r.ws<float>(W.st2), P.ffn, P.ln2,
                     layer_site(l, kKindFfnRes)));
-    NMT_TRY(self_bwd(denc, Ns, false, x_in, r.ws<half_t>(W.qkv), r.ws<half_t>(W.o), r.ws<float>(W.lse), r.ws<half_t>(W.s1),
+    NMT_TRY(self_bwd(r, denc, Ns, false, x_in, r.ws<half_t>(W.qkv), r.ws<half_t>(W.o), r.ws<float>(W.lse), r.ws<half_t>(W.s1),
                      r.ws<float>(W.st1), P.attn, P.ln1, layer_site(l, kKindSelfRes), c->src, 0));
   }
 
   // ---- the embeddings: both id streams add into the row gradients of the shared matrix (beside the second stream's last
   //      weight gradients, which touch other tensors), then join ----
   if (two_streams) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_embed, 0));
+  if (self_beside) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_self, 0));
   NMT_TRY(launch_embed_sum(denc, Ns, r.drop(kSiteEmbSrc, false, k.dropout), dx_dec0, Nt, r.drop(kSiteEmbTgt, true, k.dropout), r.g(c->embed), d,
                            r.ws<int32_t>(p.embscratch), st, c->gscale));
   if (two_streams) {
