@@ -139,13 +139,13 @@ __global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(const half_t* __re
 // then the result), which keeps the kernel at four wavefronts per SIMD.
 constexpr int kLnBwdMaxBlocks = 1024;
 
-template <int NCH, int ROWS>
-__global__ void __launch_bounds__(kThreads) res_ln_bwd_kernel(const half_t* __restrict__ dout, const half_t* __restrict__ sub,
+template <int NCH, int ROWS, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) res_ln_bwd_kernel(const half_t* __restrict__ dout, const half_t* __restrict__ sub,
                                                               const half_t* __restrict__ resid, const half_t* __restrict__ gamma,
                                                               const float* __restrict__ stats, half_t* __restrict__ dy_out,
                                                               half_t* __restrict__ dym_out, float* __restrict__ partial, int rows,
                                                               int d, DropDev drop) {
-  extern __shared__ __align__(16) float red[];  // [3][NCH][64 lanes][8] = [3][NCH*512]
+  extern __shared__ __align__(16) float red[];  // [WAVES][NCH][2][64 lanes][4]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int chunks = d >> 3;
   float sg[NCH][8], sb[NCH][8], sbias[NCH][8];
@@ -156,7 +156,7 @@ __global__ void __launch_bounds__(kThreads) res_ln_bwd_kernel(const half_t* __re
 #pragma unroll
     for (int e = 0; e < 8; ++e) sg[i][e] = sb[i][e] = sbias[i][e] = 0.f;
   }
-  for (int row0 = (blockIdx.x * kWavesPerBlock + wave) * ROWS; row0 < rows; row0 += gridDim.x * kWavesPerBlock * ROWS) {
+  for (int row0 = (blockIdx.x * WAVES + wave) * ROWS; row0 < rows; row0 += gridDim.x * WAVES * ROWS) {
     half8_t hs[ROWS][NCH], hr[ROWS][NCH], hg[ROWS][NCH];
     uint32_t bits[ROWS][NCH];
     DropRow key[ROWS] = {};
@@ -238,33 +238,38 @@ __global__ void __launch_bounds__(kThreads) res_ln_bwd_kernel(const half_t* __re
       }
     }
   }
-  // block reduction, wave after wave (fixed order), 16-byte LDS accesses
-  floatx4* red4 = reinterpret_cast<floatx4*>(red);
-  for (int w = 0; w < kWavesPerBlock; ++w) {
-    if (wave == w) {
+  // block reduction, one quantity after the other: every wavefront leaves its sums in LDS, then each thread adds four columns up over the
+  // wavefronts, in their order.  (All three at a time would take LDS that the other stream's products do not leave.)
+  floatx4 *red4 = reinterpret_cast<floatx4*>(red), *dst = reinterpret_cast<floatx4*>(partial + (size_t)blockIdx.x * 3 * d);
+  const int quads = d >> 2;
+  constexpr int SHARE = (NCH * 128 + 64 * WAVES - 1) / (64 * WAVES);  // groups of four columns to a thread
+  floatx4 total[3][SHARE];
 #pragma unroll
-      for (int i = 0; i < NCH; ++i) {
+  for (int q = 0; q < 3; ++q) {
+    if (q) __syncthreads();
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-          const float(&src)[8] = q == 0 ? sg[i] : (q == 1 ? sb[i] : sbias[i]);
-          const int idx = ((q * NCH + i) * kWave + lane) * 2;
-          floatx4 lo = {src[0], src[1], src[2], src[3]}, hi = {src[4], src[5], src[6], src[7]};
-          if (w) {
-            lo += red4[idx];
-            hi += red4[idx + 1];
-          }
-          red4[idx] = lo;
-          red4[idx + 1] = hi;
-        }
-      }
+    for (int i = 0; i < NCH; ++i) {
+      const float(&src)[8] = q == 0 ? sg[i] : (q == 1 ? sb[i] : sbias[i]);
+      floatx4* at = red4 + (wave * NCH + i) * 128 + lane;  // (the low and the high four columns of the lanes apart: every bank once)
+      at[0] = floatx4{src[0], src[1], src[2], src[3]};
+      at[64] = floatx4{src[4], src[5], src[6], src[7]};
     }
     __syncthreads();
-  }
-  floatx4* dst = reinterpret_cast<floatx4*>(partial + (size_t)blockIdx.x * 3 * d);
-  const int quads = d >> 2;
 #pragma unroll
-  for (int q = 0; q < 3; ++q)
-    for (int i = threadIdx.x; i < quads; i += kThreads) dst[q * quads + i] = red4[q * NCH * 128 + i];
+    for (int r = 0; r < SHARE; ++r) {
+      const int i = (int)threadIdx.x + r * 64 * WAVES;
+      const floatx4* at = red4 + (i >> 7) * 128 + (i & 1) * 64 + ((i >> 1) & 63);
+      if (i >= quads) continue;
+      total[q][r] = at[0];
+#pragma unroll
+      for (int w = 1; w < WAVES; ++w) total[q][r] += at[w * NCH * 128];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q)  // (stored at the end: a barrier waits for the stores before it)
+#pragma unroll
+    for (int r = 0; r < SHARE; ++r)
+      if (const int i = (int)threadIdx.x + r * 64 * WAVES; i < quads) dst[q * quads + i] = total[q][r];
 }
 
 // A layer's LayerNorm gradients are leaves like its weight gradients, so their two or three sums wait for the layer's
@@ -929,13 +934,19 @@ int64_t layernorm_bwd_scratch_floats(int d) { return (int64_t)kLnBwdMaxBlocks * 
 
 namespace {
 // One row per wavefront while that is at most one work-group per compute unit (half the code to fetch and a shorter chain: 380 rows x
-// 1024, whole update 4370 -> 4304 us; 260 x 64: 560 -> 540); from there on two, because every work-group leaves a partial row of
-// sums (3000 rows with one: 0.5 to 1 % slower).
-int ln_bwd_rows_per_wave(int rows) { return ceil_div(rows, kWavesPerBlock) <= device_info().cus ? 1 : 2; }
+// 1024, whole update 4370 -> 4304 us; 260 x 64: 560 -> 540), of four wavefronts and then, up to 512 columns, of eight: every work-group leaves a partial row of
+// sums (1400 x 256, two rows on four / one on eight: 6.5 / 5.6 us; 3100 x 512: 9.0 / 9.2).
+struct LnBwdForm { int rows_per_wave, waves; };
+LnBwdForm ln_bwd_form(int rows, int d) {
+  const int cus = device_info().cus;
+  if (ceil_div(rows, 4) <= cus) return {1, 4};
+  return ceil_div(rows, 8) <= cus && ln_nch(d) == 1 ? LnBwdForm{1, 8} : LnBwdForm{2, 4};
+}
 // a grid that is resident at once (3 or 4 work-groups per compute unit fit, by registers): no second, partly filled round
 int ln_bwd_blocks(int rows, int d) {
   const int resident = (ln_nch(d) >= 2 ? 3 : 4) * device_info().cus;
-  return min(min(kLnBwdMaxBlocks, resident), ceil_div(rows, kWavesPerBlock * ln_bwd_rows_per_wave(rows)));
+  const LnBwdForm f = ln_bwd_form(rows, d);
+  return min(min(kLnBwdMaxBlocks, resident), ceil_div(rows, f.waves * f.rows_per_wave));
 }
 }  // namespace
 
@@ -954,17 +965,19 @@ int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const h
               "layernorm_bwd: misaligned pointer");
   NMT_REQUIRE(!drop.thr || (drop.n_pos > 0 && dym), "layernorm_bwd: dropout needs the masked output and positions per sentence");
   const int nch = ln_nch(d);
-  const int per_wave = ln_bwd_rows_per_wave(rows), nblk = ln_bwd_blocks(rows, d);
-  const dim3 grid(nblk), block(kThreads);
-  const size_t smem = (size_t)3 * nch * 512 * sizeof(float);
-#define NMT_LN_BWD(N, R) hipLaunchKernelGGL((res_ln_bwd_kernel<N, R>), grid, block, smem, stream, dout, sub, resid, gamma, stats, dy, dym, partial, rows, d, drop)
-  switch (nch * 2 + per_wave - 1) {
-    case 2: NMT_LN_BWD(1, 1); break;
-    case 3: NMT_LN_BWD(1, 2); break;
-    case 4: NMT_LN_BWD(2, 1); break;
-    case 5: NMT_LN_BWD(2, 2); break;
-    case 8: NMT_LN_BWD(4, 1); break;
-    default: NMT_LN_BWD(4, 2); break;
+  const LnBwdForm form = ln_bwd_form(rows, d);
+  const int nblk = ln_bwd_blocks(rows, d);
+  const dim3 grid(nblk), block(kWave * form.waves);
+  const size_t smem = (size_t)form.waves * nch * 512 * sizeof(float);
+#define NMT_LN_BWD(N, R, W) hipLaunchKernelGGL((res_ln_bwd_kernel<N, R, W>), grid, block, smem, stream, dout, sub, resid, gamma, stats, dy, dym, partial, rows, d, drop)
+  switch (nch * 4 + (form.waves == 8 ? 2 : form.rows_per_wave - 1)) {
+    case 4: NMT_LN_BWD(1, 1, 4); break;
+    case 5: NMT_LN_BWD(1, 2, 4); break;
+    case 6: NMT_LN_BWD(1, 1, 8); break;
+    case 8: NMT_LN_BWD(2, 1, 4); break;
+    case 9: NMT_LN_BWD(2, 2, 4); break;
+    case 16: NMT_LN_BWD(4, 1, 4); break;
+    default: NMT_LN_BWD(4, 2, 4); break;
   }
 #undef NMT_LN_BWD
   NMT_LAUNCH_CHECK();
