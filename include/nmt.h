@@ -181,6 +181,12 @@ int nmt_check_overflow(nmt_ctx* ctx, float inv_scale, int32_t* d_flag, void* str
 int nmt_adam_step(nmt_ctx* ctx, float lr, float beta1, float beta2, float eps, int32_t t,
                   const int32_t* d_flag, void* stream);
 
+/* nmt_accumulate of an update's last pass, nmt_check_overflow and nmt_adam_step as one call, for callers that do nothing with
+ * acc32 in between (several GPUs: the sum over ranks lies there): every buffer and *d_flag end up with the same bits, in fewer
+ * passes over them. */
+int nmt_finish_update(nmt_ctx* ctx, int32_t first, float inv_scale, float lr, float beta1, float beta2, float eps, int32_t t,
+                      int32_t* d_flag, void* stream);
+
 /* Host helpers holding the scalar decision logic.
  * Dynamic loss scaling: overflow -> scale /= 2, clean = 0; otherwise clean += 1 and when clean
  * reaches `window` (2000 in the paper) scale *= 2, clean = 0.  Returns NMT_EINVAL if the scale

@@ -67,6 +67,7 @@ _SIGNATURES = {
     "nmt_debug_activation": (C.c_int, [_P, C.c_char_p, C.POINTER(_P), C.POINTER(_I64), C.POINTER(_I64)]),
     "nmt_check_overflow": (C.c_int, [_P, _F, _P, _P]),
     "nmt_adam_step": (C.c_int, [_P, _F, _F, _F, _F, _I32, _P, _P]),
+    "nmt_finish_update": (C.c_int, [_P, _I32, _F, _F, _F, _F, _F, _I32, _P, _P]),
     "nmt_scaler_update": (C.c_int, [C.POINTER(C.c_float), C.POINTER(_I32), _I32, _I32]),
     "nmt_lr_schedule": (C.c_double, [_I64, C.c_double, _I64]),
     "nmt_op_gemm": (C.c_int, [_P, _I32, _I32, _P, _I32, _I32, _P, _I32, _I32, _I32, _I32, _P, _I32, _DP, _P, _P, _F, _P]),
@@ -281,6 +282,10 @@ def nmt_check_overflow(ctx, inv_scale, flag, stream=None):
 
 def nmt_adam_step(ctx, lr, beta1, beta2, eps, t, flag, stream=None):
     _check(load().nmt_adam_step(ctx, lr, beta1, beta2, eps, t, _p(flag), _stream(stream)))
+
+
+def nmt_finish_update(ctx, first, inv_scale, lr, beta1, beta2, eps, t, flag, stream=None):
+    _check(load().nmt_finish_update(ctx, 1 if first else 0, inv_scale, lr, beta1, beta2, eps, t, _p(flag), _stream(stream)))
 
 
 def nmt_scaler_update(scale, clean, overflow, window=2000):

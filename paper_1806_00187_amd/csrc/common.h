@@ -311,7 +311,10 @@ int64_t embed_bwd_scratch_ints(int vocab, int rows_total, int d);
 int launch_embed_sort(const int32_t* ids_a, int rows_a, const int32_t* ids_b, int rows_b, int d, int vocab, int32_t* scratch, hipStream_t stream);
 int launch_embed_sum(const half_t* dx_a, int rows_a, const DropDev& drop_a, const half_t* dx_b, int rows_b, const DropDev& drop_b, half_t* gE,
                      int d, const int32_t* scratch, hipStream_t stream, float scale = 1.f);
-int launch_accumulate(const half_t* g16, float* acc, int64_t n, int first, hipStream_t stream, float mult = 1.f);
+// flag (cleared by the caller; null: no check) is raised if a sum is inf or NaN
+int launch_accumulate(const half_t* g16, float* acc, int64_t n, int first, hipStream_t stream, float mult = 1.f, int32_t* flag = nullptr);
+int launch_last_accumulate_and_adam(const half_t* g16, float mult, int first, float* master, float* m, float* v, float* acc, half_t* w16, int64_t n,
+                                    float lr, float b1, float b2, float eps, int t, int32_t* flag, hipStream_t stream, float grad_scale);
 // in_place: acc *= inv_scale in the same pass; otherwise acc is only read
 int launch_check_overflow(float* acc, int64_t n, float inv_scale, int32_t* flag, hipStream_t stream, bool in_place = true);
 // *loss_total (+)= *loss, *ntok_total (+)= *ntok (first: overwrite)

@@ -974,6 +974,15 @@ extern "C" int nmt_adam_step(nmt_ctx* ctx, float lr, float beta1, float beta2, f
   return launch_adam(ctx->master, ctx->m, ctx->v, ctx->acc, ctx->w16, ctx->P, lr, beta1, beta2, eps, t, d_flag,
                      static_cast<hipStream_t>(stream), ctx->inv_scale);
 }
+extern "C" int nmt_finish_update(nmt_ctx* ctx, int32_t first, float inv_scale, float lr, float beta1, float beta2, float eps, int32_t t,
+                                 int32_t* d_flag, void* stream) {
+  NMT_REQUIRE(ctx && ctx->g16 && ctx->acc && ctx->master && ctx->m && ctx->v && ctx->w16, "nmt_finish_update: g16 / acc32 / optimizer buffers not bound");
+  NMT_REQUIRE(d_flag, "nmt_finish_update: null flag");
+  NMT_REQUIRE(isfinite(inv_scale) && inv_scale > 0.f, "nmt_finish_update: inv_scale must be positive and finite");
+  ctx->inv_scale = inv_scale;
+  return launch_last_accumulate_and_adam(ctx->g16, 1.f / ctx->gscale, first, ctx->master, ctx->m, ctx->v, ctx->acc, ctx->w16, ctx->P, lr, beta1, beta2,
+                                         eps, t, d_flag, static_cast<hipStream_t>(stream), inv_scale);
+}
 
 extern "C" int nmt_gemm_timing(double* ms, int64_t* products, double* flops) { return gemm_timing_read(ms, products, flops); }
 

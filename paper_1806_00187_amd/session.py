@@ -186,6 +186,10 @@ class Session:
     def adam_step(self, lr, t, betas=(0.9, 0.98), eps=1e-8):
         nmt.nmt_adam_step(self.ctx, lr, betas[0], betas[1], eps, t, self.flag)
 
+    def finish_update(self, first, inv_scale, lr, t, betas=(0.9, 0.98), eps=1e-8):
+        """accumulate(first), check_overflow and adam_step in one call"""
+        nmt.nmt_finish_update(self.ctx, first, inv_scale, lr, betas[0], betas[1], eps, t, self.flag)
+
     # ---- one weight update from k micro-batches ----
     def update(self, dbatches, loss_scale, lr, t, step=None, betas=(0.9, 0.98), eps=1e-8, n_tok=None):
         """dbatches: device sub-batches (sub-batch j gets micro index j) or groups made by Session.group.
@@ -198,7 +202,8 @@ class Session:
             for j, db in enumerate(dbatches):
                 self.forward_loss(db, loss_scale, step, j)
                 self.backward()
-                self.accumulate(j == 0)
+                if j < len(dbatches) - 1:
+                    self.accumulate(j == 0)        # (the last one: finish_update)
                 nmt.nmt_accumulate_loss(self.ctx, j == 0, self.loss_tot, self.ntok_tot)
         else:
             if not self._streams_chosen:
@@ -206,8 +211,12 @@ class Session:
             self._update_pipes(dbatches, loss_scale, step, main)
         if n_tok is None:
             n_tok = int(self.ntok_tot.item())
-        self.check_overflow(1.0 / (loss_scale * max(n_tok, 1)))
-        self.adam_step(lr, t, betas, eps)
+        inv_scale = 1.0 / (loss_scale * max(n_tok, 1))
+        if self.n_pipes == 1 and len(dbatches):
+            self.finish_update(len(dbatches) == 1, inv_scale, lr, t, betas, eps)
+        else:
+            self.check_overflow(inv_scale)
+            self.adam_step(lr, t, betas, eps)
         report = self._report.cpu()
         return float(report[2:3].view(torch.float32).item()), n_tok, int(report[0].item())
 

@@ -344,6 +344,53 @@ def test_poisoned_gradient_element_sets_the_flag():
     sess.close()
 
 
+def _param_layout(model):
+    ctx = A.nmt_create(**model, pad_id=1, ln_eps=1e-5, label_smoothing=0.1, max_sentences=1, max_len=16)
+    out = {name: (off, rows, cols) for name, off, rows, cols in (A.nmt_param_info(ctx, i) for i in range(A.nmt_param_tensors(ctx)))}
+    A.nmt_destroy(ctx)
+    return out
+
+
+@pytest.mark.parametrize("first", [True, False])
+@pytest.mark.parametrize("model,sentences,poison", [("tiny", 8, None), ("tiny", 520, None), ("tiny", 8, (0, float("inf"))), ("tiny", 520, (-1, float("nan"))),
+                                                    ("wide", 8, None), ("wide", 8, (-5, float("-inf")))])
+def test_finish_update_equals_its_three_calls(model, sentences, poison, first):
+    """Accumulation, overflow check and Adam as one call: the same bits in every buffer, also where the update is skipped, where the
+    pass scaled its gradient (more than 8192 target positions), and with state streamed past the caches (more than 16 million parameters)."""
+    model = I.MODELS["tiny"] if model == "tiny" else dict(I.MODELS["tiny"], d_model=512, d_ff=2048, vocab=32768)
+    weights = I.init_weights(seed=0, **model) if model["d_model"] == 64 else None
+    if weights is None:
+        rng = np.random.default_rng(1)
+        weights = {n: (rng.standard_normal(r * c, dtype=np.float32) * 0.05).astype(np.float16)
+                   for n, (_, r, c) in _param_layout(model).items()}
+    ends = []
+    for fused in (False, True):
+        sess = Session(model, weights, max_sentences=520)
+        g = torch.Generator(device="cuda").manual_seed(5)
+        ids = torch.randint(4, 1000, (sentences, 16), generator=g, device="cuda", dtype=torch.int32)
+        sess.forward_loss({"src": ids, "tgt_in": ids, "tgt_out": ids}, 16.0, 1, 0)
+        sess.backward()
+        assert sess.grad_scale() == (1.0 if sentences == 8 else 0.5)
+        for x, scale in ((sess.g16, 4.0), (sess.acc, 30.0), (sess.m, 0.1), (sess.v, 0.1)):
+            x.copy_(torch.randn(x.shape, generator=g, device="cuda") * scale)
+        sess.v.abs_()
+        sess.g16[5:9] = torch.tensor([-0.0, 6e-8, -65504.0, 0.0], dtype=torch.float16)
+        if poison:
+            sess.g16[poison[0]] = poison[1]
+        sess.flag.fill_(7)
+        if fused:
+            sess.finish_update(first, 1.0 / 48.0, 5e-4, 3)
+        else:
+            sess.accumulate(first)
+            sess.check_overflow(1.0 / 48.0)
+            sess.adam_step(5e-4, 3)
+        ends.append([t.clone() for t in (sess.flag, sess.acc.view(torch.int32), sess.master, sess.m, sess.v, sess.w16, sess.g16.view(torch.int16))])
+        sess.close()
+    assert int(ends[0][0].item()) == (1 if poison else 0)
+    for a, b in zip(*ends):
+        assert torch.equal(a, b)
+
+
 def test_call_order_and_workspace_errors():
     model = I.MODELS["tiny"]
     sess = Session(model, I.init_weights(seed=0, **model), max_sentences=8)

@@ -104,6 +104,7 @@ def test_calls_out_of_order_fail_cleanly():
     assert lib.nmt_backward(ctx, None) == A.binding.NMT_ESTATE
     assert lib.nmt_accumulate(ctx, 1, None) == A.binding.NMT_EINVAL          # nothing bound
     assert b"not bound" in lib.nmt_last_error()
+    assert lib.nmt_finish_update(ctx, 1, 1.0, 1e-3, 0.9, 0.98, 1e-8, 1, None, None) == A.binding.NMT_EINVAL
     A.nmt_destroy(ctx)
 
 
