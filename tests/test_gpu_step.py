@@ -270,7 +270,7 @@ def test_layernorm_gradients_in_either_launch_are_the_same_bits(B, S, T):
         for share in (1, 16):
             A.nmt_tuning("gemm_share", share)
             sess.g16.fill_(float("nan"))
-            sess.forward_loss(db, 8.0, 1, 0)
+            sess.forward_loss(db, 64.0, 1, 0)
             sess.backward()
             got.append(sess.g16.clone())
     finally:
@@ -389,6 +389,49 @@ def test_finish_update_equals_its_three_calls(model, sentences, poison, first):
     assert int(ends[0][0].item()) == (1 if poison else 0)
     for a, b in zip(*ends):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("d,heads,ff,rows,dropout", [(64, 4, 4096, (3, 5), 0.1), (512, 8, 2048, (7, 9), 0.1), (512, 8, 4104, (13, 31), 0.0),
+                                                    (1024, 16, 4096, (16, 32), 0.3), (1040, 65, 2048, (11, 23), 0.1), (2048, 16, 4096, (5, 61), 0.1)])
+def test_products_cut_before_a_layernorm(d, heads, ff, rows, dropout):
+    """Passes of up to 1024 rows cut long contractions before a LayerNorm into pieces that it adds up; a caller with several
+    passes in flight (gemm_share) gets them whole.  Both are the same sums in another order: loss and gradients agree as far as
+    fp16 roundings that fall otherwise spread (this pass against the 64-bit oracle with the same gates: up to 5.7e-3 of a gradient on
+    130 tokens; twice that allowed here).  The feed-forward biases hold every ReLU gate open (8 against a spread of 1): a gate at zero that
+    falls the other way, one in 4000 of them, would change a gradient by sqrt(2 / 4000) = 2e-2 and hide what is looked for.  (Their
+    share of the result, the same in every row, is taken out by the second biases: with it all keys are alike, and the gradients of
+    queries and keys are differences of roundings.)"""
+    model = dict(enc_layers=2, dec_layers=2, d_model=d, n_heads=heads, d_ff=ff, vocab=1000, dropout=dropout)
+    rng = np.random.default_rng(d + rows[0])
+    weights = {n: (rng.standard_normal(r * c, dtype=np.float32) * (c ** -0.5 if r > 1 else 0.02) + (n.endswith(".g") and r == 1) + 8.0 * n.endswith("ffn.b1")).astype(np.float16)
+               for n, (_, r, c) in _param_layout(model).items()}
+    for n, (_, r, c) in _param_layout(model).items():
+        if n.endswith("ffn.w2"):
+            weights[n[:-2] + "b2"] = (-8.0 * weights[n].reshape(r, c).astype(np.float64).sum(1)).astype(np.float16)
+    B, T = rows
+    src, tgt = (rng.integers(4, 1000, size=(B, t)).astype(np.int32) for t in (T, max(1, T - 2)))
+    src[0, T // 2 + 1:] = 1
+    tgt[-1, len(tgt[0]) // 2 + 1:] = 1
+    ends = []
+    try:
+        for share in (2, 1):
+            A.nmt_tuning("gemm_share", share)
+            sess = Session(model, weights, max_sentences=B, optimizer=False)
+            db = sess.to_device({"src": src, "tgt_in": tgt, "tgt_out": tgt})
+            for _ in range(2):                  # (the second pass has a second stream to use forward)
+                sess.forward_loss(db, 64.0, 1, 0)
+                sess.backward()
+            ends.append((float(sess.loss_sum.item()), {n: sess.tensor(sess.g16.float().cpu().numpy(), n).astype(np.float64) for n in sess.layout}))
+            sess.close()
+    finally:
+        A.nmt_tuning("gemm_share", 1)
+    (whole_loss, whole), (cut_loss, cut) = ends
+    assert abs(cut_loss - whole_loss) <= 1e-3 * abs(whole_loss)
+    assert any((whole[n] != cut[n]).any() for n in whole), "nothing was cut"
+    for n in whole:
+        assert np.isfinite(cut[n]).all()
+        scale = np.linalg.norm(whole[n]) + 1e-3 * whole[n].size ** 0.5   # (a gradient of values near fp16's smallest has no relative error)
+        assert np.linalg.norm(cut[n] - whole[n]) <= 1e-2 * scale, n
 
 
 def test_call_order_and_workspace_errors():
