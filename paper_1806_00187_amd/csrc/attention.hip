@@ -5,8 +5,8 @@
 //
 // Sentences here are short (tens of positions), so the unit of work is small: ONE WAVEFRONT per
 // (sentence, head, 32-row tile), and in all kernels but the backward one by key tiles no work-group barrier anywhere.  Operands whose contraction index is contiguous in memory (Q, K, V, dO rows
-// against the head dimension) are loaded from global memory straight into MFMA operand registers,
-// 16 bytes per lane.  An operand that is contracted over its row index (V in P V, K in dS K, Q and
+// against the head dimension) are loaded as whole rows and turn into MFMA operand registers in LDS (forward, and backward by key tiles)
+// or go straight there, 16 bytes per lane.  An operand that is contracted over its row index (V in P V, K in dS K, Q and
 // dO in dS^T Q and P^T dO) passes through a wavefront-private 32-row LDS tile and comes back through
 // the transposing LDS read.
 //
@@ -23,6 +23,7 @@
 
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 #include <unordered_map>
 
 namespace {
@@ -112,7 +113,7 @@ __device__ __forceinline__ Item work_item(const AttnArgs& a, int bx, int by, int
   const int hg = (a.H + wpb - 1) / wpb;
   const int idx = bx / hg;
   Item it;
-  it.h = (bx % hg) * wpb + (threadIdx.x >> 6);
+  it.h = (bx % hg) * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // (known to be the wavefront's: addresses stay scalar)
   it.tile = by;
   it.live = it.h < a.H;
   if (LIST == 1 && a.wl_qsent) {
@@ -130,6 +131,13 @@ __device__ __forceinline__ Item work_item(const AttnArgs& a, int bx, int by, int
   return it;
 }
 
+// Orders the wavefront's LDS accesses: what other lanes wrote before is visible after (LDS
+// instructions of one wavefront execute in order; this keeps the compiler from reordering them).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 // 32 rows of a [*, DH] head slice as MFMA operand registers: lane l gets row row0 + l%32, columns
 // 16*s + 8*(l/32) .. +7 for every k-step s; rows >= row_end are zero.
 template <int DH>
@@ -139,6 +147,42 @@ __device__ __forceinline__ void load_rows(const half_t* __restrict__ base, int l
 #pragma unroll
   for (int s = 0; s < DH / 16; ++s) f[s] = row < row_end ? ld_half8(p + s * 16) : zero_half8();
 }
+// The same rows as whole 2*DH-byte rows, 64 consecutive 16-byte pieces to an instruction (piece s*64 + lane): the layout for
+// rows on their way to LDS.  (An instruction of load_rows takes 32 bytes of each of 32 rows, neighbouring lanes a row apart.)  Lanes past the
+// end ask for nothing: asking for the last row again, without branches, made the kernels 10 to 25 % slower.
+template <int DH>
+__device__ __forceinline__ void load_whole(const half_t* __restrict__ base, int ld, int row0, int row_end, int lane, half8_t (&f)[DH / 16]) {
+  constexpr int CH = DH / 8;
+#pragma unroll
+  for (int s = 0; s < DH / 16; ++s) {
+    const int idx = s * 64 + lane, row = row0 + idx / CH;
+    f[s] = row < row_end ? ld_half8(base + (size_t)row * ld + 8 * (idx % CH)) : zero_half8();
+  }
+}
+template <int DH>
+__device__ __forceinline__ void put_whole(half_t* tile, int lane, const half8_t (&f)[DH / 16]) {
+  constexpr int CH = DH / 8;
+#pragma unroll
+  for (int s = 0; s < DH / 16; ++s) {
+    const int idx = s * 64 + lane;
+    st_half8(tile + idx / CH * (DH + 8) + idx % CH * 8, f[s]);
+  }
+}
+// MFMA operand registers (load_rows' layout) from a row-major LDS tile
+template <int DH>
+__device__ __forceinline__ void get_rows(const half_t* tile, int lane, half8_t (&f)[DH / 16]) {
+  const half_t* p = tile + (lane & 31) * (DH + 8) + 8 * (lane >> 5);
+#pragma unroll
+  for (int s = 0; s < DH / 16; ++s) f[s] = ld_half8(p + s * 16);
+}
+// Whole rows to operand registers by way of the wavefront's LDS tile.
+template <int DH>
+__device__ __forceinline__ void turn_rows(half_t* tile, int lane, half8_t (&f)[DH / 16]) {
+  wave_sync();  // earlier reads of the tile are done
+  put_whole<DH>(tile, lane, f);
+  wave_sync();
+  get_rows<DH>(tile, lane, f);
+}
 // The same registers written to the wavefront's LDS tile in row-major order (pitch DH+8 halfs).
 template <int DH>
 __device__ __forceinline__ void put_rows(half_t* tile, int lane, const half8_t (&f)[DH / 16]) {
@@ -146,17 +190,14 @@ __device__ __forceinline__ void put_rows(half_t* tile, int lane, const half8_t (
 #pragma unroll
   for (int s = 0; s < DH / 16; ++s) st_half8(p + s * 16, f[s]);
 }
-// Orders the wavefront's LDS accesses: what other lanes wrote before is visible after (LDS
-// instructions of one wavefront execute in order; this keeps the compiler from reordering them).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
+// 2^x as the instruction gives it: the library's form adds five instructions for results below 2^-126, which no half and no sum of
+// probabilities next to the row's largest, 1, can tell from zero.
+__device__ __forceinline__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
 // Bit k of the result: key row0 + k (k < 32) is hidden from every query (padding or past the end).
 __device__ __forceinline__ uint32_t hidden_keys(const AttnArgs& a, const Sent& se, int row0, int lane) {
   const int key = row0 + (lane & 31);
-  const bool hid = key >= se.Tk || (a.key_ids && a.key_ids[se.k0 + key] == a.pad_id);
+  bool hid = key >= se.Tk;
+  if (a.key_ids && row0 < se.Tk) hid |= a.key_ids[se.k0 + min(key, se.Tk - 1)] == a.pad_id;
   return (uint32_t)__ballot(hid);
 }
 
@@ -208,55 +249,67 @@ __device__ __forceinline__ void attn_fwd_item(const AttnArgs& a, int bx, int by,
   const int q = q0 + (lane & 31);
   const bool qvalid = q < se.Tq;
   half8_t qf[KS];
-  load_rows<DH>(a.Q + (size_t)se.q0 * a.ldq + h * DH, a.ldq, q0, se.Tq, lane, qf);
+  load_whole<DH>(a.Q + (size_t)se.q0 * a.ldq + h * DH, a.ldq, q0, se.Tq, lane, qf);
 
   const float sc = rsqrtf((float)DH) * kLog2e;
   float m = -1e30f, l = 0.f;
   floatx16 oacc[DT];
-#pragma unroll
-  for (int t = 0; t < DT; ++t) oacc[t] = zero16();
   int nkt = (se.Tk + 31) >> 5;
   if (a.causal) nkt = min(nkt, (q0 + 31) / 32 + 1);
-  for (int kt = 0; kt < nkt; ++kt) {
+  // FIRST: nothing to scale down yet, and the products start from zero (most sentences have no other tile)
+  auto key_tile = [&](int kt, auto is_first) {
+    constexpr bool FIRST = decltype(is_first)::value;
     half8_t kf[KS], vf[KS];
-    load_rows<DH>(Kb, a.ldk, kt * 32, se.Tk, lane, kf);
-    load_rows<DH>(Vb, a.ldv, kt * 32, se.Tk, lane, vf);
-    const uint32_t hm = hidden_keys(a, se, kt * 32, lane);
-    wave_sync();  // the previous tile's reads are done
-    put_rows<DH>(Vs, lane, vf);
+    load_whole<DH>(Kb, a.ldk, kt * 32, se.Tk, lane, kf);
+    load_whole<DH>(Vb, a.ldv, kt * 32, se.Tk, lane, vf);
+    // the lane's hidden keys, bit 8 * (r / 4) + r % 4 for its score r: padding, past the end, or (causal) behind its query
+    uint32_t hm = hidden_keys(a, se, kt * 32, lane);
+    if (a.causal && kt * 32 + 31 > q0) {
+      const int last = q - kt * 32;  // (not below 0: later key tiles are left out)
+      hm |= last < 31 ? ~0u << (last + 1) : 0u;
+    }
+    hm >>= 4 * g;
+    if constexpr (FIRST) turn_rows<DH>(Vs, lane, qf);
+    turn_rows<DH>(Vs, lane, kf);
+    wave_sync();  // the keys' reads are done
+    put_whole<DH>(Vs, lane, vf);
     floatx16 s = zero16();
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) s = MFMA(kf[ks], qf[ks], s);
     float tmax = -1e30f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int kl = 8 * (r >> 2) + 4 * g + (r & 3);
-      const bool hid = ((hm >> kl) & 1u) || (a.causal && kt * 32 + kl > q);
-      s[r] = hid ? -INFINITY : s[r] * sc;
+      s[r] = (hm & (1u << (8 * (r >> 2) + (r & 3)))) ? -INFINITY : s[r] * sc;
       tmax = fmaxf(tmax, s[r]);
     }
     tmax = half_max(tmax);
     const float m_new = fmaxf(m, tmax);
-    const float alpha = exp2f(m - m_new);
+    const float alpha = exp2_raw(m - m_new);
     m = m_new;
     float psum = 0.f;
     half8_t pf[2];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const float p = exp2f(s[r] - m_new);
+      const float p = exp2_raw(s[r] - m_new);
       psum += p;
       pf[r >> 3][r & 7] = (half_t)p;
     }
-    l = l * alpha + psum;
+    l = FIRST ? psum : l * alpha + psum;
     wave_sync();  // the V tile is in LDS
 #pragma unroll
     for (int t = 0; t < DT; ++t) {
+      if constexpr (FIRST) {
+        oacc[t] = zero16();
+      } else {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[t][r] *= alpha;
+        for (int r = 0; r < 16; ++r) oacc[t][r] *= alpha;
+      }
 #pragma unroll
       for (int s2 = 0; s2 < 2; ++s2) oacc[t] = MFMA(tr_frag<DH>(Vs, PR, 16 * s2 + 4 * g, t, lane), pf[s2], oacc[t]);
     }
-  }
+  };
+  key_tile(0, std::true_type{});
+  for (int kt = 1; kt < nkt; ++kt) key_tile(kt, std::false_type{});
   l = half_sum(l);
   store_rows<DH>(Vs, oacc, 1.f / l, a.Out + (size_t)se.q0 * a.ldo + h * DH, a.ldo, q0, se.Tq, lane);
   if (!qvalid) return;
@@ -265,6 +318,9 @@ __device__ __forceinline__ void attn_fwd_item(const AttnArgs& a, int bx, int by,
 // Persistent: the launch fills the chip once and every work-group walks through the work items with the
 // grid's stride.  A wavefront that ended after each item would first wait for its stores to land; here the
 // next item's loads go out right behind them.
+// What bounds it is the way of the rows from memory.  All three come as whole rows and turn into operands in LDS; the first key tile has no
+// sums to scale down and no products to start from; per call in whole updates, before / now: 3100 positions x 512 10.9 / 9.0 us, fourteen sentences of up to
+// 256 15.4 / 12.9, 13000 x 512 23.7 / 20.5, 17700 x 1024 42.7 / 36.6.  (Four wavefronts per SIMD, 128 registers: 57 for the last.)
 template <int DH>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 64 ? 3 : 1, DH <= 64 ? 3 : 1)))
 attn_fwd_kernel(const AttnArgs a) {
@@ -350,7 +406,7 @@ __global__ void __launch_bounds__(kThreads) attn_bwd_dkv_kernel(const AttnArgs a
         const int r = 4 * rq + e;
         const int qq = qt * 32 + 8 * rq + 4 * g + e;
         const bool hid = khid || qq >= se.Tq || (a.causal && key > qq);
-        const float p = hid ? 0.f : exp2f(s[r] * sc - l4[e]);
+        const float p = hid ? 0.f : exp2_raw(s[r] * sc - l4[e]);
         pf[r >> 3][r & 7] = (half_t)p;
         dsf[r >> 3][r & 7] = (half_t)(p * (dp[r] - d4[e]) * scale);
       }
@@ -423,7 +479,7 @@ __global__ void __launch_bounds__(kThreads) attn_bwd_dq_kernel(const AttnArgs a)
     for (int r = 0; r < 16; ++r) {
       const int kl = 8 * (r >> 2) + 4 * g + (r & 3);
       const bool hid = ((hm >> kl) & 1u) || (a.causal && kt * 32 + kl > q);
-      const float p = hid ? 0.f : exp2f(s[r] * sc - lse_q);
+      const float p = hid ? 0.f : exp2_raw(s[r] * sc - lse_q);
       dsf[r >> 3][r & 7] = (half_t)(p * (dp[r] - Dq) * scale);
     }
     wave_sync();  // the K tile is in LDS
@@ -540,7 +596,7 @@ __device__ __forceinline__ void attn_bwd_fused_item(const AttnArgs& a, int bx, u
               const int r = 4 * rq + e;
               const int qq = qt * 32 + 8 * rq + 4 * g + e;
               const bool hid = khid || qq >= se.Tq || (a.causal && key > qq);
-              const float p = hid ? 0.f : exp2f(s[r] * sc - l4[e]);
+              const float p = hid ? 0.f : exp2_raw(s[r] * sc - l4[e]);
               pf[r >> 3][r & 7] = (half_t)p;
               ds4[e] = (half_t)(p * (dp[r] - d4[e]) * scale);
               dsf[r >> 3][r & 7] = ds4[e];
@@ -594,17 +650,19 @@ __global__ void __launch_bounds__(kThreads) attn_bwd_fused_kernel(const AttnArgs
 // had to be fetched) and the number of launches.  Per pass of 18 attentions, with the instances per length it replaces: fourteen
 // sentences of up to 256 positions, 8 heads: 930 -> 370 us; 130 of 16 to 40: 405 -> 268; 53000 positions, 16 heads: 5.3 -> 4.9 ms
 // (beside the weight gradients).  What bounds it at these lengths is trips to memory: everything a wavefront needs is asked for at once (K and V
-// used to follow Q, dO and O): per call 14.9 -> 14.0 us for 148 sentences of 24, 20.6 -> 20.1 for fourteen of up to 256, 40.7 -> 37.7 for 480 of about 27.
+// used to follow Q, dO and O): per call 14.9 -> 14.0 us for 148 sentences of 24, 20.6 -> 20.1 for fourteen of up to 256, 40.7 -> 37.7 for 480 of about 27; and as whole rows, which turn into operands in LDS (on average in whole updates,
+// beside the weight gradients: 3100 positions x 512 13.9 -> 13.4 us, fourteen sentences of up to 256 20.2 -> 18.3, 13000 x 512 43.9 -> 41.0, 17700 x 1024 82.5 -> 78.3).
 // ------------------------------------------------------------------------------------------------
 constexpr int kBwdTiles = 8;  // longest sentence, in tiles
 template <int DH>
 constexpr int block_wave_lds() {
+  static_assert(32 * (DH + 8) <= 2 * 32 * kDsPitch, "a tile of rows passes through the two dS tiles' place");
   return 3 * 32 * (DH + 8) * 2 + 2 * 32 * kDsPitch * 2 + 2 * 32 * 4;  // Q, dO and K tiles, two dS tiles, lse and D
 }
 template <int DH, int W>
 __device__ __forceinline__ void attn_bwd_tiles_item(const AttnArgs& a, int nt, int pair, int pairs, unsigned char* smem) {
   constexpr int DHP = DH < 32 ? 32 : DH, KS = DH / 16, DT = DHP / 32, PR = DH + 8, LDS = block_wave_lds<DH>();
-  const int lane = threadIdx.x & 63, g = lane >> 5, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, g = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int group = wave / nt, j = wave - group * nt, at = pair + group;
   // the group's (sentence, head); a group past the end, or of another class where there is no list, only keeps the barriers
   bool live = group < W / nt && at < pairs;
@@ -634,23 +692,27 @@ __device__ __forceinline__ void attn_bwd_tiles_item(const AttnArgs& a, int nt, i
   // past a sentence's end, and a tile or sentence that does not exist, ask for nothing and are zeros).
   const int q = j * 32 + (lane & 31), key = q;
   half8_t qf[KS], dof[KS], of[KS], kf[KS], vf[KS];
-  load_rows<DH>(a.Q + (size_t)se.q0 * a.ldq + h * DH, a.ldq, j * 32, se.Tq, lane, qf);
-  load_rows<DH>(a.dO + (size_t)se.q0 * a.lddo + h * DH, a.lddo, j * 32, se.Tq, lane, dof);
-  load_rows<DH>(a.O + (size_t)se.q0 * a.ldo + h * DH, a.ldo, j * 32, se.Tq, lane, of);
+  load_whole<DH>(a.Q + (size_t)se.q0 * a.ldq + h * DH, a.ldq, j * 32, se.Tq, lane, qf);
+  load_whole<DH>(a.dO + (size_t)se.q0 * a.lddo + h * DH, a.lddo, j * 32, se.Tq, lane, dof);
+  load_whole<DH>(a.O + (size_t)se.q0 * a.ldo + h * DH, a.ldo, j * 32, se.Tq, lane, of);
   const float lse_q = q < se.Tq ? a.lse[(size_t)h * a.Nq + se.q0 + q] * kLog2e : 0.f;
-  load_rows<DH>(a.K + (size_t)se.k0 * a.ldk + h * DH, a.ldk, j * 32, se.Tk, lane, kf);
-  load_rows<DH>(a.V + (size_t)se.k0 * a.ldv + h * DH, a.ldv, j * 32, se.Tk, lane, vf);
-  const bool khid = key >= se.Tk || (a.key_ids && a.key_ids[se.k0 + key] == a.pad_id);
+  load_whole<DH>(a.K + (size_t)se.k0 * a.ldk + h * DH, a.ldk, j * 32, se.Tk, lane, kf);
+  load_whole<DH>(a.V + (size_t)se.k0 * a.ldv + h * DH, a.ldv, j * 32, se.Tk, lane, vf);
+  bool khid = key >= se.Tk;
+  if (a.key_ids && j * 32 < se.Tk) khid |= a.key_ids[se.k0 + min(key, se.Tk - 1)] == a.pad_id;
   wave_sync();  // (what this wavefront staged for its last item has been stored)
+  half_t* const my_ds = ds_tile(j, 0);
   if (j < nqt) {
+    put_whole<DH>(q_tile(j), lane, qf);
+    put_whole<DH>(do_tile(j), lane, dof);
+    turn_rows<DH>(my_ds, lane, of);  // (the dS tiles' place holds a tile of rows)
+    get_rows<DH>(do_tile(j), lane, dof);
     float Dq = 0.f;
 #pragma unroll
     for (int s = 0; s < KS; ++s)
 #pragma unroll
       for (int e = 0; e < 8; ++e) Dq += (float)dof[s][e] * (float)of[s][e];
     Dq = half_sum(Dq);
-    put_rows<DH>(q_tile(j), lane, qf);
-    put_rows<DH>(do_tile(j), lane, dof);
     if (g == 0) {
       row_stats(j)[lane] = lse_q;
       row_stats(j)[32 + lane] = Dq;
@@ -659,7 +721,10 @@ __device__ __forceinline__ void attn_bwd_tiles_item(const AttnArgs& a, int nt, i
   floatx16 dKt[DT], dVt[DT];
 #pragma unroll
   for (int t = 0; t < DT; ++t) dKt[t] = dVt[t] = zero16();
-  if (j < nkt) put_rows<DH>(my_k, lane, kf);
+  if (j < nkt) {
+    turn_rows<DH>(my_k, lane, kf);
+    turn_rows<DH>(my_ds, lane, vf);
+  }
   const float scale = rsqrtf((float)DH), sc = scale * kLog2e;
   __syncthreads();  // Q, dO, K tiles and the row statistics of all groups are in LDS
 #pragma unroll 1
@@ -689,7 +754,7 @@ __device__ __forceinline__ void attn_bwd_tiles_item(const AttnArgs& a, int nt, i
             const int r = 4 * rq + e;
             const int qq = qt * 32 + 8 * rq + 4 * g + e;
             const bool hid = khid || qq >= se.Tq || (a.causal && key > qq);
-            const float p = hid ? 0.f : exp2f(s[r] * sc - l4[e]);
+            const float p = hid ? 0.f : exp2_raw(s[r] * sc - l4[e]);
             pf[r >> 3][r & 7] = (half_t)p;
             ds4[e] = (half_t)(p * (dp[r] - d4[e]) * scale);
             dsf[r >> 3][r & 7] = ds4[e];
