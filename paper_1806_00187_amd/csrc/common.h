@@ -197,8 +197,9 @@ struct CutProduct {
   const half_t *bias = nullptr, *add = nullptr;
 };
 constexpr int kMaxCuts = 4, kCutRows = 1024;
-// Pieces that C[M, N] = A[M, K] B is cheapest in when a LayerNorm over its rows adds them up (1: whole).
-int gemm_cuts(int M, int N, int K);
+// Pieces that C[M, N] = A[M, K] B is cheapest in when a LayerNorm over its rows adds them up (1: whole) and that fit
+// `floats`.
+int gemm_cuts(int M, int N, int K, int64_t floats);
 int launch_gemm_cut(const half_t* A, int lda, const half_t* B, bool b_t, int ldb, int M, int N, int K, int cuts, float* partial,
                     int64_t partial_floats, hipStream_t stream);
 

@@ -1569,14 +1569,14 @@ int launch_gemm(const half_t* A, bool a_t, int lda, const half_t* B, bool b_t, i
 // Whole update of 380 positions x 1024 wide, against the commit before: 4050 -> 3800 us.  The pieces are the more exact sums: relative error
 // of the fp16 value against 64 bits, whole / 2 / 4 pieces / of the rounding alone, 380 x 1024 x 4096 2.079898e-4 / 2.079897e-4 / 2.079896e-4 / 2.079895e-4,
 // 700 x 2048 x 4096 2.077070e-4 / 2.077067e-4 / 2.077066e-4 / 2.077065e-4.
-int gemm_cuts(int M, int N, int K) {
+int gemm_cuts(int M, int N, int K, int64_t floats) {
   if (M > kCutRows || tuning().gemm_share > 1 || tuning().gemm_tile) return 1;
   const int cus = device_info().cus;
   double best_us;
   choose_small_tile(M, N, K, cus, best_us);
   int best = 1;
   best_us -= 1.0;
-  for (int z = 2; z <= kMaxCuts; ++z) {
+  for (int z = 2; z <= kMaxCuts && (int64_t)z * M * N <= floats; ++z) {
     const int chunk = (int)round_up(ceil_div(K, z), 64);
     if (ceil_div(K, chunk) != z) continue;
     double us;

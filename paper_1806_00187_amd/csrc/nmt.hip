@@ -112,7 +112,7 @@ struct Plan {
   int64_t x0, y0, logits, rowloss, rowlse, targets;
   std::vector<EncW> enc;
   std::vector<DecW> dec;
-  int64_t cut, cut_floats, dx_dec, dx_enc, dy, dsub_dec, dsub_enc, dO, dqkv[2], dh[2], dq[2], dkv[2], lnpart[2][3], embscratch, wgpart, wgpart_floats, wg_most;
+  int64_t dx_dec, dx_enc, dy, dsub_dec, dsub_enc, dO, dqkv[2], dh[2], dq[2], dkv[2], lnpart[2][3], embscratch, wgpart, wgpart_floats, wg_most;
   int64_t total;
 };
 
@@ -272,8 +272,6 @@ int64_t plan_workspace(const nmt_ctx* c, const GroupDims& gd, Plan& p) {
   const int64_t vocab_cut = V / kVocabCutFrom < 3 ? 0 : std::min<int64_t>(kVocabCuts * Nt * d, 2ll * device_info().cus * 128 * 128);
   p.wgpart_floats = std::min(aside, std::max({wgrad_group_floats(enc_layer, Ns, aside), wgrad_group_floats(enc_layer + 4 * d * d + 4 * d, Nt, aside), vocab_cut}));
   p.wgpart = take(p.wgpart_floats * f4);
-  p.cut_floats = kMaxCuts * d * std::min<int64_t>(Nm, kCutRows);  // pieces of one product of few rows
-  p.cut = take(p.cut_floats * f4);
   p.total = cur;
   return cur;
 }
@@ -447,7 +445,8 @@ bool encoder_products_beside(const nmt_ctx* c) {
 struct Run {
   nmt_ctx* c;
   hipStream_t st;
-  bool cuts = false;  // whether products before a LayerNorm may be cut (one chain of a pass only: their pieces have one place)
+  // where the pieces of products cut before a LayerNorm lie, one product's at a time (so one chain of a pass has such a place; 0: none are cut)
+  int64_t cut_at = 0, cut_floats = 0;
   template <typename T>
   T* ws(int64_t off) const { return reinterpret_cast<T*>(c->ws + off); }
   half_t* w(int64_t off) const { return c->w16 + off; }
@@ -470,17 +469,17 @@ struct Run {
   }
   // The same before a LayerNorm over the rows of the result, which adds the pieces up if the product is cut (`cut` says so).
   int linear_to_norm(const half_t* x, int N, int in, int64_t W, int64_t b, int out, half_t* y, CutProduct& cut) const {
-    const int n = cuts ? gemm_cuts(N, out, in) : 1;
-    cut = n > 1 ? CutProduct{ws<float>(c->plan.cut), n, c->w16 + b, nullptr} : CutProduct{};
-    return n > 1 ? launch_gemm_cut(x, in, c->w16 + W, false, in, N, out, in, n, ws<float>(c->plan.cut), c->plan.cut_floats, st)
+    const int n = gemm_cuts(N, out, in, cut_floats);
+    cut = n > 1 ? CutProduct{ws<float>(cut_at), n, c->w16 + b, nullptr} : CutProduct{};
+    return n > 1 ? launch_gemm_cut(x, in, c->w16 + W, false, in, N, out, in, n, ws<float>(cut_at), cut_floats, st)
                  : linear(x, N, in, W, b, out, y);
   }
   int dgrad_to_norm(const half_t* dy, int N, int out, int64_t W, int in, half_t* dx, const half_t* add, bool may, CutProduct& cut) const {
-    const int n = cuts && may ? gemm_cuts(N, in, out) : 1;
-    cut = n > 1 ? CutProduct{ws<float>(c->plan.cut), n, nullptr, add} : CutProduct{};
+    const int n = may ? gemm_cuts(N, in, out, cut_floats) : 1;
+    cut = n > 1 ? CutProduct{ws<float>(cut_at), n, nullptr, add} : CutProduct{};
     GemmEpilogue ep;
     ep.add = add;
-    return n > 1 ? launch_gemm_cut(dy, out, c->w16 + W, true, in, N, in, out, n, ws<float>(c->plan.cut), c->plan.cut_floats, st)
+    return n > 1 ? launch_gemm_cut(dy, out, c->w16 + W, true, in, N, in, out, n, ws<float>(cut_at), cut_floats, st)
                  : dgrad(dy, N, out, W, in, dx, ep);
   }
 };
@@ -594,7 +593,7 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
   const int d = k.d_model, F = k.d_ff, V = k.vocab, H = k.n_heads, dh = d / H;
   const int Bt = c->Bt, Ns = c->Ns, Nt = c->Nt, maxS = c->maxS, maxT = c->maxT;
   const Plan& p = c->plan;
-  const Run r{c, static_cast<hipStream_t>(stream), true};
+  const Run r{c, static_cast<hipStream_t>(stream), p.logits, (int64_t)Nt * V / 2};  // (the logits come last)
   CutProduct cut;
   hipStream_t st = r.st;
   const int4 *tab_ss = r.ws<int4>(p.tab_ss), *tab_tt = r.ws<int4>(p.tab_tt), *tab_ts = r.ws<int4>(p.tab_ts);
@@ -753,7 +752,10 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   // one stream: for callers that keep several passes in flight on streams of their own, and for profiling (no overlap,
   // so per-kernel times are those of kernels running alone)
   hipStream_t st = static_cast<hipStream_t>(stream), sd = two_streams ? c->side : st;
-  const Run r{c, st, true};   // input-gradient chain
+  // input-gradient chain.  Its products' pieces lie where the weight gradients' partial sums do not: their own place is free behind the
+  // vocabulary's input gradient where they have the logits'.
+  const bool wgrad_in_logits = (int64_t)Nt * V / 2 > p.wgpart_floats;
+  const Run r{c, st, p.wgpart, wgrad_in_logits ? p.wgpart_floats : 0};
   CutProduct cut;             // what the last product of that chain left for the next LayerNorm
   const Run side{c, sd};
   const bool dropping = c->training && k.dropout > 0.f;
@@ -767,9 +769,9 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   // (both kernels that read it lie before the first group in the order of either stream)
   float* wgpart = r.ws<float>(p.wgpart);
   int64_t wgpart_floats = p.wgpart_floats;
-  if (const int64_t floats = (int64_t)Nt * V / 2; floats > wgpart_floats) {
+  if (wgrad_in_logits) {
     wgpart = r.ws<float>(p.logits);
-    wgpart_floats = std::min(floats, p.wg_most);
+    wgpart_floats = std::min((int64_t)Nt * V / 2, p.wg_most);
   }
   int set = 0, sub_at = 0;  // temporaries of the current layer; its sub-layers so far
   bool used[2] = {false, false};
