@@ -189,20 +189,6 @@ int launch_gemm(const half_t* A, bool a_t, int lda, const half_t* B, bool b_t, i
                 int M, int N, int K, const GemmEpilogue& ep, hipStream_t stream, float* partial = nullptr,
                 int64_t partial_floats = 0, int splits = 1);
 
-// A product of few rows in `cuts` pieces of its contraction, left as fp32 [cuts][rows][d] for the LayerNorm that follows: the value is
-// fp16(sum over the pieces in order + bias[column] or addend[row][column]).  cuts == 0: there is none.
-struct CutProduct {
-  const float* partial = nullptr;
-  int cuts = 0;
-  const half_t *bias = nullptr, *add = nullptr;
-};
-constexpr int kMaxCuts = 4, kCutRows = 1024;
-// Pieces that C[M, N] = A[M, K] B is cheapest in when a LayerNorm over its rows adds them up (1: whole) and that fit
-// `floats`.
-int gemm_cuts(int M, int N, int K, int64_t floats);
-int launch_gemm_cut(const half_t* A, int lda, const half_t* B, bool b_t, int ldb, int M, int N, int K, int cuts, float* partial,
-                    int64_t partial_floats, hipStream_t stream);
-
 // One weight gradient: C[M, N] = sum_k A[k, M] B[k, N], and, if colsum is set, colsum[M] = sum_k A[k, M] (the bias gradient).
 struct WgradProduct {
   const half_t *A, *B;
@@ -250,10 +236,9 @@ int launch_attention_bwd(const half_t* Q, int ldq, const half_t* K, int ldk, con
                          int causal, int B, int H, int dh, int Tq, int Tk, const int4* sent_tab, int n_q_rows,
                          const AttnWork* work, hipStream_t stream);
 
-// (cut: `sub` has not been written yet and is, from these sums)
-int launch_residual_layernorm_fwd(half_t* sub, const half_t* resid, const half_t* gamma, const half_t* beta,
+int launch_residual_layernorm_fwd(const half_t* sub, const half_t* resid, const half_t* gamma, const half_t* beta,
                                   half_t* out, float* stats, int rows, int d, float eps, const DropDev& drop,
-                                  hipStream_t stream, const CutProduct& cut = {});
+                                  hipStream_t stream);
 int64_t layernorm_bwd_scratch_floats(int d);                        // partial sums of a call of any number of rows ...
 int64_t layernorm_bwd_partial_floats(int most_rows, int d);         // ... of up to `most_rows`
 // Partial rows of column sums as a kernel left them: `rows` rows of up to three quantities, and where their totals go.
@@ -298,12 +283,11 @@ __device__ __forceinline__ void finalize_columns(const FinalizeArgs& a, int bloc
   }
 }
 // The row gradients; the gradients of gamma, beta and the bias are left as partial rows described by `sums`, which
-// launch_layernorm_param_grads adds up (several calls' in one launch).  (cut: its sums take the place of dout, which is not read; at most
-// kCutRows rows; its addend may be dy's place)
+// launch_layernorm_param_grads adds up (several calls' in one launch).
 int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const half_t* resid, const half_t* gamma,
                                   const float* stats, half_t* dy, half_t* dym, half_t* dgamma, half_t* dbeta,
                                   half_t* dbias, float* partial, int rows, int d, const DropDev& drop,
-                                  hipStream_t stream, ColumnSums& sums, const CutProduct& cut = {});
+                                  hipStream_t stream, ColumnSums& sums);
 int launch_layernorm_param_grads(const ColumnSums* sums, int n, int d, float scale, hipStream_t stream);  // scale: factor on all of them
 // All products (1..kMaxWgrad of them, results times out_scale) in one launch, or two if they are cut along k.  partial: fp32 scratch for that
 // (may be null: never cut).  tile, splits: 0 = chosen by cost.

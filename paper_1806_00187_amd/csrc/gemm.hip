@@ -1210,7 +1210,7 @@ int launch_tile(const GemmArgs& a, bool a_t, bool b_t, int splits, hipStream_t s
   else if (a_t && b_t) launch_variant<BM, BN, true, true, NS, NW>(g, splits, stream);
   else launch_variant<BM, BN, true, false, NS, NW>(g, splits, stream);
   NMT_LAUNCH_CHECK();
-  if (splits == 1 || !g.C) return NMT_OK;  // (no C: the pieces stay apart)
+  if (splits == 1) return NMT_OK;
   const int64_t n = (int64_t)g.M * (g.N / 8);
   hipLaunchKernelGGL(splitk_reduce_kernel, dim3(ceil_div(n, kThreads)), dim3(kThreads), 0, stream, g.partial, splits, g.M, g.N, g.C, g.ldc, g.ep.out_scale);
   NMT_LAUNCH_CHECK();
@@ -1244,11 +1244,11 @@ double tile_us(const TileCost& c, int64_t tiles, int K, int cus) {
   if (rest) us += nk * c.k_tile[ceil_div(rest, cus) - 1];
   return us + c.again * (double)(rounds + (rest ? 1 : 0) - 1);
 }
-SmallTile choose_small_tile(int M, int N, int K, int cus, double& best_us, int cuts = 1) {
+SmallTile choose_small_tile(int M, int N, int K, int cus, double& best_us) {
   int best = kTile64;
   best_us = 0.;
   for (int t = 0; t < kSmallTiles; ++t) {
-    const double us = tile_us(kTileCost[t], (int64_t)ceil_div(M, kTileCost[t].bm) * ceil_div(N, kTileCost[t].bn) * cuts, ceil_div(K, cuts), cus);
+    const double us = tile_us(kTileCost[t], (int64_t)ceil_div(M, kTileCost[t].bm) * ceil_div(N, kTileCost[t].bn), K, cus);
     if (t == 0 || us < best_us) { best = t; best_us = us; }
   }
   return (SmallTile)best;
@@ -1561,43 +1561,6 @@ int launch_gemm(const half_t* A, bool a_t, int lda, const half_t* B, bool b_t, i
   return timed_launch(2.0 * M * N * K, stream, [&] {
     return launch_gemm_impl(A, a_t, lda, B, b_t, ldb, C, ldc, M, N, K, ep, stream, partial, partial_floats, splits);
   });
-}
-
-// Few rows give a product few tiles, each a long walk over k with most compute units idle; the LayerNorm behind it waits for memory, not
-// for adding.  Cut where the tiles' model sees more than 1 us in it beyond what the pieces cost that kernel (they go out and come
-// back at about 3 TB/s).
-// Whole update of 380 positions x 1024 wide, against the commit before: 4050 -> 3800 us.  The pieces are the more exact sums: relative error
-// of the fp16 value against 64 bits, whole / 2 / 4 pieces / of the rounding alone, 380 x 1024 x 4096 2.079898e-4 / 2.079897e-4 / 2.079896e-4 / 2.079895e-4,
-// 700 x 2048 x 4096 2.077070e-4 / 2.077067e-4 / 2.077066e-4 / 2.077065e-4.
-int gemm_cuts(int M, int N, int K, int64_t floats) {
-  if (M > kCutRows || tuning().gemm_share > 1 || tuning().gemm_tile) return 1;
-  const int cus = device_info().cus;
-  double best_us;
-  choose_small_tile(M, N, K, cus, best_us);
-  int best = 1;
-  best_us -= 1.0;
-  for (int z = 2; z <= kMaxCuts && (int64_t)z * M * N <= floats; ++z) {
-    const int chunk = (int)round_up(ceil_div(K, z), 64);
-    if (ceil_div(K, chunk) != z) continue;
-    double us;
-    choose_small_tile(M, N, K, cus, us, z);
-    us += 8e-6 / 3.0 * z * M * N;
-    if (us < best_us) { best = z; best_us = us; }
-  }
-  return best;
-}
-int launch_gemm_cut(const half_t* A, int lda, const half_t* B, bool b_t, int ldb, int M, int N, int K, int cuts, float* partial,
-                    int64_t partial_floats, hipStream_t stream) {
-  NMT_REQUIRE(M > 0 && N > 0 && K > 0 && A && B && partial, "cut product: empty problem or null operand");
-  NMT_REQUIRE(aligned16(A) && aligned16(B) && aligned16(partial), "cut product: operands must be 16-byte aligned");
-  NMT_REQUIRE(lda % 8 == 0 && ldb % 8 == 0 && N % 8 == 0 && K % 8 == 0 && lda >= K && ldb >= (b_t ? N : K) && lda <= (1 << 20) && ldb <= (1 << 20),
-              "cut product: leading dimensions and sizes must be multiples of 8 that fit");
-  NMT_REQUIRE(cuts >= 2 && cuts <= kMaxCuts && ceil_div(K, (int)round_up(ceil_div(K, cuts), 64)) == cuts && (int64_t)cuts * M * N <= partial_floats,
-              "cut product: %d pieces do not fit", cuts);
-  const GemmArgs g{A, B, nullptr, lda, ldb, N, M, N, K, 0, 0, 0, device_info().xcds, GemmEpilogue{}, partial, 0};
-  double us;
-  const SmallTile tile = choose_small_tile(M, N, K, device_info().cus, us, cuts);
-  return timed_launch(2.0 * M * N * K, stream, [&] { return launch_small_tile(tile, g, false, b_t, cuts, stream); });
 }
 
 int64_t wgrad_group_floats(int64_t per_split, int64_t rows, int64_t most) {

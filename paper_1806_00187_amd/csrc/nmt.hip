@@ -445,8 +445,6 @@ bool encoder_products_beside(const nmt_ctx* c) {
 struct Run {
   nmt_ctx* c;
   hipStream_t st;
-  // where the pieces of products cut before a LayerNorm lie, one product's at a time (so one chain of a pass has such a place; 0: none are cut)
-  int64_t cut_at = 0, cut_floats = 0;
   template <typename T>
   T* ws(int64_t off) const { return reinterpret_cast<T*>(c->ws + off); }
   half_t* w(int64_t off) const { return c->w16 + off; }
@@ -466,21 +464,6 @@ struct Run {
   // dx[N, in] = dy[N, out] W (+ add)
   int dgrad(const half_t* dy, int N, int out, int64_t W, int in, half_t* dx, GemmEpilogue ep = {}) const {
     return launch_gemm(dy, false, out, c->w16 + W, true, in, dx, in, N, in, out, ep, st);
-  }
-  // The same before a LayerNorm over the rows of the result, which adds the pieces up if the product is cut (`cut` says so).
-  int linear_to_norm(const half_t* x, int N, int in, int64_t W, int64_t b, int out, half_t* y, CutProduct& cut) const {
-    const int n = gemm_cuts(N, out, in, cut_floats);
-    cut = n > 1 ? CutProduct{ws<float>(cut_at), n, c->w16 + b, nullptr} : CutProduct{};
-    return n > 1 ? launch_gemm_cut(x, in, c->w16 + W, false, in, N, out, in, n, ws<float>(cut_at), cut_floats, st)
-                 : linear(x, N, in, W, b, out, y);
-  }
-  int dgrad_to_norm(const half_t* dy, int N, int out, int64_t W, int in, half_t* dx, const half_t* add, bool may, CutProduct& cut) const {
-    const int n = may ? gemm_cuts(N, in, out, cut_floats) : 1;
-    cut = n > 1 ? CutProduct{ws<float>(cut_at), n, nullptr, add} : CutProduct{};
-    GemmEpilogue ep;
-    ep.add = add;
-    return n > 1 ? launch_gemm_cut(dy, out, c->w16 + W, true, in, N, in, out, n, ws<float>(cut_at), cut_floats, st)
-                 : dgrad(dy, N, out, W, in, dx, ep);
   }
 };
 
@@ -593,8 +576,7 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
   const int d = k.d_model, F = k.d_ff, V = k.vocab, H = k.n_heads, dh = d / H;
   const int Bt = c->Bt, Ns = c->Ns, Nt = c->Nt, maxS = c->maxS, maxT = c->maxT;
   const Plan& p = c->plan;
-  const Run r{c, static_cast<hipStream_t>(stream), p.logits, (int64_t)Nt * V / 2};  // (the logits come last)
-  CutProduct cut;
+  const Run r{c, static_cast<hipStream_t>(stream)};
   hipStream_t st = r.st;
   const int4 *tab_ss = r.ws<int4>(p.tab_ss), *tab_tt = r.ws<int4>(p.tab_tt), *tab_ts = r.ws<int4>(p.tab_ts);
   if (tsrc.sentences) {
@@ -628,9 +610,9 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
     NMT_TRY(on.linear(y, Nt, d, P.self.wqkv, P.self.bqkv, 3 * d, qkv));
     NMT_TRY(launch_attention_fwd(qkv, 3 * d, qkv + d, 3 * d, qkv + 2 * d, 3 * d, on.ws<half_t>(W.o1), d, on.ws<float>(W.lse1), d_tgt_in,
                                  k.pad_id, 1, Bt, H, dh, maxT, maxT, tab_tt, Nt, &wl_tt, on.st));
-    NMT_TRY(on.linear_to_norm(on.ws<half_t>(W.o1), Nt, d, P.self.wo, P.self.bo, d, on.ws<half_t>(W.s1), cut));
+    NMT_TRY(on.linear(on.ws<half_t>(W.o1), Nt, d, P.self.wo, P.self.bo, d, on.ws<half_t>(W.s1)));
     NMT_TRY(launch_residual_layernorm_fwd(on.ws<half_t>(W.s1), y, on.w(P.ln1.g), on.w(P.ln1.b), on.ws<half_t>(W.x1), on.ws<float>(W.st1),
-                                          Nt, d, k.ln_eps, on.drop(layer_site(li, kKindSelfRes), true, k.dropout), on.st, cut));
+                                          Nt, d, k.ln_eps, on.drop(layer_site(li, kKindSelfRes), true, k.dropout), on.st));
     return on.linear(on.ws<half_t>(W.x1), Nt, d, P.cross.wq, P.cross.bq, d, on.ws<half_t>(W.q));
   };
   auto embed_targets = [&](const Run& on) {
@@ -662,16 +644,16 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
     NMT_TRY(r.linear(x, Ns, d, P.attn.wqkv, P.attn.bqkv, 3 * d, qkv));
     NMT_TRY(launch_attention_fwd(qkv, 3 * d, qkv + d, 3 * d, qkv + 2 * d, 3 * d, r.ws<half_t>(W.o), d, r.ws<float>(W.lse), d_src,
                                  k.pad_id, 0, Bt, H, dh, maxS, maxS, tab_ss, Ns, &wl_ss, st));
-    NMT_TRY(r.linear_to_norm(r.ws<half_t>(W.o), Ns, d, P.attn.wo, P.attn.bo, d, r.ws<half_t>(W.s1), cut));
+    NMT_TRY(r.linear(r.ws<half_t>(W.o), Ns, d, P.attn.wo, P.attn.bo, d, r.ws<half_t>(W.s1)));
     NMT_TRY(launch_residual_layernorm_fwd(r.ws<half_t>(W.s1), x, r.w(P.ln1.g), r.w(P.ln1.b), r.ws<half_t>(W.x1), r.ws<float>(W.st1),
-                                          Ns, d, k.ln_eps, r.drop(layer_site(l, kKindSelfRes), false, k.dropout), st, cut));
+                                          Ns, d, k.ln_eps, r.drop(layer_site(l, kKindSelfRes), false, k.dropout), st));
     GemmEpilogue act;
     act.relu = 1;
     act.drop = r.drop(layer_site(l, kKindFfnAct), false, k.act_dropout);
     NMT_TRY(r.linear(r.ws<half_t>(W.x1), Ns, d, P.ffn.w1, P.ffn.b1, F, r.ws<half_t>(W.h), act));
-    NMT_TRY(r.linear_to_norm(r.ws<half_t>(W.h), Ns, F, P.ffn.w2, P.ffn.b2, d, r.ws<half_t>(W.s2), cut));
+    NMT_TRY(r.linear(r.ws<half_t>(W.h), Ns, F, P.ffn.w2, P.ffn.b2, d, r.ws<half_t>(W.s2)));
     NMT_TRY(launch_residual_layernorm_fwd(r.ws<half_t>(W.s2), r.ws<half_t>(W.x1), r.w(P.ln2.g), r.w(P.ln2.b), r.ws<half_t>(W.x2),
-                                          r.ws<float>(W.st2), Ns, d, k.ln_eps, r.drop(layer_site(l, kKindFfnRes), false, k.dropout), st, cut));
+                                          r.ws<float>(W.st2), Ns, d, k.ln_eps, r.drop(layer_site(l, kKindFfnRes), false, k.dropout), st));
     x = r.ws<half_t>(W.x2);
     if (self_beside && l == 0) NMT_TRY(decoder_ahead());
   }
@@ -704,16 +686,16 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
     if (beside && l == 1) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_join, 0));
     NMT_TRY(launch_attention_fwd(r.ws<half_t>(W.q), d, kv, 2 * d, kv + d, 2 * d, r.ws<half_t>(W.o2), d, r.ws<float>(W.lse2), d_src,
                                  k.pad_id, 0, Bt, H, dh, maxT, maxS, tab_ts, Nt, &wl_ts, st));
-    NMT_TRY(r.linear_to_norm(r.ws<half_t>(W.o2), Nt, d, P.cross.wo, P.cross.bo, d, r.ws<half_t>(W.s2), cut));
+    NMT_TRY(r.linear(r.ws<half_t>(W.o2), Nt, d, P.cross.wo, P.cross.bo, d, r.ws<half_t>(W.s2)));
     NMT_TRY(launch_residual_layernorm_fwd(r.ws<half_t>(W.s2), r.ws<half_t>(W.x1), r.w(P.ln2.g), r.w(P.ln2.b), r.ws<half_t>(W.x2),
-                                          r.ws<float>(W.st2), Nt, d, k.ln_eps, r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st, cut));
+                                          r.ws<float>(W.st2), Nt, d, k.ln_eps, r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st));
     GemmEpilogue act;
     act.relu = 1;
     act.drop = r.drop(layer_site(li, kKindFfnAct), true, k.act_dropout);
     NMT_TRY(r.linear(r.ws<half_t>(W.x2), Nt, d, P.ffn.w1, P.ffn.b1, F, r.ws<half_t>(W.h), act));
-    NMT_TRY(r.linear_to_norm(r.ws<half_t>(W.h), Nt, F, P.ffn.w2, P.ffn.b2, d, r.ws<half_t>(W.s3), cut));
+    NMT_TRY(r.linear(r.ws<half_t>(W.h), Nt, F, P.ffn.w2, P.ffn.b2, d, r.ws<half_t>(W.s3)));
     NMT_TRY(launch_residual_layernorm_fwd(r.ws<half_t>(W.s3), r.ws<half_t>(W.x2), r.w(P.ln3.g), r.w(P.ln3.b), r.ws<half_t>(W.x3),
-                                          r.ws<float>(W.st3), Nt, d, k.ln_eps, r.drop(layer_site(li, kKindFfnRes), true, k.dropout), st, cut));
+                                          r.ws<float>(W.st3), Nt, d, k.ln_eps, r.drop(layer_site(li, kKindFfnRes), true, k.dropout), st));
     y = r.ws<half_t>(W.x3);
   }
 
@@ -752,11 +734,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   // one stream: for callers that keep several passes in flight on streams of their own, and for profiling (no overlap,
   // so per-kernel times are those of kernels running alone)
   hipStream_t st = static_cast<hipStream_t>(stream), sd = two_streams ? c->side : st;
-  // input-gradient chain.  Its products' pieces lie where the weight gradients' partial sums do not: their own place is free behind the
-  // vocabulary's input gradient where they have the logits'.
-  const bool wgrad_in_logits = (int64_t)Nt * V / 2 > p.wgpart_floats;
-  const Run r{c, st, p.wgpart, wgrad_in_logits ? p.wgpart_floats : 0};
-  CutProduct cut;             // what the last product of that chain left for the next LayerNorm
+  const Run r{c, st};   // input-gradient chain
   const Run side{c, sd};
   const bool dropping = c->training && k.dropout > 0.f;
   const float act_scale = (c->training && k.act_dropout > 0.f) ? 1.f / (1.f - k.act_dropout) : 1.f;
@@ -769,9 +747,9 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   // (both kernels that read it lie before the first group in the order of either stream)
   float* wgpart = r.ws<float>(p.wgpart);
   int64_t wgpart_floats = p.wgpart_floats;
-  if (wgrad_in_logits) {
+  if (const int64_t floats = (int64_t)Nt * V / 2; floats > wgpart_floats) {
     wgpart = r.ws<float>(p.logits);
-    wgpart_floats = std::min((int64_t)Nt * V / 2, p.wg_most);
+    wgpart_floats = std::min(floats, p.wg_most);
   }
   int set = 0, sub_at = 0;  // temporaries of the current layer; its sub-layers so far
   bool used[2] = {false, false};
@@ -827,34 +805,38 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
                      const FfnP& f, const LnP& ln, uint32_t site_res) -> int {
     begin_sublayer(sub);
     NMT_TRY(launch_residual_layernorm_bwd(dx, sub, x_in, r.w(ln.g), stats, dy, dym, r.g(ln.g), r.g(ln.b), r.g(f.b2), lnpart, N, d,
-                                          r.drop(site_res, tgt, k.dropout), st, ln_sums[sub_at - 1], cut));
+                                          r.drop(site_res, tgt, k.dropout), st, ln_sums[sub_at - 1]));
     leaf(dsub, N, d, hact, F, f.w2);
     GemmEpilogue relu_bwd;
     relu_bwd.relu_src = hact;
     relu_bwd.mask_scale = act_scale;
     NMT_TRY(r.dgrad(dsub, N, d, f.w2, F, dhid, relu_bwd));
     leaf(dhid, N, F, x_in, d, f.w1, f.b1);
-    return r.dgrad_to_norm(dhid, N, F, f.w1, d, dx, dy, true, cut);
+    GemmEpilogue res;
+    res.add = dy;
+    return r.dgrad(dhid, N, F, f.w1, d, dx, res);
   };
-  // self-attention sub-layer (fused q, k, v projection); `on`: the stream its chain runs on; `last`: the embeddings come next, no LayerNorm
+  // self-attention sub-layer (fused q, k, v projection); `on`: the stream its chain runs on
   auto self_bwd = [&](const Run& on, half_t* dx, int N, bool tgt, const half_t* x_in, const half_t* qkv, const half_t* o, const float* lse,
                       const half_t* sub, const float* stats, const AttnP& a, const LnP& ln, uint32_t site_res, const int32_t* key_ids,
-                      int causal, bool last) -> int {
+                      int causal) -> int {
     begin_sublayer(sub);
     NMT_TRY(launch_residual_layernorm_bwd(dx, sub, x_in, r.w(ln.g), stats, dy, dym, r.g(ln.g), r.g(ln.b), r.g(a.bo), lnpart, N, d,
-                                          r.drop(site_res, tgt, k.dropout), on.st, ln_sums[sub_at - 1], cut));
+                                          r.drop(site_res, tgt, k.dropout), on.st, ln_sums[sub_at - 1]));
     leaf(dsub, N, d, o, d, a.wo);
     NMT_TRY(on.dgrad(dsub, N, d, a.wo, d, dO));
     NMT_TRY(launch_attention_bwd(qkv, 3 * d, qkv + d, 3 * d, qkv + 2 * d, 3 * d, o, d, dO, d, lse, dqkv, 3 * d, dqkv + d, 3 * d,
                                  dqkv + 2 * d, 3 * d, key_ids, k.pad_id, causal, Bt, H, dh, tgt ? maxT : maxS, tgt ? maxT : maxS,
                                  tgt ? tab_tt : tab_ss, N, tgt ? &wl_tt : &wl_ss, on.st));
     leaf(dqkv, N, 3 * d, x_in, d, a.wqkv, a.bqkv);
+    GemmEpilogue res;
+    res.add = dy;
     if (on.st != st) {  // (a chain on the second stream: the group ends the layer's use of its temporaries)
-      NMT_TRY(on.dgrad_to_norm(dqkv, N, 3 * d, a.wqkv, d, dx, dy, false, cut));
+      NMT_TRY(on.dgrad(dqkv, N, 3 * d, a.wqkv, d, dx, res));
       return flush_leaves(false);
     }
     NMT_TRY(flush_leaves(true));  // (the self-attention sub-layer is a layer's last)
-    return on.dgrad_to_norm(dqkv, N, 3 * d, a.wqkv, d, dx, dy, !last, cut);
+    return on.dgrad(dqkv, N, 3 * d, a.wqkv, d, dx, res);
   };
 
   // ---- output projection: logits = x E^T; the workspace holds d logits ----
@@ -898,7 +880,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     begin_sublayer(r.ws<half_t>(W.s2));
     NMT_TRY(launch_residual_layernorm_bwd(dx, r.ws<half_t>(W.s2), r.ws<half_t>(W.x1), r.w(P.ln2.g), r.ws<float>(W.st2), dy, dym,
                                           r.g(P.ln2.g), r.g(P.ln2.b), r.g(P.cross.bo), lnpart, Nt, d,
-                                          r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st, ln_sums[sub_at - 1], cut));
+                                          r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st, ln_sums[sub_at - 1]));
     leaf(dsub, Nt, d, r.ws<half_t>(W.o2), d, P.cross.wo);
     NMT_TRY(r.dgrad(dsub, Nt, d, P.cross.wo, d, dO));
     const half_t* kv = r.ws<half_t>(W.kv);
@@ -906,8 +888,9 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
                                  dkv, 2 * d, dkv + d, 2 * d, c->src, k.pad_id, 0, Bt, H, dh, maxT, maxS, tab_ts, Nt, &wl_ts, st));
     leaf(dq, Nt, d, r.ws<half_t>(W.x1), d, P.cross.wq, P.cross.bq);
     leaf(dkv, Ns, 2 * d, enc_out, d, P.cross.wkv, P.cross.bkv);
-    // (not cut where the next LayerNorm runs beside the encoder's chain, whose products use the pieces' place)
-    NMT_TRY(r.dgrad_to_norm(dq, Nt, d, P.cross.wq, d, dx, dy, !(self_beside && l == 0), cut));
+    GemmEpilogue res;
+    res.add = dy;
+    NMT_TRY(r.dgrad(dq, Nt, d, P.cross.wq, d, dx, res));
     GemmEpilogue accum;
     accum.add = (l == k.dec_layers - 1) ? nullptr : denc;  // the encoder output feeds every decoder layer
     if (beside && !(self_beside && l == 0)) {
@@ -927,7 +910,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
       dy_place = dO + (int64_t)Nt * d;
     }
     NMT_TRY(self_bwd(self_beside && l == 0 ? side : r, dx, Nt, true, x_in, r.ws<half_t>(W.qkv), r.ws<half_t>(W.o1), r.ws<float>(W.lse1),
-                     r.ws<half_t>(W.s1), r.ws<float>(W.st1), P.self, P.ln1, layer_site(li, kKindSelfRes), c->tgt_in, 1, l == 0));
+                     r.ws<half_t>(W.s1), r.ws<float>(W.st1), P.self, P.ln1, layer_site(li, kKindSelfRes), c->tgt_in, 1));
   }
   if (self_beside) {
     NMT_HIP_CHECK(hipEventRecord(c->ev_self, sd));
@@ -947,7 +930,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     NMT_TRY(ffn_bwd(denc, Ns, false, r.ws<half_t>(W.x1), r.ws<half_t>(W.h), r.ws<half_t>(W.s2), r.ws<float>(W.st2), P.ffn, P.ln2,
                     layer_site(l, kKindFfnRes)));
     NMT_TRY(self_bwd(r, denc, Ns, false, x_in, r.ws<half_t>(W.qkv), r.ws<half_t>(W.o), r.ws<float>(W.lse), r.ws<half_t>(W.s1),
-                     r.ws<float>(W.st1), P.attn, P.ln1, layer_site(l, kKindSelfRes), c->src, 0, l == 0));
+                     r.ws<float>(W.st1), P.attn, P.ln1, layer_site(l, kKindSelfRes), c->src, 0));
   }
 
   // ---- the embeddings: both id streams add into the row gradients of the shared matrix (beside the second stream's last
@@ -1116,7 +1099,7 @@ extern "C" int nmt_op_residual_layernorm_fwd(const void* d_sub, const void* d_re
                                              void* stream) {
   NMT_TRY(check_drop(drop, "nmt_op_residual_layernorm_fwd"));
   NMT_REQUIRE(eps > 0.f, "nmt_op_residual_layernorm_fwd: eps must be positive");
-  return launch_residual_layernorm_fwd(const_cast<half_t*>(static_cast<const half_t*>(d_sub)), static_cast<const half_t*>(d_resid),
+  return launch_residual_layernorm_fwd(static_cast<const half_t*>(d_sub), static_cast<const half_t*>(d_resid),
                                        static_cast<const half_t*>(d_gamma), static_cast<const half_t*>(d_beta), static_cast<half_t*>(d_out),
                                        d_stats, rows, d, eps, make_drop(drop), static_cast<hipStream_t>(stream));
 }

@@ -62,65 +62,19 @@ __global__ void __launch_bounds__(kThreads) embed_fwd_kernel(const int32_t* __re
 // they write.  With streaming forms (no retention asked for) whole updates took, start / now in us: 2 x 1400 positions x 256 1370 / 1295, 3000 x 512
 // 3830 / 3780; 3000 to 17700 x 1024 the same within 0.5 %.
 // ------------------------------------------------------------------------------------------------
-// Columns c * 8 ... of a row of a cut product: all pieces are requested before the first is added.
-struct CutChunk {
-  floatx4 lo[kMaxCuts], hi[kMaxCuts];
-  half8_t more;
-  __device__ __forceinline__ void request(const CutProduct& cut, int row, int rows, int d, int c) {
-#pragma unroll
-    for (int z = 0; z < kMaxCuts; ++z)
-      if (z < cut.cuts) {
-        const floatx4* at = reinterpret_cast<const floatx4*>(cut.partial + ((size_t)z * rows + row) * d + c * 8);
-        lo[z] = at[0];
-        hi[z] = at[1];
-      }
-    more = cut.bias ? ld_half8(cut.bias + c * 8) : (cut.add ? ld_half8(cut.add + (size_t)row * d + c * 8) : zero_half8());
-  }
-  __device__ __forceinline__ half8_t value(const CutProduct& cut) {
-#pragma unroll
-    for (int z = 1; z < kMaxCuts; ++z)
-      if (z < cut.cuts) {
-        lo[0] += lo[z];
-        hi[0] += hi[z];
-      }
-    half8_t h;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      h[e] = (half_t)(lo[0][e] + (float)more[e]);
-      h[4 + e] = (half_t)(hi[0][e] + (float)more[4 + e]);
-    }
-    return h;
-  }
-};
-
-// CUT: sub is the sum of a cut product, written here (the backward pass reads it).
-template <int NCH, bool CUT>
-__device__ __forceinline__ void load_presum(float (&y)[NCH][8], half_t* __restrict__ sub,
-                                            const half_t* __restrict__ resid, int row, int rows, int d, int lane,
-                                            const DropDev& drop, const CutProduct& cut) {
+template <int NCH>
+__device__ __forceinline__ void load_presum(float (&y)[NCH][8], const half_t* __restrict__ sub,
+                                            const half_t* __restrict__ resid, int row, int d, int lane,
+                                            const DropDev& drop) {
   const int chunks = d >> 3;
   half8_t hs[NCH], hr[NCH];  // everything the row needs is requested before anything is used
   DropRow key = {};
   if (drop.thr) key = drop_row(drop, (uint32_t)row);
-  CutChunk pieces[CUT ? NCH : 1];
 #pragma unroll
   for (int i = 0; i < NCH; ++i) {
     const int c = lane + kWave * i;
-    if constexpr (CUT) {
-      hs[i] = zero_half8();
-      if (c < chunks) pieces[i].request(cut, row, rows, d, c);
-    } else {
-      hs[i] = c < chunks ? ld_half8(sub + (size_t)row * d + c * 8) : zero_half8();
-    }
+    hs[i] = c < chunks ? ld_half8(sub + (size_t)row * d + c * 8) : zero_half8();
     hr[i] = c < chunks ? ld_half8(resid + (size_t)row * d + c * 8) : zero_half8();
-  }
-  if constexpr (CUT) {
-#pragma unroll
-    for (int i = 0; i < NCH; ++i)
-      if (const int c = lane + kWave * i; c < chunks) {
-        hs[i] = pieces[i].value(cut);
-        st_half8(sub + (size_t)row * d + c * 8, hs[i]);
-      }
   }
 #pragma unroll
   for (int i = 0; i < NCH; ++i) {
@@ -130,11 +84,11 @@ __device__ __forceinline__ void load_presum(float (&y)[NCH][8], half_t* __restri
   }
 }
 
-template <int NCH, bool CUT>
-__global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(half_t* __restrict__ sub, const half_t* __restrict__ resid,
+template <int NCH>
+__global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(const half_t* __restrict__ sub, const half_t* __restrict__ resid,
                                                               const half_t* __restrict__ gamma, const half_t* __restrict__ beta,
                                                               half_t* __restrict__ out, float* __restrict__ stats, int rows,
-                                                              int d, float eps, DropDev drop, CutProduct cut) {
+                                                              int d, float eps, DropDev drop) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   if (row >= rows) return;
@@ -147,7 +101,7 @@ __global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(half_t* __restrict
     gam[i] = c < chunks ? ld_half8(gamma + c * 8) : zero_half8();
     bet[i] = c < chunks ? ld_half8(beta + c * 8) : zero_half8();
   }
-  load_presum<NCH, CUT>(y, sub, resid, row, rows, d, lane, drop, cut);
+  load_presum<NCH>(y, sub, resid, row, d, lane, drop);
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < NCH; ++i)
@@ -185,13 +139,12 @@ __global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(half_t* __restrict
 // then the result), which keeps the kernel at four wavefronts per SIMD.
 constexpr int kLnBwdMaxBlocks = 1024;
 
-// CUT: the gradient at the output is the sum of a cut product, whose addend may lie where dy goes (read before it is written).
-template <int NCH, int ROWS, int WAVES, bool CUT = false>
+template <int NCH, int ROWS, int WAVES>
 __global__ void __launch_bounds__(64 * WAVES) res_ln_bwd_kernel(const half_t* __restrict__ dout, const half_t* __restrict__ sub,
                                                               const half_t* __restrict__ resid, const half_t* __restrict__ gamma,
-                                                              const float* __restrict__ stats, half_t* dy_out,
+                                                              const float* __restrict__ stats, half_t* __restrict__ dy_out,
                                                               half_t* __restrict__ dym_out, float* __restrict__ partial, int rows,
-                                                              int d, DropDev drop, CutProduct cut) {
+                                                              int d, DropDev drop) {
   extern __shared__ __align__(16) float red[];  // [WAVES][NCH][2][64 lanes][4]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int chunks = d >> 3;
@@ -208,7 +161,6 @@ __global__ void __launch_bounds__(64 * WAVES) res_ln_bwd_kernel(const half_t* __
     uint32_t bits[ROWS][NCH];
     DropRow key[ROWS] = {};
     float mean[ROWS], rstd[ROWS], s1[ROWS], s2[ROWS];
-    CutChunk pieces[CUT ? ROWS : 1][CUT ? NCH : 1];
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
       const int row = min(row0 + u, rows - 1);  // a row past the end repeats the last one and is not written
@@ -218,11 +170,7 @@ __global__ void __launch_bounds__(64 * WAVES) res_ln_bwd_kernel(const half_t* __
         const bool in = c < chunks;
         hs[u][i] = in ? ld_half8(sub + (size_t)row * d + c * 8) : zero_half8();
         hr[u][i] = in ? ld_half8(resid + (size_t)row * d + c * 8) : zero_half8();
-        if constexpr (CUT) {
-          if (in) pieces[u][i].request(cut, row, rows, d, c);
-        } else {
-          hg[u][i] = in ? ld_half8(dout + (size_t)row * d + c * 8) : zero_half8();
-        }
+        hg[u][i] = in ? ld_half8(dout + (size_t)row * d + c * 8) : zero_half8();
       }
       mean[u] = stats[2 * row];
       rstd[u] = stats[2 * row + 1];
@@ -232,12 +180,6 @@ __global__ void __launch_bounds__(64 * WAVES) res_ln_bwd_kernel(const half_t* __
     for (int u = 0; u < ROWS; ++u)
 #pragma unroll
       for (int i = 0; i < NCH; ++i) bits[u][i] = drop.thr ? drop_keep8(drop, key[u], (uint32_t)(lane + kWave * i)) : 0xFFu;
-    if constexpr (CUT) {
-#pragma unroll
-      for (int u = 0; u < ROWS; ++u)
-#pragma unroll
-        for (int i = 0; i < NCH; ++i) hg[u][i] = lane + kWave * i < chunks ? pieces[u][i].value(cut) : zero_half8();
-    }
     // normalised value of element e of chunk i of row u (the pre-normalisation sum is formed in fp32, as in the forward pass)
     auto xhat = [&](int u, int i, int e) {
       const float y = (float)hr[u][i][e] + (((bits[u][i] >> e) & 1u) ? (float)hs[u][i][e] * drop.scale : 0.f);
@@ -971,24 +913,19 @@ int launch_embed_fwd(const int32_t* ids, const half_t* E, half_t* x, int rows, i
   return NMT_OK;
 }
 
-int launch_residual_layernorm_fwd(half_t* sub, const half_t* resid, const half_t* gamma, const half_t* beta,
+int launch_residual_layernorm_fwd(const half_t* sub, const half_t* resid, const half_t* gamma, const half_t* beta,
                                   half_t* out, float* stats, int rows, int d, float eps, const DropDev& drop,
-                                  hipStream_t stream, const CutProduct& cut) {
+                                  hipStream_t stream) {
   NMT_REQUIRE(rows > 0 && d >= 8 && d % 8 == 0 && d <= 2048, "layernorm: d=%d must be a multiple of 8 in [8, 2048]", d);
   NMT_REQUIRE(sub && resid && gamma && beta && out && stats, "layernorm: null pointer");
   NMT_REQUIRE(aligned16(sub) && aligned16(resid) && aligned16(gamma) && aligned16(beta) && aligned16(out), "layernorm: misaligned pointer");
   NMT_REQUIRE(!drop.thr || drop.n_pos > 0, "layernorm: positions per sentence must be positive");
-  NMT_REQUIRE(!cut.cuts || (cut.cuts <= kMaxCuts && cut.partial && aligned16(cut.partial) && aligned16(cut.bias) && aligned16(cut.add)), "layernorm: bad cut product");
   const dim3 grid(ceil_div(rows, kWavesPerBlock)), block(kThreads);
-#define NMT_LN_FWD(N)                                                                                                                             \
-  hipLaunchKernelGGL((cut.cuts ? res_ln_fwd_kernel<N, true> : res_ln_fwd_kernel<N, false>), grid, block, 0, stream, sub, resid, gamma, beta, out, \
-                     stats, rows, d, eps, drop, cut)
   switch (ln_nch(d)) {
-    case 1: NMT_LN_FWD(1); break;
-    case 2: NMT_LN_FWD(2); break;
-    default: NMT_LN_FWD(4); break;
+    case 1: hipLaunchKernelGGL(res_ln_fwd_kernel<1>, grid, block, 0, stream, sub, resid, gamma, beta, out, stats, rows, d, eps, drop); break;
+    case 2: hipLaunchKernelGGL(res_ln_fwd_kernel<2>, grid, block, 0, stream, sub, resid, gamma, beta, out, stats, rows, d, eps, drop); break;
+    default: hipLaunchKernelGGL(res_ln_fwd_kernel<4>, grid, block, 0, stream, sub, resid, gamma, beta, out, stats, rows, d, eps, drop); break;
   }
-#undef NMT_LN_FWD
   NMT_LAUNCH_CHECK();
   return NMT_OK;
 }
@@ -1021,28 +958,19 @@ int64_t layernorm_bwd_partial_floats(int most_rows, int d) {
 int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const half_t* resid, const half_t* gamma,
                                   const float* stats, half_t* dy, half_t* dym, half_t* dgamma, half_t* dbeta,
                                   half_t* dbias, float* partial, int rows, int d, const DropDev& drop,
-                                  hipStream_t stream, ColumnSums& sums, const CutProduct& cut) {
+                                  hipStream_t stream, ColumnSums& sums) {
   NMT_REQUIRE(rows > 0 && d >= 8 && d % 8 == 0 && d <= 2048, "layernorm_bwd: d=%d must be a multiple of 8 in [8, 2048]", d);
-  NMT_REQUIRE((dout || cut.cuts) && sub && resid && gamma && stats && dy && partial, "layernorm_bwd: null pointer");
+  NMT_REQUIRE(dout && sub && resid && gamma && stats && dy && partial, "layernorm_bwd: null pointer");
   NMT_REQUIRE(aligned16(dout) && aligned16(sub) && aligned16(resid) && aligned16(gamma) && aligned16(dy) && aligned16(dym),
               "layernorm_bwd: misaligned pointer");
   NMT_REQUIRE(!drop.thr || (drop.n_pos > 0 && dym), "layernorm_bwd: dropout needs the masked output and positions per sentence");
   const int nch = ln_nch(d);
   const LnBwdForm form = ln_bwd_form(rows, d);
-  NMT_REQUIRE(!cut.cuts || (cut.cuts <= kMaxCuts && form.rows_per_wave == 1 && form.waves == 4 && cut.partial && aligned16(cut.partial) && aligned16(cut.bias) && aligned16(cut.add)),
-              "layernorm_bwd: bad cut product");
   const int nblk = ln_bwd_blocks(rows, d);
   const dim3 grid(nblk), block(kWave * form.waves);
   const size_t smem = (size_t)form.waves * nch * 512 * sizeof(float);
-#define NMT_LN_BWD(N, R, W, ...) \
-  hipLaunchKernelGGL((res_ln_bwd_kernel<N, R, W, ##__VA_ARGS__>), grid, block, smem, stream, dout, sub, resid, gamma, stats, dy, dym, partial, rows, d, drop, cut)
-  if (cut.cuts) {
-    switch (nch) {
-      case 1: NMT_LN_BWD(1, 1, 4, true); break;
-      case 2: NMT_LN_BWD(2, 1, 4, true); break;
-      default: NMT_LN_BWD(4, 1, 4, true); break;
-    }
-  } else switch (nch * 4 + (form.waves == 8 ? 2 : form.rows_per_wave - 1)) {
+#define NMT_LN_BWD(N, R, W) hipLaunchKernelGGL((res_ln_bwd_kernel<N, R, W>), grid, block, smem, stream, dout, sub, resid, gamma, stats, dy, dym, partial, rows, d, drop)
+  switch (nch * 4 + (form.waves == 8 ? 2 : form.rows_per_wave - 1)) {
     case 4: NMT_LN_BWD(1, 1, 4); break;
     case 5: NMT_LN_BWD(1, 2, 4); break;
     case 6: NMT_LN_BWD(1, 1, 8); break;
