@@ -46,11 +46,12 @@ __global__ void __launch_bounds__(kThreads) accumulate_kernel(const half_t* __re
 #pragma unroll
     for (int u = 0; u < kAccumulateAhead; ++u) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        a[u][e] += mult * (float)g[u][e];
-        if (CHECK) bad |= non_finite(a[u][e]);
+      for (int e = 0; e < 4; ++e) a[u][e] += mult * (float)g[u][e];
+      if (i0 + u * kThreads < nvec) {  // (a lane past the end holds the last vector, which its owner may have stored already: no sum to check)
+#pragma unroll
+        for (int e = 0; CHECK && e < 4; ++e) bad |= non_finite(a[u][e]);
+        st_state<STREAM>(acc + (i0 + u * kThreads) * 4, a[u]);
       }
-      if (i0 + u * kThreads < nvec) st_state<STREAM>(acc + (i0 + u * kThreads) * 4, a[u]);
     }
   }
   // tail (n not a multiple of 4)

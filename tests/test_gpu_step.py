@@ -391,6 +391,29 @@ def test_finish_update_equals_its_three_calls(model, sentences, poison, first):
         assert torch.equal(a, b)
 
 
+def test_finish_update_checks_each_sum_once():
+    """The last accumulation of an update checks the sums that it stores: lanes past the end of the vector hold a copy of the last four
+    elements, which their owner may already have written back, and those are no sums.  Largest finite values there, in the
+    accumulator and the gradient, raise no flag, and each element is accumulated once."""
+    model = I.MODELS["tiny"]
+    sess = Session(model, I.init_weights(seed=0, **model), max_sentences=8)
+    try:
+        db = sess.to_device(I.tiny_batch())
+        sess.forward_loss(db, 16.0, 1, 0)
+        sess.backward()
+        assert sess.P % (4 * 4 * 256) and sess.grad_scale() == 1.0     # (the last work-group's threads have four vectors each to look at)
+        acc = torch.randn(sess.P, device="cuda", generator=torch.Generator(device="cuda").manual_seed(2))
+        acc[-4:] = torch.finfo(torch.float32).max
+        sess.g16[-4:] = torch.finfo(torch.float16).max
+        for _ in range(20):
+            sess.acc.copy_(acc)
+            sess.flag.fill_(7)
+            sess.finish_update(False, 2.0 ** -10, 0.0, 1)
+            assert int(sess.flag.item()) == 0 and torch.equal(sess.acc, acc + sess.g16.float())
+    finally:
+        sess.close()
+
+
 def test_call_order_and_workspace_errors():
     model = I.MODELS["tiny"]
     sess = Session(model, I.init_weights(seed=0, **model), max_sentences=8)
