@@ -199,12 +199,14 @@ class Session:
         step = t if step is None else step
         main = torch.cuda.current_stream(self.device)
         if self.n_pipes == 1:
-            for j, db in enumerate(dbatches):
-                self.forward_loss(db, loss_scale, step, j)
+            passes = 0
+            for db in dbatches:
+                if passes:
+                    self.accumulate(passes == 1)   # (of the pass before; the last one's: finish_update)
+                self.forward_loss(db, loss_scale, step, passes)
                 self.backward()
-                if j < len(dbatches) - 1:
-                    self.accumulate(j == 0)        # (the last one: finish_update)
-                nmt.nmt_accumulate_loss(self.ctx, j == 0, self.loss_tot, self.ntok_tot)
+                nmt.nmt_accumulate_loss(self.ctx, passes == 0, self.loss_tot, self.ntok_tot)
+                passes += 1
         else:
             if not self._streams_chosen:
                 self.choose_streams(dbatches, loss_scale, tries=4)
@@ -212,8 +214,8 @@ class Session:
         if n_tok is None:
             n_tok = int(self.ntok_tot.item())
         inv_scale = 1.0 / (loss_scale * max(n_tok, 1))
-        if self.n_pipes == 1 and len(dbatches):
-            self.finish_update(len(dbatches) == 1, inv_scale, lr, t, betas, eps)
+        if self.n_pipes == 1 and passes:
+            self.finish_update(passes == 1, inv_scale, lr, t, betas, eps)
         else:
             self.check_overflow(inv_scale)
             self.adam_step(lr, t, betas, eps)

@@ -414,6 +414,21 @@ def test_finish_update_checks_each_sum_once():
         sess.close()
 
 
+def test_update_takes_sub_batches_as_they_come():
+    """Any iterable of sub-batches makes an update, such as a generator that uploads them one by one; the buffers are those of a list."""
+    model = I.MODELS["tiny"]
+    batches = [I.tiny_batch(seed=40 + i, B=8 - i) for i in range(3)]
+    for n in (1, 3):
+        ends = []
+        for lazy in (False, True):
+            sess = Session(model, I.init_weights(seed=0, **model), max_sentences=8)
+            feed = (sess.to_device(b) for b in batches[:n])
+            res = sess.update(feed if lazy else list(feed), 64.0, 5e-4, 1)
+            ends.append((res, [host(x) for x in (sess.acc, sess.master, sess.m, sess.v, sess.w16)]))
+            sess.close()
+        assert ends[0][0] == ends[1][0] and all((a == b).all() for a, b in zip(ends[0][1], ends[1][1]))
+
+
 def test_call_order_and_workspace_errors():
     model = I.MODELS["tiny"]
     sess = Session(model, I.init_weights(seed=0, **model), max_sentences=8)
