@@ -656,8 +656,8 @@ __device__ __forceinline__ void emb_add(half_t* __restrict__ dst, const half8_t 
 // threads takes every groups-th entry (AHEAD of them, all requested together) and leaves the row after dropout in LDS; then
 // the first group adds the entries up in the order of the list, a thread per eight columns.  The ids are the same for the whole
 // block and come with one load; EARLY: the table rows of runs that end here are asked for beside the gradient rows.
-// Before (a thread per eight columns drew for all sixteen entries) and now, us: 260 entries x 64 16.2 / 6.5, 2800 x 256 16.7 / 6.8,
-// 6600 x 512 16 to 28 / 10, 27000 x 512 alone 18.1 / 16.6, 35700 x 1024 alone 31.5 / 33.8, of distinct ids 42.6 / 38.3.
+// emb_segment_columns_kernel (a thread per eight columns draws for all sixteen entries) and this one, us: 260 entries x 64 16.2 / 6.5,
+// 2800 x 256 16.7 / 6.8, 6600 x 512 15.0 / 8.0, 27000 x 512 18.6 / 16.9.
 template <int THREADS, int AHEAD, bool EARLY>
 __global__ void __launch_bounds__(THREADS) emb_segment_kernel(const half_t* __restrict__ dxa, int na, DropDev da,
                                                            const half_t* __restrict__ dxb, DropDev db, half_t* __restrict__ gE, int n,
@@ -753,6 +753,74 @@ __global__ void __launch_bounds__(THREADS) emb_segment_kernel(const half_t* __re
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] = 0.f;
       }
+    }
+  }
+}
+// The same for lists so long that the blocks no longer share the chip's compute units a few at a time: one thread per 8 columns, no rows in
+// LDS.  Then not the chain of one segment counts but how many are on their way at once, and a block of d / 8 threads and no LDS leaves
+// room for more of them.  The gradient rows, row keys and table rows of kEmbAhead entries are requested together before any is used (94 -> 16 us at
+// 6000 entries x 512 columns, 113 -> 81 us at 107000 x 1024, against a chain of dependent loads per entry).
+constexpr int kEmbAhead = 8;
+static_assert(kEmbSeg % kEmbAhead == 0 && kEmbSeg + 2 <= kWave, "a block's first wavefront stages the segment's ids");
+__global__ void __launch_bounds__(kThreads) emb_segment_columns_kernel(const half_t* __restrict__ dxa, int na, DropDev da,
+                                                               const half_t* __restrict__ dxb, DropDev db, half_t* __restrict__ gE, int n,
+                                                               int d, const int32_t* __restrict__ keys, const int32_t* __restrict__ perm,
+                                                               float* __restrict__ part, float scale) {
+  __shared__ int s_pos[kEmbSeg], s_key[kEmbSeg + 2];  // s_key: with the entries before and after the segment (-1: none)
+  __shared__ DropRow s_drop[kEmbSeg];
+  const int e0 = blockIdx.x * kEmbSeg, cnt = min(kEmbSeg, n - e0);
+  if (threadIdx.x < kEmbSeg + 2) {
+    const int i = e0 - 1 + (int)threadIdx.x;
+    s_key[threadIdx.x] = i >= 0 && i < n ? keys[i] : -1;
+    if (threadIdx.x < kEmbSeg) {
+      const int pos = i + 1 < n ? perm[i + 1] : 0;
+      s_pos[threadIdx.x] = pos;
+      if (pos < na ? da.thr : db.thr) s_drop[threadIdx.x] = drop_row(pos < na ? da : db, (uint32_t)(pos < na ? pos : pos - na));
+    }
+  }
+  __syncthreads();
+  const int c = threadIdx.x;
+  if (c >= (d >> 3)) return;
+  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  int run_begin = 0;
+  for (int k0 = 0; k0 < cnt; k0 += kEmbAhead) {
+    half8_t x[kEmbAhead], row[kEmbAhead];
+    uint32_t bits[kEmbAhead];
+    int pos[kEmbAhead], key[kEmbAhead + 1];  // the same in every lane: kept in scalar registers
+#pragma unroll
+    for (int u = 0; u <= kEmbAhead; ++u) key[u] = __builtin_amdgcn_readfirstlane(s_key[min(k0 + u, cnt) + 1]);
+#pragma unroll
+    for (int u = 0; u < kEmbAhead; ++u) {
+      pos[u] = __builtin_amdgcn_readfirstlane(s_pos[min(k0 + u, cnt - 1)]);  // (an entry past the end repeats the last one and is not added)
+      x[u] = ld_half8((pos[u] < na ? dxa + (size_t)pos[u] * d : dxb + (size_t)(pos[u] - na) * d) + c * 8);
+      row[u] = zero_half8();
+      if (key[u + 1] != key[u] && key[u] >= 0) row[u] = ld_half8(gE + (size_t)key[u] * d + c * 8);  // the run ends here: its row is needed
+    }
+#pragma unroll
+    for (int u = 0; u < kEmbAhead; ++u) {
+      const bool in_a = pos[u] < na;
+      bits[u] = (in_a ? da.thr : db.thr) ? drop_keep8(in_a ? da : db, s_drop[min(k0 + u, cnt - 1)], (uint32_t)c) : 0xFFu;
+    }
+#pragma unroll
+    for (int u = 0; u < kEmbAhead; ++u) {
+      const int k = k0 + u;
+      if (k >= cnt) break;
+      const float sc = pos[u] < na ? (da.thr ? da.scale : 1.f) : (db.thr ? db.scale : 1.f);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] += ((bits[u] >> e) & 1u) ? (float)x[u][e] * sc : 0.f;
+      const bool goes_on = key[u + 1] == key[u];
+      if (goes_on && k + 1 < cnt) continue;
+      const bool came_in = run_begin == 0 && __builtin_amdgcn_readfirstlane(s_key[0]) == key[u];
+      if (!came_in && !goes_on) {
+        emb_add(gE + (size_t)key[u] * d + c * 8, row[u], d, acc, scale);
+      } else {
+        float* dst = part + ((size_t)2 * blockIdx.x + (came_in ? 0 : 1)) * d + c * 8;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dst[e] = acc[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+      run_begin = k + 1;
     }
   }
 }
@@ -1155,19 +1223,26 @@ int launch_embed_sum(const half_t* dx_a, int rows_a, const DropDev& drop_a, cons
     hipLaunchKernelGGL(kernel, dim3(e.nseg), dim3(threads), lds, stream, dx_a, rows_a, drop_a, dx_b, drop_b, gE, n, d, keys, perm, part, scale);
     return NMT_OK;
   };
-  // THREADS / (d / 8) groups times AHEAD entries are a segment or more.  From four segments per compute unit on the table's rows are asked for late and
-  // rows of 1024 take four wavefronts: what counts then is how many blocks share a compute unit, not the length of one (35700 x
-  // 1024, distinct ids: 42.6 us early and on eight, 38.3 so; 6600 x 512, all beside the last weight gradients: 14 late, 9.7 early).
-  auto form = [&](auto early) -> int {
-    constexpr bool E = decltype(early)::value;
-    const int chunks = d / 8;
-    if (chunks <= 256 / kEmbSeg) return segments(emb_segment_kernel<256, 1, E>, 256);
-    if (chunks <= 512 / kEmbSeg) return segments(emb_segment_kernel<256, 2, E>, 256);
-    if (chunks <= 1024 / kEmbSeg) return segments(emb_segment_kernel<256, 4, E>, 256);
-    if (chunks <= 2048 / kEmbSeg) return E ? segments(emb_segment_kernel<512, 4, E>, 512) : segments(emb_segment_kernel<256, 8, false>, 256);
-    return segments(emb_segment_kernel<1024, 4, E>, 1024);
-  };
-  if (int rc = e.nseg < 4 * device_info().cus ? form(std::true_type{}) : form(std::false_type{})) return rc;
+  // Entries shared out while the segments are few to a compute unit: one where a block takes 1024 threads, three where it takes 512, ten where a row is
+  // a wavefront wide; at any number up to 256 columns.  By entries, shared out / a thread per eight columns, us, on 256 compute units: 2048 wide 2800 12.1 /
+  // 15.6, 5000 21.7 / 18.0, 105000 165 / 121; 1024 wide 10000 16.1 / 17.9, 14000 20.2 / 18.7, 105000 77 / 67 (beside the last weight gradients 311 /
+  // 251); 512 wide 35700 20.1 / 20.6, 42000 22.1 / 21.7, 200000 72.8 / 64.9; 256 wide 200000 49.6 / 60.2.
+  const int chunks = d / 8, cus = device_info().cus, few = (chunks > 128 ? 1 : chunks > 64 ? 3 : 10) * cus;
+  if (chunks > 32 && e.nseg > few) {
+    hipLaunchKernelGGL(emb_segment_columns_kernel, dim3(e.nseg), dim3((int)round_up(chunks, kWave)), 0, stream, dx_a, rows_a, drop_a, dx_b, drop_b, gE, n, d,
+                       keys, perm, part, scale);
+  } else {
+    // THREADS / (d / 8) groups times AHEAD entries are a segment or more.  From four segments per compute unit on the table's rows are asked for late: what
+    // counts then is how many blocks share a compute unit, not the length of one (6600 x 512, all beside the last weight gradients: 14 late, 9.7 early).
+    auto form = [&](auto early) -> int {
+      constexpr bool E = decltype(early)::value;
+      if (chunks <= 256 / kEmbSeg) return segments(emb_segment_kernel<256, 1, E>, 256);
+      if (chunks <= 512 / kEmbSeg) return segments(emb_segment_kernel<256, 2, E>, 256);
+      if (chunks <= 1024 / kEmbSeg) return segments(emb_segment_kernel<256, 4, E>, 256);
+      return chunks <= 2048 / kEmbSeg ? segments(emb_segment_kernel<512, 4, true>, 512) : segments(emb_segment_kernel<1024, 4, true>, 1024);
+    };
+    if (int rc = e.nseg < 4 * cus ? form(std::true_type{}) : form(std::false_type{})) return rc;
+  }
   NMT_LAUNCH_CHECK();
   hipLaunchKernelGGL(emb_finish_kernel, dim3(e.nseg), dim3(kEmbFinish), 0, stream, gE, n, d, keys, part, scale);
   NMT_LAUNCH_CHECK();

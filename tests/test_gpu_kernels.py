@@ -617,6 +617,38 @@ def test_embedding_backward_run_and_list_borders(d, V, na, nb, kind):
     assert_close16(host(gE), want, f"embedding backward {kind} {n}", rel=2e-3, l2=1e-3)
 
 
+# The last list whose segments are shared out over a block and the first that takes a thread per eight columns, on both sides of each line (one,
+# three and ten segments per compute unit), with widths that divide a block evenly and not; dropout over two id streams.
+@pytest.mark.parametrize("d,V,per_cu,kind", [(1032, 304, 1, "zipf"), (2048, 304, 1, "border"), (520, 304, 3, "border"), (1024, 1000, 3, "zipf"),
+                                             (264, 3000, 10, "border"), (512, 304, 10, "zipf")])
+def test_embedding_backward_on_both_sides_of_each_form(d, V, per_cu, kind):
+    rng = np.random.default_rng(d)
+    last = 16 * per_cu * torch.cuda.get_device_properties(0).multi_processor_count
+    n_pos, p, seed = 41, 0.25, 77
+    for n in (last, last + 1):
+        rows = [n // 3, n - n // 3]
+        ids = rng.permutation(np.minimum(np.arange(n) // 16, V - 1)) if kind == "border" else np.minimum(rng.zipf(1.3, size=n), V) - 1
+        dx = torch.randn(n, d, generator=torch.Generator(device=DEV).manual_seed(n), device=DEV).half()
+        g0 = dev16(rng.normal(size=(V, d)))
+        parts = (slice(0, rows[0]), slice(rows[0], n))
+        drops = [_drop(p, site, 5, 1, seed, n_pos) for site in (0, 1)]
+        want = host(g0)
+        for part, drop, m in zip(parts, drops, rows):
+            keep = torch.empty(m, d, dtype=torch.uint8, device=DEV)
+            A.nmt_op_dropout_mask(keep, m, d, drop)
+            hot = torch.zeros(V, m, dtype=torch.float64, device=DEV).index_put_((devi(ids[part]).long(), torch.arange(m, device=DEV)), torch.ones((), dtype=torch.float64, device=DEV))
+            want += host(hot @ (dx[part].double() * keep)) * math.sqrt(d) / (1 - float(np.float32(p)))
+        outs = []
+        for _ in range(2):
+            gE = g0.clone()
+            scratch = torch.full((A.nmt_op_embed_bwd_scratch(V, n, d),), -1, dtype=torch.int32, device=DEV)
+            ids_d = devi(ids)
+            A.nmt_op_embed_bwd(ids_d[parts[0]], dx[parts[0]], rows[0], drops[0], ids_d[parts[1]], dx[parts[1]], rows[1], drops[1], gE, d, V, scratch)
+            outs.append(host(gE))
+        assert (outs[0] == outs[1]).all()
+        assert_close16(outs[0], want, f"embedding backward {d} {n}", rel=2e-3, l2=1e-3)
+
+
 # ---- fused softmax + label-smoothed cross-entropy -------------------------------------------------
 @pytest.mark.parametrize("rows,V,scale", [(128, 1000, 128.0), (37, 32768, 128.0), (9, 40000, 1.0), (16, 8, 4.0), (20, 2056, 2.0 ** 27)])
 def test_softmax_xent_matches_oracle(rows, V, scale):
