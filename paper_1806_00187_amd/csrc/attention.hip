@@ -113,7 +113,10 @@ __device__ __forceinline__ Item work_item(const AttnArgs& a, int bx, int by, int
   const int hg = (a.H + wpb - 1) / wpb;
   const int idx = bx / hg;
   Item it;
-  it.h = (bx % hg) * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // (known to be the wavefront's: addresses stay scalar)
+  // (known to be the wavefront's, so that addresses stay scalar; not for LIST 2, whose kernel for two tiles of 128 columns then spills 324 bytes a lane
+  // instead of 220: backward of 216 sentences of up to 60, 8 heads of 128, 358 us against 338)
+  const int wave = threadIdx.x >> 6;
+  it.h = (bx % hg) * wpb + (LIST == 2 ? wave : __builtin_amdgcn_readfirstlane(wave));
   it.tile = by;
   it.live = it.h < a.H;
   if (LIST == 1 && a.wl_qsent) {
