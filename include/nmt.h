@@ -346,8 +346,8 @@ int nmt_op_colsum_static(const void* d_src, int32_t ld, void* d_dst, int32_t row
 
 /* Embedding backward: d_gE[v, :] = fp16(float(d_gE[v, :]) + sqrt(d) * sum over positions r with
  * ids[r] == v of dropout-masked d_dx[r, :]), for two id streams (source then target) at once.
- * Deterministic: every sum is formed in a fixed order (increasing position within blocks of 64
- * positions of an id, then block after block).  d_scratch: 16-byte aligned int32 scratch of
+ * Deterministic: every sum is formed in a fixed order (the positions, sorted by id, in pieces of 16:
+ * increasing position within a piece, then the pieces of an id in a fixed order).  d_scratch: 16-byte aligned int32 scratch of
  * nmt_op_embed_bwd_scratch(vocab, rows_a + rows_b, d) int32 elements.  vocab <= 65536. */
 int64_t nmt_op_embed_bwd_scratch(int32_t vocab, int32_t rows_total, int32_t d);
 int nmt_op_embed_bwd(const int32_t* d_ids_a, const void* d_dx_a, int32_t rows_a, const nmt_dropout* drop_a,

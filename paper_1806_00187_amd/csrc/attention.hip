@@ -4,9 +4,11 @@
 // memory.  All products run on 32x32x16 fp16 MFMAs.
 //
 // Sentences here are short (tens of positions), so the unit of work is small: ONE WAVEFRONT per
-// (sentence, head, 32-row tile), and in all kernels but the backward one by key tiles no work-group barrier anywhere.  Operands whose contraction index is contiguous in memory (Q, K, V, dO rows
-// against the head dimension) are loaded as whole rows and turn into MFMA operand registers in LDS (forward, and backward by key tiles)
-// or go straight there, 16 bytes per lane.  An operand that is contracted over its row index (V in P V, K in dS K, Q and
+// (sentence, head, 32-row tile), and in all kernels but the backward one by key tiles no work-group
+// barrier anywhere.  Operands whose contraction index is contiguous in memory (Q, K, V, dO rows
+// against the head dimension) are loaded as whole rows and turn into MFMA operand registers in LDS
+// (forward, and backward by key tiles) or go straight there, 16 bytes per lane.  An operand that is
+// contracted over its row index (V in P V, K in dS K, Q and
 // dO in dS^T Q and P^T dO) passes through a wavefront-private 32-row LDS tile and comes back through
 // the transposing LDS read.
 //
@@ -652,9 +654,11 @@ __global__ void __launch_bounds__(kThreads) attn_bwd_fused_kernel(const AttnArgs
 // wavefront (nt here, nt * nt with one wavefront per sentence and head, whose unrolled code of up to 69 KB also
 // had to be fetched) and the number of launches.  Per pass of 18 attentions, with the instances per length it replaces: fourteen
 // sentences of up to 256 positions, 8 heads: 930 -> 370 us; 130 of 16 to 40: 405 -> 268; 53000 positions, 16 heads: 5.3 -> 4.9 ms
-// (beside the weight gradients).  What bounds it at these lengths is trips to memory: everything a wavefront needs is asked for at once (K and V
-// used to follow Q, dO and O): per call 14.9 -> 14.0 us for 148 sentences of 24, 20.6 -> 20.1 for fourteen of up to 256, 40.7 -> 37.7 for 480 of about 27; and as whole rows, which turn into operands in LDS (on average in whole updates,
-// beside the weight gradients: 3100 positions x 512 13.9 -> 13.4 us, fourteen sentences of up to 256 20.2 -> 18.3, 13000 x 512 43.9 -> 41.0, 17700 x 1024 82.5 -> 78.3).
+// (beside the weight gradients).  What bounds it at these lengths is trips to memory.  Everything a wavefront needs is asked for at
+// once (K and V used to follow Q, dO and O): per call 14.9 -> 14.0 us for 148 sentences of 24, 20.6 -> 20.1 for fourteen of up
+// to 256, 40.7 -> 37.7 for 480 of about 27.  It comes as whole rows, which turn into operands in LDS: on average in whole updates,
+// beside the weight gradients, 3100 positions x 512 13.9 -> 13.4 us, fourteen sentences of up to 256 20.2 -> 18.3, 13000 x 512
+// 43.9 -> 41.0, 17700 x 1024 82.5 -> 78.3; 53000 x 1024 alone the same (225 / 227).
 // ------------------------------------------------------------------------------------------------
 constexpr int kBwdTiles = 8;  // longest sentence, in tiles
 template <int DH>

@@ -533,9 +533,17 @@ def test_residual_layernorm_forward_and_backward_match_oracle(rows, n_pos, d, p)
     assert_close16(host(gbias), dym_ref.sum(0), "dbias")
 
 
-# the last size with one row per wavefront, the first with two, an odd last row, more rows than the resident grid holds at once
+# the last size with one row per wavefront on four wavefronts, the first with two rows (wider than 512 columns), an odd last row, more rows than the
+# resident grid holds at once
 @pytest.mark.parametrize("rows,n_pos,d,p", [(1024, 32, 64, 0.1), (1025, 41, 1024, 0.3), (1025, 25, 2048, 0.1), (3003, 33, 512, 0.0), (9009, 99, 72, 0.2)])
 def test_residual_layernorm_of_many_rows_matches_oracle(rows, n_pos, d, p):
+    test_residual_layernorm_forward_and_backward_match_oracle(rows, n_pos, d, p)
+
+
+# up to 512 columns there are work-groups of eight wavefronts with one row each in between: the first and the last size of that form, with
+# columns of which the eight wavefronts' sums leave some, half and all of a work-group's threads one, and the first size behind it
+@pytest.mark.parametrize("rows,n_pos,d,p", [(1025, 41, 8, 0.1), (1025, 25, 512, 0.3), (2048, 64, 264, 0.0), (2047, 89, 72, 0.2), (2049, 683, 512, 0.1)])
+def test_residual_layernorm_on_eight_wavefronts_matches_oracle(rows, n_pos, d, p):
     test_residual_layernorm_forward_and_backward_match_oracle(rows, n_pos, d, p)
 
 
@@ -636,7 +644,7 @@ def test_embedding_backward_on_both_sides_of_each_form(d, V, per_cu, kind):
         for part, drop, m in zip(parts, drops, rows):
             keep = torch.empty(m, d, dtype=torch.uint8, device=DEV)
             A.nmt_op_dropout_mask(keep, m, d, drop)
-            hot = torch.zeros(V, m, dtype=torch.float64, device=DEV).index_put_((devi(ids[part]).long(), torch.arange(m, device=DEV)), torch.ones((), dtype=torch.float64, device=DEV))
+            hot = torch.nn.functional.one_hot(devi(ids[part]).long(), V).double().T
             want += host(hot @ (dx[part].double() * keep)) * math.sqrt(d) / (1 - float(np.float32(p)))
         outs = []
         for _ in range(2):
