@@ -205,7 +205,7 @@ double nmt_lr_schedule(int64_t t, double peak, int64_t warmup);
 int nmt_debug_activation(const nmt_ctx* ctx, const char* name, const void** d_ptr, int64_t* rows, int64_t* cols);
 
 /* Host only.  Process-wide switches of launch forms, for tests and profiling; none of them changes a
- * result bit.  name: "gemm_group" (tile rows swept together, >= 1; default 4), "gemm_persist" (0: never the
+ * result bit but "row_chain", which changes the rounding of gradients.  name: "gemm_group" (tile rows swept together, >= 1; default 4), "gemm_persist" (0: never the
  * persistent GEMM form / 1: for 256 x 256 tiles with one of its epilogues; default 1),
  * "attn_persist" (0: one attention work item per work-group; default 1), "worklists" (0: attention
  * kernels enumerate every (sentence, tile); default 1), "one_stream" (1: forward and backward passes enqueue everything
@@ -213,7 +213,8 @@ int nmt_debug_activation(const nmt_ctx* ctx, const char* name, const void** d_pt
  * caller keeps running side by side on streams of its own; large tiles are then chosen as if each product had
  * that fraction of the compute units), "gemm_tile" (0: tile shape chosen per product, the default; 1..5: every
  * product that is not cut along k, except a layer's weight gradients, takes 256x256 / 128x128 / 128x64 / 64x128 / 64x64
- * tiles), "gemm_timing" (1: every GEMM product, and every launch of a layer's weight gradients, is bracketed by a pair of
+ * tiles), "row_chain" (0: the operations between two attentions of a narrow model are launches of their own; default 1; not to be
+ * changed between a forward call and its backward call), "gemm_timing" (1: every GEMM product, and every launch of a layer's weight gradients, is bracketed by a pair of
  * HIP events on the stream it is launched on; default 0), "defaults" (value ignored: all of the above back to
  * default).  Unknown names and values out of range return NMT_EINVAL. */
 int nmt_tuning(const char* name, int32_t value);

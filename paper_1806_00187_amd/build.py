@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnmt.so")
-SOURCES = ["nmt.hip", "gemm.hip", "gemm_f32.hip", "attention.hip", "rowops.hip", "optim.hip"]
+SOURCES = ["nmt.hip", "gemm.hip", "gemm_f32.hip", "attention.hip", "rowops.hip", "rowchain.hip", "optim.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 

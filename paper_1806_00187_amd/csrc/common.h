@@ -54,6 +54,7 @@ struct Tuning {
   int one_stream = 0;     // 1: forward and backward passes keep to the caller's stream
   int gemm_share = 1;     // products expected to run side by side (callers that keep several passes in flight): large tiles
                           // are chosen as if each product had 1/gemm_share of the compute units
+  int row_chain = 1;      // 0: narrow models' operations between two attentions are launches of their own
   int gemm_tile = 0;      // experiments: 0 = chosen per product; 1..5 force 256x256, 128x128, 128x64, 64x128, 64x64 tiles (products not cut along k, no weight-gradient groups)
   int gemm_timing = 0;    // 1: every GEMM product (a weight-gradient group: its launch) is bracketed by HIP events on its launch stream (nmt_gemm_timing reads them)
 };
@@ -289,6 +290,46 @@ int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const h
                                   half_t* dbias, float* partial, int rows, int d, const DropDev& drop,
                                   hipStream_t stream, ColumnSums& sums);
 int launch_layernorm_param_grads(const ColumnSums* sums, int n, int d, float scale, hipStream_t stream);  // scale: factor on all of them
+// What lies between two attentions of a narrow model, row by row, in one launch each way (d = 64, 128 or 256; see row_chain_fits).  Rows of
+// d columns are contiguous.  Forward: s1 = o wo^T + bo, x1 = LN(x + dropout(s1)); if F: h = relu(x1 w1^T + b1), s2 = h w2^T + b2, x2 = LN(x1 +
+// dropout(s2)); then projections of the last of these.
+constexpr int kMaxRowChainProj = 4;
+struct RowChainLn {
+  const half_t *gamma, *beta;
+  half_t *sub, *out;  // s and x of the sub-layer
+  float* stats;
+  DropDev drop;
+};
+struct RowChainFwd {
+  int rows, F, n_proj;
+  float eps;
+  const half_t *o, *wo, *bo, *x;
+  RowChainLn ln1, ln2;
+  const half_t *w1, *b1, *w2, *b2;
+  half_t* h;
+  struct Proj { const half_t *w, *b; half_t* out; int n; } proj[kMaxRowChainProj];
+};
+// Backward: the gradient at the last LayerNorm's output is dx, or head_a head_w + dy_in if head_k (the columns of head_a); LayerNorm a; if F: the
+// feed-forward sub-layer and LayerNorm b; then dO = dsub wo.  `dsub` of a LayerNorm may be where ITS sub-layer's predecessor in the order of the backward pass
+// (LayerNorm a for b) has its `sub`, dy_out where dy_in is.  dy_out null: not wanted (without dropout it is dsub).
+struct RowChainLnBwd {
+  const half_t *sub, *resid, *gamma;
+  const float* stats;
+  half_t* dsub;
+  float* partial;     // row_chain_blocks(rows) partial rows of 3 d
+  DropDev drop;
+};
+struct RowChainBwd {
+  int rows, F, head_k;
+  const half_t *head_a, *head_w, *dy_in, *dx;
+  RowChainLnBwd ln_a, ln_b;
+  const half_t *w2, *h, *w1, *wo;
+  half_t *dh, *dy_out, *dO;
+};
+bool row_chain_fits(int d, int F);
+int row_chain_blocks(int rows);
+int launch_row_chain_fwd(const RowChainFwd& a, int d, hipStream_t stream);
+int launch_row_chain_bwd(const RowChainBwd& a, int d, hipStream_t stream);
 // All products (1..kMaxWgrad of them, results times out_scale) in one launch, or two if they are cut along k.  partial: fp32 scratch for that
 // (may be null: never cut).  tile, splits: 0 = chosen by cost.
 // sums: partial rows of d columns (a layer's LayerNorm gradients) that are added up as well, times out_scale: in the same launch where that is one of

@@ -45,6 +45,7 @@ extern "C" int nmt_tuning(const char* name, int32_t value) {
   else if (!strcmp(name, "attn_persist")) t.attn_persist = value != 0;
   else if (!strcmp(name, "worklists")) t.worklists = value != 0;
   else if (!strcmp(name, "one_stream")) t.one_stream = value != 0;
+  else if (!strcmp(name, "row_chain")) t.row_chain = value != 0;
   else if (!strcmp(name, "gemm_share")) { NMT_REQUIRE(value >= 1 && value <= 16, "nmt_tuning: gemm_share must be in [1, 16]"); t.gemm_share = value; }
   else if (!strcmp(name, "gemm_tile")) { NMT_REQUIRE(value >= 0 && value <= 5, "nmt_tuning: gemm_tile is 0..5"); t.gemm_tile = value; }
   else if (!strcmp(name, "gemm_timing")) t.gemm_timing = value != 0;
@@ -442,6 +443,15 @@ bool encoder_products_beside(const nmt_ctx* c) {
   return use_second_stream(c) && (int64_t)ceil_div(c->Ns, 256) * ceil_div(2 * c->cfg.d_model, 256) < device_info().cus;
 }
 
+// Whether the operations between two attentions are one launch each way (both passes of a forward / backward pair decide alike).  256 wide a work-group
+// has 1.5 MB of weights to read, which a second round of work-groups doubles and the general kernels share among more rows; narrower models gain
+// up to four rounds and more (figures: rowchain.hip).
+bool use_row_chains(const nmt_ctx* c) {
+  const int rows = c->Ns > c->Nt ? c->Ns : c->Nt, d = c->cfg.d_model, rounds = d == 256 ? 1 : 4;
+  return tuning().row_chain && c->cfg.act_dropout == 0.f && row_chain_fits(d, c->cfg.d_ff) && row_chain_blocks(rows) <= rounds * device_info().cus &&
+         (int64_t)row_chain_blocks(rows) * 3 * d <= layernorm_bwd_partial_floats(rows, d);  // (the partial sums lie where the row kernels' do)
+}
+
 struct Run {
   nmt_ctx* c;
   hipStream_t st;
@@ -600,6 +610,23 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
   const AttnWork wl_ss = attention_work(r.ws<int32_t>(p.wl_ss), Bt, Ns, 0), wl_tt = attention_work(r.ws<int32_t>(p.wl_tt), Bt, Nt, 0),
                  wl_ts = attention_work(r.ws<int32_t>(p.wl_ts), Bt, Nt, Ns);
 
+  const bool chains = use_row_chains(c);
+  // a chain up to its first LayerNorm, a feed-forward sub-layer behind it, a projection at its end
+  auto chain = [&](const Run& on, bool tgt, const AttnP& a, int64_t o, const half_t* resid, const LnP& ln, int64_t s, int64_t x_out, int64_t st_out, uint32_t site) {
+    RowChainFwd f = {};
+    f.rows = tgt ? Nt : Ns;
+    f.eps = k.ln_eps;
+    f.o = on.ws<half_t>(o); f.wo = on.w(a.wo); f.bo = on.w(a.bo); f.x = resid;
+    f.ln1 = {on.w(ln.g), on.w(ln.b), on.ws<half_t>(s), on.ws<half_t>(x_out), on.ws<float>(st_out), on.drop(site, tgt, k.dropout)};
+    return f;
+  };
+  auto chain_ffn = [&](RowChainFwd& f, const Run& on, bool tgt, const FfnP& ffn, int64_t h, const LnP& ln, int64_t s, int64_t x_out, int64_t st_out, uint32_t site) {
+    f.F = F;
+    f.w1 = on.w(ffn.w1); f.b1 = on.w(ffn.b1); f.w2 = on.w(ffn.w2); f.b2 = on.w(ffn.b2); f.h = on.ws<half_t>(h);
+    f.ln2 = {on.w(ln.g), on.w(ln.b), on.ws<half_t>(s), on.ws<half_t>(x_out), on.ws<float>(st_out), on.drop(site, tgt, k.dropout)};
+  };
+  auto chain_proj = [&](RowChainFwd& f, const Run& on, int64_t w, int64_t b, int64_t out, int n) { f.proj[f.n_proj++] = {on.w(w), on.w(b), on.ws<half_t>(out), n}; };
+
   // a decoder layer up to the queries of its encoder-decoder attention
   auto decoder_self = [&](const Run& on, int l) -> int {
     const DecP& P = c->dec[l];
@@ -607,9 +634,14 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
     const int li = k.enc_layers + l;
     const half_t* y = l ? on.ws<half_t>(p.dec[l - 1].x3) : on.ws<half_t>(p.y0);
     half_t* qkv = on.ws<half_t>(W.qkv);
-    NMT_TRY(on.linear(y, Nt, d, P.self.wqkv, P.self.bqkv, 3 * d, qkv));
+    if (!chains || !l) NMT_TRY(on.linear(y, Nt, d, P.self.wqkv, P.self.bqkv, 3 * d, qkv));
     NMT_TRY(launch_attention_fwd(qkv, 3 * d, qkv + d, 3 * d, qkv + 2 * d, 3 * d, on.ws<half_t>(W.o1), d, on.ws<float>(W.lse1), d_tgt_in,
                                  k.pad_id, 1, Bt, H, dh, maxT, maxT, tab_tt, Nt, &wl_tt, on.st));
+    if (chains) {
+      RowChainFwd f = chain(on, true, P.self, W.o1, y, P.ln1, W.s1, W.x1, W.st1, layer_site(li, kKindSelfRes));
+      chain_proj(f, on, P.cross.wq, P.cross.bq, W.q, d);
+      return launch_row_chain_fwd(f, d, on.st);
+    }
     NMT_TRY(on.linear(on.ws<half_t>(W.o1), Nt, d, P.self.wo, P.self.bo, d, on.ws<half_t>(W.s1)));
     NMT_TRY(launch_residual_layernorm_fwd(on.ws<half_t>(W.s1), y, on.w(P.ln1.g), on.w(P.ln1.b), on.ws<half_t>(W.x1), on.ws<float>(W.st1),
                                           Nt, d, k.ln_eps, on.drop(layer_site(li, kKindSelfRes), true, k.dropout), on.st));
@@ -635,15 +667,27 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
   };
 
   // ---- encoder ----
+  const int chained_kv = chains ? std::min(k.dec_layers, kMaxRowChainProj) : 0;  // decoder layers whose keys and values end the encoder's last chain
   half_t* x = r.ws<half_t>(p.x0);
   NMT_TRY(launch_embed_fwd(d_src, r.w(c->embed), x, Ns, d, V, r.drop(kSiteEmbSrc, false, k.dropout), st));
   for (int l = 0; l < k.enc_layers; ++l) {
     const EncP& P = c->enc[l];
     const EncW& W = p.enc[l];
     half_t* qkv = r.ws<half_t>(W.qkv);
-    NMT_TRY(r.linear(x, Ns, d, P.attn.wqkv, P.attn.bqkv, 3 * d, qkv));
+    if (!chains || !l) NMT_TRY(r.linear(x, Ns, d, P.attn.wqkv, P.attn.bqkv, 3 * d, qkv));
     NMT_TRY(launch_attention_fwd(qkv, 3 * d, qkv + d, 3 * d, qkv + 2 * d, 3 * d, r.ws<half_t>(W.o), d, r.ws<float>(W.lse), d_src,
                                  k.pad_id, 0, Bt, H, dh, maxS, maxS, tab_ss, Ns, &wl_ss, st));
+    if (chains) {
+      RowChainFwd f = chain(r, false, P.attn, W.o, x, P.ln1, W.s1, W.x1, W.st1, layer_site(l, kKindSelfRes));
+      chain_ffn(f, r, false, P.ffn, W.h, P.ln2, W.s2, W.x2, W.st2, layer_site(l, kKindFfnRes));
+      if (l + 1 < k.enc_layers) chain_proj(f, r, c->enc[l + 1].attn.wqkv, c->enc[l + 1].attn.bqkv, p.enc[l + 1].qkv, 3 * d);
+      else
+        for (int j = 0; j < chained_kv; ++j) chain_proj(f, r, c->dec[j].cross.wkv, c->dec[j].cross.bkv, p.dec[j].kv, 2 * d);
+      NMT_TRY(launch_row_chain_fwd(f, d, st));
+      x = r.ws<half_t>(W.x2);
+      if (self_beside && l == 0) NMT_TRY(decoder_ahead());
+      continue;
+    }
     NMT_TRY(r.linear(r.ws<half_t>(W.o), Ns, d, P.attn.wo, P.attn.bo, d, r.ws<half_t>(W.s1)));
     NMT_TRY(launch_residual_layernorm_fwd(r.ws<half_t>(W.s1), x, r.w(P.ln1.g), r.w(P.ln1.b), r.ws<half_t>(W.x1), r.ws<float>(W.st1),
                                           Ns, d, k.ln_eps, r.drop(layer_site(l, kKindSelfRes), false, k.dropout), st));
@@ -663,12 +707,13 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
   auto project_kv = [&](const Run& on, int l) {
     return on.linear(enc_out, Ns, d, c->dec[l].cross.wkv, c->dec[l].cross.bkv, 2 * d, r.ws<half_t>(p.dec[l].kv));
   };
-  if (beside && k.dec_layers > 1) {
+  const int kv_ahead = std::max(1, chained_kv);  // (the first layer's are on the caller's stream in any case)
+  if (beside && k.dec_layers > kv_ahead) {
     NMT_TRY(ensure_second_stream(c));
     const Run side{c, c->side};
     NMT_HIP_CHECK(hipEventRecord(c->ev_fork, st));
     NMT_HIP_CHECK(hipStreamWaitEvent(c->side, c->ev_fork, 0));
-    for (int l = 1; l < k.dec_layers; ++l) NMT_TRY(project_kv(side, l));
+    for (int l = kv_ahead; l < k.dec_layers; ++l) NMT_TRY(project_kv(side, l));
     NMT_HIP_CHECK(hipEventRecord(c->ev_join, c->side));
   }
 
@@ -681,11 +726,19 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
     const int li = k.enc_layers + l;
     half_t* kv = r.ws<half_t>(W.kv);
     if (!self_beside || l) NMT_TRY(decoder_self(r, l));
-    if (!beside || !l) NMT_TRY(project_kv(r, l));
+    if (l >= chained_kv && (!beside || !l)) NMT_TRY(project_kv(r, l));
     if (self_beside && l == 0) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_self, 0));
-    if (beside && l == 1) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_join, 0));
+    if (beside && l == kv_ahead) NMT_HIP_CHECK(hipStreamWaitEvent(st, c->ev_join, 0));
     NMT_TRY(launch_attention_fwd(r.ws<half_t>(W.q), d, kv, 2 * d, kv + d, 2 * d, r.ws<half_t>(W.o2), d, r.ws<float>(W.lse2), d_src,
                                  k.pad_id, 0, Bt, H, dh, maxT, maxS, tab_ts, Nt, &wl_ts, st));
+    if (chains) {
+      RowChainFwd f = chain(r, true, P.cross, W.o2, r.ws<half_t>(W.x1), P.ln2, W.s2, W.x2, W.st2, layer_site(li, kKindCrossRes));
+      chain_ffn(f, r, true, P.ffn, W.h, P.ln3, W.s3, W.x3, W.st3, layer_site(li, kKindFfnRes));
+      if (l + 1 < k.dec_layers) chain_proj(f, r, c->dec[l + 1].self.wqkv, c->dec[l + 1].self.bqkv, p.dec[l + 1].qkv, 3 * d);
+      NMT_TRY(launch_row_chain_fwd(f, d, st));
+      y = r.ws<half_t>(W.x3);
+      continue;
+    }
     NMT_TRY(r.linear(r.ws<half_t>(W.o2), Nt, d, P.cross.wo, P.cross.bo, d, r.ws<half_t>(W.s2)));
     NMT_TRY(launch_residual_layernorm_fwd(r.ws<half_t>(W.s2), r.ws<half_t>(W.x1), r.w(P.ln2.g), r.w(P.ln2.b), r.ws<half_t>(W.x2),
                                           r.ws<float>(W.st2), Nt, d, k.ln_eps, r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st));
@@ -800,6 +853,33 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     return NMT_OK;
   };
 
+  // The same as chains: everything from one attention's backward to the next one's.  What is still to be multiplied when a
+  // chain begins (the gradient at the projections of the attention behind it) is its head.
+  const bool chains = use_row_chains(c);
+  struct Head { const half_t* a; int k; int64_t w; const half_t* dy; } head = {};
+  auto chain_ln = [&](int N, bool tgt, const half_t* sub, const half_t* resid, const float* stats, const LnP& ln, int64_t bias, uint32_t site) {
+    begin_sublayer(sub);
+    ln_sums[sub_at - 1] = ColumnSums{lnpart, row_chain_blocks(N), {r.g(ln.g), r.g(ln.b), r.g(bias)}};
+    return RowChainLnBwd{sub, resid, r.w(ln.g), stats, const_cast<half_t*>(dsub), lnpart, r.drop(site, tgt, k.dropout)};
+  };
+  // (dx: the gradient at the layer's output where no head leaves it to the chain)
+  auto layer_chain = [&](const half_t* dx, int N, bool tgt, const half_t* x2, const half_t* hact, const half_t* s3, const float* st3, const FfnP& f, const LnP& ln3,
+                         uint32_t site3, const half_t* x1, const half_t* s2, const float* st2, const half_t* o, const AttnP& a, const LnP& ln2, uint32_t site2) -> int {
+    RowChainBwd b = {};
+    b.rows = N;
+    b.F = F;
+    b.head_a = head.a; b.head_k = head.k; b.head_w = head.k ? r.w(head.w) : nullptr; b.dy_in = head.dy; b.dx = dx;
+    head = {};
+    b.ln_a = chain_ln(N, tgt, s3, x2, st3, ln3, f.b2, site3);
+    leaf(dsub, N, d, hact, F, f.w2);
+    b.w2 = r.w(f.w2); b.h = hact; b.dh = dhid; b.w1 = r.w(f.w1);
+    leaf(dhid, N, F, x2, d, f.w1, f.b1);
+    b.ln_b = chain_ln(N, tgt, s2, x1, st2, ln2, a.bo, site2);
+    leaf(dsub, N, d, o, d, a.wo);
+    b.dy_out = dropping ? dy : nullptr; b.wo = r.w(a.wo); b.dO = dO;
+    return launch_row_chain_bwd(b, d, st);
+  };
+
   // feed-forward sub-layer: out = LN(x_in + drop(relu(x_in W1^T + b1) W2^T + b2)); dx holds d out on entry, d x_in on exit
   auto ffn_bwd = [&](half_t* dx, int N, bool tgt, const half_t* x_in, const half_t* hact, const half_t* sub, const float* stats,
                      const FfnP& f, const LnP& ln, uint32_t site_res) -> int {
@@ -816,15 +896,28 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     res.add = dy;
     return r.dgrad(dhid, N, F, f.w1, d, dx, res);
   };
-  // self-attention sub-layer (fused q, k, v projection); `on`: the stream its chain runs on
-  auto self_bwd = [&](const Run& on, half_t* dx, int N, bool tgt, const half_t* x_in, const half_t* qkv, const half_t* o, const float* lse,
-                      const half_t* sub, const float* stats, const AttnP& a, const LnP& ln, uint32_t site_res, const int32_t* key_ids,
-                      int causal) -> int {
+  // self-attention sub-layer (fused q, k, v projection) up to the gradient at the attention's output; `on`: the stream its chain runs on
+  auto self_out_bwd = [&](const Run& on, const half_t* dx, int N, bool tgt, const half_t* x_in, const half_t* o, const half_t* sub, const float* stats,
+                          const AttnP& a, const LnP& ln, uint32_t site_res) -> int {
+    if (chains) {
+      RowChainBwd b = {};
+      b.rows = N;
+      b.head_a = head.a; b.head_k = head.k; b.head_w = head.k ? r.w(head.w) : nullptr; b.dy_in = head.dy; b.dx = dx;
+      head = {};
+      b.ln_a = chain_ln(N, tgt, sub, x_in, stats, ln, a.bo, site_res);
+      leaf(dsub, N, d, o, d, a.wo);
+      b.dy_out = dropping ? dy : nullptr; b.wo = r.w(a.wo); b.dO = dO;
+      return launch_row_chain_bwd(b, d, on.st);
+    }
     begin_sublayer(sub);
     NMT_TRY(launch_residual_layernorm_bwd(dx, sub, x_in, r.w(ln.g), stats, dy, dym, r.g(ln.g), r.g(ln.b), r.g(a.bo), lnpart, N, d,
                                           r.drop(site_res, tgt, k.dropout), on.st, ln_sums[sub_at - 1]));
     leaf(dsub, N, d, o, d, a.wo);
-    NMT_TRY(on.dgrad(dsub, N, d, a.wo, d, dO));
+    return on.dgrad(dsub, N, d, a.wo, d, dO);
+  };
+  // ... and from there to its input (`last`: of the lowest layer, whose gradient the embeddings take from dx)
+  auto self_in_bwd = [&](const Run& on, half_t* dx, int N, bool tgt, const half_t* x_in, const half_t* qkv, const half_t* o, const float* lse,
+                         const AttnP& a, const int32_t* key_ids, int causal, bool last) -> int {
     NMT_TRY(launch_attention_bwd(qkv, 3 * d, qkv + d, 3 * d, qkv + 2 * d, 3 * d, o, d, dO, d, lse, dqkv, 3 * d, dqkv + d, 3 * d,
                                  dqkv + 2 * d, 3 * d, key_ids, k.pad_id, causal, Bt, H, dh, tgt ? maxT : maxS, tgt ? maxT : maxS,
                                  tgt ? tab_tt : tab_ss, N, tgt ? &wl_tt : &wl_ss, on.st));
@@ -836,6 +929,10 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
       return flush_leaves(false);
     }
     NMT_TRY(flush_leaves(true));  // (the self-attention sub-layer is a layer's last)
+    if (chains && !last) {
+      head = {dqkv, 3 * d, a.wqkv, dy};
+      return NMT_OK;
+    }
     return on.dgrad(dqkv, N, 3 * d, a.wqkv, d, dx, res);
   };
 
@@ -874,23 +971,33 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     const int li = k.enc_layers + l;
     const half_t* x_in = l ? r.ws<half_t>(p.dec[l - 1].x3) : r.ws<half_t>(p.y0);
     NMT_TRY(begin_layer());
-    NMT_TRY(ffn_bwd(dx, Nt, true, r.ws<half_t>(W.x2), r.ws<half_t>(W.h), r.ws<half_t>(W.s3), r.ws<float>(W.st3), P.ffn, P.ln3,
-                    layer_site(li, kKindFfnRes)));
-    // encoder-decoder attention
-    begin_sublayer(r.ws<half_t>(W.s2));
-    NMT_TRY(launch_residual_layernorm_bwd(dx, r.ws<half_t>(W.s2), r.ws<half_t>(W.x1), r.w(P.ln2.g), r.ws<float>(W.st2), dy, dym,
-                                          r.g(P.ln2.g), r.g(P.ln2.b), r.g(P.cross.bo), lnpart, Nt, d,
-                                          r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st, ln_sums[sub_at - 1]));
-    leaf(dsub, Nt, d, r.ws<half_t>(W.o2), d, P.cross.wo);
-    NMT_TRY(r.dgrad(dsub, Nt, d, P.cross.wo, d, dO));
+    if (chains) {
+      NMT_TRY(layer_chain(dx, Nt, true, r.ws<half_t>(W.x2), r.ws<half_t>(W.h), r.ws<half_t>(W.s3), r.ws<float>(W.st3), P.ffn, P.ln3,
+                          layer_site(li, kKindFfnRes), r.ws<half_t>(W.x1), r.ws<half_t>(W.s2), r.ws<float>(W.st2), r.ws<half_t>(W.o2), P.cross, P.ln2,
+                          layer_site(li, kKindCrossRes)));
+    } else {
+      NMT_TRY(ffn_bwd(dx, Nt, true, r.ws<half_t>(W.x2), r.ws<half_t>(W.h), r.ws<half_t>(W.s3), r.ws<float>(W.st3), P.ffn, P.ln3,
+                      layer_site(li, kKindFfnRes)));
+      // encoder-decoder attention
+      begin_sublayer(r.ws<half_t>(W.s2));
+      NMT_TRY(launch_residual_layernorm_bwd(dx, r.ws<half_t>(W.s2), r.ws<half_t>(W.x1), r.w(P.ln2.g), r.ws<float>(W.st2), dy, dym,
+                                            r.g(P.ln2.g), r.g(P.ln2.b), r.g(P.cross.bo), lnpart, Nt, d,
+                                            r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st, ln_sums[sub_at - 1]));
+      leaf(dsub, Nt, d, r.ws<half_t>(W.o2), d, P.cross.wo);
+      NMT_TRY(r.dgrad(dsub, Nt, d, P.cross.wo, d, dO));
+    }
     const half_t* kv = r.ws<half_t>(W.kv);
     NMT_TRY(launch_attention_bwd(r.ws<half_t>(W.q), d, kv, 2 * d, kv + d, 2 * d, r.ws<half_t>(W.o2), d, dO, d, r.ws<float>(W.lse2), dq, d,
                                  dkv, 2 * d, dkv + d, 2 * d, c->src, k.pad_id, 0, Bt, H, dh, maxT, maxS, tab_ts, Nt, &wl_ts, st));
     leaf(dq, Nt, d, r.ws<half_t>(W.x1), d, P.cross.wq, P.cross.bq);
     leaf(dkv, Ns, 2 * d, enc_out, d, P.cross.wkv, P.cross.bkv);
-    GemmEpilogue res;
-    res.add = dy;
-    NMT_TRY(r.dgrad(dq, Nt, d, P.cross.wq, d, dx, res));
+    if (chains && !(self_beside && l == 0)) {
+      head = {dq, d, P.cross.wq, dy};
+    } else {  // (a chain on the second stream takes dx: dy's place is the encoder's by then)
+      GemmEpilogue res;
+      res.add = dy;
+      NMT_TRY(r.dgrad(dq, Nt, d, P.cross.wq, d, dx, res));
+    }
     GemmEpilogue accum;
     accum.add = (l == k.dec_layers - 1) ? nullptr : denc;  // the encoder output feeds every decoder layer
     if (beside && !(self_beside && l == 0)) {
@@ -909,8 +1016,9 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
       dO = r.ws<half_t>(p.dec[1].qkv);
       dy_place = dO + (int64_t)Nt * d;
     }
-    NMT_TRY(self_bwd(self_beside && l == 0 ? side : r, dx, Nt, true, x_in, r.ws<half_t>(W.qkv), r.ws<half_t>(W.o1), r.ws<float>(W.lse1),
-                     r.ws<half_t>(W.s1), r.ws<float>(W.st1), P.self, P.ln1, layer_site(li, kKindSelfRes), c->tgt_in, 1));
+    const Run& on = self_beside && l == 0 ? side : r;
+    NMT_TRY(self_out_bwd(on, dx, Nt, true, x_in, r.ws<half_t>(W.o1), r.ws<half_t>(W.s1), r.ws<float>(W.st1), P.self, P.ln1, layer_site(li, kKindSelfRes)));
+    NMT_TRY(self_in_bwd(on, dx, Nt, true, x_in, r.ws<half_t>(W.qkv), r.ws<half_t>(W.o1), r.ws<float>(W.lse1), P.self, c->tgt_in, 1, l == 0));
   }
   if (self_beside) {
     NMT_HIP_CHECK(hipEventRecord(c->ev_self, sd));
@@ -927,10 +1035,15 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     const EncW& W = p.enc[l];
     const half_t* x_in = l ? r.ws<half_t>(p.enc[l - 1].x2) : r.ws<half_t>(p.x0);
     NMT_TRY(begin_layer());
-    NMT_TRY(ffn_bwd(denc, Ns, false, r.ws<half_t>(W.x1), r.ws<half_t>(W.h), r.ws<half_t>(W.s2), r.ws<float>(W.st2), P.ffn, P.ln2,
-                    layer_site(l, kKindFfnRes)));
-    NMT_TRY(self_bwd(r, denc, Ns, false, x_in, r.ws<half_t>(W.qkv), r.ws<half_t>(W.o), r.ws<float>(W.lse), r.ws<half_t>(W.s1),
-                     r.ws<float>(W.st1), P.attn, P.ln1, layer_site(l, kKindSelfRes), c->src, 0));
+    if (chains) {
+      NMT_TRY(layer_chain(denc, Ns, false, r.ws<half_t>(W.x1), r.ws<half_t>(W.h), r.ws<half_t>(W.s2), r.ws<float>(W.st2), P.ffn, P.ln2,
+                          layer_site(l, kKindFfnRes), x_in, r.ws<half_t>(W.s1), r.ws<float>(W.st1), r.ws<half_t>(W.o), P.attn, P.ln1, layer_site(l, kKindSelfRes)));
+    } else {
+      NMT_TRY(ffn_bwd(denc, Ns, false, r.ws<half_t>(W.x1), r.ws<half_t>(W.h), r.ws<half_t>(W.s2), r.ws<float>(W.st2), P.ffn, P.ln2,
+                      layer_site(l, kKindFfnRes)));
+      NMT_TRY(self_out_bwd(r, denc, Ns, false, x_in, r.ws<half_t>(W.o), r.ws<half_t>(W.s1), r.ws<float>(W.st1), P.attn, P.ln1, layer_site(l, kKindSelfRes)));
+    }
+    NMT_TRY(self_in_bwd(r, denc, Ns, false, x_in, r.ws<half_t>(W.qkv), r.ws<half_t>(W.o), r.ws<float>(W.lse), P.attn, c->src, 0, l == 0));
   }
 
   // ---- the embeddings: both id streams add into the row gradients of the shared matrix (beside the second stream's last

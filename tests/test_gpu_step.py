@@ -732,6 +732,45 @@ def test_a_pass_of_few_rows_gives_the_same_bits_first_and_later_on_either_stream
     sess.close()
 
 
+# Row counts around the 16 of a work-group and the tile counts of a wavefront; every width; feed-forward layers of one to four times the width; one stream
+# and two; keys and values of more decoder layers than end the encoder's chain; the row counts on both sides of the rule (4096 at 256).
+@pytest.mark.parametrize("d,heads,ff,enc,dec,B,S,T,dropout", [
+    (64, 4, 256, 2, 2, 1, 1, 1, 0.1), (64, 4, 64, 1, 1, 3, 5, 6, 0.0), (64, 2, 192, 2, 1, 4, 4, 4, 0.3), (64, 4, 256, 1, 2, 17, 31, 33, 0.1),
+    (128, 4, 512, 2, 2, 5, 13, 17, 0.1), (128, 8, 256, 1, 5, 40, 33, 21, 0.2), (128, 2, 128, 1, 1, 2, 8, 16, 0.0),
+    (256, 4, 1024, 2, 2, 9, 21, 30, 0.1), (256, 8, 256, 1, 2, 1, 16, 17, 0.0), (256, 4, 768, 1, 1, 45, 38, 40, 0.2), (256, 4, 1024, 1, 6, 3, 7, 9, 0.3),
+    (256, 2, 512, 1, 1, 128, 32, 32, 0.1), (256, 4, 1024, 1, 1, 129, 32, 31, 0.1)])
+@pytest.mark.parametrize("packed", [False, True])
+def test_a_launch_between_two_attentions_gives_the_activations_of_a_launch_for_each_operation(d, heads, ff, enc, dec, B, S, T, dropout, packed):
+    """Activations and loss are the same bits.  Gradients pass through LayerNorms whose products and sums are contracted otherwise, so fp16 roundings of
+    the gradient between two operations fall differently now and then: relative 2^-12 (rms) for each of a tensor's roundings that does, all of one tensor's at worst."""
+    model = dict(enc_layers=enc, dec_layers=dec, d_model=d, n_heads=heads, d_ff=ff, vocab=264, dropout=dropout)
+    sess = Session(model, I.init_weights(seed=9, perturb=0.05, **model), max_sentences=256, max_len=64)
+    batch = I.tiny_batch(seed=60 + B, B=B, S=S, T=T, vocab=264, short_rows=min(B - 1, 2), short_by=min(S, T) // 3)
+    db = sess.pack([batch])[0] if packed else sess.to_device(batch)
+    names = [f"{side}{l}.{what}" for side, n in (("enc", enc), ("dec", dec)) for l in range(n) for what in ("out", "ffn.h")]
+    seen = []
+    try:
+        for chains in (0, 1):
+            A.nmt_tuning("row_chain", chains)
+            sess.g16.fill_(float("nan"))
+            sess.forward_loss(db, 32.0, 3, 0)
+            acts = [sess.activation(n).clone() for n in names] + [sess.loss_sum.clone()]
+            sess.backward()
+            seen.append((acts, sess.named(sess.g16.float())))
+    finally:
+        A.nmt_tuning("defaults")
+        sess.close()
+    (a0, g0), (a1, g1) = seen
+    assert all(torch.equal(x.view(torch.uint8), y.view(torch.uint8)) for x, y in zip(a0, a1))
+    layers = enc + dec
+    for name, want in g0.items():
+        assert np.isfinite(g1[name]).all(), name
+        scale = np.linalg.norm(want)
+        if name.endswith(("bqkv", "bkv")):      # (a bias gradient of keys is zero but for rounding: the other sums' scale)
+            scale = max(scale, np.linalg.norm(g0[name.rsplit(".", 1)[0] + ".bo"]))
+        assert np.linalg.norm(g1[name] - want) <= 2.0 ** -12 * (2 + 4 * layers) ** 0.5 * 3 * max(scale, 1e-6), name
+
+
 @pytest.mark.parametrize("first", ["captured", "eager"])
 def test_a_captured_pass_gives_the_bits_of_an_eager_one_at_every_replay(first):
     """Forward and backward recorded into one graph, as the first pass of a context (which makes its second stream meanwhile) and
