@@ -159,6 +159,34 @@ __device__ __forceinline__ uint32_t drop_keep8(const DropDev& dd, const DropRow&
 }
 __device__ __forceinline__ uint32_t drop_keep8(const DropDev& dd, uint32_t row, uint32_t grp) { return drop_keep8(dd, drop_row(dd, row), grp); }
 
+// One word of every cache line of a kernel's arguments, asked for together: where the code reads them one after the other, each line's first
+// use is a trip to memory of its own (0.4 us).
+template <typename Args>
+__device__ __forceinline__ void touch(const Args& a) {
+  const uint32_t* words = reinterpret_cast<const uint32_t*>(&a);
+  uint32_t w[(sizeof(Args) + 63) / 64];
+#pragma unroll
+  for (size_t i = 0; i < sizeof(Args) / 64; ++i) w[i] = words[16 * i];
+  w[sizeof(w) / 4 - 1] = words[sizeof(Args) / 4 - 1];
+#pragma unroll
+  for (size_t i = 0; i < sizeof(w) / 4; ++i) asm volatile("" ::"s"(w[i]));
+}
+
+// Division by a number the host knows, without the reciprocal the compiler would form first (100 instructions' time in front of a kernel's first load).
+struct Divisor {
+  uint32_t d = 1, m = 0xFFFFFFFFu;  // m = floor(2^32 / d): the high word of n m is n / d or one less
+};
+static inline Divisor divisor(uint32_t d) { return Divisor{d, d == 1 ? 0xFFFFFFFFu : (uint32_t)((1ull << 32) / d)}; }
+__device__ __forceinline__ uint32_t div_mod(uint32_t n, const Divisor& by, uint32_t& rest) {
+  uint32_t q = __umulhi(n, by.m);
+  rest = n - q * by.d;
+  if (rest >= by.d) {
+    ++q;
+    rest -= by.d;
+  }
+  return q;
+}
+
 // ---- small vector helpers ---------------------------------------------------------------------
 __device__ __forceinline__ half8_t ld_half8(const half_t* p) { return *reinterpret_cast<const half8_t*>(p); }
 __device__ __forceinline__ void st_half8(half_t* p, half8_t v) { *reinterpret_cast<half8_t*>(p) = v; }

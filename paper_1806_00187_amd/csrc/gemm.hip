@@ -47,13 +47,23 @@ typedef short short8_t __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) short4_t* lds_short4_ptr;
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
+// The order work-groups take the tiles of a product in (see place).
+struct TileOrder {
+  Divisor xcds;         // dies with their own L2: consecutive work-group ids go round-robin over them
+  uint32_t base, rem;   // work-groups to a die: base, or one more on the first rem
+  int tiles_m, group_m;
+  Divisor tiles, per_group, rows, last_rows;  // tiles of the product; of group_m tile rows; group_m; rows of the last, shorter group
+};
+TileOrder tile_order(int tiles_m, int tiles_n, int splits, int group_m, int xcds) {
+  const uint32_t tiles = (uint32_t)tiles_m * tiles_n, total = tiles * splits;
+  return TileOrder{divisor(xcds), total / xcds, total % xcds, tiles_m, group_m, divisor(tiles), divisor(group_m * tiles_n), divisor(group_m),
+                   divisor(tiles_m % group_m ? tiles_m % group_m : group_m)};
+}
 struct GemmArgs {
   const half_t* A;
   const half_t* B;
   half_t* C;
   int lda, ldb, ldc, M, N, K;
-  int tiles_m, tiles_n, group_m;
-  int xcds;  // dies with their own L2: consecutive work-group ids go round-robin over them
   GemmEpilogue ep;
   // split-K: work-group (tile, z) contracts k in [z * k_chunk, min(K, (z + 1) * k_chunk)) and writes its
   // fp32 tile to partial[z][M][N]; partial == nullptr: one work-group per tile, epilogue, fp16 result
@@ -63,6 +73,7 @@ struct GemmArgs {
   // k, else `partial_colsum`, fp32 [z][M]
   half_t* colsum = nullptr;
   float* partial_colsum = nullptr;
+  TileOrder order = {};
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const half_t* p, uint32_t bytes) {
@@ -229,21 +240,122 @@ constexpr int wait_vm_lds(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0070; 
 // tiles of one split read the same k-range of A and B and share those panels in L2.
 // Then grouped order: group_m tile rows are swept column by column, so the work-groups an XCD runs at a
 // time form a patch of tiles and each A / B panel they stream is shared by several of them in L2.
-__device__ __forceinline__ int xcd_order(int lin, int total, int xcds) {
-  const int xcd = lin % xcds, idx = lin / xcds, base = total / xcds, rem = total % xcds;
-  return xcd * base + (xcd < rem ? xcd : rem) + idx;
+__device__ __forceinline__ uint32_t xcd_order(uint32_t lin, const Divisor& xcds, uint32_t base, uint32_t rem) {
+  uint32_t xcd;
+  const uint32_t idx = div_mod(lin, xcds, xcd);
+  return xcd * base + min(xcd, rem) + idx;
 }
-__device__ __forceinline__ void place(const GemmArgs& g, int lin, int total, int& split, int& tm, int& tn) {
-  const int nt = g.tiles_m * g.tiles_n, at = xcd_order(lin, total, g.xcds);
-  split = at / nt;
-  const int pid = at - split * nt, per_group = g.group_m * g.tiles_n;
-  const int first = (pid / per_group) * g.group_m;
-  const int rows = min(g.tiles_m - first, g.group_m);
-  tm = first + (pid % per_group) % rows;
-  tn = (pid % per_group) / rows;
+__device__ __forceinline__ void place_tile(const TileOrder& o, uint32_t pid, int& tm, int& tn) {
+  uint32_t in_group, row;
+  const int first = (int)div_mod(pid, o.per_group, in_group) * o.group_m;
+  tn = (int)div_mod(in_group, first + o.group_m <= o.tiles_m ? o.rows : o.last_rows, row);
+  tm = first + (int)row;
+}
+__device__ __forceinline__ void place(const TileOrder& o, uint32_t lin, int& split, int& tm, int& tn) {
+  uint32_t pid;
+  split = (int)div_mod(xcd_order(lin, o.xcds, o.base, o.rem), o.tiles, pid);
+  place_tile(o, pid, tm, tn);
 }
 
-// Epilogue of one tile: accumulators -> per-wave LDS staging (fp32) -> row-wise 16-byte stores.
+// What an epilogue does: nothing; bias; bias and ReLU; a sum with another matrix; the ReLU mask of the backward pass; whatever it is told,
+// fp32 partial sums of a product cut along k among it; output scale or partial sums (weight gradients).  A kernel each for the
+// first five: chosen per value they cost an instruction more each, and what is loaded for one form has to be waited for in all.
+enum StoreForm { kStorePlain, kStoreBias, kStoreRelu, kStoreAdd, kStoreMask, kStoreAny, kStoreGroup };
+typedef _Float16 half4v_t __attribute__((ext_vector_type(4)));
+typedef float floatx8 __attribute__((ext_vector_type(8)));
+typedef uint32_t uint4v_t __attribute__((ext_vector_type(4)));
+constexpr int kStream = 2;  // non-temporal
+// 16 bytes at byte offset `off` (past the extent: zeros come back, nothing is stored)
+__device__ __forceinline__ half8_t buffer_half8(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+// streaming store: a result tile is not read again by its product, and letting it stay in L2 pushes out
+// the operand panels the XCD's other tiles are reading (products with wide results: +5-7 %)
+__device__ __forceinline__ void buffer_store_half8(__amdgpu_buffer_rsrc_t r, uint32_t off, half8_t v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4v_t, v), r, (int)off, 0, kStream);
+}
+
+// Epilogue of one tile whose form is known when it is compiled.  What it loads -- the bias of the lane's columns as the sums lie in registers, or what is added or
+// masks in the pieces the results leave in -- is requested before the first operands, so that nothing is waited for behind the last product but LDS; the
+// wavefront's whole share of the tile passes through LDS at once and leaves in whole rows, bounds by the descriptor of C, no branches.  (Loading the
+// bias with each 32 rows, every load waited for the stores before it: with that and the order of tiles computed by division, 4.0 us of each product of a few
+// hundred rows besides its k-tiles; now XX.)
+template <int BM, int BN, int NW, int STAGE, StoreForm FORM>
+struct TileStore {
+  static constexpr int WGN = NW / 2, WM = BM / 2, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
+  static constexpr bool kLoads = FORM == kStoreAdd || FORM == kStoreMask, kBias = FORM == kStoreBias || FORM == kStoreRelu;
+  static constexpr int CH = WN / 8, RPI = 64 / CH, P = WM / RPI;  // 16-byte pieces of a row of results, rows to an instruction, pieces a lane
+  static constexpr int HW = NW / 2, SHARE = WM * WN * (kLoads ? 4 : 2);
+  static_assert(HW * SHARE <= STAGE, "half of the wavefronts' shares fit one stage");
+  half4v_t bias[kBias ? TN : 1];
+  half8_t pre[kLoads ? P : 1];
+  uint32_t at, step;
+  __device__ __forceinline__ void request(const GemmArgs& g, int m0, int n0, int rows, int cols, int wave, int lane) {
+    const int wm = wave / WGN, wn = wave % WGN, col = wn * WN + lane % CH * 8;
+    step = (uint32_t)RPI * (uint32_t)g.ldc * 2u;
+    at = col < cols ? ((uint32_t)(wm * WM + lane / CH) * (uint32_t)g.ldc + (uint32_t)col) * 2u : kOob;
+    if constexpr (kBias) {
+      const __amdgpu_buffer_rsrc_t r = make_rsrc(g.ep.bias + n0, (uint32_t)cols * 2u);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) bias[j] = __builtin_bit_cast(half4v_t, __builtin_amdgcn_raw_buffer_load_b64(r, (wn * WN + 16 * j + 4 * (lane >> 4)) * 2, 0, 0));
+    }
+    if constexpr (kLoads) {
+      const __amdgpu_buffer_rsrc_t r = make_rsrc((FORM == kStoreAdd ? g.ep.add : g.ep.relu_src) + (size_t)m0 * g.ldc + n0,
+                                                 ((uint32_t)(rows - 1) * (uint32_t)g.ldc + (uint32_t)cols) * 2u);
+#pragma unroll
+      for (int q = 0; q < P; ++q) pre[q] = buffer_half8(r, at + q * step);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __device__ __forceinline__ void store(const GemmArgs& g, const floatx4 (&acc)[TM][TN], int m0, int n0, int rows, int cols, int wave, int lane,
+                                        unsigned char* stage0, unsigned char* stage1) {
+    unsigned char* const own = (wave < HW ? stage0 : stage1) + wave % HW * SHARE;
+    const __amdgpu_buffer_rsrc_t to = make_rsrc(g.C + (size_t)m0 * g.ldc + n0, ((uint32_t)(rows - 1) * (uint32_t)g.ldc + (uint32_t)cols) * 2u);
+    const int row = lane & 15, quad = lane >> 4, r0 = lane / CH, c8 = lane % CH;
+    if constexpr (!kLoads) {
+      // fp16; row r, 16-byte chunk c at r * 2 WN + (c ^ (r >> 1 & 7)) * 16, or, of 64 bytes, c ^ (r >> 2 & 3): 32 lanes' 8-byte pieces hit every bank once
+      auto place = [&](int r, int c) { return own + r * (2 * WN) + ((CH == 8 ? c ^ (r >> 1 & 7) : c ^ (r >> 2 & 3)) << 4); };
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          floatx4 v = acc[i][j];
+          if constexpr (kBias) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              v[e] += (float)bias[j][e];
+              if constexpr (FORM == kStoreRelu) v[e] = fmaxf(v[e], 0.f);
+            }
+          }
+          *reinterpret_cast<half4v_t*>(place(16 * i + row, 2 * j + (quad >> 1)) + ((quad & 1) << 3)) = __builtin_convertvector(v, half4v_t);
+        }
+      wave_sync();
+#pragma unroll
+      for (int q = 0; q < P; ++q) buffer_store_half8(to, at + q * step, *reinterpret_cast<const half8_t*>(place(q * RPI + r0, c8)));
+    } else {
+      // the sums as they are (one rounding, at the end); 16-byte chunks of four columns
+      auto place = [&](int r, int c) { return own + r * (4 * WN) + ((WN == 64 ? c ^ (r & 15) : c ^ (r >> 1 & 7)) << 4); };
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) *reinterpret_cast<floatx4*>(place(16 * i + row, 4 * j + quad)) = acc[i][j];
+      wave_sync();
+#pragma unroll
+      for (int q = 0; q < P; ++q) {
+        const floatx4 lo = *reinterpret_cast<const floatx4*>(place(q * RPI + r0, 2 * c8)), hi = *reinterpret_cast<const floatx4*>(place(q * RPI + r0, 2 * c8 + 1));
+        floatx8 v;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float x = e < 4 ? lo[e] : hi[e - 4];
+          v[e] = FORM == kStoreAdd ? x + (float)pre[q][e] : (float)pre[q][e] > 0.f ? x * g.ep.mask_scale : 0.f;
+        }
+        buffer_store_half8(to, at + q * step, __builtin_convertvector(v, half8_t));
+      }
+    }
+  }
+};
+
+// Epilogue of one tile of any form: accumulators -> per-wave LDS staging (fp32) -> row-wise 16-byte stores.
 // PLAIN: the epilogue is the output scale alone (weight gradients).
 template <int BM, int BN, int NW, int STAGE, bool PLAIN>
 __device__ __forceinline__ void store_tile(const GemmArgs& g, const floatx4 (&acc)[BM / 32][BN / (16 * (NW / 2))], int m0, int n0, int split,
@@ -575,14 +687,17 @@ struct StripTile {
   __device__ __forceinline__ void settle() { settle_sums(acc); }
 };
 // One tile by one work-group.
-template <int BM, int BN, bool AT, bool BT, int NW, bool SUMS, bool PLAIN>
+template <int BM, int BN, bool AT, bool BT, int NW, bool SUMS, StoreForm FORM>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int split, int tm, int tn, unsigned char* stage0, unsigned char* stage1) {
   using L = StripTile<BM, BN, AT, BT, NW, SUMS>;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int k_base = g.partial ? split * g.k_chunk : 0;
+  const bool cut = FORM >= kStoreAny && g.partial;
+  const int k_base = cut ? split * g.k_chunk : 0;
   L t(g);
-  t.k_end = g.partial ? min(g.K, k_base + g.k_chunk) : g.K;
+  t.k_end = cut ? min(g.K, k_base + g.k_chunk) : g.K;
   t.set_tile(tm * BM, tn * BN, tid);
+  TileStore<BM, BN, NW, L::T::STAGE, FORM < kStoreAny ? FORM : kStorePlain> out;
+  if constexpr (FORM < kStoreAny) out.request(g, t.m0, t.n0, t.rows_a, t.rows_b, wave, lane);
   t.set_fragments(wave, lane);
   t.clear();
   t.request_first(stage0, stage1, k_base);
@@ -595,16 +710,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int split, int tm, 
   if constexpr (SUMS) {
     store_colsum<L::WGN, L::TM>(g, t.sum, t.m0 + wave / L::WGN * L::WM, t.pair, split);
   }
-  store_tile<BM, BN, NW, L::T::STAGE, PLAIN>(g, t.acc, t.m0, t.n0, split, stage0, stage1);
+  if constexpr (FORM < kStoreAny) out.store(g, t.acc, t.m0, t.n0, t.rows_a, t.rows_b, wave, lane, stage0, stage1);
+  else store_tile<BM, BN, NW, L::T::STAGE, FORM == kStoreGroup>(g, t.acc, t.m0, t.n0, split, stage0, stage1);
 }
-template <int BM, int BN, bool AT, bool BT, int NW>
+template <int BM, int BN, bool AT, bool BT, int NW, StoreForm FORM>
 __global__ void __launch_bounds__(64 * NW) gemm_kernel(const GemmArgs g) {
+  touch(g);
   using T = Tile<BM, BN, AT, BT, NW>;
   __shared__ __align__(1024) unsigned char stage0[T::STAGE];
   __shared__ __align__(1024) unsigned char stage1[T::STAGE];
   int split, tm, tn;
-  place(g, (int)blockIdx.x + (int)blockIdx.y * (g.tiles_m * g.tiles_n), g.tiles_m * g.tiles_n * (int)gridDim.y, split, tm, tn);
-  gemm_tile<BM, BN, AT, BT, NW, false, false>(g, split, tm, tn, stage0, stage1);
+  place(g.order, blockIdx.x + blockIdx.y * g.order.tiles.d, split, tm, tn);
+  gemm_tile<BM, BN, AT, BT, NW, false, FORM>(g, split, tm, tn, stage0, stage1);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -621,7 +738,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_kernel(const GemmArgs g) {
 // The two-stage ring remains for 128 x 128 tiles on four wavefronts, two work-groups per compute unit, where there are
 // enough tiles for that: the second work-group's k-tiles then cover the first one's prologue and epilogue.
 // ------------------------------------------------------------------------------------------------
-template <int BM, int BN, bool AT, bool BT, int NW, bool SUMS, bool PLAIN>
+template <int BM, int BN, bool AT, bool BT, int NW, bool SUMS, StoreForm FORM>
 __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int split, int tm, int tn, unsigned char* stage0, unsigned char* stage1,
                                                 unsigned char* stage2, unsigned char* stage3) {
   constexpr int NS = 4;
@@ -648,8 +765,11 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int split, in
   opb.init(g.ldb, rows_b, tid);
   const typename OpA::Frag fa = OpA::frag_init(wm * WM, lane);
   const typename OpB::Frag fb = OpB::frag_init(wn * WN, lane);
-  const int k_base = g.partial ? split * g.k_chunk : 0;
-  const int k_end = g.partial ? min(g.K, k_base + g.k_chunk) : g.K;
+  const bool cut = FORM >= kStoreAny && g.partial;
+  const int k_base = cut ? split * g.k_chunk : 0;
+  const int k_end = cut ? min(g.K, k_base + g.k_chunk) : g.K;
+  TileStore<BM, BN, NW, T::STAGE, FORM < kStoreAny ? FORM : kStorePlain> out;
+  if constexpr (FORM < kStoreAny) out.request(g, m0, n0, rows_a, rows_b, wave, lane);
   auto request = [&](unsigned char* stage, int k0) {
     const int kleft = k_end - k0;
     opa.load(OpA::origin(g.A, g.lda, m0, k0), OpA::extent(rows_a, g.lda, kleft), stage, kleft);
@@ -798,29 +918,31 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int split, in
   if constexpr (SUMS) {
     store_colsum<WGN, TM>(g, colsum, m0 + wm * WM, pair, split);
   }
-  store_tile<BM, BN, NW, T::STAGE, PLAIN>(g, acc, m0, n0, split, stage0, stage1);
+  if constexpr (FORM < kStoreAny) out.store(g, acc, m0, n0, rows_a, rows_b, wave, lane, stage0, stage1);
+  else store_tile<BM, BN, NW, T::STAGE, FORM == kStoreGroup>(g, acc, m0, n0, split, stage0, stage1);
 }
-template <int BM, int BN, bool AT, bool BT, int NW>
+template <int BM, int BN, bool AT, bool BT, int NW, StoreForm FORM>
 __device__ __forceinline__ void gemm_small_group(const GemmArgs& g) {
+  touch(g);
   using T = Tile<BM, BN, AT, BT, NW>;
   __shared__ __align__(1024) unsigned char stage0[T::STAGE];  // separate arrays (see StripTile)
   __shared__ __align__(1024) unsigned char stage1[T::STAGE];
   __shared__ __align__(1024) unsigned char stage2[T::STAGE];
   __shared__ __align__(1024) unsigned char stage3[T::STAGE];
   int split, tm, tn;
-  place(g, (int)blockIdx.x + (int)blockIdx.y * (g.tiles_m * g.tiles_n), g.tiles_m * g.tiles_n * (int)gridDim.y, split, tm, tn);
-  gemm_small_tile<BM, BN, AT, BT, NW, false, false>(g, split, tm, tn, stage0, stage1, stage2, stage3);
+  place(g.order, blockIdx.x + blockIdx.y * g.order.tiles.d, split, tm, tn);
+  gemm_small_tile<BM, BN, AT, BT, NW, false, FORM>(g, split, tm, tn, stage0, stage1, stage2, stage3);
 }
-template <int BM, int BN, bool AT, bool BT, int NW>
+template <int BM, int BN, bool AT, bool BT, int NW, StoreForm FORM>
 __global__ void __launch_bounds__(64 * NW) gemm_small_kernel(const GemmArgs g) {
-  gemm_small_group<BM, BN, AT, BT, NW>(g);
+  gemm_small_group<BM, BN, AT, BT, NW, FORM>(g);
 }
 // Eight wavefronts: one such work-group fills a compute unit's LDS.  Registers for a third wavefront per SIMD (160 of 512) are left, so that the other
 // stream's row kernels can run beside it (LayerNorm backward of a 512 wide model over 3000 positions, a third of the calls beside a layer's weight
 // gradients: 16.8 us on average with 220 registers here, 14.1 with 154).  The attribute counts half of the register file.
-template <int BM, int BN, bool AT, bool BT>
+template <int BM, int BN, bool AT, bool BT, StoreForm FORM>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(88))) gemm_small_kernel_8(const GemmArgs g) {
-  gemm_small_group<BM, BN, AT, BT, 8>(g);
+  gemm_small_group<BM, BN, AT, BT, 8, FORM>(g);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -840,7 +962,6 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(88))) gemm
 // flight the compiler would otherwise put a wait for ALL of them in front of any LDS access it
 // cannot tell apart from their targets.
 __device__ __forceinline__ uint32_t lds_addr(const void* p) { return (uint32_t)(uintptr_t)(lds_void_ptr)p; }
-typedef _Float16 half4v_t __attribute__((ext_vector_type(4)));
 // eight 8-byte writes: one 32 x 64 slab of results (the lane's four consecutive columns in two rows of four column groups)
 __device__ __forceinline__ void out_write_slab(const uint32_t (&a)[8], const half4v_t (&v)[8]) {
   asm volatile(
@@ -870,24 +991,6 @@ __device__ __forceinline__ void out_read_slab(const uint32_t (&a)[4], V (&d)[4])
       : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
       : "memory");
 }
-typedef float floatx8 __attribute__((ext_vector_type(8)));
-typedef uint32_t uint4v_t __attribute__((ext_vector_type(4)));
-typedef uint32_t uint2v_t __attribute__((ext_vector_type(2)));
-constexpr int kStream = 2;  // non-temporal
-// 16 bytes at byte offset `off` (past the extent: zeros come back, nothing is stored)
-__device__ __forceinline__ half8_t buffer_half8(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
-}
-// streaming store: a result tile is not read again by its product, and letting it stay in L2 pushes out
-// the operand panels the XCD's other tiles are reading (products with wide results: +5-7 %)
-__device__ __forceinline__ void buffer_store_half8(__amdgpu_buffer_rsrc_t r, uint32_t off, half8_t v) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4v_t, v), r, (int)off, 0, kStream);
-}
-
-// What an epilogue of the persistent form does: nothing; bias; bias and ReLU; a sum with another matrix; the
-// ReLU mask of the backward pass.  (A kernel each: chosen per value inside one they cost an instruction more each, chosen per
-// slab of rows the register file overflows.)
-enum StoreForm { kStorePlain, kStoreBias, kStoreRelu, kStoreAdd, kStoreMask };
 template <bool BT, StoreForm FORM>
 __global__ void __launch_bounds__(512) gemm_persistent_kernel(const GemmArgs g) {
   constexpr int BM = 256, BN = 256, NW = 8;
@@ -899,16 +1002,14 @@ __global__ void __launch_bounds__(512) gemm_persistent_kernel(const GemmArgs g) 
   __shared__ __align__(16) unsigned char out_rows[NW * kOutBytes];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / L::WGN, wn = wave % L::WGN;
-  const int nt = g.tiles_m * g.tiles_n;
+  const int nt = (int)g.order.tiles.d;
 
   L t(g);
   t.k_end = g.K;
   auto set_tile = [&](int lin) {
-    const int pid = xcd_order(lin, nt, g.xcds);
-    const int per_group = g.group_m * g.tiles_n;
-    const int first = (pid / per_group) * g.group_m;
-    const int rows = min(g.tiles_m - first, g.group_m);
-    t.set_tile((first + (pid % per_group) % rows) * BM, ((pid % per_group) / rows) * BN, tid);
+    int split, tm, tn;
+    place(g.order, (uint32_t)lin, split, tm, tn);
+    t.set_tile(tm * BM, tn * BN, tid);
   };
   const GemmEpilogue& ep = g.ep;
   const uint32_t out = lds_addr(out_rows) + wave * kOutBytes;
@@ -1067,31 +1168,29 @@ __global__ void __launch_bounds__(kThreads) splitk_reduce_kernel(const float* __
 // time beside the chain; over 52700 positions 1024 wide: 1.24 ms (1.07 PFLOP/s).
 // ------------------------------------------------------------------------------------------------
 struct GroupArgs {
-  int n, xcds, group_m, splits, total;
+  int n, total;
+  Divisor xcds;
+  uint32_t base, rem;     // (as in TileOrder, of the whole group)
   float out_scale;
   struct Product {
     WgradProduct w;
     float *partial, *partial_colsum;
     int begin;            // first work item of the product
-    int tiles_m, tiles_n, k_chunk;
+    int k_chunk;
+    TileOrder order;
   } p[kMaxWgrad];
 };
 // Work item -> product, split and tile; consecutive items of one XCD's run share operand panels (as in place()).
 __device__ __forceinline__ GemmArgs group_item(const GroupArgs& a, int lin, int& split, int& tm, int& tn, bool& sums) {
-  const int at = xcd_order(lin, a.total, a.xcds);
+  const int at = (int)xcd_order((uint32_t)lin, a.xcds, a.base, a.rem);
   int i = 0;
   while (i + 1 < a.n && at >= a.p[i + 1].begin) ++i;
   const GroupArgs::Product& p = a.p[i];
-  GemmArgs g{p.w.A, p.w.B, p.w.C, p.w.lda, p.w.ldb, p.w.ldc, p.w.M, p.w.N, p.w.K, p.tiles_m, p.tiles_n, a.group_m, a.xcds, GemmEpilogue{},
-             p.partial, p.k_chunk, p.w.colsum, p.partial_colsum};
+  GemmArgs g{p.w.A, p.w.B, p.w.C, p.w.lda, p.w.ldb, p.w.ldc, p.w.M, p.w.N, p.w.K, GemmEpilogue{}, p.partial, p.k_chunk, p.w.colsum, p.partial_colsum};
   g.ep.out_scale = a.out_scale;
-  const int nt = g.tiles_m * g.tiles_n;
-  split = (at - p.begin) / nt;
-  const int pid = (at - p.begin) - split * nt, per_group = g.group_m * g.tiles_n;
-  const int first = (pid / per_group) * g.group_m;
-  const int rows = min(g.tiles_m - first, g.group_m);
-  tm = first + (pid % per_group) % rows;
-  tn = (pid % per_group) / rows;
+  uint32_t pid;
+  split = (int)div_mod((uint32_t)(at - p.begin), p.order.tiles, pid);
+  place_tile(p.order, pid, tm, tn);
   sums = tn == 0 && g.colsum;
   return g;
 }
@@ -1104,13 +1203,13 @@ __device__ __forceinline__ void wgrad_group(const GroupArgs& a) {
   bool sums;
   const GemmArgs g = group_item(a, (int)blockIdx.x, split, tm, tn, sums);
   if constexpr (NS == 2) {
-    if (sums) gemm_tile<BM, BN, true, true, NW, true, true>(g, split, tm, tn, stage0, stage1);
-    else gemm_tile<BM, BN, true, true, NW, false, true>(g, split, tm, tn, stage0, stage1);
+    if (sums) gemm_tile<BM, BN, true, true, NW, true, kStoreGroup>(g, split, tm, tn, stage0, stage1);
+    else gemm_tile<BM, BN, true, true, NW, false, kStoreGroup>(g, split, tm, tn, stage0, stage1);
   } else {
     __shared__ __align__(1024) unsigned char stage2[T::STAGE];
     __shared__ __align__(1024) unsigned char stage3[T::STAGE];
-    if (sums) gemm_small_tile<BM, BN, true, true, NW, true, true>(g, split, tm, tn, stage0, stage1, stage2, stage3);
-    else gemm_small_tile<BM, BN, true, true, NW, false, true>(g, split, tm, tn, stage0, stage1, stage2, stage3);
+    if (sums) gemm_small_tile<BM, BN, true, true, NW, true, kStoreGroup>(g, split, tm, tn, stage0, stage1, stage2, stage3);
+    else gemm_small_tile<BM, BN, true, true, NW, false, kStoreGroup>(g, split, tm, tn, stage0, stage1, stage2, stage3);
   }
 }
 template <int BM, int BN, int NS, int NW>
@@ -1178,25 +1277,30 @@ __global__ void __launch_bounds__(kThreads) wgrad_group_reduce_kernel(const Grou
   st_half8(p.C + (size_t)row * p.ldc + c8 * 8, o);
 }
 
+// The form of an epilogue that the kernels have compiled in: with x W^T nothing, bias, or bias and ReLU, with dy W nothing, a sum or the mask; kStoreAny otherwise.
+StoreForm store_form(const GemmEpilogue& ep, bool b_t, bool cut) {
+  if (cut || ep.drop.thr || ep.out_scale != 1.f) return kStoreAny;
+  if (!ep.bias && !ep.relu && !ep.add && !ep.relu_src) return kStorePlain;
+  if (!b_t && ep.bias && !ep.add && !ep.relu_src) return ep.relu ? kStoreRelu : kStoreBias;
+  if (b_t && !ep.bias && !ep.relu && !(ep.add && ep.relu_src)) return ep.add ? kStoreAdd : kStoreMask;
+  return kStoreAny;
+}
 // NS = 2: two stages, strip by strip; 4: a ring of four, a whole k-tile of fragments ahead
-template <int BM, int BN, bool AT, bool BT, int NS, int NW>
+template <int BM, int BN, bool AT, bool BT, int NS, int NW, StoreForm FORM>
 void launch_variant(const GemmArgs& g, int splits, hipStream_t stream) {
-  const dim3 grid(g.tiles_m * g.tiles_n, splits), block(64 * NW);
-  if constexpr (NS == 2) hipLaunchKernelGGL((gemm_kernel<BM, BN, AT, BT, NW>), grid, block, 0, stream, g);
-  else if constexpr (NW == 8) hipLaunchKernelGGL((gemm_small_kernel_8<BM, BN, AT, BT>), grid, block, 0, stream, g);
-  else hipLaunchKernelGGL((gemm_small_kernel<BM, BN, AT, BT, NW>), grid, block, 0, stream, g);
+  const dim3 grid(g.order.tiles.d, splits), block(64 * NW);
+  if constexpr (NS == 2) hipLaunchKernelGGL((gemm_kernel<BM, BN, AT, BT, NW, FORM>), grid, block, 0, stream, g);
+  else if constexpr (NW == 8) hipLaunchKernelGGL((gemm_small_kernel_8<BM, BN, AT, BT, FORM>), grid, block, 0, stream, g);
+  else hipLaunchKernelGGL((gemm_small_kernel<BM, BN, AT, BT, NW, FORM>), grid, block, 0, stream, g);
 }
 
 template <int BM, int BN, int NS, int NW = 4>
 int launch_tile(const GemmArgs& a, bool a_t, bool b_t, int splits, hipStream_t stream) {
   GemmArgs g = a;
-  g.tiles_m = ceil_div(g.M, BM);
-  g.tiles_n = ceil_div(g.N, BN);
   // tile rows per sweep: the 32 tiles an XCD works on at a time form a patch of 4 rows x 8 columns (or
   // the result's whole width); between 2 and 8 the whole update is flat within 0.5 %, 4 measured best and
   // fetches least past L2, 12 and more cost 2 %
-  g.group_m = tuning().gemm_group;
-  g.xcds = device_info().xcds;
+  const int group_m = tuning().gemm_group;
   if (splits > 1) {
     g.k_chunk = (int)round_up(ceil_div(g.K, splits), 64);  // (whatever the tile, so that its shape changes no bit)
     splits = ceil_div(g.K, g.k_chunk);  // no empty split
@@ -1205,10 +1309,26 @@ int launch_tile(const GemmArgs& a, bool a_t, bool b_t, int splits, hipStream_t s
     g.partial = nullptr;
     splits = 1;
   }
-  if (!a_t && !b_t) launch_variant<BM, BN, false, false, NS, NW>(g, splits, stream);
-  else if (!a_t && b_t) launch_variant<BM, BN, false, true, NS, NW>(g, splits, stream);
-  else if (a_t && b_t) launch_variant<BM, BN, true, true, NS, NW>(g, splits, stream);
-  else launch_variant<BM, BN, true, false, NS, NW>(g, splits, stream);
+  g.order = tile_order(ceil_div(g.M, BM), ceil_div(g.N, BN), splits, group_m, device_info().xcds);
+  constexpr bool kForms = BM < 256;  // (256 x 256 tiles have theirs in the persistent form)
+  const StoreForm form = kForms && !a_t ? store_form(g.ep, b_t, g.partial != nullptr) : kStoreAny;
+  auto run = [&](auto at, auto bt, auto f) { launch_variant<BM, BN, decltype(at)::value, decltype(bt)::value, NS, NW, decltype(f)::value>(g, splits, stream); };
+  const std::false_type no;
+  const std::true_type yes;
+#define NMT_FORM(f) std::integral_constant<StoreForm, f>{}
+  if (a_t && b_t) run(yes, yes, NMT_FORM(kStoreAny));
+  else if (a_t) run(yes, no, NMT_FORM(kStoreAny));
+  else if (form == kStoreAny && b_t) run(no, yes, NMT_FORM(kStoreAny));
+  else if (form == kStoreAny) run(no, no, NMT_FORM(kStoreAny));
+  if constexpr (kForms) {
+    if (form == kStorePlain && b_t) run(no, yes, NMT_FORM(kStorePlain));
+    else if (form == kStorePlain) run(no, no, NMT_FORM(kStorePlain));
+    else if (form == kStoreBias) run(no, no, NMT_FORM(kStoreBias));
+    else if (form == kStoreRelu) run(no, no, NMT_FORM(kStoreRelu));
+    else if (form == kStoreAdd) run(no, yes, NMT_FORM(kStoreAdd));
+    else if (form == kStoreMask) run(no, yes, NMT_FORM(kStoreMask));
+  }
+#undef NMT_FORM
   NMT_LAUNCH_CHECK();
   if (splits == 1) return NMT_OK;
   const int64_t n = (int64_t)g.M * (g.N / 8);
@@ -1288,7 +1408,7 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
   const bool plain = !ep.bias && !ep.relu && !ep.drop.thr && !ep.add && !ep.relu_src;  // (out_scale is applied by the reduction)
   NMT_REQUIRE(splits <= 1 || (partial && plain), "gemm: splitting k needs a partial-sum buffer and no epilogue");
   NMT_REQUIRE(!partial || (reinterpret_cast<uintptr_t>(partial) & 15u) == 0, "gemm: partial-sum buffer must be 16-byte aligned");
-  GemmArgs g{A, B, C, lda, ldb, ldc, M, N, K, 0, 0, 0, device_info().xcds, ep, partial, 0};
+  GemmArgs g{A, B, C, lda, ldb, ldc, M, N, K, ep, partial, 0};
   const int cus = device_info().cus;
   const int64_t plane = (int64_t)M * N;
   // Work-groups of 256 x 256 tiles run one per compute unit; they pay off once there are enough of them.
@@ -1363,9 +1483,7 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
         !(ep.add && ep.relu_src)) {
       const int groups = (int)(t256 < cus ? t256 : cus);
       GemmArgs pg = g;
-      pg.tiles_m = ceil_div(M, 256);
-      pg.tiles_n = ceil_div(N, 256);
-      pg.group_m = tuning().gemm_group;
+      pg.order = tile_order(ceil_div(M, 256), ceil_div(N, 256), 1, tuning().gemm_group, device_info().xcds);
       pg.partial = nullptr;
       auto run = [&](auto bt) {
         constexpr bool BT = decltype(bt)::value;
@@ -1486,9 +1604,7 @@ int launch_wgrad_group_impl(const WgradProduct* products, int n, float out_scale
   GroupArgs a = {};
   GroupReduceArgs ra = {};
   a.n = ra.n = n;
-  a.xcds = device_info().xcds;
-  a.group_m = tuning().gemm_group;
-  a.splits = ra.splits = splits;
+  ra.splits = splits;
   a.out_scale = ra.scale = out_scale;
   float* at = partial;
   for (int i = 0; i < n; ++i) {
@@ -1496,10 +1612,10 @@ int launch_wgrad_group_impl(const WgradProduct* products, int n, float out_scale
     GroupArgs::Product& p = a.p[i];
     p.w = w;
     p.begin = a.total;
-    p.tiles_m = ceil_div(w.M, edge);
-    p.tiles_n = ceil_div(w.N, edge);
+    const int tiles_m = ceil_div(w.M, edge), tiles_n = ceil_div(w.N, edge);
+    p.order = tile_order(tiles_m, tiles_n, splits, tuning().gemm_group, device_info().xcds);
     p.k_chunk = (int)round_up(ceil_div(w.K, splits), 64);  // (a split past the end of a short contraction writes zeros)
-    a.total += p.tiles_m * p.tiles_n * splits;
+    a.total += tiles_m * tiles_n * splits;
     if (splits > 1) {
       p.partial = at;
       p.partial_colsum = at + (int64_t)splits * w.M * w.N;
@@ -1508,6 +1624,9 @@ int launch_wgrad_group_impl(const WgradProduct* products, int n, float out_scale
       ra.total += (int64_t)w.M * (w.N / 8) + (w.colsum ? w.M / 8 : 0);
     }
   }
+  a.xcds = divisor(device_info().xcds);
+  a.base = a.total / device_info().xcds;
+  a.rem = a.total % device_info().xcds;
   const dim3 grid(a.total);
   switch (tile) {
     case kGroup256: hipLaunchKernelGGL((wgrad_group_kernel<256, 256, 2, 8>), grid, dim3(512), 0, stream, a); break;

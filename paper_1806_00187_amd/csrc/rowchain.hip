@@ -41,19 +41,6 @@ __device__ __forceinline__ void lds_barrier() {
 // (Results are rounded to fp32 first, as in the general kernels: element by element the compiler would form the last sum in fp16's own instruction.)
 __device__ __forceinline__ half8_t to_half8(const floatx8& v) { return __builtin_convertvector(v, half8_t); }
 
-// One word of every cache line of a kernel's arguments, asked for together: where the code reads them one after the other, each line's first
-// use is a trip to memory of its own (0.4 us).
-template <typename Args>
-__device__ __forceinline__ void touch(const Args& a) {
-  const uint32_t* words = reinterpret_cast<const uint32_t*>(&a);
-  uint32_t w[(sizeof(Args) + 63) / 64];
-#pragma unroll
-  for (size_t i = 0; i < sizeof(Args) / 64; ++i) w[i] = words[16 * i];
-  w[sizeof(w) / 4 - 1] = words[sizeof(Args) / 4 - 1];
-#pragma unroll
-  for (size_t i = 0; i < sizeof(w) / 4; ++i) asm volatile("" ::"s"(w[i]));
-}
-
 // A tile of kRows rows in LDS.
 struct LdsTile {
   half_t* p;
