@@ -50,7 +50,9 @@ struct AttnArgs {
   const int4* wl_sent;               // [kClasses][B] table entries of the sentences of each class
   const int4* wl_qsent;              // per query tile: its sentence's table entry ...
   const int32_t* wl_qtile;           // ... and its tile number
-  int vgx, vgy;                      // persistent kernels: the grid of work items their work-groups walk through
+  int vgx, vgy;                      // persistent kernels: the grid of work items their work-groups walk through ...
+  int stride;                        // ... in steps of the launch's work-groups
+  Divisor by_vgx, by_hg, by_h;       // vgx; groups of heads (a work-group's wavefronts) to a sentence; heads
   int cls_lo, cls_hi;                // backward by key tiles: classes (tiles of the longer side) this launch covers
 };
 
@@ -109,16 +111,16 @@ struct Item {
 // the sentence's table entry, so a work item costs one dependent load, not two.
 // (bx, by): the work-group's place in the grid of work items -- blockIdx for a kernel that takes one item
 // per work-group, the loop position for a persistent one.
-template <int LIST>
+// WPB: heads per work-group (one wavefront each).
+template <int LIST, int WPB = kThreads / 64>
 __device__ __forceinline__ Item work_item(const AttnArgs& a, int bx, int by, int cls = 0) {
-  const int wpb = blockDim.x >> 6;            // heads per work-group (one wavefront each)
-  const int hg = (a.H + wpb - 1) / wpb;
-  const int idx = bx / hg;
+  uint32_t head_group;
+  const int idx = (int)div_mod((uint32_t)bx, a.by_hg, head_group);
   Item it;
   // (known to be the wavefront's, so that addresses stay scalar; not for LIST 2, whose kernel for two tiles of 128 columns then spills 324 bytes a lane
   // instead of 220: backward of 216 sentences of up to 60, 8 heads of 128, 358 us against 338)
   const int wave = threadIdx.x >> 6;
-  it.h = (bx % hg) * wpb + (LIST == 2 ? wave : __builtin_amdgcn_readfirstlane(wave));
+  it.h = (int)head_group * WPB + (LIST == 2 ? wave : __builtin_amdgcn_readfirstlane(wave));
   it.tile = by;
   it.live = it.h < a.H;
   if (LIST == 1 && a.wl_qsent) {
@@ -330,8 +332,13 @@ template <int DH>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 64 ? 3 : 1, DH <= 64 ? 3 : 1)))
 attn_fwd_kernel(const AttnArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
+  touch(a);
   const int total = a.vgx * a.vgy;
-  for (int v = blockIdx.x; v < total; v += gridDim.x) attn_fwd_item<DH>(a, v % a.vgx, v / a.vgx, smem_raw);
+  for (int v = blockIdx.x; v < total; v += a.stride) {
+    uint32_t x;
+    const int y = (int)div_mod((uint32_t)v, a.by_vgx, x);
+    attn_fwd_item<DH>(a, (int)x, y, smem_raw);
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -510,7 +517,7 @@ constexpr int fused_wave_lds() {
 template <int DH, int NT>
 __device__ __forceinline__ void attn_bwd_fused_item(const AttnArgs& a, int bx, unsigned char* smem_raw) {
   constexpr int DHP = DH < 32 ? 32 : DH, KS = DH / 16, DT = DHP / 32, PR = DH + 8, TILE = 32 * PR;
-  const Item it = work_item<2>(a, bx, 0, NT - 1);
+  const Item it = work_item<2, NT == 1 ? 4 : 2>(a, bx, 0, NT - 1);
   if (!it.live) return;
   const Sent se = it.se;
   const int tmax = max(se.Tq, se.Tk);
@@ -638,7 +645,7 @@ __device__ __forceinline__ void attn_bwd_fused_item(const AttnArgs& a, int bx, u
 template <int DH, int NT>
 __global__ void __launch_bounds__(kThreads) attn_bwd_fused_kernel(const AttnArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  for (int v = blockIdx.x; v < a.vgx; v += gridDim.x) {
+  for (int v = blockIdx.x; v < a.vgx; v += a.stride) {
     wave_sync();  // the wavefront's LDS tiles are free again
     attn_bwd_fused_item<DH, NT>(a, v, smem_raw);
   }
@@ -666,22 +673,35 @@ constexpr int block_wave_lds() {
   static_assert(32 * (DH + 8) <= 2 * 32 * kDsPitch, "a tile of rows passes through the two dS tiles' place");
   return 3 * 32 * (DH + 8) * 2 + 2 * 32 * kDsPitch * 2 + 2 * 32 * 4;  // Q, dO and K tiles, two dS tiles, lse and D
 }
+// Sentences of nt tiles that W wavefronts (a power of two) share: W / nt, as the power of two it is for nt up to 8.
+template <int W>
+__device__ __forceinline__ int teams_log2(int nt) {
+  constexpr int kLog2W = W == 8 ? 3 : 2;
+  static_assert(W == 1 << kLog2W && 8 / 3 == 2 && 4 / 3 == 1, "W / nt rounded down is a power of two");
+  return max(0, kLog2W - (32 - __builtin_clz((unsigned)nt * 2u - 1u) - 1));
+}
 template <int DH, int W>
 __device__ __forceinline__ void attn_bwd_tiles_item(const AttnArgs& a, int nt, int pair, int pairs, unsigned char* smem) {
   constexpr int DHP = DH < 32 ? 32 : DH, KS = DH / 16, DT = DHP / 32, PR = DH + 8, LDS = block_wave_lds<DH>();
   const int lane = threadIdx.x & 63, g = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int group = wave / nt, j = wave - group * nt, at = pair + group;
+  const int teams = 1 << teams_log2<W>(nt);
+  int group = 0;  // wave / nt
+#pragma unroll
+  for (int w = 1; w < W; ++w) group += wave >= w * nt ? 1 : 0;
+  const int j = wave - group * nt, at = pair + group;
   // the group's (sentence, head); a group past the end, or of another class where there is no list, only keeps the barriers
-  bool live = group < W / nt && at < pairs;
+  bool live = group < teams && at < pairs;
   Sent se = {0, 0, 0, 0};
   int h = 0;
   if (live) {
-    h = at % a.H;
+    uint32_t head;
+    const int sent = (int)div_mod((uint32_t)at, a.by_h, head);
+    h = (int)head;
     if (a.wl_sent) {
-      const int4 t = a.wl_sent[(size_t)(nt - 1) * a.B + at / a.H];
+      const int4 t = a.wl_sent[(size_t)(nt - 1) * a.B + sent];
       se = Sent{t.x, t.y, t.z, t.w};
     } else {
-      se = sentence(a, at / a.H);
+      se = sentence(a, sent);
       live = (max(max(se.Tq, se.Tk), 1) + 31) >> 5 == nt;
     }
   }
@@ -781,7 +801,7 @@ __device__ __forceinline__ void attn_bwd_tiles_item(const AttnArgs& a, int nt, i
     __syncthreads();  // the two query tiles' dS tiles are complete; their Q tiles have been read for the last time
     for (int x = j; x < 2 * DT; x += nt) {
       const int qt = q0 + x / DT, t = x % DT;
-      if (group >= W / nt || qt >= nqt) continue;
+      if (group >= teams || qt >= nqt) continue;
       const int last = a.causal ? min(qt + 1, nkt) : nkt;
       floatx16 dQ = zero16();
       for (int kt = 0; kt < last; ++kt) {
@@ -820,11 +840,29 @@ __device__ __forceinline__ void attn_bwd_tiles_item(const AttnArgs& a, int nt, i
 template <int DH, int W>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2))) attn_bwd_tiles_kernel(const AttnArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  int v = blockIdx.x;
-  for (int nt = a.cls_hi; nt >= a.cls_lo; --nt) {
-    const int pairs = (a.wl_sent ? a.wl_counts[nt - 1] : a.B) * a.H, per = W / nt, items = (pairs + per - 1) / per;
-    for (; v < items; v += gridDim.x) attn_bwd_tiles_item<DH, W>(a, nt, v * per, pairs, smem_raw);
-    v -= items;
+  touch(a);
+  // work items of each class, longest sentences first; the counts come in one trip, and an item's class is found without another
+  int pairs[kBwdTiles], items[kBwdTiles];
+#pragma unroll
+  for (int nt = 1; nt <= kBwdTiles; ++nt) pairs[nt - 1] = a.wl_sent ? a.wl_counts[nt - 1] : a.B;
+#pragma unroll
+  for (int nt = 1; nt <= kBwdTiles; ++nt) {
+    const int lg = teams_log2<W>(nt);
+    pairs[nt - 1] = nt >= a.cls_lo && nt <= a.cls_hi ? pairs[nt - 1] * a.H : 0;
+    items[nt - 1] = (pairs[nt - 1] + (1 << lg) - 1) >> lg;
+  }
+  for (int v = blockIdx.x;; v += a.stride) {
+    int at = v, nt = 0, of = 0;
+#pragma unroll
+    for (int c = kBwdTiles; c >= 1; --c) {
+      if (!nt && at < items[c - 1]) {
+        nt = c;
+        of = pairs[c - 1];
+      }
+      if (!nt) at -= items[c - 1];
+    }
+    if (!nt) break;
+    attn_bwd_tiles_item<DH, W>(a, nt, at << teams_log2<W>(nt), of, smem_raw);
   }
 }
 
@@ -891,6 +929,9 @@ int fwd_launch(const AttnArgs& a0, hipStream_t stream) {
   const int64_t total = (int64_t)a.vgx * a.vgy;
   NMT_REQUIRE(total < (1ll << 31), "attention_fwd: too many work items");
   const int64_t grid = (total < resident || !tuning().attn_persist) ? total : resident;  // (not persistent: one work item per work-group)
+  a.stride = (int)grid;
+  a.by_vgx = divisor((uint32_t)a.vgx);
+  a.by_hg = divisor((uint32_t)ceil_div(a.H, 4));
   hipLaunchKernelGGL(attn_fwd_kernel<DH>, dim3((unsigned)grid), dim3(kThreads), tile_smem<DH>(), stream, a);
   NMT_LAUNCH_CHECK();
   return NMT_OK;
@@ -912,6 +953,8 @@ int fused_launch(const AttnArgs& a, int n_k_rows, hipStream_t stream) {
     resident_once.store(resident, std::memory_order_relaxed);
   }
   const int grid = (b.vgx < resident || !tuning().attn_persist) ? b.vgx : resident;  // (not persistent: one item per work-group)
+  b.stride = grid;
+  b.by_hg = divisor((uint32_t)ceil_div(a.H, kWaves));
   hipLaunchKernelGGL((attn_bwd_fused_kernel<DH, NT>), dim3((unsigned)grid), dim3(64 * kWaves), smem, stream, b);
   NMT_LAUNCH_CHECK();
   return NMT_OK;
@@ -934,6 +977,8 @@ int tiles_launch(const AttnArgs& a0, int lo, int hi, int n_k_rows, hipStream_t s
     resident_once.store(resident, std::memory_order_relaxed);
   }
   const int64_t grid = (most < resident || !tuning().attn_persist) ? most : resident;
+  a.stride = (int)grid;
+  a.by_h = divisor((uint32_t)a.H);
   hipLaunchKernelGGL((attn_bwd_tiles_kernel<DH, W>), dim3((unsigned)grid), dim3(64 * W), smem, stream, a);
   NMT_LAUNCH_CHECK();
   return NMT_OK;
@@ -962,6 +1007,7 @@ int bwd_launch(const AttnArgs& a0, int n_k_rows, hipStream_t stream) {
   // longer ones: a wavefront per 32 queries for dQ, a wavefront per 32 keys for dK and dV
   if (int rc = allow_big_lds(attn_bwd_dkv_kernel<DH>, dkv_smem<DH>())) return rc;
   const int groups = a.B * ((a.H + 3) / 4);
+  a.by_hg = divisor((uint32_t)ceil_div(a.H, 4));
   hipLaunchKernelGGL(attn_bwd_dq_kernel<DH>, dim3(groups, ceil_div(a.Tq, 32)), dim3(kThreads), tile_smem<DH>(), stream, a);
   NMT_LAUNCH_CHECK();
   hipLaunchKernelGGL(attn_bwd_dkv_kernel<DH>, dim3(groups, ceil_div(a.Tk, 32)), dim3(kThreads), dkv_smem<DH>(), stream, a);
