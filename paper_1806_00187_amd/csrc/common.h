@@ -172,6 +172,16 @@ __device__ __forceinline__ void touch(const Args& a) {
   for (size_t i = 0; i < sizeof(w) / 4; ++i) asm volatile("" ::"s"(w[i]));
 }
 
+// The same for a kernel whose arguments, BYTES of them, are no struct.
+template <int BYTES>
+__device__ __forceinline__ void touch_arguments() {
+  const auto* words = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
+  uint32_t w[(BYTES + 63) / 64];
+#pragma unroll
+  for (int i = 0; i < (BYTES + 63) / 64; ++i) w[i] = words[i + 1 < (BYTES + 63) / 64 ? 16 * i : BYTES / 4 - 1];
+#pragma unroll
+  for (int i = 0; i < (BYTES + 63) / 64; ++i) asm volatile("" ::"s"(w[i]));
+}
 // Division by a number the host knows, without the reciprocal the compiler would form first (100 instructions' time in front of a kernel's first load).
 struct Divisor {
   uint32_t d = 1, m = 0xFFFFFFFFu;  // m = floor(2^32 / d): the high word of n m is n / d or one less

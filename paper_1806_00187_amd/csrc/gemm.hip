@@ -279,7 +279,7 @@ __device__ __forceinline__ void buffer_store_half8(__amdgpu_buffer_rsrc_t r, uin
 // masks in the pieces the results leave in -- is requested before the first operands, so that nothing is waited for behind the last product but LDS; the
 // wavefront's whole share of the tile passes through LDS at once and leaves in whole rows, bounds by the descriptor of C, no branches.  (Loading the
 // bias with each 32 rows, every load waited for the stores before it: with that and the order of tiles computed by division, 4.0 us of each product of a few
-// hundred rows besides its k-tiles; now XX.)
+// hundred rows besides its k-tiles, whole forward pass of 3100 x 512 1360 us; now 1237.)
 template <int BM, int BN, int NW, int STAGE, StoreForm FORM>
 struct TileStore {
   static constexpr int WGN = NW / 2, WM = BM / 2, WN = BN / WGN, TM = WM / 16, TN = WN / 16;

@@ -63,20 +63,30 @@ __global__ void __launch_bounds__(kThreads) embed_fwd_kernel(const int32_t* __re
 // 1370 / 1295, 3000 x 512 3830 / 3780; 3000 to 17700 x 1024 the same within 0.5 %.  (The kernels themselves, on one stream, take up to 10 % longer at
 // 3000 to 30000 rows -- 6000 x 512, five calls forward: 28.5 / 30.2 us --; of whole passes of 550 sizes and widths on one stream none was slower by more than 0.3 %.)
 // ------------------------------------------------------------------------------------------------
-template <int NCH>
+// kKeyedRows: there are row keys (passes of a model have them; without, a branch stands between a row's key and its other loads).  kFullRows: and rows
+// of 512 NCH columns (no branch around any load, so that the draws run while the row is on its way, and divisions by a power of two).  With that,
+// and the arguments asked for together, forward passes, us: 3100 x 512 1225 -> 1185, 380 x 1024 985 -> 947, 3000 x 1024 2277 -> 2229.
+enum RowForm { kAnyRows, kKeyedRows, kFullRows };
+RowForm row_form(const DropDev& drop, int d, int nch) { return !drop.rowkey ? kAnyRows : d == 512 * nch ? kFullRows : kKeyedRows; }
+
+template <int NCH, RowForm FORM>
 __device__ __forceinline__ void load_presum(float (&y)[NCH][8], const half_t* __restrict__ sub,
                                             const half_t* __restrict__ resid, int row, int d, int lane,
                                             const DropDev& drop) {
+  constexpr bool KEYED = FORM != kAnyRows, FULL = FORM == kFullRows;
   const int chunks = d >> 3;
-  half8_t hs[NCH], hr[NCH];  // everything the row needs is requested before anything is used
-  DropRow key = {};
-  if (drop.thr) key = drop_row(drop, (uint32_t)row);
+  half8_t hs[NCH], hr[NCH];  // everything the row needs is requested before anything is used, its key first, which the draws begin with
+  uint2 rk = {};
+  if constexpr (KEYED) rk = drop.rowkey[row];
 #pragma unroll
   for (int i = 0; i < NCH; ++i) {
     const int c = lane + kWave * i;
-    hs[i] = c < chunks ? ld_half8(sub + (size_t)row * d + c * 8) : zero_half8();
-    hr[i] = c < chunks ? ld_half8(resid + (size_t)row * d + c * 8) : zero_half8();
+    hs[i] = FULL || c < chunks ? ld_half8(sub + (size_t)row * d + c * 8) : zero_half8();
+    hr[i] = FULL || c < chunks ? ld_half8(resid + (size_t)row * d + c * 8) : zero_half8();
   }
+  DropRow key = {};
+  if constexpr (KEYED) key = drop_row_of(drop, rk);
+  else if (drop.thr) key = drop_row(drop, (uint32_t)row);
 #pragma unroll
   for (int i = 0; i < NCH; ++i) {
     const uint32_t bits = drop.thr ? drop_keep8(drop, key, (uint32_t)(lane + kWave * i)) : 0xFFu;
@@ -85,11 +95,14 @@ __device__ __forceinline__ void load_presum(float (&y)[NCH][8], const half_t* __
   }
 }
 
-template <int NCH>
+template <int NCH, RowForm FORM>
 __global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(const half_t* __restrict__ sub, const half_t* __restrict__ resid,
                                                               const half_t* __restrict__ gamma, const half_t* __restrict__ beta,
                                                               half_t* __restrict__ out, float* __restrict__ stats, int rows,
-                                                              int d, float eps, DropDev drop) {
+                                                              int d_in, float eps, DropDev drop) {
+  constexpr bool FULL = FORM == kFullRows;
+  const int d = FULL ? 512 * NCH : d_in;
+  touch_arguments<64 + sizeof(DropDev)>();
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   if (row >= rows) return;
@@ -99,10 +112,10 @@ __global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(const half_t* __re
 #pragma unroll
   for (int i = 0; i < NCH; ++i) {
     const int c = lane + kWave * i;
-    gam[i] = c < chunks ? ld_half8(gamma + c * 8) : zero_half8();
-    bet[i] = c < chunks ? ld_half8(beta + c * 8) : zero_half8();
+    gam[i] = FULL || c < chunks ? ld_half8(gamma + c * 8) : zero_half8();
+    bet[i] = FULL || c < chunks ? ld_half8(beta + c * 8) : zero_half8();
   }
-  load_presum<NCH>(y, sub, resid, row, d, lane, drop);
+  load_presum<NCH, FORM>(y, sub, resid, row, d, lane, drop);
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < NCH; ++i)
@@ -112,7 +125,7 @@ __global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(const half_t* __re
   float q = 0.f;
 #pragma unroll
   for (int i = 0; i < NCH; ++i)
-    if (lane + kWave * i < chunks) {
+    if (FULL || lane + kWave * i < chunks) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) q += (y[i][e] - mean) * (y[i][e] - mean);
     }
@@ -120,7 +133,7 @@ __global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(const half_t* __re
 #pragma unroll
   for (int i = 0; i < NCH; ++i) {
     const int c = lane + kWave * i;
-    if (c < chunks) {
+    if (FULL || c < chunks) {
       float o[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) o[e] = (y[i][e] - mean) * rstd * (float)gam[i][e] + (float)bet[i][e];
@@ -140,20 +153,23 @@ __global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(const half_t* __re
 // then the result), which keeps the kernel at four wavefronts per SIMD.
 constexpr int kLnBwdMaxBlocks = 1024;
 
-template <int NCH, int ROWS, int WAVES>
+template <int NCH, int ROWS, int WAVES, RowForm FORM>
 __global__ void __launch_bounds__(64 * WAVES) res_ln_bwd_kernel(const half_t* __restrict__ dout, const half_t* __restrict__ sub,
                                                               const half_t* __restrict__ resid, const half_t* __restrict__ gamma,
                                                               const float* __restrict__ stats, half_t* __restrict__ dy_out,
                                                               half_t* __restrict__ dym_out, float* __restrict__ partial, int rows,
-                                                              int d, DropDev drop) {
+                                                              int d_in, DropDev drop) {
+  constexpr bool KEYED = FORM != kAnyRows, FULL = FORM == kFullRows;
+  const int d = FULL ? 512 * NCH : d_in;
   extern __shared__ __align__(16) float red[];  // [WAVES][NCH][2][64 lanes][4]
+  touch_arguments<72 + sizeof(DropDev)>();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int chunks = d >> 3;
   float sg[NCH][8], sb[NCH][8], sbias[NCH][8];
   half8_t gam[NCH];
 #pragma unroll
   for (int i = 0; i < NCH; ++i) {
-    gam[i] = lane + kWave * i < chunks ? ld_half8(gamma + (lane + kWave * i) * 8) : zero_half8();
+    gam[i] = FULL || lane + kWave * i < chunks ? ld_half8(gamma + (lane + kWave * i) * 8) : zero_half8();
 #pragma unroll
     for (int e = 0; e < 8; ++e) sg[i][e] = sb[i][e] = sbias[i][e] = 0.f;
   }
@@ -161,6 +177,11 @@ __global__ void __launch_bounds__(64 * WAVES) res_ln_bwd_kernel(const half_t* __
     half8_t hs[ROWS][NCH], hr[ROWS][NCH], hg[ROWS][NCH];
     uint32_t bits[ROWS][NCH];
     DropRow key[ROWS] = {};
+    uint2 rk[ROWS];
+    if constexpr (KEYED) {
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u) rk[u] = drop.rowkey[min(row0 + u, rows - 1)];
+    }
     float mean[ROWS], rstd[ROWS], s1[ROWS], s2[ROWS];
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
@@ -168,14 +189,18 @@ __global__ void __launch_bounds__(64 * WAVES) res_ln_bwd_kernel(const half_t* __
 #pragma unroll
       for (int i = 0; i < NCH; ++i) {
         const int c = lane + kWave * i;
-        const bool in = c < chunks;
+        const bool in = FULL || c < chunks;
         hs[u][i] = in ? ld_half8(sub + (size_t)row * d + c * 8) : zero_half8();
         hr[u][i] = in ? ld_half8(resid + (size_t)row * d + c * 8) : zero_half8();
         hg[u][i] = in ? ld_half8(dout + (size_t)row * d + c * 8) : zero_half8();
       }
       mean[u] = stats[2 * row];
       rstd[u] = stats[2 * row + 1];
-      if (drop.thr) key[u] = drop_row(drop, (uint32_t)row);
+      if (!KEYED && drop.thr) key[u] = drop_row(drop, (uint32_t)row);
+    }
+    if constexpr (KEYED) {
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u) key[u] = drop_row_of(drop, rk[u]);
     }
 #pragma unroll
     for (int u = 0; u < ROWS; ++u)
@@ -192,7 +217,7 @@ __global__ void __launch_bounds__(64 * WAVES) res_ln_bwd_kernel(const half_t* __
       s1[u] = s2[u] = 0.f;
 #pragma unroll
       for (int i = 0; i < NCH; ++i) {
-        if (lane + kWave * i < chunks) {
+        if (FULL || lane + kWave * i < chunks) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             const float xh = xhat(u, i, e), go = (float)hg[u][i][e];
@@ -225,7 +250,7 @@ __global__ void __launch_bounds__(64 * WAVES) res_ln_bwd_kernel(const half_t* __
 #pragma unroll
       for (int i = 0; i < NCH; ++i) {
         const int c = lane + kWave * i;
-        if (c < chunks) {
+        if (FULL || c < chunks) {
           float dy[8], dm[8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
@@ -982,6 +1007,13 @@ int launch_embed_fwd(const int32_t* ids, const half_t* E, half_t* x, int rows, i
   return NMT_OK;
 }
 
+// The kernel of the form the rows have.
+#define NMT_ROW_FORM(run, kernel, ...)                                \
+  switch (row_form(drop, d, ln_nch(d))) {                             \
+    case kFullRows: run(kernel<__VA_ARGS__, kFullRows>); break;       \
+    case kKeyedRows: run(kernel<__VA_ARGS__, kKeyedRows>); break;     \
+    default: run(kernel<__VA_ARGS__, kAnyRows>);                      \
+  }
 int launch_residual_layernorm_fwd(const half_t* sub, const half_t* resid, const half_t* gamma, const half_t* beta,
                                   half_t* out, float* stats, int rows, int d, float eps, const DropDev& drop,
                                   hipStream_t stream) {
@@ -990,10 +1022,11 @@ int launch_residual_layernorm_fwd(const half_t* sub, const half_t* resid, const 
   NMT_REQUIRE(aligned16(sub) && aligned16(resid) && aligned16(gamma) && aligned16(beta) && aligned16(out), "layernorm: misaligned pointer");
   NMT_REQUIRE(!drop.thr || drop.n_pos > 0, "layernorm: positions per sentence must be positive");
   const dim3 grid(ceil_div(rows, kWavesPerBlock)), block(kThreads);
+  auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, sub, resid, gamma, beta, out, stats, rows, d, eps, drop); };
   switch (ln_nch(d)) {
-    case 1: hipLaunchKernelGGL(res_ln_fwd_kernel<1>, grid, block, 0, stream, sub, resid, gamma, beta, out, stats, rows, d, eps, drop); break;
-    case 2: hipLaunchKernelGGL(res_ln_fwd_kernel<2>, grid, block, 0, stream, sub, resid, gamma, beta, out, stats, rows, d, eps, drop); break;
-    default: hipLaunchKernelGGL(res_ln_fwd_kernel<4>, grid, block, 0, stream, sub, resid, gamma, beta, out, stats, rows, d, eps, drop); break;
+    case 1: NMT_ROW_FORM(run, res_ln_fwd_kernel, 1); break;
+    case 2: NMT_ROW_FORM(run, res_ln_fwd_kernel, 2); break;
+    default: NMT_ROW_FORM(run, res_ln_fwd_kernel, 4); break;
   }
   NMT_LAUNCH_CHECK();
   return NMT_OK;
@@ -1038,7 +1071,8 @@ int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const h
   const int nblk = ln_bwd_blocks(rows, d);
   const dim3 grid(nblk), block(kWave * form.waves);
   const size_t smem = (size_t)form.waves * nch * 512 * sizeof(float);
-#define NMT_LN_BWD(N, R, W) hipLaunchKernelGGL((res_ln_bwd_kernel<N, R, W>), grid, block, smem, stream, dout, sub, resid, gamma, stats, dy, dym, partial, rows, d, drop)
+  auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, smem, stream, dout, sub, resid, gamma, stats, dy, dym, partial, rows, d, drop); };
+#define NMT_LN_BWD(N, R, W) NMT_ROW_FORM(run, res_ln_bwd_kernel, N, R, W)
   switch (nch * 4 + (form.waves == 8 ? 2 : form.rows_per_wave - 1)) {
     case 4: NMT_LN_BWD(1, 1, 4); break;
     case 5: NMT_LN_BWD(1, 2, 4); break;
