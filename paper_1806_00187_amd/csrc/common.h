@@ -275,9 +275,34 @@ int launch_attention_bwd(const half_t* Q, int ldq, const half_t* K, int ldk, con
                          int causal, int B, int H, int dh, int Tq, int Tk, const int4* sent_tab, int n_q_rows,
                          const AttnWork* work, hipStream_t stream);
 
+// A stretch of weights that products soon after a LayerNorm read.  A pass touches each weight once, and between two passes the activations and the
+// optimizer's state push it out of the 256 MB last-level cache: a product of few rows then waits for memory at each k-tile (3100 x 2048 x 512 and the
+// 3100 x 512 x 2048 that reads its result: 21.9 us with the weights and that result in the cache, 27.6 with neither).  So the LayerNorm's launch has work-groups of its own,
+// behind the rows', that read one word of each 128-byte line and drop it: the compute units are not full then, and memory is nearly idle.  With the
+// products' results kept in the same cache (kWriteThrough in the products' file), Transformer-base on 2990 tokens, forward / backward 1196 / 1762 -> 1164 / 1724 us,
+// Transformer-big on 380 tokens 956 / 1401 -> 901 / 1310, on 2600 tokens 2230 / 3840 -> 2220 / 3774; 40000 tokens lose nothing (9180 / 16680 -> 9065 / 16615), so
+// every number of rows does it.  Activations asked for in the same way cost more than they gave (backward +1 to +3 %: they are read at memory's full rate already).
+struct Ahead {
+  const half_t* p = nullptr;
+  uint32_t lines = 0, first = 0;  // 128-byte lines; the work-groups of rows, which come first (the launcher's)
+};
+constexpr int kAheadThreads = 256, kAheadLoads = 2;  // of a work-group: 64 KB
+static inline Ahead ahead(const half_t* p, int64_t halves) { return Ahead{p, (uint32_t)(halves / 64), 0}; }  // (whole lines: nothing behind the stretch is read)
+static inline int ahead_groups(const Ahead& a) { return ceil_div(a.lines, kAheadThreads * kAheadLoads); }
+__device__ __forceinline__ void ask_ahead(const Ahead& a, int group) {
+  if ((int)threadIdx.x >= kAheadThreads) return;
+  uint32_t v[kAheadLoads];
+#pragma unroll
+  for (int i = 0; i < kAheadLoads; ++i) {
+    const uint32_t line = ((uint32_t)group * kAheadLoads + i) * kAheadThreads + threadIdx.x;
+    v[i] = *reinterpret_cast<const uint32_t*>(a.p + (size_t)min(line, a.lines - 1) * 64);
+  }
+#pragma unroll
+  for (int i = 0; i < kAheadLoads; ++i) asm volatile("" ::"v"(v[i]));
+}
 int launch_residual_layernorm_fwd(const half_t* sub, const half_t* resid, const half_t* gamma, const half_t* beta,
                                   half_t* out, float* stats, int rows, int d, float eps, const DropDev& drop,
-                                  hipStream_t stream);
+                                  hipStream_t stream, const Ahead& next = {});
 int64_t layernorm_bwd_scratch_floats(int d);                        // partial sums of a call of any number of rows ...
 int64_t layernorm_bwd_partial_floats(int most_rows, int d);         // ... of up to `most_rows`
 // Partial rows of column sums as a kernel left them: `rows` rows of up to three quantities, and where their totals go.
@@ -326,7 +351,7 @@ __device__ __forceinline__ void finalize_columns(const FinalizeArgs& a, int bloc
 int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const half_t* resid, const half_t* gamma,
                                   const float* stats, half_t* dy, half_t* dym, half_t* dgamma, half_t* dbeta,
                                   half_t* dbias, float* partial, int rows, int d, const DropDev& drop,
-                                  hipStream_t stream, ColumnSums& sums);
+                                  hipStream_t stream, ColumnSums& sums, const Ahead& next = {});
 int launch_layernorm_param_grads(const ColumnSums* sums, int n, int d, float scale, hipStream_t stream);  // scale: factor on all of them
 // What lies between two attentions of a narrow model, row by row, in one launch each way (d = 64, 128 or 256; see row_chain_fits).  Rows of
 // d columns are contiguous.  Forward: s1 = o wo^T + bo, x1 = LN(x + dropout(s1)); if F: h = relu(x1 w1^T + b1), s2 = h w2^T + b2, x2 = LN(x1 +

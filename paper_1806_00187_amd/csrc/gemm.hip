@@ -74,6 +74,7 @@ struct GemmArgs {
   half_t* colsum = nullptr;
   float* partial_colsum = nullptr;
   TileOrder order = {};
+  int keep = 0;  // the result is written through (else non-temporally)
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const half_t* p, uint32_t bytes) {
@@ -264,15 +265,21 @@ enum StoreForm { kStorePlain, kStoreBias, kStoreRelu, kStoreAdd, kStoreMask, kSt
 typedef _Float16 half4v_t __attribute__((ext_vector_type(4)));
 typedef float floatx8 __attribute__((ext_vector_type(8)));
 typedef uint32_t uint4v_t __attribute__((ext_vector_type(4)));
-constexpr int kStream = 2;  // non-temporal
+constexpr int kStream = 2;         // non-temporal
+constexpr int kWriteThrough = 16;  // device scope
+// A result up to this size is written through to the last-level cache, where the next kernel finds it: a non-temporal one it reads from memory.  Larger ones
+// push out what the kernels after it read: written through without a limit, a batch of 26000 tokens in validation (results of 54 to 100 MB) took 4 % longer, 16
+// batches of Transformer-big 2.5 % longer forward; with the limit neither changes and Transformer-base on 2990 tokens gains 1.5 % (with the weights read ahead).
+constexpr int64_t kKeptBytes = 16ll << 20;
 // 16 bytes at byte offset `off` (past the extent: zeros come back, nothing is stored)
 __device__ __forceinline__ half8_t buffer_half8(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
 }
 // streaming store: a result tile is not read again by its product, and letting it stay in L2 pushes out
 // the operand panels the XCD's other tiles are reading (products with wide results: +5-7 %)
+template <int POLICY = kStream>
 __device__ __forceinline__ void buffer_store_half8(__amdgpu_buffer_rsrc_t r, uint32_t off, half8_t v) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4v_t, v), r, (int)off, 0, kStream);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4v_t, v), r, (int)off, 0, POLICY);
 }
 
 // Epilogue of one tile whose form is known when it is compiled.  What it loads -- the bias of the lane's columns as the sums lie in registers, or what is added or
@@ -331,7 +338,11 @@ struct TileStore {
         }
       wave_sync();
 #pragma unroll
-      for (int q = 0; q < P; ++q) buffer_store_half8(to, at + q * step, *reinterpret_cast<const half8_t*>(place(q * RPI + r0, c8)));
+      for (int q = 0; q < P; ++q) {
+        const half8_t v = *reinterpret_cast<const half8_t*>(place(q * RPI + r0, c8));
+        if (g.keep) buffer_store_half8<kWriteThrough>(to, at + q * step, v);
+        else buffer_store_half8(to, at + q * step, v);
+      }
     } else {
       // the sums as they are (one rounding, at the end); 16-byte chunks of four columns
       auto place = [&](int r, int c) { return own + r * (4 * WN) + ((WN == 64 ? c ^ (r & 15) : c ^ (r >> 1 & 7)) << 4); };
@@ -349,7 +360,9 @@ struct TileStore {
           const float x = e < 4 ? lo[e] : hi[e - 4];
           v[e] = FORM == kStoreAdd ? x + (float)pre[q][e] : (float)pre[q][e] > 0.f ? x * g.ep.mask_scale : 0.f;
         }
-        buffer_store_half8(to, at + q * step, __builtin_convertvector(v, half8_t));
+        const half8_t o = __builtin_convertvector(v, half8_t);
+        if (g.keep) buffer_store_half8<kWriteThrough>(to, at + q * step, o);
+        else buffer_store_half8(to, at + q * step, o);
       }
     }
   }
@@ -1310,6 +1323,7 @@ int launch_tile(const GemmArgs& a, bool a_t, bool b_t, int splits, hipStream_t s
     splits = 1;
   }
   g.order = tile_order(ceil_div(g.M, BM), ceil_div(g.N, BN), splits, group_m, device_info().xcds);
+  g.keep = (int64_t)g.M * g.N * 2 <= kKeptBytes;
   constexpr bool kForms = BM < 256;  // (256 x 256 tiles have theirs in the persistent form)
   const StoreForm form = kForms && !a_t ? store_form(g.ep, b_t, g.partial != nullptr) : kStoreAny;
   auto run = [&](auto at, auto bt, auto f) { launch_variant<BM, BN, decltype(at)::value, decltype(bt)::value, NS, NW, decltype(f)::value>(g, splits, stream); };

@@ -613,6 +613,7 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
                  wl_ts = attention_work(r.ws<int32_t>(p.wl_ts), Bt, Nt, Ns);
 
   const bool chains = use_row_chains(c);
+  auto weights = [&](int64_t from, int64_t to) { return ahead(r.w(from), to - from); };  // (those of the next products, in the order they lie in)
   // a chain up to its first LayerNorm, a feed-forward sub-layer behind it, a projection at its end
   auto chain = [&](const Run& on, bool tgt, const AttnP& a, int64_t o, const half_t* resid, const LnP& ln, int64_t s, int64_t x_out, int64_t st_out, uint32_t site) {
     RowChainFwd f = {};
@@ -646,7 +647,7 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
     }
     NMT_TRY(on.linear(on.ws<half_t>(W.o1), Nt, d, P.self.wo, P.self.bo, d, on.ws<half_t>(W.s1)));
     NMT_TRY(launch_residual_layernorm_fwd(on.ws<half_t>(W.s1), y, on.w(P.ln1.g), on.w(P.ln1.b), on.ws<half_t>(W.x1), on.ws<float>(W.st1),
-                                          Nt, d, k.ln_eps, on.drop(layer_site(li, kKindSelfRes), true, k.dropout), on.st));
+                                          Nt, d, k.ln_eps, on.drop(layer_site(li, kKindSelfRes), true, k.dropout), on.st, weights(P.cross.wq, P.cross.bo)));
     return on.linear(on.ws<half_t>(W.x1), Nt, d, P.cross.wq, P.cross.bq, d, on.ws<half_t>(W.q));
   };
   auto embed_targets = [&](const Run& on) {
@@ -692,14 +693,15 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
     }
     NMT_TRY(r.linear(r.ws<half_t>(W.o), Ns, d, P.attn.wo, P.attn.bo, d, r.ws<half_t>(W.s1)));
     NMT_TRY(launch_residual_layernorm_fwd(r.ws<half_t>(W.s1), x, r.w(P.ln1.g), r.w(P.ln1.b), r.ws<half_t>(W.x1), r.ws<float>(W.st1),
-                                          Ns, d, k.ln_eps, r.drop(layer_site(l, kKindSelfRes), false, k.dropout), st));
+                                          Ns, d, k.ln_eps, r.drop(layer_site(l, kKindSelfRes), false, k.dropout), st, weights(P.ffn.w1, P.ffn.b2)));
     GemmEpilogue act;
     act.relu = 1;
     act.drop = r.drop(layer_site(l, kKindFfnAct), false, k.act_dropout);
     NMT_TRY(r.linear(r.ws<half_t>(W.x1), Ns, d, P.ffn.w1, P.ffn.b1, F, r.ws<half_t>(W.h), act));
     NMT_TRY(r.linear(r.ws<half_t>(W.h), Ns, F, P.ffn.w2, P.ffn.b2, d, r.ws<half_t>(W.s2)));
     NMT_TRY(launch_residual_layernorm_fwd(r.ws<half_t>(W.s2), r.ws<half_t>(W.x1), r.w(P.ln2.g), r.w(P.ln2.b), r.ws<half_t>(W.x2),
-                                          r.ws<float>(W.st2), Ns, d, k.ln_eps, r.drop(layer_site(l, kKindFfnRes), false, k.dropout), st));
+                                          r.ws<float>(W.st2), Ns, d, k.ln_eps, r.drop(layer_site(l, kKindFfnRes), false, k.dropout), st,
+                                          l + 1 < k.enc_layers ? weights(c->enc[l + 1].attn.wqkv, c->enc[l + 1].attn.bo) : Ahead{}));
     x = r.ws<half_t>(W.x2);
     if (self_beside && l == 0) NMT_TRY(decoder_ahead());
   }
@@ -743,14 +745,15 @@ int forward_pass(nmt_ctx* c, const GroupDims& gd, const TableSource& tsrc, const
     }
     NMT_TRY(r.linear(r.ws<half_t>(W.o2), Nt, d, P.cross.wo, P.cross.bo, d, r.ws<half_t>(W.s2)));
     NMT_TRY(launch_residual_layernorm_fwd(r.ws<half_t>(W.s2), r.ws<half_t>(W.x1), r.w(P.ln2.g), r.w(P.ln2.b), r.ws<half_t>(W.x2),
-                                          r.ws<float>(W.st2), Nt, d, k.ln_eps, r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st));
+                                          r.ws<float>(W.st2), Nt, d, k.ln_eps, r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st, weights(P.ffn.w1, P.ffn.b2)));
     GemmEpilogue act;
     act.relu = 1;
     act.drop = r.drop(layer_site(li, kKindFfnAct), true, k.act_dropout);
     NMT_TRY(r.linear(r.ws<half_t>(W.x2), Nt, d, P.ffn.w1, P.ffn.b1, F, r.ws<half_t>(W.h), act));
     NMT_TRY(r.linear(r.ws<half_t>(W.h), Nt, F, P.ffn.w2, P.ffn.b2, d, r.ws<half_t>(W.s3)));
     NMT_TRY(launch_residual_layernorm_fwd(r.ws<half_t>(W.s3), r.ws<half_t>(W.x2), r.w(P.ln3.g), r.w(P.ln3.b), r.ws<half_t>(W.x3),
-                                          r.ws<float>(W.st3), Nt, d, k.ln_eps, r.drop(layer_site(li, kKindFfnRes), true, k.dropout), st));
+                                          r.ws<float>(W.st3), Nt, d, k.ln_eps, r.drop(layer_site(li, kKindFfnRes), true, k.dropout), st,
+                                          l + 1 < k.dec_layers ? weights(c->dec[l + 1].self.wqkv, c->dec[l + 1].self.bo) : Ahead{}));
     y = r.ws<half_t>(W.x3);
   }
 
@@ -858,6 +861,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
   // The same as chains: everything from one attention's backward to the next one's.  What is still to be multiplied when a
   // chain begins (the gradient at the projections of the attention behind it) is its head.
   const bool chains = use_row_chains(c);
+  auto weights = [&](int64_t from, int64_t to) { return ahead(r.w(from), to - from); };  // (those of the next products, in the order they lie in)
   struct Head { const half_t* a; int k; int64_t w; const half_t* dy; } head = {};
   auto chain_ln = [&](int N, bool tgt, const half_t* sub, const half_t* resid, const float* stats, const LnP& ln, int64_t bias, uint32_t site) {
     begin_sublayer(sub);
@@ -887,7 +891,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
                      const FfnP& f, const LnP& ln, uint32_t site_res) -> int {
     begin_sublayer(sub);
     NMT_TRY(launch_residual_layernorm_bwd(dx, sub, x_in, r.w(ln.g), stats, dy, dym, r.g(ln.g), r.g(ln.b), r.g(f.b2), lnpart, N, d,
-                                          r.drop(site_res, tgt, k.dropout), st, ln_sums[sub_at - 1]));
+                                          r.drop(site_res, tgt, k.dropout), st, ln_sums[sub_at - 1], weights(f.w1, f.b2)));
     leaf(dsub, N, d, hact, F, f.w2);
     GemmEpilogue relu_bwd;
     relu_bwd.relu_src = hact;
@@ -913,7 +917,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
     }
     begin_sublayer(sub);
     NMT_TRY(launch_residual_layernorm_bwd(dx, sub, x_in, r.w(ln.g), stats, dy, dym, r.g(ln.g), r.g(ln.b), r.g(a.bo), lnpart, N, d,
-                                          r.drop(site_res, tgt, k.dropout), on.st, ln_sums[sub_at - 1]));
+                                          r.drop(site_res, tgt, k.dropout), on.st, ln_sums[sub_at - 1], weights(a.wqkv, a.bo)));
     leaf(dsub, N, d, o, d, a.wo);
     return on.dgrad(dsub, N, d, a.wo, d, dO);
   };
@@ -984,7 +988,7 @@ extern "C" int nmt_backward(nmt_ctx* ctx, void* stream) {
       begin_sublayer(r.ws<half_t>(W.s2));
       NMT_TRY(launch_residual_layernorm_bwd(dx, r.ws<half_t>(W.s2), r.ws<half_t>(W.x1), r.w(P.ln2.g), r.ws<float>(W.st2), dy, dym,
                                             r.g(P.ln2.g), r.g(P.ln2.b), r.g(P.cross.bo), lnpart, Nt, d,
-                                            r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st, ln_sums[sub_at - 1]));
+                                            r.drop(layer_site(li, kKindCrossRes), true, k.dropout), st, ln_sums[sub_at - 1], weights(P.cross.wq, P.cross.bo)));
       leaf(dsub, Nt, d, r.ws<half_t>(W.o2), d, P.cross.wo);
       NMT_TRY(r.dgrad(dsub, Nt, d, P.cross.wo, d, dO));
     }

@@ -99,10 +99,14 @@ template <int NCH, RowForm FORM>
 __global__ void __launch_bounds__(kThreads) res_ln_fwd_kernel(const half_t* __restrict__ sub, const half_t* __restrict__ resid,
                                                               const half_t* __restrict__ gamma, const half_t* __restrict__ beta,
                                                               half_t* __restrict__ out, float* __restrict__ stats, int rows,
-                                                              int d_in, float eps, DropDev drop) {
+                                                              int d_in, float eps, DropDev drop, Ahead next) {
   constexpr bool FULL = FORM == kFullRows;
   const int d = FULL ? 512 * NCH : d_in;
-  touch_arguments<64 + sizeof(DropDev)>();
+  touch_arguments<64 + sizeof(DropDev) + sizeof(Ahead)>();
+  if (blockIdx.x >= next.first) {
+    ask_ahead(next, (int)(blockIdx.x - next.first));
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   if (row >= rows) return;
@@ -158,11 +162,15 @@ __global__ void __launch_bounds__(64 * WAVES) res_ln_bwd_kernel(const half_t* __
                                                               const half_t* __restrict__ resid, const half_t* __restrict__ gamma,
                                                               const float* __restrict__ stats, half_t* __restrict__ dy_out,
                                                               half_t* __restrict__ dym_out, float* __restrict__ partial, int rows,
-                                                              int d_in, DropDev drop) {
+                                                              int d_in, DropDev drop, Ahead next) {
   constexpr bool KEYED = FORM != kAnyRows, FULL = FORM == kFullRows;
   const int d = FULL ? 512 * NCH : d_in;
   extern __shared__ __align__(16) float red[];  // [WAVES][NCH][2][64 lanes][4]
-  touch_arguments<72 + sizeof(DropDev)>();
+  touch_arguments<72 + sizeof(DropDev) + sizeof(Ahead)>();
+  if (blockIdx.x >= next.first) {
+    ask_ahead(next, (int)(blockIdx.x - next.first));
+    return;
+  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int chunks = d >> 3;
   float sg[NCH][8], sb[NCH][8], sbias[NCH][8];
@@ -173,7 +181,7 @@ __global__ void __launch_bounds__(64 * WAVES) res_ln_bwd_kernel(const half_t* __
 #pragma unroll
     for (int e = 0; e < 8; ++e) sg[i][e] = sb[i][e] = sbias[i][e] = 0.f;
   }
-  for (int row0 = (blockIdx.x * WAVES + wave) * ROWS; row0 < rows; row0 += gridDim.x * WAVES * ROWS) {
+  for (int row0 = (blockIdx.x * WAVES + wave) * ROWS; row0 < rows; row0 += next.first * WAVES * ROWS) {
     half8_t hs[ROWS][NCH], hr[ROWS][NCH], hg[ROWS][NCH];
     uint32_t bits[ROWS][NCH];
     DropRow key[ROWS] = {};
@@ -1016,13 +1024,15 @@ int launch_embed_fwd(const int32_t* ids, const half_t* E, half_t* x, int rows, i
   }
 int launch_residual_layernorm_fwd(const half_t* sub, const half_t* resid, const half_t* gamma, const half_t* beta,
                                   half_t* out, float* stats, int rows, int d, float eps, const DropDev& drop,
-                                  hipStream_t stream) {
+                                  hipStream_t stream, const Ahead& next) {
   NMT_REQUIRE(rows > 0 && d >= 8 && d % 8 == 0 && d <= 2048, "layernorm: d=%d must be a multiple of 8 in [8, 2048]", d);
   NMT_REQUIRE(sub && resid && gamma && beta && out && stats, "layernorm: null pointer");
   NMT_REQUIRE(aligned16(sub) && aligned16(resid) && aligned16(gamma) && aligned16(beta) && aligned16(out), "layernorm: misaligned pointer");
   NMT_REQUIRE(!drop.thr || drop.n_pos > 0, "layernorm: positions per sentence must be positive");
-  const dim3 grid(ceil_div(rows, kWavesPerBlock)), block(kThreads);
-  auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, sub, resid, gamma, beta, out, stats, rows, d, eps, drop); };
+  Ahead a = next;
+  a.first = (uint32_t)ceil_div(rows, kWavesPerBlock);
+  const dim3 grid(a.first + ahead_groups(a)), block(kThreads);
+  auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, sub, resid, gamma, beta, out, stats, rows, d, eps, drop, a); };
   switch (ln_nch(d)) {
     case 1: NMT_ROW_FORM(run, res_ln_fwd_kernel, 1); break;
     case 2: NMT_ROW_FORM(run, res_ln_fwd_kernel, 2); break;
@@ -1060,7 +1070,7 @@ int64_t layernorm_bwd_partial_floats(int most_rows, int d) {
 int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const half_t* resid, const half_t* gamma,
                                   const float* stats, half_t* dy, half_t* dym, half_t* dgamma, half_t* dbeta,
                                   half_t* dbias, float* partial, int rows, int d, const DropDev& drop,
-                                  hipStream_t stream, ColumnSums& sums) {
+                                  hipStream_t stream, ColumnSums& sums, const Ahead& next) {
   NMT_REQUIRE(rows > 0 && d >= 8 && d % 8 == 0 && d <= 2048, "layernorm_bwd: d=%d must be a multiple of 8 in [8, 2048]", d);
   NMT_REQUIRE(dout && sub && resid && gamma && stats && dy && partial, "layernorm_bwd: null pointer");
   NMT_REQUIRE(aligned16(dout) && aligned16(sub) && aligned16(resid) && aligned16(gamma) && aligned16(dy) && aligned16(dym),
@@ -1069,9 +1079,11 @@ int launch_residual_layernorm_bwd(const half_t* dout, const half_t* sub, const h
   const int nch = ln_nch(d);
   const LnBwdForm form = ln_bwd_form(rows, d);
   const int nblk = ln_bwd_blocks(rows, d);
-  const dim3 grid(nblk), block(kWave * form.waves);
+  Ahead a = next;
+  a.first = (uint32_t)nblk;
+  const dim3 grid(a.first + ahead_groups(a)), block(kWave * form.waves);
   const size_t smem = (size_t)form.waves * nch * 512 * sizeof(float);
-  auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, smem, stream, dout, sub, resid, gamma, stats, dy, dym, partial, rows, d, drop); };
+  auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, smem, stream, dout, sub, resid, gamma, stats, dy, dym, partial, rows, d, drop, a); };
 #define NMT_LN_BWD(N, R, W) NMT_ROW_FORM(run, res_ln_bwd_kernel, N, R, W)
   switch (nch * 4 + (form.waves == 8 ? 2 : form.rows_per_wave - 1)) {
     case 4: NMT_LN_BWD(1, 1, 4); break;

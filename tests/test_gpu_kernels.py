@@ -415,6 +415,52 @@ def test_gemm_epilogues_match_oracle():
     assert_close16(host(dC), (x @ W.T) * (hact > 0) * 1.25, "relu backward mask")
 
 
+# A kernel for each kind of epilogue in each tile shape, in rows and columns that end inside a tile (and, 8 wide, inside one store).  A bias together with an
+# addend of zeros takes the general epilogue: the same sum, so the same bits.  Behind the result's rows and beside its columns nothing is written.
+@pytest.mark.parametrize("tile", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("M,N,K", [(8, 8, 8), (129, 72, 72), (257, 264, 200)])
+def test_gemm_epilogue_forms_match_oracle_in_every_tile(tile, M, N, K):
+    rng = np.random.default_rng(M + K)
+    x, W, b = f16(rng.normal(size=(M, K))), f16(rng.normal(size=(N, K)) / math.sqrt(K)), f16(rng.normal(size=N))
+    other = f16(rng.normal(size=(M, N)))
+    dx, dW, db = dev16(x), dev16(W), dev16(b)
+    zeros = torch.zeros(M, N + 8, dtype=torch.float16, device=DEV)   # (the addend and the mask's source lie as the result does)
+    d_other = zeros.clone()
+    d_other[:, :N] = dev16(other)
+    b_t, ldb, y = 0, K, x @ W.T
+
+    def run(**kw):
+        c = torch.full((M + 1, N + 8), 77., dtype=torch.float16, device=DEV)
+        A.nmt_op_gemm(dx, 0, K, dW, b_t, ldb, c, N + 8, M, N, K, **kw)
+        assert (c[M] == 77).all() and (c[:, N:] == 77).all()
+        return c[:M, :N].contiguous()
+
+    try:
+        A.nmt_tuning("gemm_tile", tile)
+        assert_close16(host(run()), y, "plain")
+        biased = run(bias=db)
+        assert_close16(host(biased), y + b, "bias")
+        assert torch.equal(biased, run(bias=db, add=zeros))
+        assert_close16(host(run(bias=db, relu=True)), np.maximum(y + b, 0), "bias, ReLU")
+        dW, b_t, ldb = dev16(W.T), 1, N   # (the sum and the mask belong to the products of the backward pass)
+        assert_close16(host(run()), y, "plain")
+        assert_close16(host(run(add=d_other)), y + other, "sum")
+        assert_close16(host(run(relu_src=d_other, mask_scale=1.25)), y * 1.25 * (other > 0), "mask")
+    finally:
+        A.nmt_tuning("defaults")
+
+
+@pytest.mark.parametrize("M", [4096, 4097])   # a result of 16 MB, which is written through, and one that is more
+def test_gemm_results_on_both_sides_of_the_store_policy_match_oracle(M):
+    N, K = 2048, 40
+    rng = np.random.default_rng(M)
+    x, W, b = f16(rng.normal(size=(M, K))), f16(rng.normal(size=(N, K)) / 6), f16(rng.normal(size=N))
+    for kw, want in ((dict(), x @ W.T), (dict(bias=dev16(b), relu=True), np.maximum(x @ W.T + b, 0))):
+        c = torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV)
+        A.nmt_op_gemm(dev16(x), 0, K, dev16(W), 0, K, c, N, M, N, K, **kw)
+        assert_close16(host(c), want, f"{M} rows")
+
+
 def test_gemm_strided_operands_and_rejections():
     rng = np.random.default_rng(6)
     M, N, K = 96, 64, 32
