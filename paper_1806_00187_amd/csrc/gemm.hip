@@ -1354,9 +1354,12 @@ int launch_tile(const GemmArgs& a, bool a_t, bool b_t, int splits, hipStream_t s
 // The tile shapes below 256 x 256 and what a product takes with each, in us, fitted to timings of 160 shapes (130 to 26000 rows,
 // 64 to 4096 columns, k 64 to 4096; x W^T and dy W, operands rotating through 300 MB): `fixed` (launch, first operands,
 // epilogue) + k-tiles of 64 x the time of one, which depends on how many tiles share a compute unit (at most `per_cu`, by
-// LDS), + `again` for every further round of work-groups.  The model is within 3 to 5 % of
+// LDS), + `again` for every further round of work-groups.  The model was within 3 to 5 % of
 // the measured times on average; the shape it picks, with the large tile among them, costs 0.6 % more than the fastest on average and 15 % at worst
 // (constants fitted to the kernels before these: 1.3 % and 26 %, 6000 x 1024 x 3072 in large tiles, 55 us, for 44 in 128 x 128).
+// Since then an epilogue of its own for each form and arguments fetched together have taken 1.3 to 1.7 us off every shape alike: with operands in the
+// last-level cache the model is 10 to 23 % high, but over 286 products of 130 to 13000 rows its pick costs 0.8 % more than the fastest on average, 10 % at worst;
+// constants fitted to those timings pick no better (0.7 %, 13 %).
 enum SmallTile { kTile64, kTile128x64, kTile64x128, kTile128, kTile128x64Many, kTile128Many, kSmallTiles };
 struct TileCost {
   int bm, bn, per_cu;
