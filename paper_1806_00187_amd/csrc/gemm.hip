@@ -56,6 +56,7 @@ struct TileOrder {
 };
 TileOrder tile_order(int tiles_m, int tiles_n, int splits, int group_m, int xcds) {
   const uint32_t tiles = (uint32_t)tiles_m * tiles_n, total = tiles * splits;
+  group_m = group_m < tiles_m ? group_m : tiles_m;  // (the same order; callers may ask for groups of any size, whose tiles have to be counted in 32 bits)
   return TileOrder{divisor(xcds), total / xcds, total % xcds, tiles_m, group_m, divisor(tiles), divisor(group_m * tiles_n), divisor(group_m),
                    divisor(tiles_m % group_m ? tiles_m % group_m : group_m)};
 }

@@ -359,7 +359,7 @@ def test_gemm_tile_order_changes_no_bit():
         ref = run()                                   # the built-in group size
         assert all(torch.isfinite(c).all() for c in ref)
         assert torch.equal(ref[0].view(torch.int16), ref[1].view(torch.int16))
-        for group in (1, 3, 16, 200):                 # 200: more rows per group than there are tile rows
+        for group in (1, 3, 16, 200, 1 << 30, 2 ** 31 - 1):   # from 200 on: more rows per group than there are tile rows
             A.nmt_tuning("gemm_group", group)
             for a, b in zip(ref, run()):
                 assert torch.equal(a.view(torch.int16), b.view(torch.int16)), group

@@ -2,6 +2,8 @@
 logic (parameter layout, workspace sizing, scaler, schedule, argument validation) is right."""
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -147,6 +149,27 @@ def test_tuning_switches_accept_their_names_and_reject_others():
         with pytest.raises(A.NmtError) as e:
             A.nmt_tuning(name, value)
         assert e.value.code == A.binding.NMT_EINVAL
+
+
+# Groups whose tiles do not fit 32 bits: 2^30 rows of four tiles each, 2^31 - 1 of three.  (No device is visible to the process, so the launches at the end are
+# refused; what comes before them runs.)
+@pytest.mark.parametrize("group,N", [(1 << 30, 1024), (2 ** 31 - 1, 768), (1 << 30, 256)])
+def test_tile_groups_of_any_size_are_placed(group, N):
+    code = f"""
+import ctypes as C, paper_1806_00187_amd as A
+lib, p = A.load(), C.c_void_p(1 << 20)
+A.nmt_tuning("gemm_group", {group})
+for tile in range(6):
+    A.nmt_tuning("gemm_tile", tile)
+    assert lib.nmt_op_gemm(p, 0, 64, p, 0, 64, p, {N}, 520, {N}, 64, None, 0, None, None, None, 1.0, None) == A.NMT_EHIP
+w = A.binding.nmt_wgrad(p, p, p, None, {N}, {N}, {N}, {N}, {N}, 512)
+for tile in range(1, 5):
+    assert lib.nmt_op_wgrad_group(1, C.byref(w), 1.0, None, 0, tile, 1, None) == A.NMT_EHIP
+print("placed")
+"""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", ROCR_VISIBLE_DEVICES="-1", PYTHONPATH=ROOT)
+    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, env=env, cwd=ROOT)
+    assert res.returncode == 0 and "placed" in res.stdout, (res.returncode, res.stderr[-500:])
 
 
 def test_loss_totals_need_a_forward_call():
