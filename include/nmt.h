@@ -205,7 +205,7 @@ double nmt_lr_schedule(int64_t t, double peak, int64_t warmup);
 int nmt_debug_activation(const nmt_ctx* ctx, const char* name, const void** d_ptr, int64_t* rows, int64_t* cols);
 
 /* Host only.  Process-wide switches of launch forms, for tests and profiling; none of them changes a
- * result bit but "row_chain", which changes the rounding of gradients.  name: "gemm_group" (tile rows swept together, >= 1; default 4), "gemm_persist" (0: never the
+ * result bit but "row_chain", which changes the order in which the gradients of gains, shifts and output biases are summed over the rows.  name: "gemm_group" (tile rows swept together, >= 1; default 4), "gemm_persist" (0: never the
  * persistent GEMM form / 1: for 256 x 256 tiles with one of its epilogues; default 1),
  * "attn_persist" (0: one attention work item per work-group; default 1), "worklists" (0: attention
  * kernels enumerate every (sentence, tile); default 1), "one_stream" (1: forward and backward passes enqueue everything

@@ -305,6 +305,18 @@ int launch_residual_layernorm_fwd(const half_t* sub, const half_t* resid, const 
                                   hipStream_t stream, const Ahead& next = {});
 int64_t layernorm_bwd_scratch_floats(int d);                        // partial sums of a call of any number of rows ...
 int64_t layernorm_bwd_partial_floats(int most_rows, int d);         // ... of up to `most_rows`
+// LayerNorm backward of one element, for every kernel that has one: the gradient of a row is the same bits whichever computes it.  So the operations are
+// spelled out; left to the compiler it takes two products of a sum into one v_dot2c_f32_f16 here and not there, which rounds once for both.
+// go, gamma: fp16 values (their product is exact); xhat: the normalised element; m1, m2: means of go gamma and go gamma xhat over the row.
+__device__ __forceinline__ void ln_bwd_row_sums(float& s1, float& s2, float go, float gamma, float xhat) {
+#pragma clang fp contract(off)
+  s1 = __builtin_fmaf(go, gamma, s1);
+  s2 = __builtin_fmaf(go * gamma, xhat, s2);
+}
+__device__ __forceinline__ float ln_bwd_dy(float go, float gamma, float xhat, float rstd, float m1, float m2) {
+#pragma clang fp contract(off)
+  return rstd * __builtin_fmaf(-xhat, m2, __builtin_fmaf(go, gamma, -m1));
+}
 // Partial rows of column sums as a kernel left them: `rows` rows of up to three quantities, and where their totals go.
 struct ColumnSums {
   const float* partial;

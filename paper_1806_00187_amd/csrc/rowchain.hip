@@ -12,8 +12,8 @@
 // rounds of work-groups) 991 / 1005.
 //
 // Every product adds up in the order of the general kernels (32 k at a time, increasing), every tensor is rounded where they round it,
-// and a row's LayerNorm is computed lane by lane as they do, so activations are the same bits as theirs.  (Backward the compiler contracts a few products and
-// sums of a LayerNorm otherwise, and the sums over rows for the gradients of gains, shifts and output biases are taken in another order.)
+// and a row's LayerNorm is computed lane by lane as they do, so activations and their gradients are the same bits as theirs.  (The sums over rows for the
+// gradients of gains, shifts and output biases are taken in another order.)
 #include <mutex>
 #include <type_traits>
 #include <unordered_map>
@@ -432,9 +432,7 @@ __device__ __forceinline__ void ln_backward(const LnBwdRow& r, const RowChainLnB
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const float xh = xhat(e), go = (float)hg[e];
-    const float g = go * (float)r.gamma[e];
-    s1 += g;
-    s2 += g * xh;
+    ln_bwd_row_sums(s1, s2, go, (float)r.gamma[e], xh);
     sums3[0][e] = L.live ? go * xh : 0.f;
     sums3[1][e] = L.live ? go : 0.f;
   }
@@ -442,7 +440,7 @@ __device__ __forceinline__ void ln_backward(const LnBwdRow& r, const RowChainLnB
   floatx8 df, mf;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    df[e] = r.stats.y * ((float)hg[e] * (float)r.gamma[e] - m1 - xhat(e) * m2);
+    df[e] = ln_bwd_dy((float)hg[e], (float)r.gamma[e], xhat(e), r.stats.y, m1, m2);
     mf[e] = ((bits >> e) & 1u) ? df[e] * ln.drop.scale : 0.f;
     sums3[2][e] = L.live ? mf[e] : 0.f;
   }

@@ -229,9 +229,7 @@ __global__ void __launch_bounds__(64 * WAVES) res_ln_bwd_kernel(const half_t* __
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             const float xh = xhat(u, i, e), go = (float)hg[u][i][e];
-            const float g = go * (float)gam[i][e];
-            s1[u] += g;
-            s2[u] += g * xh;
+            ln_bwd_row_sums(s1[u], s2[u], go, (float)gam[i][e], xh);
             if (live) {
               sg[i][e] += go * xh;
               sb[i][e] += go;
@@ -262,7 +260,7 @@ __global__ void __launch_bounds__(64 * WAVES) res_ln_bwd_kernel(const half_t* __
           float dy[8], dm[8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            dy[e] = rstd[u] * ((float)hg[u][i][e] * (float)gam[i][e] - m1 - xhat(u, i, e) * m2);
+            dy[e] = ln_bwd_dy((float)hg[u][i][e], (float)gam[i][e], xhat(u, i, e), rstd[u], m1, m2);
             dm[e] = ((bits[u][i] >> e) & 1u) ? dy[e] * drop.scale : 0.f;
             sbias[i][e] += dm[e];
           }

@@ -733,42 +733,56 @@ def test_a_pass_of_few_rows_gives_the_same_bits_first_and_later_on_either_stream
 
 
 # Row counts around the 16 of a work-group and the tile counts of a wavefront; every width; feed-forward layers of one to four times the width; one stream
-# and two; keys and values of more decoder layers than end the encoder's chain; the row counts on both sides of the rule (4096 at 256).
+# and two; keys and values of more decoder layers than end the encoder's chain; several work-groups to a compute unit; the row counts on both sides of the
+# rule (4096 rows at 256 columns, 16384 at fewer, where the partial sums fill their place) and feed-forward widths that chains do not take.
 @pytest.mark.parametrize("d,heads,ff,enc,dec,B,S,T,dropout", [
     (64, 4, 256, 2, 2, 1, 1, 1, 0.1), (64, 4, 64, 1, 1, 3, 5, 6, 0.0), (64, 2, 192, 2, 1, 4, 4, 4, 0.3), (64, 4, 256, 1, 2, 17, 31, 33, 0.1),
     (128, 4, 512, 2, 2, 5, 13, 17, 0.1), (128, 8, 256, 1, 5, 40, 33, 21, 0.2), (128, 2, 128, 1, 1, 2, 8, 16, 0.0),
     (256, 4, 1024, 2, 2, 9, 21, 30, 0.1), (256, 8, 256, 1, 2, 1, 16, 17, 0.0), (256, 4, 768, 1, 1, 45, 38, 40, 0.2), (256, 4, 1024, 1, 6, 3, 7, 9, 0.3),
-    (256, 2, 512, 1, 1, 128, 32, 32, 0.1), (256, 4, 1024, 1, 1, 129, 32, 31, 0.1)])
+    (256, 2, 512, 1, 1, 128, 32, 32, 0.1), (256, 4, 1024, 1, 1, 129, 32, 31, 0.1),
+    (64, 4, 256, 2, 2, 130, 32, 31, 0.1), (128, 2, 256, 1, 2, 129, 31, 32, 0.2), (64, 4, 256, 1, 1, 256, 64, 64, 0.1), (64, 4, 256, 1, 1, 257, 64, 60, 0.1),
+    (128, 4, 512, 1, 1, 256, 61, 64, 0.1), (128, 4, 512, 1, 1, 257, 61, 64, 0.1), (64, 4, 320, 1, 1, 5, 6, 7, 0.1), (128, 4, 200, 1, 1, 5, 6, 7, 0.1)])
 @pytest.mark.parametrize("packed", [False, True])
 def test_a_launch_between_two_attentions_gives_the_activations_of_a_launch_for_each_operation(d, heads, ff, enc, dec, B, S, T, dropout, packed):
-    """Activations and loss are the same bits.  Gradients pass through LayerNorms whose products and sums are contracted otherwise, so fp16 roundings of
-    the gradient between two operations fall differently now and then: relative 2^-12 (rms) for each of a tensor's roundings that does, all of one tensor's at worst."""
+    """Activations, loss and every gradient are the same bits but for the gradients of gains, shifts and output biases, whose fp32 sums over the rows are taken in
+    another order: an fp16 result then falls on the other side of a rounding now and then (by one unit in the last place, 2^-10 of the value at most).  The
+    number of products that are launches of their own tells which way a pass went."""
     model = dict(enc_layers=enc, dec_layers=dec, d_model=d, n_heads=heads, d_ff=ff, vocab=264, dropout=dropout)
-    sess = Session(model, I.init_weights(seed=9, perturb=0.05, **model), max_sentences=256, max_len=64)
+    sess = Session(model, I.init_weights(seed=9, perturb=0.05, **model), max_sentences=260, max_len=64)
     batch = I.tiny_batch(seed=60 + B, B=B, S=S, T=T, vocab=264, short_rows=min(B - 1, 2), short_by=min(S, T) // 3)
     db = sess.pack([batch])[0] if packed else sess.to_device(batch)
+    chained = (d, ff, B) not in ((256, 1024, 129), (64, 256, 257), (128, 512, 257), (64, 320, 5), (128, 200, 5))
     names = [f"{side}{l}.{what}" for side, n in (("enc", enc), ("dec", dec)) for l in range(n) for what in ("out", "ffn.h")]
     seen = []
     try:
+        A.nmt_tuning("gemm_timing", 1)
         for chains in (0, 1):
             A.nmt_tuning("row_chain", chains)
+            A.nmt_gemm_timing()
             sess.g16.fill_(float("nan"))
             sess.forward_loss(db, 32.0, 3, 0)
+            forward = A.nmt_gemm_timing()[1]
             acts = [sess.activation(n).clone() for n in names] + [sess.loss_sum.clone()]
             sess.backward()
-            seen.append((acts, sess.named(sess.g16.float())))
+            backward = A.nmt_gemm_timing()[1]
+            if chains and chained:    # (the lowest layers' ends, what needs the encoder's output; the vocabulary's products; a group of weight gradients to a layer)
+                assert forward == 3 + max(0, dec - 4) and backward in (4 + 2 * dec + enc, 5 + 2 * dec + enc), (forward, backward)
+            else:
+                assert forward == 1 + 4 * enc + 7 * dec and backward == 2 + 5 * enc + 8 * dec, (forward, backward)
+            seen.append((acts, sess.named(sess.g16)))
     finally:
         A.nmt_tuning("defaults")
         sess.close()
     (a0, g0), (a1, g1) = seen
     assert all(torch.equal(x.view(torch.uint8), y.view(torch.uint8)) for x, y in zip(a0, a1))
-    layers = enc + dec
     for name, want in g0.items():
-        assert np.isfinite(g1[name]).all(), name
-        scale = np.linalg.norm(want)
-        if name.endswith(("bqkv", "bkv")):      # (a bias gradient of keys is zero but for rounding: the other sums' scale)
-            scale = max(scale, np.linalg.norm(g0[name.rsplit(".", 1)[0] + ".bo"]))
-        assert np.linalg.norm(g1[name] - want) <= 2.0 ** -12 * (2 + 4 * layers) ** 0.5 * 3 * max(scale, 1e-6), name
+        got = g1[name]
+        assert np.isfinite(got).all() and np.abs(want).max() > 0, name
+        if name.endswith((".g", ".b", ".bo", ".b2")):
+            want, got = want.astype(np.float64), got.astype(np.float64)
+            assert np.linalg.norm(got - want) <= 2.0 ** -10 * np.linalg.norm(want), name
+        else:
+            assert (got == want).all(), (name, int((got != want).sum()))
 
 
 @pytest.mark.parametrize("first", ["captured", "eager"])
