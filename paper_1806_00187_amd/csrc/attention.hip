@@ -138,13 +138,6 @@ __device__ __forceinline__ Item work_item(const AttnArgs& a, int bx, int by, int
   return it;
 }
 
-// Orders the wavefront's LDS accesses: what other lanes wrote before is visible after (LDS
-// instructions of one wavefront execute in order; this keeps the compiler from reordering them).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 // 32 rows of a [*, DH] head slice as MFMA operand registers: lane l gets row row0 + l%32, columns
 // 16*s + 8*(l/32) .. +7 for every k-step s; rows >= row_end are zero.
 template <int DH>

@@ -197,6 +197,14 @@ __device__ __forceinline__ uint32_t div_mod(uint32_t n, const Divisor& by, uint3
   return q;
 }
 
+// Orders one wavefront's LDS accesses: what its other lanes wrote before is visible after (LDS
+// instructions of a wavefront execute in order; this keeps the compiler from reordering them).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---- small vector helpers ---------------------------------------------------------------------
 __device__ __forceinline__ half8_t ld_half8(const half_t* p) { return *reinterpret_cast<const half8_t*>(p); }
 __device__ __forceinline__ void st_half8(half_t* p, half8_t v) { *reinterpret_cast<half8_t*>(p) = v; }

@@ -224,14 +224,6 @@ struct Tile {
   static constexpr int STAGE = OpA::BYTES + OpB::BYTES;   // (BM + BN) * BK * 2 bytes
 };
 
-// Orders one wavefront's LDS accesses: what its other lanes wrote before is visible after (LDS
-// instructions of a wavefront execute in order; this keeps the compiler from reordering them).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // s_waitcnt immediates (gfx9 encoding): at most n vector-memory operations outstanding, with or
 // without also waiting for every LDS operation
 constexpr int wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }

@@ -139,9 +139,11 @@ __device__ __forceinline__ void product(FwdUnit<D> (&u)[2], const FwdProduct& p,
   ahead.next(pieces);
   ahead.next(pieces);
   auto step = [&](const F& f, auto refill) {
+    wave_sync();  // the unit before has been read
 #pragma unroll
     for (int s = 0; s < KS; ++s) *reinterpret_cast<half8_t*>(own.at(s * (64 / F::CH) + lane / F::CH, lane % F::CH * 8)) = f.w[s];
     refill();
+    wave_sync();  // this one is in LDS
     if (DEEP) operands(at.piece);
 #pragma unroll
     for (int s = 0; s < KS; ++s)
