@@ -24,9 +24,7 @@
 #include "common.h"
 
 #include <atomic>
-#include <mutex>
 #include <type_traits>
-#include <unordered_map>
 
 namespace {
 
@@ -864,21 +862,6 @@ constexpr size_t tile_smem() { return (size_t)4 * 32 * (DH + 8) * sizeof(half_t)
 template <int DH>
 constexpr size_t dkv_smem() { return (size_t)4 * (2 * 32 * (DH + 8) * sizeof(half_t) + 2 * 32 * sizeof(float)); }
 
-template <typename Kern>
-int allow_big_lds(Kern kern, size_t bytes) {
-  if (bytes <= 64 * 1024) return NMT_OK;
-  // asked of the runtime once per kernel and size, not once per launch (callers may launch from several threads)
-  static std::mutex mu;
-  static std::unordered_map<const void*, size_t> allowed;
-  const void* key = reinterpret_cast<const void*>(kern);
-  std::lock_guard<std::mutex> lock(mu);
-  auto it = allowed.find(key);
-  if (it != allowed.end() && it->second >= bytes) return NMT_OK;
-  NMT_HIP_CHECK(hipFuncSetAttribute(key, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-  allowed[key] = bytes;
-  return NMT_OK;
-}
-
 // Upper bounds of the list lengths, from what the host knows (the lists themselves are made on the device).
 // Query tiles: sum_b ceil(Tq_b / 32) <= (sum_b Tq_b) / 32 + B, and sum_b Tq_b <= Nq + B (a table made from
 // lengths that exceed the host's totals cuts sentences down to one row, which they may share).
@@ -933,7 +916,7 @@ template <int DH, int NT>
 int fused_launch(const AttnArgs& a, int n_k_rows, hipStream_t stream) {
   constexpr int kWaves = NT == 1 ? 4 : 2;   // wavefronts (heads) per work-group: bounded by LDS
   const size_t smem = (size_t)kWaves * fused_wave_lds<DH, NT>();
-  if (int rc = allow_big_lds(attn_bwd_fused_kernel<DH, NT>, smem)) return rc;
+  if (int rc = allow_lds(reinterpret_cast<const void*>(attn_bwd_fused_kernel<DH, NT>), smem)) return rc;
   const int64_t n = a.wl_sent ? class_bound(a.B, a.Nq, n_k_rows, NT - 1) : a.B;
   if (n == 0) return NMT_OK;
   AttnArgs b = a;
@@ -959,7 +942,7 @@ int tiles_launch(const AttnArgs& a0, int lo, int hi, int n_k_rows, hipStream_t s
   a.cls_lo = lo;
   a.cls_hi = hi;
   const size_t smem = (size_t)W * block_wave_lds<DH>();
-  if (int rc = allow_big_lds(attn_bwd_tiles_kernel<DH, W>, smem)) return rc;
+  if (int rc = allow_lds(reinterpret_cast<const void*>(attn_bwd_tiles_kernel<DH, W>), smem)) return rc;
   int64_t most = 0;  // work items at most
   for (int nt = lo; nt <= hi; ++nt) most += ((a.wl_sent ? class_bound(a.B, a.Nq, n_k_rows, nt - 1) : a.B) * a.H + W / nt - 1) / (W / nt);
   NMT_REQUIRE(most < (1ll << 31), "attention_bwd: too many work items");
@@ -998,7 +981,7 @@ int bwd_launch(const AttnArgs& a0, int n_k_rows, hipStream_t stream) {
   }
   if (tmax <= a.fused_max) return NMT_OK;
   // longer ones: a wavefront per 32 queries for dQ, a wavefront per 32 keys for dK and dV
-  if (int rc = allow_big_lds(attn_bwd_dkv_kernel<DH>, dkv_smem<DH>())) return rc;
+  if (int rc = allow_lds(reinterpret_cast<const void*>(attn_bwd_dkv_kernel<DH>), dkv_smem<DH>())) return rc;
   const int groups = a.B * ((a.H + 3) / 4);
   a.by_hg = divisor((uint32_t)ceil_div(a.H, 4));
   hipLaunchKernelGGL(attn_bwd_dq_kernel<DH>, dim3(groups, ceil_div(a.Tq, 32)), dim3(kThreads), tile_smem<DH>(), stream, a);

@@ -45,6 +45,8 @@ struct DeviceInfo {
   int cus = 256, xcds = 8;
 };
 const DeviceInfo& device_info();
+// More than 64 KB of dynamic LDS has to be asked for: once per device, kernel and size (from any thread), not once per launch.
+int allow_lds(const void* kernel, size_t bytes);
 // Process-wide switches of launch forms (nmt_tuning): which work-group computes what, never what is computed.
 struct Tuning {
   int gemm_group = 4;     // tile rows swept column by column before the next rows

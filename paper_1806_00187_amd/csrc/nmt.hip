@@ -5,7 +5,11 @@
 #include <stdlib.h>
 
 #include <algorithm>
+#include <exception>
+#include <map>
+#include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "common.h"
@@ -32,6 +36,24 @@ const DeviceInfo& device_info() {
     return d;
   }();
   return info;
+}
+int allow_lds(const void* kernel, size_t bytes) {
+  if (bytes <= 64 * 1024) return NMT_OK;
+  static std::mutex mu;
+  static std::map<std::pair<int, const void*>, size_t> allowed;
+  int device = 0;
+  NMT_HIP_CHECK(hipGetDevice(&device));
+  try {
+    std::lock_guard<std::mutex> lock(mu);
+    size_t& most = allowed[{device, kernel}];
+    if (most >= bytes) return NMT_OK;
+    NMT_HIP_CHECK(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+    most = bytes;
+  } catch (const std::exception& e) {
+    nmt_set_error("asking for LDS: %s", e.what());
+    return NMT_EHIP;
+  }
+  return NMT_OK;
 }
 Tuning& tuning() {
   static Tuning t;

@@ -14,9 +14,7 @@
 // Every product adds up in the order of the general kernels (32 k at a time, increasing), every tensor is rounded where they round it,
 // and a row's LayerNorm is computed lane by lane as they do, so activations and their gradients are the same bits as theirs.  (The sums over rows for the
 // gradients of gains, shifts and output biases are taken in another order.)
-#include <mutex>
 #include <type_traits>
-#include <unordered_map>
 
 #include "common.h"
 
@@ -543,17 +541,6 @@ __global__ void __launch_bounds__(kThreads) row_chain_bwd_kernel(const RowChainB
   store_tile(wide, a.dO, D, row0, rows);
 }
 
-// More than 48 KB of LDS has to be asked for, once per kernel and device.
-int allow_lds(const void* kern, size_t bytes) {
-  static std::mutex mu;
-  static std::unordered_map<const void*, size_t> allowed;
-  std::lock_guard<std::mutex> lock(mu);
-  auto it = allowed.find(kern);
-  if (it != allowed.end() && it->second >= bytes) return NMT_OK;
-  NMT_HIP_CHECK(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-  allowed[kern] = bytes;
-  return NMT_OK;
-}
 constexpr int64_t kLdsBytes = 160 * 1024;
 int64_t fwd_lds(int d, int F, int wide, int n_proj) {
   const int unit = d == 256 ? 256 : d / 2;
