@@ -47,17 +47,26 @@ typedef short short8_t __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) short4_t* lds_short4_ptr;
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
-// The order work-groups take the tiles of a product in (see place).
+// The order work-groups take the tiles of a launch in (see xcd_order), and those of one product (see place_tile).
+struct XcdOrder {
+  Divisor xcds;        // dies with their own L2: consecutive work-group ids go round-robin over them
+  uint32_t base, rem;  // work-groups to a die: base, or one more on the first rem
+};
+XcdOrder xcd_runs(uint32_t total) {
+  const uint32_t xcds = (uint32_t)device_info().xcds;
+  return XcdOrder{divisor(xcds), total / xcds, total % xcds};
+}
 struct TileOrder {
-  Divisor xcds;         // dies with their own L2: consecutive work-group ids go round-robin over them
-  uint32_t base, rem;   // work-groups to a die: base, or one more on the first rem
   int tiles_m, group_m;
   Divisor tiles, per_group, rows, last_rows;  // tiles of the product; of group_m tile rows; group_m; rows of the last, shorter group
 };
-TileOrder tile_order(int tiles_m, int tiles_n, int splits, int group_m, int xcds) {
-  const uint32_t tiles = (uint32_t)tiles_m * tiles_n, total = tiles * splits;
+TileOrder tile_order(int tiles_m, int tiles_n) {
+  // tile rows per sweep: the 32 tiles an XCD works on at a time form a patch of 4 rows x 8 columns (or
+  // the result's whole width); between 2 and 8 the whole update is flat within 0.5 %, 4 measured best and
+  // fetches least past L2, 12 and more cost 2 %
+  int group_m = tuning().gemm_group;
   group_m = group_m < tiles_m ? group_m : tiles_m;  // (the same order; callers may ask for groups of any size, whose tiles have to be counted in 32 bits)
-  return TileOrder{divisor(xcds), total / xcds, total % xcds, tiles_m, group_m, divisor(tiles), divisor(group_m * tiles_n), divisor(group_m),
+  return TileOrder{tiles_m, group_m, divisor((uint32_t)tiles_m * tiles_n), divisor(group_m * tiles_n), divisor(group_m),
                    divisor(tiles_m % group_m ? tiles_m % group_m : group_m)};
 }
 struct GemmArgs {
@@ -74,6 +83,7 @@ struct GemmArgs {
   // k, else `partial_colsum`, fp32 [z][M]
   half_t* colsum = nullptr;
   float* partial_colsum = nullptr;
+  XcdOrder runs = {};
   TileOrder order = {};
   int keep = 0;  // the result is written through (else non-temporally)
 };
@@ -234,10 +244,10 @@ constexpr int wait_vm_lds(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0070; 
 // tiles of one split read the same k-range of A and B and share those panels in L2.
 // Then grouped order: group_m tile rows are swept column by column, so the work-groups an XCD runs at a
 // time form a patch of tiles and each A / B panel they stream is shared by several of them in L2.
-__device__ __forceinline__ uint32_t xcd_order(uint32_t lin, const Divisor& xcds, uint32_t base, uint32_t rem) {
+__device__ __forceinline__ uint32_t xcd_order(uint32_t lin, const XcdOrder& o) {
   uint32_t xcd;
-  const uint32_t idx = div_mod(lin, xcds, xcd);
-  return xcd * base + min(xcd, rem) + idx;
+  const uint32_t idx = div_mod(lin, o.xcds, xcd);
+  return xcd * o.base + min(xcd, o.rem) + idx;
 }
 __device__ __forceinline__ void place_tile(const TileOrder& o, uint32_t pid, int& tm, int& tn) {
   uint32_t in_group, row;
@@ -245,10 +255,10 @@ __device__ __forceinline__ void place_tile(const TileOrder& o, uint32_t pid, int
   tn = (int)div_mod(in_group, first + o.group_m <= o.tiles_m ? o.rows : o.last_rows, row);
   tm = first + (int)row;
 }
-__device__ __forceinline__ void place(const TileOrder& o, uint32_t lin, int& split, int& tm, int& tn) {
+__device__ __forceinline__ void place(const GemmArgs& g, uint32_t lin, int& split, int& tm, int& tn) {
   uint32_t pid;
-  split = (int)div_mod(xcd_order(lin, o.xcds, o.base, o.rem), o.tiles, pid);
-  place_tile(o, pid, tm, tn);
+  split = (int)div_mod(xcd_order(lin, g.runs), g.order.tiles, pid);
+  place_tile(g.order, pid, tm, tn);
 }
 
 // What an epilogue does: nothing; bias; bias and ReLU; a sum with another matrix; the ReLU mask of the backward pass; whatever it is told,
@@ -726,7 +736,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_kernel(const GemmArgs g) {
   __shared__ __align__(1024) unsigned char stage0[T::STAGE];
   __shared__ __align__(1024) unsigned char stage1[T::STAGE];
   int split, tm, tn;
-  place(g.order, blockIdx.x + blockIdx.y * g.order.tiles.d, split, tm, tn);
+  place(g, blockIdx.x + blockIdx.y * g.order.tiles.d, split, tm, tn);
   gemm_tile<BM, BN, AT, BT, NW, false, FORM>(g, split, tm, tn, stage0, stage1);
 }
 
@@ -936,7 +946,7 @@ __device__ __forceinline__ void gemm_small_group(const GemmArgs& g) {
   __shared__ __align__(1024) unsigned char stage2[T::STAGE];
   __shared__ __align__(1024) unsigned char stage3[T::STAGE];
   int split, tm, tn;
-  place(g.order, blockIdx.x + blockIdx.y * g.order.tiles.d, split, tm, tn);
+  place(g, blockIdx.x + blockIdx.y * g.order.tiles.d, split, tm, tn);
   gemm_small_tile<BM, BN, AT, BT, NW, false, FORM>(g, split, tm, tn, stage0, stage1, stage2, stage3);
 }
 template <int BM, int BN, bool AT, bool BT, int NW, StoreForm FORM>
@@ -1014,7 +1024,7 @@ __global__ void __launch_bounds__(512) gemm_persistent_kernel(const GemmArgs g) 
   t.k_end = g.K;
   auto set_tile = [&](int lin) {
     int split, tm, tn;
-    place(g.order, (uint32_t)lin, split, tm, tn);
+    place(g, (uint32_t)lin, split, tm, tn);
     t.set_tile(tm * BM, tn * BN, tid);
   };
   const GemmEpilogue& ep = g.ep;
@@ -1175,8 +1185,7 @@ __global__ void __launch_bounds__(kThreads) splitk_reduce_kernel(const float* __
 // ------------------------------------------------------------------------------------------------
 struct GroupArgs {
   int n, total;
-  Divisor xcds;
-  uint32_t base, rem;     // (as in TileOrder, of the whole group)
+  XcdOrder runs;          // of the whole group
   float out_scale;
   struct Product {
     WgradProduct w;
@@ -1188,7 +1197,7 @@ struct GroupArgs {
 };
 // Work item -> product, split and tile; consecutive items of one XCD's run share operand panels (as in place()).
 __device__ __forceinline__ GemmArgs group_item(const GroupArgs& a, int lin, int& split, int& tm, int& tn, bool& sums) {
-  const int at = (int)xcd_order((uint32_t)lin, a.xcds, a.base, a.rem);
+  const int at = (int)xcd_order((uint32_t)lin, a.runs);
   int i = 0;
   while (i + 1 < a.n && at >= a.p[i + 1].begin) ++i;
   const GroupArgs::Product& p = a.p[i];
@@ -1303,10 +1312,6 @@ void launch_variant(const GemmArgs& g, int splits, hipStream_t stream) {
 template <int BM, int BN, int NS, int NW = 4>
 int launch_tile(const GemmArgs& a, bool a_t, bool b_t, int splits, hipStream_t stream) {
   GemmArgs g = a;
-  // tile rows per sweep: the 32 tiles an XCD works on at a time form a patch of 4 rows x 8 columns (or
-  // the result's whole width); between 2 and 8 the whole update is flat within 0.5 %, 4 measured best and
-  // fetches least past L2, 12 and more cost 2 %
-  const int group_m = tuning().gemm_group;
   if (splits > 1) {
     g.k_chunk = (int)round_up(ceil_div(g.K, splits), 64);  // (whatever the tile, so that its shape changes no bit)
     splits = ceil_div(g.K, g.k_chunk);  // no empty split
@@ -1315,7 +1320,8 @@ int launch_tile(const GemmArgs& a, bool a_t, bool b_t, int splits, hipStream_t s
     g.partial = nullptr;
     splits = 1;
   }
-  g.order = tile_order(ceil_div(g.M, BM), ceil_div(g.N, BN), splits, group_m, device_info().xcds);
+  g.order = tile_order(ceil_div(g.M, BM), ceil_div(g.N, BN));
+  g.runs = xcd_runs(g.order.tiles.d * splits);
   g.keep = (int64_t)g.M * g.N * 2 <= kKeptBytes;
   constexpr bool kForms = BM < 256;  // (256 x 256 tiles have theirs in the persistent form)
   const StoreForm form = kForms && !a_t ? store_form(g.ep, b_t, g.partial != nullptr) : kStoreAny;
@@ -1493,7 +1499,8 @@ int launch_gemm_impl(const half_t* A, bool a_t, int lda, const half_t* B, bool b
         !(ep.add && ep.relu_src)) {
       const int groups = (int)(t256 < cus ? t256 : cus);
       GemmArgs pg = g;
-      pg.order = tile_order(ceil_div(M, 256), ceil_div(N, 256), 1, tuning().gemm_group, device_info().xcds);
+      pg.order = tile_order(ceil_div(M, 256), ceil_div(N, 256));
+      pg.runs = xcd_runs(pg.order.tiles.d);
       pg.partial = nullptr;
       auto run = [&](auto bt) {
         constexpr bool BT = decltype(bt)::value;
@@ -1623,7 +1630,7 @@ int launch_wgrad_group_impl(const WgradProduct* products, int n, float out_scale
     p.w = w;
     p.begin = a.total;
     const int tiles_m = ceil_div(w.M, edge), tiles_n = ceil_div(w.N, edge);
-    p.order = tile_order(tiles_m, tiles_n, splits, tuning().gemm_group, device_info().xcds);
+    p.order = tile_order(tiles_m, tiles_n);
     p.k_chunk = (int)round_up(ceil_div(w.K, splits), 64);  // (a split past the end of a short contraction writes zeros)
     a.total += tiles_m * tiles_n * splits;
     if (splits > 1) {
@@ -1634,9 +1641,7 @@ int launch_wgrad_group_impl(const WgradProduct* products, int n, float out_scale
       ra.total += (int64_t)w.M * (w.N / 8) + (w.colsum ? w.M / 8 : 0);
     }
   }
-  a.xcds = divisor(device_info().xcds);
-  a.base = a.total / device_info().xcds;
-  a.rem = a.total % device_info().xcds;
+  a.runs = xcd_runs(a.total);
   const dim3 grid(a.total);
   switch (tile) {
     case kGroup256: hipLaunchKernelGGL((wgrad_group_kernel<256, 256, 2, 8>), grid, dim3(512), 0, stream, a); break;
