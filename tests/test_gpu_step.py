@@ -123,6 +123,14 @@ def _check_grads(sess, got_flat, want, d, what, also=None, note=None):
     return worst
 
 
+@pytest.fixture(params=[1, 0], ids=["chains", "general"])
+def row_chain(request):
+    """Narrow models in row chains, and in the launches for each operation that wider ones have."""
+    A.nmt_tuning("row_chain", request.param)
+    yield request.param
+    A.nmt_tuning("defaults")
+
+
 RAW, FP16 = "fp64 oracle with its own gate decisions", "oracle with fp16 storage"
 
 
@@ -251,6 +259,18 @@ def test_tiny_with_activation_dropout_and_other_seed():
 @pytest.mark.parametrize("d,heads,B,S,T", [(16, 1, 2, 3, 4), (48, 3, 5, 9, 7), (80, 5, 90, 38, 31), (144, 9, 45, 21, 40)])
 def test_layernorm_gradients_beside_small_weight_gradients_match_oracle(d, heads, B, S, T):
     model = dict(enc_layers=1, dec_layers=1, d_model=d, n_heads=heads, d_ff=2 * d, vocab=136, dropout=0.1)
+    weights = I.init_weights(seed=21, perturb=0.05, **model)
+    batch = I.tiny_batch(seed=300 + d, B=B, S=S, T=T, vocab=136, short_rows=min(B - 1, 3), short_by=1)
+    sess = _step_parity(model, [batch], weights, step=4, loss_scale=8.0, lr=1e-4, what=f"{d}-wide model, {B} sentences")
+    sess.close()
+
+
+# The LayerNorm kernels of a pass, whose rows have keys: rows of two and of four pieces that end inside one (528, 1008; 1040, 1536, 2032 columns) and whole
+# ones of four (2048), a row and two to a wavefront.  (Whole rows of one and two pieces are Transformer-base's and -big's, partial rows of one the test's above.)
+@pytest.mark.parametrize("d,heads,B,S,T", [(528, 33, 3, 9, 7), (1008, 63, 30, 36, 35), (1040, 65, 3, 9, 7), (1536, 12, 30, 36, 35), (2032, 127, 2, 5, 6), (2048, 16, 3, 9, 7),
+                                           (2048, 16, 30, 36, 35)])
+def test_layernorm_of_wide_models_matches_oracle(d, heads, B, S, T):
+    model = dict(enc_layers=1, dec_layers=1, d_model=d, n_heads=heads, d_ff=64, vocab=136, dropout=0.1)
     weights = I.init_weights(seed=21, perturb=0.05, **model)
     batch = I.tiny_batch(seed=300 + d, B=B, S=S, T=T, vocab=136, short_rows=min(B - 1, 3), short_by=1)
     sess = _step_parity(model, [batch], weights, step=4, loss_scale=8.0, lr=1e-4, what=f"{d}-wide model, {B} sentences")
@@ -470,7 +490,7 @@ def test_sub_batches_in_flight_give_bit_identical_updates():
             assert (a == b).all()
 
 
-def test_passes_that_use_the_second_stream_are_unchanged_by_others_in_flight():
+def test_passes_that_use_the_second_stream_are_unchanged_by_others_in_flight(row_chain):
     """The model of the test above is too small for the second stream; this one uses it.  Serial updates (second stream) against two
     and three pipes in flight (each on its own stream alone), then two contexts whose passes, both with a second stream, are in
     flight at once against the same passes one after the other."""
@@ -668,7 +688,7 @@ def _pass_bits(sess, db, one_stream, fill):
         sess.backward()
         torch.cuda.synchronize()
     finally:
-        A.nmt_tuning("defaults")
+        A.nmt_tuning("one_stream", 0)
     assert bool((guarded[need:] == fill).all())
     return sess.loss_sum.clone(), sess.ntok.clone(), sess.g16.clone(), out
 
@@ -678,7 +698,7 @@ def _pass_bits(sess, db, one_stream, fill):
 # the positions, whose partial sums lie in a place of their own (136 symbols) or in that of the logits.
 @pytest.mark.parametrize("enc_layers,dec_layers,d,vocab,dropout,B", [(2, 1, 256, 2056, 0.1, 45), (1, 2, 256, 264, 0.0, 45), (3, 3, 256, 2056, 0.0, 45),
                                                                      (2, 3, 256, 12296, 0.2, 45), (2, 2, 64, 136, 0.1, 180), (2, 2, 64, 1000, 0.0, 180)])
-def test_second_stream_and_what_the_workspace_held_change_no_bit(enc_layers, dec_layers, d, vocab, dropout, B):
+def test_second_stream_and_what_the_workspace_held_change_no_bit(enc_layers, dec_layers, d, vocab, dropout, B, row_chain):
     model = dict(enc_layers=enc_layers, dec_layers=dec_layers, d_model=d, n_heads=4, d_ff=4 * d, vocab=vocab, dropout=dropout)
     sess = Session(model, I.init_weights(seed=9, perturb=0.05, **model), max_sentences=256, max_len=64)
     try:
@@ -786,7 +806,7 @@ def test_a_launch_between_two_attentions_gives_the_activations_of_a_launch_for_e
 
 
 @pytest.mark.parametrize("first", ["captured", "eager"])
-def test_a_captured_pass_gives_the_bits_of_an_eager_one_at_every_replay(first):
+def test_a_captured_pass_gives_the_bits_of_an_eager_one_at_every_replay(first, row_chain):
     """Forward and backward recorded into one graph, as the first pass of a context (which makes its second stream meanwhile) and
     after an eager pass; eager passes on other ids between the replays."""
     model = dict(enc_layers=2, dec_layers=2, d_model=256, n_heads=4, d_ff=1024, vocab=2056, dropout=0.1)
