@@ -213,8 +213,9 @@ int nmt_debug_activation(const nmt_ctx* ctx, const char* name, const void** d_pt
  * caller keeps running side by side on streams of its own; large tiles are then chosen as if each product had
  * that fraction of the compute units), "gemm_tile" (0: tile shape chosen per product, the default; 1..5: every
  * product that is not cut along k, except a layer's weight gradients, takes 256x256 / 128x128 / 128x64 / 64x128 / 64x64
- * tiles), "row_chain" (0: the operations between two attentions of a narrow model are launches of their own; default 1; not to be
- * changed between a forward call and its backward call), "gemm_timing" (1: every GEMM product, and every launch of a layer's weight gradients, is bracketed by a pair of
+ * tiles), "row_chain" (0: the operations between two attentions of a narrow model are launches of their own; 1, the default: one launch
+ * each way for models 64, 128 or 256 wide with d_ff = 1 to 4 times d_model, act_dropout = 0 and at most four, 256 wide one, work-groups of 16 rows to a
+ * compute unit; not to be changed between a forward call and its backward call), "gemm_timing" (1: every GEMM product, and every launch of a layer's weight gradients, is bracketed by a pair of
  * HIP events on the stream it is launched on; default 0), "defaults" (value ignored: all of the above back to
  * default).  Unknown names and values out of range return NMT_EINVAL. */
 int nmt_tuning(const char* name, int32_t value);

@@ -289,8 +289,8 @@ int launch_attention_bwd(const half_t* Q, int ldq, const half_t* K, int ldk, con
 // optimizer's state push it out of the 256 MB last-level cache: a product of few rows then waits for memory at each k-tile (3100 x 2048 x 512 and the
 // 3100 x 512 x 2048 that reads its result: 21.9 us with the weights and that result in the cache, 27.6 with neither).  So the LayerNorm's launch has work-groups of its own,
 // behind the rows', that read one word of each 128-byte line and drop it: the compute units are not full then, and memory is nearly idle.  With the
-// products' results kept in the same cache (kWriteThrough in the products' file), Transformer-base on 2990 tokens, forward / backward 1196 / 1762 -> 1164 / 1724 us,
-// Transformer-big on 380 tokens 956 / 1401 -> 901 / 1310, on 2600 tokens 2230 / 3840 -> 2220 / 3774; 40000 tokens lose nothing (9180 / 16680 -> 9065 / 16615), so
+// products' results kept in the same cache (kWriteThrough in the products' file), Transformer-base on 2990 tokens, forward / backward 1196 / 1762 -> 1157 / 1716 us,
+// Transformer-big on 380 tokens 956 / 1401 -> 881 / 1302, on 2600 tokens 2230 / 3840 -> 2220 / 3774; 40000 tokens lose nothing (9180 / 16680 -> 9065 / 16615), so
 // every number of rows does it.  Activations asked for in the same way cost more than they gave (backward +1 to +3 %: they are read at memory's full rate already).
 struct Ahead {
   const half_t* p = nullptr;

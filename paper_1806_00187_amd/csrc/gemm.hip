@@ -85,7 +85,7 @@ struct GemmArgs {
   float* partial_colsum = nullptr;
   XcdOrder runs = {};
   TileOrder order = {};
-  int keep = 0;  // the result is written through (else non-temporally)
+  int keep = 0;  // the result is written through (else non-temporally): by the epilogues of TileStore; store_tile and the persistent form never do
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const half_t* p, uint32_t bytes) {
@@ -271,8 +271,10 @@ typedef uint32_t uint4v_t __attribute__((ext_vector_type(4)));
 constexpr int kStream = 2;         // non-temporal
 constexpr int kWriteThrough = 16;  // device scope
 // A result up to this size is written through to the last-level cache, where the next kernel finds it: a non-temporal one it reads from memory.  Larger ones
-// push out what the kernels after it read: written through without a limit, a batch of 26000 tokens in validation (results of 54 to 100 MB) took 4 % longer, 16
-// batches of Transformer-big 2.5 % longer forward; with the limit neither changes and Transformer-base on 2990 tokens gains 1.5 % (with the weights read ahead).
+// push out what the kernels after it read: written through without a limit in every form, a batch of 26000 tokens in validation (results of 54 to 100 MB) took 4 % longer,
+// 16 batches of Transformer-big 2.5 % longer forward.  Where the limit lies between is of no account, because larger results mostly come from 256 x 256 tiles, which never
+// write through: 16, 32 and 64 MB time the same (Transformer-base on 2990 and 13000 tokens, -big on 2600 and 18000, validation), 8 MB costs
+// Transformer-base on 2990 tokens 1161 / 1718 -> 1205 / 1771 us forward / backward.
 constexpr int64_t kKeptBytes = 16ll << 20;
 // 16 bytes at byte offset `off` (past the extent: zeros come back, nothing is stored)
 __device__ __forceinline__ half8_t buffer_half8(__amdgpu_buffer_rsrc_t r, uint32_t off) {

@@ -467,9 +467,11 @@ bool encoder_products_beside(const nmt_ctx* c) {
   return use_second_stream(c) && (int64_t)ceil_div(c->Ns, 256) * ceil_div(2 * c->cfg.d_model, 256) < device_info().cus;
 }
 
-// Whether the operations between two attentions are one launch each way (both passes of a forward / backward pair decide alike).  256 wide a work-group
-// has 1.5 MB of weights to read, which a second round of work-groups doubles and the general kernels share among more rows; narrower models gain
-// up to four rounds and more (figures: rowchain.hip).
+// Whether the operations between two attentions are one launch each way (both passes of a forward / backward pair decide alike): without dropout behind the ReLU, which
+// the chains do not have, and with feed-forward layers of one, two, three or four times the width.  256 wide a work-group has 1.5 MB of weights to read, which a
+// second round of work-groups doubles and the general kernels share among more rows (8192 rows 991 us in launches, 1005 in chains).  Narrower models still
+// gain at four rounds, 16384 rows (64 wide 703 / 565 us, 128 wide 859 / 814), and stop there because the LayerNorm gradients' partial sums lie where the row
+// kernels' do, which has room for 1024 work-groups' of them; nothing above was timed.
 bool use_row_chains(const nmt_ctx* c) {
   const int rows = c->Ns > c->Nt ? c->Ns : c->Nt, d = c->cfg.d_model, rounds = d == 256 ? 1 : 4;
   return tuning().row_chain && c->cfg.act_dropout == 0.f && row_chain_fits(d, c->cfg.d_ff) && row_chain_blocks(rows) <= rounds * device_info().cus &&

@@ -6,10 +6,13 @@
 //
 // What bounds it: 64 wide the chain of dependent steps (7 us a layer forward, 9 backward), 256 wide the weights' way into the compute unit: 1.5 MB
 // a layer, 64 bytes a clock from L2 at most, forward through LDS (20 of 25 us at 80 GB/s), backward straight into registers (16 of 23).  So it pays
-// where the weights of a layer are few, and is not offered above 256 columns.  Sixteen rows are the least a matrix instruction takes: more work-groups, each
+// where the weights of a layer are few, and is not offered above 256 columns; the widest feed-forward layer is four times the width.  Sixteen rows are the least a matrix instruction takes: more work-groups, each
 // with the same weights to read, cost nothing while compute units are idle.  Whole passes of 2 + 2 layers, forward and backward, a launch for each operation / chains, us:
-// 64 wide 32 rows 359 / 226, 1024 449 / 283, 16384 764 / 560; 128 wide 381 / 261, 440 / 296, 950 / 833; 256 wide 447 / 428, 489 / 434, 4096 rows 651 / 573, 8192 (two
-// rounds of work-groups) 991 / 1005.
+// 64 wide 32 rows 301 / 212, 2048 419 / 306, 16384 703 / 565; 128 wide 326 / 245, 436 / 303, 859 / 814; 256 wide 512 rows 423 / 402, 2048 497 / 444, 4096 594 / 568, 8192 (two
+// rounds of work-groups) 991 / 1005.  The GPU's time alone: a pass of up to 128 rows 256 wide with 1024 hidden units takes 5 to 9 % longer in chains than in today's
+// general kernels (6 + 6 layers, 128 rows 1115 / 1210); the host, which enqueues half as many launches, bounds such a pass otherwise (its update alone 1270 to 1470 / 1370).
+//
+// No product is cut along k among the wavefronts: backward 64 wide a product with 64 columns is two tiles, and six of the eight wavefronts wait for them.
 //
 // Every product adds up in the order of the general kernels (32 k at a time, increasing), every tensor is rounded where they round it,
 // and a row's LayerNorm is computed lane by lane as they do, so activations and their gradients are the same bits as theirs.  (The sums over rows for the
