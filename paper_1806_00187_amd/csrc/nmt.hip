@@ -473,7 +473,7 @@ bool encoder_products_beside(const nmt_ctx* c) {
 // gain at four rounds, 16384 rows (64 wide 703 / 565 us, 128 wide 859 / 814), and stop there because the LayerNorm gradients' partial sums lie where the row
 // kernels' do, which has room for 1024 work-groups' of them; nothing above was timed.
 // (Passes in flight beside this one do not move the line: eight sub-batches of 4092 rows 256 wide, 3 + 3 layers, one / two / four in flight, whole update in launches 6.89 /
-// 6.11 / 5.70 ms, in chains 6.85 / 5.91 / 5.11; of 128 to 4092 rows 64 and 128 wide 4.0 to 6.3 and 2.2 to 4.3.)
+// 6.11 / 5.70 ms, in chains 6.85 / 5.91 / 5.11; of 128 to 4092 rows 64 and 128 wide 3.8 to 6.3 and 2.2 to 4.3.)
 bool use_row_chains(const nmt_ctx* c) {
   const int rows = c->Ns > c->Nt ? c->Ns : c->Nt, d = c->cfg.d_model, rounds = d == 256 ? 1 : 4;
   return tuning().row_chain && c->cfg.act_dropout == 0.f && row_chain_fits(d, c->cfg.d_ff) && row_chain_blocks(rows) <= rounds * device_info().cus &&

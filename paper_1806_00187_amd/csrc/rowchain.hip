@@ -10,7 +10,9 @@
 // with the same weights to read, cost nothing while compute units are idle.  Whole passes of 2 + 2 layers, forward and backward, a launch for each operation / chains, us:
 // 64 wide 32 rows 301 / 212, 2048 419 / 306, 16384 703 / 565; 128 wide 326 / 245, 436 / 303, 859 / 814; 256 wide 512 rows 423 / 402, 2048 497 / 444, 4096 594 / 568, 8192 (two
 // rounds of work-groups) 991 / 1005.  The GPU's time alone: a pass of up to 128 rows 256 wide with 1024 hidden units takes 5 to 9 % longer in chains than in today's
-// general kernels (6 + 6 layers, 128 rows 1115 / 1210); the host, which enqueues half as many launches, bounds such a pass otherwise (its update alone 1270 to 1470 / 1370).
+// general kernels (6 + 6 layers, 128 rows 1115 / 1210); so does an update of several such passes one
+// after the other (eight of 128 rows, 3 + 3 layers, 4.88 / 5.15 ms; 5.68 before either).  A single one's is bound by the host, which enqueues half as many launches (1270 to 1470 / 1370), as are
+// passes in flight (four at a time 4.16 / 3.04 ms), so no line is drawn there.
 //
 // No product is cut along k among the wavefronts: backward 64 wide a product with 64 columns is two tiles, and six of the eight wavefronts wait for them.
 //
